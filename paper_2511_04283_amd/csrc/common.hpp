@@ -93,6 +93,73 @@ __device__ __forceinline__ bool cb_tile_hit(float mx, float my, float A, float B
     return qmin <= Q;
 }
 
+// ---- wavefront helpers ----------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63u; }
+
+// Inclusive scan across the 64 lanes of a wavefront with data-parallel-primitive moves instead of shuffles through
+// LDS: four shifts within the rows of 16 lanes (zeros move in at a row's start), then lane 15 of rows 0 and 2 is
+// added to every lane of the row after it, then lane 31 to every lane of rows 2 and 3.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v)
+{
+    v += dpp_or_zero<0x111, 0xF>(v);   // row_shr:1
+    v += dpp_or_zero<0x112, 0xF>(v);   // row_shr:2
+    v += dpp_or_zero<0x114, 0xF>(v);   // row_shr:4
+    v += dpp_or_zero<0x118, 0xF>(v);   // row_shr:8
+    v += dpp_or_zero<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+    v += dpp_or_zero<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+    return v;
+}
+// The same with max (on unsigned values, for which zero is the neutral element).
+__device__ __forceinline__ uint32_t wave_inclusive_max(uint32_t v)
+{
+    v = max(v, dpp_or_zero<0x111, 0xF>(v));
+    v = max(v, dpp_or_zero<0x112, 0xF>(v));
+    v = max(v, dpp_or_zero<0x114, 0xF>(v));
+    v = max(v, dpp_or_zero<0x118, 0xF>(v));
+    v = max(v, dpp_or_zero<0x142, 0xA>(v));
+    v = max(v, dpp_or_zero<0x143, 0xC>(v));
+    return v;
+}
+
+// Which of a wavefront's 64 runs holds element j0 + lane of their concatenation?  Lane l's run is [excl, excl + cnt).
+// Every non-empty run leaves 1 + its lane at the slot of its first element (if that falls into this window of 64; the
+// slots are distinct), and a running maximum over the slots spreads it over the rest of the run; the window's first slots
+// belong to `carry` (zero before the first window; the windows have to be walked in order).  One trip through LDS (a
+// wavefront's LDS operations complete in the order they were issued) instead of the six dependent shuffles of a binary
+// search over the prefix sums.  `mark`: 64 words of LDS of this wavefront's own.
+__device__ __forceinline__ uint32_t wave_run_owner(uint32_t* mark, uint32_t cnt, uint32_t excl, uint32_t j0, uint32_t& carry)
+{
+    const uint32_t lane = lane_id();
+    mark[lane] = 0u;
+    const uint32_t rel = excl - j0;
+    if (cnt != 0u && rel < 64u) mark[rel] = lane + 1u;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    uint32_t own = mark[lane];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    own = wave_inclusive_max(lane == 0u ? max(own, carry) : own);
+    carry = (uint32_t)__builtin_amdgcn_readlane((int)own, 63);
+    return (own - 1u) & 63u;   // (own >= 1 wherever an element is: element 0 is some run's first)
+}
+
+// k / w for the place of a candidate in a rectangle w wide: estimated with the fast reciprocal, off by at most one
+// (k < 2^32 and w < 2^16 make the quotient's error < 0.02): corrected by one step either way, never by a loop that bad
+// operands could keep a wavefront in.
+__device__ __forceinline__ uint32_t rect_row(uint32_t k, uint32_t w)
+{
+    uint32_t row = (uint32_t)((float)k * __builtin_amdgcn_rcpf((float)w));
+    row -= row * w > k ? 1u : 0u;
+    row += (row + 1) * w <= k ? 1u : 0u;
+    return row;
+}
+
 // ---- workgroup reductions in double precision (fixed tree: results do not depend on scheduling) ----------
 constexpr int RED_BLOCKS = 1024;  // partial sums per reduction (a multiple of RED_THREADS)
 constexpr int RED_THREADS = 256;

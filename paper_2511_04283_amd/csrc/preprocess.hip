@@ -189,7 +189,11 @@ __device__ __forceinline__ void view_dir(const float* __restrict__ means, int64_
     d[2] = dir[2] / len;
 }
 
-template <int DEG>
+// Bound by memory (12 bytes read and 55 written per Gaussian, 224 more read per visible one).  CB (Compact Box): the
+// ellipse-tile tests of a wavefront's 64 boxes are dealt out to its lanes 64 at a time.  One lane testing its own box
+// tile after tile kept the wavefront for as many trips as its largest box has tiles (300k Gaussians, SH degree 3,
+// 1332x876: 63 us against 17 us without the tests; 16 us this way).
+template <int DEG, bool CB>
 __global__ __launch_bounds__(256) void k_preprocess(int64_t n, const float* __restrict__ means,
                                                     const float* __restrict__ scales,
                                                     const float* __restrict__ quats,
@@ -200,20 +204,47 @@ __global__ __launch_bounds__(256) void k_preprocess(int64_t n, const float* __re
                                                     uint32_t* __restrict__ touched, uint8_t* __restrict__ clamped)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    if (!CB && i >= n) return;
     Splat s;
-    project(means, scales, quats, opac[i], i, cam, cfg, s);
+    s.visible = false;
+    if (i < n) project(means, scales, quats, opac[i], i, cam, cfg, s);
     uint32_t hits = 0;
-    if (s.visible) {
-        if (!cfg.compact_box) {
-            hits = (uint32_t)((s.x1 - s.x0) * (s.y1 - s.y0));
-        } else {
+    if (!CB) {
+        if (s.visible) hits = (uint32_t)((s.x1 - s.x0) * (s.y1 - s.y0));
+    } else {
+        __shared__ uint32_t s_mark[4][64];
+        uint32_t* const mark = s_mark[threadIdx.x >> 6];
+        const uint32_t lane = lane_id();
+        float mx = 0.f, my = 0.f, A = 1.f, B = 0.f, C = 1.f, Q = 0.f;
+        uint32_t w = 0, cnt = 0, xy = 0;
+        if (s.visible) {
             const float idet = 1.0f / s.det;
-            const float A = s.c * idet, B = -s.b * idet, C = s.a * idet;
-            for (int ty = s.y0; ty < s.y1; ty++)
-                for (int tx = s.x0; tx < s.x1; tx++) hits += cb_tile_hit(s.mx, s.my, A, B, C, s.Q, tx, ty) ? 1u : 0u;
-            s.visible = hits > 0;
+            A = s.c * idet; B = -s.b * idet; C = s.a * idet;
+            mx = s.mx; my = s.my; Q = s.Q;
+            w = (uint32_t)(s.x1 - s.x0);
+            cnt = w * (uint32_t)(s.y1 - s.y0);
+            xy = (uint32_t)s.x0 | (uint32_t)s.y0 << 16;
         }
+        const uint32_t inc = wave_inclusive_scan(cnt), excl = inc - cnt;
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        uint32_t carry = 0;
+        for (uint32_t j0 = 0; j0 < total; j0 += 64) {
+            const uint32_t o = wave_run_owner(mark, cnt, excl, j0, carry);
+            const uint32_t k = j0 + lane - (uint32_t)__shfl((int)excl, (int)o, 64);
+            const uint32_t ow = (uint32_t)__shfl((int)w, (int)o, 64), oxy = (uint32_t)__shfl((int)xy, (int)o, 64);
+            const float omx = __shfl(mx, (int)o, 64), omy = __shfl(my, (int)o, 64);
+            const float oA = __shfl(A, (int)o, 64), oB = __shfl(B, (int)o, 64), oC = __shfl(C, (int)o, 64);
+            const float oQ = __shfl(Q, (int)o, 64);
+            const uint32_t row = rect_row(k, ow);
+            const bool hit = j0 + lane < total && cb_tile_hit(omx, omy, oA, oB, oC, oQ, (int)((oxy & 0xffffu) + (k - row * ow)),
+                                                              (int)((oxy >> 16) + row));
+            const uint64_t hb = __ballot(hit);
+            // every lane counts the hits of its own run within this window
+            const uint32_t a0 = excl > j0 ? excl - j0 : 0u, a1 = inc > j0 ? min(inc - j0, 64u) : 0u;
+            if (a1 > a0) hits += (uint32_t)__popcll(hb & (a1 >= 64 ? ~0ull : (1ull << a1) - 1ull) & (~0ull << a0));
+        }
+        s.visible = hits > 0;
+        if (i >= n) return;
     }
     float2 m2 = make_float2(0.f, 0.f);
     float4 co = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -715,8 +746,10 @@ hipError_t launch_preprocess(hipStream_t st, int64_t n, int deg, const fs_gaussi
 {
     if (n == 0) return hipSuccess;
     const dim3 grid((unsigned)((n + 255) / 256)), block(256);
-#define FS_LAUNCH(D)                                                                                         \
-    hipLaunchKernelGGL(k_preprocess<D>, grid, block, 0, st, n, g.means, g.scales, g.quats, g.opacities, g.sh, \
+#define FS_LAUNCH(D) \
+    do { if (cfg.compact_box) FS_LAUNCH_C(D, true); else FS_LAUNCH_C(D, false); } while (0)
+#define FS_LAUNCH_C(D, CB)                                                                                   \
+    hipLaunchKernelGGL((k_preprocess<D, CB>), grid, block, 0, st, n, g.means, g.scales, g.quats, g.opacities, g.sh, \
                        cam, cfg, o.mean2d, o.depth, o.conic_opacity, o.rgb, o.rect, o.tiles_touched, o.clamped)
     switch (deg) {
         case 0: FS_LAUNCH(0); break;
@@ -725,6 +758,7 @@ hipError_t launch_preprocess(hipStream_t st, int64_t n, int deg, const fs_gaussi
         default: FS_LAUNCH(3); break;
     }
 #undef FS_LAUNCH
+#undef FS_LAUNCH_C
     return hipGetLastError();
 }
 
