@@ -563,18 +563,14 @@ __global__ __launch_bounds__(1024) void k_tile_scan(const uint32_t* __restrict__
         if (q < per && t0 + q < num_tiles) order[atomicAdd(&cnt[bucket(c[q])], 1u)] = (uint32_t)(t0 + q);
 }
 
-// Step (3): one workgroup sorts one tile's segment in LDS (bitonic network on the 64-bit words, padded to
-// a power of two with all-ones words) and writes the final keys tile << 32 | depth_bits and the Gaussian
-// indices.  The network is bound by LDS traffic (every step reads and writes every word), so the steps at
-// distances 4, 2, 1 of a stage -- which stay inside aligned groups of 8 words -- are done in registers: a thread
-// loads a group, runs the three steps (all of the stages 2, 4, 8 at the start) and stores it back; the steps at
-// larger distances are taken three at a time as well, on groups of 8 words the right distance apart, which makes
-// 13 passes over LDS of the 36 steps of a 256-word sort.  Long lists use groups of 16 words (four steps a pass).
-// Groups are 16 bytes further apart in LDS than their size so that the 16-byte accesses of neighbouring lanes fall
-// into different banks.  (Replacing the workgroup barrier by a wavefront-level one for the steps at
-// distance <= 64, a register/shuffle variant of those steps, and giving short lists to single wavefronts were
-// all measured slower.)
-// Handles the tiles whose length is in (len_lo, CAP]; the others are left to another launch.
+// Step (3): one workgroup sorts one tile's segment in LDS on the 64-bit words and writes the final keys
+// tile << 32 | depth_bits and the Gaussian indices.
+//
+// First the network that the few lists take which the buckets below do not suit: bitonic, on the words padded to a power
+// of two with all-ones words.  The steps at distances 4, 2, 1 of a stage -- which stay inside aligned groups of 8 words
+// -- are done in registers: a thread loads a group, runs the three steps (all of the stages 2, 4, 8 at the start) and
+// stores it back; the steps at larger distances are taken three at a time as well, on groups of 8 words the right
+// distance apart.
 __device__ __forceinline__ void cmpx(uint64_t& a, uint64_t& b, bool up)
 {
     const bool sw = (a > b) == up;
@@ -586,127 +582,214 @@ __device__ __forceinline__ void cmpx(uint64_t& a, uint64_t& b, bool up)
 // GG words at distance 2^a from each other through registers: the GG/2 .. 1 steps of stage k2 at distances
 // 2^a GG/2 .. 2^a.  The words of a group agree in every index bit outside [a, a + log2 GG), the stage's bit
 // among them, so one direction serves the group.  Ends with a workgroup barrier.
-template <int GG, int LG, int THREADS>
-__device__ __forceinline__ void tile_sort_strided(uint64_t* k, int N, int a, int k2)
+template <int GG, int THREADS>
+__device__ __forceinline__ void network_strided(uint64_t* k, int N, int a, int k2)
 {
-    constexpr int LGG = GG == 2 ? 1 : GG == 4 ? 2 : GG == 8 ? 3 : 4;
-    auto at = [](int e) { return e + ((e >> LG) << 1); };
+    constexpr int LGG = GG == 2 ? 1 : GG == 4 ? 2 : 3;
     for (int g = threadIdx.x; g < N / GG; g += THREADS) {
         const int e0 = ((g >> a) << (a + LGG)) | (g & ((1 << a) - 1));
         const bool up = (e0 & k2) == 0;
         uint64_t v[GG];
 #pragma unroll
-        for (int q = 0; q < GG; q++) v[q] = k[at(e0 + (q << a))];
+        for (int q = 0; q < GG; q++) v[q] = k[e0 + (q << a)];
 #pragma unroll
         for (int jj = GG / 2; jj > 0; jj >>= 1)
 #pragma unroll
             for (int q = 0; q < GG; q++)
                 if ((q & jj) == 0) cmpx(v[q], v[q | jj], up);
 #pragma unroll
-        for (int q = 0; q < GG; q++) k[at(e0 + (q << a))] = v[q];
+        for (int q = 0; q < GG; q++) k[e0 + (q << a)] = v[q];
     }
     __syncthreads();
 }
 
-// The sort proper, with G (8 or 16) words per register group; k holds N + 2 N / G words.  A stage's steps are
-// taken log2 G at a time, from the largest distance down: first the odd ones out (a smaller group), then groups
-// of G words ever closer together, last the contiguous groups with 16-byte LDS accesses.
-template <int G, int THREADS, int CAP>
-__device__ __forceinline__ void tile_sort_lds(uint64_t* k, int N, int n, uint32_t tile, uint32_t first,
-                                              const uint64_t* __restrict__ bucket, uint64_t* __restrict__ keys_out,
-                                              uint32_t* __restrict__ vals_out)
+// k[0, n) <- the segment's words in order; k holds N words, N >= 16 a power of two, N >= n.
+template <int THREADS>
+__device__ __forceinline__ void network_sort(uint64_t* k, int N, int n, const uint64_t* __restrict__ words)
 {
-    constexpr int LG = G == 8 ? 3 : 4;
-    static_assert(G == 8 || G == 16, "group of 8 or 16 words");
-    auto at = [](int e) { return e + ((e >> LG) << 1); };   // word e of the sequence -> its place in k
-    {
-        // (all of a thread's loads are issued before the first LDS write: written as one loop, each load would be
-        // waited for in turn)
-        constexpr int PER = (CAP + THREADS - 1) / THREADS;
-        uint64_t w[PER];
+    for (int i = threadIdx.x; i < N; i += THREADS) k[i] = i < n ? words[i] : ~0ull;
+    __syncthreads();
+    for (int g = threadIdx.x; g < N / 8; g += THREADS) {   // the complete stages 2, 4, 8
+        uint64_t v[8];
 #pragma unroll
-        for (int u = 0; u < PER; u++) {
-            const int i = threadIdx.x + u * THREADS;
-            w[u] = i < n ? bucket[first + i] : ~0ull;
-        }
+        for (int q = 0; q < 8; q++) v[q] = k[8 * g + q];
 #pragma unroll
-        for (int u = 0; u < PER; u++) {
-            const int i = threadIdx.x + u * THREADS;
-            if (i < N) k[at(i)] = w[u];
-        }
+        for (int k2 = 2; k2 <= 8; k2 <<= 1)
+#pragma unroll
+            for (int j = k2 >> 1; j > 0; j >>= 1)
+#pragma unroll
+                for (int e = 0; e < 8; e++)
+                    if ((e & j) == 0) cmpx(v[e], v[e | j], k2 == 8 ? (g & 1) == 0 : (e & k2) == 0);
+#pragma unroll
+        for (int q = 0; q < 8; q++) k[8 * g + q] = v[q];
     }
     __syncthreads();
-    // one contiguous group through registers: FIRST = the complete stages 2 .. G, otherwise the steps at
-    // distances G/2 .. 1 of a later stage, whose direction `up` is the same for the whole group
-    auto local = [&](int g, bool first_stages, bool up) {
-        uint4* q = reinterpret_cast<uint4*>(&k[(G + 2) * g]);
-        uint64_t v[G];
-#pragma unroll
-        for (int h = 0; h < G / 2; h++) {
-            const uint4 w = q[h];
-            v[2 * h] = ((uint64_t)w.y << 32) | w.x;
-            v[2 * h + 1] = ((uint64_t)w.w << 32) | w.z;
-        }
-        if (first_stages) {
-#pragma unroll
-            for (int k2 = 2; k2 < G; k2 <<= 1)
-#pragma unroll
-                for (int j = k2 >> 1; j > 0; j >>= 1)
-#pragma unroll
-                    for (int e = 0; e < G; e++)
-                        if ((e & j) == 0) cmpx(v[e], v[e | j], (e & k2) == 0);
-        }
-#pragma unroll
-        for (int j = G / 2; j > 0; j >>= 1)
-#pragma unroll
-            for (int e = 0; e < G; e++)
-                if ((e & j) == 0) cmpx(v[e], v[e | j], up);
-#pragma unroll
-        for (int h = 0; h < G / 2; h++)
-            q[h] = make_uint4((uint32_t)v[2 * h], (uint32_t)(v[2 * h] >> 32), (uint32_t)v[2 * h + 1],
-                              (uint32_t)(v[2 * h + 1] >> 32));
-    };
-    for (int g = threadIdx.x; g < (N >> LG); g += THREADS) local(g, true, ((G * g) & G) == 0);
-    __syncthreads();
-    for (int k2 = 2 * G, m = LG + 1; k2 <= N; k2 <<= 1, m++) {   // m = log2 k2: the stage has steps 2^(m-1) .. 1
+    for (int k2 = 16, m = 4; k2 <= N; k2 <<= 1, m++) {   // m = log2 k2: the stage has steps 2^(m-1) .. 1
         int top = m;
-        const int odd = (m - LG) % LG;
-        if (odd == 1) tile_sort_strided<2, LG, THREADS>(k, N, top - 1, k2);
-        if (odd == 2) tile_sort_strided<4, LG, THREADS>(k, N, top - 2, k2);
-        if (odd == 3) tile_sort_strided<8, LG, THREADS>(k, N, top - 3, k2);
-        top -= odd;
-        for (; top > LG; top -= LG) tile_sort_strided<G, LG, THREADS>(k, N, top - LG, k2);
-        for (int g = threadIdx.x; g < (N >> LG); g += THREADS) local(g, false, ((G * g) & k2) == 0);
-        __syncthreads();
-    }
-    for (int i = threadIdx.x; i < n; i += THREADS) {
-        const uint64_t v = k[at(i)];
-        keys_out[first + i] = ((uint64_t)tile << 32) | (v >> 32);
-        vals_out[first + i] = (uint32_t)v;
+        if (m % 3 == 1) network_strided<2, THREADS>(k, N, top - 1, k2);
+        if (m % 3 == 2) network_strided<4, THREADS>(k, N, top - 2, k2);
+        top -= m % 3;
+        for (; top > 0; top -= 3) network_strided<8, THREADS>(k, N, top - 3, k2);
     }
 }
 
-template <int CAP, int THREADS>
-__global__ __launch_bounds__(THREADS) void k_tile_sort(const uint2* __restrict__ ranges,
+// A list is ordered by spreading it over about as many buckets as it has words, monotonically in the depth bits, and
+// ranking every word among the few words of its own bucket: a constant number of trips through LDS and a handful of
+// comparisons per word, where the network needs log2(N)^2 / 2 of them per word (91 at 8 192).  The bucket function is
+// linear between the list's smallest and largest depth for short lists; longer ones (depths that cluster, an outlier
+// that stretches the range) go through a histogram of COARSE equal parts first and then interpolate its running sum,
+// which gives every word a bucket share whatever the distribution between the parts.  A list with more than
+// BUCKET_LIMIT words in one bucket (hundreds of equal depths) is left to the network above.
+// What is left is the segments' loads and stores (20 bytes per pair) and, for the shortest lists, the chain of six
+// barriers.  Against the network for everything: 27 M pairs (lists of 3 350 on average) 830 -> 259 us in four launches,
+// 10 M pairs 177 -> 75 us, 300k Gaussians at 1332x876 55 -> 23 us, 100k at 980x545 16.4 -> 8.4 us.
+// Handles the tiles whose length is in (len_lo, CAP]; the others are left to another launch.
+constexpr int COARSE = 256;
+constexpr int BUCKET_LIMIT = 256;
+
+template <int CAP, int THREADS, int NB>
+__global__ __launch_bounds__(THREADS, CAP == TILE_SORT_MAX ? 8 : 4) void k_tile_sort(const uint2* __restrict__ ranges,
                                                    const uint32_t* __restrict__ tile_order,
                                                    const uint64_t* __restrict__ bucket, int len_lo, uint32_t limit,
                                                    uint64_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out)
 {
-    // (groups of 8 words are padded by a quarter, groups of 16, which every list beyond 512 words uses, by an eighth)
-    __shared__ __align__(16) uint64_t k[CAP + CAP / (CAP > 8192 ? 8 : 4)];
+    constexpr int PER = CAP / THREADS, WAVES = THREADS / 64, NBT = NB / THREADS;
+    static_assert(CAP % THREADS == 0 && NB % THREADS == 0 && THREADS >= COARSE, "whole words and buckets per thread");
+    __shared__ __align__(16) uint64_t k[CAP + NB / 2 + 1];           // the words in bucket order, and behind them
+    uint32_t* const start = reinterpret_cast<uint32_t*>(k + CAP);   // [NB + 1]: the buckets' counts, then first places
+    __shared__ float2 part[COARSE];                                  // words before a part, words in it
+    __shared__ uint32_t red[3][WAVES];
     const uint32_t tile = tile_order[blockIdx.x];
     const uint2 r = ranges[tile];
     const int n = (int)(r.y - r.x);
     // (uniform over the workgroup; `limit` = the words the buffers hold: a segment that reaches beyond it is left alone)
     if (n <= len_lo || n > CAP || r.y > limit) return;
-    int N = 16;
-    while (N < n) N <<= 1;
-    // groups of 16 words make fewer passes over LDS but leave N / 16 threads busy in the register phases:
-    // measured better from 1024 words on
-    if (N <= TILE_SORT_GROUP16_FROM / 2)
-        tile_sort_lds<8, THREADS, CAP>(k, N, n, tile, r.x, bucket, keys_out, vals_out);
-    else
-        tile_sort_lds<16, THREADS, CAP>(k, N, n, tile, r.x, bucket, keys_out, vals_out);
+    const int t = threadIdx.x, wave = t >> 6;
+    uint64_t w[PER];
+    uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+    for (int u = 0; u < PER; u++) {
+        const int i = t + u * THREADS;
+        w[u] = i < n ? bucket[r.x + i] : 0ull;
+    }
+#pragma unroll
+    for (int u = 0; u < PER; u++) {
+        if (t + u * THREADS < n) {
+            const uint32_t d = (uint32_t)(w[u] >> 32);
+            lo = min(lo, d);
+            hi = max(hi, d);
+        }
+    }
+    const bool two_level = n > 2 * COARSE;
+    uint32_t* const coarse = start;   // (the parts' counters sit where the buckets' will)
+    if (two_level) {
+        if (t < COARSE) coarse[t] = 0u;
+    } else {
+#pragma unroll
+        for (int q = 0; q < NBT; q++) start[t + q * THREADS] = 0u;
+    }
+    const uint32_t nlo = wave_inclusive_max(~lo);   // (zero is the neutral element of this maximum)
+    hi = wave_inclusive_max(hi);
+    if ((t & 63) == 63) { red[0][wave] = nlo; red[1][wave] = hi; }
+    __syncthreads();
+    uint32_t all_nlo = 0u, all_hi = 0u;
+#pragma unroll
+    for (int q = 0; q < WAVES; q++) { all_nlo = max(all_nlo, red[0][q]); all_hi = max(all_hi, red[1][q]); }
+    const uint32_t first = ~all_nlo;
+    const float range = (float)(all_hi - first);
+    // every step (conversion, product, sum of exactly representable counts, truncation) is monotone in the depth bits
+    const float scale = range > 0.f ? (two_level ? (float)COARSE : (float)NB) / range : 0.f;
+    const float per_word = (float)NB / (float)n;
+    if (two_level) {
+#pragma unroll
+        for (int u = 0; u < PER; u++) {
+            if (t + u * THREADS < n) {
+                const float x = (float)((uint32_t)(w[u] >> 32) - first) * scale;
+                atomicAdd(&coarse[min((uint32_t)x, (uint32_t)COARSE - 1u)], 1u);
+            }
+        }
+        __syncthreads();
+        uint32_t c = 0, inc = 0;
+        if (t < COARSE) {
+            c = coarse[t];
+            inc = wave_inclusive_scan(c);
+            if ((t & 63) == 63) red[2][wave] = inc;
+        }
+        __syncthreads();
+        if (t < COARSE) {
+            uint32_t before = inc - c;
+            for (int q = 0; q < wave; q++) before += red[2][q];
+            part[t] = make_float2((float)before, (float)c);
+        }
+#pragma unroll
+        for (int q = 0; q < NBT; q++) start[t + q * THREADS] = 0u;
+        __syncthreads();
+    }
+    auto bucket_of = [&](uint64_t word) {
+        float x = (float)((uint32_t)(word >> 32) - first) * scale;
+        if (two_level) {
+            const uint32_t c = min((uint32_t)x, (uint32_t)COARSE - 1u);
+            const float2 p = part[c];
+            x = (p.x + fminf(x - (float)c, 1.0f) * p.y) * per_word;
+        }
+        return min((uint32_t)x, (uint32_t)NB - 1u);
+    };
+    uint32_t at[PER];   // a word's bucket and its place of arrival in it (each below 65 536)
+#pragma unroll
+    for (int u = 0; u < PER; u++) {
+        if (t + u * THREADS < n) {
+            const uint32_t b = bucket_of(w[u]);
+            at[u] = b << 16 | atomicAdd(&start[b], 1u);
+        }
+    }
+    __syncthreads();
+    {
+        // thread t turns the counts of buckets [t NBT, t NBT + NBT) into first places
+        uint32_t c[NBT], sum = 0, most = 0;
+#pragma unroll
+        for (int q = 0; q < NBT; q++) { c[q] = start[t * NBT + q]; sum += c[q]; most = max(most, c[q]); }
+        const uint32_t inc = wave_inclusive_scan(sum);
+        most = wave_inclusive_max(most);
+        if ((t & 63) == 63) { red[0][wave] = inc; red[1][wave] = most; }
+        __syncthreads();
+        uint32_t run = inc - sum;
+        most = 0u;
+#pragma unroll
+        for (int q = 0; q < WAVES; q++) { run += q < wave ? red[0][q] : 0u; most = max(most, red[1][q]); }
+        if (most > (uint32_t)BUCKET_LIMIT) {   // (uniform over the workgroup)
+            int N = 16;
+            while (N < n) N <<= 1;
+            network_sort<THREADS>(k, N, n, bucket + r.x);
+            for (int i = t; i < n; i += THREADS) {
+                keys_out[r.x + i] = ((uint64_t)tile << 32) | (k[i] >> 32);
+                vals_out[r.x + i] = (uint32_t)k[i];
+            }
+            return;
+        }
+#pragma unroll
+        for (int q = 0; q < NBT; q++) { start[t * NBT + q] = run; run += c[q]; }
+        if (t == 0) start[NB] = (uint32_t)n;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; u++)
+        if (t + u * THREADS < n) k[start[at[u] >> 16] + (at[u] & 0xffffu)] = w[u];
+    __syncthreads();
+    // (words are taken in bucket order now, so that neighbouring lanes write neighbouring places)
+#pragma unroll
+    for (int u = 0; u < PER; u++) {
+        const int i = t + u * THREADS;
+        if (i < n) {
+            const uint64_t word = k[i];
+            const uint32_t b = bucket_of(word);
+            const uint32_t s = start[b], e = start[b + 1];
+            uint32_t rank = s;
+            if (e - s > 1u)
+                for (uint32_t q = s; q < e; q++) rank += k[q] < word ? 1u : 0u;
+            keys_out[r.x + rank] = ((uint64_t)tile << 32) | (word >> 32);
+            vals_out[r.x + rank] = (uint32_t)word;
+        }
+    }
 }
 
 // ---- radix sort -------------------------------------------------------------------------
@@ -966,16 +1049,16 @@ hipError_t launch_tile_sorts(hipStream_t st, int num_tiles, int variants, uint32
     if (num_tiles <= 0) return hipSuccess;
     // the long lists first: few workgroups, each a long chain of steps, which more threads shorten
     if (variants & TS_HUGE)
-        hipLaunchKernelGGL((k_tile_sort<TILE_SORT_HUGE, 1024>), dim3(num_tiles), dim3(1024), 0, st, ranges, tile_order,
+        hipLaunchKernelGGL((k_tile_sort<TILE_SORT_HUGE, 1024, 4096>), dim3(num_tiles), dim3(1024), 0, st, ranges, tile_order,
                            bucket, TILE_SORT_MAX, pair_limit, keys_out, vals_out);
     if (variants & (TS_MAX | TS_MIDMAX))
-        hipLaunchKernelGGL((k_tile_sort<TILE_SORT_MAX, 1024>), dim3(num_tiles), dim3(1024), 0, st, ranges, tile_order,
+        hipLaunchKernelGGL((k_tile_sort<TILE_SORT_MAX, 1024, 2048>), dim3(num_tiles), dim3(1024), 0, st, ranges, tile_order,
                            bucket, (variants & TS_MIDMAX) ? TILE_SORT_SMALL : TILE_SORT_MID, pair_limit, keys_out, vals_out);
     if (variants & TS_MID)
-        hipLaunchKernelGGL((k_tile_sort<TILE_SORT_MID, 512>), dim3(num_tiles), dim3(512), 0, st, ranges, tile_order,
+        hipLaunchKernelGGL((k_tile_sort<TILE_SORT_MID, 512, 1536>), dim3(num_tiles), dim3(512), 0, st, ranges, tile_order,
                            bucket, TILE_SORT_SMALL, pair_limit, keys_out, vals_out);
     if (variants & TS_SMALL)
-        hipLaunchKernelGGL((k_tile_sort<TILE_SORT_SMALL, 256>), dim3(num_tiles), dim3(256), 0, st, ranges, tile_order, bucket,
+        hipLaunchKernelGGL((k_tile_sort<TILE_SORT_SMALL, 256, 1024>), dim3(num_tiles), dim3(256), 0, st, ranges, tile_order, bucket,
                            0, pair_limit, keys_out, vals_out);
     return hipGetLastError();
 }

@@ -243,7 +243,6 @@ hipError_t launch_emit_pairs_cb(hipStream_t st, int64_t n, const fs_projected& p
 constexpr int TILE_COPIES = 256;        // workgroups of the counting / placement kernels, each with its own counters (a multiple of 64)
 constexpr int TILE_PAIR_THREADS = 1024;
 constexpr int TILE_LDS_MAX_TILES = 15360;  // their per-tile counters live in LDS (60 KB)
-constexpr int TILE_SORT_GROUP16_FROM = 1024;  // padded list length from which a thread merges 16 words in registers, not 8
 constexpr int TILE_SORT_SMALL = 2048;  // longest list one workgroup sorts with 20 KB of LDS (256 threads)
 constexpr int TILE_SORT_MID = 4096;    // ... with 40 KB (512 threads: four such workgroups fit a compute unit, two of the next)
 constexpr int TILE_SORT_MAX = 8192;    // ... with 80 KB (1024 threads)
