@@ -199,8 +199,6 @@ CfgDev make_cfg(const fs_config& c)
     d.T_min = c.T_min;
     d.bg[0] = c.bg[0]; d.bg[1] = c.bg[1]; d.bg[2] = c.bg[2];
     d.jclamp = c.jclamp;
-    // conservative: for opacity <= 1, sigma*exp(power) < alpha_min whenever power < ln(alpha_min) - 0.01
-    d.power_min = (float)(log((double)c.alpha_min) - 0.01);
     d.score_mode = c.score_mode;
     d.compact_box = c.compact_box != 0;
     d.cb_beta = c.cb_beta;

@@ -24,7 +24,6 @@ struct CfgDev {
     float z_near, lowpass, alpha_min, alpha_max, T_min;
     float bg[3];
     float jclamp;
-    float power_min;  // exponents below this cannot reach alpha_min for opacity <= 1 (conservative)
     int score_mode;
     int compact_box;  // pairs from the ellipse-tile test instead of the 3-sigma square
     float cb_beta;

@@ -25,10 +25,12 @@ namespace fs {
 
 namespace {
 
-constexpr int BATCH = 256;
+constexpr int SLOTS = 256;        // records a workgroup holds in LDS: one per thread
+constexpr int BATCH = SLOTS - 1;  // list entries staged at a time; the last record is the empty one that pads the sub-tile lists
+constexpr int GROUP = 4;          // entries of a sub-tile list that a lane evaluates side by side (one 32-bit word of slots)
 
-// exp(x) for pmin <= x <= 0: t = x*log2(e); n = rint(t); r = t - n; 2^r by a degree-5 polynomial
-// (Horner, fused), scaled by 2^n.  The caller guarantees x >= about -5.6, so no range clamp.
+// exp(x) for x <= 0: t = x*log2(e); n = rint(t); r = t - n; 2^r by a degree-5 polynomial (Horner, fused), scaled by 2^n.
+// No range clamp: the scaling underflows to zero by itself.
 __device__ __forceinline__ float exp_c(float x)
 {
     const float t = x * 0x1.715476p+0f;
@@ -82,24 +84,31 @@ __device__ __forceinline__ Pixel pixel_of_thread(const CamDev& cam, int tile)
     return pixel_of_thread(cam, tile, (int)threadIdx.x);
 }
 
-// LDS image of one batch of a tile's list, shared by the kernels.  A staged Gaussian is one record of RS 16-byte
-// words, so that the loops form one address per entry: (mu_x, mu_y, a, 2b), (c, sigma, r, g) and, with WITH_RGB,
-// (r, g, b, -sigma/2).
+// LDS image of one batch of a tile's list, shared by the kernels.  A staged Gaussian is one 16-byte word in each of two
+// or (WITH_RGB) three arrays, so that one slot number, shifted once, addresses all of them:
+//   r0 = (mu_x, mu_y, -a/2, -b)   r1 = (-c/2, sigma, r, g)   r2 = (r, g, b, 0)
+// The factors make the quadratic form come out as the exponent -1/2 (a dx^2 + 2 b dx dy + c dy^2) itself: halving and
+// negating commute with every rounding on the way, so the exponent is the same to the bit.
 template <bool WITH_RGB>
 struct Stage {
-    static constexpr int RS = WITH_RGB ? 3 : 2;
-    float4 rec[BATCH * RS];
-    uint64_t bits[16][4];      // per sub-tile, per staging wavefront: which of its 64 slots the sub-tile visits
-    uint8_t list[16][BATCH];   // per sub-tile (index wave*4 + row): batch slots to visit, in list order
-    int len[16];               // length of each sub-tile's list
-    __device__ __forceinline__ const float4* at(int j) const { return rec + j * RS; }
-    // unfilled slots must hold finite numbers: lanes past their list's end compute with a stale slot and
-    // contribute exact zeros
+    float4 r0[SLOTS], r1[SLOTS];
+    float4 r2[WITH_RGB ? SLOTS : 1];
+    uint32_t list[16][SLOTS / 4];  // per sub-tile (index wave*4 + row): batch slots to visit, in list order, one byte each
+    __align__(16) uint32_t sub[SLOTS / 2];  // per slot, 16 bits: the sub-tiles that visit it (see sub_place)
+    int len[16];                   // length of each sub-tile's list
+    // Slot BATCH is the empty record (sigma = 0: alpha = 0, nothing is ever blended); the others must hold finite numbers
+    // before they are filled for the first time.
     __device__ __forceinline__ void clear(int t)
     {
-#pragma unroll
-        for (int q = 0; q < RS; q++) rec[t * RS + q] = make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+        r0[t] = z;
+        r1[t] = z;
+        if (WITH_RGB) r2[t] = z;
     }
+    // where slot t's 16 bits sit in `sub` (in units of 16 bits): word 8 (t / 16) + t % 8, upper half for t % 16 >= 8, so
+    // that the eight words of 16 slots turn into one sub-tile's 16 bits with a shift, a mask and an insertion each
+    static __device__ __forceinline__ int sub_place(int t) { return ((t >> 4) * 8 + (t & 7)) * 2 + ((t >> 3) & 1); }
+    __device__ __forceinline__ int slot(int st, int k) const { return reinterpret_cast<const uint8_t*>(list[st])[k & (SLOTS - 1)]; }
 };
 
 // Sub-tile st = wave*4 + row of a tile sits at column kx = (wave&1)*2 + (row&1), line ky = (wave>>1)*2 + (row>>1).
@@ -121,24 +130,26 @@ __device__ __forceinline__ uint32_t dpp_shr_add(uint32_t v)
 
 // Loads entries [first, first+m) of the tile's list into `s` (slot t <- entry first+t) and builds
 // the 16 per-sub-tile slot lists.  Returns the length of the list of the calling lane's sub-tile.
-// Contains two workgroup barriers; every thread of the workgroup must call it.
+// Contains one workgroup barrier; every thread of the workgroup must call it, after a barrier behind the previous
+// batch's walk.  A wavefront's own four lists are complete when it returns (the others' only behind another barrier).
 //
 // Box of a Gaussian: it can only be blended where sigma*G >= alpha_min, i.e. where
-// q <= qg = 2 ln(sigma/alpha_min), and the kernels also reject q > -2*power_min.  With
+// q <= qg = 2 ln(sigma/alpha_min).  With
 // Sigma_2D = conic^-1, the set {q <= Q} lies within |dx| <= sqrt(Q Sigma_xx), |dy| <= sqrt(Q Sigma_yy).
-// Q is taken as min(qg, -2 power_min) + 0.1 + e, where e bounds the rounding error of the fp32 q
+// Q is taken as qg + 0.1 + e, where e bounds the rounding error of the fp32 q
 // for any pixel of a tile the Gaussian is paired with (|dx|,|dy| <= 3 sqrt(lambda_max) + 17), and the
 // half-widths get a further 0.2 % + 0.01 px (the box itself is computed with the fast reciprocal,
-// square root and logarithm): outside the box the pinned arithmetic yields alpha < 0.96 alpha_min
-// (or power < power_min), so dropping the pair cannot change any result.  The same argument gives
+// square root and logarithm): outside the box the pinned arithmetic yields alpha < 0.96 alpha_min,
+// so dropping the pair cannot change any result.  The same argument gives
 // bounds on dx + dy and dx - dy (an octagon around the support).
 //
-// Lists: each staging wavefront ballots, per sub-tile, which of its 64 slots are kept (phase 1);
-// then the 16 lanes that own a sub-tile in the render loops expand its 256-bit mask into slot
-// numbers, 16 slots per lane, with a prefix sum over the row (phase 2).
+// Lists: every thread leaves its entry's 16 sub-tile bits in LDS; then the 16 lanes that own a sub-tile in the render
+// loops gather that sub-tile's bit of 16 slots each and expand them into slot numbers with a prefix sum over the row.
+// The rest of a list is filled with the empty slot, so that the loops may run past a list's end.
+// REVERSED: the lists run from the last entry to the first.
 // ID_MODE: 0 = s_id unused, 1 = s_id[t] <- Gaussian index, 2 = s_id[t] <- index of the pair's
 // gradient record (where the pair was emitted before the sort: offset + place in the rectangle).
-template <bool WITH_RGB, int ID_MODE>
+template <bool WITH_RGB, int ID_MODE, bool REVERSED = false>
 __device__ __forceinline__ int stage_batch(Stage<WITH_RGB>& s, uint32_t* s_id, const CamDev& cam,
                                            const CfgDev& cfg, int tile, const uint32_t* __restrict__ gauss_sorted,
                                            const float4* __restrict__ splats, uint32_t first, int m)
@@ -152,10 +163,9 @@ __device__ __forceinline__ int stage_batch(Stage<WITH_RGB>& s, uint32_t* s_id, c
         const float4 r0 = rec[0], r1 = rec[1], r2 = rec[2];
         const float2 xy = make_float2(r0.x, r0.y);
         const float4 co = make_float4(r0.z, r0.w, r1.x, r1.y);
-        s.rec[t * s.RS] = make_float4(xy.x, xy.y, co.x, co.y + co.y);
-        s.rec[t * s.RS + 1] = make_float4(co.z, co.w, r1.z, r1.w);
-        // (the backward pass takes the colour and -sigma / 2 with one aligned 16-byte read)
-        if (WITH_RGB) s.rec[t * s.RS + 2] = make_float4(r1.z, r1.w, r2.x, -0.5f * co.w);
+        s.r0[t] = make_float4(xy.x, xy.y, -0.5f * co.x, -co.y);
+        s.r1[t] = make_float4(-0.5f * co.z, co.w, r1.z, r1.w);
+        if (WITH_RGB) s.r2[t] = make_float4(r1.z, r1.w, r2.x, 0.f);
         if (ID_MODE == 1) s_id[t] = g;
         if (ID_MODE == 2) {
             const uint32_t r01 = __float_as_uint(r2.z), r23 = __float_as_uint(r2.w);
@@ -170,7 +180,7 @@ __device__ __forceinline__ int stage_batch(Stage<WITH_RGB>& s, uint32_t* s_id, c
             const float sxx = co.z * inv, syy = co.x * inv;
             const float D = 3.0f * __builtin_amdgcn_sqrtf(sxx + syy) + 17.0f;
             const float e = 1e-6f * (fabsf(co.x) + 2.0f * fabsf(co.y) + fabsf(co.z)) * D * D;
-            const float Q = fminf(2.0f * __logf(ratio), -2.0f * cfg.power_min) + 0.1f + e;
+            const float Q = 2.0f * __logf(ratio) + 0.1f + e;
             const float hx = __builtin_amdgcn_sqrtf(Q * sxx) * 1.002f + 0.01f;
             const float hy = __builtin_amdgcn_sqrtf(Q * syy) * 1.002f + 0.01f;
             // sub-tile column k has its centre at +4k+2 from the tile origin; pixel centres reach 1.5 from it
@@ -204,34 +214,33 @@ __device__ __forceinline__ int stage_batch(Stage<WITH_RGB>& s, uint32_t* s_id, c
             sub_mask = colm & rowm & (nan8 ? 0xffffu : (summ & difm));
         }
     }
-    // phase 1: one 64-bit keep mask per (sub-tile, staging wavefront)
-    uint64_t keep = 0;
-#pragma unroll
-    for (int st = 0; st < 16; st++) {
-        const uint64_t bal = __ballot((sub_mask >> st) & 1u);
-        keep = lane == st ? bal : keep;
-    }
-    if (lane < 16) s.bits[lane][swave] = keep;
+    reinterpret_cast<uint16_t*>(s.sub)[s.sub_place(t)] = (uint16_t)sub_mask;
+    reinterpret_cast<uint4*>(s.list)[t] = make_uint4(0x01010101u * BATCH, 0x01010101u * BATCH, 0x01010101u * BATCH, 0x01010101u * BATCH);
     __syncthreads();
-    // phase 2: lane i of the row that owns sub-tile st expands slots [16 i, 16 i + 16)
+    // lane i of the row that owns sub-tile st expands slots [16 i, 16 i + 16)
     const int st = swave * 4 + (lane >> 4);
     const int i = lane & 15;
-    uint32_t b16 = (uint32_t)(s.bits[st][i >> 2] >> ((i & 3) * 16)) & 0xffffu;
+    const uint4 lo = *reinterpret_cast<const uint4*>(&s.sub[8 * i]), hi = *reinterpret_cast<const uint4*>(&s.sub[8 * i + 4]);
+    auto bits_of = [&](uint32_t word, int q) { return ((word >> st) & 0x00010001u) << q; };
+    const uint32_t both = bits_of(lo.x, 0) | bits_of(lo.y, 1) | bits_of(lo.z, 2) | bits_of(lo.w, 3) | bits_of(hi.x, 4) |
+                          bits_of(hi.y, 5) | bits_of(hi.z, 6) | bits_of(hi.w, 7);
+    uint32_t b16 = (both & 0xffu) | (both >> 16) << 8;
     const uint32_t cnt = __popc(b16);
     uint32_t inc = cnt;
     inc = dpp_shr_add<0x111>(inc);  // row_shr:1
     inc = dpp_shr_add<0x112>(inc);  // row_shr:2
     inc = dpp_shr_add<0x114>(inc);  // row_shr:4
     inc = dpp_shr_add<0x118>(inc);  // row_shr:8
-    uint32_t pos = inc - cnt;
+    const int mine = __shfl((int)inc, (lane & 48) | 15, 64);
+    uint8_t* dst = reinterpret_cast<uint8_t*>(s.list[st]) + (REVERSED ? mine - 1 - (int)(inc - cnt) : (int)(inc - cnt));
     while (b16) {
-        const uint32_t b = __builtin_ctz(b16);
-        s.list[st][pos++] = (uint8_t)(16 * i + b);
+        *dst = (uint8_t)(16 * i + __builtin_ctz(b16));
+        dst += REVERSED ? -1 : 1;
         b16 &= b16 - 1u;
     }
-    const int mine = __shfl((int)inc, (lane & 48) | 15, 64);
-    if (i == 15) s.len[st] = (int)inc;
-    __syncthreads();
+    if (i == 15) s.len[st] = mine;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     return mine;
 }
 
@@ -254,6 +263,24 @@ __device__ __forceinline__ void wave_step(double& a, double& b, double& c, uint3
     // (the minimum must not meet the zero a missing source reads as: its own value stands in)
     lo = min(lo, (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)lo, CTRL, ROW_MASK, 0xF, false));
     hi = max(hi, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, CTRL, ROW_MASK, 0xF, SHIFT));
+}
+
+__device__ __forceinline__ uint64_t ballot(bool v) { return __builtin_amdgcn_ballot_w64(v); }
+
+// Where `mask` has a lane's bit: C += w c, T = Tn, last = at.  Five vector instructions under the lane mask, where selects
+// would take two more, and no branch in the way of the instructions around them.  Called with all 64 lanes active.
+__device__ __forceinline__ void blend_under_mask(uint64_t mask, float& C0, float& C1, float& C2, float& T, int& last, float c0,
+                                                 float c1, float c2, float w, float Tn, int at)
+{
+    asm("s_mov_b64 exec, %[m]\n\t"
+        "v_fmac_f32_e32 %[C0], %[c0], %[w]\n\t"
+        "v_fmac_f32_e32 %[C1], %[c1], %[w]\n\t"
+        "v_fmac_f32_e32 %[C2], %[c2], %[w]\n\t"
+        "v_mov_b32_e32 %[T], %[Tn]\n\t"
+        "v_mov_b32_e32 %[l], %[at]\n\t"
+        "s_mov_b64 exec, -1"
+        : [C0] "+v"(C0), [C1] "+v"(C1), [C2] "+v"(C2), [T] "+v"(T), [l] "+v"(last)
+        : [m] "s"(mask), [c0] "v"(c0), [c1] "v"(c1), [c2] "v"(c2), [w] "v"(w), [Tn] "v"(Tn), [at] "s"(at));
 }
 
 // Longest of the four sub-tile lists of the calling wavefront (`mine` is uniform within a row).
@@ -286,7 +313,7 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
                                                     double* __restrict__ tile_partial, ScoreRecord record)
 {
     __shared__ Stage<true> s;
-    __shared__ __align__(16) uint16_t s_pb[BITS ? BATCH : 1][16];  // this batch's bits, [slot][sub-tile]
+    __shared__ __align__(16) uint16_t s_pb[BITS ? SLOTS : 1][16];  // this batch's bits, [slot][sub-tile]
     __shared__ uint32_t s_rows;                                    // rows of the record this tile has written so far
 
     const int tile = (int)tile_order[blockIdx.x];  // longest lists first
@@ -295,12 +322,10 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
     const uint2 range = ranges[tile];
     const int total = (int)(range.y - range.x);
 
-    bool done = !p.inside;
+    uint64_t done = ballot(!p.inside);   // the wavefront's pixels that have terminated
     float T = 1.0f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
     uint32_t last = 0;
 
-    // Slots a batch does not fill must still hold finite numbers: lanes past the end of their list
-    // read a stale slot and multiply its colour by a zero weight.
     s.clear(threadIdx.x);
 
     // BITS: row t of s_pb is zeroed and written out by thread t alone; the other wavefronts set bits in it between
@@ -337,7 +362,7 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
         }
     };
     for (int start = 0; start < total; start += BATCH) {
-        const int alive = __syncthreads_count(!done);
+        const int alive = __syncthreads_or(done != ~0ull);
         if (BITS && pending >= 0) {
             write_bits(pending, pending_m);
             pending = -1;
@@ -353,50 +378,53 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
         }
         const int mine = stage_batch<true, 0>(s, nullptr, cam, cfg, tile, gauss_sorted, splats, range.x + start, m);
         // a row whose 16 pixels have all finished does not lengthen the wavefront's loop
-        const bool row_alive = ((__ballot(!done) >> (threadIdx.x & 48)) & 0xffffull) != 0;
+        const bool row_alive = ((~done >> (threadIdx.x & 48)) & 0xffffull) != 0;
         const int longest = wave_max_of_rows(row_alive ? mine : 0);
-        // Straight-line body with selects: lanes past their list's end (or finished) read a stale
-        // slot and discard the result; one wave-uniform branch per iteration.  (Skipping the rest of an
-        // iteration when no lane passes the range test does not pay: four rows look at four different
-        // Gaussians, so all of them missing is rare, and the test costs more than it saves.)
-        int lastj = -1;   // batch slot of the last Gaussian this pixel blended in this batch
-        for (int k = 0; k < longest; k++) {
-            // (every fourth trip: a wavefront whose pixels have all terminated leaves the loop)
-            if ((k & 3) == 0 && __ballot(!done) == 0) break;
-            const int j = s.list[sub][k];
-            const float4* e = s.at(j);
-            const float4 r0 = e[0], r1 = e[1];           // (mu_x, mu_y, a, 2b), (c, sigma, r, g)
-            const float dx = p.px - r0.x, dy = p.py - r0.y;
-            const float u = __builtin_fmaf(r0.w, dy, r0.z * dx);
-            const float q = __builtin_fmaf(dx, u, (r1.x * dy) * dy);
-            const float power = -0.5f * q;
-            bool ok = (k < mine) & !done & !(power > 0.0f) & !(power < cfg.power_min);
-            const float colb = e[2].z;
-            const float G = exp_c(power);
-            const float alpha = fminf(cfg.alpha_max, r1.y * G);
-            ok = ok & (alpha >= cfg.alpha_min);
-            const float Tn = T * (1.0f - alpha);
-            const bool stop = ok & (Tn < cfg.T_min);
-            const bool blend = ok & !stop;
-            done = done | stop;
-            const float w = blend ? alpha * T : 0.0f;  // a zero weight leaves C unchanged bit for bit
-            C0 = __builtin_fmaf(r1.z, w, C0);
-            C1 = __builtin_fmaf(r1.w, w, C1);
-            C2 = __builtin_fmaf(colb, w, C2);
-            if (BITS) {
-                // (kept behind the colour update: scheduled ahead of it, the LDS store below would sit between the
-                // colour's LDS read and the wait for it, and every iteration would wait for the store as well)
-                asm volatile("" : "+v"(C0), "+v"(C1), "+v"(C2) : : "memory");
-                // w is alpha T with the transmittance in front of this Gaussian where it is blended (> 0 then), else 0:
-                // one comparison against alpha_min (FS_SCORE_WEIGHT) or 0 (FS_SCORE_ALPHA) decides
-                const uint64_t hb = __builtin_amdgcn_ballot_w64(w > hit_above);
-                // the row's first lane stores the row's 16 bits (past the end of the row's list j is stale)
-                if ((threadIdx.x & 15) == 0 && k < mine) s_pb[j][sub] = (uint16_t)(hb >> (threadIdx.x & 48));
+        // What bounds the loop is the number of vector instructions where the chip is full (they took 96 % of the issue
+        // slots at 500k Gaussians, 1600x1064), and the latency of one trip where the longest tiles are left alone.  Four
+        // entries' alphas are formed side by side from one word of slots -- four independent chains -- and only the
+        // transmittance runs through them one after the other; conditions are lane masks in the scalar unit and blending
+        // happens under the mask instead of through selects: 32 vector instructions per entry instead of 46 (with the
+        // record of counted pixels 35).  Lanes past their list's end evaluate the empty record.  The kernel, before and
+        // after: 4k Gaussians at 128x128 31 and 18 us, 100k at 980x545 96 and 68, 500k at 1600x1064 167 and 132.
+        // (Skipping an entry when no lane passes the range test does not pay: four rows look at four different
+        // Gaussians, so all of them missing is rare.)
+        int lastk = -1;   // place on the row's list of the last Gaussian this pixel blended in this batch
+        uint32_t next = s.list[sub][0];
+        for (int k = 0; k < longest && done != ~0ull; k += GROUP) {   // (leaves when all of the wavefront's pixels have terminated)
+            const uint32_t word = next;
+            next = s.list[sub][(k / GROUP + 1) & (SLOTS / GROUP - 1)];
+            float alpha[GROUP], cr[GROUP], cg[GROUP], cb[GROUP];
+            uint64_t ok[GROUP];
+#pragma unroll
+            for (int u = 0; u < GROUP; u++) {
+                const int j = (word >> (8 * u)) & 0xffu;
+                const float4 r0 = s.r0[j], r1 = s.r1[j];
+                cr[u] = r1.z;
+                cg[u] = r1.w;
+                cb[u] = s.r2[j].z;
+                const float dx = p.px - r0.x, dy = p.py - r0.y;
+                const float h = __builtin_fmaf(r0.w, dy, r0.z * dx);
+                const float power = __builtin_fmaf(dx, h, (r1.x * dy) * dy);
+                alpha[u] = fminf(cfg.alpha_max, r1.y * exp_c(power));
+                ok[u] = ballot(!(power > 0.0f)) & ballot(alpha[u] >= cfg.alpha_min);
             }
-            T = blend ? Tn : T;
-            lastj = blend ? j : lastj;
+#pragma unroll
+            for (int u = 0; u < GROUP; u++) {
+                const float Tn = T * (1.0f - alpha[u]), w = alpha[u] * T;
+                const uint64_t in = ok[u] & ~done, stop = in & ballot(Tn < cfg.T_min), blend = in ^ stop;
+                done |= stop;
+                blend_under_mask(blend, C0, C1, C2, T, lastk, cr[u], cg[u], cb[u], w, Tn, k + u);
+                if (BITS) {
+                    // w is alpha T with the transmittance in front of this Gaussian: where it is blended, w > alpha_min
+                    // (FS_SCORE_WEIGHT) or w > 0 (FS_SCORE_ALPHA, always) decides; the row's first lane stores the row's
+                    // 16 bits
+                    const uint64_t hb = blend & ballot(w > hit_above);
+                    if ((threadIdx.x & 15) == 0) s_pb[(word >> (8 * u)) & 0xffu][sub] = (uint16_t)(hb >> (threadIdx.x & 48));
+                }
+            }
         }
-        last = lastj >= 0 ? (uint32_t)(start + lastj + 1) : last;
+        last = lastk >= 0 ? (uint32_t)(start + s.slot(sub, lastk) + 1) : last;
     }
     if (BITS) {
         if (pending >= 0) {
@@ -446,10 +474,10 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
         wave_step<0x142, 0xA, false>(l1, esum, esq, lo_e, hi_e);
         wave_step<0x143, 0xC, false>(l1, esum, esq, lo_e, hi_e);
         const float fmin_e = __uint_as_float(lo_e), fmax_e = __uint_as_float(hi_e);
-        // (the staging masks serve as the 4 x 5 doubles of scratch: they are only live inside stage_batch, between
-        // its two barriers, and every wavefront has left its last stage_batch before any of them gets here)
-        static_assert(sizeof(s.bits) >= 4 * 5 * sizeof(double), "scratch for the per-wavefront partials");
-        double (*s_part)[5] = reinterpret_cast<double (*)[5]>(&s.bits[0][0]);
+        // (the staging masks serve as the 4 x 5 doubles of scratch: they are only live inside stage_batch)
+        static_assert(sizeof(s.sub) >= 4 * 5 * sizeof(double), "scratch for the per-wavefront partials");
+        __syncthreads();
+        double (*s_part)[5] = reinterpret_cast<double (*)[5]>(s.sub);
         if ((threadIdx.x & 63) == 63) {
             double* w = s_part[threadIdx.x >> 6];
             w[0] = l1; w[1] = esum; w[2] = (double)fmin_e; w[3] = (double)fmax_e; w[4] = esq;
@@ -544,13 +572,13 @@ __global__ __launch_bounds__(256) void k_render_bwd(
     const float* __restrict__ dL_dimage, float4* __restrict__ pair_grad, uint8_t* __restrict__ rec_valid)
 {
     __shared__ Stage<true> s;
-    __shared__ uint32_t s_id[BATCH];
+    __shared__ uint32_t s_id[SLOTS];
     constexpr int NV = ABS ? 11 : 9;
     // The sub-tiles' sums of a Gaussian meet in double precision: on this chip the LDS atomic add of a double is
     // markedly cheaper than that of a float (the kernel takes 0.19 ms instead of 0.23 at 500k Gaussians), and the
     // sum of up to 16 single-precision terms is then exact unless their exponents span more than 29 bits.
     typedef double acc_t;
-    __shared__ acc_t s_acc[BATCH][NV];
+    __shared__ acc_t s_acc[SLOTS][NV];
     __shared__ int s_max;
 
     const int tile = (int)tile_order[blockIdx.x];  // longest lists first
@@ -594,14 +622,12 @@ __global__ __launch_bounds__(256) void k_render_bwd(
         const int last_here = last - start;   // slots below this one hold entries this pixel blended (or examined)
         for (int it = 0; it < longest; it++) {
             const int k = mine - 1 - it;      // every row walks its own list from the back
-            const int j = s.list[sub][k & (BATCH - 1)];
-            const float4* e = s.at(j);
-            const float4 r0 = e[0], r1 = e[1];           // (mu_x, mu_y, a, 2b), (c, sigma, r, g)
+            const int j = s.slot(sub, k);
+            const float4 r0 = s.r0[j], r1 = s.r1[j];
             const float dx = p.px - r0.x, dy = p.py - r0.y;
-            const float u = __builtin_fmaf(r0.w, dy, r0.z * dx);
-            const float q = __builtin_fmaf(dx, u, (r1.x * dy) * dy);
-            const float power = -0.5f * q;
-            bool act = (k >= 0) & (j < last_here) & !(power > 0.0f) & !(power < cfg.power_min);
+            const float h = __builtin_fmaf(r0.w, dy, r0.z * dx);
+            const float power = __builtin_fmaf(dx, h, (r1.x * dy) * dy);
+            bool act = (k >= 0) & (j < last_here) & !(power > 0.0f);
             float G = exp_c(power);   // (whatever the exponent of a lane that fails the test: its result is dropped)
             const float sG = r1.y * G;
             float alpha = fminf(cfg.alpha_max, sG);
@@ -612,7 +638,7 @@ __global__ __launch_bounds__(256) void k_render_bwd(
             // every one of their 9 contributions is then an exact zero (and T / (1 - 0) leaves T as it is)
             alpha = act ? alpha : 0.f;
             G = act ? G : 0.f;
-            const float4 r2 = e[2];   // (r, g, b, -sigma / 2)
+            const float4 r2 = s.r2[j];
             T = T * __builtin_amdgcn_rcpf(1.0f - alpha);             // transmittance in front of this Gaussian
             const float w = alpha * T;
             float v[9];
@@ -625,7 +651,7 @@ __global__ __launch_bounds__(256) void k_render_bwd(
             S = __builtin_fmaf(alpha, diff, S);
             dL_dalpha = sG > cfg.alpha_max ? 0.f : dL_dalpha;  // capped alpha is a constant
             v[3] = G * dL_dalpha;                              // d/d sigma
-            const float gq = r2.w * v[3];                      // d/d q = -1/2 sigma G dL/dalpha
+            const float gq = -0.5f * r1.y * v[3];                      // d/d q = -1/2 sigma G dL/dalpha
             const float gx = gq * dx, gy = gq * dy;
             v[4] = gx * dx;
             v[5] = gx * dy;
@@ -637,8 +663,8 @@ __global__ __launch_bounds__(256) void k_render_bwd(
             // lanes 0..7 of a row hold the totals of values 0..7, lane 8 adds the ninth
             const int li = lane & 15;
             if (ABS) {
-                // |dq/dmu . g| per pixel: (2a dx + 2b dy, 2b dx + 2c dy) scaled by |g|  (r0.w holds 2b)
-                const float ag = fabsf(gq);
+                // |dq/dmu . g| per pixel: (2a dx + 2b dy, 2b dx + 2c dy) scaled by |g|
+                const float ag = 2.0f * fabsf(gq);
                 const float ax = ag * fabsf(__builtin_fmaf(r0.w, dy, 2.0f * r0.z * dx));
                 const float ay = ag * fabsf(__builtin_fmaf(r0.w, dx, 2.0f * r1.x * dy));
                 const float r2 = row_reduce2(ax, ay, lane);
@@ -664,8 +690,8 @@ __global__ __launch_bounds__(256) void k_render_bwd(
                 for (int k = 0; k < NV; k++) any = any | (a[k] != 0.f);
             }
             if (any) {
-                const float4 f0 = s.at(threadIdx.x)[0], f1 = s.at(threadIdx.x)[1];
-                const float4 co = make_float4(f0.z, f0.w, f1.x, f1.y);  // (a, 2b, c, sigma)
+                const float4 f0 = s.r0[threadIdx.x];
+                const float3 co = make_float3(-2.0f * f0.z, -2.0f * f0.w, -2.0f * s.r1[threadIdx.x].x);  // (a, 2b, c)
                 const uint32_t idx = s_id[threadIdx.x];
                 float4* rec = pair_grad + (size_t)idx * (PAIR_REC / 4);
                 rec[0] = make_float4(a[0], a[1], a[2], a[3]);
@@ -741,10 +767,10 @@ __global__ __launch_bounds__(256) void k_render_bwd_splat(
     const float* __restrict__ dL_dimage, float4* __restrict__ pair_grad, uint8_t* __restrict__ rec_valid)
 {
     __shared__ Stage<true> s;
-    __shared__ uint32_t s_id[BATCH];
+    __shared__ uint32_t s_id[SLOTS];
     constexpr int NV = ABS ? 11 : 9;
-    __shared__ double s_acc[BATCH][NV];   // (double: the cheaper LDS atomic add on this chip, see k_render_bwd)
-    __shared__ uint8_t s_qlist[4][BATCH];   // per quadrant: the batch slots on its list, in list order
+    __shared__ double s_acc[SLOTS][NV];   // (double: the cheaper LDS atomic add on this chip, see k_render_bwd)
+    __shared__ uint8_t s_qlist[4][SLOTS];   // per quadrant: the batch slots on its list, in list order
     __shared__ int s_max;
 
     const int tile = (int)tile_order[blockIdx.x];
@@ -786,11 +812,9 @@ __global__ __launch_bounds__(256) void k_render_bwd_splat(
         // the quadrant's list: lane l looks at slots 4 l .. 4 l + 3 of the union of its four sub-tiles' masks
         uint32_t b4 = 0;
         {
-            const int word = lane >> 4, shift = (lane & 15) * 4;
-            uint64_t u = 0;
+            const uint16_t* of = reinterpret_cast<const uint16_t*>(s.sub);
 #pragma unroll
-            for (int r = 0; r < 4; r++) u |= s.bits[wave * 4 + r][word];
-            b4 = (uint32_t)(u >> shift) & 0xFu;
+            for (int k = 0; k < 4; k++) b4 |= (of[s.sub_place(4 * lane + k)] >> (wave * 4) & 0xfu) != 0u ? 1u << k : 0u;
         }
         const int cnt = __popc(b4);
         int inc = cnt;
@@ -817,9 +841,9 @@ __global__ __launch_bounds__(256) void k_render_bwd_splat(
                 const int idx = c_end - 1 - lane;
                 const bool have = idx >= 0;
                 const int j = have ? (int)s_qlist[wave][idx] : 0;
-                const float4 f0 = s.at(j)[0], f1 = s.at(j)[1], f2 = s.at(j)[2];
+                const float4 f0 = s.r0[j], f1 = s.r1[j], f2 = s.r2[j];
                 const float2 xy = make_float2(f0.x, f0.y);
-                const float4 co = make_float4(f0.z, f0.w, f1.x, f1.y);    // (a, 2b, c, sigma)
+                const float4 co = make_float4(f0.z, f0.w, f1.x, f1.y);    // (-a/2, -b, -c/2, sigma)
                 const float4 col = make_float4(f2.x, f2.y, f2.z, 0.f);
                 const int pos_j = start + j;
                 float acc[NV];
@@ -832,10 +856,9 @@ __global__ __launch_bounds__(256) void k_render_bwd_splat(
                     const float px = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p.px), q));
                     const float py = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p.py), q));
                     const float dx = px - xy.x, dy = py - xy.y;
-                    const float u = __builtin_fmaf(co.y, dy, co.x * dx);
-                    const float qq = __builtin_fmaf(dx, u, (co.z * dy) * dy);
-                    const float power = -0.5f * qq;
-                    bool act = have & (pos_j < last_q) & !(power > 0.0f) & !(power < cfg.power_min);
+                    const float h = __builtin_fmaf(co.y, dy, co.x * dx);
+                    const float power = __builtin_fmaf(dx, h, (co.z * dy) * dy);
+                    bool act = have & (pos_j < last_q) & !(power > 0.0f);
                     if (__ballot(act) == 0) continue;
                     float G = exp_c(act ? power : 0.0f);
                     const float sG = co.w * G;
@@ -873,7 +896,7 @@ __global__ __launch_bounds__(256) void k_render_bwd_splat(
                     acc[7] += gx;
                     acc[8] += gy;
                     if (ABS) {
-                        const float ag = fabsf(gq);
+                        const float ag = 2.0f * fabsf(gq);
                         acc[NV - 2] = __builtin_fmaf(ag, fabsf(__builtin_fmaf(co.y, dy, 2.0f * co.x * dx)), acc[NV - 2]);
                         acc[NV - 1] = __builtin_fmaf(ag, fabsf(__builtin_fmaf(co.y, dx, 2.0f * co.z * dy)), acc[NV - 1]);
                     }
@@ -905,8 +928,8 @@ __global__ __launch_bounds__(256) void k_render_bwd_splat(
                 for (int k = 0; k < NV; k++) any = any | (a[k] != 0.f);
             }
             if (any) {
-                const float4 f0 = s.at(threadIdx.x)[0], f1 = s.at(threadIdx.x)[1];
-                const float4 co = make_float4(f0.z, f0.w, f1.x, f1.y);  // (a, 2b, c, sigma)
+                const float4 f0 = s.r0[threadIdx.x];
+                const float3 co = make_float3(-2.0f * f0.z, -2.0f * f0.w, -2.0f * s.r1[threadIdx.x].x);  // (a, 2b, c)
                 const uint32_t idx = s_id[threadIdx.x];
                 float4* rec = pair_grad + (size_t)idx * (PAIR_REC / 4);
                 rec[0] = make_float4(a[0], a[1], a[2], a[3]);
@@ -945,8 +968,8 @@ __global__ __launch_bounds__(256) void k_score(CamDev cam, CfgDev cfg, const uin
                                                const uint8_t* __restrict__ mask, int32_t* __restrict__ counts)
 {
     __shared__ Stage<false> s;
-    __shared__ uint32_t s_id[BATCH];
-    __shared__ int s_cnt[BATCH];
+    __shared__ uint32_t s_id[SLOTS];
+    __shared__ int s_cnt[SLOTS];
     __shared__ int s_max;
 
     const int tile = (int)tile_order[blockIdx.x];  // longest lists first
@@ -999,25 +1022,23 @@ __global__ __launch_bounds__(256) void k_score(CamDev cam, CfgDev cfg, const uin
             __syncthreads();  // the previous batch's flush has read s_cnt / s_id
             s_cnt[threadIdx.x] = 0;
             stage_batch<false, 1>(s, s_id, cam, cfg, tile, gauss_sorted, splats, range.x + start, m);
+            __syncthreads();  // (a walker follows the list of its own sub-tile, whichever wavefront made it)
             if (wave_on) {
                 const int len = start < my_last ? s.len[my_sub] : 0;
                 // two list entries per trip: their alphas are independent, only the transmittance chains
                 for (int k = 0; __ballot(k < len) != 0; k += 2) {
-                    const int j0 = s.list[my_sub][k & (BATCH - 1)], j1 = s.list[my_sub][(k + 1) & (BATCH - 1)];
-                    const float4 a0 = s.at(j0)[0], b0 = s.at(j0)[1], a1 = s.at(j1)[0], b1 = s.at(j1)[1];
-                    const float2 xy0 = make_float2(a0.x, a0.y), xy1 = make_float2(a1.x, a1.y);
-                    const float4 co0 = make_float4(a0.z, a0.w, b0.x, b0.y), co1 = make_float4(a1.z, a1.w, b1.x, b1.y);
-                    const float dx0 = pw.px - xy0.x, dy0 = pw.py - xy0.y;
-                    const float dx1 = pw.px - xy1.x, dy1 = pw.py - xy1.y;
-                    const float q0 = __builtin_fmaf(dx0, __builtin_fmaf(co0.y, dy0, co0.x * dx0), (co0.z * dy0) * dy0);
-                    const float q1 = __builtin_fmaf(dx1, __builtin_fmaf(co1.y, dy1, co1.x * dx1), (co1.z * dy1) * dy1);
-                    const float power0 = -0.5f * q0, power1 = -0.5f * q1;
-                    bool act0 = (k < len) & (start + j0 < my_last) & !(power0 > 0.0f) & !(power0 < cfg.power_min);
-                    bool act1 = (k + 1 < len) & (start + j1 < my_last) & !(power1 > 0.0f) & !(power1 < cfg.power_min);
+                    const int j0 = s.slot(my_sub, k), j1 = s.slot(my_sub, k + 1);
+                    const float4 a0 = s.r0[j0], b0 = s.r1[j0], a1 = s.r0[j1], b1 = s.r1[j1];
+                    const float dx0 = pw.px - a0.x, dy0 = pw.py - a0.y;
+                    const float dx1 = pw.px - a1.x, dy1 = pw.py - a1.y;
+                    const float power0 = __builtin_fmaf(dx0, __builtin_fmaf(a0.w, dy0, a0.z * dx0), (b0.x * dy0) * dy0);
+                    const float power1 = __builtin_fmaf(dx1, __builtin_fmaf(a1.w, dy1, a1.z * dx1), (b1.x * dy1) * dy1);
+                    bool act0 = (k < len) & (start + j0 < my_last) & !(power0 > 0.0f);
+                    bool act1 = (k + 1 < len) & (start + j1 < my_last) & !(power1 > 0.0f);
                     if (__ballot(act0 | act1) == 0) continue;
                     // (an inactive entry's exponent may be anything: clamp it so that exp_c stays in range)
-                    const float alpha0 = fminf(cfg.alpha_max, co0.w * exp_c(act0 ? power0 : 0.0f));
-                    const float alpha1 = fminf(cfg.alpha_max, co1.w * exp_c(act1 ? power1 : 0.0f));
+                    const float alpha0 = fminf(cfg.alpha_max, b0.y * exp_c(act0 ? power0 : 0.0f));
+                    const float alpha1 = fminf(cfg.alpha_max, b1.y * exp_c(act1 ? power1 : 0.0f));
                     act0 = act0 & (alpha0 >= cfg.alpha_min);
                     act1 = act1 & (alpha1 >= cfg.alpha_min);
                     const bool hit0 = act0 & (cfg.score_mode == FS_SCORE_ALPHA || alpha0 * T > cfg.alpha_min);
@@ -1048,17 +1069,13 @@ __global__ __launch_bounds__(256) void k_score(CamDev cam, CfgDev cfg, const uin
             const bool row_walks = ((walking >> (lane & 48)) & 0xffffull) != 0;
             const int longest = wave_max_of_rows(row_walks ? mine : 0);
             for (int k = 0; k < longest; k++) {
-                const int j = s.list[sub][k];
-                const float4 a0 = s.at(j)[0], b0 = s.at(j)[1];
-                const float2 xy = make_float2(a0.x, a0.y);
-                const float4 co = make_float4(a0.z, a0.w, b0.x, b0.y);
-                const float dx = p.px - xy.x, dy = p.py - xy.y;
-                const float u = __builtin_fmaf(co.y, dy, co.x * dx);
-                const float q = __builtin_fmaf(dx, u, (co.z * dy) * dy);
-                const float power = -0.5f * q;
-                bool act = (k < mine) & (start + j < last) & !(power > 0.0f) & !(power < cfg.power_min);
+                const int j = s.slot(sub, k);
+                const float4 a0 = s.r0[j], b0 = s.r1[j];
+                const float dx = p.px - a0.x, dy = p.py - a0.y;
+                const float power = __builtin_fmaf(dx, __builtin_fmaf(a0.w, dy, a0.z * dx), (b0.x * dy) * dy);
+                bool act = (k < mine) & (start + j < last) & !(power > 0.0f);
                 if (__ballot(act) == 0) continue;
-                const float alpha = fminf(cfg.alpha_max, co.w * exp_c(power));
+                const float alpha = fminf(cfg.alpha_max, b0.y * exp_c(power));
                 act = act & (alpha >= cfg.alpha_min);
                 const float w = alpha * T;
                 const bool hit = act & (cfg.score_mode == FS_SCORE_ALPHA || w > cfg.alpha_min);
