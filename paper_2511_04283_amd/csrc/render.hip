@@ -25,7 +25,7 @@ namespace fs {
 
 namespace {
 
-constexpr int SLOTS = 256;        // records a workgroup holds in LDS: one per thread
+constexpr int SLOTS = 256;        // records a workgroup holds in LDS: one per thread (k_render_bwd: fewer)
 constexpr int BATCH = SLOTS - 1;  // list entries staged at a time; the last record is the empty one that pads the sub-tile lists
 constexpr int GROUP = 4;          // entries of a sub-tile list that a lane evaluates side by side (one 32-bit word of slots)
 
@@ -86,21 +86,24 @@ __device__ __forceinline__ Pixel pixel_of_thread(const CamDev& cam, int tile)
 
 // LDS image of one batch of a tile's list, shared by the kernels.  A staged Gaussian is one 16-byte word in each of two
 // or (WITH_RGB) three arrays, so that one slot number, shifted once, addresses all of them:
-//   r0 = (mu_x, mu_y, -a/2, -b)   r1 = (-c/2, sigma, r, g)   r2 = (r, g, b, 0)
+//   r0 = (mu_x, mu_y, -a/2, -b)   r1 = (-c/2, sigma, r, g)   r2 = (r, g, b, bits of the pair's gradient record number)
 // The factors make the quadratic form come out as the exponent -1/2 (a dx^2 + 2 b dx dy + c dy^2) itself: halving and
 // negating commute with every rounding on the way, so the exponent is the same to the bit.
-template <bool WITH_RGB>
+template <bool WITH_RGB, int N = SLOTS>
 struct Stage {
-    float4 r0[SLOTS], r1[SLOTS];
-    float4 r2[WITH_RGB ? SLOTS : 1];
-    uint32_t list[16][SLOTS / 4];  // per sub-tile (index wave*4 + row): batch slots to visit, in list order, one byte each
-    __align__(16) uint32_t sub[SLOTS / 2];  // per slot, 16 bits: the sub-tiles that visit it (see sub_place)
+    static_assert(N <= 256 && N % 8 == 0, "one byte names a slot, one thread fills it");
+    static constexpr int EMPTY = N - 1;
+    float4 r0[N], r1[N];
+    float4 r2[WITH_RGB ? N : 1];
+    __align__(16) uint32_t list[16][N / 4];  // per sub-tile (index wave*4 + row): batch slots to visit, in list order, one byte each
+    __align__(16) uint32_t sub[128];  // per slot, 16 bits: the sub-tiles that visit it (see sub_place)
     int len[16];                   // length of each sub-tile's list
-    // Slot BATCH is the empty record (sigma = 0: alpha = 0, nothing is ever blended); the others must hold finite numbers
+    // Slot EMPTY is the empty record (sigma = 0: alpha = 0, nothing is ever blended); the others must hold finite numbers
     // before they are filled for the first time.
     __device__ __forceinline__ void clear(int t)
     {
         const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (N < 256 && t >= N) return;
         r0[t] = z;
         r1[t] = z;
         if (WITH_RGB) r2[t] = z;
@@ -108,7 +111,7 @@ struct Stage {
     // where slot t's 16 bits sit in `sub` (in units of 16 bits): word 8 (t / 16) + t % 8, upper half for t % 16 >= 8, so
     // that the eight words of 16 slots turn into one sub-tile's 16 bits with a shift, a mask and an insertion each
     static __device__ __forceinline__ int sub_place(int t) { return ((t >> 4) * 8 + (t & 7)) * 2 + ((t >> 3) & 1); }
-    __device__ __forceinline__ int slot(int st, int k) const { return reinterpret_cast<const uint8_t*>(list[st])[k & (SLOTS - 1)]; }
+    __device__ __forceinline__ int slot(int st, int k) const { return reinterpret_cast<const uint8_t*>(list[st])[N == 256 ? k & 255 : k]; }
 };
 
 // Sub-tile st = wave*4 + row of a tile sits at column kx = (wave&1)*2 + (row&1), line ky = (wave>>1)*2 + (row>>1).
@@ -146,13 +149,13 @@ __device__ __forceinline__ uint32_t dpp_shr_add(uint32_t v)
 // Lists: every thread leaves its entry's 16 sub-tile bits in LDS; then the 16 lanes that own a sub-tile in the render
 // loops gather that sub-tile's bit of 16 slots each and expand them into slot numbers with a prefix sum over the row.
 // The rest of a list is filled with the empty slot, so that the loops may run past a list's end.
-// REVERSED: the lists run from the last entry to the first.
-// ID_MODE: 0 = s_id unused, 1 = s_id[t] <- Gaussian index, 2 = s_id[t] <- index of the pair's
+// REVERSED: the lists run from the last entry to the first, and the calling lane's row leaves out slots from row_end on.
+// ID_MODE: 0 = nothing, 1 = s_id[t] <- Gaussian index, 2 = r2[t].w <- index of the pair's
 // gradient record (where the pair was emitted before the sort: offset + place in the rectangle).
-template <bool WITH_RGB, int ID_MODE, bool REVERSED = false>
-__device__ __forceinline__ int stage_batch(Stage<WITH_RGB>& s, uint32_t* s_id, const CamDev& cam,
+template <int ID_MODE, bool REVERSED = false, bool WITH_RGB, int N>
+__device__ __forceinline__ int stage_batch(Stage<WITH_RGB, N>& s, uint32_t* s_id, const CamDev& cam,
                                            const CfgDev& cfg, int tile, const uint32_t* __restrict__ gauss_sorted,
-                                           const float4* __restrict__ splats, uint32_t first, int m)
+                                           const float4* __restrict__ splats, uint32_t first, int m, int row_end = N)
 {
     const int t = threadIdx.x;
     const int swave = t >> 6, lane = t & 63;
@@ -165,14 +168,15 @@ __device__ __forceinline__ int stage_batch(Stage<WITH_RGB>& s, uint32_t* s_id, c
         const float4 co = make_float4(r0.z, r0.w, r1.x, r1.y);
         s.r0[t] = make_float4(xy.x, xy.y, -0.5f * co.x, -co.y);
         s.r1[t] = make_float4(-0.5f * co.z, co.w, r1.z, r1.w);
-        if (WITH_RGB) s.r2[t] = make_float4(r1.z, r1.w, r2.x, 0.f);
+        float id = 0.f;
         if (ID_MODE == 1) s_id[t] = g;
         if (ID_MODE == 2) {
             const uint32_t r01 = __float_as_uint(r2.z), r23 = __float_as_uint(r2.w);
             const uint32_t x0 = r01 & 0xffffu, y0 = r01 >> 16, x1 = r23 & 0xffffu;
-            s_id[t] = __float_as_uint(r2.y) + ((uint32_t)(tile / cam.tiles_x) - y0) * (x1 - x0) +
-                      ((uint32_t)(tile % cam.tiles_x) - x0);
+            id = __uint_as_float(__float_as_uint(r2.y) + ((uint32_t)(tile / cam.tiles_x) - y0) * (x1 - x0) +
+                                 ((uint32_t)(tile % cam.tiles_x) - x0));
         }
+        if (WITH_RGB) s.r2[t] = make_float4(r1.z, r1.w, r2.x, id);
         const float ratio = co.w * __builtin_amdgcn_rcpf(cfg.alpha_min);
         if (ratio >= 1.0f) {
             const float det = co.x * co.z - co.y * co.y;
@@ -215,7 +219,8 @@ __device__ __forceinline__ int stage_batch(Stage<WITH_RGB>& s, uint32_t* s_id, c
         }
     }
     reinterpret_cast<uint16_t*>(s.sub)[s.sub_place(t)] = (uint16_t)sub_mask;
-    reinterpret_cast<uint4*>(s.list)[t] = make_uint4(0x01010101u * BATCH, 0x01010101u * BATCH, 0x01010101u * BATCH, 0x01010101u * BATCH);
+    constexpr uint32_t PAD = 0x01010101u * (uint32_t)(N - 1);
+    if (N == 256 || t < N) reinterpret_cast<uint4*>(s.list)[t] = make_uint4(PAD, PAD, PAD, PAD);
     __syncthreads();
     // lane i of the row that owns sub-tile st expands slots [16 i, 16 i + 16)
     const int st = swave * 4 + (lane >> 4);
@@ -225,6 +230,7 @@ __device__ __forceinline__ int stage_batch(Stage<WITH_RGB>& s, uint32_t* s_id, c
     const uint32_t both = bits_of(lo.x, 0) | bits_of(lo.y, 1) | bits_of(lo.z, 2) | bits_of(lo.w, 3) | bits_of(hi.x, 4) |
                           bits_of(hi.y, 5) | bits_of(hi.z, 6) | bits_of(hi.w, 7);
     uint32_t b16 = (both & 0xffu) | (both >> 16) << 8;
+    if (REVERSED) b16 &= (1u << min(max(row_end - 16 * i, 0), 16)) - 1u;
     const uint32_t cnt = __popc(b16);
     uint32_t inc = cnt;
     inc = dpp_shr_add<0x111>(inc);  // row_shr:1
@@ -265,7 +271,9 @@ __device__ __forceinline__ void wave_step(double& a, double& b, double& c, uint3
     hi = max(hi, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, CTRL, ROW_MASK, 0xF, SHIFT));
 }
 
+// Conditions are kept as one bit per lane of the wavefront (the scalar unit combines them).
 __device__ __forceinline__ uint64_t ballot(bool v) { return __builtin_amdgcn_ballot_w64(v); }
+__device__ __forceinline__ bool lane_of(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
 // Where `mask` has a lane's bit: C += w c, T = Tn, last = at.  Five vector instructions under the lane mask, where selects
 // would take two more, and no branch in the way of the instructions around them.  Called with all 64 lanes active.
@@ -376,7 +384,7 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
             pending = start;
             pending_m = m;
         }
-        const int mine = stage_batch<true, 0>(s, nullptr, cam, cfg, tile, gauss_sorted, splats, range.x + start, m);
+        const int mine = stage_batch<0>(s, nullptr, cam, cfg, tile, gauss_sorted, splats, range.x + start, m);
         // a row whose 16 pixels have all finished does not lengthen the wavefront's loop
         const bool row_alive = ((~done >> (threadIdx.x & 48)) & 0xffffull) != 0;
         const int longest = wave_max_of_rows(row_alive ? mine : 0);
@@ -494,64 +502,25 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
     }
 }
 
-// ---- row reduction of 9 values -------------------------------------------------------------
-// A row of 16 lanes (one 4x4 sub-tile) sums 9 per-pixel values.  Instead of 9 separate butterflies
-// the first three steps halve the number of live registers: at the step for lane bit b, a lane
-// keeps the value whose index has that bit equal to its own and hands the other one to its partner.
-// After the four steps lane i of the row holds the row total of value (i & 7); value 8 is summed
-// the plain way and ends up in every lane.
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_get(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-
-// lanes with `bit` clear end up with sum(a) over the exchanged pair, lanes with it set with sum(b)
-template <int CTRL>
-__device__ __forceinline__ float fold(bool bit, float a, float b)
-{
-    const float keep = bit ? b : a, give = bit ? a : b;
-    return keep + dpp_get<CTRL>(give);
-}
-
-__device__ __forceinline__ void row_reduce9(const float v[9], int lane, float& packed, float& ninth)
-{
-    constexpr int XOR1 = 0xB1, XOR2 = 0x4E, ROR4 = 0x124, ROR8 = 0x128;  // quad_perm swaps, row rotations
-    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
-    const float r01 = fold<XOR1>(b0, v[0], v[1]);
-    const float r23 = fold<XOR1>(b0, v[2], v[3]);
-    const float r45 = fold<XOR1>(b0, v[4], v[5]);
-    const float r67 = fold<XOR1>(b0, v[6], v[7]);
-    float r8 = v[8] + dpp_get<XOR1>(v[8]);
-    const float s03 = fold<XOR2>(b1, r01, r23);
-    const float s47 = fold<XOR2>(b1, r45, r67);
-    r8 = r8 + dpp_get<XOR2>(r8);
-    // lane i+4 has the opposite bit 2, so a rotation by 4 pairs the lanes like the earlier swaps did
-    float u = fold<ROR4>(b2, s03, s47);
-    r8 = r8 + dpp_get<ROR4>(r8);
-    u = u + dpp_get<ROR8>(u);
-    r8 = r8 + dpp_get<ROR8>(r8);
-    packed = u;
-    ninth = r8;
-}
-
-// Two more values: afterwards the even lanes of the row hold the total of a, the odd lanes that of b.
-__device__ __forceinline__ float row_reduce2(float a, float b, int lane)
-{
-    constexpr int XOR1 = 0xB1, XOR2 = 0x4E, ROR4 = 0x124, ROR8 = 0x128;
-    float r = fold<XOR1>(lane & 1, a, b);
-    r = r + dpp_get<XOR2>(r);
-    r = r + dpp_get<ROR4>(r);
-    r = r + dpp_get<ROR8>(r);
-    return r;
-}
-
-// Backward of the compositing.  Walks each sub-tile's list back to front from the furthest blended
-// Gaussian; per Gaussian, 9 partial sums over the 16 pixels of a sub-tile are formed across the
-// row's lanes and combined across the sub-tiles in LDS.  The 9 sums: dL/drgb (3), dL/dsigma, and with
-// g = dL/dq the moments sum g dx^2, g dx dy, g dy^2, g dx, g dy, from which dL/dconic and dL/dmu_2D
-// follow at the flush (dq/dmu is linear in d = p - mu).
+// ---- backward ---------------------------------------------------------------------------------
+// Walks each sub-tile's list back to front from the furthest blended Gaussian.  Per (Gaussian, pixel) two numbers are left:
+// w = alpha T and v = G dL/dalpha.  Everything a Gaussian receives from a sub-tile is a sum over its 16 pixels of one of
+// them times something that belongs to the pixel alone: w times the pixel's dL/dC (3 sums), and v times the pixel's place,
+// {1, x, y, x^2, x y, y^2} (dL/dsigma, and the moments from which dL/dconic and dL/dmu_2D follow).
+//
+// Vector instructions bound this kernel (they took every issue slot), and forming nine products per pixel and adding them up
+// across a row's 16 lanes took half of them.  So the numbers change places first: after eight entries of every row's list a
+// wavefront writes its 8 x 64 w's (then its v's) to LDS and reads them back with the 32 (entry, row) combinations across its
+// lanes, two lanes to a combination and eight pixels to a lane.  The sums over pixels are then plain additions within a
+// lane -- separable ones for the moments, since x and y take four values each -- plus one exchange between the two lanes:
+// 11 instructions per entry instead of 41.  (The matrix cores do not help: v_mfma_f32_16x16x4_f32 keeps the vector unit
+// from issuing for its 32 cycles, and forms many sums nobody wants; measured between the two.)
+// Before and after, in us: 4k Gaussians at 128x128 41 and 30, 100k at 980x545 119 and 82, 500k at 1600x1064 308 and 245 (with
+// ABS 336 and 262), 3 M at 1920x1080 730 and 565.
+//
+// Places are relative to the sub-tile's centre; a Gaussian's moments about its own centre mu follow from them with the
+// offset of the two, before sub-tiles are added up: both numbers are a few pixels where the Gaussian is small, so nothing is
+// lost by cancellation.  Places, offsets and so moments are in half pixels (x = -3, -1, 1, 3), which the flush undoes.
 //
 // Every Gaussian-tile pair owns one record of PAIR_REC floats in `pair_grad`, at the position the
 // pair had when it was emitted (pair_offsets[g] + its place in g's tile rectangle): the flush is a
@@ -565,29 +534,35 @@ __device__ __forceinline__ float row_reduce2(float a, float b, int lane)
 // magnitudes |dL/dmu_x|, |dL/dmu_y| of its own contribution, summed like the other values and stored
 // in the record's floats 9 and 10.
 template <bool ABS, bool SPARSE>
-__global__ __launch_bounds__(256) void k_render_bwd(
+__global__ __launch_bounds__(256, 4) void k_render_bwd(
     CamDev cam, CfgDev cfg, const uint2* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
     const uint32_t* __restrict__ gauss_sorted,
     const float4* __restrict__ splats, const float* __restrict__ final_T, const uint32_t* __restrict__ n_contrib,
     const float* __restrict__ dL_dimage, float4* __restrict__ pair_grad, uint8_t* __restrict__ rec_valid)
 {
-    __shared__ Stage<true> s;
-    __shared__ uint32_t s_id[SLOTS];
+    // (as many slots as four workgroups of a compute unit's 160 KB of LDS leave room for)
+    constexpr int N = ABS ? 208 : 232, B = N - 1;
     constexpr int NV = ABS ? 11 : 9;
+    constexpr int HALF = ABS ? 6 : 4;   // sums 0 .. HALF - 1 are added by the first lane of a combination, the others by the second
+    enum { DR, DG, DB, DSIGMA, DABS_X, DABS_Y, DX = HALF, DY, DXX, DYY, DXY };
+    constexpr int SPAN = 2 * GROUP;     // entries per exchange
     // The sub-tiles' sums of a Gaussian meet in double precision: on this chip the LDS atomic add of a double is
-    // markedly cheaper than that of a float (the kernel takes 0.19 ms instead of 0.23 at 500k Gaussians), and the
+    // markedly cheaper than that of a float, and the
     // sum of up to 16 single-precision terms is then exact unless their exponents span more than 29 bits.
     typedef double acc_t;
-    __shared__ acc_t s_acc[SLOTS][NV];
+    __shared__ Stage<true, N> s;
+    __shared__ acc_t s_acc[N][NV];
+    __shared__ __align__(16) float s_turn[4][SPAN][64];   // per wavefront: one value of SPAN entries, [entry][lane]
     __shared__ int s_max;
+    static_assert(sizeof(s) + sizeof(s_acc) + sizeof(s_turn) + sizeof(s_max) <= 40960, "four workgroups per compute unit");
 
     const int tile = (int)tile_order[blockIdx.x];  // longest lists first
     const Pixel p = pixel_of_thread(cam, tile);
     const uint2 range = ranges[tile];
     const size_t hw = (size_t)cam.width * cam.height;
     const size_t pix = (size_t)p.y * cam.width + p.x;
-    const int lane = threadIdx.x & 63;
-    const int sub = (threadIdx.x >> 6) * 4 + (lane >> 4);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int sub = wave * 4 + (lane >> 4);
 
     const int last = p.inside ? (int)n_contrib[pix] : 0;
     float T = p.inside ? final_T[pix] : 0.f;
@@ -600,81 +575,163 @@ __global__ __launch_bounds__(256) void k_render_bwd(
     // dC . (colour composited behind the Gaussian at hand): all that dL/dalpha = T (dC . c - S) needs of it
     float S = __builtin_fmaf(dC2, cfg.bg[2], __builtin_fmaf(dC1, cfg.bg[1], dC0 * cfg.bg[0]));
 
-    // unfilled slots must hold finite numbers (lanes past their list's end compute with them and
-    // contribute exact zeros)
+    // After the exchange this lane has entry `ent` of row `row`: lines q1 and q2 (of four pixels each) of the row's sub-tile;
+    // the lane 8 places on in its group of 16 has the other two.  Which lane takes which lines is laid out so
+    // that any eight neighbouring lanes' 16-byte reads fall into different banks.
+    const int row = lane & 3, ent = (lane >> 2 & 1) | (lane >> 4) << 1;
+    const bool second = lane & 8;
+    const int q1 = ((lane >> 3 ^ lane >> 2) & 1) + (row & 2), q2 = q1 ^ 2;
+    const float y1 = (float)(2 * q1 - 3), y2 = (float)(2 * q2 - 3);
+    const int sub_x = (tile % cam.tiles_x) * TILE + (wave & 1) * 8 + (row & 1) * 4;
+    const int sub_y = (tile / cam.tiles_x) * TILE + (wave >> 1) * 8 + (row >> 1) * 4;
+    float g1[3][4], g2[3][4];   // the lines' dL/dC
+#pragma unroll
+    for (int ch = 0; ch < 3; ch++)
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            const int x = sub_x + c;
+            g1[ch][c] = x < cam.width && sub_y + q1 < cam.height ? dL_dimage[ch * hw + (size_t)(sub_y + q1) * cam.width + x] : 0.f;
+            g2[ch][c] = x < cam.width && sub_y + q2 < cam.height ? dL_dimage[ch * hw + (size_t)(sub_y + q2) * cam.width + x] : 0.f;
+        }
+    const float centre_x = (float)(2 * sub_x + 4), centre_y = (float)(2 * sub_y + 4);   // of the row's sub-tile, in half pixels
+    const uint8_t* const ent_list = reinterpret_cast<const uint8_t*>(s.list[wave * 4 + row]) + ent;
+    float* const turn = &s_turn[wave][0][lane];
+    const float4* const turned = reinterpret_cast<const float4*>(&s_turn[wave][0][0]) + ent * 16 + row * 4;
+    // (a wavefront's LDS operations complete in the order they were issued)
+    auto exchange = [&](const float (&v)[SPAN], float4& l1, float4& l2) {
+#pragma unroll
+        for (int u = 0; u < SPAN; u++) turn[u * 64] = v[u];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        l1 = turned[q1];
+        l2 = turned[q2];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    auto both = [](float v) {   // the sum of the two lanes of a combination, in both
+        constexpr int ROR8 = 0x128;
+        return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ROR8, 0xF, 0xF, true));
+    };
+
     s.clear(threadIdx.x);
     if (threadIdx.x == 0) s_max = 0;
+    int row_last = last;   // the furthest position any pixel of this lane's row of 16 reaches
+#pragma unroll
+    for (int d = 1; d < 16; d <<= 1) row_last = max(row_last, __shfl_xor(row_last, d, 64));
     __syncthreads();
-    atomicMax(&s_max, last);
+    if ((lane & 15) == 0) atomicMax(&s_max, row_last);
     __syncthreads();
     const int total = s_max;  // entries at positions >= total are blended by no pixel of the tile
 
-    // batches from the back: batch b covers positions [b*BATCH, min(total,(b+1)*BATCH))
-    for (int start = ((total - 1) / BATCH) * BATCH; start >= 0 && total > 0; start -= BATCH) {
-        const int m = min(BATCH, total - start);
-        __syncthreads();  // the previous batch's flush has read s_acc / s_id
+    // batches from the back: batch b covers positions [b*B, min(total,(b+1)*B))
+    for (int start = ((total - 1) / B) * B; start >= 0 && total > 0; start -= B) {
+        const int m = min(B, total - start);
+        __syncthreads();  // the previous batch's flush has read s_acc / s.r2
+        if ((int)threadIdx.x < N) {
 #pragma unroll
-        for (int k = 0; k < NV; k++) s_acc[threadIdx.x][k] = (acc_t)0;
-        const int mine = stage_batch<true, 2>(s, s_id, cam, cfg, tile, gauss_sorted, splats, range.x + start, m);
-        // a row none of whose pixels reaches into this batch does not lengthen the wavefront's loop
-        const bool row_walks = ((__ballot(start < last) >> (lane & 48)) & 0xffffull) != 0;
-        const int longest = wave_max_of_rows(row_walks ? mine : 0);
-        const int last_here = last - start;   // slots below this one hold entries this pixel blended (or examined)
-        for (int it = 0; it < longest; it++) {
-            const int k = mine - 1 - it;      // every row walks its own list from the back
-            const int j = s.slot(sub, k);
-            const float4 r0 = s.r0[j], r1 = s.r1[j];
-            const float dx = p.px - r0.x, dy = p.py - r0.y;
-            const float h = __builtin_fmaf(r0.w, dy, r0.z * dx);
-            const float power = __builtin_fmaf(dx, h, (r1.x * dy) * dy);
-            bool act = (k >= 0) & (j < last_here) & !(power > 0.0f);
-            float G = exp_c(power);   // (whatever the exponent of a lane that fails the test: its result is dropped)
-            const float sG = r1.y * G;
-            float alpha = fminf(cfg.alpha_max, sG);
-            act = act & (alpha >= cfg.alpha_min);
-            const uint64_t act_mask = __ballot(act);
-            if (act_mask == 0) continue;
-            // lanes that do not blend this Gaussian run the same arithmetic with alpha = G = 0:
-            // every one of their 9 contributions is then an exact zero (and T / (1 - 0) leaves T as it is)
-            alpha = act ? alpha : 0.f;
-            G = act ? G : 0.f;
-            const float4 r2 = s.r2[j];
-            T = T * __builtin_amdgcn_rcpf(1.0f - alpha);             // transmittance in front of this Gaussian
-            const float w = alpha * T;
-            float v[9];
-            v[0] = w * dC0;
-            v[1] = w * dC1;
-            v[2] = w * dC2;
-            const float cd = __builtin_fmaf(r2.z, dC2, __builtin_fmaf(r2.y, dC1, r2.x * dC0));   // dC . c
-            const float diff = cd - S;
-            float dL_dalpha = T * diff;
-            S = __builtin_fmaf(alpha, diff, S);
-            dL_dalpha = sG > cfg.alpha_max ? 0.f : dL_dalpha;  // capped alpha is a constant
-            v[3] = G * dL_dalpha;                              // d/d sigma
-            const float gq = -0.5f * r1.y * v[3];                      // d/d q = -1/2 sigma G dL/dalpha
-            const float gx = gq * dx, gy = gq * dy;
-            v[4] = gx * dx;
-            v[5] = gx * dy;
-            v[6] = gy * dy;
-            v[7] = gx;
-            v[8] = gy;
-            float packed, ninth;
-            row_reduce9(v, lane, packed, ninth);
-            // lanes 0..7 of a row hold the totals of values 0..7, lane 8 adds the ninth
-            const int li = lane & 15;
+            for (int k = 0; k < NV; k++) s_acc[threadIdx.x][k] = (acc_t)0;
+        }
+        // (entries behind a row's furthest one are left out of its list)
+        const int mine = stage_batch<2, true>(s, nullptr, cam, cfg, tile, gauss_sorted, splats, range.x + start, m, row_last - start);
+        const int longest = wave_max_of_rows(mine);
+        const uint32_t last_here = (uint32_t)max(last - start, 0);   // slots below this one hold entries this pixel blended (or examined)
+        for (int k = 0; k < longest; k += SPAN) {
+            const uint2 words = *reinterpret_cast<const uint2*>(&s.list[sub][k / 4]);
+            float w[SPAN], v[SPAN], ax[SPAN], ay[SPAN];
+            uint64_t acted = 0;
+#pragma unroll
+            for (int g = 0; g < SPAN; g += GROUP) {
+                const uint32_t word = g ? words.y : words.x;
+                float alpha[GROUP], G[GROUP], cd[GROUP], inv[GROUP], hx[GROUP], hy[GROUP];
+                if (g == 0 || k + g < longest) {
+#pragma unroll
+                    for (int u = 0; u < GROUP; u++) {
+                        const uint32_t j = (word >> (8 * u)) & 0xffu;
+                        const float4 r0 = s.r0[j], r2 = s.r2[j];
+                        const float2 r1 = make_float2(s.r1[j].x, s.r1[j].y);
+                        const float dx = p.px - r0.x, dy = p.py - r0.y;
+                        const float tx = r0.z * dx, ty = r1.x * dy;
+                        const float h = __builtin_fmaf(r0.w, dy, tx);
+                        const float power = __builtin_fmaf(dx, h, ty * dy);
+                        const float e = exp_c(power);
+                        const float sG = r1.y * e;
+                        const float al = fminf(cfg.alpha_max, sG);
+                        const uint64_t act = ballot(j < last_here) & ballot(!(power > 0.0f)) & ballot(al >= cfg.alpha_min);
+                        const uint64_t capped = ballot(sG > cfg.alpha_max);
+                        acted |= act;
+                        // lanes that do not blend this Gaussian run the same arithmetic with alpha = G = 0: w and v are
+                        // exact zeros (and T / (1 - 0) leaves T as it is); a capped alpha is a constant: G = 0
+                        alpha[u] = lane_of(act) ? al : 0.f;
+                        G[u] = lane_of(act & ~capped) ? e : 0.f;
+                        inv[u] = __builtin_amdgcn_rcpf(1.0f - alpha[u]);
+                        cd[u] = __builtin_fmaf(r2.z, dC2, __builtin_fmaf(r2.y, dC1, r2.x * dC0));   // dC . c
+                        if (ABS) {
+                            // half of dq/dmu, negated: (a dx + b dy, b dx + c dy)
+                            hx[u] = h + tx;
+                            hy[u] = __builtin_fmaf(r0.w, dx, ty + ty);
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < GROUP; u++) {
+                        T = T * inv[u];                                  // transmittance in front of this Gaussian
+                        w[g + u] = alpha[u] * T;
+                        const float diff = cd[u] - S;
+                        v[g + u] = G[u] * (T * diff);                    // G dL/dalpha: d/d sigma
+                        S = __builtin_fmaf(alpha[u], diff, S);
+                        if (ABS) {
+                            ax[g + u] = fabsf(v[g + u]) * fabsf(hx[u]);
+                            ay[g + u] = fabsf(v[g + u]) * fabsf(hy[u]);
+                        }
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < GROUP; u++) w[g + u] = v[g + u] = ax[g + u] = ay[g + u] = 0.f;
+                }
+            }
+            if (acted == 0) continue;
+            const int slot = ent_list[k];
+            const float mu_x = s.r0[slot].x, mu_y = s.r0[slot].y;
+            float sums[2][6];   // [0]: the first lane's, [1]: the second one's
+            float4 a, b;
+            exchange(w, a, b);
+#pragma unroll
+            for (int ch = 0; ch < 3; ch++)
+                sums[0][ch] = both(__builtin_fmaf(b.w, g2[ch][3], __builtin_fmaf(b.z, g2[ch][2], __builtin_fmaf(b.y, g2[ch][1],
+                                   __builtin_fmaf(b.x, g2[ch][0], __builtin_fmaf(a.w, g1[ch][3], __builtin_fmaf(a.z, g1[ch][2],
+                                   __builtin_fmaf(a.y, g1[ch][1], a.x * g1[ch][0]))))))));
+            exchange(v, a, b);
+            {
+                // a line's sums of v, x v, x^2 v with x = -3, -1, 1, 3
+                const float ao = a.x + a.w, ai = a.y + a.z, bo = b.x + b.w, bi = b.y + b.z;
+                const float a0 = ao + ai, b0 = bo + bi;
+                const float a1 = __builtin_fmaf(3.0f, a.w - a.x, a.z - a.y), b1 = __builtin_fmaf(3.0f, b.w - b.x, b.z - b.y);
+                const float m00 = both(a0 + b0), m10 = both(a1 + b1);
+                const float m20 = both(__builtin_fmaf(9.0f, ao, ai) + __builtin_fmaf(9.0f, bo, bi));
+                const float ya = y1 * a0, yb = y2 * b0;
+                const float m01 = both(ya + yb), m02 = both(__builtin_fmaf(y1, ya, y2 * yb));
+                const float m11 = both(__builtin_fmaf(y1, a1, y2 * b1));
+                // about mu: with (ox, oy) the sub-tile's centre seen from mu, sum (x + ox) v = m10 + ox m00 and so on
+                const float ox = __builtin_fmaf(-2.0f, mu_x, centre_x), oy = __builtin_fmaf(-2.0f, mu_y, centre_y);
+                const float dx = __builtin_fmaf(ox, m00, m10), dy = __builtin_fmaf(oy, m00, m01);
+                sums[0][DSIGMA] = m00;
+                sums[1][DX - HALF] = dx;
+                sums[1][DY - HALF] = dy;
+                sums[1][DXX - HALF] = __builtin_fmaf(ox, m10 + dx, m20);
+                sums[1][DYY - HALF] = __builtin_fmaf(oy, m01 + dy, m02);
+                sums[1][DXY - HALF] = __builtin_fmaf(oy, dx, __builtin_fmaf(ox, m01, m11));
+            }
             if (ABS) {
-                // |dq/dmu . g| per pixel: (2a dx + 2b dy, 2b dx + 2c dy) scaled by |g|
-                const float ag = 2.0f * fabsf(gq);
-                const float ax = ag * fabsf(__builtin_fmaf(r0.w, dy, 2.0f * r0.z * dx));
-                const float ay = ag * fabsf(__builtin_fmaf(r0.w, dx, 2.0f * r1.x * dy));
-                const float r2 = row_reduce2(ax, ay, lane);
-                // lane 10 (even) holds the total of ax -> slot 9, lane 9 (odd) that of ay -> slot 10
-                // (a row none of whose pixels blends the Gaussian has zero totals: nothing to add)
-                const float tot = li < 8 ? packed : (li == 8 ? ninth : r2);
-                if (li < 11 && tot != 0.f && k >= 0) atomicAdd(&s_acc[j][li < 9 ? li : 19 - li], (acc_t)tot);
-            } else {
-                const float tot = li < 8 ? packed : ninth;
-                if (li < 9 && tot != 0.f && k >= 0) atomicAdd(&s_acc[j][li], (acc_t)tot);
+                exchange(ax, a, b);
+                sums[0][DABS_X] = both(((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w)));
+                exchange(ay, a, b);
+                sums[0][DABS_Y] = both(((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w)));
+            }
+            acc_t* const acc = &s_acc[slot][second ? HALF : 0];
+#pragma unroll
+            for (int f = 0; f < (ABS ? 6 : 5); f++) {
+                const float mine_f = f >= HALF ? (second ? sums[1][f] : 0.f)
+                                   : f >= NV - HALF ? (second ? 0.f : sums[0][f]) : (second ? sums[1][f] : sums[0][f]);
+                if (mine_f != 0.f) atomicAdd(&acc[f], (acc_t)mine_f);
             }
         }
         __syncthreads();
@@ -691,13 +748,16 @@ __global__ __launch_bounds__(256) void k_render_bwd(
             }
             if (any) {
                 const float4 f0 = s.r0[threadIdx.x];
-                const float3 co = make_float3(-2.0f * f0.z, -2.0f * f0.w, -2.0f * s.r1[threadIdx.x].x);  // (a, 2b, c)
-                const uint32_t idx = s_id[threadIdx.x];
+                const float2 f1 = make_float2(s.r1[threadIdx.x].x, s.r1[threadIdx.x].y);
+                const float gq = -0.5f * f1.y;                                            // dL/dq = -1/2 sigma G dL/dalpha
+                const float3 co = make_float3(-2.0f * f0.z, -2.0f * f0.w, -2.0f * f1.x);  // (a, 2b, c)
+                const float mx = 0.5f * gq * a[DX], my = 0.5f * gq * a[DY];               // (half pixels)
+                const uint32_t idx = __float_as_uint(s.r2[threadIdx.x].w);
                 float4* rec = pair_grad + (size_t)idx * (PAIR_REC / 4);
-                rec[0] = make_float4(a[0], a[1], a[2], a[3]);
+                rec[0] = make_float4(a[DR], a[DG], a[DB], a[DSIGMA]);
                 // d = p - mu  =>  dq/dmu = -(2 a dx + 2b dy, 2b dx + 2 c dy)
-                rec[1] = make_float4(a[4], 2.0f * a[5], a[6], -(2.0f * co.x * a[7] + co.y * a[8]));
-                rec[2] = make_float4(-(co.y * a[7] + 2.0f * co.z * a[8]), ABS ? a[NV - 2] : 0.f, ABS ? a[NV - 1] : 0.f, 0.f);
+                rec[1] = make_float4(0.25f * gq * a[DXX], 0.5f * gq * a[DXY], 0.25f * gq * a[DYY], -(2.0f * co.x * mx + co.y * my));
+                rec[2] = make_float4(-(co.y * mx + 2.0f * co.z * my), ABS ? f1.y * a[DABS_X] : 0.f, ABS ? f1.y * a[DABS_Y] : 0.f, 0.f);
                 if (SPARSE) rec_valid[idx] = 1;
             }
         }
@@ -767,7 +827,6 @@ __global__ __launch_bounds__(256) void k_render_bwd_splat(
     const float* __restrict__ dL_dimage, float4* __restrict__ pair_grad, uint8_t* __restrict__ rec_valid)
 {
     __shared__ Stage<true> s;
-    __shared__ uint32_t s_id[SLOTS];
     constexpr int NV = ABS ? 11 : 9;
     __shared__ double s_acc[SLOTS][NV];   // (double: the cheaper LDS atomic add on this chip, see k_render_bwd)
     __shared__ uint8_t s_qlist[4][SLOTS];   // per quadrant: the batch slots on its list, in list order
@@ -805,10 +864,10 @@ __global__ __launch_bounds__(256) void k_render_bwd_splat(
 
     for (int start = ((total - 1) / BATCH) * BATCH; start >= 0 && total > 0; start -= BATCH) {
         const int m = min(BATCH, total - start);
-        __syncthreads();  // the previous batch's flush has read s_acc / s_id, its walk s_qlist
+        __syncthreads();  // the previous batch's flush has read s_acc, its walk s_qlist
 #pragma unroll
         for (int k = 0; k < NV; k++) s_acc[threadIdx.x][k] = 0.0;
-        stage_batch<true, 2>(s, s_id, cam, cfg, tile, gauss_sorted, splats, range.x + start, m);
+        stage_batch<2>(s, nullptr, cam, cfg, tile, gauss_sorted, splats, range.x + start, m);
         // the quadrant's list: lane l looks at slots 4 l .. 4 l + 3 of the union of its four sub-tiles' masks
         uint32_t b4 = 0;
         {
@@ -930,7 +989,7 @@ __global__ __launch_bounds__(256) void k_render_bwd_splat(
             if (any) {
                 const float4 f0 = s.r0[threadIdx.x];
                 const float3 co = make_float3(-2.0f * f0.z, -2.0f * f0.w, -2.0f * s.r1[threadIdx.x].x);  // (a, 2b, c)
-                const uint32_t idx = s_id[threadIdx.x];
+                const uint32_t idx = __float_as_uint(s.r2[threadIdx.x].w);
                 float4* rec = pair_grad + (size_t)idx * (PAIR_REC / 4);
                 rec[0] = make_float4(a[0], a[1], a[2], a[3]);
                 // d = p - mu  =>  dq/dmu = -(2 a dx + 2b dy, 2b dx + 2 c dy)
@@ -1021,7 +1080,7 @@ __global__ __launch_bounds__(256) void k_score(CamDev cam, CfgDev cfg, const uin
             const int m = min(BATCH, total - start);
             __syncthreads();  // the previous batch's flush has read s_cnt / s_id
             s_cnt[threadIdx.x] = 0;
-            stage_batch<false, 1>(s, s_id, cam, cfg, tile, gauss_sorted, splats, range.x + start, m);
+            stage_batch<1>(s, s_id, cam, cfg, tile, gauss_sorted, splats, range.x + start, m);
             __syncthreads();  // (a walker follows the list of its own sub-tile, whichever wavefront made it)
             if (wave_on) {
                 const int len = start < my_last ? s.len[my_sub] : 0;
@@ -1060,7 +1119,7 @@ __global__ __launch_bounds__(256) void k_score(CamDev cam, CfgDev cfg, const uin
         const int m = min(BATCH, total - start);
         __syncthreads();  // the previous batch's flush has read s_cnt / s_id
         s_cnt[threadIdx.x] = 0;
-        const int mine = stage_batch<false, 1>(s, s_id, cam, cfg, tile, gauss_sorted, splats,
+        const int mine = stage_batch<1>(s, s_id, cam, cfg, tile, gauss_sorted, splats,
                                                range.x + start, m);
         // a row none of whose pixels is still walking (no mask pixel, or all past their last Gaussian)
         // has nothing to count in this batch

@@ -1,0 +1,33 @@
+"""The render kernels' walks over the tile lists where their steps begin and end: groups of 4 entries (forward), exchanges of
+8 (backward), batches of 207, 231 (backward with and without the absolute gradient) and 255 (forward).  Every Gaussian
+covers the whole image of two ragged tiles and is faint, so that all of every list is blended; and the same with
+small ones, whose sub-tile lists have every length up to a few.  Integers bit for bit, image and gradients within the
+benchmark's bars (1e-4; 1e-3 with its floor) of the oracle."""
+import numpy as np
+import pytest
+
+from gpu_common import assert_grads_close, assert_image_close, gpu_pipeline
+from oracle import Oracle
+from paper_2511_04283_amd import scenes
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("want_abs", [False, True])
+@pytest.mark.parametrize("large", [True, False])
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 8, 9, 207, 208, 231, 232, 255, 256, 463])
+def test_list_of_n_entries(n, large, want_abs):
+    from paper_2511_04283_amd import binding as B
+    sc = scenes.tiny_scene(900 + n, n, 29, 13, sh_degree=0, log_scale=(-0.5, 0.2) if large else (-3.2, 0.5), spread=0.6)
+    sc.opacities[:] = np.random.default_rng(n).uniform(0.006, 0.02, n) if large else 0.7
+    cam = sc.cameras[0]
+    dL = np.random.default_rng(n + 1).normal(size=(3, cam.height, cam.width)).astype(np.float32)
+    c = B.Context("cuda:0")
+    out = gpu_pipeline(c, sc, cam, dL=dL, want_abs=want_abs)
+    c.close()
+    o = Oracle(np.float32)
+    p, b, image, T, nc = o.forward(sc, cam)
+    assert out["num_pairs"] == b.num_pairs
+    assert np.array_equal(out["n_contrib"], nc)
+    assert_image_close(out["image"], image)
+    assert_grads_close(out["grads"], o.backward(sc, cam, p, b, dL))
