@@ -47,8 +47,8 @@ struct fs_ctx {
     int spec_set = 0;                    // the sort launches (TS_*) the previous per-tile ordering on this ctx would have
                                          // chosen (0: none): what fs_bin_sort enqueues ahead of its read-back
     uint64_t* total_dev = nullptr;   // device: totals [4]: pairs, backward records, pairs counted per tile, longest tile list
-    uint64_t* total_host = nullptr;  // pinned host block of four totals (copied from total_dev, or written by k_tile_scan)
-    uint64_t* alloc_dev = nullptr;   // device: the two counters of the counting kernel (zero between calls)
+    uint64_t* total_host = nullptr;  // pinned host block of four totals (copied from total_dev, or written by k_tile_layout)
+    uint64_t* alloc_dev = nullptr;   // device: the two counters of the counting kernel and the arrivals of the next one (zero between calls)
     bool alloc_dirty = false;        // a call failed between the kernel that adds to them and the one that clears them
     ScratchBuf tile_partial;         // double [5, tiles]: per-tile sums of the fused forward pass
     ScratchBuf pair_bits;            // the record of the forward passes for the count pass (score_record_at)
@@ -278,8 +278,8 @@ int fs_create(fs_ctx** out, int device, void* hip_stream, const fs_config* cfg)
         fs_destroy(ctx);
         return FS_EHIP;
     }
-    if (hipMalloc(reinterpret_cast<void**>(&ctx->alloc_dev), 2 * sizeof(uint64_t)) != hipSuccess ||
-        hipMemset(ctx->alloc_dev, 0, 2 * sizeof(uint64_t)) != hipSuccess ||
+    if (hipMalloc(reinterpret_cast<void**>(&ctx->alloc_dev), 3 * sizeof(uint64_t)) != hipSuccess ||
+        hipMemset(ctx->alloc_dev, 0, 3 * sizeof(uint64_t)) != hipSuccess ||
         hipMalloc(reinterpret_cast<void**>(&ctx->total_dev), 4 * sizeof(uint64_t)) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&ctx->total_host), 4 * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
@@ -384,12 +384,13 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
         // enqueued ahead of the read-back)
         ProfScope prof(ctx, FS_K_EMIT);
         fs_projected none = {};
-        if (ctx->alloc_dirty) FS_HIP(launch_fill_u32(st, reinterpret_cast<uint32_t*>(ctx->alloc_dev), 0u, 4), "k_fill_u32");
+        if (ctx->alloc_dirty) FS_HIP(launch_fill_u32(st, reinterpret_cast<uint32_t*>(ctx->alloc_dev), 0u, 6), "k_fill_u32");
         ctx->alloc_dirty = true;
         FS_HIP(launch_tile_count(st, n, proj ? *proj : none, cf, cd.tiles_x, tiles, tcount_p, ttotal_p,
                                  reinterpret_cast<uint2*>(ranges_p), order_p, ctx->total_host,
                                  static_cast<uint32_t*>(cb ? ctx->rec_offsets.ptr : ctx->offsets.ptr),
-                                 cb ? static_cast<uint32_t*>(ctx->rec_counts.ptr) : nullptr, ctx->alloc_dev),
+                                 cb ? static_cast<uint32_t*>(ctx->rec_counts.ptr) : nullptr, ctx->alloc_dev,
+                                 static_cast<float*>(ctx->splats.ptr)),
                "k_tile_pairs (count)");
         ctx->alloc_dirty = false;
     } else {
@@ -423,8 +424,7 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
             spec_variants = ctx->spec_set;
             FS_HIP(launch_tile_scatter(st, n, proj ? *proj : none, cf, recs_p, cd.tiles_x, tiles, (uint32_t)cap_pairs,
                                        (uint32_t)cap_recs, reinterpret_cast<const uint2*>(ranges_p), tcount_p,
-                                       static_cast<uint64_t*>(ctx->keys[1].ptr), static_cast<float*>(ctx->splats.ptr),
-                                       static_cast<float*>(ctx->pair_grad.ptr)),
+                                       static_cast<uint64_t*>(ctx->keys[1].ptr), static_cast<float*>(ctx->pair_grad.ptr)),
                    "k_tile_pairs (placement)");
             FS_HIP(launch_tile_sorts(st, tiles, spec_variants, (uint32_t)cap_pairs, reinterpret_cast<const uint2*>(ranges_p),
                                      order_p, static_cast<const uint64_t*>(ctx->keys[1].ptr),
@@ -469,7 +469,7 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
             if (!spec_fits) {
                 FS_HIP(launch_tile_scatter(st, n, proj ? *proj : none, cf, recs_p, cd.tiles_x, tiles, (uint32_t)P,
                                            (uint32_t)NR, reinterpret_cast<const uint2*>(ranges_p), tcount_p, keys[1],
-                                           static_cast<float*>(ctx->splats.ptr), static_cast<float*>(ctx->pair_grad.ptr)),
+                                           static_cast<float*>(ctx->pair_grad.ptr)),
                        "k_tile_pairs (placement)");
             }
             FS_HIP(launch_tile_sorts(st, tiles, variants, (uint32_t)P, reinterpret_cast<const uint2*>(ranges_p), order_p,
@@ -491,7 +491,7 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
                                                 static_cast<float*>(ctx->pair_grad.ptr)),
                            "k_emit_pairs_cb");
                 else
-                    FS_HIP(launch_emit_pairs(st, n, *proj, static_cast<const uint32_t*>(ctx->offsets.ptr), cd.tiles_x,
+                    FS_HIP(launch_emit_pairs(st, n, *proj, cf, static_cast<const uint32_t*>(ctx->offsets.ptr), cd.tiles_x,
                                              keys[0], vals[0], static_cast<float*>(ctx->splats.ptr)),
                            "k_emit_pairs");
             }

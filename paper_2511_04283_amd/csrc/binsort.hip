@@ -107,6 +107,18 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_apply(const uint32_t* in,
     }
 }
 
+// The 64-byte record the render kernels gather for Gaussian i (see SPLAT_REC).
+__device__ __forceinline__ void pack_splat(float4* __restrict__ splats, int64_t i, const float2& m, const float4& co,
+                                           const float* __restrict__ rgb, uint32_t first_record, const ushort4& r, const CfgDev& cfg)
+{
+    float4* rec = splats + (size_t)i * (SPLAT_REC / 4);
+    rec[0] = make_float4(m.x, m.y, co.x, co.y);
+    rec[1] = make_float4(co.z, co.w, rgb[3 * i], rgb[3 * i + 1]);
+    rec[2] = make_float4(rgb[3 * i + 2], __uint_as_float(first_record), __uint_as_float((uint32_t)r.x | (uint32_t)r.y << 16),
+                         __uint_as_float((uint32_t)r.z | (uint32_t)r.w << 16));
+    rec[3] = support_octagon(co, cfg);
+}
+
 // One key per tile of each Gaussian's rectangle, rows then columns, starting at offsets[i].  A
 // wavefront takes 64 consecutive Gaussians; their pairs occupy one contiguous run of the output, and
 // the wavefront writes that run 64 pairs at a time (lane j of a round finds the Gaussian that owns
@@ -118,7 +130,7 @@ __global__ __launch_bounds__(256) void k_emit_pairs(int64_t n, const ushort4* __
                                                     const float* __restrict__ depth,
                                                     const float2* __restrict__ mean2d,
                                                     const float4* __restrict__ conic_opacity,
-                                                    const float* __restrict__ rgb,
+                                                    const float* __restrict__ rgb, CfgDev cfg,
                                                     const uint32_t* __restrict__ offsets, int tiles_x,
                                                     uint64_t* __restrict__ keys, uint32_t* __restrict__ vals,
                                                     float4* __restrict__ splats)
@@ -134,11 +146,7 @@ __global__ __launch_bounds__(256) void k_emit_pairs(int64_t n, const ushort4* __
     if (cnt) {
         const float2 m = mean2d[i];
         const float4 co = conic_opacity[i];
-        float4* rec = splats + (size_t)i * (SPLAT_REC / 4);
-        rec[0] = make_float4(m.x, m.y, co.x, co.y);
-        rec[1] = make_float4(co.z, co.w, rgb[3 * i], rgb[3 * i + 1]);
-        rec[2] = make_float4(rgb[3 * i + 2], __uint_as_float(off), __uint_as_float((uint32_t)r.x | (uint32_t)r.y << 16),
-                             __uint_as_float((uint32_t)r.z | (uint32_t)r.w << 16));
+        pack_splat(splats, i, m, co, rgb, off, r, cfg);
     }
     const uint32_t inc = wave_inclusive_scan(cnt);
     const uint32_t excl = inc - cnt;                       // this lane's first slot within the wave's run
@@ -211,11 +219,7 @@ __global__ __launch_bounds__(256) void k_emit_pairs_cb(int64_t n, const ushort4*
         const float4 co = conic_opacity[i];
         mx = m.x; my = m.y; A = co.x; B = co.y; C = co.z;
         Q = cb_threshold(co.w, cfg);
-        float4* rec = splats + (size_t)i * (SPLAT_REC / 4);
-        rec[0] = make_float4(m.x, m.y, co.x, co.y);
-        rec[1] = make_float4(co.z, co.w, rgb[3 * i], rgb[3 * i + 1]);
-        rec[2] = make_float4(rgb[3 * i + 2], __uint_as_float(roff), __uint_as_float((uint32_t)r.x | (uint32_t)r.y << 16),
-                             __uint_as_float((uint32_t)r.z | (uint32_t)r.w << 16));
+        pack_splat(splats, i, m, co, rgb, roff, r, cfg);
     }
     const uint32_t inc = wave_inclusive_scan(cnt);
     const uint32_t excl = inc - cnt;
@@ -281,14 +285,14 @@ __global__ __launch_bounds__(256) void k_emit_pairs_cb(int64_t n, const ushort4*
 
 // Steps (1) and (2) are launched as TILE_COPIES workgroups, each keeping its own counter per tile in LDS
 // (so num_tiles * 4 bytes must fit there) and walking the same Gaussians in both steps; step (1) ends by
-// writing its counters as one row of a [TILE_COPIES, num_tiles] table, which k_tile_sum turns into each
+// writing its counters as one row of a [TILE_COPIES, num_tiles] table, which k_tile_layout turns into each
 // workgroup's start within every tile's segment, and step (2) starts from that row.  Global atomics reach
 // about 45 G/s on this chip whatever the contention; LDS atomics are an order of magnitude cheaper.
 //
 // Steps (1) and (2) walk the candidate tiles of 64 consecutive Gaussians per wavefront the way k_emit_pairs
 // does.  SCATTER = false: count[tile] += 1 per pair.  SCATTER = true: slot = first[tile] + counter[tile]++
-// (k_tile_sum has turned each copy's counter into that copy's start within the tile's segment),
-// bucket[slot] = depth_bits << 32 | index; also packs the splat records and, with
+// (k_tile_layout has turned each copy's counter into that copy's start within the tile's segment),
+// bucket[slot] = depth_bits << 32 | index; also, with
 // the Compact Box, zeroes the gradient records of the candidates that are no pairs.  In this mode `P` and `rec_limit`
 // are the numbers of words / records the buffers hold: nothing is written at or beyond them (the kernel may be
 // enqueued before the host has seen the real totals).
@@ -311,12 +315,11 @@ template <bool CB, bool SCATTER>
 __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, const ushort4* __restrict__ rect,
                                                     const float* __restrict__ depth,
                                                     const float2* __restrict__ mean2d,
-                                                    const float4* __restrict__ conic_opacity,
-                                                    const float* __restrict__ rgb, CfgDev cfg,
+                                                    const float4* __restrict__ conic_opacity, CfgDev cfg,
                                                     const uint32_t* __restrict__ rec_offsets, int tiles_x,
                                                     int num_tiles, uint32_t* __restrict__ tile_counter,
                                                     const uint2* __restrict__ ranges, uint32_t P, uint32_t rec_limit,
-                                                    uint64_t* __restrict__ bucket, float4* __restrict__ splats,
+                                                    uint64_t* __restrict__ bucket,
                                                     float4* __restrict__ pair_grad, RecAlloc ra)
 {
     extern __shared__ uint32_t s_tile[];   // this workgroup's counter per tile
@@ -376,7 +379,7 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
     const int64_t i_first = (int64_t)blockIdx.x * TILE_PAIR_THREADS + threadIdx.x;
     const int64_t round_stride = (int64_t)gridDim.x * TILE_PAIR_THREADS;
     ushort4 r_next = i_first < n ? rect[i_first] : make_ushort4(0, 0, 0, 0);
-    uint32_t roff_next = (SCATTER && i_first < n) ? rec_offsets[i_first] : 0u;
+    uint32_t roff_next = (SCATTER && CB && i_first < n) ? rec_offsets[i_first] : 0u;
     uint32_t dbits_next = (SCATTER && i_first < n) ? __float_as_uint(depth[i_first]) : 0u;
     for (int64_t i = i_first; i - lane < n; i += round_stride) {
         const bool valid = i < n;
@@ -390,22 +393,16 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
             const bool in = i2 < n;
             r_next = in ? rect[i2] : make_ushort4(0, 0, 0, 0);
             if (SCATTER) {
-                roff_next = in ? rec_offsets[i2] : 0u;
+                roff_next = CB && in ? rec_offsets[i2] : 0u;
                 dbits_next = in ? __float_as_uint(depth[i2]) : 0u;
             }
         }
         float mx = 0.f, my = 0.f, A = 1.f, B = 0.f, C = 1.f, Q = 0.f;
-        if (cnt && (CB || SCATTER)) {
+        if (CB && cnt) {
             const float2 m = mean2d[i];
             const float4 co = conic_opacity[i];
-            if (CB) { mx = m.x; my = m.y; A = co.x; B = co.y; C = co.z; Q = cb_threshold(co.w, cfg); }
-            if (SCATTER) {
-                float4* rec = splats + (size_t)i * (SPLAT_REC / 4);
-                rec[0] = make_float4(m.x, m.y, co.x, co.y);
-                rec[1] = make_float4(co.z, co.w, rgb[3 * i], rgb[3 * i + 1]);
-                rec[2] = make_float4(rgb[3 * i + 2], __uint_as_float(roff), __uint_as_float((uint32_t)r.x | (uint32_t)r.y << 16),
-                                     __uint_as_float((uint32_t)r.z | (uint32_t)r.w << 16));
-            }
+            mx = m.x; my = m.y; A = co.x; B = co.y; C = co.z;
+            Q = cb_threshold(co.w, cfg);
         }
         const uint32_t inc = wave_inclusive_scan(cnt);
         const uint32_t excl = inc - cnt;
@@ -460,52 +457,83 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
     }
 }
 
-// Per tile: its count summed over the workgroups' rows -> tile_total; each row's counter is replaced by the
-// number of the tile's pairs in the rows before it (where that workgroup's pairs start within the tile's
-// segment).  A workgroup takes 64 tiles; its wavefront g takes rows [64 g, 64 g + 64) of each.
-__global__ __launch_bounds__(64 * (TILE_COPIES / 64)) void k_tile_sum(uint32_t* __restrict__ count, int num_tiles,
-                                                                     uint32_t* __restrict__ tile_total)
+// Between steps (1) and (2), in one launch:
+//
+// The first `sum_blocks` workgroups, per tile: its count summed over the workgroups' rows; each row's counter is replaced
+// by the number of the tile's pairs in the rows before it (where that workgroup's pairs start within the tile's
+// segment).  A workgroup takes 64 tiles; its wavefront g takes rows [16 g, 16 g + 16) of each.
+//
+// Whichever of them is done last then turns the tile totals into ranges [first, last), by an exclusive scan (thread t owns
+// the consecutive tiles [t*per, t*per + per)); totals[2] = sum,
+// totals[3] = longest list (totals[0..1] come from the counting kernel's two counters); and the order in which
+// the render kernels take the tiles (longest list first, bucketed by length / 8, as k_tile_order).
+//
+// The other workgroups pack the projected splats into the records the render kernels gather (SPLAT_REC).  The placement
+// kernel did this on the way, with one workgroup per compute unit; here it has the whole chip and hides the chain of the
+// two steps above, and the records no longer drive the placement's half-filled lines out of the L2.
+// Placement, sums and scan together, before and after: 222 and 185 us at 3 M Gaussians / 10 M pairs, 18.3 and 16.8 at 4k.
+constexpr int LAYOUT_THREADS = 1024;
+constexpr int LAYOUT_WAVES = LAYOUT_THREADS / 64;
+__global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __restrict__ count, int num_tiles, int sum_blocks,
+                                                                uint32_t* __restrict__ tile_total, uint2* __restrict__ ranges,
+                                                                uint32_t* __restrict__ order, uint64_t* __restrict__ totals,
+                                                                unsigned long long* __restrict__ counters, int64_t n,
+                                                                const ushort4* __restrict__ rect, const float2* __restrict__ mean2d,
+                                                                const float4* __restrict__ conic_opacity, const float* __restrict__ rgb,
+                                                                CfgDev cfg, const uint32_t* __restrict__ rec_offsets,
+                                                                float4* __restrict__ splats)
 {
-    constexpr int GROUPS = TILE_COPIES / 64;
+    if ((int)blockIdx.x >= sum_blocks) {
+        const int64_t i = (int64_t)((int)blockIdx.x - sum_blocks) * LAYOUT_THREADS + threadIdx.x;
+        if (i >= n) return;
+        const ushort4 r = rect[i];
+        if (r.z <= r.x || r.w <= r.y) return;   // (no pair names it)
+        pack_splat(splats, i, mean2d[i], conic_opacity[i], rgb, rec_offsets[i], r, cfg);
+        return;
+    }
     // Order of the workgroups' shares within a tile's segment: workgroups are handed to the 8 XCDs in turn, so
     // those with the same index mod 8 share an L2; putting their shares next to each other lets the 8-byte words
     // they scatter into a segment fill whole lines in one L2 before they are written back.
     auto row_at = [](int pos) { return (pos % (TILE_COPIES / 8)) * 8 + pos / (TILE_COPIES / 8); };
-    __shared__ uint32_t gsum[GROUPS][64];
-    const int g = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int t = blockIdx.x * 64 + lane;
-    uint32_t part[64];
-    uint32_t sum = 0;
+    constexpr int PER_WAVE = TILE_COPIES / LAYOUT_WAVES;
+    __shared__ uint32_t gsum[LAYOUT_WAVES][64];
+    __shared__ bool s_last;
+    {
+        const int g = threadIdx.x >> 6, lane = threadIdx.x & 63;
+        const int t = blockIdx.x * 64 + lane;
+        uint32_t part[PER_WAVE];
+        uint32_t sum = 0;
 #pragma unroll
-    for (int k = 0; k < 64; k++) {
-        part[k] = t < num_tiles ? count[(size_t)row_at(g * 64 + k) * num_tiles + t] : 0u;
-        sum += part[k];
+        for (int k = 0; k < PER_WAVE; k++) {
+            part[k] = t < num_tiles ? count[(size_t)row_at(g * PER_WAVE + k) * num_tiles + t] : 0u;
+            sum += part[k];
+        }
+        gsum[g][lane] = sum;
+        __syncthreads();
+        uint32_t run = 0, all = 0;
+#pragma unroll
+        for (int q = 0; q < LAYOUT_WAVES; q++) {
+            run += q < g ? gsum[q][lane] : 0u;
+            all += gsum[q][lane];
+        }
+        if (t < num_tiles) {
+#pragma unroll
+            for (int k = 0; k < PER_WAVE; k++) {
+                count[(size_t)row_at(g * PER_WAVE + k) * num_tiles + t] = run;
+                run += part[k];
+            }
+        }
+        if (g == 0) {
+            // (another compute die may read these: they go past this one's L2, and are there before the arrival counts)
+            if (t < num_tiles) __hip_atomic_store(&tile_total[t], all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            if (lane == 0) s_last = atomicAdd(&counters[2], 1ull) + 1 == (unsigned long long)sum_blocks;
+        }
     }
-    gsum[g][lane] = sum;
     __syncthreads();
-    uint32_t run = 0, all = 0;
-#pragma unroll
-    for (int q = 0; q < GROUPS; q++) {
-        run += q < g ? gsum[q][lane] : 0u;
-        all += gsum[q][lane];
-    }
-    if (t >= num_tiles) return;
-#pragma unroll
-    for (int k = 0; k < 64; k++) {
-        count[(size_t)row_at(g * 64 + k) * num_tiles + t] = run;
-        run += part[k];
-    }
-    if (g == 0) tile_total[t] = all;
-}
+    if (!s_last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 
-// One workgroup: exclusive scan of the tile totals -> ranges [first, last); totals[2] = sum,
-// totals[3] = longest list (totals[0..1] come from the counting kernel's two counters); and the order in which
-// the render kernels take the tiles (longest list first, bucketed by length / 8, as k_tile_order).  Thread t owns the consecutive tiles [t*per, t*per + per).
-__global__ __launch_bounds__(1024) void k_tile_scan(const uint32_t* __restrict__ tile_total, int num_tiles,
-                                                    uint2* __restrict__ ranges, uint32_t* __restrict__ order,
-                                                    uint64_t* __restrict__ totals,
-                                                    unsigned long long* __restrict__ counters)
-{
     constexpr int NB = 512;
     __shared__ uint32_t wsum[16];
     __shared__ uint32_t max_s;
@@ -522,10 +550,13 @@ __global__ __launch_bounds__(1024) void k_tile_scan(const uint32_t* __restrict__
 #pragma unroll
     for (int q = 0; q < PER_MAX; q++) {
         const bool in = q < per && t0 + q < num_tiles;
-        c[q] = in ? tile_total[t0 + q] : 0u;
+        c[q] = in ? __hip_atomic_load(&tile_total[t0 + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < PER_MAX; q++) {
         v += c[q];
         mymax = max(mymax, c[q]);
-        if (in) atomicAdd(&cnt[bucket(c[q])], 1u);
+        if (q < per && t0 + q < num_tiles) atomicAdd(&cnt[bucket(c[q])], 1u);
     }
     const uint32_t inc = wave_inclusive_scan(v);
     if (lane_id() == 63) wsum[threadIdx.x >> 6] = inc;
@@ -539,14 +570,15 @@ __global__ __launch_bounds__(1024) void k_tile_scan(const uint32_t* __restrict__
         run += c[q];
     }
     if (threadIdx.x == 1023) {
-        // totals: sum of tiles_touched, backward records, pairs counted per tile, longest list; the two counters of
-        // the counting kernel start the next call at zero
+        // totals: sum of tiles_touched, backward records, pairs counted per tile, longest list; the counters of
+        // the counting kernel and the arrivals of this one start the next call at zero
         totals[0] = counters[1];
         totals[1] = counters[0];
         totals[2] = run;
         totals[3] = max_s;
         counters[0] = 0ull;
         counters[1] = 0ull;
+        counters[2] = 0ull;
     }
     // tile order: exclusive prefix over the 512 length buckets by one wavefront, then a counting placement
     if (threadIdx.x < 64) {
@@ -948,14 +980,14 @@ hipError_t launch_exclusive_scan(hipStream_t st, const uint32_t* in, uint32_t* o
     return hipGetLastError();
 }
 
-hipError_t launch_emit_pairs(hipStream_t st, int64_t n, const fs_projected& proj, const uint32_t* offsets,
+hipError_t launch_emit_pairs(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, const uint32_t* offsets,
                              int tiles_x, uint64_t* keys, uint32_t* vals, float* splats)
 {
     if (n == 0) return hipSuccess;
     hipLaunchKernelGGL(k_emit_pairs, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n,
                        reinterpret_cast<const ushort4*>(proj.rect), proj.depth,
                        reinterpret_cast<const float2*>(proj.mean2d), reinterpret_cast<const float4*>(proj.conic_opacity),
-                       proj.rgb, offsets, tiles_x, keys, vals, reinterpret_cast<float4*>(splats));
+                       proj.rgb, cfg, offsets, tiles_x, keys, vals, reinterpret_cast<float4*>(splats));
     return hipGetLastError();
 }
 
@@ -984,7 +1016,7 @@ hipError_t launch_emit_pairs_cb(hipStream_t st, int64_t n, const fs_projected& p
 hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, int tiles_x,
                              int num_tiles, uint32_t* tile_count, uint32_t* tile_total, uint2* ranges,
                              uint32_t* tile_order, uint64_t* totals, uint32_t* rec_offsets, uint32_t* rec_counts,
-                             uint64_t* counters)
+                             uint64_t* counters, float* splats)
 {
     const RecAlloc ra = {proj.tiles_touched, rec_offsets, rec_counts, reinterpret_cast<unsigned long long*>(counters)};
     {
@@ -994,23 +1026,24 @@ hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj
         const float2* m2 = reinterpret_cast<const float2*>(proj.mean2d);
         const float4* co = reinterpret_cast<const float4*>(proj.conic_opacity);
         if (cfg.compact_box)
-            hipLaunchKernelGGL((k_tile_pairs<true, false>), grid, block, lds, st, n, rect, proj.depth, m2, co, proj.rgb, cfg,
-                               nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, nullptr, ra);
+            hipLaunchKernelGGL((k_tile_pairs<true, false>), grid, block, lds, st, n, rect, proj.depth, m2, co, cfg,
+                               nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, ra);
         else
-            hipLaunchKernelGGL((k_tile_pairs<false, false>), grid, block, lds, st, n, rect, proj.depth, m2, co, proj.rgb,
-                               cfg, nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, nullptr, ra);
+            hipLaunchKernelGGL((k_tile_pairs<false, false>), grid, block, lds, st, n, rect, proj.depth, m2, co,
+                               cfg, nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, ra);
     }
-    hipLaunchKernelGGL(k_tile_sum, dim3((unsigned)((num_tiles + 63) / 64)), dim3(64 * (TILE_COPIES / 64)), 0, st, tile_count,
-                       num_tiles, tile_total);
-    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, st, tile_total, num_tiles, ranges, tile_order, totals,
-                       reinterpret_cast<unsigned long long*>(counters));
+    const int sum_blocks = (num_tiles + 63) / 64;
+    hipLaunchKernelGGL(k_tile_layout, dim3((unsigned)(sum_blocks + (n + LAYOUT_THREADS - 1) / LAYOUT_THREADS)), dim3(LAYOUT_THREADS), 0, st,
+                       tile_count, num_tiles, sum_blocks, tile_total, ranges, tile_order, totals,
+                       reinterpret_cast<unsigned long long*>(counters), n, reinterpret_cast<const ushort4*>(proj.rect),
+                       reinterpret_cast<const float2*>(proj.mean2d), reinterpret_cast<const float4*>(proj.conic_opacity), proj.rgb,
+                       cfg, rec_offsets, reinterpret_cast<float4*>(splats));
     return hipGetLastError();
 }
 
 hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg,
                                const uint32_t* rec_offsets, int tiles_x, int num_tiles, uint32_t pair_limit,
-                               uint32_t rec_limit, const uint2* ranges, uint32_t* cursor, uint64_t* bucket, float* splats,
-                               float* pair_grad)
+                               uint32_t rec_limit, const uint2* ranges, uint32_t* cursor, uint64_t* bucket, float* pair_grad)
 {
     if (n <= 0) return hipSuccess;
     const dim3 grid(TILE_COPIES), block(TILE_PAIR_THREADS);
@@ -1019,13 +1052,13 @@ hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& pr
     const float2* m2 = reinterpret_cast<const float2*>(proj.mean2d);
     const float4* co = reinterpret_cast<const float4*>(proj.conic_opacity);
     if (cfg.compact_box)
-        hipLaunchKernelGGL((k_tile_pairs<true, true>), grid, block, lds, st, n, rect, proj.depth, m2, co, proj.rgb, cfg,
+        hipLaunchKernelGGL((k_tile_pairs<true, true>), grid, block, lds, st, n, rect, proj.depth, m2, co, cfg,
                            rec_offsets, tiles_x, num_tiles, cursor, ranges, pair_limit, rec_limit, bucket,
-                           reinterpret_cast<float4*>(splats), reinterpret_cast<float4*>(pair_grad), RecAlloc{});
+                           reinterpret_cast<float4*>(pair_grad), RecAlloc{});
     else
-        hipLaunchKernelGGL((k_tile_pairs<false, true>), grid, block, lds, st, n, rect, proj.depth, m2, co, proj.rgb, cfg,
+        hipLaunchKernelGGL((k_tile_pairs<false, true>), grid, block, lds, st, n, rect, proj.depth, m2, co, cfg,
                            rec_offsets, tiles_x, num_tiles, cursor, ranges, pair_limit, rec_limit, bucket,
-                           reinterpret_cast<float4*>(splats), reinterpret_cast<float4*>(pair_grad), RecAlloc{});
+                           reinterpret_cast<float4*>(pair_grad), RecAlloc{});
     return hipGetLastError();
 }
 

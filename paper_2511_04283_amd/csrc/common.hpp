@@ -92,6 +92,38 @@ __device__ __forceinline__ bool cb_tile_hit(float mx, float my, float A, float B
     return qmin <= Q;
 }
 
+// ---- the render kernels' bound of a Gaussian's support ----------------------------------------------
+// A Gaussian can only be blended where sigma*G >= alpha_min, i.e. where q <= qg = 2 ln(sigma/alpha_min).  With
+// Sigma_2D = conic^-1, the set {q <= Q} lies within |dx| <= sqrt(Q Sigma_xx), |dy| <= sqrt(Q Sigma_yy), and between the
+// tangent lines at +-45 degrees, |dx + dy| <= sqrt(Q (Sxx + Syy + 2 Sxy)), |dx - dy| <= sqrt(Q (Sxx + Syy - 2 Sxy)) with
+// Sxy = -b/det (which trims the corners of the box for slanted, elongated Gaussians).
+// Q is taken as qg + 0.1 + e, where e bounds the rounding error of the fp32 q
+// for any pixel of a tile the Gaussian is paired with (|dx|,|dy| <= 3 sqrt(lambda_max) + 17), and the
+// half-widths get a further 0.2 % + 0.01 px (they are computed with the fast reciprocal,
+// square root and logarithm): outside the octagon the render kernels' arithmetic yields alpha < 0.96 alpha_min,
+// so dropping the pair cannot change any result.
+// Returned: the four half-widths, each with the reach of a 4x4 sub-tile's pixel centres from its centre (1.5, and 3 along
+// the diagonals) added; negative where the Gaussian is blended nowhere, huge where they come out as NaN (a degenerate conic:
+// the exact test decides).
+__device__ __forceinline__ float4 support_octagon(const float4& co /* a, b, c, sigma */, const CfgDev& cfg)
+{
+    const float ratio = co.w * __builtin_amdgcn_rcpf(cfg.alpha_min);
+    if (!(ratio >= 1.0f)) return make_float4(-1.f, -1.f, -1.f, -1.f);
+    const float det = co.x * co.z - co.y * co.y;
+    const float inv = __builtin_amdgcn_rcpf(det);
+    const float sxx = co.z * inv, syy = co.x * inv, sxy = -co.y * inv;
+    const float D = 3.0f * __builtin_amdgcn_sqrtf(sxx + syy) + 17.0f;
+    const float e = 1e-6f * (fabsf(co.x) + 2.0f * fabsf(co.y) + fabsf(co.z)) * D * D;
+    const float Q = 2.0f * __logf(ratio) + 0.1f + e;
+    const float hx = __builtin_amdgcn_sqrtf(Q * sxx) * 1.002f + 0.01f;
+    const float hy = __builtin_amdgcn_sqrtf(Q * syy) * 1.002f + 0.01f;
+    const float hu = __builtin_amdgcn_sqrtf(fmaxf(Q * (sxx + syy + 2.0f * sxy), 0.f)) * 1.002f + 0.02f;
+    const float hv = __builtin_amdgcn_sqrtf(fmaxf(Q * (sxx + syy - 2.0f * sxy), 0.f)) * 1.002f + 0.02f;
+    const float all = 3.0e38f;
+    const bool box = hx == hx && hy == hy, diagonals = hu == hu && hv == hv;
+    return make_float4(box ? hx + 1.5f : all, box ? hy + 1.5f : all, diagonals ? hu + 3.0f : all, diagonals ? hv + 3.0f : all);
+}
+
 // ---- wavefront helpers ----------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63u; }
 
@@ -218,9 +250,10 @@ size_t scan_tmp_bytes(int64_t n);
 hipError_t launch_exclusive_scan(hipStream_t st, const uint32_t* in, uint32_t* out, int64_t n, void* tmp,
                                  uint64_t* total_dev);
 
-// Splat record (SPLAT_REC floats = 64 bytes, one per Gaussian): mx my a b | c sigma r g | b offset rect01 rect23 | unused
+// Splat record (SPLAT_REC floats = 64 bytes, one per Gaussian): mx my a b | c sigma r g | b offset rect01 rect23 | the
+// half-widths of support_octagon (formed here once: the render kernels would form them for every pair)
 constexpr int SPLAT_REC = 16;
-hipError_t launch_emit_pairs(hipStream_t st, int64_t n, const fs_projected& proj, const uint32_t* offsets,
+hipError_t launch_emit_pairs(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, const uint32_t* offsets,
                              int tiles_x, uint64_t* keys, uint32_t* vals, float* splats);
 // Compact Box: rec_counts[i] = tiles in Gaussian i's box (the candidates of the ellipse test)
 hipError_t launch_rect_area(hipStream_t st, int64_t n, const uint16_t* rect, uint32_t* rec_counts);
@@ -237,7 +270,7 @@ hipError_t launch_emit_pairs_cb(hipStream_t st, int64_t n, const fs_projected& p
 // launch_tile_count into each copy's start within its tile (the `cursor` of launch_tile_scatter_sort).
 // launch_tile_count also gives every Gaussian the place of its backward records (rec_offsets [n]: disjoint,
 // contiguous per Gaussian, not ordered by index; rec_counts [n], may be null: the area of its rectangle) from
-// `counters` (two uint64 that are zero at the start and are left zero), and writes
+// `counters` (three uint64 that are zero at the start and are left zero), packs the splat records, and writes
 // totals [4] = {sum of proj.tiles_touched, records handed out, pairs counted per tile, longest list}.
 constexpr int TILE_COPIES = 256;        // workgroups of the counting / placement kernels, each with its own counters (a multiple of 64)
 constexpr int TILE_PAIR_THREADS = 1024;
@@ -250,14 +283,13 @@ constexpr int TILE_SORT_HUGE = 16384;  // ... with 144 KB (a compute unit of thi
 hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, int tiles_x,
                              int num_tiles, uint32_t* tile_count, uint32_t* tile_total, uint2* ranges,
                              uint32_t* tile_order, uint64_t* totals, uint32_t* rec_offsets, uint32_t* rec_counts,
-                             uint64_t* counters);
+                             uint64_t* counters, float* splats);
 // Placement and the per-tile sorts.  pair_limit / rec_limit: how many words / gradient records the buffers hold; the
 // kernels write nothing at or beyond them and leave alone a segment that reaches beyond pair_limit, so they may be
 // enqueued before the host knows the totals.
 hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg,
                                const uint32_t* rec_offsets, int tiles_x, int num_tiles, uint32_t pair_limit,
-                               uint32_t rec_limit, const uint2* ranges, uint32_t* cursor, uint64_t* bucket, float* splats,
-                               float* pair_grad);
+                               uint32_t rec_limit, const uint2* ranges, uint32_t* cursor, uint64_t* bucket, float* pair_grad);
 // The sort launches, by the list lengths they take: (0, SMALL], (SMALL, MID], (MID, MAX], (MAX, HUGE], and
 // (SMALL, MAX] in one launch (TS_MIDMAX, instead of TS_MID and TS_MAX).  The lists between SMALL and MID get a launch of
 // their own (four of its workgroups fit a compute unit, two of the MAX kind) when the lists are long throughout

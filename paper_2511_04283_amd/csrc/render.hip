@@ -131,20 +131,13 @@ __device__ __forceinline__ uint32_t dpp_shr_add(uint32_t v)
     return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
 }
 
-// Loads entries [first, first+m) of the tile's list into `s` (slot t <- entry first+t) and builds
+// Loads m entries of the tile's list into `s` (slot t <- Gaussian g of thread t) and builds
 // the 16 per-sub-tile slot lists.  Returns the length of the list of the calling lane's sub-tile.
 // Contains one workgroup barrier; every thread of the workgroup must call it, after a barrier behind the previous
 // batch's walk.  A wavefront's own four lists are complete when it returns (the others' only behind another barrier).
 //
-// Box of a Gaussian: it can only be blended where sigma*G >= alpha_min, i.e. where
-// q <= qg = 2 ln(sigma/alpha_min).  With
-// Sigma_2D = conic^-1, the set {q <= Q} lies within |dx| <= sqrt(Q Sigma_xx), |dy| <= sqrt(Q Sigma_yy).
-// Q is taken as qg + 0.1 + e, where e bounds the rounding error of the fp32 q
-// for any pixel of a tile the Gaussian is paired with (|dx|,|dy| <= 3 sqrt(lambda_max) + 17), and the
-// half-widths get a further 0.2 % + 0.01 px (the box itself is computed with the fast reciprocal,
-// square root and logarithm): outside the box the pinned arithmetic yields alpha < 0.96 alpha_min,
-// so dropping the pair cannot change any result.  The same argument gives
-// bounds on dx + dy and dx - dy (an octagon around the support).
+// Which sub-tiles may blend a Gaussian: those whose centres lie within its support octagon, widened by a sub-tile's reach
+// (support_octagon; part of the splat record).
 //
 // Lists: every thread leaves its entry's 16 sub-tile bits in LDS; then the 16 lanes that own a sub-tile in the render
 // loops gather that sub-tile's bit of 16 slots each and expand them into slot numbers with a prefix sum over the row.
@@ -154,14 +147,12 @@ __device__ __forceinline__ uint32_t dpp_shr_add(uint32_t v)
 // gradient record (where the pair was emitted before the sort: offset + place in the rectangle).
 template <int ID_MODE, bool REVERSED = false, bool WITH_RGB, int N>
 __device__ __forceinline__ int stage_batch(Stage<WITH_RGB, N>& s, uint32_t* s_id, const CamDev& cam,
-                                           const CfgDev& cfg, int tile, const uint32_t* __restrict__ gauss_sorted,
-                                           const float4* __restrict__ splats, uint32_t first, int m, int row_end = N)
+                                           int tile, const float4* __restrict__ splats, uint32_t g, int m, int row_end = N)
 {
     const int t = threadIdx.x;
     const int swave = t >> 6, lane = t & 63;
     uint32_t sub_mask = 0;  // bit (wave*4 + row) of every sub-tile the box meets
     if (t < m) {
-        const uint32_t g = gauss_sorted[first + t];
         const float4* rec = splats + (size_t)g * (SPLAT_REC / 4);  // one 64-byte line
         const float4 r0 = rec[0], r1 = rec[1], r2 = rec[2];
         const float2 xy = make_float2(r0.x, r0.y);
@@ -177,46 +168,27 @@ __device__ __forceinline__ int stage_batch(Stage<WITH_RGB, N>& s, uint32_t* s_id
                                  ((uint32_t)(tile % cam.tiles_x) - x0));
         }
         if (WITH_RGB) s.r2[t] = make_float4(r1.z, r1.w, r2.x, id);
-        const float ratio = co.w * __builtin_amdgcn_rcpf(cfg.alpha_min);
-        if (ratio >= 1.0f) {
-            const float det = co.x * co.z - co.y * co.y;
-            const float inv = __builtin_amdgcn_rcpf(det);
-            const float sxx = co.z * inv, syy = co.x * inv;
-            const float D = 3.0f * __builtin_amdgcn_sqrtf(sxx + syy) + 17.0f;
-            const float e = 1e-6f * (fabsf(co.x) + 2.0f * fabsf(co.y) + fabsf(co.z)) * D * D;
-            const float Q = 2.0f * __logf(ratio) + 0.1f + e;
-            const float hx = __builtin_amdgcn_sqrtf(Q * sxx) * 1.002f + 0.01f;
-            const float hy = __builtin_amdgcn_sqrtf(Q * syy) * 1.002f + 0.01f;
-            // sub-tile column k has its centre at +4k+2 from the tile origin; pixel centres reach 1.5 from it
-            const float ox = xy.x - (float)((tile % cam.tiles_x) * TILE), oy = xy.y - (float)((tile / cam.tiles_x) * TILE);
-            // Every test below concerns a whole family of sub-tiles at once (a column, a line, a diagonal), so each is
-            // made once and switches on the family's 16-bit pattern (SubTiles::col ...): 22 tests and a few ANDs instead
-            // of four tests per sub-tile.
-            uint32_t colm = 0, rowm = 0;
+        const float4 reach = rec[3];
+        // sub-tile column k has its centre at +4k+2 from the tile origin
+        const float ox = xy.x - (float)((tile % cam.tiles_x) * TILE), oy = xy.y - (float)((tile / cam.tiles_x) * TILE);
+        // Every test below concerns a whole family of sub-tiles at once (a column, a line, a diagonal), so each is
+        // made once and switches on the family's 16-bit pattern (SubTiles::col ...): 22 tests and a few ANDs instead
+        // of four tests per sub-tile.
+        uint32_t colm = 0, rowm = 0;
 #pragma unroll
-            for (int k = 0; k < 4; k++) {
-                colm |= (fabsf(ox - (float)(4 * k + 2)) <= hx + 1.5f) ? SubTiles::col(k) : 0u;
-                rowm |= (fabsf(oy - (float)(4 * k + 2)) <= hy + 1.5f) ? SubTiles::line(k) : 0u;
-            }
-            // NaN half-widths (degenerate conic) keep the Gaussian everywhere: the exact test decides
-            if (!(hx == hx) || !(hy == hy)) { colm = 0xffffu; rowm = 0xffffu; }
-            // The same set also lies between the tangent lines at +-45 degrees: |dx + dy| <= sqrt(Q (Sxx + Syy + 2 Sxy)),
-            // |dx - dy| <= sqrt(Q (Sxx + Syy - 2 Sxy)) with Sxy = -b/det; a sub-tile's pixel centres reach 3 from
-            // its centre in these sums.  This trims the corners of the box for slanted, elongated Gaussians.
-            const float sxy = -co.y * inv;
-            const float hu = __builtin_amdgcn_sqrtf(fmaxf(Q * (sxx + syy + 2.0f * sxy), 0.f)) * 1.002f + 0.02f;
-            const float hv = __builtin_amdgcn_sqrtf(fmaxf(Q * (sxx + syy - 2.0f * sxy), 0.f)) * 1.002f + 0.02f;
-            const float su = ox + oy, sv = ox - oy;
-            const bool nan8 = !(hu == hu) || !(hv == hv);
-            // the sub-tile in column kx, line ky has its centre at sum 4 (kx + ky) + 4 and difference 4 (kx - ky)
-            uint32_t summ = 0, difm = 0;
-#pragma unroll
-            for (int d = 0; d < 7; d++) {
-                summ |= (fabsf(su - (float)(4 * d + 4)) <= hu + 3.0f) ? SubTiles::sum(d) : 0u;
-                difm |= (fabsf(sv - (float)(4 * (d - 3))) <= hv + 3.0f) ? SubTiles::dif(d - 3) : 0u;
-            }
-            sub_mask = colm & rowm & (nan8 ? 0xffffu : (summ & difm));
+        for (int k = 0; k < 4; k++) {
+            colm |= (fabsf(ox - (float)(4 * k + 2)) <= reach.x) ? SubTiles::col(k) : 0u;
+            rowm |= (fabsf(oy - (float)(4 * k + 2)) <= reach.y) ? SubTiles::line(k) : 0u;
         }
+        const float su = ox + oy, sv = ox - oy;
+        // the sub-tile in column kx, line ky has its centre at sum 4 (kx + ky) + 4 and difference 4 (kx - ky)
+        uint32_t summ = 0, difm = 0;
+#pragma unroll
+        for (int d = 0; d < 7; d++) {
+            summ |= (fabsf(su - (float)(4 * d + 4)) <= reach.z) ? SubTiles::sum(d) : 0u;
+            difm |= (fabsf(sv - (float)(4 * (d - 3))) <= reach.w) ? SubTiles::dif(d - 3) : 0u;
+        }
+        sub_mask = colm & rowm & summ & difm;
     }
     reinterpret_cast<uint16_t*>(s.sub)[s.sub_place(t)] = (uint16_t)sub_mask;
     constexpr uint32_t PAD = 0x01010101u * (uint32_t)(N - 1);
@@ -339,9 +311,14 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
     // BITS: row t of s_pb is zeroed and written out by thread t alone; the other wavefronts set bits in it between
     // a batch's staging barriers and the barrier at the top of the next batch
     const float hit_above = cfg.score_mode == FS_SCORE_ALPHA ? 0.0f : cfg.alpha_min;
-    int pending = -1, pending_m = 0;  // the batch whose bits are in s_pb and not yet in memory (uniform)
+    int pending_m = 0;  // length of the batch whose bits are in s_pb and not yet in memory (uniform; 0: none)
     if (BITS && threadIdx.x == 0) s_rows = 0;   // (the first use lies behind the barrier at the top of the second batch)
-    auto write_bits = [&](int first, int count) {
+    auto entry = [&](int start) {   // the Gaussian of this thread's slot of the batch that starts there
+        const int i = start + (int)threadIdx.x;
+        return i < total && threadIdx.x < BATCH ? gauss_sorted[range.x + i] : 0u;
+    };
+    uint32_t g_next = entry(0), g_here = 0;
+    auto write_bits = [&](int count) {
         // A pair that is counted nowhere (at 500k Gaussians half of them: the rectangle's corners, entries behind the
         // last blended one) leaves nothing.  The others' rows are packed at the start of the tile's segment: a
         // wavefront reserves as many places as it has rows with one LDS atomic, so the order of the rows within the
@@ -365,15 +342,15 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
                 // other arrays from the caches)
                 nt_store(lo, record.rows + at * 2);
                 nt_store(hi, record.rows + at * 2 + 1);
-                record.row_gauss[at] = gauss_sorted[(size_t)range.x + first + threadIdx.x];
+                record.row_gauss[at] = g_here;
             }
         }
     };
     for (int start = 0; start < total; start += BATCH) {
         const int alive = __syncthreads_or(done != ~0ull);
-        if (BITS && pending >= 0) {
-            write_bits(pending, pending_m);
-            pending = -1;
+        if (BITS && pending_m > 0) {
+            write_bits(pending_m);
+            pending_m = 0;
         }
         if (alive == 0) break;
         const int m = min(BATCH, total - start);
@@ -381,10 +358,11 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
             uint4* row = reinterpret_cast<uint4*>(s_pb[threadIdx.x]);
             row[0] = make_uint4(0u, 0u, 0u, 0u);
             row[1] = make_uint4(0u, 0u, 0u, 0u);
-            pending = start;
             pending_m = m;
         }
-        const int mine = stage_batch<0>(s, nullptr, cam, cfg, tile, gauss_sorted, splats, range.x + start, m);
+        const int mine = stage_batch<0>(s, nullptr, cam, tile, splats, g_next, m);
+        if (BITS) g_here = g_next;
+        g_next = entry(start + BATCH);   // (its latency passes during the walk)
         // a row whose 16 pixels have all finished does not lengthen the wavefront's loop
         const bool row_alive = ((~done >> (threadIdx.x & 48)) & 0xffffull) != 0;
         const int longest = wave_max_of_rows(row_alive ? mine : 0);
@@ -435,9 +413,9 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
         last = lastk >= 0 ? (uint32_t)(start + s.slot(sub, lastk) + 1) : last;
     }
     if (BITS) {
-        if (pending >= 0) {
+        if (pending_m > 0) {
             __syncthreads();
-            write_bits(pending, pending_m);
+            write_bits(pending_m);
         }
         // (pairs the loop never reached -- every pixel had finished -- are blended nowhere and leave no row)
         __syncthreads();
@@ -624,7 +602,13 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
     const int total = s_max;  // entries at positions >= total are blended by no pixel of the tile
 
     // batches from the back: batch b covers positions [b*B, min(total,(b+1)*B))
-    for (int start = ((total - 1) / B) * B; start >= 0 && total > 0; start -= B) {
+    const int final_start = total > 0 ? ((total - 1) / B) * B : -1;
+    auto entry = [&](int start) {   // the Gaussian of this thread's slot of the batch that starts there
+        const int i = start + (int)threadIdx.x;
+        return start >= 0 && i < total && threadIdx.x < B ? gauss_sorted[range.x + i] : 0u;
+    };
+    uint32_t g_next = entry(final_start);
+    for (int start = final_start; start >= 0; start -= B) {
         const int m = min(B, total - start);
         __syncthreads();  // the previous batch's flush has read s_acc / s.r2
         if ((int)threadIdx.x < N) {
@@ -632,7 +616,8 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
             for (int k = 0; k < NV; k++) s_acc[threadIdx.x][k] = (acc_t)0;
         }
         // (entries behind a row's furthest one are left out of its list)
-        const int mine = stage_batch<2, true>(s, nullptr, cam, cfg, tile, gauss_sorted, splats, range.x + start, m, row_last - start);
+        const int mine = stage_batch<2, true>(s, nullptr, cam, tile, splats, g_next, m, row_last - start);
+        g_next = entry(start - B);   // (its latency passes during the walk)
         const int longest = wave_max_of_rows(mine);
         const uint32_t last_here = (uint32_t)max(last - start, 0);   // slots below this one hold entries this pixel blended (or examined)
         for (int k = 0; k < longest; k += SPAN) {
@@ -867,7 +852,7 @@ __global__ __launch_bounds__(256) void k_render_bwd_splat(
         __syncthreads();  // the previous batch's flush has read s_acc, its walk s_qlist
 #pragma unroll
         for (int k = 0; k < NV; k++) s_acc[threadIdx.x][k] = 0.0;
-        stage_batch<2>(s, nullptr, cam, cfg, tile, gauss_sorted, splats, range.x + start, m);
+        stage_batch<2>(s, nullptr, cam, tile, splats, (int)threadIdx.x < m ? gauss_sorted[range.x + start + threadIdx.x] : 0u, m);
         // the quadrant's list: lane l looks at slots 4 l .. 4 l + 3 of the union of its four sub-tiles' masks
         uint32_t b4 = 0;
         {
@@ -1080,7 +1065,7 @@ __global__ __launch_bounds__(256) void k_score(CamDev cam, CfgDev cfg, const uin
             const int m = min(BATCH, total - start);
             __syncthreads();  // the previous batch's flush has read s_cnt / s_id
             s_cnt[threadIdx.x] = 0;
-            stage_batch<1>(s, s_id, cam, cfg, tile, gauss_sorted, splats, range.x + start, m);
+            stage_batch<1>(s, s_id, cam, tile, splats, (int)threadIdx.x < m ? gauss_sorted[range.x + start + threadIdx.x] : 0u, m);
             __syncthreads();  // (a walker follows the list of its own sub-tile, whichever wavefront made it)
             if (wave_on) {
                 const int len = start < my_last ? s.len[my_sub] : 0;
@@ -1119,8 +1104,7 @@ __global__ __launch_bounds__(256) void k_score(CamDev cam, CfgDev cfg, const uin
         const int m = min(BATCH, total - start);
         __syncthreads();  // the previous batch's flush has read s_cnt / s_id
         s_cnt[threadIdx.x] = 0;
-        const int mine = stage_batch<1>(s, s_id, cam, cfg, tile, gauss_sorted, splats,
-                                               range.x + start, m);
+        const int mine = stage_batch<1>(s, s_id, cam, tile, splats, (int)threadIdx.x < m ? gauss_sorted[range.x + start + threadIdx.x] : 0u, m);
         // a row none of whose pixels is still walking (no mask pixel, or all past their last Gaussian)
         // has nothing to count in this batch
         const uint64_t walking = __ballot(start < last);
