@@ -22,6 +22,7 @@
  *   fs_photo_loss        E = (1-lambda) L1 + lambda (1 - SSIM) and dE/dC        (Sec. 4.3 E_photo; Sec. 4.5 Eq. for L)
  *   fs_prune_score_accumulate / fs_prune_score_normalize
  *                        s_p = N(sum over views of count * E_photo)             (Sec. 4.3, Eq. for s_p)
+ *   fs_train_step        a whole training iteration as one call, gradients consumed where they are formed
  *   fs_adam_step / fs_grad_accumulate / fs_adam_interval / fs_activate / fs_activate_bwd
  *                        fused Adam update with the 32/64 schedule, parameter activations
  *                                                                               (Sec. 5.1, supplement)
@@ -432,6 +433,37 @@ int fs_activate(fs_ctx *ctx, int64_t n, const float *raw_scales, const float *ra
 int fs_activate_bwd(fs_ctx *ctx, int64_t n, const float *raw_scales, const float *raw_quats,
                     const float *raw_opacities, const float *d_scales, const float *d_quats, const float *d_opacities,
                     float *d_raw_scales, float *d_raw_quats, float *d_raw_opacities);
+
+/* ---- one training iteration on one view as a single call -------------------------------------------------
+ * The five parameter groups in this order: means [n,3], SH coefficients [n,K,3], stored scales [n,3], stored quaternions
+ * [n,4], stored opacities [n] (fs_activate gives the used ones).  All arrays 16-byte aligned, caller-owned. */
+typedef struct {
+    int64_t n;
+    int32_t sh_degree;
+    float *param[5];
+    float *m[5], *v[5];  /* Adam moments; needed when `update` is set                               */
+    float *acc[5];       /* gradient sums; needed when `sum` is set or `update` is not               */
+    float *grad_accum, *abs_accum; /* densification statistics, as fs_densify_accumulate: [n] each   */
+    uint32_t *denom;
+} fs_train_state;
+
+typedef struct {
+    float lambda;        /* weight of the SSIM term                                                 */
+    float lr[5];
+    float beta1, beta2, eps;
+    int32_t step;        /* number of this update, >= 1 (with `update`)                             */
+    int32_t sum;         /* add the gradients to acc; an update then takes and clears acc           */
+    int32_t update;      /* apply an Adam update; without it the gradients only join acc            */
+} fs_train_params;
+
+/* fs_activate, fs_preprocess, fs_bin_sort, fs_render_fwd, fs_photo_loss, fs_render_bwd with the absolute gradient,
+ * fs_densify_accumulate, fs_activate_bwd and fs_grad_accumulate / fs_adam_step of the five groups, with the same results; the
+ * image, the projected splats and the gradients are not handed out.  target: [3,H,W] on the device.  out3: three
+ * HOST doubles {L1, SSIM, E}: the call returns once these are known; the rest of its work is enqueued on the ctx's
+ * stream then, like that of every other call.  bins of earlier fs_bin_sort calls become invalid.
+ * Errors: as the calls named. */
+int fs_train_step(fs_ctx *ctx, const fs_train_state *state, const fs_camera *cam, const float *target,
+                  const fs_train_params *params, double *out3);
 
 /* Used -> stored parameters, the inverse of fs_activate for scale and opacity: raw_scale = ln(scale),
  * raw_opacity = ln(o / (1 - o)) with o = the opacity limited to [lo, hi], 0 < lo <= hi < 1 (an opacity of exactly

@@ -30,7 +30,7 @@ EXPORTS = ("fs_default_config", "fs_create", "fs_destroy", "fs_last_error", "fs_
            "fs_photo_loss", "fs_prune_score_accumulate", "fs_prune_score_normalize",
            "fs_densify_accumulate", "fs_select", "fs_compact", "fs_gather_rows",
            "fs_combine_masks", "fs_counts_add", "fs_split_children", "fs_sample_by_score", "fs_activate_inv",
-           "fs_adam_step", "fs_grad_accumulate", "fs_adam_interval", "fs_activate", "fs_activate_bwd",
+           "fs_adam_step", "fs_grad_accumulate", "fs_adam_interval", "fs_activate", "fs_activate_bwd", "fs_train_step",
            "fs_profile_enable", "fs_profile_read", "fs_measure_peaks")
 KERNEL_GROUPS = ("preprocess", "scan", "emit_pairs", "order_pairs", "tile_ranges", "render_fwd", "l1_grad", "photo_loss",
                  "render_bwd", "preprocess_bwd", "error_mask", "score")
@@ -78,6 +78,17 @@ class fs_grads(ctypes.Structure):
     _fields_ = [("dmeans", ctypes.c_void_p), ("dscales", ctypes.c_void_p), ("dquats", ctypes.c_void_p),
                 ("dopacities", ctypes.c_void_p), ("dsh", ctypes.c_void_p), ("dmean2d", ctypes.c_void_p),
                 ("dconic", ctypes.c_void_p), ("drgb", ctypes.c_void_p), ("dmean2d_abs", ctypes.c_void_p)]
+
+
+class fs_train_state(ctypes.Structure):
+    _fields_ = [("n", ctypes.c_int64), ("sh_degree", ctypes.c_int32), ("param", ctypes.c_void_p * 5), ("m", ctypes.c_void_p * 5),
+                ("v", ctypes.c_void_p * 5), ("acc", ctypes.c_void_p * 5), ("grad_accum", ctypes.c_void_p),
+                ("abs_accum", ctypes.c_void_p), ("denom", ctypes.c_void_p)]
+
+
+class fs_train_params(ctypes.Structure):
+    _fields_ = [("lam", ctypes.c_float), ("lr", ctypes.c_float * 5), ("beta1", ctypes.c_float), ("beta2", ctypes.c_float),
+                ("eps", ctypes.c_float), ("step", ctypes.c_int32), ("sum", ctypes.c_int32), ("update", ctypes.c_int32)]
 
 
 _lib = None
@@ -131,6 +142,7 @@ def load_library() -> ctypes.CDLL:
     lib.fs_adam_interval.argtypes = [i32]
     lib.fs_activate.argtypes = [vp, i64, vp, vp, vp, vp, vp, vp]
     lib.fs_activate_bwd.argtypes = [vp, i64, vp, vp, vp, vp, vp, vp, vp, vp, vp]
+    lib.fs_train_step.argtypes = [vp, P(fs_train_state), P(fs_camera), vp, P(fs_train_params), P(ctypes.c_double)]
     lib.fs_combine_masks.argtypes = [vp, i64, vp, vp, vp, vp, vp, vp]
     lib.fs_counts_add.argtypes = [vp, vp, vp, i64]
     lib.fs_split_children.argtypes = [vp, vp, vp, vp, vp, i64, vp, f32, vp, vp]
@@ -159,8 +171,8 @@ def make_camera(cam) -> fs_camera:
     c = fs_camera()
     c.width, c.height = int(cam.width), int(cam.height)
     c.fx, c.fy, c.cx, c.cy = float(cam.fx), float(cam.fy), float(cam.cx), float(cam.cy)
-    c.R = (ctypes.c_float * 9)(*[float(x) for x in np.asarray(cam.R, dtype=np.float32).reshape(9)])
-    c.t = (ctypes.c_float * 3)(*[float(x) for x in np.asarray(cam.t, dtype=np.float32).reshape(3)])
+    c.R = (ctypes.c_float * 9)(*np.asarray(cam.R, dtype=np.float32).reshape(9).tolist())
+    c.t = (ctypes.c_float * 3)(*np.asarray(cam.t, dtype=np.float32).reshape(3).tolist())
     return c
 
 
@@ -498,6 +510,29 @@ class Context:
                                              _ptr(d_scales), _ptr(d_quats), _ptr(d_opacities), _ptr(outs[0]), _ptr(outs[1]),
                                              _ptr(outs[2])), "fs_activate_bwd")
         return outs
+
+    def fs_train_step(self, cam: fs_camera, target, sh_degree, params, m, v, acc, grad_accum, abs_accum, denom, lr, lam=0.2,
+                      beta1=0.9, beta2=0.999, eps=1e-15, step=1, sum=False, update=True):
+        """One training iteration in place.  params, m, v, acc and lr: the five groups (means, sh, raw scales, raw
+        quaternions, raw opacities).  Returns (L1, SSIM, E) as soon as they are known."""
+        n, K = int(params[4].shape[0]), (int(sh_degree) + 1) ** 2
+        _chk(target, torch.float32, (3, cam.height, cam.width), "target")
+        shapes = ((n, 3), (n, K, 3), (n, 3), (n, 4), (n,))
+        t = fs_train_state()
+        t.n, t.sh_degree = n, int(sh_degree)
+        for group, name in ((params, "param"), (m, "m"), (v, "v"), (acc, "acc")):
+            out = getattr(t, name)
+            for k in range(5):
+                out[k] = _chk(group[k], torch.float32, shapes[k], name).data_ptr()
+        t.grad_accum = _chk(grad_accum, torch.float32, (n,), "grad_accum").data_ptr()
+        t.abs_accum = _chk(abs_accum, torch.float32, (n,), "abs_accum").data_ptr()
+        t.denom = _chk(denom, torch.int32, (n,), "denom").data_ptr()
+        prm = fs_train_params(float(lam), (ctypes.c_float * 5)(*lr), float(beta1), float(beta2), float(eps), int(step),
+                              int(bool(sum)), int(bool(update)))
+        out3 = (ctypes.c_double * 3)()
+        self._check(self.lib.fs_train_step(self.handle, ctypes.byref(t), ctypes.byref(cam), _ptr(target), ctypes.byref(prm), out3),
+                    "fs_train_step")
+        return out3[0], out3[1], out3[2]
 
     def fs_densify_accumulate(self, dmean2d, dmean2d_abs, tiles_touched, grad_accum, abs_accum, denom):
         n = int(dmean2d.shape[0])

@@ -50,6 +50,10 @@ struct fs_ctx {
     uint64_t* total_host = nullptr;  // pinned host block of four totals (copied from total_dev, or written by k_tile_layout)
     uint64_t* alloc_dev = nullptr;   // device: the two counters of the counting kernel and the arrivals of the next one (zero between calls)
     bool alloc_dirty = false;        // a call failed between the kernel that adds to them and the one that clears them
+    ScratchBuf train_proj;           // fs_train_step: the projected splats of its view ...
+    ScratchBuf train_frame;          // ... its image, dL/dimage, final_T and n_contrib
+    double* loss_host = nullptr;     // pinned host block for its loss (three doubles, written by k_photo_final)
+    hipEvent_t loss_event = nullptr; // recorded behind that kernel
     ScratchBuf tile_partial;         // double [5, tiles]: per-tile sums of the fused forward pass
     ScratchBuf pair_bits;            // the record of the forward passes for the count pass (score_record_at)
     ScratchBuf rec_valid;            // uint8 [records]: 1 where k_render_bwd left a gradient record; k_preprocess_bwd puts
@@ -220,6 +224,29 @@ bool proj_ok(const fs_projected* p)
 // bins of an earlier fs_bin_sort (or of another ctx) point at memory that has been reused since
 bool bins_stale(const fs_ctx* ctx, const fs_bins* bins) { return bins->generation != ctx->generation || ctx->generation == 0; }
 
+// sparse records pay where the lists are long (most of their pairs receive nothing)
+bool sparse_records(const fs_ctx* ctx, const fs_bins* bins, int tiles)
+{
+    return ctx->record_mode == FS_RECORDS_SPARSE ||
+           (ctx->record_mode == FS_RECORDS_AUTO && bins->num_pairs >= (int64_t)320 * tiles);
+}
+
+// The backward pass's per-pair records and, where they are sparse, one flag per record place, all zeros here (a fresh or
+// left-over array is cleared first); the caller clears rec_valid_dirty when k_preprocess_bwd is enqueued.
+int record_buffers(fs_ctx* ctx, const fs_bins* bins, int tiles)
+{
+    FS_TRY(ensure(ctx, ctx->pair_grad, (size_t)(bins->num_records ? bins->num_records : 1) * PAIR_REC * sizeof(float),
+                  "pair gradients"));
+    if (!sparse_records(ctx, bins, tiles)) return FS_OK;
+    FS_TRY(ensure(ctx, ctx->rec_valid, ((size_t)(bins->num_records ? bins->num_records : 1) + 3) / 4 * 4, "record flags"));
+    if (ctx->rec_valid_zeroed != ctx->rec_valid.cap || ctx->rec_valid_dirty) {
+        FS_HIP(launch_fill_u32(ctx->stream, static_cast<uint32_t*>(ctx->rec_valid.ptr), 0u, (int64_t)(ctx->rec_valid.cap / 4)), "k_fill_u32");
+        ctx->rec_valid_zeroed = ctx->rec_valid.cap;
+    }
+    ctx->rec_valid_dirty = true;
+    return FS_OK;
+}
+
 // the record in ctx->pair_bits now describes the forward pass over these bins
 void note_bits(fs_ctx* ctx, const fs_bins* bins, int tiles)
 {
@@ -273,6 +300,12 @@ int fs_create(fs_ctx** out, int device, void* hip_stream, const fs_config* cfg)
         fs_destroy(ctx);
         return FS_EHIP;
     }
+    if (hipEventCreateWithFlags(&ctx->loss_event, hipEventDisableTiming) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&ctx->loss_host), 3 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        fs_destroy(ctx);
+        return FS_EHIP;
+    }
     if (noalloc_setup(device) != hipSuccess) {
         (void)hipGetLastError();
         fs_destroy(ctx);
@@ -298,6 +331,7 @@ void fs_destroy(fs_ctx* ctx)
     ScratchBuf* all[] = {&ctx->offsets, &ctx->scan_tmp, &ctx->keys[0], &ctx->keys[1], &ctx->vals[0], &ctx->vals[1],
                          &ctx->hist, &ctx->ranges, &ctx->pair_grad, &ctx->splats, &ctx->rec_counts, &ctx->rec_offsets,
                          &ctx->err_map, &ctx->ssim_maps, &ctx->partial, &ctx->tile_partial, &ctx->pair_bits, &ctx->rec_valid,
+                         &ctx->train_proj, &ctx->train_frame,
                          &ctx->compact_pos, &ctx->compact_scan, &ctx->sel_keys[0], &ctx->sel_keys[1], &ctx->sel_vals[0],
                          &ctx->sel_vals[1], &ctx->sel_hist};
     for (ScratchBuf* b : all)
@@ -306,6 +340,8 @@ void fs_destroy(fs_ctx* ctx)
     if (ctx->alloc_dev) (void)hipFree(ctx->alloc_dev);
     if (ctx->total_host) (void)hipHostFree(ctx->total_host);
     if (ctx->totals_event) (void)hipEventDestroy(ctx->totals_event);
+    if (ctx->loss_event) (void)hipEventDestroy(ctx->loss_event);
+    if (ctx->loss_host) (void)hipHostFree(ctx->loss_host);
     for (auto& v : ctx->prof_pending)
         for (auto& pr : v) { (void)hipEventDestroy(pr.first); (void)hipEventDestroy(pr.second); }
     for (hipEvent_t e : ctx->prof_free) (void)hipEventDestroy(e);
@@ -325,7 +361,7 @@ int fs_preprocess(fs_ctx* ctx, const fs_gaussians* g, const fs_camera* cam, fs_p
     if (g->n >= (int64_t)1 << 31) return fail(ctx, FS_ECAPACITY, "fs_preprocess: n does not fit 31 bits");
     FS_HIP(hipSetDevice(ctx->device), "hipSetDevice");
     ProfScope prof(ctx, FS_K_PREPROCESS);
-    FS_HIP(launch_preprocess(ctx->stream, g->n, g->sh_degree, *g, cd, make_cfg(ctx->cfg), *out), "k_preprocess");
+    FS_HIP(launch_preprocess(ctx->stream, g->n, g->sh_degree, *g, false, cd, make_cfg(ctx->cfg), *out), "k_preprocess");
     return FS_OK;
 }
 
@@ -659,23 +695,9 @@ int fs_render_bwd(fs_ctx* ctx, const fs_gaussians* g, const fs_camera* cam, cons
     // (the records, their places and -- with the Compact Box -- the zeroed records of the candidate tiles that are
     // no pairs all live in this ctx and belong to its latest fs_bin_sort)
     if (bins_stale(ctx, bins)) return fail(ctx, FS_EINVAL, "fs_render_bwd: bins do not come from this context's latest fs_bin_sort");
-    FS_TRY(ensure(ctx, ctx->pair_grad, (size_t)(bins->num_records ? bins->num_records : 1) * PAIR_REC * sizeof(float),
-                  "pair gradients"));
-    float* pair_grad = static_cast<float*>(ctx->pair_grad.ptr);
-    // sparse records: one flag per record place, all zeros here (a fresh or left-over array is cleared first)
-    const int tiles = cd.tiles_x * cd.tiles_y;
-    const bool sparse = ctx->record_mode == FS_RECORDS_SPARSE ||
-                        (ctx->record_mode == FS_RECORDS_AUTO && bins->num_pairs >= (int64_t)320 * tiles);
-    uint8_t* rec_valid = nullptr;
-    if (sparse) {
-        FS_TRY(ensure(ctx, ctx->rec_valid, ((size_t)(bins->num_records ? bins->num_records : 1) + 3) / 4 * 4, "record flags"));
-        if (ctx->rec_valid_zeroed != ctx->rec_valid.cap || ctx->rec_valid_dirty) {
-            FS_HIP(launch_fill_u32(st, static_cast<uint32_t*>(ctx->rec_valid.ptr), 0u, (int64_t)(ctx->rec_valid.cap / 4)), "k_fill_u32");
-            ctx->rec_valid_zeroed = ctx->rec_valid.cap;
-        }
-        rec_valid = static_cast<uint8_t*>(ctx->rec_valid.ptr);
-        ctx->rec_valid_dirty = true;
-    }
+    FS_TRY(record_buffers(ctx, bins, cd.tiles_x * cd.tiles_y));
+    float* const pair_grad = static_cast<float*>(ctx->pair_grad.ptr);
+    uint8_t* const rec_valid = sparse_records(ctx, bins, cd.tiles_x * cd.tiles_y) ? static_cast<uint8_t*>(ctx->rec_valid.ptr) : nullptr;
     const CfgDev cf = make_cfg(ctx->cfg);
     // a8: every pair's record is written exactly once (sparse: that of every pair that received something, and flagged)
     if (bins->num_pairs > 0) {
@@ -692,7 +714,7 @@ int fs_render_bwd(fs_ctx* ctx, const fs_gaussians* g, const fs_camera* cam, cons
                                  bins->record_counts ? bins->record_counts : proj->tiles_touched, bins->record_offsets,
                                  pair_grad, rec_valid, *out),
            "k_preprocess_bwd");
-    if (sparse) ctx->rec_valid_dirty = false;
+    ctx->rec_valid_dirty = false;
     return FS_OK;
 }
 
@@ -947,6 +969,103 @@ int fs_grad_accumulate(fs_ctx* ctx, float* acc, const float* grad, int64_t count
         return fail(ctx, FS_EINVAL, "fs_grad_accumulate: bad arguments");
     FS_HIP(hipSetDevice(ctx->device), "hipSetDevice");
     FS_HIP(launch_grad_accumulate(ctx->stream, acc, grad, count), "k_grad_accumulate");
+    return FS_OK;
+}
+
+int fs_train_step(fs_ctx* ctx, const fs_train_state* t, const fs_camera* cam, const float* target, const fs_train_params* prm,
+                  double* out3)
+{
+    if (!ctx) return FS_EINVAL;
+    CamDev cd;
+    if (!t || !prm || !target || !out3 || t->n < 0 || t->sh_degree < 0 || t->sh_degree > 3 || !make_cam(cam, cd) ||
+        !(prm->lambda >= 0.f && prm->lambda <= 1.f) || !(prm->beta1 >= 0.f && prm->beta1 < 1.f) ||
+        !(prm->beta2 >= 0.f && prm->beta2 < 1.f) || !(prm->eps >= 0.f) || (prm->update && prm->step < 1))
+        return fail(ctx, FS_EINVAL, "fs_train_step: bad arguments");
+    const int64_t n = t->n;
+    if (n >= (int64_t)1 << 31) return fail(ctx, FS_ECAPACITY, "fs_train_step: n does not fit 31 bits");
+    TrainDev dev = {};
+    for (int k = 0; k < 5; k++) {
+        dev.p[k] = t->param[k]; dev.m[k] = t->m[k]; dev.v[k] = t->v[k]; dev.acc[k] = t->acc[k];
+        const bool moments = prm->update != 0, sums = prm->sum != 0 || !moments;
+        if (n > 0 && (!dev.p[k] || (moments && (!dev.m[k] || !dev.v[k])) || (sums && !dev.acc[k])))
+            return fail(ctx, FS_EINVAL, "fs_train_step: null array");
+        if (!aligned16(dev.p[k]) || !aligned16(dev.m[k]) || !aligned16(dev.v[k]) || !aligned16(dev.acc[k]))
+            return fail(ctx, FS_EINVAL, "fs_train_step: arrays must be 16-byte aligned");
+        dev.lr[k] = prm->lr[k];
+    }
+    if (prm->update) dev.adam = adam_args(0.0f, prm->beta1, prm->beta2, prm->eps, prm->step, 1.0f);
+    dev.grad_accum = t->grad_accum; dev.abs_accum = t->abs_accum; dev.denom = t->denom;
+    if (n > 0 && (!dev.grad_accum || !dev.abs_accum || !dev.denom)) return fail(ctx, FS_EINVAL, "fs_train_step: null array");
+    FS_HIP(hipSetDevice(ctx->device), "hipSetDevice");
+    hipStream_t st = ctx->stream;
+    const CfgDev cf = make_cfg(ctx->cfg);
+    const int tiles = cd.tiles_x * cd.tiles_y;
+    const size_t hw = (size_t)cd.width * cd.height, rows = ((size_t)n + 15) / 16 * 16;
+
+    // the view's projected splats and frame live in the ctx (every sub-array on a 16-byte boundary)
+    FS_TRY(ensure(ctx, ctx->train_proj, (rows ? rows : 16) * 56, "projected splats"));
+    FS_TRY(ensure(ctx, ctx->train_frame, 8 * (hw + 3) / 4 * 4 * sizeof(float), "frame"));
+    float* const proj_base = static_cast<float*>(ctx->train_proj.ptr);
+    fs_projected proj = {};
+    proj.conic_opacity = proj_base;
+    proj.mean2d = proj_base + 4 * rows;
+    proj.rect = reinterpret_cast<uint16_t*>(proj_base + 6 * rows);
+    proj.rgb = proj_base + 8 * rows;
+    proj.depth = proj_base + 11 * rows;
+    proj.tiles_touched = reinterpret_cast<uint32_t*>(proj_base + 12 * rows);
+    proj.clamped = reinterpret_cast<uint8_t*>(proj_base + 13 * rows);
+    const size_t plane = (hw + 3) / 4 * 4;
+    float* const frame = static_cast<float*>(ctx->train_frame.ptr);
+    float *const final_T = frame, *const image = frame + 2 * plane, *const dL = image + 3 * hw;
+    uint32_t* const n_contrib = reinterpret_cast<uint32_t*>(frame + plane);
+    const fs_gaussians g = {n, t->sh_degree, t->param[0], t->param[2], t->param[3], t->param[4], t->param[1]};
+
+    {
+        ProfScope prof(ctx, FS_K_PREPROCESS);
+        FS_HIP(launch_preprocess(st, n, t->sh_degree, g, true, cd, cf, proj), "k_preprocess");
+    }
+    fs_bins bins = {};
+    FS_TRY(fs_bin_sort(ctx, &proj, cam, n, &bins));
+    {
+        ProfScope prof(ctx, FS_K_RENDER_FWD);
+        FS_HIP(launch_render_fwd(st, cd, cf, bins.tile_ranges, bins.tile_order, bins.gauss_sorted,
+                                 static_cast<const float*>(bins.splats), image, final_T, n_contrib, ScoreRecord{nullptr, nullptr, nullptr}),
+               "k_render_fwd");
+    }
+    FS_TRY(fs_photo_loss(ctx, image, target, cd.height, cd.width, prm->lambda, dL, ctx->loss_host));
+    FS_HIP(hipEventRecord(ctx->loss_event, st), "hipEventRecord");
+    if (n > 0) {
+        FS_TRY(record_buffers(ctx, &bins, tiles));
+        uint8_t* const rec_valid = sparse_records(ctx, &bins, tiles) ? static_cast<uint8_t*>(ctx->rec_valid.ptr) : nullptr;
+        float* const pair_grad = static_cast<float*>(ctx->pair_grad.ptr);
+        if (bins.num_pairs > 0) {
+            ProfScope prof(ctx, FS_K_RENDER_BWD);
+            FS_HIP(launch_render_bwd(st, cd, cf, bins.tile_ranges, bins.tile_order, bins.gauss_sorted,
+                                     static_cast<const float*>(bins.splats), final_T, n_contrib, dL, pair_grad, rec_valid, true,
+                                     ctx->per_splat_bwd),
+                   "k_render_bwd");
+        }
+        {
+            ProfScope prof(ctx, FS_K_PREPROCESS_BWD);
+            const bool at_once = prm->update && !prm->sum;
+            FS_HIP(launch_preprocess_bwd_train(st, n, t->sh_degree, g, cd, cf, proj.clamped, proj.tiles_touched,
+                                               bins.record_counts ? bins.record_counts : proj.tiles_touched, bins.record_offsets,
+                                               pair_grad, rec_valid, at_once ? BWD_UPDATE : BWD_SUM, dev),
+                   "k_preprocess_bwd");
+        }
+        ctx->rec_valid_dirty = false;
+        if (prm->update && prm->sum) {
+            const int64_t K = (int64_t)(t->sh_degree + 1) * (t->sh_degree + 1);
+            const int64_t count[5] = {3 * n, 3 * K * n, 3 * n, 4 * n, n};
+            for (int k = 0; k < 5; k++)
+                FS_HIP(launch_adam(st, dev.p[k], dev.acc[k], dev.m[k], dev.v[k], count[k], prm->lr[k], prm->beta1, prm->beta2,
+                                   prm->eps, prm->step, 1.0f, true),
+                       "k_adam");
+        }
+    }
+    // the loss is complete long before the backward pass: only it is waited for
+    FS_HIP(hipEventSynchronize(ctx->loss_event), "hipEventSynchronize");
+    for (int k = 0; k < 3; k++) out3[k] = ctx->loss_host[k];
     return FS_OK;
 }
 

@@ -124,6 +124,16 @@ __device__ __forceinline__ float4 support_octagon(const float4& co /* a, b, c, s
     return make_float4(box ? hx + 1.5f : all, box ? hy + 1.5f : all, diagonals ? hu + 3.0f : all, diagonals ? hv + 3.0f : all);
 }
 
+// A needle: a splat at least some thirty times as long as wide (the ratio of the eigenvalues of Sigma_2D, which is about
+// (a + c)^2 / det, above 1000).  What its scales and rotation receive is the small difference of large second moments, down to
+// a millionth of them, so the order in which k_render_bwd adds those up is kept for needles whatever it does for the others.
+constexpr uint32_t NEEDLE = 0x80000000u;   // (in a splat record: a bit of its first gradient record's number, which is below 2^31)
+__device__ __forceinline__ bool is_needle(const float4& co /* a, b, c, sigma */)
+{
+    const float tr = co.x + co.z;
+    return !(tr * tr <= 1000.0f * (co.x * co.z - co.y * co.y));
+}
+
 // ---- wavefront helpers ----------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63u; }
 
@@ -191,6 +201,38 @@ __device__ __forceinline__ uint32_t rect_row(uint32_t k, uint32_t w)
     return row;
 }
 
+// ---- optimiser ------------------------------------------------------------------------------------
+struct AdamArgs {
+    float lr, beta1, beta2, omb1, omb2, eps, grad_scale;
+    float inv_bc1, inv_bc2;   // 1 / (1 - beta1^t), 1 / (1 - beta2^t), computed on the host in double
+};
+AdamArgs adam_args(float lr, float beta1, float beta2, float eps, int step, float grad_scale);
+
+__device__ __forceinline__ void adam_one(float& p, float g, float& m, float& v, const AdamArgs& a, float lr)
+{
+    g = g * a.grad_scale;
+    m = a.beta1 * m + a.omb1 * g;
+    v = a.beta2 * v + a.omb2 * (g * g);
+    const float mhat = m * a.inv_bc1;
+    const float vhat = v * a.inv_bc2;
+    p = p - lr * mhat / (sqrtf(vhat) + a.eps);
+}
+
+// Used from stored parameters (fs_activate) and the chain rule through it.
+__device__ __forceinline__ float4 unit_quat(const float4& r, float& inv)
+{
+    inv = 1.0f / sqrtf(r.x * r.x + r.y * r.y + r.z * r.z + r.w * r.w);
+    return make_float4(r.x * inv, r.y * inv, r.z * inv, r.w * inv);
+}
+__device__ __forceinline__ float logistic(float raw) { return 1.0f / (1.0f + expf(-raw)); }
+__device__ __forceinline__ float4 unit_quat_bwd(const float4& r, const float4& g)
+{
+    float inv;
+    const float4 u = unit_quat(r, inv);
+    const float dot = u.x * g.x + u.y * g.y + u.z * g.z + u.w * g.w;
+    return make_float4((g.x - u.x * dot) * inv, (g.y - u.y * dot) * inv, (g.z - u.z * dot) * inv, (g.w - u.w * dot) * inv);
+}
+
 // ---- workgroup reductions in double precision (fixed tree: results do not depend on scheduling) ----------
 constexpr int RED_BLOCKS = 1024;  // partial sums per reduction (a multiple of RED_THREADS)
 constexpr int RED_THREADS = 256;
@@ -235,7 +277,8 @@ __device__ __forceinline__ double red_identity()
 }
 
 // ---- launchers (each enqueues on `st` and returns hipGetLastError()) ------------------------
-hipError_t launch_preprocess(hipStream_t st, int64_t n, int deg, const fs_gaussians& g, const CamDev& cam,
+// raw: g's scales, quaternions and opacities are the stored parameters (fs_activate is applied on the way)
+hipError_t launch_preprocess(hipStream_t st, int64_t n, int deg, const fs_gaussians& g, bool raw, const CamDev& cam,
                              const CfgDev& cfg, const fs_projected& out);
 // pair_grad: records of PAIR_REC floats (see render.hip); Gaussian i owns records
 // [rec_offsets[i], rec_offsets[i] + rec_counts[i]); touched as in fs_projected (0 = not visible)
@@ -245,12 +288,31 @@ hipError_t launch_preprocess_bwd(hipStream_t st, int64_t n, int deg, const fs_ga
                                  const uint32_t* rec_counts, const uint32_t* rec_offsets, const float* pair_grad, uint8_t* rec_valid,
                                  const fs_grads& out);
 
+// What a training iteration does with a Gaussian's gradients instead of storing them (g of launch_preprocess_bwd_train
+// holds stored parameters then): the five groups are means, sh, raw scales, raw quaternions, raw opacities.
+struct TrainDev {
+    float* p[5];        // the parameters themselves (the arrays g names), updated in place ...
+    float* m[5];        // ... with their moments (UPDATE), or null
+    float* v[5];
+    float* acc[5];      // gradient sums (SUM), or null
+    AdamArgs adam;      // (its lr is not used)
+    float lr[5];
+    float* grad_accum;  // densification statistics (fs_densify_accumulate)
+    float* abs_accum;
+    uint32_t* denom;
+};
+enum BwdOut { BWD_GRADS, BWD_UPDATE, BWD_SUM };
+hipError_t launch_preprocess_bwd_train(hipStream_t st, int64_t n, int deg, const fs_gaussians& g, const CamDev& cam,
+                                       const CfgDev& cfg, const uint8_t* clamped, const uint32_t* touched,
+                                       const uint32_t* rec_counts, const uint32_t* rec_offsets, const float* pair_grad,
+                                       uint8_t* rec_valid, BwdOut out, const TrainDev& train);
+
 // exclusive scan of n uint32 values; total (uint64) written to *total_dev. tmp: >= scan_tmp_bytes(n).
 size_t scan_tmp_bytes(int64_t n);
 hipError_t launch_exclusive_scan(hipStream_t st, const uint32_t* in, uint32_t* out, int64_t n, void* tmp,
                                  uint64_t* total_dev);
 
-// Splat record (SPLAT_REC floats = 64 bytes, one per Gaussian): mx my a b | c sigma r g | b offset rect01 rect23 | the
+// Splat record (SPLAT_REC floats = 64 bytes, one per Gaussian): mx my a b | c sigma r g | b offset(+NEEDLE) rect01 rect23 | the
 // half-widths of support_octagon (formed here once: the render kernels would form them for every pair)
 constexpr int SPLAT_REC = 16;
 hipError_t launch_emit_pairs(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, const uint32_t* offsets,

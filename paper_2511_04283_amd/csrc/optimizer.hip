@@ -8,21 +8,6 @@ namespace fs {
 
 namespace {
 
-struct AdamArgs {
-    float lr, beta1, beta2, omb1, omb2, eps, grad_scale;
-    float inv_bc1, inv_bc2;   // 1 / (1 - beta1^t), 1 / (1 - beta2^t), computed on the host in double
-};
-
-__device__ __forceinline__ void adam_one(float& p, float g, float& m, float& v, const AdamArgs& a)
-{
-    g = g * a.grad_scale;
-    m = a.beta1 * m + a.omb1 * g;
-    v = a.beta2 * v + a.omb2 * (g * g);
-    const float mhat = m * a.inv_bc1;
-    const float vhat = v * a.inv_bc2;
-    p = p - a.lr * mhat / (sqrtf(vhat) + a.eps);
-}
-
 // 28 bytes of traffic per parameter (p, g, m, v read; p, m, v written); 16-byte accesses on the aligned body.
 // When zero_grad is set the gradient is cleared in the same pass (+4 bytes), which saves the separate fill
 // that an accumulate-then-step schedule needs.
@@ -38,10 +23,10 @@ __global__ __launch_bounds__(256) void k_adam(float* __restrict__ p, float* __re
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvec; i += stride) {
         float4 pp = p4[i], mm = m4[i], vv = v4[i];
         const float4 gg = g4[i];
-        adam_one(pp.x, gg.x, mm.x, vv.x, a);
-        adam_one(pp.y, gg.y, mm.y, vv.y, a);
-        adam_one(pp.z, gg.z, mm.z, vv.z, a);
-        adam_one(pp.w, gg.w, mm.w, vv.w, a);
+        adam_one(pp.x, gg.x, mm.x, vv.x, a, a.lr);
+        adam_one(pp.y, gg.y, mm.y, vv.y, a, a.lr);
+        adam_one(pp.z, gg.z, mm.z, vv.z, a, a.lr);
+        adam_one(pp.w, gg.w, mm.w, vv.w, a, a.lr);
         p4[i] = pp; m4[i] = mm; v4[i] = vv;
         if (zero_grad) g4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
@@ -49,7 +34,7 @@ __global__ __launch_bounds__(256) void k_adam(float* __restrict__ p, float* __re
     const int64_t t = (nvec << 2) + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t < count) {
         float pp = p[t], mm = m[t], vv = v[t];
-        adam_one(pp, g[t], mm, vv, a);
+        adam_one(pp, g[t], mm, vv, a, a.lr);
         p[t] = pp; m[t] = mm; v[t] = vv;
         if (zero_grad) g[t] = 0.f;
     }
@@ -81,10 +66,9 @@ __global__ __launch_bounds__(256) void k_activate(int64_t n, const float* __rest
     if (i >= n) return;
 #pragma unroll
     for (int k = 0; k < 3; k++) s[3 * i + k] = expf(raw_s[3 * i + k]);
-    const float4 r = raw_q[i];
-    const float inv = 1.0f / sqrtf(r.x * r.x + r.y * r.y + r.z * r.z + r.w * r.w);
-    q[i] = make_float4(r.x * inv, r.y * inv, r.z * inv, r.w * inv);
-    o[i] = 1.0f / (1.0f + expf(-raw_o[i]));
+    float inv;
+    q[i] = unit_quat(raw_q[i], inv);
+    o[i] = logistic(raw_o[i]);
 }
 
 // chain rule through k_activate; gradients may be written over the incoming ones
@@ -98,14 +82,8 @@ __global__ __launch_bounds__(256) void k_activate_bwd(int64_t n, const float* __
     if (i >= n) return;
 #pragma unroll
     for (int k = 0; k < 3; k++) d_raw_s[3 * i + k] = d_s[3 * i + k] * expf(raw_s[3 * i + k]);
-    const float4 r = raw_q[i];
-    const float inv = 1.0f / sqrtf(r.x * r.x + r.y * r.y + r.z * r.z + r.w * r.w);
-    const float4 u = make_float4(r.x * inv, r.y * inv, r.z * inv, r.w * inv);
-    const float4 g = d_q[i];
-    const float dot = u.x * g.x + u.y * g.y + u.z * g.z + u.w * g.w;
-    d_raw_q[i] = make_float4((g.x - u.x * dot) * inv, (g.y - u.y * dot) * inv, (g.z - u.z * dot) * inv,
-                             (g.w - u.w * dot) * inv);
-    const float sg = 1.0f / (1.0f + expf(-raw_o[i]));
+    d_raw_q[i] = unit_quat_bwd(raw_q[i], d_q[i]);
+    const float sg = logistic(raw_o[i]);
     d_raw_o[i] = d_o[i] * sg * (1.0f - sg);
 }
 
@@ -151,15 +129,21 @@ int stream_blocks(int64_t work_items)
 
 }  // namespace
 
-hipError_t launch_adam(hipStream_t st, float* p, float* g, float* m, float* v, int64_t count, float lr, float beta1,
-                       float beta2, float eps, int step, float grad_scale, bool zero_grad)
+AdamArgs adam_args(float lr, float beta1, float beta2, float eps, int step, float grad_scale)
 {
-    if (count <= 0) return hipSuccess;
     AdamArgs a;
     a.lr = lr; a.beta1 = beta1; a.beta2 = beta2; a.omb1 = (float)(1.0 - (double)beta1);
     a.omb2 = (float)(1.0 - (double)beta2); a.eps = eps; a.grad_scale = grad_scale;
     a.inv_bc1 = (float)(1.0 / (1.0 - pow((double)beta1, (double)step)));
     a.inv_bc2 = (float)(1.0 / (1.0 - pow((double)beta2, (double)step)));
+    return a;
+}
+
+hipError_t launch_adam(hipStream_t st, float* p, float* g, float* m, float* v, int64_t count, float lr, float beta1,
+                       float beta2, float eps, int step, float grad_scale, bool zero_grad)
+{
+    if (count <= 0) return hipSuccess;
+    const AdamArgs a = adam_args(lr, beta1, beta2, eps, step, grad_scale);
     hipLaunchKernelGGL(k_adam, dim3(stream_blocks(count >> 2)), dim3(256), 0, st, p, g, m, v, count, a, zero_grad ? 1 : 0);
     return hipGetLastError();
 }

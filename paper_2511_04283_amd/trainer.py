@@ -72,37 +72,19 @@ class Trainer:
     # -- one training iteration on one view -------------------------------------------
     def step(self, cam, target) -> float:
         ctx, c = self.ctx, self.cfg
-        fcam = B.make_camera(cam)
-        g = self.gaussians()
-        proj = ctx.fs_preprocess(g, fcam)
-        bins = ctx.fs_bin_sort(proj, fcam)
-        image, fT, nc = ctx.fs_render_fwd(proj, bins, fcam)
-        out3, dL = ctx.fs_photo_loss(image, target, c.lam)
-        gr = ctx.fs_render_bwd(g, fcam, proj, bins, fT, nc, dL, want_abs=True)
-        ctx.fs_densify_accumulate(gr["mean2d"], gr["mean2d_abs"], proj.tiles_touched, self.grad_accum, self.abs_accum,
-                                  self.denom)
-        ctx.fs_activate_bwd(self.p["raw_scales"], self.p["raw_quats"], self.p["raw_opacities"], gr["scales"], gr["quats"],
-                            gr["opacities"])
-        grads = dict(means=gr["means"], sh=gr["sh"], raw_scales=gr["scales"], raw_quats=gr["quats"],
-                     raw_opacities=gr["opacities"])
         # optimiser schedule: an update every fs_adam_interval iterations, on the sum of the gradients since the last
         interval = ctx.fs_adam_interval(self.iteration)
         self.iteration += 1
         self.pending += 1
         last = self.pending >= interval
-        for k in GROUPS:
-            if interval == 1:
-                src = grads[k]
-            else:
-                ctx.fs_grad_accumulate(self.acc[k], grads[k])
-                src = self.acc[k]
-            if last:
-                ctx.fs_adam_step(self.p[k], src, self.m[k], self.v[k], self.updates + 1, c.lr[k], eps=c.eps,
-                                 zero_grad=(interval != 1))
+        groups = lambda d: [d[k] for k in GROUPS]
+        loss = ctx.fs_train_step(B.make_camera(cam), target, self.sh_degree, groups(self.p), groups(self.m), groups(self.v),
+                                 groups(self.acc), self.grad_accum, self.abs_accum, self.denom, groups(c.lr), c.lam, eps=c.eps,
+                                 step=self.updates + 1, sum=interval != 1, update=last)[2]
         if last:
             self.updates += 1
             self.pending = 0
-        return float(out3[2].item())
+        return loss
 
     # -- multi-view consistency scores (Sec. 4.2, 4.3) ----------------------------------
     def score_views(self, cams, targets):

@@ -1,0 +1,60 @@
+"""fs_train_step against the calls it stands for, one after the other on copies of the same state: every array of the state bit
+for bit the same (the arithmetic is the same, operation by operation) over iterations with an update each, iterations that only
+sum, and the update on the sum, for every SH degree, both pair rules, dense and sparse records, and counts of
+Gaussians off the wavefront, the workgroup and the 16-byte row."""
+import numpy as np
+import pytest
+
+from paper_2511_04283_amd import scenes
+
+pytestmark = pytest.mark.gpu
+LR = dict(means=1e-3, sh=2e-3, raw_scales=5e-3, raw_quats=1e-3, raw_opacities=5e-2)
+
+
+@pytest.mark.parametrize("compact,records", [(1, "dense"), (0, "sparse")])
+@pytest.mark.parametrize("deg", [0, 1, 2, 3])
+@pytest.mark.parametrize("n", [1, 33, 97, 611])
+def test_train_step_equals_the_calls_it_replaces(n, deg, compact, records):
+    import torch
+    from paper_2511_04283_amd import binding as B
+    from paper_2511_04283_amd.trainer import GROUPS, TrainConfig, Trainer
+    cfg = B.default_config()
+    cfg.compact_box = compact
+    c = B.Context("cuda:0", cfg)
+    c.fs_set_record_mode(B.FS_RECORDS_DENSE if records == "dense" else B.FS_RECORDS_SPARSE)
+    sc = scenes.tiny_scene(40 + n, n, 83, 50, sh_degree=deg, log_scale=(-2.3, 0.6), spread=1.3)
+    cam, fcam = sc.cameras[0], B.make_camera(sc.cameras[0])
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).to(c.device)
+    target = t(np.random.default_rng(n).uniform(0, 1, (3, cam.height, cam.width)))
+    tr = Trainer(c, t(sc.means), t(sc.scales), t(sc.quats * 1.7), t(sc.opacities), t(sc.sh), deg, TrainConfig(lr=LR, eps=1e-8))
+    copy = lambda d: {k: v.clone() for k, v in d.items()}
+    p, m, v, acc = copy(tr.p), copy(tr.m), copy(tr.v), copy(tr.acc)
+    ga, aa, den = tr.grad_accum.clone(), tr.abs_accum.clone(), tr.denom.clone()
+    updates = 0
+    for it, (sums, update) in enumerate([(False, True), (False, True), (True, False), (True, False), (True, True), (False, True)]):
+        s, q, o = c.fs_activate(p["raw_scales"], p["raw_quats"], p["raw_opacities"])
+        g = B.Gaussians(p["means"], s, q, o, p["sh"], deg)
+        proj = c.fs_preprocess(g, fcam)
+        bins = c.fs_bin_sort(proj, fcam)
+        image, fT, nc = c.fs_render_fwd(proj, bins, fcam)
+        out3, dL = c.fs_photo_loss(image, target, 0.2)
+        gr = c.fs_render_bwd(g, fcam, proj, bins, fT, nc, dL, want_abs=True)
+        c.fs_densify_accumulate(gr["mean2d"], gr["mean2d_abs"], proj.tiles_touched, ga, aa, den)
+        c.fs_activate_bwd(p["raw_scales"], p["raw_quats"], p["raw_opacities"], gr["scales"], gr["quats"], gr["opacities"])
+        grads = dict(zip(GROUPS, (gr["means"], gr["sh"], gr["scales"], gr["quats"], gr["opacities"])))
+        for k in GROUPS:
+            if sums:
+                c.fs_grad_accumulate(acc[k], grads[k])
+            if update:
+                c.fs_adam_step(p[k], acc[k] if sums else grads[k], m[k], v[k], updates + 1, LR[k], eps=1e-8, zero_grad=sums)
+        got = c.fs_train_step(fcam, target, deg, *[[d[k] for k in GROUPS] for d in (tr.p, tr.m, tr.v, tr.acc)], tr.grad_accum,
+                              tr.abs_accum, tr.denom, [LR[k] for k in GROUPS], eps=1e-8, step=updates + 1, sum=sums,
+                              update=update)
+        updates += update
+        assert list(got) == out3.tolist(), it
+        for a, b in ((tr.p, p), (tr.m, m), (tr.v, v), (tr.acc, acc)):
+            for k in GROUPS:
+                assert torch.equal(a[k], b[k]), (it, k)
+        assert torch.equal(tr.grad_accum, ga) and torch.equal(tr.abs_accum, aa) and torch.equal(tr.denom, den), it
+    assert int(den.max().item()) == 6
+    c.close()
