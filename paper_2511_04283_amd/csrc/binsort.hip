@@ -114,7 +114,7 @@ __device__ __forceinline__ void pack_splat(float4* __restrict__ splats, int64_t 
     float4* rec = splats + (size_t)i * (SPLAT_REC / 4);
     rec[0] = make_float4(m.x, m.y, co.x, co.y);
     rec[1] = make_float4(co.z, co.w, rgb[3 * i], rgb[3 * i + 1]);
-    rec[2] = make_float4(rgb[3 * i + 2], __uint_as_float(first_record), __uint_as_float((uint32_t)r.x | (uint32_t)r.y << 16),
+    rec[2] = make_float4(rgb[3 * i + 2], __uint_as_float(first_record | (is_needle(co) ? NEEDLE : 0u)), __uint_as_float((uint32_t)r.x | (uint32_t)r.y << 16),
                          __uint_as_float((uint32_t)r.z | (uint32_t)r.w << 16));
     rec[3] = support_octagon(co, cfg);
 }

@@ -86,7 +86,7 @@ __device__ __forceinline__ Pixel pixel_of_thread(const CamDev& cam, int tile)
 
 // LDS image of one batch of a tile's list, shared by the kernels.  A staged Gaussian is one 16-byte word in each of two
 // or (WITH_RGB) three arrays, so that one slot number, shifted once, addresses all of them:
-//   r0 = (mu_x, mu_y, -a/2, -b)   r1 = (-c/2, sigma, r, g)   r2 = (r, g, b, bits of the pair's gradient record number)
+//   r0 = (mu_x, mu_y, -a/2, -b)   r1 = (-c/2, sigma, r, g)   r2 = (r, g, b, bits of the pair's gradient record number + NEEDLE)
 // The factors make the quadratic form come out as the exponent -1/2 (a dx^2 + 2 b dx dy + c dy^2) itself: halving and
 // negating commute with every rounding on the way, so the exponent is the same to the bit.
 template <bool WITH_RGB, int N = SLOTS>
@@ -676,12 +676,13 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
             if (acted == 0) continue;
             const int slot = ent_list[k];
             const float mu_x = s.r0[slot].x, mu_y = s.r0[slot].y;
-            float sums[2][6];   // [0]: the first lane's, [1]: the second one's
+            const bool needle = __float_as_uint(s.r2[slot].w) & NEEDLE;
+            float sums0[6], sums1[6];   // the first lane's, the second one's
             float4 a, b;
             exchange(w, a, b);
 #pragma unroll
             for (int ch = 0; ch < 3; ch++)
-                sums[0][ch] = both(__builtin_fmaf(b.w, g2[ch][3], __builtin_fmaf(b.z, g2[ch][2], __builtin_fmaf(b.y, g2[ch][1],
+                sums0[ch] = both(__builtin_fmaf(b.w, g2[ch][3], __builtin_fmaf(b.z, g2[ch][2], __builtin_fmaf(b.y, g2[ch][1],
                                    __builtin_fmaf(b.x, g2[ch][0], __builtin_fmaf(a.w, g1[ch][3], __builtin_fmaf(a.z, g1[ch][2],
                                    __builtin_fmaf(a.y, g1[ch][1], a.x * g1[ch][0]))))))));
             exchange(v, a, b);
@@ -698,25 +699,55 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
                 // about mu: with (ox, oy) the sub-tile's centre seen from mu, sum (x + ox) v = m10 + ox m00 and so on
                 const float ox = __builtin_fmaf(-2.0f, mu_x, centre_x), oy = __builtin_fmaf(-2.0f, mu_y, centre_y);
                 const float dx = __builtin_fmaf(ox, m00, m10), dy = __builtin_fmaf(oy, m00, m01);
-                sums[0][DSIGMA] = m00;
-                sums[1][DX - HALF] = dx;
-                sums[1][DY - HALF] = dy;
-                sums[1][DXX - HALF] = __builtin_fmaf(ox, m10 + dx, m20);
-                sums[1][DYY - HALF] = __builtin_fmaf(oy, m01 + dy, m02);
-                sums[1][DXY - HALF] = __builtin_fmaf(oy, dx, __builtin_fmaf(ox, m01, m11));
+                sums0[DSIGMA] = m00;
+                sums1[DX - HALF] = dx;
+                sums1[DY - HALF] = dy;
+                sums1[DXX - HALF] = __builtin_fmaf(ox, m10 + dx, m20);
+                sums1[DYY - HALF] = __builtin_fmaf(oy, m01 + dy, m02);
+                sums1[DXY - HALF] = __builtin_fmaf(oy, dx, __builtin_fmaf(ox, m01, m11));
+            }
+            // needles: dL/dq times dx^2, dx dy, dy^2 pixel by pixel, added in the order of a balanced tree over the lines and
+            // their pixels (7 instructions more per entry; 500k Gaussians: one exchange in ten has one).  The v's are read
+            // from LDS once more, so that the common path does not hold them in registers.
+            if (ballot(needle) != 0) {
+                const float gq = -0.5f * s.r1[slot].y;
+                float xx = 0.f, xy = 0.f, yy = 0.f;
+#pragma unroll
+                for (int l = 0; l < 2; l++) {
+                    const int line = l ? q2 : q1;
+                    const float4 v4 = turned[line];
+                    const float py = (float)(sub_y + line) + 0.5f - mu_y;
+                    const float vv[4] = {v4.x, v4.y, v4.z, v4.w};
+                    float pxx[4], pxy[4], pyy[4];
+#pragma unroll
+                    for (int c = 0; c < 4; c++) {
+                        const float px = (float)(sub_x + c) + 0.5f - mu_x;
+                        const float gv = gq * vv[c], gx = gv * px, gy = gv * py;
+                        pxx[c] = gx * px;
+                        pxy[c] = gx * py;
+                        pyy[c] = gy * py;
+                    }
+                    // (lines 0 and 1, then 2 and 3, or the other way round)
+                    xx = xx + both((pxx[0] + pxx[1]) + (pxx[2] + pxx[3]));
+                    xy = xy + both((pxy[0] + pxy[1]) + (pxy[2] + pxy[3]));
+                    yy = yy + both((pyy[0] + pyy[1]) + (pyy[2] + pyy[3]));
+                }
+                sums1[DXX - HALF] = needle ? xx : sums1[DXX - HALF];
+                sums1[DYY - HALF] = needle ? yy : sums1[DYY - HALF];
+                sums1[DXY - HALF] = needle ? xy : sums1[DXY - HALF];
             }
             if (ABS) {
                 exchange(ax, a, b);
-                sums[0][DABS_X] = both(((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w)));
+                sums0[DABS_X] = both(((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w)));
                 exchange(ay, a, b);
-                sums[0][DABS_Y] = both(((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w)));
+                sums0[DABS_Y] = both(((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w)));
             }
             acc_t* const acc = &s_acc[slot][second ? HALF : 0];
 #pragma unroll
             for (int f = 0; f < (ABS ? 6 : 5); f++) {
-                const float mine_f = f >= HALF ? (second ? sums[1][f] : 0.f)
-                                   : f >= NV - HALF ? (second ? 0.f : sums[0][f]) : (second ? sums[1][f] : sums[0][f]);
-                if (mine_f != 0.f) atomicAdd(&acc[f], (acc_t)mine_f);
+                const float u0 = f < HALF ? sums0[f] : 0.f, u1 = f < NV - HALF ? sums1[f] : 0.f;
+                const float u = second ? u1 : u0;
+                if (u != 0.f) atomicAdd(&acc[f], (acc_t)u);
             }
         }
         __syncthreads();
@@ -737,11 +768,13 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
                 const float gq = -0.5f * f1.y;                                            // dL/dq = -1/2 sigma G dL/dalpha
                 const float3 co = make_float3(-2.0f * f0.z, -2.0f * f0.w, -2.0f * f1.x);  // (a, 2b, c)
                 const float mx = 0.5f * gq * a[DX], my = 0.5f * gq * a[DY];               // (half pixels)
-                const uint32_t idx = __float_as_uint(s.r2[threadIdx.x].w);
+                const uint32_t idx = __float_as_uint(s.r2[threadIdx.x].w) & ~NEEDLE;
                 float4* rec = pair_grad + (size_t)idx * (PAIR_REC / 4);
                 rec[0] = make_float4(a[DR], a[DG], a[DB], a[DSIGMA]);
                 // d = p - mu  =>  dq/dmu = -(2 a dx + 2b dy, 2b dx + 2 c dy)
-                rec[1] = make_float4(0.25f * gq * a[DXX], 0.5f * gq * a[DXY], 0.25f * gq * a[DYY], -(2.0f * co.x * mx + co.y * my));
+                const bool needle = __float_as_uint(s.r2[threadIdx.x].w) & NEEDLE;
+                const float second = needle ? 1.0f : 0.25f * gq;   // (a needle's second moments are in pixels, times dL/dq)
+                rec[1] = make_float4(second * a[DXX], 2.0f * second * a[DXY], second * a[DYY], -(2.0f * co.x * mx + co.y * my));
                 rec[2] = make_float4(-(co.y * mx + 2.0f * co.z * my), ABS ? f1.y * a[DABS_X] : 0.f, ABS ? f1.y * a[DABS_Y] : 0.f, 0.f);
                 if (SPARSE) rec_valid[idx] = 1;
             }
@@ -753,7 +786,7 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
             const float4 r2 = splats[(size_t)gauss_sorted[pos] * (SPLAT_REC / 4) + 2];
             const uint32_t r01 = __float_as_uint(r2.z), r23 = __float_as_uint(r2.w);
             const uint32_t x0 = r01 & 0xffffu, y0 = r01 >> 16, x1 = r23 & 0xffffu;
-            const uint32_t idx = __float_as_uint(r2.y) + ((uint32_t)(tile / cam.tiles_x) - y0) * (x1 - x0) +
+            const uint32_t idx = (__float_as_uint(r2.y) & ~NEEDLE) + ((uint32_t)(tile / cam.tiles_x) - y0) * (x1 - x0) +
                                  ((uint32_t)(tile % cam.tiles_x) - x0);
             float4* rec = pair_grad + (size_t)idx * (PAIR_REC / 4);
             rec[0] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -974,7 +1007,7 @@ __global__ __launch_bounds__(256) void k_render_bwd_splat(
             if (any) {
                 const float4 f0 = s.r0[threadIdx.x];
                 const float3 co = make_float3(-2.0f * f0.z, -2.0f * f0.w, -2.0f * s.r1[threadIdx.x].x);  // (a, 2b, c)
-                const uint32_t idx = __float_as_uint(s.r2[threadIdx.x].w);
+                const uint32_t idx = __float_as_uint(s.r2[threadIdx.x].w) & ~NEEDLE;
                 float4* rec = pair_grad + (size_t)idx * (PAIR_REC / 4);
                 rec[0] = make_float4(a[0], a[1], a[2], a[3]);
                 // d = p - mu  =>  dq/dmu = -(2 a dx + 2b dy, 2b dx + 2 c dy)
@@ -990,7 +1023,7 @@ __global__ __launch_bounds__(256) void k_render_bwd_splat(
             const float4 r2 = splats[(size_t)gauss_sorted[pos] * (SPLAT_REC / 4) + 2];
             const uint32_t r01 = __float_as_uint(r2.z), r23 = __float_as_uint(r2.w);
             const uint32_t x0 = r01 & 0xffffu, y0 = r01 >> 16, x1 = r23 & 0xffffu;
-            const uint32_t idx = __float_as_uint(r2.y) + ((uint32_t)(tile / cam.tiles_x) - y0) * (x1 - x0) +
+            const uint32_t idx = (__float_as_uint(r2.y) & ~NEEDLE) + ((uint32_t)(tile / cam.tiles_x) - y0) * (x1 - x0) +
                                  ((uint32_t)(tile % cam.tiles_x) - x0);
             float4* rec = pair_grad + (size_t)idx * (PAIR_REC / 4);
             rec[0] = make_float4(0.f, 0.f, 0.f, 0.f);

@@ -31,3 +31,30 @@ def test_list_of_n_entries(n, large, want_abs):
     assert np.array_equal(out["n_contrib"], nc)
     assert_image_close(out["image"], image)
     assert_grads_close(out["grads"], o.backward(sc, cam, p, b, dL))
+
+
+@pytest.mark.parametrize("want_abs", [False, True])
+@pytest.mark.parametrize("every", [1, 5])
+def test_needles_among_other_splats(every, want_abs):
+    """Splats more than thirty times as long as wide have their second moments added up another way (k_render_bwd): all of
+    the splats, or every fifth.  What the render pass itself leaves (the screen-space gradients) within the benchmark's
+    bar; the scales' gradients are the small difference of large moments, to a few parts in 10^4 of the largest."""
+    from paper_2511_04283_amd import binding as B
+    sc = scenes.tiny_scene(77, 300, 150, 83, sh_degree=0, log_scale=(-3.0, 0.3), spread=1.0)
+    sc.scales[::every] *= np.array([40.0, 0.02, 0.02], np.float32)
+    sc.opacities[::every] = 0.3
+    cam = sc.cameras[0]
+    dL = np.random.default_rng(5).normal(size=(3, cam.height, cam.width)).astype(np.float32)
+    c = B.Context("cuda:0")
+    out = gpu_pipeline(c, sc, cam, dL=dL, want_abs=want_abs)
+    c.close()
+    o = Oracle(np.float32)
+    p, b, image, T, nc = o.forward(sc, cam)
+    co = p.conic_opacity.astype(np.float64)
+    needles = (co[:, 0] + co[:, 2]) ** 2 > 1000.0 * (co[:, 0] * co[:, 2] - co[:, 1] ** 2)
+    assert needles[p.tiles_touched > 0].sum() > (100 if every == 1 else 20)
+    assert np.array_equal(out["n_contrib"], nc)
+    ref = o.backward(sc, cam, p, b, dL)
+    assert_grads_close(out["grads"], {k: ref[k] for k in ("conic", "mean2d", "rgb", "opacities", "sh") + (("mean2d_abs",) if want_abs else ())})
+    for k in ("scales", "quats", "means"):
+        assert np.linalg.norm(out["grads"][k] - ref[k]) <= 1e-3 * np.linalg.norm(ref[k]), k
