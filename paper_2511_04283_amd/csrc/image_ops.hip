@@ -211,45 +211,58 @@ __global__ __launch_bounds__(256) void k_err_mask_stats(const float* __restrict_
 // Gradient with respect to x: the three maps d ssim/d mu1, d ssim/d e11, d ssim/d e12 are window-summed
 // again (the window is symmetric) and combined as  g = <d_mu1> + 2 x <d_e11> + y <d_e12>.
 //
-// One workgroup produces a 32x32 block of one channel: the (32+10)x(32+10) input region goes to LDS,
-// a horizontal 11-tap pass (one lane: 4 neighbouring columns of one row, sliding over 14 inputs) leaves
-// NQ row-filtered planes in LDS, and a vertical pass (one lane: 4 neighbouring rows of one column) finishes.
+// One workgroup produces a 32-wide block of one channel: the block's input region goes to LDS, a horizontal 11-tap pass
+// (one lane: 4 neighbouring columns of one row, sliding over 14 inputs) leaves the row-filtered planes in registers and then
+// in the same LDS, and a vertical pass (one lane: SS_VO neighbouring rows of one column) finishes.
+// Vector instructions bound both kernels: 102 multiply-adds per value forward (44 of them 48/38 times for the rows of the
+// halo), about 210 instructions in all.  What went, against a 32x32 block with separate LDS for the row-filtered planes, which
+// took 260: the inputs' addresses and edge tests (a wavefront loads whole rows), 3 of 12 memory instructions per value (the
+// three derivative maps lie side by side), and the serial epilogue (all of a lane's outputs are formed at once and only the
+// stores are masked); the row-filtered planes take the inputs' place, so that six workgroups fit a compute unit instead of
+// four.  38 rows: 48 rows of eight 4-column units are 384 = 1.5 trips of the 256 lanes.  Forward and backward, before and after:
+// 51 and 46 us -> 42 and 34 at 1600x1064, 10.7 and 8.1 -> 8.8 and 7.1 at 509x337; forward alone at 1332x876 27.5 -> 23.7.
+// (Blocks 32 rows high: 45 and 34 us at 1600x1064; 54 rows: 42 and 34, but 9.8 and 7.9 at 509x337.)
 constexpr int SS_R = 5, SS_TAPS = 2 * SS_R + 1;
-constexpr int SS_TW = 32, SS_TH = 32;   // (32x16: 9 % slower, 64x16: the same, 64x32: 5 % slower, 16x32: 27 % slower)
-constexpr int SS_VO = SS_TW * SS_TH / 256;                         // outputs (neighbouring rows of one column) per lane
-constexpr int SS_IW = SS_TW + 2 * SS_R, SS_IH = SS_TH + 2 * SS_R;   // 42 x 42
+constexpr int SS_TW = 32, SS_TH = 38;
+constexpr int SS_VO = (SS_TH + 7) / 8;                               // outputs (neighbouring rows of one column) per lane
+constexpr int SS_IW = SS_TW + 2 * SS_R, SS_IH = SS_TH + 2 * SS_R;
 constexpr int SS_IP = SS_IW + 2;                                     // padded LDS row
+constexpr int SS_HR = 8 * SS_VO + 2 * SS_R;                          // rows the vertical pass reads (those from SS_IH on: for outputs nobody wants)
+constexpr int SS_UNITS = SS_IH * (SS_TW / 4), SS_TRIPS = (SS_UNITS + 255) / 256;   // of the horizontal pass
+constexpr int ss_floats(int planes_in, int planes_h)
+{
+    return planes_in * SS_IH * SS_IP > planes_h * SS_HR * SS_TW ? planes_in * SS_IH * SS_IP : planes_h * SS_HR * SS_TW;
+}
 
 struct SsimWin { float w[SS_TAPS]; };
+struct Floats3 { float v[3]; };
 
-// zero-continued load of the block's input region of NP planes: every global load is issued before the
-// first LDS write, so that their latencies overlap
-template <int NP>
-__device__ __forceinline__ void ss_load(const float* const (&base)[NP], int H, int W, int x0, int y0,
-                                        float (*dst)[SS_IH][SS_IP])
+// The block's input region of one channel, continued by zeros, into NP planes in LDS: a wavefront takes whole rows (their
+// addresses are scalar), and every load is issued before the first LDS write, so that their latencies overlap.
+// fetch(row's first pixel, column) reads the NP values of one pixel.
+template <int NP, typename Fetch>
+__device__ __forceinline__ void ss_load(Fetch fetch, int H, int W, int x0, int y0, float (*dst)[SS_IH][SS_IP])
 {
-    constexpr int IT = (SS_IH * SS_IW + 255) / 256;
-    float v[NP][IT];
+    constexpr int IT = (SS_IH + 3) / 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int gx = x0 + lane - SS_R;
+    const bool in_col = lane < SS_IW && gx >= 0 && gx < W;
+    const uint32_t col = in_col ? (uint32_t)gx : 0u;
+    float v[IT][NP];
 #pragma unroll
     for (int it = 0; it < IT; it++) {
-        const int e = threadIdx.x + 256 * it;
-        const int r = e / SS_IW, c = e - r * SS_IW;
-        const int gy = y0 + r - SS_R, gx = x0 + c - SS_R;
-        const bool in = e < SS_IH * SS_IW && gy >= 0 && gy < H && gx >= 0 && gx < W;
-        const size_t off = in ? (size_t)gy * W + gx : 0;
+        const int gy = y0 + wave + 4 * it - SS_R;
+        const bool in_row = gy >= 0 && gy < H;
+        fetch((size_t)(in_row ? gy : 0) * W, col, v[it]);   // (always a valid address)
 #pragma unroll
-        for (int p = 0; p < NP; p++) {
-            const float t = base[p][off];   // (off = 0 is always a valid address)
-            v[p][it] = in ? t : 0.0f;
-        }
+        for (int p = 0; p < NP; p++) v[it][p] = in_row && in_col ? v[it][p] : 0.0f;
     }
 #pragma unroll
     for (int it = 0; it < IT; it++) {
-        const int e = threadIdx.x + 256 * it;
-        const int r = e / SS_IW, c = e - r * SS_IW;
-        if (e < SS_IH * SS_IW) {
+        const int r = wave + 4 * it;
+        if (r < SS_IH && lane < SS_IW) {
 #pragma unroll
-            for (int p = 0; p < NP; p++) dst[p][r][c] = v[p][it];
+            for (int p = 0; p < NP; p++) dst[p][r][lane] = v[it][p];
         }
     }
 }
@@ -270,19 +283,26 @@ __device__ __forceinline__ void ss_vertical(const float (*h)[SS_TW], int r0, int
     }
 }
 
-__global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ image, const float* __restrict__ target,
+// dmaps: the three derivatives of a pixel side by side (12 bytes; null: not wanted)
+__global__ __launch_bounds__(256, 6) void k_ssim_fwd(const float* __restrict__ image, const float* __restrict__ target,
                                                   int H, int W, SsimWin win, float* __restrict__ dmaps,
                                                   double* __restrict__ partial, int nblocks)
 {
-    __shared__ __attribute__((aligned(16))) float s_in[2][SS_IH][SS_IP];
-    __shared__ __attribute__((aligned(16))) float s_h[4][SS_IH][SS_TW];
-    __shared__ double smem[4];
+    __shared__ __attribute__((aligned(16))) float s_buf[ss_floats(2, 4)];
+    __shared__ double s_sum[2][4];
+    float (*const s_in)[SS_IH][SS_IP] = reinterpret_cast<float (*)[SS_IH][SS_IP]>(s_buf);
+    float (*const s_h)[SS_HR][SS_TW] = reinterpret_cast<float (*)[SS_HR][SS_TW]>(s_buf);
     const int x0 = blockIdx.x * SS_TW, y0 = blockIdx.y * SS_TH;
     const size_t plane = (size_t)blockIdx.z * H * W;
-    const float* const src[2] = {image + plane, target + plane};
-    ss_load<2>(src, H, W, x0, y0, s_in);
+    const float *const img = image + plane, *const tgt = target + plane;
+    ss_load<2>([=](size_t row, uint32_t col, float (&v)[2]) { v[0] = (img + row)[col]; v[1] = (tgt + row)[col]; }, H, W, x0, y0, s_in);
     __syncthreads();
-    for (int u = threadIdx.x; u < SS_IH * (SS_TW / 4); u += 256) {
+    double ssum = 0.0, lsum = 0.0;
+    float4 hor[SS_TRIPS][4];
+#pragma unroll
+    for (int t = 0; t < SS_TRIPS; t++) {
+        const int u = threadIdx.x + 256 * t;
+        if (u >= SS_UNITS) continue;
         const int r = u / (SS_TW / 4), c0 = (u % (SS_TW / 4)) * 4;
         // 16-byte LDS accesses: a lane's 16 inputs are four aligned float4s, and 8 neighbouring lanes cover
         // all banks (a 4-byte access pattern with stride 4 would hit every fourth bank only)
@@ -300,6 +320,10 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ imag
             sq[i] = __builtin_fmaf(xv[i], xv[i], yv[i] * yv[i]);
             xy[i] = xv[i] * yv[i];
         }
+        if (r >= SS_R && r < SS_R + SS_TH) {   // the block's own pixels (both images are zero beyond the edge)
+#pragma unroll
+            for (int j = 0; j < 4; j++) lsum += (double)fabsf(xv[SS_R + j] - yv[SS_R + j]);
+        }
         float o[4][4];
 #pragma unroll
         for (int j = 0; j < 4; j++) {
@@ -315,8 +339,15 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ imag
             o[0][j] = m1; o[1][j] = m2; o[2][j] = esq; o[3][j] = e12;
         }
 #pragma unroll
-        for (int k = 0; k < 4; k++)
-            *reinterpret_cast<float4*>(&s_h[k][r][c0]) = make_float4(o[k][0], o[k][1], o[k][2], o[k][3]);
+        for (int k = 0; k < 4; k++) hor[t][k] = make_float4(o[k][0], o[k][1], o[k][2], o[k][3]);
+    }
+    __syncthreads();   // (the inputs have been read: their place is taken)
+#pragma unroll
+    for (int t = 0; t < SS_TRIPS; t++) {
+        const int u = threadIdx.x + 256 * t;
+        if (u >= SS_UNITS) continue;
+#pragma unroll
+        for (int k = 0; k < 4; k++) *reinterpret_cast<float4*>(&s_h[k][u / (SS_TW / 4)][(u % (SS_TW / 4)) * 4]) = hor[t][k];
     }
     __syncthreads();
     const int c = threadIdx.x % SS_TW, r0 = (threadIdx.x / SS_TW) * SS_VO;
@@ -324,32 +355,35 @@ __global__ __launch_bounds__(256) void k_ssim_fwd(const float* __restrict__ imag
 #pragma unroll
     for (int k = 0; k < 4; k++) ss_vertical(s_h[k], r0, c, win, q[k]);
     const float C1 = 0.01f * 0.01f, C2 = 0.03f * 0.03f;
-    double ssum = 0.0, lsum = 0.0;
+    const int gx = x0 + c, gy0 = y0 + r0, rows = gx < W ? min(min(SS_VO, SS_TH - r0), H - gy0) : 0;   // (may be negative)
+    float* const d0 = dmaps + 3 * (plane + (size_t)gy0 * W + gx);
 #pragma unroll
     for (int o = 0; o < SS_VO; o++) {
-        const int gy = y0 + r0 + o, gx = x0 + c;
-        if (gy < H && gx < W) {
-            const float m1 = q[0][o], m2 = q[1][o];
-            const float mm = m1 * m1 + m2 * m2, s12 = q[3][o] - m1 * m2;
-            const float A = 2.f * m1 * m2 + C1, B = 2.f * s12 + C2, Cq = mm + C1, D = (q[2][o] - mm) + C2;
-            const float inv = 1.0f / (Cq * D);
-            const float sv = A * B * inv;
-            ssum += (double)sv;
-            lsum += (double)fabsf(s_in[0][r0 + o + SS_R][c + SS_R] - s_in[1][r0 + o + SS_R][c + SS_R]);
-            if (dmaps) {
-                const size_t n3 = (size_t)3 * H * W, p = plane + (size_t)gy * W + gx;
-                dmaps[p] = (2.f * m2 * (B - A) - sv * 2.f * m1 * (D - Cq)) * inv;
-                dmaps[n3 + p] = -sv / D;
-                dmaps[2 * n3 + p] = 2.f * A * inv;
-            }
+        const float m1 = q[0][o], m2 = q[1][o];
+        const float mm = m1 * m1 + m2 * m2, s12 = q[3][o] - m1 * m2;
+        const float A = 2.f * m1 * m2 + C1, B = 2.f * s12 + C2, Cq = mm + C1, D = (q[2][o] - mm) + C2;
+        const float inv = 1.0f / (Cq * D);
+        const float sv = A * B * inv;
+        ssum += o < rows ? (double)sv : 0.0;
+        if (dmaps) {
+            Floats3 d;
+            d.v[0] = (2.f * m2 * (B - A) - sv * 2.f * m1 * (D - Cq)) * inv;
+            d.v[1] = -sv / D;
+            d.v[2] = 2.f * A * inv;
+            if (o < rows) *reinterpret_cast<Floats3*>(d0 + (size_t)o * 3 * W) = d;
         }
     }
-    ssum = block_reduce<RED_SUM>(ssum, smem);
-    lsum = block_reduce<RED_SUM>(lsum, smem);
-    if (threadIdx.x == 0) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        ssum += shfl_down_f64(ssum, d);
+        lsum += shfl_down_f64(lsum, d);
+    }
+    if ((threadIdx.x & 63) == 0) { s_sum[0][threadIdx.x >> 6] = ssum; s_sum[1][threadIdx.x >> 6] = lsum; }
+    __syncthreads();
+    if (threadIdx.x < 2) {
         const int b = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-        partial[b] = ssum;
-        partial[nblocks + b] = lsum;
+        const double* const w = s_sum[threadIdx.x];
+        partial[threadIdx.x * nblocks + b] = (w[0] + w[1]) + (w[2] + w[3]);
     }
 }
 
@@ -386,14 +420,22 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ imag
                                                   int H, int W, SsimWin win, const float* __restrict__ dmaps,
                                                   float c_l1, float c_ss, float* __restrict__ dL)
 {
-    __shared__ __attribute__((aligned(16))) float s_in[3][SS_IH][SS_IP];
-    __shared__ __attribute__((aligned(16))) float s_h[3][SS_IH][SS_TW];
+    __shared__ __attribute__((aligned(16))) float s_buf[ss_floats(3, 3)];
+    float (*const s_in)[SS_IH][SS_IP] = reinterpret_cast<float (*)[SS_IH][SS_IP]>(s_buf);
+    float (*const s_h)[SS_HR][SS_TW] = reinterpret_cast<float (*)[SS_HR][SS_TW]>(s_buf);
     const int x0 = blockIdx.x * SS_TW, y0 = blockIdx.y * SS_TH;
-    const size_t plane = (size_t)blockIdx.z * H * W, n3 = (size_t)3 * H * W;
-    const float* const src[3] = {dmaps + plane, dmaps + n3 + plane, dmaps + 2 * n3 + plane};
-    ss_load<3>(src, H, W, x0, y0, s_in);
+    const size_t plane = (size_t)blockIdx.z * H * W;
+    const float* const maps = dmaps + 3 * plane;
+    ss_load<3>([=](size_t row, uint32_t col, float (&v)[3]) {
+        const Floats3 d = reinterpret_cast<const Floats3*>(maps + 3 * row)[col];
+        v[0] = d.v[0]; v[1] = d.v[1]; v[2] = d.v[2];
+    }, H, W, x0, y0, s_in);
     __syncthreads();
-    for (int u = threadIdx.x; u < SS_IH * (SS_TW / 4); u += 256) {
+    float4 hor[SS_TRIPS][3];
+#pragma unroll
+    for (int t = 0; t < SS_TRIPS; t++) {
+        const int u = threadIdx.x + 256 * t;
+        if (u >= SS_UNITS) continue;
         const int r = u / (SS_TW / 4), c0 = (u % (SS_TW / 4)) * 4;
 #pragma unroll
         for (int k = 0; k < 3; k++) {
@@ -407,28 +449,40 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ imag
             for (int j = 0; j < 4; j++) {
                 float a = 0.f;
 #pragma unroll
-                for (int t = 0; t < SS_TAPS; t++) a = __builtin_fmaf(win.w[t], v[j + t], a);
+                for (int i = 0; i < SS_TAPS; i++) a = __builtin_fmaf(win.w[i], v[j + i], a);
                 o[j] = a;
             }
-            *reinterpret_cast<float4*>(&s_h[k][r][c0]) = make_float4(o[0], o[1], o[2], o[3]);
+            hor[t][k] = make_float4(o[0], o[1], o[2], o[3]);
         }
     }
     __syncthreads();
+    // this lane's pixels (requested here, needed at the end)
     const int c = threadIdx.x % SS_TW, r0 = (threadIdx.x / SS_TW) * SS_VO;
+    const int gx = x0 + c, gy0 = y0 + r0, rows = gx < W ? min(min(SS_VO, SS_TH - r0), H - gy0) : 0;   // (may be negative)
+    const size_t p0 = plane + (size_t)gy0 * W + gx;
+    float x[SS_VO], y[SS_VO];
+#pragma unroll
+    for (int o = 0; o < SS_VO; o++) {
+        x[o] = o < rows ? image[p0 + (size_t)o * W] : 0.f;
+        y[o] = o < rows ? target[p0 + (size_t)o * W] : 0.f;
+    }
+#pragma unroll
+    for (int t = 0; t < SS_TRIPS; t++) {
+        const int u = threadIdx.x + 256 * t;
+        if (u >= SS_UNITS) continue;
+#pragma unroll
+        for (int k = 0; k < 3; k++) *reinterpret_cast<float4*>(&s_h[k][u / (SS_TW / 4)][(u % (SS_TW / 4)) * 4]) = hor[t][k];
+    }
+    __syncthreads();
     float q[3][SS_VO];
 #pragma unroll
     for (int k = 0; k < 3; k++) ss_vertical(s_h[k], r0, c, win, q[k]);
 #pragma unroll
     for (int o = 0; o < SS_VO; o++) {
-        const int gy = y0 + r0 + o, gx = x0 + c;
-        if (gy < H && gx < W) {
-            const size_t p = plane + (size_t)gy * W + gx;
-            const float x = image[p], y = target[p];
-            const float g = q[0][o] + 2.f * x * q[1][o] + y * q[2][o];
-            const float d = x - y;
-            const float sg = d > 0.f ? c_l1 : (d < 0.f ? -c_l1 : 0.f);
-            dL[p] = sg - c_ss * g;
-        }
+        const float g = q[0][o] + 2.f * x[o] * q[1][o] + y[o] * q[2][o];
+        const float d = x[o] - y[o];
+        const float sg = d > 0.f ? c_l1 : (d < 0.f ? -c_l1 : 0.f);
+        if (o < rows) dL[p0 + (size_t)o * W] = sg - c_ss * g;
     }
 }
 

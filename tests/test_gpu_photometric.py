@@ -135,3 +135,15 @@ def test_vcp_pipeline_three_views(ctx, orc32):
     sp = ctx.fs_prune_score_normalize(acc).cpu().numpy()
     _, ref = oracle.prune_score(np.stack(counts_ref), np.array(E_ref))
     assert np.abs(sp - ref).max() < 2e-5 and ref.max() == 1.0
+
+
+@pytest.mark.parametrize("H,W", [(37, 31), (38, 32), (39, 33), (76, 64), (77, 65), (6, 200), (200, 6)])
+def test_sizes_round_a_block_with_and_without_the_gradient(ctx, H, W):
+    """Blocks are 38 x 32: one block exactly, one row or column fewer and more, two blocks, slivers.  The value-only call and
+    the one with a gradient add the same numbers in the same order."""
+    rng = np.random.default_rng(7 * H + W)
+    x = rng.uniform(0, 1, (3, H, W))
+    y = np.clip(x + rng.normal(0, 0.15, x.shape), 0, 1)
+    out3, _ = _check(ctx, x, y, 0.2, threads=1)
+    value_only, _ = _run(ctx, x, y, 0.2, want_grad=False)
+    assert np.array_equal(value_only, out3)
