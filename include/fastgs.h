@@ -20,7 +20,7 @@
  *   fs_mask_score_fused  fs_error_mask_fused + fs_score_accumulate as one call (one kernel launch with the record)
  *   fs_score_record_rows how many pairs of every tile that record holds a row for (a diagnostic)
  *   fs_photo_loss        E = (1-lambda) L1 + lambda (1 - SSIM) and dE/dC        (Sec. 4.3 E_photo; Sec. 4.5 Eq. for L)
- *   fs_prune_score_accumulate / fs_prune_score_normalize
+ *   fs_prune_score_accumulate / fs_score_view_end / fs_prune_score_normalize
  *                        s_p = N(sum over views of count * E_photo)             (Sec. 4.3, Eq. for s_p)
  *   fs_train_step        a whole training iteration as one call, gradients consumed where they are formed
  *   fs_adam_step / fs_grad_accumulate / fs_adam_interval / fs_activate / fs_activate_bwd
@@ -329,6 +329,10 @@ int fs_photo_loss(fs_ctx *ctx, const float *image, const float *target, int32_t 
  *   acc[i] += counts_view[i] * (*E)          acc: [n] doubles, caller-owned, zeroed before the first view.
  * E points at ONE device double (e.g. out3 + 2 of fs_photo_loss). */
 int fs_prune_score_accumulate(fs_ctx *ctx, const int32_t *counts_view, int64_t n, const double *E, double *acc);
+
+/* The end of one view of a pass over several: fs_prune_score_accumulate, then counts[i] += counts_view[i] (fs_counts_add), then
+ * counts_view is zeroed for the next view, in one launch.  counts: [n], not the same array as counts_view. */
+int fs_score_view_end(fs_ctx *ctx, int32_t *counts_view, int64_t n, const double *E, double *acc, int32_t *counts);
 
 /* s_p[i] = (acc[i] - min acc) / (max acc - min acc): the min-max normalisation N over the Gaussians;
  * all zeros when max = min.  s_p: [n] floats. */

@@ -27,7 +27,7 @@ _STATUS = {0: "FS_OK", -1: "FS_EINVAL", -2: "FS_ENOMEM", -3: "FS_EHIP", -4: "FS_
 
 EXPORTS = ("fs_default_config", "fs_create", "fs_destroy", "fs_last_error", "fs_preprocess", "fs_bin_sort",
            "fs_render_fwd", "fs_render_fwd_loss", "fs_set_score_record", "fs_set_backward_mode", "fs_set_record_mode", "fs_error_mask_fused", "fs_l1_grad", "fs_render_bwd", "fs_error_mask", "fs_error_mask_noalloc", "fs_score_accumulate", "fs_score_record_rows", "fs_mask_score_fused",
-           "fs_photo_loss", "fs_prune_score_accumulate", "fs_prune_score_normalize",
+           "fs_photo_loss", "fs_prune_score_accumulate", "fs_score_view_end", "fs_prune_score_normalize",
            "fs_densify_accumulate", "fs_select", "fs_compact", "fs_gather_rows",
            "fs_combine_masks", "fs_counts_add", "fs_split_children", "fs_sample_by_score", "fs_activate_inv",
            "fs_adam_step", "fs_grad_accumulate", "fs_adam_interval", "fs_activate", "fs_activate_bwd", "fs_train_step",
@@ -132,6 +132,7 @@ def load_library() -> ctypes.CDLL:
     lib.fs_mask_score_fused.argtypes = [vp, P(fs_projected), P(fs_bins), P(fs_camera), vp, ctypes.c_int32, ctypes.c_float, vp, vp, vp]
     lib.fs_photo_loss.argtypes = [vp, vp, vp, i32, i32, f32, vp, vp]
     lib.fs_prune_score_accumulate.argtypes = [vp, vp, i64, vp, vp]
+    lib.fs_score_view_end.argtypes = [vp, vp, i64, vp, vp, vp]
     lib.fs_prune_score_normalize.argtypes = [vp, vp, i64, vp]
     lib.fs_densify_accumulate.argtypes = [vp, vp, vp, vp, i64, vp, vp, vp]
     lib.fs_select.argtypes = [vp, i64, vp, vp, vp, vp, vp, vp, vp, P(fs_select_params), vp, vp, vp]
@@ -450,7 +451,7 @@ class Context:
         """Returns (out3, dL_dimage): out3 = device doubles {L1, SSIM, E}; dL_dimage is None if not wanted."""
         _, H, W = image.shape
         if out3 is None:
-            out3 = torch.zeros(3, dtype=torch.float64, device=self.device)
+            out3 = torch.empty(3, dtype=torch.float64, device=self.device)
         if dL_dimage is None and want_grad:
             dL_dimage = torch.empty_like(image)
         self._check(self.lib.fs_photo_loss(self.handle, _ptr(image), _ptr(target), H, W, float(lam),
@@ -465,6 +466,15 @@ class Context:
         self._check(self.lib.fs_prune_score_accumulate(self.handle, _ptr(counts_view), n, _ptr(E), _ptr(acc)),
                     "fs_prune_score_accumulate")
         return acc
+
+    def fs_score_view_end(self, counts_view, E, acc, counts):
+        n = int(counts_view.shape[0])
+        _chk(counts_view, torch.int32, (n,), "counts_view")
+        _chk(acc, torch.float64, (n,), "acc")
+        _chk(counts, torch.int32, (n,), "counts")
+        assert E.dtype == torch.float64 and E.numel() >= 1
+        self._check(self.lib.fs_score_view_end(self.handle, _ptr(counts_view), n, _ptr(E), _ptr(acc), _ptr(counts)),
+                    "fs_score_view_end")
 
     def fs_prune_score_normalize(self, acc, s_p=None):
         n = int(acc.shape[0])

@@ -876,6 +876,16 @@ int fs_prune_score_accumulate(fs_ctx* ctx, const int32_t* counts_view, int64_t n
     return FS_OK;
 }
 
+int fs_score_view_end(fs_ctx* ctx, int32_t* counts_view, int64_t n, const double* E, double* acc, int32_t* counts)
+{
+    if (!ctx) return FS_EINVAL;
+    if (n < 0 || (n > 0 && (!counts_view || !E || !acc || !counts || counts == counts_view)))
+        return fail(ctx, FS_EINVAL, "fs_score_view_end: bad arguments");
+    FS_HIP(hipSetDevice(ctx->device), "hipSetDevice");
+    FS_HIP(launch_score_view_end(ctx->stream, counts_view, n, E, acc, counts), "k_score_view_end");
+    return FS_OK;
+}
+
 int fs_prune_score_normalize(fs_ctx* ctx, const double* acc, int64_t n, float* s_p)
 {
     if (!ctx) return FS_EINVAL;

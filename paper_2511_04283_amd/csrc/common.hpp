@@ -468,6 +468,7 @@ hipError_t launch_photo_loss(hipStream_t st, const float* image, const float* ta
                              float* dmaps, double* partial, float* dL, double* out3);
 // acc[i] += counts[i] * *E;  then out = min-max normalised acc (partial: >= 2*mask_partials() + 2 doubles)
 hipError_t launch_prune_accumulate(hipStream_t st, const int32_t* counts, int64_t n, const double* E, double* acc);
+hipError_t launch_score_view_end(hipStream_t st, int32_t* counts, int64_t n, const double* E, double* acc, int32_t* total);
 hipError_t launch_prune_normalize(hipStream_t st, const double* acc, int64_t n, double* partial, float* out);
 
 // densification / pruning decisions and index plumbing (densify.hip)

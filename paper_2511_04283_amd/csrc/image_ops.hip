@@ -494,6 +494,20 @@ __global__ __launch_bounds__(256) void k_prune_accumulate(const int32_t* __restr
     if (i < n) acc[i] = acc[i] + (double)counts[i] * *E;
 }
 
+// The end of one view of a score pass in one launch: its counts weighed into the score and added to the total, and cleared for
+// the next view.  (12 bytes read and 16 written per Gaussian: a launch's own few microseconds.  As a weighing, an addition and
+// a fill: 4.6 + 3.3 + 4.4 us at 300k Gaussians, 5.2 this way.)
+__global__ __launch_bounds__(256) void k_score_view_end(int32_t* __restrict__ counts, int64_t n, const double* __restrict__ E,
+                                                        double* __restrict__ acc, int32_t* __restrict__ total)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int32_t c = counts[i];
+    acc[i] = acc[i] + (double)c * *E;
+    total[i] = total[i] + c;
+    counts[i] = 0;
+}
+
 __global__ __launch_bounds__(RED_THREADS) void k_minmax_f64(const double* __restrict__ v, int64_t n,
                                                            double* __restrict__ partial)
 {
@@ -585,6 +599,13 @@ hipError_t launch_prune_accumulate(hipStream_t st, const int32_t* counts, int64_
 {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_prune_accumulate, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, counts, n, E, acc);
+    return hipGetLastError();
+}
+
+hipError_t launch_score_view_end(hipStream_t st, int32_t* counts, int64_t n, const double* E, double* acc, int32_t* total)
+{
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_score_view_end, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, counts, n, E, acc, total);
     return hipGetLastError();
 }
 

@@ -94,6 +94,7 @@ class Trainer:
         n, dev = self.n, ctx.device
         counts = torch.zeros(n, dtype=torch.int32, device=dev)
         acc = torch.zeros(n, dtype=torch.float64, device=dev)
+        view = torch.zeros(n, dtype=torch.int32, device=dev)
         ctx.fs_set_score_record(True)   # (off during the training iterations, which no count pass follows)
         for cam, target in zip(cams, targets):
             fcam = B.make_camera(cam)
@@ -101,11 +102,9 @@ class Trainer:
             bins = ctx.fs_bin_sort(proj, fcam)
             # forward pass with the error map and the per-pair record of counted pixels fused into it
             image, fT, nc, _ = ctx.fs_render_fwd_loss(proj, bins, fcam, target, want_grad=False)
-            view = torch.zeros(n, dtype=torch.int32, device=dev)
             ctx.fs_mask_score_fused(proj, bins, fcam, nc, view, c.mask_rule, c.mask_k)   # mask, then the view's counts
             out3, _ = ctx.fs_photo_loss(image, target, c.lam, want_grad=False)
-            ctx.fs_prune_score_accumulate(view, out3[2:3], acc)
-            ctx.fs_counts_add(counts, view)
+            ctx.fs_score_view_end(view, out3[2:3], acc, counts)
         ctx.fs_set_score_record(False)
         return counts, ctx.fs_prune_score_normalize(acc)
 

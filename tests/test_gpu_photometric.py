@@ -104,6 +104,23 @@ def test_prune_score_over_views_bit_exact(ctx):
     assert not ctx.fs_prune_score_normalize(acc).cpu().numpy().any()
 
 
+@pytest.mark.parametrize("n", [1, 255, 256, 257, 70001])
+def test_view_end_is_the_three_separate_steps(ctx, n):
+    """Bit for bit (the same additions), and the view's counts are zero afterwards."""
+    import torch
+    rng = np.random.default_rng(n)
+    dev = ctx.device
+    view = torch.from_numpy(rng.integers(0, 4000, n).astype(np.int32)).to(dev)
+    E = torch.from_numpy(rng.uniform(0.02, 0.4, 1)).to(dev)
+    acc = torch.from_numpy(rng.uniform(0, 100, n)).to(dev)
+    counts = torch.from_numpy(rng.integers(0, 9000, n).astype(np.int32)).to(dev)
+    acc_ref, counts_ref = acc.clone(), counts.clone()
+    ctx.fs_prune_score_accumulate(view, E, acc_ref)
+    ctx.fs_counts_add(counts_ref, view)
+    ctx.fs_score_view_end(view, E, acc, counts)
+    assert torch.equal(acc, acc_ref) and torch.equal(counts, counts_ref) and not view.any()
+
+
 def test_vcp_pipeline_three_views(ctx, orc32):
     """Counts and E_photo of several views chained on the GPU exactly as the pruning score needs them."""
     import torch
