@@ -526,7 +526,9 @@ class Context:
         """One training iteration in place.  params, m, v, acc and lr: the five groups (means, sh, raw scales, raw
         quaternions, raw opacities).  Returns (L1, SSIM, E) as soon as they are known."""
         n, K = int(params[4].shape[0]), (int(sh_degree) + 1) ** 2
-        _chk(target, torch.float32, (3, cam.height, cam.width), "target")
+        # (any shape, as with fs_photo_loss: a batch of one, or flat)
+        if _chk(target, torch.float32, None, "target").numel() < 3 * cam.height * cam.width:
+            raise ValueError(f"target: {tuple(target.shape)} holds no [3, {cam.height}, {cam.width}] image")
         shapes = ((n, 3), (n, K, 3), (n, 3), (n, 4), (n,))
         t = fs_train_state()
         t.n, t.sh_degree = n, int(sh_degree)

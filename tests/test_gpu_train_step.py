@@ -58,3 +58,23 @@ def test_train_step_equals_the_calls_it_replaces(n, deg, compact, records):
         assert torch.equal(tr.grad_accum, ga) and torch.equal(tr.abs_accum, aa) and torch.equal(tr.denom, den), it
     assert int(den.max().item()) == 6
     c.close()
+
+
+@pytest.mark.parametrize("shape", [(1, 3, 50, 83), (3 * 50 * 83,)])
+def test_target_of_another_shape_and_too_small_a_target(shape):
+    import torch
+    from paper_2511_04283_amd import binding as B
+    from paper_2511_04283_amd.trainer import TrainConfig, Trainer
+    c = B.Context("cuda:0")
+    sc = scenes.tiny_scene(44, 61, 83, 50, sh_degree=1, log_scale=(-2.3, 0.6), spread=1.3)
+    cam = sc.cameras[0]
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).to(c.device)
+    target = t(np.random.default_rng(5).uniform(0, 1, (3, 50, 83)))
+    make = lambda: Trainer(c, t(sc.means), t(sc.scales), t(sc.quats), t(sc.opacities), t(sc.sh), 1, TrainConfig(lr=LR))
+    a, b = make(), make()
+    assert a.step(cam, target) == b.step(cam, target.view(shape))
+    for k in a.p:
+        assert torch.equal(a.p[k], b.p[k]), k
+    with pytest.raises(ValueError):   # refused on the host, before anything is enqueued
+        b.step(cam, target[:2])
+    c.close()
