@@ -74,13 +74,13 @@ class Trainer:
         ctx, c = self.ctx, self.cfg
         # optimiser schedule: an update every fs_adam_interval iterations, on the sum of the gradients since the last
         interval = ctx.fs_adam_interval(self.iteration)
-        self.iteration += 1
-        self.pending += 1
-        last = self.pending >= interval
+        last = self.pending + 1 >= interval
         groups = lambda d: [d[k] for k in GROUPS]
         loss = ctx.fs_train_step(B.make_camera(cam), target, self.sh_degree, groups(self.p), groups(self.m), groups(self.v),
                                  groups(self.acc), self.grad_accum, self.abs_accum, self.denom, groups(c.lr), c.lam, eps=c.eps,
                                  step=self.updates + 1, sum=interval != 1, update=last)[2]
+        self.iteration += 1   # (not where the call was refused)
+        self.pending += 1
         if last:
             self.updates += 1
             self.pending = 0

@@ -77,4 +77,5 @@ def test_target_of_another_shape_and_too_small_a_target(shape):
         assert torch.equal(a.p[k], b.p[k]), k
     with pytest.raises(ValueError):   # refused on the host, before anything is enqueued
         b.step(cam, target[:2])
+    assert (b.iteration, b.pending, b.updates) == (a.iteration, a.pending, a.updates) == (1, 0, 1)
     c.close()
