@@ -52,7 +52,7 @@ struct fs_ctx {
     bool alloc_dirty = false;        // a call failed between the kernel that adds to them and the one that clears them
     ScratchBuf train_proj;           // fs_train_step: the projected splats of its view ...
     ScratchBuf train_frame;          // ... its image, dL/dimage, final_T and n_contrib
-    double* loss_host = nullptr;     // pinned host block for its loss (three doubles, written by k_photo_final)
+    double* loss_host = nullptr;     // pinned host block for its loss (three doubles, written by k_ssim_bwd)
     hipEvent_t loss_event = nullptr; // recorded behind that kernel
     ScratchBuf tile_partial;         // double [5, tiles]: per-tile sums of the fused forward pass
     ScratchBuf pair_bits;            // the record of the forward passes for the count pass (score_record_at)

@@ -388,10 +388,9 @@ __global__ __launch_bounds__(256, 6) void k_ssim_fwd(const float* __restrict__ i
 }
 
 // out3 = {L1, SSIM, (1 - lambda) L1 + lambda (1 - SSIM)}: one workgroup adds the partials in a fixed order
-__global__ __launch_bounds__(RED_THREADS) void k_photo_final(const double* __restrict__ partial, int nblocks,
-                                                            double count, double lambda, double* __restrict__ out3)
+__device__ __forceinline__ void photo_final(const double* __restrict__ partial, int nblocks, double count, double lambda,
+                                            double* __restrict__ out3, double* smem /*[4]*/)
 {
-    __shared__ double smem[4];
     // 2 x 8 loads in flight per lane and round; the order of the additions is fixed
     double s = 0.0, l = 0.0;
     for (int i0 = threadIdx.x; i0 < nblocks; i0 += 8 * RED_THREADS) {
@@ -415,15 +414,31 @@ __global__ __launch_bounds__(RED_THREADS) void k_photo_final(const double* __res
     }
 }
 
+__global__ __launch_bounds__(RED_THREADS) void k_photo_final(const double* __restrict__ partial, int nblocks,
+                                                            double count, double lambda, double* __restrict__ out3)
+{
+    __shared__ double smem[4];
+    photo_final(partial, nblocks, count, lambda, out3, smem);
+}
+
 // dE/dx = c_l1 sign(x - y) - c_ss (<d_mu1> + 2 x <d_e11> + y <d_e12>),  c_l1 = (1-lambda)/N, c_ss = lambda/N
 __global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ image, const float* __restrict__ target,
                                                   int H, int W, SsimWin win, const float* __restrict__ dmaps,
-                                                  float c_l1, float c_ss, float* __restrict__ dL)
+                                                  float c_l1, float c_ss, float* __restrict__ dL,
+                                                  const double* __restrict__ partial, int nblocks, double count, double lambda,
+                                                  double* __restrict__ out3)
 {
+    static_assert(RED_THREADS == 256, "the loss is finished by a workgroup of this kernel");
     __shared__ __attribute__((aligned(16))) float s_buf[ss_floats(3, 3)];
+    // with out3, the first row of the grid is no block of the image: one of its workgroups finishes the loss
+    const int row0 = out3 ? 1 : 0;
+    if ((int)blockIdx.y < row0) {
+        if (blockIdx.x == 0 && blockIdx.z == 0) photo_final(partial, nblocks, count, lambda, out3, reinterpret_cast<double*>(s_buf));
+        return;
+    }
     float (*const s_in)[SS_IH][SS_IP] = reinterpret_cast<float (*)[SS_IH][SS_IP]>(s_buf);
     float (*const s_h)[SS_HR][SS_TW] = reinterpret_cast<float (*)[SS_HR][SS_TW]>(s_buf);
-    const int x0 = blockIdx.x * SS_TW, y0 = blockIdx.y * SS_TH;
+    const int x0 = blockIdx.x * SS_TW, y0 = ((int)blockIdx.y - row0) * SS_TH;
     const size_t plane = (size_t)blockIdx.z * H * W;
     const float* const maps = dmaps + 3 * plane;
     ss_load<3>([=](size_t row, uint32_t col, float (&v)[3]) {
@@ -588,10 +603,14 @@ hipError_t launch_photo_loss(hipStream_t st, const float* image, const float* ta
     const int nb = photo_blocks(H, W);
     const double count = 3.0 * (double)H * (double)W;
     hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(256), 0, st, image, target, H, W, win, dL ? dmaps : nullptr, partial, nb);
-    if (out3) hipLaunchKernelGGL(k_photo_final, dim3(1), dim3(RED_THREADS), 0, st, partial, nb, count, (double)lambda, out3);
+    // the loss is a few thousand partials, most of whose own launch is waiting: with a gradient it is finished beside it
+    // (a training iteration at 12k Gaussians / 509x337 106.3 -> 103.1 us, 300k / 1332x876 428.0 -> 424.4, 500k / 1600x1064 704.8 -> 700.2)
     if (dL)
-        hipLaunchKernelGGL(k_ssim_bwd, grid, dim3(256), 0, st, image, target, H, W, win, dmaps,
-                           (float)((1.0 - (double)lambda) / count), (float)((double)lambda / count), dL);
+        hipLaunchKernelGGL(k_ssim_bwd, dim3(grid.x, grid.y + (out3 ? 1 : 0), 3), dim3(256), 0, st, image, target, H, W, win, dmaps,
+                           (float)((1.0 - (double)lambda) / count), (float)((double)lambda / count), dL, partial, nb, count,
+                           (double)lambda, out3);
+    else if (out3)
+        hipLaunchKernelGGL(k_photo_final, dim3(1), dim3(RED_THREADS), 0, st, partial, nb, count, (double)lambda, out3);
     return hipGetLastError();
 }
 
