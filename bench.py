@@ -288,8 +288,8 @@ def main() -> int:
     sparse_records = P >= 320 * tiles
     work = {
         "preprocess": ("hbm", n * (12 + g_proj) + n_vis * (g_in - 12)),
-        "emit_pairs": ("hbm", n * 16 + n_vis * 4 + 3 * 4 * tiles * copies + 16 * tiles),
-        "order_pairs": ("hbm", n * 8 + n_vis * (44 + 64) + P * 8 + P * (8 + 12) + 4 * tiles * copies),
+        "emit_pairs": ("hbm", n * 16 + n_vis * 4 + 3 * 4 * tiles * copies + 16 * tiles + n * 8 + n_vis * (40 + 64)),
+        "order_pairs": ("hbm", n * 8 + n_vis * 4 + P * 8 + P * (8 + 12) + 4 * tiles * copies),
         "render_fwd": ("alu", FWD_FLOPS_PER_EVAL * evals + FWD_FLOPS_PER_BLEND * blends),
         "render_bwd": ("alu", BWD_FLOPS_PER_EVAL * evals + BWD_FLOPS_PER_BLEND * blends),
         "preprocess_bwd": ("hbm", (48 * pairs_blended + 2 * R if sparse_records else 48 * R) + n * 8 + n_vis * (g_in + 3) + n * (g_in + 8)),

@@ -155,13 +155,13 @@ def main() -> int:
         c = bench["config"]
         f.write(f"# rocprofv3 summary: {c['workload']} ({c['gaussians']} Gaussians, SH degree {c['sh_degree']}, "
                 f"{c['image'][0]}x{c['image'][1]}, {c['pairs']} pairs)\n\n")
-        f.write("Commands (MI355X box, repository root, after `python -m paper_2511_04283_amd.build`; one run each):\n\n")
-        pre = "    cd /tmp && export TMPDIR=/tmp && cd $GRAFT_REPO_ROOT && rocprofv3 "
-        f.write(f"{pre}--kernel-trace --stats --output-format csv -d gpurun_out/prof/stats -o p -- {cmd}\n")
-        f.write(f"{pre}--pmc FETCH_SIZE --output-format csv -d gpurun_out/prof/fetch -o p -- {cmd}\n")
-        f.write(f"{pre}--pmc WRITE_SIZE --output-format csv -d gpurun_out/prof/write -o p -- {cmd}\n")
+        f.write("Commands (MI355X, repository root, after `python -m paper_2511_04283_amd.build`; one run each):\n\n")
+        pre = "    rocprofv3 "
+        f.write(f"{pre}--kernel-trace --stats --output-format csv -d prof/stats -o p -- {cmd}\n")
+        f.write(f"{pre}--pmc FETCH_SIZE --output-format csv -d prof/fetch -o p -- {cmd}\n")
+        f.write(f"{pre}--pmc WRITE_SIZE --output-format csv -d prof/write -o p -- {cmd}\n")
         if a.sq:
-            f.write(f"{pre}--pmc {SQ_COUNTERS} --output-format csv -d gpurun_out/prof/sq -o p -- {cmd}\n")
+            f.write(f"{pre}--pmc {SQ_COUNTERS} --output-format csv -d prof/sq -o p -- {cmd}\n")
         f.write(f"    python -m paper_2511_04283_amd.profile_summary --config {a.config} --name {a.name} --stats ... --fetch ... "
                 "--write ... --sq ... --bench <the line of the first run>\n\n")
         f.write(f"Durations: `*_kernel_stats.csv` of the first run (averages over all calls of the run).  HBM bytes per launch: "
