@@ -29,11 +29,12 @@ constexpr int SLOTS = 256;        // records a workgroup holds in LDS: one per t
 constexpr int BATCH = SLOTS - 1;  // list entries staged at a time; the last record is the empty one that pads the sub-tile lists
 constexpr int GROUP = 4;          // entries of a sub-tile list that a lane evaluates side by side (one 32-bit word of slots)
 
-// exp(x) for x <= 0: t = x*log2(e); n = rint(t); r = t - n; 2^r by a degree-5 polynomial (Horner, fused), scaled by 2^n.
-// No range clamp: the scaling underflows to zero by itself.
-__device__ __forceinline__ float exp_c(float x)
+// exp(x) for x <= 0, with t = x*log2(e) (exponent_of): n = rint(t); r = t - n; 2^r by a degree-5 polynomial (Horner,
+// fused), scaled by 2^n.  No range clamp: the scaling underflows to zero by itself where t is finite; t = -infinity, which
+// conics at the end of the single-precision range give, would leave a NaN and is what takes_part keeps out.
+__device__ __forceinline__ float exponent_of(float x) { return x * 0x1.715476p+0f; }
+__device__ __forceinline__ float exp_c(float t)
 {
-    const float t = x * 0x1.715476p+0f;
     const float n = __builtin_rintf(t);
     const float r = t - n;
     float p = 0x1.5bba14p-10f;
@@ -43,6 +44,17 @@ __device__ __forceinline__ float exp_c(float x)
     p = __builtin_fmaf(p, r, 0x1.62e42ap-1f);
     p = __builtin_fmaf(p, r, 1.0f);
     return __builtin_ldexpf(p, (int)n);
+}
+// Neither positive nor -infinity.  Class bits: 0, 1 NaNs; 3, 4 negative numbers; 5, 6 zeros.
+constexpr int TAKES_PART = 0x003 | 0x018 | 0x060;
+__device__ __forceinline__ bool takes_part(float t) { return __builtin_amdgcn_classf(t, TAKES_PART); }
+// The same as one bit per lane, in one instruction like the comparison with zero that it stands for (the compiler makes three
+// of a ballot of the above: the render kernels 1 to 2 % slower).
+__device__ __forceinline__ uint64_t takes_part_mask(float t)
+{
+    uint64_t mask;
+    asm("v_cmp_class_f32_e64 %0, %1, %2" : "=s"(mask) : "v"(t), "s"(TAKES_PART));
+    return mask;
 }
 
 // 16-byte streaming (non-temporal) store / load
@@ -391,9 +403,9 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
                 cb[u] = s.r2[j].z;
                 const float dx = p.px - r0.x, dy = p.py - r0.y;
                 const float h = __builtin_fmaf(r0.w, dy, r0.z * dx);
-                const float power = __builtin_fmaf(dx, h, (r1.x * dy) * dy);
-                alpha[u] = fminf(cfg.alpha_max, r1.y * exp_c(power));
-                ok[u] = ballot(!(power > 0.0f)) & ballot(alpha[u] >= cfg.alpha_min);
+                const float t = exponent_of(__builtin_fmaf(dx, h, (r1.x * dy) * dy));
+                alpha[u] = fminf(cfg.alpha_max, r1.y * exp_c(t));
+                ok[u] = takes_part_mask(t) & ballot(alpha[u] >= cfg.alpha_min);
             }
 #pragma unroll
             for (int u = 0; u < GROUP; u++) {
@@ -637,11 +649,11 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
                         const float dx = p.px - r0.x, dy = p.py - r0.y;
                         const float tx = r0.z * dx, ty = r1.x * dy;
                         const float h = __builtin_fmaf(r0.w, dy, tx);
-                        const float power = __builtin_fmaf(dx, h, ty * dy);
-                        const float e = exp_c(power);
+                        const float t = exponent_of(__builtin_fmaf(dx, h, ty * dy));
+                        const float e = exp_c(t);
                         const float sG = r1.y * e;
                         const float al = fminf(cfg.alpha_max, sG);
-                        const uint64_t act = ballot(j < last_here) & ballot(!(power > 0.0f)) & ballot(al >= cfg.alpha_min);
+                        const uint64_t act = ballot(j < last_here) & takes_part_mask(t) & ballot(al >= cfg.alpha_min);
                         const uint64_t capped = ballot(sG > cfg.alpha_max);
                         acted |= act;
                         // lanes that do not blend this Gaussian run the same arithmetic with alpha = G = 0: w and v are
@@ -934,10 +946,10 @@ __global__ __launch_bounds__(256) void k_render_bwd_splat(
                     const float py = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p.py), q));
                     const float dx = px - xy.x, dy = py - xy.y;
                     const float h = __builtin_fmaf(co.y, dy, co.x * dx);
-                    const float power = __builtin_fmaf(dx, h, (co.z * dy) * dy);
-                    bool act = have & (pos_j < last_q) & !(power > 0.0f);
+                    const float t = exponent_of(__builtin_fmaf(dx, h, (co.z * dy) * dy));
+                    bool act = have & (pos_j < last_q) & takes_part(t);
                     if (__ballot(act) == 0) continue;
-                    float G = exp_c(act ? power : 0.0f);
+                    float G = exp_c(act ? t : 0.0f);
                     const float sG = co.w * G;
                     float alpha = fminf(cfg.alpha_max, sG);
                     act = act & (alpha >= cfg.alpha_min);
@@ -1108,14 +1120,14 @@ __global__ __launch_bounds__(256) void k_score(CamDev cam, CfgDev cfg, const uin
                     const float4 a0 = s.r0[j0], b0 = s.r1[j0], a1 = s.r0[j1], b1 = s.r1[j1];
                     const float dx0 = pw.px - a0.x, dy0 = pw.py - a0.y;
                     const float dx1 = pw.px - a1.x, dy1 = pw.py - a1.y;
-                    const float power0 = __builtin_fmaf(dx0, __builtin_fmaf(a0.w, dy0, a0.z * dx0), (b0.x * dy0) * dy0);
-                    const float power1 = __builtin_fmaf(dx1, __builtin_fmaf(a1.w, dy1, a1.z * dx1), (b1.x * dy1) * dy1);
-                    bool act0 = (k < len) & (start + j0 < my_last) & !(power0 > 0.0f);
-                    bool act1 = (k + 1 < len) & (start + j1 < my_last) & !(power1 > 0.0f);
+                    const float t0 = exponent_of(__builtin_fmaf(dx0, __builtin_fmaf(a0.w, dy0, a0.z * dx0), (b0.x * dy0) * dy0));
+                    const float t1 = exponent_of(__builtin_fmaf(dx1, __builtin_fmaf(a1.w, dy1, a1.z * dx1), (b1.x * dy1) * dy1));
+                    bool act0 = (k < len) & (start + j0 < my_last) & takes_part(t0);
+                    bool act1 = (k + 1 < len) & (start + j1 < my_last) & takes_part(t1);
                     if (__ballot(act0 | act1) == 0) continue;
                     // (an inactive entry's exponent may be anything: clamp it so that exp_c stays in range)
-                    const float alpha0 = fminf(cfg.alpha_max, b0.y * exp_c(act0 ? power0 : 0.0f));
-                    const float alpha1 = fminf(cfg.alpha_max, b1.y * exp_c(act1 ? power1 : 0.0f));
+                    const float alpha0 = fminf(cfg.alpha_max, b0.y * exp_c(act0 ? t0 : 0.0f));
+                    const float alpha1 = fminf(cfg.alpha_max, b1.y * exp_c(act1 ? t1 : 0.0f));
                     act0 = act0 & (alpha0 >= cfg.alpha_min);
                     act1 = act1 & (alpha1 >= cfg.alpha_min);
                     const bool hit0 = act0 & (cfg.score_mode == FS_SCORE_ALPHA || alpha0 * T > cfg.alpha_min);
@@ -1148,10 +1160,10 @@ __global__ __launch_bounds__(256) void k_score(CamDev cam, CfgDev cfg, const uin
                 const int j = s.slot(sub, k);
                 const float4 a0 = s.r0[j], b0 = s.r1[j];
                 const float dx = p.px - a0.x, dy = p.py - a0.y;
-                const float power = __builtin_fmaf(dx, __builtin_fmaf(a0.w, dy, a0.z * dx), (b0.x * dy) * dy);
-                bool act = (k < mine) & (start + j < last) & !(power > 0.0f);
+                const float t = exponent_of(__builtin_fmaf(dx, __builtin_fmaf(a0.w, dy, a0.z * dx), (b0.x * dy) * dy));
+                bool act = (k < mine) & (start + j < last) & takes_part(t);
                 if (__ballot(act) == 0) continue;
-                const float alpha = fminf(cfg.alpha_max, b0.y * exp_c(power));
+                const float alpha = fminf(cfg.alpha_max, b0.y * exp_c(t));
                 act = act & (alpha >= cfg.alpha_min);
                 const float w = alpha * T;
                 const bool hit = act & (cfg.score_mode == FS_SCORE_ALPHA || w > cfg.alpha_min);
