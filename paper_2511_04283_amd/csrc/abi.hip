@@ -232,7 +232,7 @@ bool sparse_records(const fs_ctx* ctx, const fs_bins* bins, int tiles)
 }
 
 // The backward pass's per-pair records and, where they are sparse, one flag per record place, all zeros here (a fresh or
-// left-over array is cleared first); the caller clears rec_valid_dirty when k_preprocess_bwd is enqueued.
+// left-over array is cleared first); the caller of a sparse pass clears rec_valid_dirty when k_preprocess_bwd is enqueued.
 int record_buffers(fs_ctx* ctx, const fs_bins* bins, int tiles)
 {
     FS_TRY(ensure(ctx, ctx->pair_grad, (size_t)(bins->num_records ? bins->num_records : 1) * PAIR_REC * sizeof(float),
@@ -716,7 +716,7 @@ int fs_render_bwd(fs_ctx* ctx, const fs_gaussians* g, const fs_camera* cam, cons
                                  bins->record_counts ? bins->record_counts : proj->tiles_touched, bins->record_offsets,
                                  pair_grad, rec_valid, *out),
            "k_preprocess_bwd");
-    ctx->rec_valid_dirty = false;
+    if (rec_valid) ctx->rec_valid_dirty = false;   // (a dense pass leaves the flags as they are)
     return FS_OK;
 }
 
@@ -1065,7 +1065,7 @@ int fs_train_step(fs_ctx* ctx, const fs_train_state* t, const fs_camera* cam, co
                                                pair_grad, rec_valid, at_once ? BWD_UPDATE : BWD_SUM, dev),
                    "k_preprocess_bwd");
         }
-        ctx->rec_valid_dirty = false;
+        if (rec_valid) ctx->rec_valid_dirty = false;
         if (prm->update && prm->sum) {
             const int64_t K = (int64_t)(t->sh_degree + 1) * (t->sh_degree + 1);
             const int64_t count[5] = {3 * n, 3 * K * n, 3 * n, 4 * n, n};

@@ -1,0 +1,109 @@
+// A GPU that is host memory, for tests of the order and the bookkeeping of abi.hip's launches on the CPU: the HIP calls it
+// makes and the launchers it calls, each as little as the test needs.  Linked against abi.hip's host code.
+#include <stdlib.h>
+#include <string.h>
+
+#include "common.hpp"
+
+extern "C" {
+// what the test sets ...
+int stub_fail_preprocess_bwd = 0;   // the next launch of k_preprocess_bwd fails
+int64_t stub_pairs = 0;             // pairs of every view
+// ... and reads: flags found set when k_render_bwd is launched
+int64_t stub_stale_flags = -1;
+
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "stub"; }
+hipError_t hipMalloc(void** p, size_t bytes)
+{
+    *p = malloc(bytes);
+    memset(*p, 1, bytes);   // (fresh device memory holds anything)
+    return hipSuccess;
+}
+hipError_t hipFree(void* p) { free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) { *p = calloc(1, bytes); return hipSuccess; }
+hipError_t hipHostFree(void* p) { free(p); return hipSuccess; }
+hipError_t hipMemset(void* p, int v, size_t bytes) { memset(p, v, bytes); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t bytes, hipMemcpyKind, hipStream_t) { memcpy(d, s, bytes); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { *e = nullptr; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = nullptr; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void* s) { *p = const_cast<void*>(s); return hipSuccess; }
+void** __hipRegisterFatBinary(const void*) { return nullptr; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterVar(void**, void*, char*, const char*, int, size_t, int, int) {}
+}
+
+namespace fs {
+
+size_t scan_tmp_bytes(int64_t) { return 64; }
+int photo_blocks(int, int) { return 1; }
+int mask_partials() { return 1; }
+AdamArgs adam_args(float, float, float, float, int, float) { return {}; }
+int tile_sort_variants(int64_t, bool, int) { return 1; }
+
+hipError_t launch_fill_u32(hipStream_t, uint32_t* p, uint32_t v, int64_t n)
+{
+    for (int64_t i = 0; i < n; i++) p[i] = v;
+    return hipSuccess;
+}
+hipError_t launch_preprocess(hipStream_t, int64_t, int, const fs_gaussians&, bool, const CamDev&, const CfgDev&, const fs_projected&)
+{
+    return hipSuccess;
+}
+hipError_t launch_tile_count(hipStream_t, int64_t, const fs_projected&, const CfgDev&, int, int, uint32_t*, uint32_t*, uint2*, uint32_t*,
+                             uint64_t* totals, uint32_t*, uint32_t*, uint64_t*, float*)
+{
+    totals[0] = totals[1] = totals[2] = (uint64_t)stub_pairs;
+    totals[3] = 1;
+    return hipSuccess;
+}
+hipError_t launch_tile_scatter(hipStream_t, int64_t, const fs_projected&, const CfgDev&, const uint32_t*, int, int, uint32_t, uint32_t,
+                               const uint2*, uint32_t*, uint64_t*, float*)
+{
+    return hipSuccess;
+}
+hipError_t launch_tile_sorts(hipStream_t, int, int, uint32_t, const uint2*, const uint32_t*, const uint64_t*, uint64_t*, uint32_t*)
+{
+    return hipSuccess;
+}
+hipError_t launch_render_fwd(hipStream_t, const CamDev&, const CfgDev&, const uint32_t*, const uint32_t*, const uint32_t*, const float*,
+                             float*, float*, uint32_t*, const ScoreRecord&)
+{
+    return hipSuccess;
+}
+hipError_t launch_photo_loss(hipStream_t, const float*, const float*, int, int, float, float*, double*, float*, double*) { return hipSuccess; }
+
+// every pair's flag is set, as where every pair has received something
+hipError_t launch_render_bwd(hipStream_t, const CamDev&, const CfgDev&, const uint32_t*, const uint32_t*, const uint32_t*, const float*,
+                             const float*, const uint32_t*, const float*, float*, uint8_t* rec_valid, bool, bool)
+{
+    if (!rec_valid) return hipSuccess;
+    stub_stale_flags = 0;
+    for (int64_t i = 0; i < stub_pairs; i++) { stub_stale_flags += rec_valid[i]; rec_valid[i] = 1; }
+    return hipSuccess;
+}
+static hipError_t clear_flags(uint8_t* rec_valid)
+{
+    if (stub_fail_preprocess_bwd) { stub_fail_preprocess_bwd = 0; return hipErrorUnknown; }
+    if (rec_valid) memset(rec_valid, 0, (size_t)stub_pairs);
+    return hipSuccess;
+}
+hipError_t launch_preprocess_bwd(hipStream_t, int64_t, int, const fs_gaussians&, const CamDev&, const CfgDev&, const uint8_t*, const uint32_t*,
+                                 const uint32_t*, const uint32_t*, const float*, uint8_t* rec_valid, const fs_grads&)
+{
+    return clear_flags(rec_valid);
+}
+hipError_t launch_preprocess_bwd_train(hipStream_t, int64_t, int, const fs_gaussians&, const CamDev&, const CfgDev&, const uint8_t*,
+                                       const uint32_t*, const uint32_t*, const uint32_t*, const float*, uint8_t* rec_valid, BwdOut,
+                                       const TrainDev&)
+{
+    return clear_flags(rec_valid);
+}
+
+}  // namespace fs

@@ -1,0 +1,84 @@
+"""What a context's bookkeeping says after a call that failed half way, on the CPU: abi.hip's host code on a stub of the GPU
+(host_abi_stub.cpp) whose launches and allocations fail on request."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    if not os.path.exists(HIPCC) or not shutil.which("objcopy"):
+        pytest.skip("no hipcc / objcopy")
+    out = str(tmp_path_factory.mktemp("stub"))
+    csrc = os.path.join(ROOT, "paper_2511_04283_amd", "csrc")
+    flags = ["-x", "hip", "--offload-arch=gfx950", "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-w", "-I", csrc, "-I",
+             os.path.join(ROOT, "include")]
+    for name, src in (("abi", os.path.join(csrc, "abi.hip")), ("stub", os.path.join(ROOT, "tests", "host_abi_stub.cpp"))):
+        subprocess.run([HIPCC, *flags, "-c", src, "-o", f"{out}/{name}.o"], check=True)
+    # (launchers that no test here reaches, and the device code, stay undefined: weak, so that the library loads without them)
+    subprocess.run(["objcopy", "--wildcard", "--weaken-symbol=_ZN2fs*", "--weaken-symbol=__hip_fatbin*", f"{out}/abi.o"], check=True)
+    subprocess.run(["g++", "-shared", "-Wl,-Bsymbolic", "-o", f"{out}/libstub.so", f"{out}/abi.o", f"{out}/stub.o"], check=True)
+    return ctypes.CDLL(f"{out}/libstub.so")
+
+
+class Ctx:
+    """A context on the stub and the arguments of its calls (arrays nobody reads)."""
+
+    def __init__(self, lib, pairs):
+        from paper_2511_04283_amd import binding as B
+        self.B, self.lib, self.h = B, lib, ctypes.c_void_p()
+        lib.fs_last_error.restype = ctypes.c_char_p
+        assert lib.fs_create(ctypes.byref(self.h), 0, None, None) == B.FS_OK
+        self.room = ctypes.create_string_buffer(1 << 16)
+        some = (ctypes.addressof(self.room) + 15) // 16 * 16
+        fill = lambda s, names: [setattr(s, k, some) for k in names] and s
+        self.cam = B.fs_camera(width=32, height=16, fx=16.0, fy=16.0)
+        self.g = fill(B.fs_gaussians(n=1, sh_degree=0), ("means", "scales", "quats", "opacities", "sh"))
+        self.proj = fill(B.fs_projected(), [f for f, _ in B.fs_projected._fields_])
+        self.grads = fill(B.fs_grads(), ("dmeans", "dscales", "dquats", "dopacities", "dsh", "dmean2d"))
+        five = (ctypes.c_void_p * 5)(*[some] * 5)
+        self.state = B.fs_train_state(1, 0, five, five, five, five, some, some, some)
+        self.some = ctypes.c_void_p(some)
+        self.pairs(pairs)
+
+    def pairs(self, n):
+        ctypes.c_int64.in_dll(self.lib, "stub_pairs").value = n
+
+    def backward(self, mode):
+        """fs_bin_sort and fs_render_bwd; the flags that were set when its first kernel was launched, or the status."""
+        b = self.B.fs_bins()
+        r = ctypes.byref
+        self.lib.fs_set_record_mode(self.h, mode)
+        rc = self.lib.fs_bin_sort(self.h, r(self.proj), r(self.cam), ctypes.c_int64(1), r(b))
+        if rc == self.B.FS_OK:
+            rc = self.lib.fs_render_bwd(self.h, r(self.g), r(self.cam), r(self.proj), r(b), self.some, self.some, self.some,
+                                        r(self.grads))
+        return rc or ctypes.c_int64.in_dll(self.lib, "stub_stale_flags").value
+
+    def train(self, mode):
+        prm = self.B.fs_train_params(0.2, (ctypes.c_float * 5)(), 0.9, 0.999, 1e-15, 1, 0, 1)
+        out3 = (ctypes.c_double * 3)()
+        r = ctypes.byref
+        self.lib.fs_set_record_mode(self.h, mode)
+        rc = self.lib.fs_train_step(self.h, r(self.state), r(self.cam), self.some, r(prm), out3)
+        return rc or ctypes.c_int64.in_dll(self.lib, "stub_stale_flags").value
+
+
+@pytest.mark.parametrize("call", ["backward", "train"])
+def test_flags_left_by_a_failed_backward_outlive_a_dense_one(stub, call):
+    """A sparse backward pass that fails behind its first kernel leaves flags; a dense one in between does not touch them, so
+    the next sparse one has to clear them."""
+    c = Ctx(stub, pairs=100)
+    step, B = getattr(c, call), c.B
+    assert step(B.FS_RECORDS_SPARSE) == 0
+    ctypes.c_int.in_dll(stub, "stub_fail_preprocess_bwd").value = 1
+    assert step(B.FS_RECORDS_SPARSE) == -3   # FS_EHIP
+    step(B.FS_RECORDS_DENSE)
+    assert step(B.FS_RECORDS_SPARSE) == 0    # not 100
+    stub.fs_destroy(c.h)
