@@ -238,7 +238,9 @@ int record_buffers(fs_ctx* ctx, const fs_bins* bins, int tiles)
     FS_TRY(ensure(ctx, ctx->pair_grad, (size_t)(bins->num_records ? bins->num_records : 1) * PAIR_REC * sizeof(float),
                   "pair gradients"));
     if (!sparse_records(ctx, bins, tiles)) return FS_OK;
-    FS_TRY(ensure(ctx, ctx->rec_valid, ((size_t)(bins->num_records ? bins->num_records : 1) + 3) / 4 * 4, "record flags"));
+    const size_t flags = ((size_t)(bins->num_records ? bins->num_records : 1) + 3) / 4 * 4;
+    if (flags > ctx->rec_valid.cap) ctx->rec_valid_zeroed = 0;   // (also where growing fails: a later array may have the old size)
+    FS_TRY(ensure(ctx, ctx->rec_valid, flags, "record flags"));
     if (ctx->rec_valid_zeroed != ctx->rec_valid.cap || ctx->rec_valid_dirty) {
         FS_HIP(launch_fill_u32(ctx->stream, static_cast<uint32_t*>(ctx->rec_valid.ptr), 0u, (int64_t)(ctx->rec_valid.cap / 4)), "k_fill_u32");
         ctx->rec_valid_zeroed = ctx->rec_valid.cap;

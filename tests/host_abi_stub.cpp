@@ -8,6 +8,7 @@
 extern "C" {
 // what the test sets ...
 int stub_fail_preprocess_bwd = 0;   // the next launch of k_preprocess_bwd fails
+size_t stub_fail_malloc_of = 0;     // allocations of this size fail (0: none does)
 int64_t stub_pairs = 0;             // pairs of every view
 // ... and reads: flags found set when k_render_bwd is launched
 int64_t stub_stale_flags = -1;
@@ -17,6 +18,7 @@ hipError_t hipGetLastError() { return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "stub"; }
 hipError_t hipMalloc(void** p, size_t bytes)
 {
+    if (bytes == stub_fail_malloc_of) return hipErrorOutOfMemory;
     *p = malloc(bytes);
     memset(*p, 1, bytes);   // (fresh device memory holds anything)
     return hipSuccess;

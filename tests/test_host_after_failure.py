@@ -82,3 +82,22 @@ def test_flags_left_by_a_failed_backward_outlive_a_dense_one(stub, call):
     step(B.FS_RECORDS_DENSE)
     assert step(B.FS_RECORDS_SPARSE) == 0    # not 100
     stub.fs_destroy(c.h)
+
+
+@pytest.mark.parametrize("call", ["backward", "train"])
+def test_flags_after_their_array_failed_to_grow(stub, call):
+    """The array of flags is given back before a larger one is asked for; where that fails, the next one may have the old
+    one's size, and holds anything."""
+    c = Ctx(stub, pairs=100)
+    step, B = getattr(c, call), c.B
+    assert step(B.FS_RECORDS_SPARSE) == 0
+    c.pairs(30_000)
+    step(B.FS_RECORDS_DENSE)                 # (every other array grows here)
+    fail = ctypes.c_size_t.in_dll(stub, "stub_fail_malloc_of")
+    fail.value = 32768
+    assert step(B.FS_RECORDS_SPARSE) == -2   # FS_ENOMEM
+    fail.value = 0
+    assert b"record flags" in stub.fs_last_error(c.h)
+    c.pairs(100)
+    assert step(B.FS_RECORDS_SPARSE) == 0    # not 100
+    stub.fs_destroy(c.h)
