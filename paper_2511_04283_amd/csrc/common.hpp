@@ -126,7 +126,10 @@ __device__ __forceinline__ float4 support_octagon(const float4& co /* a, b, c, s
 
 // A needle: a splat at least some thirty times as long as wide (the ratio of the eigenvalues of Sigma_2D, which is about
 // (a + c)^2 / det, above 1000).  What its scales and rotation receive is the small difference of large second moments, down to
-// a millionth of them, so the order in which k_render_bwd adds those up is kept for needles whatever it does for the others.
+// a millionth of them, so any other order of the additions in k_render_bwd shows in their first digits, an equally accurate
+// one too: for needles the order is fixed, pixel by pixel, whatever it is for the others.  (3 M Gaussians, scales from
+// N(-5, 1.2): from one equally accurate order to another the gradients move by 1e-4 to 3e-4 of their norm where no needles are told
+// apart, by 2e-5 where those from 10 000 on are, by 1e-5 with those from 1000 on.)
 constexpr uint32_t NEEDLE = 0x80000000u;   // (in a splat record: a bit of its first gradient record's number, which is below 2^31)
 __device__ __forceinline__ bool is_needle(const float4& co /* a, b, c, sigma */)
 {

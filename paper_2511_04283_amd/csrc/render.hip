@@ -503,14 +503,16 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
 // wavefront writes its 8 x 64 w's (then its v's) to LDS and reads them back with the 32 (entry, row) combinations across its
 // lanes, two lanes to a combination and eight pixels to a lane.  The sums over pixels are then plain additions within a
 // lane -- separable ones for the moments, since x and y take four values each -- plus one exchange between the two lanes:
-// 11 instructions per entry instead of 41.  (The matrix cores do not help: v_mfma_f32_16x16x4_f32 keeps the vector unit
+// 12 instructions per entry instead of 41.  (The matrix cores do not help: v_mfma_f32_16x16x4_f32 keeps the vector unit
 // from issuing for its 32 cycles, and forms many sums nobody wants; measured between the two.)
 // Before and after, in us: 4k Gaussians at 128x128 41 and 30, 100k at 980x545 119 and 82, 500k at 1600x1064 308 and 245 (with
 // ABS 336 and 262), 3 M at 1920x1080 730 and 565.
 //
-// Places are relative to the sub-tile's centre; a Gaussian's moments about its own centre mu follow from them with the
-// offset of the two, before sub-tiles are added up: both numbers are a few pixels where the Gaussian is small, so nothing is
-// lost by cancellation.  Places, offsets and so moments are in half pixels (x = -3, -1, 1, 3), which the flush undoes.
+// Places are relative to mu itself, as one subtraction per column and line: a line's sums of v, v dx, v dx^2, then dy and dy^2
+// times those.  (Sums about the sub-tile's centre, shifted to mu afterwards, take 8 of the 48 instructions per exchange less
+// and cancel: 3 to 9 times the rounding error for splats below two pixels.)  The flush works in double and rounds once.
+// Measured against exact sums on splats with a tile to themselves, dL/dconic: 8.2e-8 at the low-pass floor (5.6e-7 with the
+// shift, 8.6e-8 with products per pixel added over 16 lanes), 8.8e-8 at eigenvalues 2 and 4 (1.6e-7, 9.5e-8).
 //
 // Every Gaussian-tile pair owns one record of PAIR_REC floats in `pair_grad`, at the position the
 // pair had when it was emitted (pair_offsets[g] + its place in g's tile rectangle): the flush is a
@@ -571,7 +573,6 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
     const int row = lane & 3, ent = (lane >> 2 & 1) | (lane >> 4) << 1;
     const bool second = lane & 8;
     const int q1 = ((lane >> 3 ^ lane >> 2) & 1) + (row & 2), q2 = q1 ^ 2;
-    const float y1 = (float)(2 * q1 - 3), y2 = (float)(2 * q2 - 3);
     const int sub_x = (tile % cam.tiles_x) * TILE + (wave & 1) * 8 + (row & 1) * 4;
     const int sub_y = (tile / cam.tiles_x) * TILE + (wave >> 1) * 8 + (row >> 1) * 4;
     float g1[3][4], g2[3][4];   // the lines' dL/dC
@@ -583,7 +584,8 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
             g1[ch][c] = x < cam.width && sub_y + q1 < cam.height ? dL_dimage[ch * hw + (size_t)(sub_y + q1) * cam.width + x] : 0.f;
             g2[ch][c] = x < cam.width && sub_y + q2 < cam.height ? dL_dimage[ch * hw + (size_t)(sub_y + q2) * cam.width + x] : 0.f;
         }
-    const float centre_x = (float)(2 * sub_x + 4), centre_y = (float)(2 * sub_y + 4);   // of the row's sub-tile, in half pixels
+    const float px0 = (float)sub_x + 0.5f;   // centres of the first column, of the lines
+    const float py1 = (float)(sub_y + q1) + 0.5f, py2 = (float)(sub_y + q2) + 0.5f;
     const uint8_t* const ent_list = reinterpret_cast<const uint8_t*>(s.list[wave * 4 + row]) + ent;
     float* const turn = &s_turn[wave][0][lane];
     const float4* const turned = reinterpret_cast<const float4*>(&s_turn[wave][0][0]) + ent * 16 + row * 4;
@@ -597,6 +599,11 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
         l2 = turned[q2];
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
+    };
+    auto column = [&](int c) {   // (formed where it is used: kept, the four of them spill registers of the ABS kernel)
+        float x = px0;
+        asm volatile("" : "+v"(x));
+        return x + (float)c;
     };
     auto both = [](float v) {   // the sum of the two lanes of a combination, in both
         constexpr int ROR8 = 0x128;
@@ -699,45 +706,40 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
                                    __builtin_fmaf(a.y, g1[ch][1], a.x * g1[ch][0]))))))));
             exchange(v, a, b);
             {
-                // a line's sums of v, x v, x^2 v with x = -3, -1, 1, 3
-                const float ao = a.x + a.w, ai = a.y + a.z, bo = b.x + b.w, bi = b.y + b.z;
-                const float a0 = ao + ai, b0 = bo + bi;
-                const float a1 = __builtin_fmaf(3.0f, a.w - a.x, a.z - a.y), b1 = __builtin_fmaf(3.0f, b.w - b.x, b.z - b.y);
-                const float m00 = both(a0 + b0), m10 = both(a1 + b1);
-                const float m20 = both(__builtin_fmaf(9.0f, ao, ai) + __builtin_fmaf(9.0f, bo, bi));
-                const float ya = y1 * a0, yb = y2 * b0;
-                const float m01 = both(ya + yb), m02 = both(__builtin_fmaf(y1, ya, y2 * yb));
-                const float m11 = both(__builtin_fmaf(y1, a1, y2 * b1));
-                // about mu: with (ox, oy) the sub-tile's centre seen from mu, sum (x + ox) v = m10 + ox m00 and so on
-                const float ox = __builtin_fmaf(-2.0f, mu_x, centre_x), oy = __builtin_fmaf(-2.0f, mu_y, centre_y);
-                const float dx = __builtin_fmaf(ox, m00, m10), dy = __builtin_fmaf(oy, m00, m01);
-                sums0[DSIGMA] = m00;
-                sums1[DX - HALF] = dx;
-                sums1[DY - HALF] = dy;
-                sums1[DXX - HALF] = __builtin_fmaf(ox, m10 + dx, m20);
-                sums1[DYY - HALF] = __builtin_fmaf(oy, m01 + dy, m02);
-                sums1[DXY - HALF] = __builtin_fmaf(oy, dx, __builtin_fmaf(ox, m01, m11));
+                const float dx[4] = {px0 - mu_x, column(1) - mu_x, column(2) - mu_x, column(3) - mu_x}, dy1 = py1 - mu_y, dy2 = py2 - mu_y;
+                const float dxx[4] = {dx[0] * dx[0], dx[1] * dx[1], dx[2] * dx[2], dx[3] * dx[3]};
+                auto along = [](const float4& l, const float (&d)[4]) {
+                    return __builtin_fmaf(l.w, d[3], __builtin_fmaf(l.z, d[2], __builtin_fmaf(l.y, d[1], l.x * d[0])));
+                };
+                const float a0 = (a.x + a.y) + (a.z + a.w), b0 = (b.x + b.y) + (b.z + b.w);
+                const float a1 = along(a, dx), b1 = along(b, dx);
+                const float ya = dy1 * a0, yb = dy2 * b0;
+                sums0[DSIGMA] = both(a0 + b0);
+                sums1[DX - HALF] = both(a1 + b1);
+                sums1[DY - HALF] = both(ya + yb);
+                sums1[DXX - HALF] = both(along(a, dxx) + along(b, dxx));
+                sums1[DYY - HALF] = both(__builtin_fmaf(dy1, ya, dy2 * yb));
+                sums1[DXY - HALF] = both(__builtin_fmaf(dy1, a1, dy2 * b1));
             }
             // needles: dL/dq times dx^2, dx dy, dy^2 pixel by pixel, added in the order of a balanced tree over the lines and
-            // their pixels (7 instructions more per entry; 500k Gaussians: one exchange in ten has one).  The v's are read
-            // from LDS once more, so that the common path does not hold them in registers.
+            // their pixels (500k Gaussians: one exchange in ten has one).  The v's are read from LDS once more, so that the common
+            // path does not hold them in registers.
             if (ballot(needle) != 0) {
                 const float gq = -0.5f * s.r1[slot].y;
                 float xx = 0.f, xy = 0.f, yy = 0.f;
 #pragma unroll
                 for (int l = 0; l < 2; l++) {
-                    const int line = l ? q2 : q1;
-                    const float4 v4 = turned[line];
-                    const float py = (float)(sub_y + line) + 0.5f - mu_y;
+                    const float4 v4 = turned[l ? q2 : q1];
+                    const float dy = (l ? py2 : py1) - mu_y;
                     const float vv[4] = {v4.x, v4.y, v4.z, v4.w};
                     float pxx[4], pxy[4], pyy[4];
 #pragma unroll
                     for (int c = 0; c < 4; c++) {
-                        const float px = (float)(sub_x + c) + 0.5f - mu_x;
-                        const float gv = gq * vv[c], gx = gv * px, gy = gv * py;
-                        pxx[c] = gx * px;
-                        pxy[c] = gx * py;
-                        pyy[c] = gy * py;
+                        const float dx = column(c) - mu_x;
+                        const float gv = gq * vv[c], gx = gv * dx, gy = gv * dy;
+                        pxx[c] = gx * dx;
+                        pxy[c] = gx * dy;
+                        pyy[c] = gy * dy;
                     }
                     // (lines 0 and 1, then 2 and 3, or the other way round)
                     xx = xx + both((pxx[0] + pxx[1]) + (pxx[2] + pxx[3]));
@@ -764,30 +766,31 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
         }
         __syncthreads();
         if ((int)threadIdx.x < m) {
-            float a[NV];
+            acc_t a[NV];
 #pragma unroll
-            for (int k = 0; k < NV; k++) a[k] = (float)s_acc[threadIdx.x][k];
+            for (int k = 0; k < NV; k++) a[k] = s_acc[threadIdx.x][k];
             // SPARSE: a pair that received nothing (blended at no pixel of the tile) leaves no record; its flag stays 0
             // and k_preprocess_bwd does not read the record's place
             bool any = !SPARSE;
             if (SPARSE) {
 #pragma unroll
-                for (int k = 0; k < NV; k++) any = any | (a[k] != 0.f);
+                for (int k = 0; k < NV; k++) any = any | (a[k] != (acc_t)0);
             }
             if (any) {
                 const float4 f0 = s.r0[threadIdx.x];
                 const float2 f1 = make_float2(s.r1[threadIdx.x].x, s.r1[threadIdx.x].y);
-                const float gq = -0.5f * f1.y;                                            // dL/dq = -1/2 sigma G dL/dalpha
                 const float3 co = make_float3(-2.0f * f0.z, -2.0f * f0.w, -2.0f * f1.x);  // (a, 2b, c)
-                const float mx = 0.5f * gq * a[DX], my = 0.5f * gq * a[DY];               // (half pixels)
+                const acc_t sigma = f1.y, gq = -0.5 * sigma;                              // dL/dq = -1/2 sigma G dL/dalpha
+                const float mx = (float)(gq * a[DX]), my = (float)(gq * a[DY]);
                 const uint32_t idx = __float_as_uint(s.r2[threadIdx.x].w) & ~NEEDLE;
                 float4* rec = pair_grad + (size_t)idx * (PAIR_REC / 4);
-                rec[0] = make_float4(a[DR], a[DG], a[DB], a[DSIGMA]);
+                rec[0] = make_float4((float)a[DR], (float)a[DG], (float)a[DB], (float)a[DSIGMA]);
                 // d = p - mu  =>  dq/dmu = -(2 a dx + 2b dy, 2b dx + 2 c dy)
-                const bool needle = __float_as_uint(s.r2[threadIdx.x].w) & NEEDLE;
-                const float second = needle ? 1.0f : 0.25f * gq;   // (a needle's second moments are in pixels, times dL/dq)
-                rec[1] = make_float4(second * a[DXX], 2.0f * second * a[DXY], second * a[DYY], -(2.0f * co.x * mx + co.y * my));
-                rec[2] = make_float4(-(co.y * mx + 2.0f * co.z * my), ABS ? f1.y * a[DABS_X] : 0.f, ABS ? f1.y * a[DABS_Y] : 0.f, 0.f);
+                const acc_t second = __float_as_uint(s.r2[threadIdx.x].w) & NEEDLE ? 1.0 : gq;   // (a needle's come times dL/dq)
+                rec[1] = make_float4((float)(second * a[DXX]), (float)(2.0 * second * a[DXY]), (float)(second * a[DYY]),
+                                     -(2.0f * co.x * mx + co.y * my));
+                rec[2] = make_float4(-(co.y * mx + 2.0f * co.z * my), ABS ? (float)(sigma * a[DABS_X]) : 0.f,
+                                     ABS ? (float)(sigma * a[DABS_Y]) : 0.f, 0.f);
                 if (SPARSE) rec_valid[idx] = 1;
             }
         }
