@@ -369,9 +369,9 @@ __device__ __forceinline__ float wave_sum_to_last(float v)
 // TB/s); 300k, summing: 110 us in eight launches, 64 in this one.
 template <int DEG, bool SPARSE, BwdOut OUT>
 __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
-    int64_t n, const float* means, const float* __restrict__ scales, const float* __restrict__ quats,
-    const float* __restrict__ opac, const float* sh, CamDev cam, CfgDev cfg,
-    const uint8_t* __restrict__ clamped, const uint32_t* __restrict__ touched,
+    int64_t n, const float* means, const float* scales, const float* quats,
+    const float* opac, const float* sh /* (the five of them are train.p in a training iteration, written there: no __restrict__) */,
+    CamDev cam, CfgDev cfg, const uint8_t* __restrict__ clamped, const uint32_t* __restrict__ touched,
     const uint32_t* __restrict__ rec_counts, const uint32_t* __restrict__ offsets,
     const float4* __restrict__ pair_grad, uint8_t* __restrict__ rec_valid, float* __restrict__ d_means,
     float* __restrict__ d_scales,
