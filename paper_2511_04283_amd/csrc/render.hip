@@ -260,19 +260,22 @@ __device__ __forceinline__ uint64_t ballot(bool v) { return __builtin_amdgcn_bal
 __device__ __forceinline__ bool lane_of(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
 // Where `mask` has a lane's bit: C += w c, T = Tn, last = at.  Five vector instructions under the lane mask, where selects
-// would take two more, and no branch in the way of the instructions around them.  Called with all 64 lanes active.
+// would take two more, and no branch in the way of the instructions around them.  Whichever lanes are active stay so: the mask is
+// taken out of them and they are put back.  (Outputs are written before all inputs have been read: they share no registers.)
 __device__ __forceinline__ void blend_under_mask(uint64_t mask, float& C0, float& C1, float& C2, float& T, int& last, float c0,
                                                  float c1, float c2, float w, float Tn, int at)
 {
-    asm("s_mov_b64 exec, %[m]\n\t"
+    uint64_t active;
+    asm("s_and_saveexec_b64 %[active], %[m]\n\t"
         "v_fmac_f32_e32 %[C0], %[c0], %[w]\n\t"
         "v_fmac_f32_e32 %[C1], %[c1], %[w]\n\t"
         "v_fmac_f32_e32 %[C2], %[c2], %[w]\n\t"
         "v_mov_b32_e32 %[T], %[Tn]\n\t"
         "v_mov_b32_e32 %[l], %[at]\n\t"
-        "s_mov_b64 exec, -1"
-        : [C0] "+v"(C0), [C1] "+v"(C1), [C2] "+v"(C2), [T] "+v"(T), [l] "+v"(last)
-        : [m] "s"(mask), [c0] "v"(c0), [c1] "v"(c1), [c2] "v"(c2), [w] "v"(w), [Tn] "v"(Tn), [at] "s"(at));
+        "s_mov_b64 exec, %[active]"
+        : [C0] "+&v"(C0), [C1] "+&v"(C1), [C2] "+&v"(C2), [T] "+&v"(T), [l] "+&v"(last), [active] "=&s"(active)
+        : [m] "s"(mask), [c0] "v"(c0), [c1] "v"(c1), [c2] "v"(c2), [w] "v"(w), [Tn] "v"(Tn), [at] "s"(at)
+        : "scc");
 }
 
 // Longest of the four sub-tile lists of the calling wavefront (`mine` is uniform within a row).

@@ -17,3 +17,22 @@ def test_parameters_that_a_training_iteration_writes_are_not_restrict():
     for name in ("means", "scales", "quats", "opac", "sh"):
         declared = [a.strip() for a in signature.split(",") if a.split()[-1] == name]
         assert declared == [f"const float* {name}"], declared
+
+
+def test_inline_assembly_gives_back_the_lanes_it_found():
+    """Assembly that narrows the lane mask saves the one it found and restores that, not a constant: it may stand where some
+    lanes are inactive."""
+    seen = 0
+    for path in sorted(glob.glob(os.path.join(CSRC, "*.h*"))):
+        for block in re.findall(r"\basm\b[^;]*;", open(path).read()):
+            code = "".join(re.findall(r'"([^"]*)"', block))
+            if not re.search(r"\bexec\b|saveexec", code):
+                continue
+            seen += 1
+            steps = [line.strip() for line in code.replace("\\t", "").split("\\n")]
+            saved = re.match(r"s_and_saveexec_b64 (%\[\w+\]), ", steps[0])
+            assert saved, (path, steps[0])
+            restored = steps[-1].split("=")[0]
+            assert restored.startswith(f"s_mov_b64 exec, {saved.group(1)}"), (path, restored)
+            assert not any("exec" in line for line in steps[1:-1]), path
+    assert seen == 1
