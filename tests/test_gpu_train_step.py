@@ -11,27 +11,23 @@ pytestmark = pytest.mark.gpu
 LR = dict(means=1e-3, sh=2e-3, raw_scales=5e-3, raw_quats=1e-3, raw_opacities=5e-2)
 
 
-@pytest.mark.parametrize("compact,records", [(1, "dense"), (0, "sparse")])
-@pytest.mark.parametrize("deg", [0, 1, 2, 3])
-@pytest.mark.parametrize("n", [1, 33, 97, 611])
-def test_train_step_equals_the_calls_it_replaces(n, deg, compact, records):
+SCHEDULE = [(False, True), (False, True), (True, False), (True, False), (True, True), (False, True)]   # (sums, update)
+
+
+def compare_with_the_calls(c, sc, deg, views):
+    """A training iteration per (camera, sums, update), each way on its own copy of the state; the statistics' view counts."""
     import torch
     from paper_2511_04283_amd import binding as B
     from paper_2511_04283_amd.trainer import GROUPS, TrainConfig, Trainer
-    cfg = B.default_config()
-    cfg.compact_box = compact
-    c = B.Context("cuda:0", cfg)
-    c.fs_set_record_mode(B.FS_RECORDS_DENSE if records == "dense" else B.FS_RECORDS_SPARSE)
-    sc = scenes.tiny_scene(40 + n, n, 83, 50, sh_degree=deg, log_scale=(-2.3, 0.6), spread=1.3)
-    cam, fcam = sc.cameras[0], B.make_camera(sc.cameras[0])
     t = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).to(c.device)
-    target = t(np.random.default_rng(n).uniform(0, 1, (3, cam.height, cam.width)))
     tr = Trainer(c, t(sc.means), t(sc.scales), t(sc.quats * 1.7), t(sc.opacities), t(sc.sh), deg, TrainConfig(lr=LR, eps=1e-8))
     copy = lambda d: {k: v.clone() for k, v in d.items()}
     p, m, v, acc = copy(tr.p), copy(tr.m), copy(tr.v), copy(tr.acc)
     ga, aa, den = tr.grad_accum.clone(), tr.abs_accum.clone(), tr.denom.clone()
     updates = 0
-    for it, (sums, update) in enumerate([(False, True), (False, True), (True, False), (True, False), (True, True), (False, True)]):
+    for it, (cam, sums, update) in enumerate(views):
+        fcam = B.make_camera(cam)
+        target = t(np.random.default_rng(sc.n).uniform(0, 1, (3, cam.height, cam.width)))
         s, q, o = c.fs_activate(p["raw_scales"], p["raw_quats"], p["raw_opacities"])
         g = B.Gaussians(p["means"], s, q, o, p["sh"], deg)
         proj = c.fs_preprocess(g, fcam)
@@ -56,7 +52,54 @@ def test_train_step_equals_the_calls_it_replaces(n, deg, compact, records):
             for k in GROUPS:
                 assert torch.equal(a[k], b[k]), (it, k)
         assert torch.equal(tr.grad_accum, ga) and torch.equal(tr.abs_accum, aa) and torch.equal(tr.denom, den), it
+    return den
+
+
+def context(compact, records):
+    from paper_2511_04283_amd import binding as B
+    cfg = B.default_config()
+    cfg.compact_box = compact
+    c = B.Context("cuda:0", cfg)
+    c.fs_set_record_mode(B.FS_RECORDS_DENSE if records == "dense" else B.FS_RECORDS_SPARSE)
+    return c
+
+
+@pytest.mark.parametrize("compact,records", [(1, "dense"), (0, "sparse"), (1, "sparse"), (0, "dense")])
+@pytest.mark.parametrize("deg", [0, 1, 2, 3])
+@pytest.mark.parametrize("n", [1, 33, 97, 611])
+def test_train_step_equals_the_calls_it_replaces(n, deg, compact, records):
+    c = context(compact, records)
+    sc = scenes.tiny_scene(40 + n, n, 83, 50, sh_degree=deg, log_scale=(-2.3, 0.6), spread=1.3)
+    den = compare_with_the_calls(c, sc, deg, [(sc.cameras[0], *it) for it in SCHEDULE])
     assert int(den.max().item()) == 6
+    c.close()
+
+
+@pytest.mark.parametrize("compact,records", [(1, "dense"), (0, "sparse"), (1, "sparse"), (0, "dense")])
+@pytest.mark.parametrize("n", [0, 97])
+def test_train_step_where_nothing_is_visible(n, compact, records):
+    """No Gaussians at all, and views that see none of them, first and between others that do (moments decay and parameters
+    move on all the same)."""
+    c = context(compact, records)
+    sc = scenes.tiny_scene(70, 97, 83, 50, sh_degree=1, log_scale=(-2.3, 0.6), spread=1.3)
+    cam = sc.cameras[0]
+    away = scenes.Camera(cam.width, cam.height, cam.fx, cam.fy, cam.cx, cam.cy, cam.R, cam.t - np.array([0, 0, 100.0], np.float32))
+    if n == 0:
+        sc = scenes.Scene("empty", 1, *(a[:0] for a in (sc.means, sc.scales, sc.quats, sc.opacities, sc.sh)), [cam], 0)
+    den = compare_with_the_calls(c, sc, 1, [(away, *SCHEDULE[0])] + [(k, *it) for it in SCHEDULE for k in (cam, away)])
+    assert den.numel() == n and (n == 0 or int(den.max().item()) == 6)
+    c.close()
+
+
+@pytest.mark.parametrize("compact,records", [(1, "dense"), (0, "sparse"), (1, "sparse"), (0, "dense")])
+def test_train_step_on_frames_and_lists_that_grow(compact, records):
+    """Frames of other sizes on one context, each with more pairs than its buffers hold, and back: they grow within an
+    iteration."""
+    c = context(compact, records)
+    sc = scenes.tiny_scene(71, 611, 83, 50, sh_degree=2, log_scale=(-2.3, 0.6), spread=1.3)
+    cam = sc.cameras[0]
+    sized = lambda k: scenes.Camera(int(k * cam.width), int(k * cam.height), k * cam.fx, k * cam.fy, k * cam.cx, k * cam.cy, cam.R, cam.t)
+    compare_with_the_calls(c, sc, 2, [(sized(k), *it) for k, it in zip((0.3, 1.0, 2.7, 6.1, 0.5, 2.7), SCHEDULE)])
     c.close()
 
 
