@@ -1016,7 +1016,8 @@ int fs_train_step(fs_ctx* ctx, const fs_train_state* t, const fs_camera* cam, co
     const int tiles = cd.tiles_x * cd.tiles_y;
     const size_t hw = (size_t)cd.width * cd.height, rows = ((size_t)n + 15) / 16 * 16;
 
-    // the view's projected splats and frame live in the ctx (every sub-array on a 16-byte boundary)
+    // the view's projected splats and frame live in the ctx (every sub-array on a 16-byte boundary but dL, which follows an image
+    // of 3 hw floats directly)
     FS_TRY(ensure(ctx, ctx->train_proj, (rows ? rows : 16) * 56, "projected splats"));
     FS_TRY(ensure(ctx, ctx->train_frame, 8 * (hw + 3) / 4 * 4 * sizeof(float), "frame"));
     float* const proj_base = static_cast<float*>(ctx->train_proj.ptr);

@@ -526,7 +526,9 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
         if (g == 0) {
             // (another compute die may read these: they go past this one's L2, and have arrived before the workgroup counts
             // as done.  A release fence would do the same, and write the whole L2 back each time: the launch took 15 us instead
-            // of 11 at 100k Gaussians.)
+            // of 11 at 100k Gaussians.  The reader needs no acquire fence for its part: it loads them with agent-scope atomics,
+            // which do not look for them in its own L2 either, and only after the branch on the count.  This is the cache policy of
+            // this chip's agent-scope accesses, not an ordering of the language's memory model.)
             if (t < num_tiles) __hip_atomic_store(&tile_total[t], all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if (lane == 0) s_last = atomicAdd(&counters[2], 1ull) + 1 == (unsigned long long)sum_blocks;
@@ -674,7 +676,8 @@ __device__ __forceinline__ void network_sort(uint64_t* k, int N, int n, const ui
 // which gives every word a bucket share whatever the distribution between the parts.  A list with more than
 // BUCKET_LIMIT words in one bucket (hundreds of equal depths) is left to the network above.
 // What is left is the segments' loads and stores (20 bytes per pair) and, for the shortest lists, the chain of six
-// barriers.  Against the network for everything: 27 M pairs (lists of 3 350 on average) 830 -> 259 us in four launches,
+// barriers.  Against the network for everything: 27 M pairs (lists of 3 350 on average) 830 -> 259 us in four launches
+// (<= 2 048, <= 4 096, <= 8 192, <= 16 384 words),
 // 10 M pairs 177 -> 75 us, 300k Gaussians at 1332x876 55 -> 23 us, 100k at 980x545 16.4 -> 8.4 us.
 // Handles the tiles whose length is in (len_lo, CAP]; the others are left to another launch.
 constexpr int COARSE = 256;

@@ -340,10 +340,10 @@ hipError_t launch_emit_pairs_cb(hipStream_t st, int64_t n, const fs_projected& p
 constexpr int TILE_COPIES = 256;        // workgroups of the counting / placement kernels, each with its own counters (a multiple of 64)
 constexpr int TILE_PAIR_THREADS = 1024;
 constexpr int TILE_LDS_MAX_TILES = 15360;  // their per-tile counters live in LDS (60 KB)
-constexpr int TILE_SORT_SMALL = 2048;  // longest list one workgroup sorts with 20 KB of LDS (256 threads)
-constexpr int TILE_SORT_MID = 4096;    // ... with 40 KB (512 threads: four such workgroups fit a compute unit, two of the next)
-constexpr int TILE_SORT_MAX = 8192;    // ... with 80 KB (1024 threads)
-constexpr int TILE_SORT_HUGE = 16384;  // ... with 144 KB (a compute unit of this chip has 160 KB): the longest list of the
+constexpr int TILE_SORT_SMALL = 2048;  // longest list one workgroup sorts with 22 KB of LDS (256 threads)
+constexpr int TILE_SORT_MID = 4096;    // ... with 40.1 KB (512 threads: three such workgroups fit a compute unit, two of the next)
+constexpr int TILE_SORT_MAX = 8192;    // ... with 74 KB (1024 threads)
+constexpr int TILE_SORT_HUGE = 16384;  // ... with 146 KB (a compute unit of this chip has 160 KB): the longest list of the
                                        // per-tile ordering; anything longer takes the radix path
 hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, int tiles_x,
                              int num_tiles, uint32_t* tile_count, uint32_t* tile_total, uint2* ranges,
@@ -357,9 +357,11 @@ hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& pr
                                uint32_t rec_limit, const uint2* ranges, uint32_t* cursor, uint64_t* bucket, float* pair_grad);
 // The sort launches, by the list lengths they take: (0, SMALL], (SMALL, MID], (MID, MAX], (MAX, HUGE], and
 // (SMALL, MAX] in one launch (TS_MIDMAX, instead of TS_MID and TS_MAX).  The lists between SMALL and MID get a launch of
-// their own (four of its workgroups fit a compute unit, two of the MAX kind) when the lists are long throughout
+// their own (three of its workgroups fit a compute unit, two of the MAX kind) when the lists are long throughout
 // (`long_lists`: there are then enough of them to fill the chip); when only a few tiles are that long, every launch is
 // a chain of steps that nothing overlaps with, and one launch fewer is the better deal.
+// With MID and without: 3 M Gaussians with lists of 3350 on average 2557 and 2565 us per step, of 1228 1726 and 1730, 30k at
+// 189x106 207.2 and 208.0; ten views at 300k, whose lists are 400 long and a few 7000, 2254 and 2167.
 // tile_sort_variants: the launches still needed for lists of up to max_len entries when those in `have` are enqueued.
 enum { TS_SMALL = 1, TS_MID = 2, TS_MAX = 4, TS_HUGE = 8, TS_MIDMAX = 16 };
 int tile_sort_variants(int64_t max_len, bool long_lists, int have);

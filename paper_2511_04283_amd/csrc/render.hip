@@ -8,9 +8,10 @@
 // One workgroup (4 wavefronts) per 16x16 tile, one pixel per lane.  Wavefront w owns the 8x8
 // quadrant (w&1, w>>1); each of its four rows of 16 lanes (the unit of the DPP row operations) owns
 // one 4x4 sub-tile of that quadrant.  The tile's depth-ordered Gaussians are staged through LDS in
-// batches of 256.  While staging, every Gaussian's support {alpha >= alpha_min} is bounded by an
-// axis-aligned box (conservatively, see stage_batch) and each of the 16 sub-tiles gets its own
-// order-preserving list of the staged Gaussians whose box meets it.  In the inner loops the four
+// batches of 255 (k_render_bwd: 231, with the absolute gradient 207).  Every Gaussian's support
+// {alpha >= alpha_min} is bounded by an octagon (conservatively, support_octagon; it comes with the splat
+// record) and each of the 16 sub-tiles gets its own order-preserving list of the staged Gaussians
+// whose octagon meets it.  In the inner loops the four
 // rows of a wavefront walk their own lists side by side, so one wavefront iteration evaluates
 // four different Gaussians on 16 pixels each.  A wavefront stops as soon as all of its 64 pixels
 // have terminated.
@@ -18,7 +19,7 @@
 // alpha, T and the blend weights follow a fixed fp32 operation order (fused multiply-adds only
 // where written as __builtin_fmaf; the file is compiled with -ffp-contract=off) so that the
 // integer outputs they decide (n_contrib, counts) can be reproduced bit for bit on a CPU.  The
-// box test only ever drops (Gaussian, pixel) pairs that this arithmetic would reject as well.
+// octagon only ever drops (Gaussian, pixel) pairs that this arithmetic would reject as well.
 #include "common.hpp"
 
 namespace fs {
@@ -163,7 +164,7 @@ __device__ __forceinline__ int stage_batch(Stage<WITH_RGB, N>& s, uint32_t* s_id
 {
     const int t = threadIdx.x;
     const int swave = t >> 6, lane = t & 63;
-    uint32_t sub_mask = 0;  // bit (wave*4 + row) of every sub-tile the box meets
+    uint32_t sub_mask = 0;  // bit (wave*4 + row) of every sub-tile the octagon meets
     if (t < m) {
         const float4* rec = splats + (size_t)g * (SPLAT_REC / 4);  // one 64-byte line
         const float4 r0 = rec[0], r1 = rec[1], r2 = rec[2];
@@ -295,8 +296,8 @@ __device__ __forceinline__ int wave_max_of_rows(int mine)
 // BITS: the kernel also records, for every pair of the tile's list (by its position in the sorted order), at which
 // of the tile's 256 pixels the Gaussian is counted by the multi-view score (Sec. 4.2): where it is blended and, in
 // FS_SCORE_WEIGHT mode, alpha T > alpha_min.  32 bytes per pair: 16 sub-tiles (index wave*4 + row) x 16 bits (lane
-// within the row); one more byte per pair says whether any of them is set, and only then is the row written.  With
-// these the count pass is a population count per pair instead of a second walk over the lists (k_score_bits).
+// within the row); only the rows with a bit set are written, packed at the start of the tile's segment, each with its Gaussian.
+// With these the count pass is a population count per pair instead of a second walk over the lists (k_score_bits).
 template <bool FUSED, bool BITS>
 __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, const uint2* __restrict__ ranges,
                                                     const uint32_t* __restrict__ tile_order,
@@ -817,7 +818,7 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
 // ---- per-splat-parallel backward (the mapping of Taming-3DGS that the paper's baseline uses) -------------
 // Alternative to k_render_bwd with the same inputs, outputs and record layout; kept for comparison.
 // A wavefront owns one 8x8 quadrant of the tile.  Per batch it forms the quadrant's list (the staged entries
-// whose box meets any of its four sub-tiles), takes it in chunks of 64 entries from the back, one entry per
+// whose octagon meets any of its four sub-tiles), takes it in chunks of 64 entries from the back, one entry per
 // lane (lane 0 = the entry furthest back), and passes the quadrant's 64 pixels by one after the other.  For a
 // pixel p every lane evaluates its own Gaussian; what the per-pixel kernel carries from entry to entry becomes
 // two scans over the lanes:
