@@ -48,8 +48,9 @@ struct fs_ctx {
                                          // chosen (0: none): what fs_bin_sort enqueues ahead of its read-back
     uint64_t* total_dev = nullptr;   // device: totals [4]: pairs, backward records, pairs counted per tile, longest tile list
     uint64_t* total_host = nullptr;  // pinned host block of four totals (copied from total_dev, or written by k_tile_layout)
-    uint64_t* alloc_dev = nullptr;   // device: the two counters of the counting kernel and the arrivals of the next one (zero between calls)
-    bool alloc_dirty = false;        // a call failed between the kernel that adds to them and the one that clears them
+    uint64_t* arrivals = nullptr;    // device: the arrivals of k_tile_layout's workgroups (zero between calls), and behind them
+                                     // the totals of the counting kernel's workgroups [2][TILE_COPIES]
+    bool arrivals_dirty = false;     // a call failed where it may have left arrivals behind
     ScratchBuf train_proj;           // fs_train_step: the projected splats of its view ...
     ScratchBuf train_frame;          // ... its image, dL/dimage, final_T and n_contrib
     double* loss_host = nullptr;     // its loss (three doubles, written by k_ssim_bwd), within total_host's allocation
@@ -315,8 +316,8 @@ int fs_create(fs_ctx** out, int device, void* hip_stream, const fs_config* cfg)
         fs_destroy(ctx);
         return FS_EHIP;
     }
-    if (hipMalloc(reinterpret_cast<void**>(&ctx->alloc_dev), 3 * sizeof(uint64_t)) != hipSuccess ||
-        hipMemset(ctx->alloc_dev, 0, 3 * sizeof(uint64_t)) != hipSuccess ||
+    if (hipMalloc(reinterpret_cast<void**>(&ctx->arrivals), (1 + 2 * TILE_COPIES) * sizeof(uint64_t)) != hipSuccess ||
+        hipMemset(ctx->arrivals, 0, sizeof(uint64_t)) != hipSuccess ||
         hipMalloc(reinterpret_cast<void**>(&ctx->total_dev), 4 * sizeof(uint64_t)) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&ctx->total_host), LOSS_HOST_AT + 3 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
@@ -342,7 +343,7 @@ void fs_destroy(fs_ctx* ctx)
     for (ScratchBuf* b : all)
         if (b->ptr) (void)hipFree(b->ptr);
     if (ctx->total_dev) (void)hipFree(ctx->total_dev);
-    if (ctx->alloc_dev) (void)hipFree(ctx->alloc_dev);
+    if (ctx->arrivals) (void)hipFree(ctx->arrivals);
     if (ctx->total_host) (void)hipHostFree(ctx->total_host);
     if (ctx->totals_event) (void)hipEventDestroy(ctx->totals_event);
     if (ctx->loss_event) (void)hipEventDestroy(ctx->loss_event);
@@ -424,15 +425,15 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
         // enqueued ahead of the read-back)
         ProfScope prof(ctx, FS_K_EMIT);
         fs_projected none = {};
-        if (ctx->alloc_dirty) FS_HIP(launch_fill_u32(st, reinterpret_cast<uint32_t*>(ctx->alloc_dev), 0u, 6), "k_fill_u32");
-        ctx->alloc_dirty = true;
+        if (ctx->arrivals_dirty) FS_HIP(launch_fill_u32(st, reinterpret_cast<uint32_t*>(ctx->arrivals), 0u, 2), "k_fill_u32");
+        ctx->arrivals_dirty = true;
         FS_HIP(launch_tile_count(st, n, proj ? *proj : none, cf, cd.tiles_x, tiles, tcount_p, ttotal_p,
                                  reinterpret_cast<uint2*>(ranges_p), order_p, ctx->total_host,
                                  static_cast<uint32_t*>(cb ? ctx->rec_offsets.ptr : ctx->offsets.ptr),
-                                 cb ? static_cast<uint32_t*>(ctx->rec_counts.ptr) : nullptr, ctx->alloc_dev,
+                                 cb ? static_cast<uint32_t*>(ctx->rec_counts.ptr) : nullptr, ctx->arrivals, ctx->arrivals + 1,
                                  static_cast<float*>(ctx->splats.ptr)),
                "k_tile_pairs (count)");
-        ctx->alloc_dirty = false;
+        ctx->arrivals_dirty = false;
     } else {
         FS_TRY(prefix_sums());
     }

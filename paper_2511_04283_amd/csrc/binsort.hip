@@ -113,6 +113,11 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_apply(const uint32_t* in,
     }
 }
 
+__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int d)
+{
+    return (uint64_t)(uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), d, 64) << 32 | (uint32_t)__shfl_xor((int)(uint32_t)v, d, 64);
+}
+
 // The 64-byte record the render kernels gather for Gaussian i (see SPLAT_REC).
 __device__ __forceinline__ void pack_splat(float4* __restrict__ splats, int64_t i, const float2& m, const float4& co,
                                            const float* __restrict__ rgb, uint32_t first_record, const ushort4& r, const CfgDev& cfg)
@@ -303,18 +308,19 @@ __global__ __launch_bounds__(256) void k_emit_pairs_cb(int64_t n, const ushort4*
 // are the numbers of words / records the buffers hold: nothing is written at or beyond them (the kernel may be
 // enqueued before the host has seen the real totals).
 //
-// Step (1) also hands every Gaussian the place of its backward records (one per tile of its rectangle): a
-// workgroup first adds up the records of all its Gaussians and reserves them with one add on a global counter
-// (adds on one address take about 10 ns each, so one per wavefront and round would cost more than the prefix sum
-// it replaces); inside the reservation the wavefronts, their rounds and the 64 Gaussians of a round follow each
-// other.  The places are disjoint, each Gaussian's are contiguous and so are those of 64 consecutive Gaussians,
-// which is all their users need -- no prefix sum over the Gaussians.  A second counter receives the sum of
-// tiles_touched, which the host compares with the number of pairs counted per tile.
+// Step (1) also hands every Gaussian the place of its backward records (one per tile of its rectangle), counted from the
+// first record of its workgroup: inside a workgroup the wavefronts, their rounds and the 64 Gaussians of a round follow each
+// other.  k_tile_layout adds what the workgroups before have (wg_totals).  The places are disjoint, each Gaussian's are
+// contiguous and so are those of 64 consecutive Gaussians, which is all their users need -- no prefix sum over the Gaussians.
+// (Reserved with adds on global counters, which take about 10 ns on one address, the 256 workgroups waited for one another.  Without
+// them and with the Gaussians dealt out evenly, counting and k_tile_layout together, before and after: 21.2 and 18.4 us at 100k
+// Gaussians, 44.8 and 41.2 at 500k, 38.3 and 30.5 at 300k with the Compact Box, 105.8 and 108.5 at 3 M, where placement gains more.)
+// The sums of tiles_touched are there for the host, which compares them with the number of pairs counted per tile.
 struct RecAlloc {
     const uint32_t* tiles_touched;   // [n]
     uint32_t* rec_offsets;           // [n] out: first record of each Gaussian
     uint32_t* rec_counts;            // [n] out (may be null): records of each Gaussian = area of its rectangle
-    unsigned long long* counters;    // [2]: records handed out, sum of tiles_touched
+    uint64_t* wg_totals;             // [2][TILE_COPIES] out: each workgroup's records, and its sum of tiles_touched
 };
 
 template <bool CB, bool SCATTER>
@@ -336,16 +342,18 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
     const uint32_t lane = lane_id();
     __shared__ uint32_t s_mark[TILE_PAIR_THREADS / 64][64];
     uint32_t* const mark = s_mark[threadIdx.x >> 6];   // this wavefront's own
+    // Wavefront w of workgroup b takes the 64 Gaussians from 64 (w gridDim + b) on in its first round, so that every workgroup has as
+    // much to do as the next, also where there are fewer Gaussians than threads.
+    const int64_t i_first = ((int64_t)(threadIdx.x >> 6) * gridDim.x + blockIdx.x) * 64 + lane;
     uint32_t rec_next = 0;   // (counting) where the records of this wavefront's next round start
     if (!SCATTER) {
         __shared__ uint32_t s_wave_recs[TILE_PAIR_THREADS / 64];
         __shared__ uint32_t s_tt[TILE_PAIR_THREADS / 64];
-        __shared__ uint32_t s_base[2];
         uint32_t recs = 0, tt = 0;
         // (four rounds' loads are requested together: with one wavefront's worth of loads in flight per round the
         // loop would take one memory latency per round)
         const int64_t stride = (int64_t)gridDim.x * TILE_PAIR_THREADS;
-        for (int64_t i = (int64_t)blockIdx.x * TILE_PAIR_THREADS + threadIdx.x; i < n; i += 4 * stride) {
+        for (int64_t i = i_first; i < n; i += 4 * stride) {
             ushort4 r[4];
             uint32_t t4[4];
 #pragma unroll
@@ -365,24 +373,16 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
         if (lane == 63) { s_wave_recs[threadIdx.x >> 6] = recs; s_tt[threadIdx.x >> 6] = tt; }
         __syncthreads();
         if (threadIdx.x == 0) {
-            unsigned long long all = 0, all_tt = 0;
+            uint64_t all = 0, all_tt = 0;
             for (int w = 0; w < TILE_PAIR_THREADS / 64; w++) { all += s_wave_recs[w]; all_tt += s_tt[w]; }
-            unsigned long long b = 0;
-            if (all | all_tt) {
-                b = atomicAdd(&ra.counters[0], all);
-                atomicAdd(&ra.counters[1], all_tt);
-            }
-            // (a reservation that reaches beyond 32 bits is never used: the host rejects the call on the total)
-            s_base[0] = (uint32_t)b;
-            s_base[1] = (b + all) >> 32 ? 1u : 0u;
+            ra.wg_totals[blockIdx.x] = all;
+            ra.wg_totals[TILE_COPIES + blockIdx.x] = all_tt;
         }
-        __syncthreads();
-        rec_next = s_base[1] ? 0u : s_base[0];
-        for (int w = 0; w < (int)(threadIdx.x >> 6); w++) rec_next += s_base[1] ? 0u : s_wave_recs[w];
+        // (32 bits: the host rejects a call whose records do not fit them)
+        for (int w = 0; w < (int)(threadIdx.x >> 6); w++) rec_next += s_wave_recs[w];
     }
     // (every wavefront of the workgroup walks its own 64 Gaussians per round; no barrier inside the rounds)
     // (the next round's rectangle, record place and depth are requested before this round's candidates are walked)
-    const int64_t i_first = (int64_t)blockIdx.x * TILE_PAIR_THREADS + threadIdx.x;
     const int64_t round_stride = (int64_t)gridDim.x * TILE_PAIR_THREADS;
     ushort4 r_next = i_first < n ? rect[i_first] : make_ushort4(0, 0, 0, 0);
     uint32_t roff_next = (SCATTER && CB && i_first < n) ? rec_offsets[i_first] : 0u;
@@ -483,18 +483,27 @@ constexpr int LAYOUT_WAVES = LAYOUT_THREADS / 64;
 __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __restrict__ count, int num_tiles, int sum_blocks,
                                                                 uint32_t* __restrict__ tile_total, uint2* __restrict__ ranges,
                                                                 uint32_t* __restrict__ order, uint64_t* __restrict__ totals,
-                                                                unsigned long long* __restrict__ counters, int64_t n,
+                                                                unsigned long long* __restrict__ arrivals,
+                                                                const uint64_t* __restrict__ wg_totals, int64_t n,
                                                                 const ushort4* __restrict__ rect, const float2* __restrict__ mean2d,
                                                                 const float4* __restrict__ conic_opacity, const float* __restrict__ rgb,
-                                                                CfgDev cfg, const uint32_t* __restrict__ rec_offsets,
+                                                                CfgDev cfg, uint32_t* __restrict__ rec_offsets,
                                                                 float4* __restrict__ splats)
 {
     if ((int)blockIdx.x >= sum_blocks) {
         const int64_t i = (int64_t)((int)blockIdx.x - sum_blocks) * LAYOUT_THREADS + threadIdx.x;
+        // the records of the workgroups before the one that counted these 64 Gaussians (see k_tile_pairs)
+        const uint32_t wg = (uint32_t)(i >> 6) % TILE_COPIES;
+        uint32_t before = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < TILE_COPIES; k += 64) before += k + lane_id() < wg ? (uint32_t)wg_totals[k + lane_id()] : 0u;
+        before = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(before), 63);
         if (i >= n) return;
+        const uint32_t first_record = rec_offsets[i] + before;
+        rec_offsets[i] = first_record;
         const ushort4 r = rect[i];
         if (r.z <= r.x || r.w <= r.y) return;   // (no pair names it)
-        pack_splat(splats, i, mean2d[i], conic_opacity[i], rgb, rec_offsets[i], r, cfg);
+        pack_splat(splats, i, mean2d[i], conic_opacity[i], rgb, first_record, r, cfg);
         return;
     }
     // Order of the workgroups' shares within a tile's segment: workgroups are handed to the 8 XCDs in turn, so
@@ -537,7 +546,7 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
             // this chip's agent-scope accesses, not an ordering of the language's memory model.)
             if (t < num_tiles) __hip_atomic_store(&tile_total[t], all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            if (lane == 0) s_last = atomicAdd(&counters[2], 1ull) + 1 == (unsigned long long)sum_blocks;
+            if (lane == 0) s_last = atomicAdd(arrivals, 1ull) + 1 == (unsigned long long)sum_blocks;
         }
     }
     __syncthreads();
@@ -579,15 +588,19 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
         run += c[q];
     }
     if (threadIdx.x == 1023) {
-        // totals: sum of tiles_touched, backward records, pairs counted per tile, longest list; the counters of
-        // the counting kernel and the arrivals of this one start the next call at zero
-        totals[0] = counters[1];
-        totals[1] = counters[0];
+        // totals: sum of tiles_touched, backward records, pairs counted per tile, longest list; the arrivals start the
+        // next call at zero
         totals[2] = run;
         totals[3] = max_s;
-        counters[0] = 0ull;
-        counters[1] = 0ull;
-        counters[2] = 0ull;
+        *arrivals = 0ull;
+    }
+    if (threadIdx.x >= 64 && threadIdx.x < 128) {   // (the second wavefront: the first one is busy below)
+        uint64_t recs = 0, tt = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < TILE_COPIES; k += 64) { recs += wg_totals[k + lane_id()]; tt += wg_totals[TILE_COPIES + k + lane_id()]; }
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) { recs += shfl_xor_u64(recs, d); tt += shfl_xor_u64(tt, d); }
+        if (lane_id() == 0) { totals[0] = tt; totals[1] = recs; }
     }
     // tile order: exclusive prefix over the 512 length buckets by one wavefront, then a counting placement
     if (threadIdx.x < 64) {
@@ -1026,9 +1039,9 @@ hipError_t launch_emit_pairs_cb(hipStream_t st, int64_t n, const fs_projected& p
 hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, int tiles_x,
                              int num_tiles, uint32_t* tile_count, uint32_t* tile_total, uint2* ranges,
                              uint32_t* tile_order, uint64_t* totals, uint32_t* rec_offsets, uint32_t* rec_counts,
-                             uint64_t* counters, float* splats)
+                             uint64_t* arrivals, uint64_t* wg_totals, float* splats)
 {
-    const RecAlloc ra = {proj.tiles_touched, rec_offsets, rec_counts, reinterpret_cast<unsigned long long*>(counters)};
+    const RecAlloc ra = {proj.tiles_touched, rec_offsets, rec_counts, wg_totals};
     {
         const dim3 grid(TILE_COPIES), block(TILE_PAIR_THREADS);
         const size_t lds = (size_t)num_tiles * sizeof(uint32_t);
@@ -1045,7 +1058,7 @@ hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj
     const int sum_blocks = (num_tiles + 63) / 64;
     hipLaunchKernelGGL(k_tile_layout, dim3((unsigned)(sum_blocks + (n + LAYOUT_THREADS - 1) / LAYOUT_THREADS)), dim3(LAYOUT_THREADS), 0, st,
                        tile_count, num_tiles, sum_blocks, tile_total, ranges, tile_order, totals,
-                       reinterpret_cast<unsigned long long*>(counters), n, reinterpret_cast<const ushort4*>(proj.rect),
+                       reinterpret_cast<unsigned long long*>(arrivals), wg_totals, n, reinterpret_cast<const ushort4*>(proj.rect),
                        reinterpret_cast<const float2*>(proj.mean2d), reinterpret_cast<const float4*>(proj.conic_opacity), proj.rgb,
                        cfg, rec_offsets, reinterpret_cast<float4*>(splats));
     return hipGetLastError();

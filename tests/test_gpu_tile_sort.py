@@ -62,3 +62,46 @@ def test_every_list_is_long(n):
         order = np.lexsort((np.arange(m), d.view(np.uint32), tile))
         assert np.array_equal(bins.copy_gauss().cpu().numpy(), order.astype(np.int32)), turn
     c.close()
+
+
+@pytest.mark.parametrize("compact", [False, True])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 16384, 16385, 262143, 262209])
+def test_pairs_and_record_places(n, compact):
+    """The counting and placement kernels deal 64 Gaussians at a time out to their workgroups: one chunk, a last one that is not
+    full, one for every workgroup and one more, one for every wavefront and a second round of one.  The order bit for bit,
+    and every Gaussian's gradient records (one per tile of its rectangle) a place of their own."""
+    import torch
+    from paper_2511_04283_amd import binding as B
+    from paper_2511_04283_amd import scenes
+    rng = np.random.default_rng(n)
+    config = B.default_config()
+    config.compact_box = 1 if compact else 0
+    c = B.Context("cuda:0", config)
+    tx, ty = 45, 29
+    cam = B.make_camera(scenes.Camera(16 * tx, 16 * ty, 500.0, 500.0, 8.0 * tx, 8.0 * ty))
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(c.device)
+    x0, y0 = rng.integers(0, tx, n), rng.integers(0, ty, n)
+    w, h = np.minimum(rng.integers(0, 4, n), tx - x0), np.minimum(rng.integers(0, 3, n), ty - y0)
+    rect = np.stack([x0, y0, x0 + w, y0 + h], 1).astype(np.int16)
+    area = w * h
+    d = rng.uniform(0.2, 50.0, n).astype(np.float32)
+    # (so wide that every tile of the rectangle meets the ellipse)
+    co = np.tile(np.array([1e-5, 0.0, 1e-5, 0.5], np.float32), (n, 1))
+    mean = np.stack([16.0 * x0 + 8.0, 16.0 * y0 + 8.0], 1).astype(np.float32)
+    proj = B.Projected(t(mean), t(d), t(co), t(np.full((n, 3), 0.5, np.float32)), t(rect), t(area.astype(np.int32)),
+                       t(np.zeros((n, 3), np.uint8)))
+    for turn in range(2):   # (the second one's placement is enqueued ahead of the totals)
+        bins = c.fs_bin_sort(proj, cam)
+        assert bins.num_pairs == area.sum() and bins.struct.num_records == area.sum()
+        gauss = np.repeat(np.arange(n), area)
+        k = np.arange(area.sum()) - np.repeat(np.cumsum(area) - area, area)
+        tile = (y0[gauss] + k // np.maximum(w[gauss], 1)) * tx + x0[gauss] + k % np.maximum(w[gauss], 1)
+        order = np.lexsort((gauss, d.view(np.uint32)[gauss], tile))
+        assert np.array_equal(bins.copy_gauss().cpu().numpy(), gauss[order].astype(np.int32))
+        first = bins._copy(bins.struct.record_offsets, n, torch.int32).cpu().numpy().astype(np.int64)
+        places = np.repeat(first, area) + k
+        assert np.array_equal(np.sort(places), np.arange(area.sum()))
+        chunks = np.arange(n) // 64
+        same = (chunks[1:] == chunks[:-1])
+        assert np.array_equal((first[1:] - first[:-1])[same], area[:-1][same])   # (those of 64 Gaussians follow each other)
+    c.close()
