@@ -526,6 +526,15 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
 // Gaussian's (up to 16) sub-tile totals within a tile, taken in double precision in LDS: the record is the same from
 // run to run unless the exponents of those terms span more than 29 bits.
 //
+// What else shapes the inner loop is what this chip's vector unit and LDS do with an instruction (measured, in cycles of one SIMD):
+// it takes plain additions, products and three-register multiply-adds from two wavefronts at a time, 2.35 each; an exponential or a
+// reciprocal (8.3), a data-parallel move, a permutation of the lanes or a read of one lane (4.3) also ends that for some sixteen
+// instructions after it, wherever it stands: so they stand together (the reciprocals of four entries, the exchange between
+// the two lanes).  An LDS add of doubles takes 8.4 cycles of its compute unit where all lanes name places of their own, 44 where
+// four lanes name each: the adds were a seventh of the kernel, and now rows take turns (see there).  ABS needs no more exchanges:
+// its sums are formed behind the one of the v's.  Together, before and after, in us: 500k Gaussians at 1600x1064 225 and 212, 3 M
+// at 1920x1080 543 and 512, 100k at 980x545 81 and 78; with ABS 253 and 222 (500k, Compact Box), 176 and 153 (300k at 1332x876).
+//
 // ABS adds the absolute positional gradient (used by FastGS for the split decision): per pixel the
 // magnitudes |dL/dmu_x|, |dL/dmu_y| of its own contribution, summed like the other values and stored
 // in the record's floats 9 and 10.
@@ -609,10 +618,11 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
         asm volatile("" : "+v"(x));
         return x + (float)c;
     };
-    auto both = [](float v) {   // the sum of the two lanes of a combination, in both
+    auto other = [](float v) {   // what the other lane of the combination has
         constexpr int ROR8 = 0x128;
-        return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ROR8, 0xF, 0xF, true));
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ROR8, 0xF, 0xF, true));
     };
+    auto both = [&](float v) { return v + other(v); };   // the sum of the two lanes, in both
 
     s.clear(threadIdx.x);
     if (threadIdx.x == 0) s_max = 0;
@@ -645,18 +655,18 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
         const uint32_t last_here = (uint32_t)max(last - start, 0);   // slots below this one hold entries this pixel blended (or examined)
         for (int k = 0; k < longest; k += SPAN) {
             const uint2 words = *reinterpret_cast<const uint2*>(&s.list[sub][k / 4]);
-            float w[SPAN], v[SPAN], ax[SPAN], ay[SPAN];
+            float w[SPAN], v[SPAN];
             uint64_t acted = 0;
 #pragma unroll
             for (int g = 0; g < SPAN; g += GROUP) {
                 const uint32_t word = g ? words.y : words.x;
-                float alpha[GROUP], G[GROUP], cd[GROUP], inv[GROUP], hx[GROUP], hy[GROUP];
+                float alpha[GROUP], G[GROUP], cd[GROUP], inv[GROUP];
                 if (g == 0 || k + g < longest) {
 #pragma unroll
                     for (int u = 0; u < GROUP; u++) {
                         const uint32_t j = (word >> (8 * u)) & 0xffu;
-                        const float4 r0 = s.r0[j], r2 = s.r2[j];
-                        const float2 r1 = make_float2(s.r1[j].x, s.r1[j].y);
+                        const float4 r0 = s.r0[j], r1 = s.r1[j];
+                        const float cb = s.r2[j].z;   // (16 bytes twice and 4 are read faster than 16, 8 and 12)
                         const float dx = p.px - r0.x, dy = p.py - r0.y;
                         const float tx = r0.z * dx, ty = r1.x * dy;
                         const float h = __builtin_fmaf(r0.w, dy, tx);
@@ -671,14 +681,13 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
                         // exact zeros (and T / (1 - 0) leaves T as it is); a capped alpha is a constant: G = 0
                         alpha[u] = lane_of(act) ? al : 0.f;
                         G[u] = lane_of(act & ~capped) ? e : 0.f;
-                        inv[u] = __builtin_amdgcn_rcpf(1.0f - alpha[u]);
-                        cd[u] = __builtin_fmaf(r2.z, dC2, __builtin_fmaf(r2.y, dC1, r2.x * dC0));   // dC . c
-                        if (ABS) {
-                            // half of dq/dmu, negated: (a dx + b dy, b dx + c dy)
-                            hx[u] = h + tx;
-                            hy[u] = __builtin_fmaf(r0.w, dx, ty + ty);
-                        }
+                        inv[u] = 1.0f - alpha[u];
+                        cd[u] = __builtin_fmaf(cb, dC2, __builtin_fmaf(r1.w, dC1, r1.z * dC0));   // dC . c
                     }
+                    __builtin_amdgcn_sched_barrier(0);   // (side by side)
+#pragma unroll
+                    for (int u = 0; u < GROUP; u++) inv[u] = __builtin_amdgcn_rcpf(inv[u]);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int u = 0; u < GROUP; u++) {
                         T = T * inv[u];                                  // transmittance in front of this Gaussian
@@ -686,18 +695,14 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
                         const float diff = cd[u] - S;
                         v[g + u] = G[u] * (T * diff);                    // G dL/dalpha: d/d sigma
                         S = __builtin_fmaf(alpha[u], diff, S);
-                        if (ABS) {
-                            ax[g + u] = fabsf(v[g + u]) * fabsf(hx[u]);
-                            ay[g + u] = fabsf(v[g + u]) * fabsf(hy[u]);
-                        }
                     }
                 } else {
 #pragma unroll
-                    for (int u = 0; u < GROUP; u++) w[g + u] = v[g + u] = ax[g + u] = ay[g + u] = 0.f;
+                    for (int u = 0; u < GROUP; u++) w[g + u] = v[g + u] = 0.f;
                 }
             }
             if (acted == 0) continue;
-            const int slot = ent_list[k];
+            const uint32_t slot = ent_list[k];
             const float mu_x = s.r0[slot].x, mu_y = s.r0[slot].y;
             const bool needle = __float_as_uint(s.r2[slot].w) & NEEDLE;
             float sums0[6], sums1[6];   // the first lane's, the second one's
@@ -705,7 +710,7 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
             exchange(w, a, b);
 #pragma unroll
             for (int ch = 0; ch < 3; ch++)
-                sums0[ch] = both(__builtin_fmaf(b.w, g2[ch][3], __builtin_fmaf(b.z, g2[ch][2], __builtin_fmaf(b.y, g2[ch][1],
+                sums0[ch] = (__builtin_fmaf(b.w, g2[ch][3], __builtin_fmaf(b.z, g2[ch][2], __builtin_fmaf(b.y, g2[ch][1],
                                    __builtin_fmaf(b.x, g2[ch][0], __builtin_fmaf(a.w, g1[ch][3], __builtin_fmaf(a.z, g1[ch][2],
                                    __builtin_fmaf(a.y, g1[ch][1], a.x * g1[ch][0]))))))));
             exchange(v, a, b);
@@ -718,19 +723,48 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
                 const float a0 = (a.x + a.y) + (a.z + a.w), b0 = (b.x + b.y) + (b.z + b.w);
                 const float a1 = along(a, dx), b1 = along(b, dx);
                 const float ya = dy1 * a0, yb = dy2 * b0;
-                sums0[DSIGMA] = both(a0 + b0);
-                sums1[DX - HALF] = both(a1 + b1);
-                sums1[DY - HALF] = both(ya + yb);
-                sums1[DXX - HALF] = both(along(a, dxx) + along(b, dxx));
-                sums1[DYY - HALF] = both(__builtin_fmaf(dy1, ya, dy2 * yb));
-                sums1[DXY - HALF] = both(__builtin_fmaf(dy1, a1, dy2 * b1));
+                sums0[DSIGMA] = a0 + b0;
+                sums1[DX - HALF] = a1 + b1;
+                sums1[DY - HALF] = ya + yb;
+                sums1[DXX - HALF] = along(a, dxx) + along(b, dxx);
+                sums1[DYY - HALF] = __builtin_fmaf(dy1, ya, dy2 * yb);
+                sums1[DXY - HALF] = __builtin_fmaf(dy1, a1, dy2 * b1);
+                if (ABS) {
+                    // |v| times half of |dq/dmu| = |a dx + b dy|, |b dx + c dy|, pixel by pixel
+                    const float4 r0 = s.r0[slot];
+                    const float qa = r0.z + r0.z, qb = r0.w, qc = 2.0f * s.r1[slot].x;
+                    auto sizes = [&](const float4& l, float dy, float& x, float& y) {
+                        const float v4[4] = {l.x, l.y, l.z, l.w}, bx = qb * dy, by = qc * dy;
+#pragma unroll
+                        for (int c = 0; c < 4; c++) {
+                            const float hx = __builtin_fmaf(qa, dx[c], bx), hy = __builtin_fmaf(qb, dx[c], by);
+                            x = c == 0 ? fabsf(v4[c]) * fabsf(hx) : __builtin_fmaf(fabsf(v4[c]), fabsf(hx), x);
+                            y = c == 0 ? fabsf(v4[c]) * fabsf(hy) : __builtin_fmaf(fabsf(v4[c]), fabsf(hy), y);
+                        }
+                    };
+                    float x1, y1, x2, y2;
+                    sizes(a, dy1, x1, y1);
+                    sizes(b, dy2, x2, y2);
+                    sums0[DABS_X] = x1 + x2;
+                    sums0[DABS_Y] = y1 + y2;
+                }
             }
+            // the two lanes of a combination: the first one gets the whole of sums0, the second one that of sums1
+            float sum[6];
+            __builtin_amdgcn_sched_barrier(0);   // (side by side)
+#pragma unroll
+            for (int f = 0; f < (ABS ? 6 : 5); f++) {
+                const float s0 = f < HALF ? sums0[f] : 0.f, s1 = f < NV - HALF ? sums1[f] : 0.f;
+                const float keep = second ? s1 : s0, give = second ? s0 : s1;
+                sum[f] = keep + other(give);
+            }
+            __builtin_amdgcn_sched_barrier(0);
             // needles: dL/dq times dx^2, dx dy, dy^2 pixel by pixel, added in the order of a balanced tree over the lines and
             // their pixels (500k Gaussians: one exchange in ten has one).  The v's are read from LDS once more, so that the common
             // path does not hold them in registers.
             if (ballot(needle) != 0) {
-                const float gq = -0.5f * s.r1[slot].y;
                 float xx = 0.f, xy = 0.f, yy = 0.f;
+                const float gq = -0.5f * s.r1[slot].y;
 #pragma unroll
                 for (int l = 0; l < 2; l++) {
                     const float4 v4 = turned[l ? q2 : q1];
@@ -750,22 +784,26 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
                     xy = xy + both((pxy[0] + pxy[1]) + (pxy[2] + pxy[3]));
                     yy = yy + both((pyy[0] + pyy[1]) + (pyy[2] + pyy[3]));
                 }
-                sums1[DXX - HALF] = needle ? xx : sums1[DXX - HALF];
-                sums1[DYY - HALF] = needle ? yy : sums1[DYY - HALF];
-                sums1[DXY - HALF] = needle ? xy : sums1[DXY - HALF];
+                const bool mine = needle & second;
+                sum[DXX - HALF] = mine ? xx : sum[DXX - HALF];
+                sum[DYY - HALF] = mine ? yy : sum[DYY - HALF];
+                sum[DXY - HALF] = mine ? xy : sum[DXY - HALF];
             }
-            if (ABS) {
-                exchange(ax, a, b);
-                sums0[DABS_X] = both(((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w)));
-                exchange(ay, a, b);
-                sums0[DABS_Y] = both(((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w)));
-            }
-            acc_t* const acc = &s_acc[slot][second ? HALF : 0];
+            // The four rows of a quadrant often have the same Gaussian in the same exchange, and an LDS atomic takes one round for every
+            // lane that names the same place: so each row takes the first four sums in an order of its own (number i ^ row in
+            // round i), and neighbouring lanes name neighbouring places.
+            const uint32_t acc = slot * (uint32_t)(NV * sizeof(acc_t)) + (second ? HALF * (uint32_t)sizeof(acc_t) : 0u);
+            auto add = [&](uint32_t place, float u) {
+                if (u != 0.f) atomicAdd(reinterpret_cast<acc_t*>(reinterpret_cast<char*>(&s_acc[0][0]) + place), (acc_t)u);
+            };
+            {
+                static_assert(sizeof(acc_t) == 8, "places of the sums");
+                const float p0 = row & 1 ? sum[1] : sum[0], p1 = row & 1 ? sum[0] : sum[1], p2 = row & 1 ? sum[3] : sum[2], p3 = row & 1 ? sum[2] : sum[3];
+                const float mine[4] = {row & 2 ? p2 : p0, row & 2 ? p3 : p1, row & 2 ? p0 : p2, row & 2 ? p1 : p3};
 #pragma unroll
-            for (int f = 0; f < (ABS ? 6 : 5); f++) {
-                const float u0 = f < HALF ? sums0[f] : 0.f, u1 = f < NV - HALF ? sums1[f] : 0.f;
-                const float u = second ? u1 : u0;
-                if (u != 0.f) atomicAdd(&acc[f], (acc_t)u);
+                for (int f = 0; f < 4; f++) add(acc + 8u * (uint32_t)(f ^ row), mine[f]);
+#pragma unroll
+                for (int f = 4; f < (ABS ? 6 : 5); f++) add(acc + 8u * f, sum[f]);
             }
         }
         __syncthreads();

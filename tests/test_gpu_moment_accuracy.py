@@ -26,7 +26,7 @@ def exp_c(x):
 
 def gradient_errors(B, eigenvalues, one_sign, want_abs, tiles=64):
     """The 2-norm of the difference over that of the exact gradients (mean2d: of its contributions' magnitudes): conic, mean2d,
-    opacity, rgb."""
+    opacity, rgb, and with want_abs the absolute mean2d."""
     import torch
     rng = np.random.default_rng(int(1000 * eigenvalues[1]) + one_sign)
     n, W, H = tiles * 24, 16 * tiles, 16 * 24
@@ -81,8 +81,13 @@ def gradient_errors(B, eigenvalues, one_sign, want_abs, tiles=64):
     mx, my = total(np.abs(v * dx)) * -gq, total(np.abs(v * dy)) * -gq
     of_mean = 2 * np.stack([a * mx + np.abs(b) * my, np.abs(b) * mx + cc * my], 1)
     norm = lambda got, want, of=None: float(np.linalg.norm(got - want) / np.linalg.norm(want if of is None else of))
-    return (norm(gr["conic"], want_conic), norm(gr["mean2d"], want_mean, of_mean), norm(gr["opacities"], total(v)),
-            norm(gr["rgb"][:, 0], total(alpha * d0)))
+    errors = (norm(gr["conic"], want_conic), norm(gr["mean2d"], want_mean, of_mean), norm(gr["opacities"], total(v)),
+              norm(gr["rgb"][:, 0], total(alpha * d0)))
+    if want_abs:
+        a, b, cc = ax(a), ax(b), ax(cc)
+        sizes = np.stack([total(np.abs(v * (a * dx + b * dy))), total(np.abs(v * (b * dx + cc * dy)))], 1)
+        errors += (norm(gr["mean2d_abs"], co[:, 3:].astype(np.float64) * sizes),)
+    return errors
 
 
 @pytest.mark.parametrize("want_abs", [False, True])
