@@ -48,9 +48,8 @@ struct fs_ctx {
                                          // chosen (0: none): what fs_bin_sort enqueues ahead of its read-back
     uint64_t* total_dev = nullptr;   // device: totals [4]: pairs, backward records, pairs counted per tile, longest tile list
     uint64_t* total_host = nullptr;  // pinned host block of four totals (copied from total_dev, or written by k_tile_layout)
-    uint64_t* arrivals = nullptr;    // device: the arrivals of k_tile_layout's workgroups (zero between calls), and behind them
-                                     // the totals of the counting kernel's workgroups [2][TILE_COPIES]
-    bool arrivals_dirty = false;     // a call failed where it may have left arrivals behind
+    uint64_t* counters = nullptr;    // device: TILE_COUNTERS of launch_tile_count (the first is zero between calls)
+    bool counters_dirty = false;     // a call failed where it may have left that one as it was
     ScratchBuf train_proj;           // fs_train_step: the projected splats of its view ...
     ScratchBuf train_frame;          // ... its image, dL/dimage, final_T and n_contrib
     double* loss_host = nullptr;     // its loss (three doubles, written by k_ssim_bwd), within total_host's allocation
@@ -316,8 +315,8 @@ int fs_create(fs_ctx** out, int device, void* hip_stream, const fs_config* cfg)
         fs_destroy(ctx);
         return FS_EHIP;
     }
-    if (hipMalloc(reinterpret_cast<void**>(&ctx->arrivals), (1 + 2 * TILE_COPIES) * sizeof(uint64_t)) != hipSuccess ||
-        hipMemset(ctx->arrivals, 0, sizeof(uint64_t)) != hipSuccess ||
+    if (hipMalloc(reinterpret_cast<void**>(&ctx->counters), TILE_COUNTERS * sizeof(uint64_t)) != hipSuccess ||
+        hipMemset(ctx->counters, 0, TILE_COUNTERS * sizeof(uint64_t)) != hipSuccess ||
         hipMalloc(reinterpret_cast<void**>(&ctx->total_dev), 4 * sizeof(uint64_t)) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&ctx->total_host), LOSS_HOST_AT + 3 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
@@ -343,7 +342,7 @@ void fs_destroy(fs_ctx* ctx)
     for (ScratchBuf* b : all)
         if (b->ptr) (void)hipFree(b->ptr);
     if (ctx->total_dev) (void)hipFree(ctx->total_dev);
-    if (ctx->arrivals) (void)hipFree(ctx->arrivals);
+    if (ctx->counters) (void)hipFree(ctx->counters);
     if (ctx->total_host) (void)hipHostFree(ctx->total_host);
     if (ctx->totals_event) (void)hipEventDestroy(ctx->totals_event);
     if (ctx->loss_event) (void)hipEventDestroy(ctx->loss_event);
@@ -425,15 +424,15 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
         // enqueued ahead of the read-back)
         ProfScope prof(ctx, FS_K_EMIT);
         fs_projected none = {};
-        if (ctx->arrivals_dirty) FS_HIP(launch_fill_u32(st, reinterpret_cast<uint32_t*>(ctx->arrivals), 0u, 2), "k_fill_u32");
-        ctx->arrivals_dirty = true;
+        if (ctx->counters_dirty) FS_HIP(launch_fill_u32(st, reinterpret_cast<uint32_t*>(ctx->counters), 0u, 2), "k_fill_u32");
+        ctx->counters_dirty = true;
         FS_HIP(launch_tile_count(st, n, proj ? *proj : none, cf, cd.tiles_x, tiles, tcount_p, ttotal_p,
                                  reinterpret_cast<uint2*>(ranges_p), order_p, ctx->total_host,
                                  static_cast<uint32_t*>(cb ? ctx->rec_offsets.ptr : ctx->offsets.ptr),
-                                 cb ? static_cast<uint32_t*>(ctx->rec_counts.ptr) : nullptr, ctx->arrivals, ctx->arrivals + 1,
+                                 cb ? static_cast<uint32_t*>(ctx->rec_counts.ptr) : nullptr, ctx->counters,
                                  static_cast<float*>(ctx->splats.ptr)),
                "k_tile_pairs (count)");
-        ctx->arrivals_dirty = false;
+        ctx->counters_dirty = false;
     } else {
         FS_TRY(prefix_sums());
     }

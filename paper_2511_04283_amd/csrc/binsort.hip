@@ -1039,8 +1039,9 @@ hipError_t launch_emit_pairs_cb(hipStream_t st, int64_t n, const fs_projected& p
 hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, int tiles_x,
                              int num_tiles, uint32_t* tile_count, uint32_t* tile_total, uint2* ranges,
                              uint32_t* tile_order, uint64_t* totals, uint32_t* rec_offsets, uint32_t* rec_counts,
-                             uint64_t* arrivals, uint64_t* wg_totals, float* splats)
+                             uint64_t* counters, float* splats)
 {
+    uint64_t* const wg_totals = counters + 1;
     const RecAlloc ra = {proj.tiles_touched, rec_offsets, rec_counts, wg_totals};
     {
         const dim3 grid(TILE_COPIES), block(TILE_PAIR_THREADS);
@@ -1058,7 +1059,7 @@ hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj
     const int sum_blocks = (num_tiles + 63) / 64;
     hipLaunchKernelGGL(k_tile_layout, dim3((unsigned)(sum_blocks + (n + LAYOUT_THREADS - 1) / LAYOUT_THREADS)), dim3(LAYOUT_THREADS), 0, st,
                        tile_count, num_tiles, sum_blocks, tile_total, ranges, tile_order, totals,
-                       reinterpret_cast<unsigned long long*>(arrivals), wg_totals, n, reinterpret_cast<const ushort4*>(proj.rect),
+                       reinterpret_cast<unsigned long long*>(counters), wg_totals, n, reinterpret_cast<const ushort4*>(proj.rect),
                        reinterpret_cast<const float2*>(proj.mean2d), reinterpret_cast<const float4*>(proj.conic_opacity), proj.rgb,
                        cfg, rec_offsets, reinterpret_cast<float4*>(splats));
     return hipGetLastError();

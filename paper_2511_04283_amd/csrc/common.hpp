@@ -334,10 +334,11 @@ hipError_t launch_emit_pairs_cb(hipStream_t st, int64_t n, const fs_projected& p
 // of every segment.  ranges/tile_order/tile_total: [num_tiles]; tile_count: [TILE_COPIES, num_tiles], turned by
 // launch_tile_count into each copy's start within its tile (the `cursor` of launch_tile_scatter_sort).
 // launch_tile_count also gives every Gaussian the place of its backward records (rec_offsets [n]: disjoint,
-// contiguous per Gaussian, not ordered by index; rec_counts [n], may be null: the area of its rectangle; wg_totals
-// [2][TILE_COPIES]: scratch for them), packs the splat records, and, with `arrivals` (zero at the start and left zero), writes
+// contiguous per Gaussian, not ordered by index; rec_counts [n], may be null: the area of its rectangle), packs the splat
+// records, and, with `counters` (TILE_COUNTERS uint64, the first of which is zero at the start and left zero), writes
 // totals [4] = {sum of proj.tiles_touched, records handed out, pairs counted per tile, longest list}.
 constexpr int TILE_COPIES = 256;        // workgroups of the counting / placement kernels, each with its own counters (a multiple of 64)
+constexpr int TILE_COUNTERS = 1 + 2 * TILE_COPIES;   // the arrivals of k_tile_layout's workgroups; the records and pairs of the counting ones
 constexpr int TILE_PAIR_THREADS = 1024;
 constexpr int TILE_LDS_MAX_TILES = 15360;  // their per-tile counters live in LDS (60 KB)
 constexpr int TILE_SORT_SMALL = 2048;  // longest list one workgroup sorts with 22 KB of LDS (256 threads)
@@ -348,7 +349,7 @@ constexpr int TILE_SORT_HUGE = 16384;  // ... with 146 KB (a compute unit of thi
 hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, int tiles_x,
                              int num_tiles, uint32_t* tile_count, uint32_t* tile_total, uint2* ranges,
                              uint32_t* tile_order, uint64_t* totals, uint32_t* rec_offsets, uint32_t* rec_counts,
-                             uint64_t* arrivals, uint64_t* wg_totals, float* splats);
+                             uint64_t* counters, float* splats);
 // Placement and the per-tile sorts.  pair_limit / rec_limit: how many words / gradient records the buffers hold; the
 // kernels write nothing at or beyond them and leave alone a segment that reaches beyond pair_limit, so they may be
 // enqueued before the host knows the totals.
