@@ -260,24 +260,40 @@ __device__ __forceinline__ void wave_step(double& a, double& b, double& c, uint3
 __device__ __forceinline__ uint64_t ballot(bool v) { return __builtin_amdgcn_ballot_w64(v); }
 __device__ __forceinline__ bool lane_of(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
-// Where `mask` has a lane's bit: C += w c, T = Tn, last = at.  Five vector instructions under the lane mask, where selects
-// would take two more, and no branch in the way of the instructions around them.  Whichever lanes are active stay so: the mask is
-// taken out of them and they are put back.  (Outputs are written before all inputs have been read: they share no registers.)
-__device__ __forceinline__ void blend_under_mask(uint64_t mask, float& C0, float& C1, float& C2, float& T, int& last, float c0,
-                                                 float c1, float c2, float w, float Tn, int at)
+// One list entry in the lanes of `mask`: those that it leaves at Tn >= T_min blend it (C += w c, T = Tn, last = at), the others come
+// back in `stop`.  HITS: returns the lanes that blended with w > hit_above.  Under the lane mask this is six (seven) vector
+// instructions, where selects would take more, with no branch in the way of the instructions around them; the comparison narrows
+// the mask itself, so that no scalar instruction stands between it and what depends on it.  Whichever lanes are active stay so:
+// the mask is taken out of them and they are put back.  (Outputs are written before all inputs have been read: they share no
+// registers.  `hits` is read by a vector instruction behind at least two others: it is written early.)
+template <bool HITS>
+__device__ __forceinline__ uint64_t blend_under_mask(uint64_t mask, float& C0, float& C1, float& C2, float& T, int& last, float c0, float c1,
+                                                     float c2, float w, float Tn, float T_min, float hit_above, int at, uint64_t& stop)
 {
-    uint64_t active;
-    asm("s_and_saveexec_b64 %[active], %[m]\n\t"
-        "v_fmac_f32_e32 %[C0], %[c0], %[w]\n\t"
-        "v_fmac_f32_e32 %[C1], %[c1], %[w]\n\t"
-        "v_fmac_f32_e32 %[C2], %[c2], %[w]\n\t"
-        "v_mov_b32_e32 %[T], %[Tn]\n\t"
-        "v_mov_b32_e32 %[l], %[at]\n\t"
-        "s_mov_b64 exec, %[active]"
-        : [C0] "+&v"(C0), [C1] "+&v"(C1), [C2] "+&v"(C2), [T] "+&v"(T), [l] "+&v"(last), [active] "=&s"(active)
-        : [m] "s"(mask), [c0] "v"(c0), [c1] "v"(c1), [c2] "v"(c2), [w] "v"(w), [Tn] "v"(Tn), [at] "s"(at)
-        : "scc");
+    uint64_t active, hits;
+#define FS_BLEND(COUNT)                                                                                                        \
+    asm("s_and_saveexec_b64 %[active], %[m]\n\t"                                                                               \
+        "v_cmpx_ngt_f32_e32 vcc, %[T_min], %[Tn]\n\t"                                                                          \
+        "v_mov_b32_e32 %[T], %[Tn]\n\t" COUNT                                                                                  \
+        "v_fmac_f32_e32 %[C0], %[c0], %[w]\n\t"                                                                                \
+        "v_fmac_f32_e32 %[C1], %[c1], %[w]\n\t"                                                                                \
+        "v_fmac_f32_e32 %[C2], %[c2], %[w]\n\t"                                                                                \
+        "v_mov_b32_e32 %[l], %[at]\n\t"                                                                                        \
+        "s_andn2_b64 %[stop], %[m], vcc\n\t"                                                                                   \
+        "s_mov_b64 exec, %[active]"                                                                                            \
+        : [C0] "+&v"(C0), [C1] "+&v"(C1), [C2] "+&v"(C2), [T] "+&v"(T), [l] "+&v"(last), [active] "=&s"(active), [stop] "=&s"(stop), \
+          [hits] "=&s"(hits)                                                                                                   \
+        : [m] "s"(mask), [c0] "v"(c0), [c1] "v"(c1), [c2] "v"(c2), [w] "v"(w), [Tn] "v"(Tn), [T_min] "s"(T_min), [at] "s"(at), \
+          [hit_above] "v"(hit_above)                                                                                           \
+        : "scc", "vcc");
+    if (HITS) { FS_BLEND("v_cmp_gt_f32_e64 %[hits], %[w], %[hit_above]\n\t") }
+    else { FS_BLEND("") }
+#undef FS_BLEND
+    return hits;
 }
+
+// v with `value` (uniform) in lane `at`: the instruction v_writelane_b32, for which this compiler has no builtin.
+extern "C" __device__ uint32_t fs_write_lane(uint32_t value, uint32_t at, uint32_t v) __asm("llvm.amdgcn.writelane.i32");
 
 // Longest of the four sub-tile lists of the calling wavefront (`mine` is uniform within a row).
 __device__ __forceinline__ int wave_max_of_rows(int mine)
@@ -298,8 +314,11 @@ __device__ __forceinline__ int wave_max_of_rows(int mine)
 // FS_SCORE_WEIGHT mode, alpha T > alpha_min.  32 bytes per pair: 16 sub-tiles (index wave*4 + row) x 16 bits (lane
 // within the row); only the rows with a bit set are written, packed at the start of the tile's segment, each with its Gaussian.
 // With these the count pass is a population count per pair instead of a second walk over the lists (k_score_bits).
+//
+// (80 registers: with two more, where the compiler goes by itself, a SIMD holds five wavefronts instead of six, and the kernel with the
+// record takes 129 us instead of 119 at 500k Gaussians.)
 template <bool FUSED, bool BITS>
-__global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, const uint2* __restrict__ ranges,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_render_fwd(CamDev cam, CfgDev cfg, const uint2* __restrict__ ranges,
                                                     const uint32_t* __restrict__ tile_order,
                                                     const uint32_t* __restrict__ gauss_sorted,
                                                     const float4* __restrict__ splats, float* __restrict__ image,
@@ -382,18 +401,35 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
         // a row whose 16 pixels have all finished does not lengthen the wavefront's loop
         const bool row_alive = ((~done >> (threadIdx.x & 48)) & 0xffffull) != 0;
         const int longest = wave_max_of_rows(row_alive ? mine : 0);
-        // What bounds the loop is the number of vector instructions where the chip is full (they took 96 % of the issue
-        // slots at 500k Gaussians, 1600x1064), and the latency of one trip where the longest tiles are left alone.  Four
+        // What bounds the loop is the number of vector instructions where the chip is full (a SIMD takes one in 2.35 cycles at
+        // best, and with half of its wavefronts in this loop it does), and the latency of one trip where the longest tiles are left
+        // alone (4.5 to 6 cycles for every instruction, scalar ones included).  Four
         // entries' alphas are formed side by side from one word of slots -- four independent chains -- and only the
         // transmittance runs through them one after the other; conditions are lane masks in the scalar unit and blending
-        // happens under the mask instead of through selects: 32 vector instructions per entry instead of 46 (with the
-        // record of counted pixels 35).  Lanes past their list's end evaluate the empty record.  The kernel, before and
-        // after: 4k Gaussians at 128x128 31 and 18 us, 100k at 980x545 96 and 68, 500k at 1600x1064 167 and 132.
+        // happens under the mask instead of through selects: 33 vector instructions per entry, with the record of counted
+        // pixels 36, and five scalar ones (eight where the mask was formed outside).  Lanes past their list's end evaluate the
+        // empty record.
+        // The record: each entry's 64 bits go into one lane of two registers, and 64 entries later to the slots' rows; stored
+        // entry by entry they took a 64-bit shift, an address, an LDS store and a change of the lane mask each.  Both steps together,
+        // before and after, in us, with the record: 4k Gaussians at 128x128 26.7 and 24.2, 100k at 980x545 67.7 and 60.2, 500k at
+        // 1600x1064 123.6 and 119.5, 3 M at 1920x1080 291 and 280; without it: 12k at 509x337 21.6 and 20.9, 300k and 500k the same.
         // (Skipping an entry when no lane passes the range test does not pay: four rows look at four different
         // Gaussians, so all of them missing is rare.)
         int lastk = -1;   // place on the row's list of the last Gaussian this pixel blended in this batch
         uint32_t next = s.list[sub][0];
-        for (int k = 0; k < longest && done != ~0ull; k += GROUP) {   // (leaves when all of the wavefront's pixels have terminated)
+        uint32_t hits_lo = 0, hits_hi = 0;   // BITS: lane l holds the pixels counted for place l of the four rows' lists, 64 places at a time
+        // the pixels counted for places [k0, k0 + 64), to their slots' rows
+        auto hits_to_rows = [&](int k0) {
+            const int k = k0 + ((int)threadIdx.x & 63), first = sub & 12;
+            if (k < longest) {
+#pragma unroll
+                for (int r = 0; r < 4; r++) s_pb[s.slot(first + r, k)][first + r] = (uint16_t)((r < 2 ? hits_lo : hits_hi) >> (16 * (r & 1)));
+            }
+            hits_lo = hits_hi = 0;
+        };
+        int k = 0;
+        for (; k < longest && done != ~0ull; k += GROUP) {   // (leaves when all of the wavefront's pixels have terminated)
+            if (BITS && k != 0 && (k & 63) == 0) hits_to_rows(k - 64);
             const uint32_t word = next;
             next = s.list[sub][(k / GROUP + 1) & (SLOTS / GROUP - 1)];
             float alpha[GROUP], cr[GROUP], cg[GROUP], cb[GROUP];
@@ -414,18 +450,19 @@ __global__ __launch_bounds__(256) void k_render_fwd(CamDev cam, CfgDev cfg, cons
 #pragma unroll
             for (int u = 0; u < GROUP; u++) {
                 const float Tn = T * (1.0f - alpha[u]), w = alpha[u] * T;
-                const uint64_t in = ok[u] & ~done, stop = in & ballot(Tn < cfg.T_min), blend = in ^ stop;
+                // w is alpha T with the transmittance in front of this Gaussian: where it is blended, w > alpha_min
+                // (FS_SCORE_WEIGHT) or w > 0 (FS_SCORE_ALPHA, always) decides
+                uint64_t stop;
+                const uint64_t hb = blend_under_mask<BITS>(ok[u] & ~done, C0, C1, C2, T, lastk, cr[u], cg[u], cb[u], w, Tn, cfg.T_min,
+                                                           hit_above, k + u, stop);
                 done |= stop;
-                blend_under_mask(blend, C0, C1, C2, T, lastk, cr[u], cg[u], cb[u], w, Tn, k + u);
                 if (BITS) {
-                    // w is alpha T with the transmittance in front of this Gaussian: where it is blended, w > alpha_min
-                    // (FS_SCORE_WEIGHT) or w > 0 (FS_SCORE_ALPHA, always) decides; the row's first lane stores the row's
-                    // 16 bits
-                    const uint64_t hb = blend & ballot(w > hit_above);
-                    if ((threadIdx.x & 15) == 0) s_pb[(word >> (8 * u)) & 0xffu][sub] = (uint16_t)(hb >> (threadIdx.x & 48));
+                    hits_lo = fs_write_lane((uint32_t)hb, (uint32_t)(k + u) & 63u, hits_lo);
+                    hits_hi = fs_write_lane((uint32_t)(hb >> 32), (uint32_t)(k + u) & 63u, hits_hi);
                 }
             }
         }
+        if (BITS && k != 0) hits_to_rows((k - 1) & ~63);
         last = lastk >= 0 ? (uint32_t)(start + s.slot(sub, lastk) + 1) : last;
     }
     if (BITS) {

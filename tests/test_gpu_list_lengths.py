@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from gpu_common import assert_grads_close, assert_image_close, gpu_pipeline
-from oracle import Oracle
+from oracle import Config, Oracle
 from paper_2511_04283_amd import scenes
 
 pytestmark = pytest.mark.gpu
@@ -58,3 +58,27 @@ def test_needles_among_other_splats(every, want_abs):
     assert_grads_close(out["grads"], {k: ref[k] for k in ("conic", "mean2d", "rgb", "opacities", "sh") + (("mean2d_abs",) if want_abs else ())})
     for k in ("scales", "quats", "means"):
         assert np.linalg.norm(out["grads"][k] - ref[k]) <= 1e-3 * np.linalg.norm(ref[k]), k
+
+
+@pytest.mark.parametrize("mode", ["weight", "alpha"])
+@pytest.mark.parametrize("large", [True, False])
+@pytest.mark.parametrize("n", [1, 4, 63, 64, 65, 127, 128, 129, 191, 193, 255, 256, 320, 463])
+def test_counts_of_n_entries(n, large, mode):
+    """The record of counted pixels leaves the forward kernel's registers after every 64 places of a list and at its end, also where
+    all pixels have stopped before it: the counts of such lists, from the record and from a second walk, against the oracle's."""
+    from paper_2511_04283_amd import binding as B
+    sc = scenes.tiny_scene(1900 + n, n, 29, 13, sh_degree=0, log_scale=(-0.5, 0.2) if large else (-3.2, 0.5), spread=0.6)
+    sc.opacities[:] = np.random.default_rng(n).uniform(0.006, 0.12, n) if large else 0.7
+    cam = sc.cameras[0]
+    target = np.random.default_rng(n + 1).uniform(size=(3, cam.height, cam.width)).astype(np.float32)
+    config = B.default_config()
+    config.score_mode = B.FS_SCORE_WEIGHT if mode == "weight" else B.FS_SCORE_ALPHA
+    c = B.Context("cuda:0", config)
+    out = gpu_pipeline(c, sc, cam, target=target)   # (which compares the record's counts with the walk's)
+    c.close()
+    o = Oracle(np.float32, Config(score_mode=config.score_mode))
+    p, b, image, T, nc = o.forward(sc, cam)
+    mask, thr, _ = o.error_mask(image, target)
+    assert np.array_equal(out["n_contrib"], nc)
+    assert np.array_equal(out["mask"], mask)
+    assert np.array_equal(out["counts"], o.score(p, b, cam, mask, np.zeros(n, np.int32)))
