@@ -234,7 +234,11 @@ constexpr int ss_floats(int planes_in, int planes_h)
     return planes_in * SS_IH * SS_IP > planes_h * SS_HR * SS_TW ? planes_in * SS_IH * SS_IP : planes_h * SS_HR * SS_TW;
 }
 
-struct SsimWin { float w[SS_TAPS]; };
+// The window, rounded once from double: exp(-(k - 5)^2 / (2 1.5^2)) over their sum.  Literals: with the weight in a scalar register
+// a multiply-add takes 4.3 cycles of a SIMD, with a literal or three vector registers 2.35.  Both kernels, in us, before and after:
+// 73.7 and 71.1 at 1600x1064, 57.5 and 54.4 at 1332x876, 18.6 and 17.5 at 509x337; the forward one and the loss at 1332x876 29.5 and 26.7.
+__device__ constexpr float SS_W[SS_TAPS] = {0x1.0d956c0000000p-10f, 0x1.f1fe020000000p-8f, 0x1.26eb180000000p-5f, 0x1.bff0fe0000000p-4f, 0x1.b43c400000000p-3f, 0x1.1065600000000p-2f,
+                                            0x1.b43c400000000p-3f, 0x1.bff0fe0000000p-4f, 0x1.26eb180000000p-5f, 0x1.f1fe020000000p-8f, 0x1.0d956c0000000p-10f};
 struct Floats3 { float v[3]; };
 
 // The block's input region of one channel, continued by zeros, into NP planes in LDS: a wavefront takes whole rows (their
@@ -268,8 +272,7 @@ __device__ __forceinline__ void ss_load(Fetch fetch, int H, int W, int x0, int y
 }
 
 // vertical pass for the SS_VO outputs of this lane: rows r0 .. r0+SS_VO-1 of column c of one row-filtered plane
-__device__ __forceinline__ void ss_vertical(const float (*h)[SS_TW], int r0, int c, const SsimWin& win,
-                                            float out[SS_VO])
+__device__ __forceinline__ void ss_vertical(const float (*h)[SS_TW], int r0, int c, float out[SS_VO])
 {
     float col[SS_TAPS + SS_VO - 1];
 #pragma unroll
@@ -278,14 +281,14 @@ __device__ __forceinline__ void ss_vertical(const float (*h)[SS_TW], int r0, int
     for (int o = 0; o < SS_VO; o++) {
         float a = 0.f;
 #pragma unroll
-        for (int k = 0; k < SS_TAPS; k++) a = __builtin_fmaf(win.w[k], col[k + o], a);
+        for (int k = 0; k < SS_TAPS; k++) a = __builtin_fmaf(SS_W[k], col[k + o], a);
         out[o] = a;
     }
 }
 
 // dmaps: the three derivatives of a pixel side by side (12 bytes; null: not wanted)
 __global__ __launch_bounds__(256, 6) void k_ssim_fwd(const float* __restrict__ image, const float* __restrict__ target,
-                                                  int H, int W, SsimWin win, float* __restrict__ dmaps,
+                                                  int H, int W, float* __restrict__ dmaps,
                                                   double* __restrict__ partial, int nblocks)
 {
     __shared__ __attribute__((aligned(16))) float s_buf[ss_floats(2, 4)];
@@ -330,7 +333,7 @@ __global__ __launch_bounds__(256, 6) void k_ssim_fwd(const float* __restrict__ i
             float m1 = 0.f, m2 = 0.f, esq = 0.f, e12 = 0.f;
 #pragma unroll
             for (int k = 0; k < SS_TAPS; k++) {
-                const float wk = win.w[k];
+                const float wk = SS_W[k];
                 m1 = __builtin_fmaf(wk, xv[j + k], m1);
                 m2 = __builtin_fmaf(wk, yv[j + k], m2);
                 esq = __builtin_fmaf(wk, sq[j + k], esq);
@@ -353,7 +356,7 @@ __global__ __launch_bounds__(256, 6) void k_ssim_fwd(const float* __restrict__ i
     const int c = threadIdx.x % SS_TW, r0 = (threadIdx.x / SS_TW) * SS_VO;
     float q[4][SS_VO];
 #pragma unroll
-    for (int k = 0; k < 4; k++) ss_vertical(s_h[k], r0, c, win, q[k]);
+    for (int k = 0; k < 4; k++) ss_vertical(s_h[k], r0, c, q[k]);
     const float C1 = 0.01f * 0.01f, C2 = 0.03f * 0.03f;
     const int gx = x0 + c, gy0 = y0 + r0, rows = gx < W ? min(min(SS_VO, SS_TH - r0), H - gy0) : 0;   // (may be negative)
     float* const d0 = dmaps + 3 * (plane + (size_t)gy0 * W + gx);
@@ -423,7 +426,7 @@ __global__ __launch_bounds__(RED_THREADS) void k_photo_final(const double* __res
 
 // dE/dx = c_l1 sign(x - y) - c_ss (<d_mu1> + 2 x <d_e11> + y <d_e12>),  c_l1 = (1-lambda)/N, c_ss = lambda/N
 __global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ image, const float* __restrict__ target,
-                                                  int H, int W, SsimWin win, const float* __restrict__ dmaps,
+                                                  int H, int W, const float* __restrict__ dmaps,
                                                   float c_l1, float c_ss, float* __restrict__ dL,
                                                   const double* __restrict__ partial, int nblocks, double count, double lambda,
                                                   double* __restrict__ out3)
@@ -464,7 +467,7 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ imag
             for (int j = 0; j < 4; j++) {
                 float a = 0.f;
 #pragma unroll
-                for (int i = 0; i < SS_TAPS; i++) a = __builtin_fmaf(win.w[i], v[j + i], a);
+                for (int i = 0; i < SS_TAPS; i++) a = __builtin_fmaf(SS_W[i], v[j + i], a);
                 o[j] = a;
             }
             hor[t][k] = make_float4(o[0], o[1], o[2], o[3]);
@@ -491,7 +494,7 @@ __global__ __launch_bounds__(256) void k_ssim_bwd(const float* __restrict__ imag
     __syncthreads();
     float q[3][SS_VO];
 #pragma unroll
-    for (int k = 0; k < 3; k++) ss_vertical(s_h[k], r0, c, win, q[k]);
+    for (int k = 0; k < 3; k++) ss_vertical(s_h[k], r0, c, q[k]);
 #pragma unroll
     for (int o = 0; o < SS_VO; o++) {
         const float g = q[0][o] + 2.f * x[o] * q[1][o] + y[o] * q[2][o];
@@ -595,18 +598,14 @@ int photo_blocks(int H, int W) { return ((W + SS_TW - 1) / SS_TW) * ((H + SS_TH 
 hipError_t launch_photo_loss(hipStream_t st, const float* image, const float* target, int H, int W, float lambda,
                              float* dmaps, double* partial, float* dL, double* out3)
 {
-    SsimWin win;
-    double w[SS_TAPS], sum = 0.0;
-    for (int k = 0; k < SS_TAPS; k++) { w[k] = exp(-(double)((k - SS_R) * (k - SS_R)) / (2.0 * 1.5 * 1.5)); sum += w[k]; }
-    for (int k = 0; k < SS_TAPS; k++) win.w[k] = (float)(w[k] / sum);
     const dim3 grid((unsigned)((W + SS_TW - 1) / SS_TW), (unsigned)((H + SS_TH - 1) / SS_TH), 3);
     const int nb = photo_blocks(H, W);
     const double count = 3.0 * (double)H * (double)W;
-    hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(256), 0, st, image, target, H, W, win, dL ? dmaps : nullptr, partial, nb);
+    hipLaunchKernelGGL(k_ssim_fwd, grid, dim3(256), 0, st, image, target, H, W, dL ? dmaps : nullptr, partial, nb);
     // the loss is a few thousand partials, most of whose own launch is waiting: with a gradient it is finished beside it
     // (a training iteration at 12k Gaussians / 509x337 106.3 -> 103.1 us, 300k / 1332x876 428.0 -> 424.4, 500k / 1600x1064 704.8 -> 700.2)
     if (dL)
-        hipLaunchKernelGGL(k_ssim_bwd, dim3(grid.x, grid.y + (out3 ? 1 : 0), 3), dim3(256), 0, st, image, target, H, W, win, dmaps,
+        hipLaunchKernelGGL(k_ssim_bwd, dim3(grid.x, grid.y + (out3 ? 1 : 0), 3), dim3(256), 0, st, image, target, H, W, dmaps,
                            (float)((1.0 - (double)lambda) / count), (float)((double)lambda / count), dL, partial, nb, count,
                            (double)lambda, out3);
     else if (out3)
