@@ -340,7 +340,7 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
     for (int t = threadIdx.x; t < num_tiles; t += TILE_PAIR_THREADS) s_tile[t] = SCATTER ? ranges[t].x + my_row[t] : 0u;
     __syncthreads();
     const uint32_t lane = lane_id();
-    __shared__ uint32_t s_mark[TILE_PAIR_THREADS / 64][64];
+    __shared__ uint32_t s_mark[TILE_PAIR_THREADS / 64][128];
     uint32_t* const mark = s_mark[threadIdx.x >> 6];   // this wavefront's own
     // Wavefront w of workgroup b takes the 64 Gaussians from 64 (w gridDim + b) on in its first round, so that every workgroup has as
     // much to do as the next, also where there are fewer Gaussians than threads.
@@ -422,38 +422,66 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
             rec_next += total;
         }
         uint32_t carry = 0;   // 1 + the lane whose rectangle holds candidate j0 - 1 (uniform)
-        for (uint32_t j0 = 0; j0 < total; j0 += 64) {
-            const bool live = j0 + lane < total;
-            const uint32_t j = min(j0 + lane, total - 1);
-            const uint32_t s = wave_run_owner(mark, cnt, excl, j0, carry);   // whose candidate is number j?
-            const uint32_t k = j - (uint32_t)__shfl((int)excl, (int)s, 64);
-            const uint32_t ow = (uint32_t)__shfl((int)w, (int)s, 64);
-            const uint32_t oxy = (uint32_t)__shfl((int)rect_xy, (int)s, 64);
-            const uint32_t row = rect_row(k, ow);
-            const uint32_t col = k - row * ow;
-            const uint32_t tx = (oxy & 0xffffu) + col, ty = (oxy >> 16) + row;
-            bool hit = live;
-            if (CB) {
-                const float omx = __shfl(mx, (int)s, 64), omy = __shfl(my, (int)s, 64);
-                const float oA = __shfl(A, (int)s, 64), oB = __shfl(B, (int)s, 64), oC = __shfl(C, (int)s, 64);
-                const float oQ = __shfl(Q, (int)s, 64);
-                hit = live && cb_tile_hit(omx, omy, oA, oB, oC, oQ, (int)tx, (int)ty);
+        // Candidates j0 + 64 q + lane, whose owners are lanes owners[q].  Two windows of 64 at a time where there are two: a window is a
+        // chain of some ten LDS operations (owner, its rectangle, the tile's counter) with four wavefronts on a SIMD to hide it.
+        // Counting with k_tile_layout, and placement with the sorts, one window at a time and two, in us: 155.6 and 147.2, 610 and
+        // 602 at 27 M pairs; 109.4 and 107.2, 236 and 234 at 10 M; 41.5 and 40.3, 70.6 and 68.6 at 500k Gaussians.
+        auto candidates = [&](uint32_t j0, auto& owners) {
+            constexpr int W = sizeof(owners) / sizeof(owners[0]);
+            uint32_t k[W], tile[W], od[W], oroff[W];
+            bool live[W], hit[W];
+#pragma unroll
+            for (int q = 0; q < W; q++) {
+                const uint32_t j1 = j0 + 64 * q + lane, j = min(j1, total - 1), s = owners[q];
+                live[q] = j1 < total;
+                k[q] = j - (uint32_t)__shfl((int)excl, (int)s, 64);
+                const uint32_t ow = (uint32_t)__shfl((int)w, (int)s, 64);
+                const uint32_t oxy = (uint32_t)__shfl((int)rect_xy, (int)s, 64);
+                const uint32_t row = rect_row(k[q], ow);
+                const uint32_t col = k[q] - row * ow;
+                const uint32_t tx = (oxy & 0xffffu) + col, ty = (oxy >> 16) + row;
+                hit[q] = live[q];
+                if (CB) {
+                    const float omx = __shfl(mx, (int)s, 64), omy = __shfl(my, (int)s, 64);
+                    const float oA = __shfl(A, (int)s, 64), oB = __shfl(B, (int)s, 64), oC = __shfl(C, (int)s, 64);
+                    const float oQ = __shfl(Q, (int)s, 64);
+                    hit[q] = live[q] && cb_tile_hit(omx, omy, oA, oB, oC, oQ, (int)tx, (int)ty);
+                }
+                tile[q] = ty * (uint32_t)tiles_x + tx;
+                hit[q] = hit[q] && tile[q] < (uint32_t)num_tiles;   // (always true for a rect made for this camera)
+                if (SCATTER) {
+                    od[q] = (uint32_t)__shfl((int)dbits, (int)s, 64);
+                    oroff[q] = (uint32_t)__shfl((int)roff, (int)s, 64);
+                }
             }
-            const uint32_t tile = ty * (uint32_t)tiles_x + tx;
-            hit = hit && tile < (uint32_t)num_tiles;   // (always true for a rect made for this camera)
             if (!SCATTER) {
-                if (hit) atomicAdd(&s_tile[tile], 1u);
-            } else {
-                const uint32_t od = (uint32_t)__shfl((int)dbits, (int)s, 64);
-                const uint32_t oroff = (uint32_t)__shfl((int)roff, (int)s, 64);
-                if (hit) {
-                    const uint32_t slot = atomicAdd(&s_tile[tile], 1u);
-                    if (slot < P) bucket[slot] = ((uint64_t)od << 32) | (uint32_t)(i - lane + s);
-                } else if (CB && live && (uint64_t)oroff + k < rec_limit) {
-                    float4* g = pair_grad + ((size_t)oroff + k) * (PAIR_REC / 4);
+#pragma unroll
+                for (int q = 0; q < W; q++)
+                    if (hit[q]) atomicAdd(&s_tile[tile[q]], 1u);
+                return;
+            }
+            uint32_t slot[W];
+#pragma unroll
+            for (int q = 0; q < W; q++) slot[q] = hit[q] ? atomicAdd(&s_tile[tile[q]], 1u) : P;
+#pragma unroll
+            for (int q = 0; q < W; q++) {
+                if (hit[q]) {
+                    if (slot[q] < P) bucket[slot[q]] = ((uint64_t)od[q] << 32) | (uint32_t)(i - lane + owners[q]);
+                } else if (CB && live[q] && (uint64_t)oroff[q] + k[q] < rec_limit) {
+                    float4* g = pair_grad + ((size_t)oroff[q] + k[q]) * (PAIR_REC / 4);
                     const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
                     g[0] = z; g[1] = z; g[2] = z;
                 }
+            }
+        };
+        for (uint32_t j0 = 0; j0 < total; j0 += 128) {
+            if (total - j0 > 64) {
+                uint32_t owners[2];
+                wave_run_owner2(mark, cnt, excl, j0, carry, owners);
+                candidates(j0, owners);
+            } else {
+                uint32_t owners[1] = {wave_run_owner(mark, cnt, excl, j0, carry)};
+                candidates(j0, owners);
             }
         }
     }

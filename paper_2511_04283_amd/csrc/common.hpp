@@ -193,6 +193,29 @@ __device__ __forceinline__ uint32_t wave_run_owner(uint32_t* mark, uint32_t cnt,
     return (own - 1u) & 63u;   // (own >= 1 wherever an element is: element 0 is some run's first)
 }
 
+// The same for the elements j0 + lane and j0 + 64 + lane at once: the two trips through LDS overlap.  `mark`: 128 words.
+__device__ __forceinline__ void wave_run_owner2(uint32_t* mark, uint32_t cnt, uint32_t excl, uint32_t j0, uint32_t& carry, uint32_t (&owner)[2])
+{
+    const uint32_t lane = lane_id();
+    mark[lane] = 0u;
+    mark[64 + lane] = 0u;
+    const uint32_t rel = excl - j0;
+    if (cnt != 0u && rel < 128u) mark[rel] = lane + 1u;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    uint32_t a = mark[lane], b = mark[64 + lane];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    a = wave_inclusive_max(lane == 0u ? max(a, carry) : a);
+    carry = (uint32_t)__builtin_amdgcn_readlane((int)a, 63);
+    b = wave_inclusive_max(b);
+    b = max(b, carry);   // (lanes in front of the window's first mark belong to the run before)
+    carry = (uint32_t)__builtin_amdgcn_readlane((int)b, 63);
+    owner[0] = (a - 1u) & 63u;
+    owner[1] = (b - 1u) & 63u;
+}
+
 // k / w for the place of a candidate in a rectangle w wide: estimated with the fast reciprocal, off by at most one
 // (k < 2^32 and w < 2^16 make the quotient's error < 0.02): corrected by one step either way, never by a loop that bad
 // operands could keep a wavefront in.

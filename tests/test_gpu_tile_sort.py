@@ -65,10 +65,13 @@ def test_every_list_is_long(n):
 
 
 @pytest.mark.parametrize("compact", [False, True])
-@pytest.mark.parametrize("n", [1, 63, 64, 65, 16384, 16385, 262143, 262209])
-def test_pairs_and_record_places(n, compact):
+@pytest.mark.parametrize("n, grid, most", [(1, (45, 29), 3), (63, (45, 29), 3), (64, (45, 29), 3), (65, (45, 29), 3), (16384, (45, 29), 3),
+                                           (16385, (45, 29), 3), (262143, (45, 29), 3), (262209, (45, 29), 3),
+                                           (64, (20, 30), 1), (64, (20, 30), 20), (129, (3, 1), 2), (2000, (128, 120), 40)])
+def test_pairs_and_record_places(n, grid, most, compact):
     """The counting and placement kernels deal 64 Gaussians at a time out to their workgroups: one chunk, a last one that is not
-    full, one for every workgroup and one more, one for every wavefront and a second round of one.  The order bit for bit,
+    full, one for every workgroup and one more, one for every wavefront and a second round of one.  A chunk's pairs are walked
+    128 at a time: none, fewer than 64, many, and on the largest grid of the per-tile ordering.  The order bit for bit,
     and every Gaussian's gradient records (one per tile of its rectangle) a place of their own."""
     import torch
     from paper_2511_04283_amd import binding as B
@@ -77,11 +80,11 @@ def test_pairs_and_record_places(n, compact):
     config = B.default_config()
     config.compact_box = 1 if compact else 0
     c = B.Context("cuda:0", config)
-    tx, ty = 45, 29
+    tx, ty = grid
     cam = B.make_camera(scenes.Camera(16 * tx, 16 * ty, 500.0, 500.0, 8.0 * tx, 8.0 * ty))
     t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(c.device)
     x0, y0 = rng.integers(0, tx, n), rng.integers(0, ty, n)
-    w, h = np.minimum(rng.integers(0, 4, n), tx - x0), np.minimum(rng.integers(0, 3, n), ty - y0)
+    w, h = np.minimum(rng.integers(0, most + 1, n), tx - x0), np.minimum(rng.integers(0, most, n), ty - y0)
     rect = np.stack([x0, y0, x0 + w, y0 + h], 1).astype(np.int16)
     area = w * h
     d = rng.uniform(0.2, 50.0, n).astype(np.float32)
