@@ -113,62 +113,47 @@ __global__ __launch_bounds__(RED_THREADS) void k_err_map(const float* __restrict
     }
 }
 
-// After the fused forward kernel: one workgroup adds up its per-tile partials ([5][tiles]: sum |d|; sum, min,
-// max, sum of squares of e) in a fixed order (thread b takes tiles b, b + 1024, ...; then a shuffle tree) and leaves
-// stats[0..3] = {sum e, min e, max e, sum e^2} and the L1 loss.
+// After the fused forward kernel: workgroup q folds number q of its per-tile partials ([5][tiles]: sum |d|; sum, min,
+// max, sum of squares of e) in a fixed order (thread b takes tiles b, b + 1024, ...; then a shuffle tree), which leaves
+// stats[0..3] = {sum e, min e, max e, sum e^2} and the L1 loss.  A chain of latencies (loads, six steps of the tree, sixteen
+// wavefronts' results one after the other): one workgroup for all five went through them with five times the work in each.
+// 7.1 and 4.2 us at 1600x1064; ten views of the score pass at 300k Gaussians 2016 and 1984 us, at 100k 1468 and 1432.
 constexpr int FOLD_THREADS = 1024;
+constexpr int FOLD_QUANTITIES = 5;
 __global__ __launch_bounds__(FOLD_THREADS) void k_fold_tile_stats(const double* __restrict__ tile_partial, int tiles,
                                                                   int64_t count, double* __restrict__ stats,
                                                                   double* __restrict__ loss_out)
 {
-    __shared__ double sm[5][FOLD_THREADS / 64];
-    double l1 = 0.0, s = 0.0, sq = 0.0, lo = 1.0e300, hi = -1.0e300;
-    for (int t0 = threadIdx.x; t0 < tiles; t0 += 4 * FOLD_THREADS) {   // 20 loads in flight per round
-        double v[4][5];
+    __shared__ double sm[FOLD_THREADS / 64];
+    const int q = blockIdx.x;
+    if (q == 0 && !loss_out) return;
+    const double* const part = tile_partial + (size_t)q * tiles;
+    auto fold = [&](double none, auto join) {   // (the result is thread 0's)
+        double a = none;
+        for (int t0 = threadIdx.x; t0 < tiles; t0 += 8 * FOLD_THREADS) {   // 8 loads in flight per round
+            double v[8];
 #pragma unroll
-        for (int u = 0; u < 4; u++) {
-            const int t = t0 + u * FOLD_THREADS;
-            const bool in = t < tiles;
-            v[u][0] = in ? tile_partial[t] : 0.0;
-            v[u][1] = in ? tile_partial[(size_t)tiles + t] : 0.0;
-            v[u][2] = in ? tile_partial[2 * (size_t)tiles + t] : 1.0e300;
-            v[u][3] = in ? tile_partial[3 * (size_t)tiles + t] : -1.0e300;
-            v[u][4] = in ? tile_partial[4 * (size_t)tiles + t] : 0.0;
+            for (int u = 0; u < 8; u++) v[u] = t0 + u * FOLD_THREADS < tiles ? part[t0 + u * FOLD_THREADS] : none;
+#pragma unroll
+            for (int u = 0; u < 8; u++) a = join(a, v[u]);
         }
 #pragma unroll
-        for (int u = 0; u < 4; u++) {
-            l1 += v[u][0];
-            s += v[u][1];
-            lo = v[u][2] < lo ? v[u][2] : lo;
-            hi = v[u][3] > hi ? v[u][3] : hi;
-            sq += v[u][4];
-        }
-    }
+        for (int d = 32; d >= 1; d >>= 1) a = join(a, shfl_down_f64(a, d));
+        if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = a;
+        __syncthreads();
+        a = none;
+        if (threadIdx.x == 0)
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        l1 += shfl_down_f64(l1, d);
-        s += shfl_down_f64(s, d);
-        sq += shfl_down_f64(sq, d);
-        const double a = shfl_down_f64(lo, d), b = shfl_down_f64(hi, d);
-        lo = a < lo ? a : lo;
-        hi = b > hi ? b : hi;
-    }
-    if ((threadIdx.x & 63) == 0) {
-        const int w = threadIdx.x >> 6;
-        sm[0][w] = l1; sm[1][w] = s; sm[2][w] = lo; sm[3][w] = hi; sm[4][w] = sq;
-    }
-    __syncthreads();
+            for (int w = 0; w < FOLD_THREADS / 64; w++) a = join(a, sm[w]);
+        return a;
+    };
+    double r;
+    if (q == 2) r = fold(1.0e300, [](double a, double v) { return v < a ? v : a; });
+    else if (q == 3) r = fold(-1.0e300, [](double a, double v) { return v > a ? v : a; });
+    else r = fold(0.0, [](double a, double v) { return a + v; });
     if (threadIdx.x == 0) {
-        l1 = 0.0; s = 0.0; sq = 0.0; lo = 1.0e300; hi = -1.0e300;
-        for (int w = 0; w < FOLD_THREADS / 64; w++) {
-            l1 += sm[0][w];
-            s += sm[1][w];
-            lo = sm[2][w] < lo ? sm[2][w] : lo;
-            hi = sm[3][w] > hi ? sm[3][w] : hi;
-            sq += sm[4][w];
-        }
-        stats[0] = s; stats[1] = lo; stats[2] = hi; stats[3] = sq;
-        if (loss_out) *loss_out = l1 / (double)count;
+        if (q == 0) *loss_out = r / (double)count;
+        else stats[q - 1] = r;
     }
 }
 
@@ -641,7 +626,7 @@ hipError_t launch_prune_normalize(hipStream_t st, const double* acc, int64_t n, 
 hipError_t launch_fold_tile_partials(hipStream_t st, const double* tile_partial, int tiles, int64_t count,
                                      double* stats, double* loss_out)
 {
-    hipLaunchKernelGGL(k_fold_tile_stats, dim3(1), dim3(FOLD_THREADS), 0, st, tile_partial, tiles, count, stats, loss_out);
+    hipLaunchKernelGGL(k_fold_tile_stats, dim3(FOLD_QUANTITIES), dim3(FOLD_THREADS), 0, st, tile_partial, tiles, count, stats, loss_out);
     return hipGetLastError();
 }
 
