@@ -108,17 +108,20 @@ __global__ __launch_bounds__(256) void k_copy(const float4* __restrict__ src, fl
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvec; i += stride) dst[i] = src[i];
 }
 
-// 8 independent chains of fused multiply-adds per lane; the result is stored so that nothing is optimised away
+// 8 independent chains of fused multiply-adds per lane; the result is stored so that nothing is optimised away.  Factor and
+// addend are in vector registers and the sum replaces its third operand, the form that issues fastest: with the factor in a scalar
+// register, where a kernel's argument stays, an instruction takes 4.6 cycles of a SIMD instead of 2.6 (71 and 128 TFLOP/s).
 __global__ __launch_bounds__(256) void k_fma_chain(float* __restrict__ out, int iters, float a, float b)
 {
-    float x0 = (float)threadIdx.x, x1 = x0 + 1.f, x2 = x0 + 2.f, x3 = x0 + 3.f, x4 = x0 + 4.f, x5 = x0 + 5.f,
-          x6 = x0 + 6.f, x7 = x0 + 7.f;
-    for (int i = 0; i < iters; i++) {
-        x0 = __builtin_fmaf(x0, a, b); x1 = __builtin_fmaf(x1, a, b); x2 = __builtin_fmaf(x2, a, b);
-        x3 = __builtin_fmaf(x3, a, b); x4 = __builtin_fmaf(x4, a, b); x5 = __builtin_fmaf(x5, a, b);
-        x6 = __builtin_fmaf(x6, a, b); x7 = __builtin_fmaf(x7, a, b);
-    }
-    out[(size_t)blockIdx.x * blockDim.x + threadIdx.x] = ((x0 + x1) + (x2 + x3)) + ((x4 + x5) + (x6 + x7));
+    asm volatile("" : "+v"(a), "+v"(b));
+    float x[8];
+#pragma unroll
+    for (int k = 0; k < 8; k++) x[k] = (float)threadIdx.x + (float)k;
+#pragma unroll 8
+    for (int i = 0; i < iters; i++)
+#pragma unroll
+        for (int k = 0; k < 8; k++) x[k] = __builtin_fmaf(a, b, x[k]);
+    out[(size_t)blockIdx.x * blockDim.x + threadIdx.x] = ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
 }
 
 int stream_blocks(int64_t work_items)

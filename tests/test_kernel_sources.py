@@ -2,6 +2,7 @@
 import glob
 import os
 import re
+import subprocess
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2511_04283_amd", "csrc")
 
@@ -36,3 +37,21 @@ def test_inline_assembly_gives_back_the_lanes_it_found():
             assert restored.startswith(f"s_mov_b64 exec, {saved.group(1)}"), (path, restored)
             assert not any("exec" in line for line in steps[1:-1]), path
     assert seen == 1
+
+
+def test_multiply_add_rate_is_measured_on_vector_registers():
+    """fs_measure_peaks times chains of multiply-adds as the fastest that the kernels could issue.  One that reads a scalar register
+    takes nearly twice as long on this chip as one of vector registers only, and a kernel's arguments arrive in scalar ones."""
+    from paper_2511_04283_amd import build
+    flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-Wall")]
+    asm = subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), *flags, "-w", "-I", os.path.join(build.ROOT, "include"), "-I", CSRC,
+                          "--cuda-device-only", "-S", "-o", "-", os.path.join(CSRC, "optimizer.hip")], check=True, capture_output=True,
+                         text=True).stdout
+    kernel = re.search(r"^\w*k_fma_chain\w*:(.*?)s_endpgm", asm, re.S | re.M).group(1)
+    chains = re.findall(r"^\s+(v_fma\w*)\s+(.*)$", kernel, re.M)
+    for name, operands in chains:
+        assert all(re.fullmatch(r"v\d+", o.strip()) for o in operands.split(";")[0].split(",")), (name, operands)
+    # (and no other vector instruction between them)
+    loop = re.search(r"^(\.\w+):[^\n]*\n((?:(?!^\.\w+:).)*?)s_cbranch_\w+ \1", kernel, re.S | re.M).group(2)
+    work = [line.split()[0] for line in loop.splitlines() if line.strip() and not line.strip().startswith(";")]
+    assert sum(w.startswith("v_fma") for w in work) >= 64 and sum(w.startswith("v_") and not w.startswith("v_fma") for w in work) == 0, work
