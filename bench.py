@@ -29,7 +29,7 @@ FWD_FLOPS_PER_EVAL = 11     # dx, dy, q (2 mul + 2 fma + mul), -0.5*q
 FWD_FLOPS_PER_BLEND = 26    # exp (mul, rint, sub, 5 fma, ldexp) 14; alpha 2; T 2; w 1; colour 3 fma 6; + min
 BWD_FLOPS_PER_EVAL = 11
 BWD_FLOPS_PER_BLEND = 66    # exp 14; alpha 2; 1/(1-a), T, w 4; colour/alpha grads 17; conic/mean grads 20; 9-value sum 9
-PEAK_FP32_TFLOPS = 157.3    # MI355X vector fp32 (packed FMA), 256 CU x 4 SIMD x 16 lanes x 2 x 2 x 2.4 GHz
+PEAK_FP32_TFLOPS = 157.3    # MI355X vector fp32, 256 CU x 4 SIMD x 16 lanes x 2 (packed, or two wavefronts at a time) x 2 (FMA) x 2.4 GHz
 PEAK_HBM_GBS = 8000.0
 KERNEL_OF_GROUP = {"preprocess": "k_preprocess", "scan": "k_scan_*", "emit_pairs": "k_tile_pairs (count) + k_tile_layout",
                    "order_pairs": "k_tile_pairs (placement) + k_tile_sort", "tile_ranges": "k_tile_ranges + k_tile_order",
@@ -365,7 +365,7 @@ def main() -> int:
 
     copy_gbs, fma_tf = ctx.fs_measure_peaks(1 << 30)
     out["measured_peaks"] = {"copy_GBps": round(copy_gbs, 1), "fp32_fma_TFLOPs_unpacked": round(fma_tf, 2),
-                             "note": "1 GiB device copy (read + write) and chains of independent v_fma_f32, same process"}
+                             "note": "1 GiB device copy (read + write) and chains of independent multiply-adds of vector registers, same process"}
     if not args.no_cpu_baseline and not args.train_iteration:   # (the oracle leg times the hot path on the untouched scene)
         out["cpu_baseline"] = cpu_baseline(args, sc, cam, target_np, out["loss"], tiles)
     print(json.dumps(out))

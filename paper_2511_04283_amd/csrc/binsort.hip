@@ -6,6 +6,8 @@
 // the 3-sigma rule (or the Compact Box) produces.  A pair's key is tile_id << 32 | bits(depth).  Two ways
 // to the same order live here: the tile-bucketed one (count per tile, place, sort each tile's segment in
 // LDS), used whenever the lists are short enough, and a global stable LSD radix sort of index-ordered keys.
+//
+// Times "at 500k Gaussians" and the like are of the scenes of perf/cases.py, those at 10 M and 27 M pairs of bench.py's largest.
 #include <algorithm>
 
 #include "common.hpp"
@@ -499,13 +501,15 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
 //
 // Whichever of them is done last then turns the tile totals into ranges [first, last), by an exclusive scan (thread t owns
 // the consecutive tiles [t*per, t*per + per)); totals[2] = sum,
-// totals[3] = longest list (totals[0..1] come from the counting kernel's two counters); and the order in which
+// totals[3] = longest list, totals[0..1] = the sums of the counting workgroups' totals (wg_totals); and the order in which
 // the render kernels take the tiles (longest list first, bucketed by length / 8, as k_tile_order).
 //
 // The other workgroups pack the projected splats into the records the render kernels gather (SPLAT_REC).  The placement
 // kernel did this on the way, with one workgroup per compute unit; here it has the whole chip and hides the chain of the
 // two steps above, and the records no longer drive the placement's half-filled lines out of the L2.
 // Placement, sums and scan together, before and after: 222 and 185 us at 3 M Gaussians / 10 M pairs, 18.3 and 16.8 at 4k.
+// They also complete the record places of all Gaussians (4 bytes read and written for each): this launch went from 20.7 to 21.8 us at
+// 500k Gaussians and from 64 to 69 at 3 M with it, the counting kernel from 18.1 to 12.6 and from 43.5 to 39.
 constexpr int LAYOUT_THREADS = 1024;
 constexpr int LAYOUT_WAVES = LAYOUT_THREADS / 64;
 __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __restrict__ count, int num_tiles, int sum_blocks,

@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256) void k_err_mask_stats(const float* __restrict_
 // One workgroup produces a 32-wide block of one channel: the block's input region goes to LDS, a horizontal 11-tap pass
 // (one lane: 4 neighbouring columns of one row, sliding over 14 inputs) leaves the row-filtered planes in registers and then
 // in the same LDS, and a vertical pass (one lane: SS_VO neighbouring rows of one column) finishes.
-// Vector instructions bound both kernels: 102 multiply-adds per value forward (44 of them 48/38 times for the rows of the
+// Vector instructions weigh most in both kernels: 102 multiply-adds per value forward (44 of them 48/38 times for the rows of the
 // halo), about 210 instructions in all.  What went, against a 32x32 block with separate LDS for the row-filtered planes, which
 // took 260: the inputs' addresses and edge tests (a wavefront loads whole rows), 3 of 12 memory instructions per value (the
 // three derivative maps lie side by side), and the serial epilogue (all of a lane's outputs are formed at once and only the
@@ -220,7 +220,7 @@ constexpr int ss_floats(int planes_in, int planes_h)
 }
 
 // The window, rounded once from double: exp(-(k - 5)^2 / (2 1.5^2)) over their sum.  Literals: with the weight in a scalar register
-// a multiply-add takes 4.3 cycles of a SIMD, with a literal or three vector registers 2.35.  Both kernels, in us, before and after:
+// a run of multiply-adds takes 4.4 cycles of a SIMD each, with a literal or three vector registers 2.6.  Both kernels, in us, before and after:
 // 73.7 and 71.1 at 1600x1064, 57.5 and 54.4 at 1332x876, 18.6 and 17.5 at 509x337; the forward one and the loss at 1332x876 29.5 and 26.7.
 __device__ constexpr float SS_W[SS_TAPS] = {0x1.0d956c0000000p-10f, 0x1.f1fe020000000p-8f, 0x1.26eb180000000p-5f, 0x1.bff0fe0000000p-4f, 0x1.b43c400000000p-3f, 0x1.1065600000000p-2f,
                                             0x1.b43c400000000p-3f, 0x1.bff0fe0000000p-4f, 0x1.26eb180000000p-5f, 0x1.f1fe020000000p-8f, 0x1.0d956c0000000p-10f};

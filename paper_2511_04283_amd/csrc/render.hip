@@ -20,6 +20,10 @@
 // where written as __builtin_fmaf; the file is compiled with -ffp-contract=off) so that the
 // integer outputs they decide (n_contrib, counts) can be reproduced bit for bit on a CPU.  The
 // octagon only ever drops (Gaussian, pixel) pairs that this arithmetic would reject as well.
+//
+// Times "at 500k Gaussians and 1600x1064" and the like are of the scenes of perf/cases.py.  They have other pairs than those of
+// bench.py with the same sizes: 6 k against 11 k at 4k Gaussians and 128x128, 0.4 M to 0.5 M against 0.5 M at 100k, 2.1 M to 2.9 M
+// against 1.4 M at 500k, 11 M to 13 M against 10 M at 3 M (wide: 30 M to 37 M against 27 M).
 #include "common.hpp"
 
 namespace fs {
@@ -316,7 +320,7 @@ __device__ __forceinline__ int wave_max_of_rows(int mine)
 // With these the count pass is a population count per pair instead of a second walk over the lists (k_score_bits).
 //
 // (80 registers: with two more, where the compiler goes by itself, a SIMD holds five wavefronts instead of six, and the kernel with the
-// record takes 129 us instead of 119 at 500k Gaussians.)
+// record takes 129 us instead of 119 at 500k Gaussians and 1600x1064.)
 template <bool FUSED, bool BITS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_render_fwd(CamDev cam, CfgDev cfg, const uint2* __restrict__ ranges,
                                                     const uint32_t* __restrict__ tile_order,
@@ -401,18 +405,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_re
         // a row whose 16 pixels have all finished does not lengthen the wavefront's loop
         const bool row_alive = ((~done >> (threadIdx.x & 48)) & 0xffffull) != 0;
         const int longest = wave_max_of_rows(row_alive ? mine : 0);
-        // What bounds the loop is the number of vector instructions where the chip is full (a SIMD takes one in 2.35 cycles at
-        // best, and with half of its wavefronts in this loop it does), and the latency of one trip where the longest tiles are left
+        // What weighs in the loop is the number of vector instructions where the chip is full (a SIMD takes one of this mixture in
+        // 2.3 cycles at best; over the whole kernel one takes 3.3 to 4.0 at bench.py's 3 M and 500k Gaussians), and the latency of one trip where the longest tiles are left
         // alone (4.5 to 6 cycles for every instruction, scalar ones included).  Four
         // entries' alphas are formed side by side from one word of slots -- four independent chains -- and only the
         // transmittance runs through them one after the other; conditions are lane masks in the scalar unit and blending
-        // happens under the mask instead of through selects: 33 vector instructions per entry, with the record of counted
-        // pixels 36, and five scalar ones (eight where the mask was formed outside).  Lanes past their list's end evaluate the
-        // empty record.
+        // happens under the mask instead of through selects: a trip of four entries has 126 vector and 37 scalar instructions, the
+        // loop's own included (41 scalar ones where the mask was formed outside), with the record of counted pixels 139 and 44 (140
+        // and 53).  Lanes past their list's end evaluate the empty record.
         // The record: each entry's 64 bits go into one lane of two registers, and 64 entries later to the slots' rows; stored
         // entry by entry they took a 64-bit shift, an address, an LDS store and a change of the lane mask each.  Both steps together,
-        // before and after, in us, with the record: 4k Gaussians at 128x128 26.7 and 24.2, 100k at 980x545 67.7 and 60.2, 500k at
-        // 1600x1064 123.6 and 119.5, 3 M at 1920x1080 291 and 280; without it: 12k at 509x337 21.6 and 20.9, 300k and 500k the same.
+        // before and after, kernel durations in us, with the record: 4k Gaussians at 128x128 18.7 and 16.9, 100k at 980x545 54.8 and
+        // 50.0, 500k at 1600x1064 124.5 and 117.3, 3 M at 1920x1080 276 and 265; without it: 4k 13.4 and 12.2, 12k at 509x337 17.7 and
+        // 17.3, 300k at 1332x876 (two scenes) 68.3 and 68.6, 64.3 and 65.7, 500k 88.4 and 88.4.
         // (Skipping an entry when no lane passes the range test does not pay: four rows look at four different
         // Gaussians, so all of them missing is rare.)
         int lastk = -1;   // place on the row's list of the last Gaussian this pixel blended in this batch
@@ -539,7 +544,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_re
 // them times something that belongs to the pixel alone: w times the pixel's dL/dC (3 sums), and v times the pixel's place,
 // {1, x, y, x^2, x y, y^2} (dL/dsigma, and the moments from which dL/dconic and dL/dmu_2D follow).
 //
-// Vector instructions bound this kernel (they took every issue slot), and forming nine products per pixel and adding them up
+// Vector instructions weigh most in this kernel, and forming nine products per pixel and adding them up
 // across a row's 16 lanes took half of them.  So the numbers change places first: after eight entries of every row's list a
 // wavefront writes its 8 x 64 w's (then its v's) to LDS and reads them back with the 32 (entry, row) combinations across its
 // lanes, two lanes to a combination and eight pixels to a lane.  The sums over pixels are then plain additions within a
@@ -564,13 +569,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_re
 // run to run unless the exponents of those terms span more than 29 bits.
 //
 // What else shapes the inner loop is what this chip's vector unit and LDS do with an instruction (measured, in cycles of one SIMD):
-// it takes plain additions, products and three-register multiply-adds from two wavefronts at a time, 2.35 each; an exponential or a
-// reciprocal (8.3), a data-parallel move, a permutation of the lanes or a read of one lane (4.3) also ends that for some sixteen
-// instructions after it, wherever it stands: so they stand together (the reciprocals of four entries, the exchange between
-// the two lanes).  An LDS add of doubles takes 8.4 cycles of its compute unit where all lanes name places of their own, 44 where
+// it takes them from two wavefronts at a time, 2.2 to 2.6 each, as long as one in two is a plain addition, product or multiply-add of
+// vector registers (4.4 in an unbroken run of comparisons, minima, selects, shifts, conversions or operations with a scalar
+// operand); an exponential or a reciprocal (8.4), a data-parallel move, a permutation of the lanes or a read of one lane (4.3) ends that
+// for some sixteen instructions after it (one in 16: 4.2 on average, one in 32: 3.6), wherever it stands: so they stand
+// together (the reciprocals of four entries, the exchange between
+// the two lanes).  An LDS add of doubles takes 8 cycles of its compute unit where all lanes name places of their own, 44 where
 // four lanes name each: the adds were a seventh of the kernel, and now rows take turns (see there).  ABS needs no more exchanges:
-// its sums are formed behind the one of the v's.  Together, before and after, in us: 500k Gaussians at 1600x1064 225 and 212, 3 M
-// at 1920x1080 543 and 512, 100k at 980x545 81 and 78; with ABS 253 and 222 (500k, Compact Box), 176 and 153 (300k at 1332x876).
+// its sums are formed behind the one of the v's.  Together, before and after, kernel durations in us: 500k Gaussians at 1600x1064 224
+// and 207, 3 M at 1920x1080 512 and 484, 100k at 980x545 74.5 and 70.5; with ABS 245 and 216 (500k, Compact Box), 170 and 152 (300k at
+// 1332x876).
+// A trip of eight entries has about 415 vector instructions (without needles), which at these rates would take a SIMD 1 050
+// cycles, 2.55 for each; over the whole kernel one takes 4.1 to 4.8 at bench.py's 3 M (wide) and 500k Gaussians.  What the other two
+// fifths are spent on (the LDS adds and exchanges, their waits, wavefronts that end early) has not been taken apart.
 //
 // ABS adds the absolute positional gradient (used by FastGS for the split decision): per pixel the
 // magnitudes |dL/dmu_x|, |dL/dmu_y| of its own contribution, summed like the other values and stored

@@ -122,8 +122,8 @@ def main() -> int:
             row["valu"] = c.get("SQ_INSTS_VALU", 0.0)
             row["lds"] = c.get("SQ_INSTS_LDS", 0.0)
             # vector instructions per SIMD and 4 cycles of a fixed nominal clock, over the dispatch's own duration under the
-            # counters; not given for kernels under 30 us, whose ramp-up and tail dominate.  No utilisation: long runs of
-            # v_fma_f32 or v_cmp read 0.92 here, of v_mul_f32, v_mov_b32 or v_add_u32, which take two cycles instead of four, 1.7
+            # counters; not given for kernels under 30 us, whose ramp-up and tail dominate.  No utilisation: instructions take
+            # different times, see the text below
             row["issue"] = c.get("SQ_INSTS_VALU", 0.0) * 4.0 / (dur_s * CLOCK_GHZ * 1e9 * SIMDS) if dur_s >= 30e-6 else None
             act = c.get("SQ_ACTIVE_INST_VALU", 0.0)
             row["lanes"] = c.get("SQ_THREAD_CYCLES_VALU", 0.0) / (act * 64.0) if act else None
@@ -168,8 +168,9 @@ def main() -> int:
         f.write(f"Durations: `*_kernel_stats.csv` of the first run (averages over all calls of the run).  HBM bytes per launch: "
                 f"FETCH_SIZE x {f_scale:.3f} and WRITE_SIZE x {w_scale:.3f} (KiB -> bytes), the factors with which the 256 MiB "
                 "`__amd_rocclr_copyBuffer` of the same runs reads as 256 MiB each way.  Vector-issue rate = SQ_INSTS_VALU x 4 cycles "
-                f"/ (duration x {CLOCK_GHZ} GHz x {SIMDS} SIMDs), only for kernels of 30 us and more (an unbroken run of v_fma_f32 or v_cmp "
-                "reads 0.92, of v_mul_f32, v_mov_b32 or v_add_u32, which take two cycles, 1.7: no utilisation, and mixtures exceed 1); lane utilisation = "
+                f"/ (duration x {CLOCK_GHZ} GHz x {SIMDS} SIMDs), only for kernels of 30 us and more (no utilisation: an unbroken run "
+                "of additions, products, multiply-adds or moves of vector registers reads 1.6, of comparisons, minima, selects, shifts, conversions or anything with "
+                "a scalar operand 0.9, of exponentials or reciprocals 0.48; where at least every second one is of the first kind, 1.8); lane utilisation = "
                 "SQ_THREAD_CYCLES_VALU / (SQ_ACTIVE_INST_VALU x 64); LDS conflict rate = SQ_LDS_BANK_CONFLICT / SQ_LDS_IDX_ACTIVE.  "
                 "MB = 1e6 bytes.\n\n")
         f.write("| kernel | calls | avg us | min us | % GPU time | fetch MB | write MB | GB/s | VALU insts | issue rate | lane util | LDS conflict |\n")
