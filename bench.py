@@ -280,7 +280,7 @@ def main() -> int:
     else:
         rows_masked_tiles = pairs_masked_tiles
 
-    # algorithmic work per launch of each kernel group (the design doc section 7 states the per-unit figures)
+    # algorithmic work per launch of each kernel group (bytes and operations that the step cannot do without)
     g_in = 4 * (3 + 3 + 4 + 1 + 3 * K)            # bytes of one Gaussian's parameters (236 at degree 3)
     g_proj = 8 + 4 + 16 + 12 + 8 + 4 + 3           # bytes of one projected splat (fs_projected)
     copies = 256                                   # workgroups of the counting / placement kernels
