@@ -38,15 +38,16 @@ constexpr int GROUP = 4;          // entries of a sub-tile list that a lane eval
 // fused), scaled by 2^n.  No range clamp: the scaling underflows to zero by itself where t is finite; t = -infinity, which
 // conics at the end of the single-precision range give, would leave a NaN and is what takes_part keeps out.
 __device__ __forceinline__ float exponent_of(float x) { return x * 0x1.715476p+0f; }
+__device__ constexpr float EXP_C[5] = {0x1.5bba14p-10f, 0x1.3cea88p-7f, 0x1.c6b752p-5f, 0x1.ebf9bcp-3f, 0x1.62e42ap-1f};
 __device__ __forceinline__ float exp_c(float t)
 {
     const float n = __builtin_rintf(t);
     const float r = t - n;
-    float p = 0x1.5bba14p-10f;
-    p = __builtin_fmaf(p, r, 0x1.3cea88p-7f);
-    p = __builtin_fmaf(p, r, 0x1.c6b752p-5f);
-    p = __builtin_fmaf(p, r, 0x1.ebf9bcp-3f);
-    p = __builtin_fmaf(p, r, 0x1.62e42ap-1f);
+    float p = EXP_C[0];
+    p = __builtin_fmaf(p, r, EXP_C[1]);
+    p = __builtin_fmaf(p, r, EXP_C[2]);
+    p = __builtin_fmaf(p, r, EXP_C[3]);
+    p = __builtin_fmaf(p, r, EXP_C[4]);
     p = __builtin_fmaf(p, r, 1.0f);
     return __builtin_ldexpf(p, (int)n);
 }
@@ -61,6 +62,9 @@ __device__ __forceinline__ uint64_t takes_part_mask(float t)
     asm("v_cmp_class_f32_e64 %0, %1, %2" : "=s"(mask) : "v"(t), "s"(TAKES_PART));
     return mask;
 }
+
+// One step of four entries' chains of arithmetic: nothing moves into it or out of it.
+#define FS_STEP __builtin_amdgcn_sched_barrier(0); _Pragma("unroll") for (int u = 0; u < GROUP; u++)
 
 // 16-byte streaming (non-temporal) store / load
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -701,67 +705,93 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
         g_next = entry(start - B);   // (its latency passes during the walk)
         const int longest = wave_max_of_rows(mine);
         const uint32_t last_here = (uint32_t)max(last - start, 0);   // slots below this one hold entries this pixel blended (or examined)
+        uint64_t acted = 0;   // lanes that blend any of the trip's entries
+        // the records of a word's four slots
+        float4 r0[GROUP], r1[GROUP];
+        float cb[GROUP];
+        uint32_t js[GROUP];
+        auto fetch = [&](uint32_t word) {
+#pragma unroll
+            for (int u = 0; u < GROUP; u++) {
+                js[u] = (word >> (8 * u)) & 0xffu;
+                r0[u] = s.r0[js[u]];
+                r1[u] = s.r1[js[u]];
+                cb[u] = s.r2[js[u]].z;   // (16 bytes twice and 4 are read faster than 16, 8 and 12)
+            }
+        };
+        float alpha[GROUP], G[GROUP], cd[GROUP], inv[GROUP];
+        // The four entries' alphas and what else does not depend on the transmittance, one step of all four after the other: a result
+        // is read 8.4 cycles after its instruction was issued, the next independent one is issued after 5.2.  The compiler by itself
+        // forms one alpha after the other, each behind the wait for its own record.  Kernel durations before and after, in us: 4k Gaussians
+        // at 128x128 23.6 and 22.4, 100k at 980x545 57.5 and 54.4, 12k at 509x337 28.3 and 26.7; where the chip is full 1 to 2 % (500k at
+        // 1600x1064 175 and 173): there the LDS takes as long as the vector units do (three of four fetches left out: 0.85 of the time).
+        auto evaluate = [&]() {
+            float dx[GROUP], dy[GROUP], tx[GROUP], ty[GROUP], t[GROUP], n[GROUP], sG[GROUP], al[GROUP];
+            uint64_t act[GROUP], capped[GROUP];
+            FS_STEP { dx[u] = p.px - r0[u].x; dy[u] = p.py - r0[u].y; }
+            FS_STEP { tx[u] = r0[u].z * dx[u]; ty[u] = r1[u].x * dy[u]; }
+            FS_STEP { tx[u] = __builtin_fmaf(r0[u].w, dy[u], tx[u]); ty[u] = ty[u] * dy[u]; }
+            FS_STEP { t[u] = __builtin_fmaf(dx[u], tx[u], ty[u]); cd[u] = r1[u].z * dC0; }
+            FS_STEP { t[u] = exponent_of(t[u]); cd[u] = __builtin_fmaf(r1[u].w, dC1, cd[u]); }
+            FS_STEP { n[u] = __builtin_rintf(t[u]); cd[u] = __builtin_fmaf(cb[u], dC2, cd[u]); }   // dC . c
+            FS_STEP { act[u] = takes_part_mask(t[u]); t[u] = t[u] - n[u]; }
+            FS_STEP { G[u] = __builtin_fmaf(EXP_C[0], t[u], EXP_C[1]); }
+            FS_STEP { G[u] = __builtin_fmaf(G[u], t[u], EXP_C[2]); }
+            FS_STEP { G[u] = __builtin_fmaf(G[u], t[u], EXP_C[3]); act[u] &= ballot(js[u] < last_here); }
+            FS_STEP { G[u] = __builtin_fmaf(G[u], t[u], EXP_C[4]); }
+            FS_STEP { G[u] = __builtin_fmaf(G[u], t[u], 1.0f); }
+            FS_STEP { G[u] = __builtin_ldexpf(G[u], (int)n[u]); }
+            FS_STEP { sG[u] = r1[u].y * G[u]; }
+            FS_STEP { al[u] = fminf(cfg.alpha_max, sG[u]); }
+            FS_STEP { capped[u] = ballot(sG[u] > cfg.alpha_max); act[u] &= ballot(al[u] >= cfg.alpha_min); }
+            // lanes that do not blend this Gaussian run the same arithmetic with alpha = G = 0: w and v are
+            // exact zeros (and T / (1 - 0) leaves T as it is); a capped alpha is a constant: G = 0
+            FS_STEP { acted |= act[u]; alpha[u] = lane_of(act[u]) ? al[u] : 0.f; }
+            FS_STEP { G[u] = lane_of(act[u] & ~capped[u]) ? G[u] : 0.f; inv[u] = 1.0f - alpha[u]; }
+            FS_STEP { inv[u] = __builtin_amdgcn_rcpf(inv[u]); }
+            __builtin_amdgcn_sched_barrier(0);
+        };
         for (int k = 0; k < longest; k += SPAN) {
             const uint2 words = *reinterpret_cast<const uint2*>(&s.list[sub][k / 4]);
             float w[SPAN], v[SPAN];
-            uint64_t acted = 0;
+            acted = 0;
+            auto chain = [&](int g) {
 #pragma unroll
-            for (int g = 0; g < SPAN; g += GROUP) {
-                const uint32_t word = g ? words.y : words.x;
-                float alpha[GROUP], G[GROUP], cd[GROUP], inv[GROUP];
-                if (g == 0 || k + g < longest) {
-#pragma unroll
-                    for (int u = 0; u < GROUP; u++) {
-                        const uint32_t j = (word >> (8 * u)) & 0xffu;
-                        const float4 r0 = s.r0[j], r1 = s.r1[j];
-                        const float cb = s.r2[j].z;   // (16 bytes twice and 4 are read faster than 16, 8 and 12)
-                        const float dx = p.px - r0.x, dy = p.py - r0.y;
-                        const float tx = r0.z * dx, ty = r1.x * dy;
-                        const float h = __builtin_fmaf(r0.w, dy, tx);
-                        const float t = exponent_of(__builtin_fmaf(dx, h, ty * dy));
-                        const float e = exp_c(t);
-                        const float sG = r1.y * e;
-                        const float al = fminf(cfg.alpha_max, sG);
-                        const uint64_t act = ballot(j < last_here) & takes_part_mask(t) & ballot(al >= cfg.alpha_min);
-                        const uint64_t capped = ballot(sG > cfg.alpha_max);
-                        acted |= act;
-                        // lanes that do not blend this Gaussian run the same arithmetic with alpha = G = 0: w and v are
-                        // exact zeros (and T / (1 - 0) leaves T as it is); a capped alpha is a constant: G = 0
-                        alpha[u] = lane_of(act) ? al : 0.f;
-                        G[u] = lane_of(act & ~capped) ? e : 0.f;
-                        inv[u] = 1.0f - alpha[u];
-                        cd[u] = __builtin_fmaf(cb, dC2, __builtin_fmaf(r1.w, dC1, r1.z * dC0));   // dC . c
-                    }
-                    __builtin_amdgcn_sched_barrier(0);   // (side by side)
-#pragma unroll
-                    for (int u = 0; u < GROUP; u++) inv[u] = __builtin_amdgcn_rcpf(inv[u]);
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int u = 0; u < GROUP; u++) {
-                        T = T * inv[u];                                  // transmittance in front of this Gaussian
-                        w[g + u] = alpha[u] * T;
-                        const float diff = cd[u] - S;
-                        v[g + u] = G[u] * (T * diff);                    // G dL/dalpha: d/d sigma
-                        S = __builtin_fmaf(alpha[u], diff, S);
-                    }
-                } else {
-#pragma unroll
-                    for (int u = 0; u < GROUP; u++) w[g + u] = v[g + u] = 0.f;
+                for (int u = 0; u < GROUP; u++) {
+                    T = T * inv[u];                                  // transmittance in front of this Gaussian
+                    w[g + u] = alpha[u] * T;
+                    const float diff = cd[u] - S;
+                    v[g + u] = G[u] * (T * diff);                    // G dL/dalpha: d/d sigma
+                    S = __builtin_fmaf(alpha[u], diff, S);
                 }
+            };
+            fetch(words.x);
+            evaluate();
+            const uint32_t slot = ent_list[k];
+            if (k + GROUP < longest) {
+                fetch(words.y);   // (on its way during the chain)
+                __builtin_amdgcn_sched_barrier(0);
+                chain(0);
+                evaluate();
+                chain(GROUP);
+            } else {
+                chain(0);
+#pragma unroll
+                for (int u = 0; u < GROUP; u++) w[GROUP + u] = v[GROUP + u] = 0.f;
             }
             if (acted == 0) continue;
-            const uint32_t slot = ent_list[k];
             const float mu_x = s.r0[slot].x, mu_y = s.r0[slot].y;
             const bool needle = __float_as_uint(s.r2[slot].w) & NEEDLE;
             float sums0[6], sums1[6];   // the first lane's, the second one's
-            float4 a, b;
-            exchange(w, a, b);
+            float4 wa, wb, a, b;
+            exchange(w, wa, wb);
+            exchange(v, a, b);   // (its writes need not wait for the reads before them)
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int ch = 0; ch < 3; ch++)
-                sums0[ch] = (__builtin_fmaf(b.w, g2[ch][3], __builtin_fmaf(b.z, g2[ch][2], __builtin_fmaf(b.y, g2[ch][1],
-                                   __builtin_fmaf(b.x, g2[ch][0], __builtin_fmaf(a.w, g1[ch][3], __builtin_fmaf(a.z, g1[ch][2],
-                                   __builtin_fmaf(a.y, g1[ch][1], a.x * g1[ch][0]))))))));
-            exchange(v, a, b);
+                sums0[ch] = (__builtin_fmaf(wb.w, g2[ch][3], __builtin_fmaf(wb.z, g2[ch][2], __builtin_fmaf(wb.y, g2[ch][1],
+                                   __builtin_fmaf(wb.x, g2[ch][0], __builtin_fmaf(wa.w, g1[ch][3], __builtin_fmaf(wa.z, g1[ch][2],
+                                   __builtin_fmaf(wa.y, g1[ch][1], wa.x * g1[ch][0]))))))));
             {
                 const float dx[4] = {px0 - mu_x, column(1) - mu_x, column(2) - mu_x, column(3) - mu_x}, dy1 = py1 - mu_y, dy2 = py2 - mu_y;
                 const float dxx[4] = {dx[0] * dx[0], dx[1] * dx[1], dx[2] * dx[2], dx[3] * dx[3]};
