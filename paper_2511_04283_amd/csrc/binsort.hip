@@ -622,8 +622,9 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
     if (threadIdx.x == 1023) {
         // totals: sum of tiles_touched, backward records, pairs counted per tile, longest list; the arrivals start the
         // next call at zero
-        totals[2] = run;
-        totals[3] = max_s;
+        // (the host looks at the totals while the kernel runs: past every cache)
+        __hip_atomic_store(&totals[2], (uint64_t)run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&totals[3], (uint64_t)max_s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         *arrivals = 0ull;
     }
     if (threadIdx.x >= 64 && threadIdx.x < 128) {   // (the second wavefront: the first one is busy below)
@@ -632,7 +633,10 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
         for (uint32_t k = 0; k < TILE_COPIES; k += 64) { recs += wg_totals[k + lane_id()]; tt += wg_totals[TILE_COPIES + k + lane_id()]; }
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) { recs += shfl_xor_u64(recs, d); tt += shfl_xor_u64(tt, d); }
-        if (lane_id() == 0) { totals[0] = tt; totals[1] = recs; }
+        if (lane_id() == 0) {
+            __hip_atomic_store(&totals[0], tt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(&totals[1], recs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
     }
     // tile order: exclusive prefix over the 512 length buckets by one wavefront, then a counting placement
     if (threadIdx.x < 64) {

@@ -396,9 +396,10 @@ __device__ __forceinline__ void photo_final(const double* __restrict__ partial, 
     l = block_reduce<RED_SUM>(l, smem);
     if (threadIdx.x == 0) {
         const double ssim = s / count, l1 = l / count;
-        out3[0] = l1;
-        out3[1] = ssim;
-        out3[2] = (1.0 - lambda) * l1 + lambda * (1.0 - ssim);
+        // (a training iteration's host looks at these while the kernel runs: past every cache)
+        __hip_atomic_store(&out3[0], l1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&out3[1], ssim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&out3[2], (1.0 - lambda) * l1 + lambda * (1.0 - ssim), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
