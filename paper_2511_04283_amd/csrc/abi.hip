@@ -477,6 +477,8 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
     // call.  The kernels write nothing beyond the capacities they are given; what the totals then say was not covered
     // (a longer list's sort variant, or buffers that have to grow first) is enqueued afterwards.
     const uint32_t* recs_p = cb ? static_cast<const uint32_t*>(ctx->rec_offsets.ptr) : static_cast<const uint32_t*>(ctx->offsets.ptr);
+    const bool bands = placed_by_bands(n, tiles);   // (then keys[0] is placed into, and split into keys[1] ahead of the sorts)
+    const int split = bands ? TS_SPLIT : 0;
     fs_projected none = {};
     uint64_t cap_pairs = 0, cap_recs = 0;
     int spec_variants = 0;
@@ -490,11 +492,12 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
         if (cap_pairs > 0 && (!cb || cap_recs > 0)) {
             ProfScope prof(ctx, FS_K_ORDER);
             spec_variants = ctx->spec_set;
+            uint64_t* const words = static_cast<uint64_t*>(ctx->keys[bands ? 0 : 1].ptr);
             FS_HIP(launch_tile_scatter(st, n, proj ? *proj : none, cf, recs_p, cd.tiles_x, tiles, (uint32_t)cap_pairs,
                                        (uint32_t)cap_recs, reinterpret_cast<const uint2*>(ranges_p), tcount_p,
-                                       static_cast<uint64_t*>(ctx->keys[1].ptr), static_cast<float*>(ctx->pair_grad.ptr)),
+                                       words, static_cast<float*>(ctx->pair_grad.ptr)),
                    "k_tile_pairs (placement)");
-            FS_HIP(launch_tile_sorts(st, tiles, spec_variants, (uint32_t)cap_pairs, reinterpret_cast<const uint2*>(ranges_p),
+            FS_HIP(launch_tile_sorts(st, tiles, spec_variants | split, (uint32_t)cap_pairs, reinterpret_cast<const uint2*>(ranges_p),
                                      order_p, static_cast<const uint64_t*>(ctx->keys[1].ptr),
                                      static_cast<uint64_t*>(ctx->keys[0].ptr), static_cast<uint32_t*>(ctx->vals[0].ptr)),
                    "k_tile_sort");
@@ -543,11 +546,11 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
             ProfScope prof(ctx, FS_K_ORDER);
             if (!spec_fits) {
                 FS_HIP(launch_tile_scatter(st, n, proj ? *proj : none, cf, recs_p, cd.tiles_x, tiles, (uint32_t)P,
-                                           (uint32_t)NR, reinterpret_cast<const uint2*>(ranges_p), tcount_p, keys[1],
+                                           (uint32_t)NR, reinterpret_cast<const uint2*>(ranges_p), tcount_p, keys[bands ? 0 : 1],
                                            static_cast<float*>(ctx->pair_grad.ptr)),
                        "k_tile_pairs (placement)");
             }
-            FS_HIP(launch_tile_sorts(st, tiles, variants, (uint32_t)P, reinterpret_cast<const uint2*>(ranges_p), order_p,
+            FS_HIP(launch_tile_sorts(st, tiles, variants | (spec_fits ? 0 : split), (uint32_t)P, reinterpret_cast<const uint2*>(ranges_p), order_p,
                                      keys[1], keys[0], vals[0]),
                    "k_tile_sort");
         }

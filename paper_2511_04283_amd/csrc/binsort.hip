@@ -302,6 +302,15 @@ __global__ __launch_bounds__(256) void k_emit_pairs_cb(int64_t n, const ushort4*
 // workgroup's start within every tile's segment, and step (2) starts from that row.  Global atomics reach
 // about 45 G/s on this chip whatever the contention; LDS atomics are an order of magnitude cheaper.
 //
+// First and last + 1 place of the pairs of band [t0, t0 + BAND_TILES) ({~0, 0}: there are none); lane l looks at tile t0 + l.
+__device__ __forceinline__ uint2 band_bounds(const uint2* __restrict__ ranges, int t0, int num_tiles, uint32_t lane)
+{
+    static_assert(BAND_TILES == 64, "a tile for each lane");
+    const uint2 r = t0 + (int)lane < num_tiles ? ranges[t0 + lane] : make_uint2(0u, 0u);
+    const uint32_t above = wave_inclusive_max(r.y > r.x ? ~r.x : 0u), last = wave_inclusive_max(r.y > r.x ? r.y : 0u);
+    return make_uint2(~(uint32_t)__builtin_amdgcn_readlane((int)above, 63), (uint32_t)__builtin_amdgcn_readlane((int)last, 63));
+}
+
 // Steps (1) and (2) walk the candidate tiles of 64 consecutive Gaussians per wavefront the way k_emit_pairs
 // does.  SCATTER = false: count[tile] += 1 per pair.  SCATTER = true: slot = first[tile] + counter[tile]++
 // (k_tile_layout has turned each copy's counter into that copy's start within the tile's segment),
@@ -325,7 +334,8 @@ struct RecAlloc {
     uint64_t* wg_totals;             // [2][TILE_COPIES] out: each workgroup's records, and its sum of tiles_touched
 };
 
-template <bool CB, bool SCATTER>
+// BANDS (placement): the words go into their band of tiles instead, and tile_place[t] <- the first place of tile t (see k_band_split).
+template <bool CB, bool SCATTER, bool BANDS>
 __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, const ushort4* __restrict__ rect,
                                                     const float* __restrict__ depth,
                                                     const float2* __restrict__ mean2d,
@@ -334,14 +344,24 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
                                                     int num_tiles, uint32_t* __restrict__ tile_counter,
                                                     const uint2* __restrict__ ranges, uint32_t P, uint32_t rec_limit,
                                                     uint64_t* __restrict__ bucket,
-                                                    float4* __restrict__ pair_grad, RecAlloc ra)
+                                                    float4* __restrict__ pair_grad, RecAlloc ra, uint32_t* __restrict__ tile_place)
 {
-    extern __shared__ uint32_t s_tile[];   // this workgroup's counter per tile
+    static_assert(SCATTER || !BANDS, "a variant of the placement");
+    extern __shared__ uint32_t s_tile[];   // this workgroup's counter per tile (BANDS: per band)
     uint32_t* const my_row = tile_counter + (size_t)blockIdx.x * num_tiles;
     // placement: the counter starts at the absolute position of this workgroup's first pair of the tile
-    for (int t = threadIdx.x; t < num_tiles; t += TILE_PAIR_THREADS) s_tile[t] = SCATTER ? ranges[t].x + my_row[t] : 0u;
-    __syncthreads();
     const uint32_t lane = lane_id();
+    if (BANDS) {
+        for (int t0 = (int)(threadIdx.x & ~63u); t0 < num_tiles; t0 += TILE_PAIR_THREADS) {
+            const uint32_t first = band_bounds(ranges, t0, num_tiles, lane).x;
+            if (lane == 0) s_tile[t0 / BAND_TILES] = first + my_row[t0];
+        }
+        for (int t = (int)(blockIdx.x * TILE_PAIR_THREADS + threadIdx.x); t < num_tiles; t += (int)gridDim.x * TILE_PAIR_THREADS)
+            tile_place[t] = ranges[t].x;
+    } else {
+        for (int t = threadIdx.x; t < num_tiles; t += TILE_PAIR_THREADS) s_tile[t] = SCATTER ? ranges[t].x + my_row[t] : 0u;
+    }
+    __syncthreads();
     __shared__ uint32_t s_mark[TILE_PAIR_THREADS / 64][128];
     uint32_t* const mark = s_mark[threadIdx.x >> 6];   // this wavefront's own
     // Wavefront w of workgroup b takes the 64 Gaussians from 64 (w gridDim + b) on in its first round, so that every workgroup has as
@@ -464,11 +484,12 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
             }
             uint32_t slot[W];
 #pragma unroll
-            for (int q = 0; q < W; q++) slot[q] = hit[q] ? atomicAdd(&s_tile[tile[q]], 1u) : P;
+            for (int q = 0; q < W; q++) slot[q] = hit[q] ? atomicAdd(&s_tile[BANDS ? tile[q] / BAND_TILES : tile[q]], 1u) : P;
 #pragma unroll
             for (int q = 0; q < W; q++) {
                 if (hit[q]) {
-                    if (slot[q] < P) bucket[slot[q]] = ((uint64_t)od[q] << 32) | (uint32_t)(i - lane + owners[q]);
+                    const uint32_t of = BANDS ? tile[q] % BAND_TILES << BAND_SHIFT : 0u;
+                    if (slot[q] < P) bucket[slot[q]] = ((uint64_t)od[q] << 32) | of | (uint32_t)(i - lane + owners[q]);
                 } else if (CB && live[q] && (uint64_t)oroff[q] + k[q] < rec_limit) {
                     float4* g = pair_grad + ((size_t)oroff[q] + k[q]) * (PAIR_REC / 4);
                     const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -520,7 +541,7 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
                                                                 const ushort4* __restrict__ rect, const float2* __restrict__ mean2d,
                                                                 const float4* __restrict__ conic_opacity, const float* __restrict__ rgb,
                                                                 CfgDev cfg, uint32_t* __restrict__ rec_offsets,
-                                                                float4* __restrict__ splats)
+                                                                float4* __restrict__ splats, int bands)
 {
     if ((int)blockIdx.x >= sum_blocks) {
         const int64_t i = (int64_t)((int)blockIdx.x - sum_blocks) * LAYOUT_THREADS + threadIdx.x;
@@ -544,6 +565,7 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
     auto row_at = [](int pos) { return (pos % (TILE_COPIES / 8)) * 8 + pos / (TILE_COPIES / 8); };
     constexpr int PER_WAVE = TILE_COPIES / LAYOUT_WAVES;
     __shared__ uint32_t gsum[LAYOUT_WAVES][64];
+    __shared__ uint32_t bsum[TILE_COPIES];
     __shared__ bool s_last;
     {
         const int g = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -556,6 +578,14 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
             sum += part[k];
         }
         gsum[g][lane] = sum;
+        if (bands) {
+            // the rows' sums over the whole band, by their position in the order of shares
+#pragma unroll
+            for (int k = 0; k < PER_WAVE; k++) {
+                const uint32_t s = wave_inclusive_scan(part[k]);
+                if (lane == 63) bsum[g * PER_WAVE + k] = s;
+            }
+        }
         __syncthreads();
         uint32_t run = 0, all = 0;
 #pragma unroll
@@ -563,7 +593,16 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
             run += q < g ? gsum[q][lane] : 0u;
             all += gsum[q][lane];
         }
-        if (t < num_tiles) {
+        if (bands) {
+            // only where a workgroup's pairs start within the band is wanted, in the place of its first tile's counter
+            uint32_t before = 0;
+#pragma unroll
+            for (int k = 0; k < TILE_COPIES; k += 64) before += k + lane < g * PER_WAVE ? bsum[k + lane] : 0u;
+            before = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(before), 63);
+            const uint32_t own = lane < PER_WAVE ? bsum[g * PER_WAVE + lane] : 0u;
+            const uint32_t start = before + wave_inclusive_scan(own) - own;
+            if (lane < PER_WAVE) count[(size_t)row_at(g * PER_WAVE + lane) * num_tiles + blockIdx.x * BAND_TILES] = start;
+        } else if (t < num_tiles) {
 #pragma unroll
             for (int k = 0; k < PER_WAVE; k++) {
                 count[(size_t)row_at(g * PER_WAVE + k) * num_tiles + t] = run;
@@ -651,6 +690,64 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
 #pragma unroll
     for (int q = 0; q < PER_MAX; q++)
         if (q < per && t0 + q < num_tiles) order[atomicAdd(&cnt[bucket(c[q])], 1u)] = (uint32_t)(t0 + q);
+}
+
+// Step (2), second half, where the first one has placed the words by bands: a workgroup takes SPLIT_WORDS of a band's words at a time,
+// orders them by tile in LDS, reserves a place for each tile's share and writes the shares, as words without their tile.
+// Memory traffic bounds the placement at millions of pairs.  With a share of some five words for each workgroup and tile, the 32
+// workgroups of a compute die keep a half-filled line open for each of 8160 tiles, 33 MB where its L2 holds four: 345 MB
+// were written for 80 at 10 M pairs, 849 for 219 at 27 M.  A band's share is 64 times as long and all open lines fit; the second
+// step reads and writes every word once more, in whole lines (a tile's share of 4096 words is 64 of them).
+// Kernel durations in one step and in two, us: 166 and 57 + 36 at 10 M pairs (3 M Gaussians, 1920x1080), 394 and 126 + 108 at 27 M;
+// a step 1660 and 1585, 2480 and 2295.  Taking 2048 words with 256 threads, 4096 with 1024 or 8192 with 1024: order and placement
+// 158, 161, 162 instead of 157 at 10 M pairs, 446, 434, 433 instead of 432 at 27 M.
+constexpr int SPLIT_THREADS = 512;
+constexpr int SPLIT_WORDS = 4096;
+__global__ __launch_bounds__(SPLIT_THREADS) void k_band_split(const uint2* __restrict__ ranges, int num_tiles, uint32_t limit,
+                                                              uint32_t* __restrict__ tile_place, const uint64_t* __restrict__ by_band,
+                                                              uint64_t* __restrict__ by_tile)
+{
+    constexpr int PER = SPLIT_WORDS / SPLIT_THREADS;
+    __shared__ uint64_t k[SPLIT_WORDS];
+    __shared__ uint32_t cnt[BAND_TILES], first[BAND_TILES], to[BAND_TILES];   // words of each tile, the first one's place in k; from there to by_tile
+    const int t = threadIdx.x, t0 = (int)blockIdx.y * BAND_TILES;
+    const uint2 band = band_bounds(ranges, t0, num_tiles, lane_id());   // (every wavefront for itself)
+    const uint32_t end = min(band.y, limit);   // (nothing was placed beyond the limit)
+    // (64 bits: the next round's first place may not fit 32)
+    for (uint64_t p = (uint64_t)band.x + (uint64_t)blockIdx.x * SPLIT_WORDS; p < end; p += (uint64_t)gridDim.x * SPLIT_WORDS) {
+        const uint64_t* const src = by_band + p;
+        const int m = (int)min((uint64_t)SPLIT_WORDS, end - p);
+        uint64_t w[PER];
+#pragma unroll
+        for (int u = 0; u < PER; u++) w[u] = t + u * SPLIT_THREADS < m ? src[t + u * SPLIT_THREADS] : 0ull;
+        if (t < BAND_TILES) cnt[t] = 0u;
+        __syncthreads();
+        uint32_t rank[PER];
+#pragma unroll
+        for (int u = 0; u < PER; u++)
+            if (t + u * SPLIT_THREADS < m) rank[u] = atomicAdd(&cnt[(uint32_t)w[u] >> BAND_SHIFT], 1u);
+        __syncthreads();
+        if (t < BAND_TILES) {
+            const uint32_t c = cnt[t], at = wave_inclusive_scan(c) - c;
+            first[t] = at;
+            to[t] = (c != 0u && t0 + t < num_tiles ? atomicAdd(&tile_place[t0 + t], c) : limit) - at;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < PER; u++)
+            if (t + u * SPLIT_THREADS < m) k[first[(uint32_t)w[u] >> BAND_SHIFT] + rank[u]] = w[u];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < PER; u++) {
+            const uint32_t i = (uint32_t)(t + u * SPLIT_THREADS);
+            if ((int)i < m) {
+                const uint64_t word = k[i];
+                const uint32_t place = to[(uint32_t)word >> BAND_SHIFT] + i;
+                if (place < limit) by_tile[place] = word & ~((uint64_t)(BAND_TILES - 1) << BAND_SHIFT);
+            }
+        }
+        __syncthreads();
+    }
 }
 
 // Step (3): one workgroup sorts one tile's segment in LDS on the 64-bit words and writes the final keys
@@ -1072,6 +1169,12 @@ hipError_t launch_emit_pairs_cb(hipStream_t st, int64_t n, const fs_projected& p
     return hipGetLastError();
 }
 
+// The tiles' totals lie behind their ranges [T, 2] and order [T]; once k_tile_layout is done with them they are free.
+static uint32_t* tile_places(const uint2* ranges, int num_tiles)
+{
+    return const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(ranges)) + 3 * (size_t)num_tiles;
+}
+
 hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, int tiles_x,
                              int num_tiles, uint32_t* tile_count, uint32_t* tile_total, uint2* ranges,
                              uint32_t* tile_order, uint64_t* totals, uint32_t* rec_offsets, uint32_t* rec_counts,
@@ -1086,18 +1189,18 @@ hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj
         const float2* m2 = reinterpret_cast<const float2*>(proj.mean2d);
         const float4* co = reinterpret_cast<const float4*>(proj.conic_opacity);
         if (cfg.compact_box)
-            hipLaunchKernelGGL((k_tile_pairs<true, false>), grid, block, lds, st, n, rect, proj.depth, m2, co, cfg,
-                               nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, ra);
+            hipLaunchKernelGGL((k_tile_pairs<true, false, false>), grid, block, lds, st, n, rect, proj.depth, m2, co, cfg,
+                               nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, ra, nullptr);
         else
-            hipLaunchKernelGGL((k_tile_pairs<false, false>), grid, block, lds, st, n, rect, proj.depth, m2, co,
-                               cfg, nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, ra);
+            hipLaunchKernelGGL((k_tile_pairs<false, false, false>), grid, block, lds, st, n, rect, proj.depth, m2, co,
+                               cfg, nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, ra, nullptr);
     }
     const int sum_blocks = (num_tiles + 63) / 64;
     hipLaunchKernelGGL(k_tile_layout, dim3((unsigned)(sum_blocks + (n + LAYOUT_THREADS - 1) / LAYOUT_THREADS)), dim3(LAYOUT_THREADS), 0, st,
                        tile_count, num_tiles, sum_blocks, tile_total, ranges, tile_order, totals,
                        reinterpret_cast<unsigned long long*>(counters), wg_totals, n, reinterpret_cast<const ushort4*>(proj.rect),
                        reinterpret_cast<const float2*>(proj.mean2d), reinterpret_cast<const float4*>(proj.conic_opacity), proj.rgb,
-                       cfg, rec_offsets, reinterpret_cast<float4*>(splats));
+                       cfg, rec_offsets, reinterpret_cast<float4*>(splats), placed_by_bands(n, num_tiles) ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -1111,14 +1214,17 @@ hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& pr
     const ushort4* rect = reinterpret_cast<const ushort4*>(proj.rect);
     const float2* m2 = reinterpret_cast<const float2*>(proj.mean2d);
     const float4* co = reinterpret_cast<const float4*>(proj.conic_opacity);
-    if (cfg.compact_box)
-        hipLaunchKernelGGL((k_tile_pairs<true, true>), grid, block, lds, st, n, rect, proj.depth, m2, co, cfg,
-                           rec_offsets, tiles_x, num_tiles, cursor, ranges, pair_limit, rec_limit, bucket,
-                           reinterpret_cast<float4*>(pair_grad), RecAlloc{});
-    else
-        hipLaunchKernelGGL((k_tile_pairs<false, true>), grid, block, lds, st, n, rect, proj.depth, m2, co, cfg,
-                           rec_offsets, tiles_x, num_tiles, cursor, ranges, pair_limit, rec_limit, bucket,
-                           reinterpret_cast<float4*>(pair_grad), RecAlloc{});
+    auto launch = [&](auto kernel, size_t bytes) {
+        hipLaunchKernelGGL(kernel, grid, block, bytes, st, n, rect, proj.depth, m2, co, cfg, rec_offsets, tiles_x, num_tiles, cursor,
+                           ranges, pair_limit, rec_limit, bucket, reinterpret_cast<float4*>(pair_grad), RecAlloc{},
+                           tile_places(ranges, num_tiles));
+    };
+    if (placed_by_bands(n, num_tiles)) {
+        const size_t bytes = (size_t)(num_tiles + BAND_TILES - 1) / BAND_TILES * sizeof(uint32_t);
+        if (cfg.compact_box) launch(k_tile_pairs<true, true, true>, bytes);
+        else launch(k_tile_pairs<false, true, true>, bytes);
+    } else if (cfg.compact_box) launch(k_tile_pairs<true, true, false>, lds);
+    else launch(k_tile_pairs<false, true, false>, lds);
     return hipGetLastError();
 }
 
@@ -1148,6 +1254,13 @@ hipError_t launch_tile_sorts(hipStream_t st, int num_tiles, int variants, uint32
         const uint32_t least = ORDER_STEP * std::min((len_lo + 1) / ORDER_STEP, (uint32_t)ORDER_BUCKETS - 1);
         return dim3(std::min((uint32_t)num_tiles, std::max(1u, pair_limit / least)));
     };
+    if (variants & TS_SPLIT) {
+        // (the words of a band are dealt out to a fixed number of workgroups: bands are of different lengths, and the host does not know them)
+        const uint32_t bands = (uint32_t)((num_tiles + BAND_TILES - 1) / BAND_TILES);
+        const uint32_t each = std::max(1u, std::min(pair_limit / SPLIT_WORDS, 4096u) / bands);
+        hipLaunchKernelGGL(k_band_split, dim3(each, bands), dim3(SPLIT_THREADS), 0, st, ranges, num_tiles, pair_limit,
+                           tile_places(ranges, num_tiles), keys_out, const_cast<uint64_t*>(bucket));
+    }
     // the long lists first: few workgroups, each a long chain of steps, which more threads shorten
     if (variants & TS_HUGE)
         hipLaunchKernelGGL((k_tile_sort<TILE_SORT_HUGE, 1024, 4096>), grid(TILE_SORT_MAX), dim3(1024), 0, st, ranges, tile_order,

@@ -373,6 +373,17 @@ hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj
                              int num_tiles, uint32_t* tile_count, uint32_t* tile_total, uint2* ranges,
                              uint32_t* tile_order, uint64_t* totals, uint32_t* rec_offsets, uint32_t* rec_counts,
                              uint64_t* counters, float* splats);
+// With many pairs the placement goes in two steps, into bands of BAND_TILES consecutive tiles first (see k_band_split): `bucket` of
+// launch_tile_scatter is then what launch_tile_sorts knows as keys_out, and launch_tile_sorts is given TS_SPLIT.  The words of the
+// first step hold the tile within the band above the Gaussian's index.
+constexpr int BAND_TILES = 64;                 // the tiles of one of k_tile_layout's workgroups
+constexpr int BAND_SHIFT = 26;                 // bits of a word that the index has
+// (The host does not know the number of pairs when it chooses, so the number of Gaussians decides.  Placement and sorts in one step and
+// in two, us: 1920x1080, 3.4 pairs per Gaussian, 500k 37.6 and 49.1, 700k 50.6 and 56.1, 1 M 74.1 and 64.3, 1.4 M 104 and 80, 2 M 155
+// and 109, 3 M 236 and 158; 9 pairs per Gaussian, 300k 72 and 79, 500k 115 and 107, 1 M 205 and 150, 3 M 603 and 432; 1600x1064, 1 M
+// 73.4 and 66.4; 1332x876 with the Compact Box, 300k 28.1 and 39.1.)
+constexpr int64_t BAND_MIN_N = 1000000;
+inline bool placed_by_bands(int64_t n, int num_tiles) { return n >= BAND_MIN_N && n <= (int64_t)1 << BAND_SHIFT && num_tiles > BAND_TILES; }
 // Placement and the per-tile sorts.  pair_limit / rec_limit: how many words / gradient records the buffers hold; the
 // kernels write nothing at or beyond them and leave alone a segment that reaches beyond pair_limit, so they may be
 // enqueued before the host knows the totals.
@@ -387,7 +398,7 @@ hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& pr
 // With MID and without: 3 M Gaussians with lists of 3350 on average 2557 and 2565 us per step, of 1228 1726 and 1730, 30k at
 // 189x106 207.2 and 208.0; ten views at 300k, whose lists are 400 long and a few 7000, 2254 and 2167.
 // tile_sort_variants: the launches still needed for lists of up to max_len entries when those in `have` are enqueued.
-enum { TS_SMALL = 1, TS_MID = 2, TS_MAX = 4, TS_HUGE = 8, TS_MIDMAX = 16 };
+enum { TS_SMALL = 1, TS_MID = 2, TS_MAX = 4, TS_HUGE = 8, TS_MIDMAX = 16, TS_SPLIT = 32 };
 int tile_sort_variants(int64_t max_len, bool long_lists, int have);
 hipError_t launch_tile_sorts(hipStream_t st, int num_tiles, int variants, uint32_t pair_limit, const uint2* ranges,
                              const uint32_t* tile_order, const uint64_t* bucket, uint64_t* keys_out, uint32_t* vals_out);
