@@ -551,6 +551,18 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
 #pragma unroll
         for (uint32_t k = 0; k < TILE_COPIES; k += 64) before += k + lane_id() < wg ? (uint32_t)wg_totals[k + lane_id()] : 0u;
         before = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(before), 63);
+        if ((int)blockIdx.x == sum_blocks && threadIdx.x < 64) {
+            uint64_t recs = 0, tt = 0;
+#pragma unroll
+            for (uint32_t k = 0; k < TILE_COPIES; k += 64) { recs += wg_totals[k + lane_id()]; tt += wg_totals[TILE_COPIES + k + lane_id()]; }
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) { recs += shfl_xor_u64(recs, d); tt += shfl_xor_u64(tt, d); }
+            // (the host looks at the totals while the kernel runs: past every cache)
+            if (lane_id() == 0) {
+                __hip_atomic_store(&totals[0], tt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                __hip_atomic_store(&totals[1], recs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+        }
         if (i >= n) return;
         const uint32_t first_record = rec_offsets[i] + before;
         rec_offsets[i] = first_record;
@@ -593,6 +605,17 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
             run += q < g ? gsum[q][lane] : 0u;
             all += gsum[q][lane];
         }
+        if (g == 0) {
+            // (ahead of the table's stores, which nothing in this launch waits for)
+            // (another compute die may read these: they go past this one's L2, and have arrived before the workgroup counts
+            // as done.  A release fence would do the same, and write the whole L2 back each time: the launch took 15 us instead
+            // of 11 at 100k Gaussians.  The reader needs no acquire fence for its part: it loads them with agent-scope atomics,
+            // which do not look for them in its own L2 either, and only after the branch on the count.  This is the cache policy of
+            // this chip's agent-scope accesses, not an ordering of the language's memory model.)
+            if (t < num_tiles) __hip_atomic_store(&tile_total[t], all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (lane == 0) s_last = atomicAdd(arrivals, 1ull) + 1 == (unsigned long long)sum_blocks;
+        }
         if (bands) {
             // only where a workgroup's pairs start within the band is wanted, in the place of its first tile's counter
             uint32_t before = 0;
@@ -609,87 +632,74 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
                 run += part[k];
             }
         }
-        if (g == 0) {
-            // (another compute die may read these: they go past this one's L2, and have arrived before the workgroup counts
-            // as done.  A release fence would do the same, and write the whole L2 back each time: the launch took 15 us instead
-            // of 11 at 100k Gaussians.  The reader needs no acquire fence for its part: it loads them with agent-scope atomics,
-            // which do not look for them in its own L2 either, and only after the branch on the count.  This is the cache policy of
-            // this chip's agent-scope accesses, not an ordering of the language's memory model.)
-            if (t < num_tiles) __hip_atomic_store(&tile_total[t], all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            if (lane == 0) s_last = atomicAdd(arrivals, 1ull) + 1 == (unsigned long long)sum_blocks;
-        }
     }
     __syncthreads();
     if (!s_last) return;
 
+    // Round q of thread t: tile 1024 q + t.
     constexpr int NB = ORDER_BUCKETS;
-    __shared__ uint32_t wsum[16];
-    __shared__ uint32_t max_s;
-    __shared__ uint32_t cnt[NB];
-    for (int b = threadIdx.x; b < NB; b += 1024) cnt[b] = 0;
-    if (threadIdx.x == 0) max_s = 0;
-    __syncthreads();
-    constexpr int PER_MAX = (TILE_LDS_MAX_TILES + 1023) / 1024;   // this path is only taken up to that many tiles
-    const int per = (num_tiles + 1023) / 1024;
-    const int t0 = threadIdx.x * per;
+    constexpr int PER_MAX = (TILE_LDS_MAX_TILES + LAYOUT_THREADS - 1) / LAYOUT_THREADS;   // this path is only taken up to that many tiles
+    static_assert(PER_MAX * LAYOUT_WAVES <= 256 && NB == 512, "four of the sums, eight of the buckets for a lane");
+    __shared__ __align__(16) uint32_t wsum[256];   // pairs of each round's wavefronts
+    __shared__ uint32_t wmax[LAYOUT_WAVES];
+    __shared__ __align__(16) uint32_t cnt[NB];
+    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    const int per = (num_tiles + LAYOUT_THREADS - 1) / LAYOUT_THREADS;
     auto bucket = [](uint32_t len) { return (int)(NB - 1 - min(len / ORDER_STEP, (uint32_t)NB - 1)); };
-    uint32_t c[PER_MAX];   // this thread's tile totals, read once
-    uint32_t v = 0, mymax = 0;
-#pragma unroll
-    for (int q = 0; q < PER_MAX; q++) {
-        const bool in = q < per && t0 + q < num_tiles;
-        c[q] = in ? __hip_atomic_load(&tile_total[t0 + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-    }
-#pragma unroll
-    for (int q = 0; q < PER_MAX; q++) {
-        v += c[q];
-        mymax = max(mymax, c[q]);
-        if (q < per && t0 + q < num_tiles) atomicAdd(&cnt[bucket(c[q])], 1u);
-    }
-    const uint32_t inc = wave_inclusive_scan(v);
-    if (lane_id() == 63) wsum[threadIdx.x >> 6] = inc;
-    if (mymax) atomicMax(&max_s, mymax);
-    __syncthreads();
-    uint32_t run = inc - v;
-    for (int w = 0; w < (int)(threadIdx.x >> 6); w++) run += wsum[w];
-#pragma unroll
-    for (int q = 0; q < PER_MAX; q++) {
-        if (q < per && t0 + q < num_tiles) ranges[t0 + q] = c[q] ? make_uint2(run, run + c[q]) : make_uint2(0u, 0u);
-        run += c[q];
-    }
-    if (threadIdx.x == 1023) {
-        // totals: sum of tiles_touched, backward records, pairs counted per tile, longest list; the arrivals start the
-        // next call at zero
-        // (the host looks at the totals while the kernel runs: past every cache)
-        __hip_atomic_store(&totals[2], (uint64_t)run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        __hip_atomic_store(&totals[3], (uint64_t)max_s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        *arrivals = 0ull;
-    }
-    if (threadIdx.x >= 64 && threadIdx.x < 128) {   // (the second wavefront: the first one is busy below)
-        uint64_t recs = 0, tt = 0;
-#pragma unroll
-        for (uint32_t k = 0; k < TILE_COPIES; k += 64) { recs += wg_totals[k + lane_id()]; tt += wg_totals[TILE_COPIES + k + lane_id()]; }
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) { recs += shfl_xor_u64(recs, d); tt += shfl_xor_u64(tt, d); }
-        if (lane_id() == 0) {
-            __hip_atomic_store(&totals[0], tt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            __hip_atomic_store(&totals[1], recs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        }
-    }
-    // tile order: exclusive prefix over the 512 length buckets by one wavefront, then a counting placement
-    if (threadIdx.x < 64) {
-        uint32_t b8[8], sum = 0;
-#pragma unroll
-        for (int q = 0; q < 8; q++) { b8[q] = cnt[threadIdx.x * 8 + q]; sum += b8[q]; }
-        uint32_t pre = wave_inclusive_scan(sum) - sum;
-#pragma unroll
-        for (int q = 0; q < 8; q++) { cnt[threadIdx.x * 8 + q] = pre; pre += b8[q]; }
-    }
-    __syncthreads();
+    uint32_t c[PER_MAX], inc[PER_MAX];   // this thread's tile totals, and those of its wavefront's tiles up to them
 #pragma unroll
     for (int q = 0; q < PER_MAX; q++)
-        if (q < per && t0 + q < num_tiles) order[atomicAdd(&cnt[bucket(c[q])], 1u)] = (uint32_t)(t0 + q);
+        c[q] = q * LAYOUT_THREADS + t < num_tiles ? __hip_atomic_load(&tile_total[q * LAYOUT_THREADS + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    if (t < NB) cnt[t] = 0u;
+    if (t >= per * LAYOUT_WAVES && t < 256) wsum[t] = 0u;
+    __syncthreads();
+    uint32_t most = 0;
+#pragma unroll
+    for (int q = 0; q < PER_MAX; q++) {
+        if (q >= per) continue;
+        inc[q] = wave_inclusive_scan(c[q]);
+        if (lane == 63) wsum[q * LAYOUT_WAVES + wave] = inc[q];
+        most = max(most, c[q]);
+        if (q * LAYOUT_THREADS + t < num_tiles) atomicAdd(&cnt[bucket(c[q])], 1u);
+    }
+    // (one LDS address for 1024 threads' maximum took 2 us of the launch)
+    most = wave_inclusive_max(most);
+    if (lane == 63) wmax[wave] = most;
+    __syncthreads();
+    // tile order: exclusive prefix over the 512 length buckets by one wavefront, then a counting placement
+    if (wave == 0) {
+        uint4* const mine = reinterpret_cast<uint4*>(cnt) + 2 * lane;
+        const uint4 a = mine[0], b = mine[1];
+        const uint32_t sum = a.x + a.y + a.z + a.w + b.x + b.y + b.z + b.w;
+        const uint32_t pre = wave_inclusive_scan(sum) - sum, mid = pre + a.x + a.y + a.z + a.w;
+        mine[0] = make_uint4(pre, pre + a.x, pre + a.x + a.y, pre + a.x + a.y + a.z);
+        mine[1] = make_uint4(mid, mid + b.x, mid + b.x + b.y, mid + b.x + b.y + b.z);
+    }
+    // the pairs before this wavefront's tiles of each round: in lane 4 q + wave / 4
+    const uint4 w4 = reinterpret_cast<const uint4*>(wsum)[lane];
+    const uint32_t upto = wave_inclusive_scan(w4.x + w4.y + w4.z + w4.w);
+    const int w3 = wave & 3;
+    const uint32_t start = upto - (w4.w + (w3 < 3 ? w4.z : 0u) + (w3 < 2 ? w4.y : 0u) + (w3 < 1 ? w4.x : 0u));
+    if (t == LAYOUT_THREADS - 1) {
+        // totals: sum of tiles_touched, backward records, pairs counted per tile, longest list; the arrivals start the
+        // next call at zero
+#pragma unroll
+        for (int w = 0; w < LAYOUT_WAVES; w++) most = max(most, wmax[w]);
+        __hip_atomic_store(&totals[2], (uint64_t)upto, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&totals[3], (uint64_t)most, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        *arrivals = 0ull;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER_MAX; q++) {
+        if (q >= per) continue;
+        const int tile = q * LAYOUT_THREADS + t;
+        const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)start, 4 * q + wave / 4) + inc[q] - c[q];
+        if (tile < num_tiles) {
+            ranges[tile] = c[q] ? make_uint2(first, first + c[q]) : make_uint2(0u, 0u);
+            order[atomicAdd(&cnt[bucket(c[q])], 1u)] = (uint32_t)tile;
+        }
+    }
 }
 
 // Step (2), second half, where the first one has placed the words by bands: a workgroup takes SPLIT_WORDS of a band's words at a time,
@@ -1196,7 +1206,7 @@ hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj
                                cfg, nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, ra, nullptr);
     }
     const int sum_blocks = (num_tiles + 63) / 64;
-    hipLaunchKernelGGL(k_tile_layout, dim3((unsigned)(sum_blocks + (n + LAYOUT_THREADS - 1) / LAYOUT_THREADS)), dim3(LAYOUT_THREADS), 0, st,
+    hipLaunchKernelGGL(k_tile_layout, dim3((unsigned)(sum_blocks + std::max<int64_t>(1, (n + LAYOUT_THREADS - 1) / LAYOUT_THREADS))), dim3(LAYOUT_THREADS), 0, st,
                        tile_count, num_tiles, sum_blocks, tile_total, ranges, tile_order, totals,
                        reinterpret_cast<unsigned long long*>(counters), wg_totals, n, reinterpret_cast<const ushort4*>(proj.rect),
                        reinterpret_cast<const float2*>(proj.mean2d), reinterpret_cast<const float4*>(proj.conic_opacity), proj.rgb,
