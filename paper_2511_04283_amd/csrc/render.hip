@@ -24,6 +24,8 @@
 // Times "at 500k Gaussians and 1600x1064" and the like are of the scenes of perf/cases.py.  They have other pairs than those of
 // bench.py with the same sizes: 6 k against 11 k at 4k Gaussians and 128x128, 0.4 M to 0.5 M against 0.5 M at 100k, 2.1 M to 2.9 M
 // against 1.4 M at 500k, 11 M to 13 M against 10 M at 3 M (wide: 30 M to 37 M against 27 M).
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace fs {
@@ -610,8 +612,7 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
     __shared__ Stage<true, N> s;
     __shared__ acc_t s_acc[N][NV];
     __shared__ __align__(16) float s_turn[4][SPAN][64];   // per wavefront: one value of SPAN entries, [entry][lane]
-    __shared__ int s_max;
-    static_assert(sizeof(s) + sizeof(s_acc) + sizeof(s_turn) + sizeof(s_max) <= 40960, "four workgroups per compute unit");
+    static_assert(sizeof(s) + sizeof(s_acc) + sizeof(s_turn) <= 40960, "four workgroups per compute unit");
 
     const int tile = (int)tile_order[blockIdx.x];  // longest lists first
     const Pixel p = pixel_of_thread(cam, tile);
@@ -677,14 +678,23 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
     auto both = [&](float v) { return v + other(v); };   // the sum of the two lanes, in both
 
     s.clear(threadIdx.x);
-    if (threadIdx.x == 0) s_max = 0;
-    int row_last = last;   // the furthest position any pixel of this lane's row of 16 reaches
-#pragma unroll
-    for (int d = 1; d < 16; d <<= 1) row_last = max(row_last, __shfl_xor(row_last, d, 64));
+    // the furthest position any pixel of this lane's row of 16 reaches (by rotations of the row: every lane has it)
+    int row_last = last;
+    auto rotated_max = [&](auto ctrl) {
+        row_last = max(row_last, __builtin_amdgcn_update_dpp(0, row_last, decltype(ctrl)::value, 0xF, 0xF, true));
+    };
+    rotated_max(std::integral_constant<int, 0x121>{});
+    rotated_max(std::integral_constant<int, 0x122>{});
+    rotated_max(std::integral_constant<int, 0x124>{});
+    rotated_max(std::integral_constant<int, 0x128>{});
+    // (With exchanges through LDS, a maximum added up by LDS atomics and a second barrier for it: 22.9 us instead of 22.3 at 4k Gaussians,
+    // 54.6 and 53.8 at 100k, 174.6 and 172.6 at 500k.  s_turn is not in use before the first batch's barriers.)
+    int* const wave_last = reinterpret_cast<int*>(&s_turn[0][0][0]);
+    const int wave_max = wave_max_of_rows(row_last);
+    if (lane == 0) wave_last[wave] = wave_max;
     __syncthreads();
-    if ((lane & 15) == 0) atomicMax(&s_max, row_last);
-    __syncthreads();
-    const int total = s_max;  // entries at positions >= total are blended by no pixel of the tile
+    const int4 furthest = *reinterpret_cast<const int4*>(wave_last);
+    const int total = max(max(furthest.x, furthest.y), max(furthest.z, furthest.w));  // entries at positions >= total are blended by no pixel of the tile
 
     // batches from the back: batch b covers positions [b*B, min(total,(b+1)*B))
     const int final_start = total > 0 ? ((total - 1) / B) * B : -1;
