@@ -531,6 +531,13 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
 // Placement, sums and scan together, before and after: 222 and 185 us at 3 M Gaussians / 10 M pairs, 18.3 and 16.8 at 4k.
 // They also complete the record places of all Gaussians (4 bytes read and written for each): this launch went from 20.7 to 21.8 us at
 // 500k Gaussians and from 64 to 69 at 3 M with it, the counting kernel from 18.1 to 12.6 and from 43.5 to 39.
+//
+// Up to 500k Gaussians the chain of the first two is what the launch takes: the rows' loads (1.5 us), the totals' way past the L2 and
+// the count of arrivals (1.5), the totals' loads (0.6 to 0.9), sums and maximum (1), places and stores (0.5 to 4).  So a round is 1024
+// neighbouring tiles, a thread each (whole lines), the store that is waited for comes ahead of the table's, and the maximum goes through
+// the wavefronts: all threads on one LDS address took 2 to 3.5 us.  Counting and this launch, before and after, us: 14.8 and 12.4 at 4k
+// Gaussians, 18.5 and 15.5 at 100k, 27.5 and 23.5 at 300k, 36.0 and 30.7 at 500k.  (Two workgroups to a compute unit, at 64 registers:
+// 5 % slower at 300k; nearly empty tiles counted a wavefront at a time: 3 to 11 % slower.)
 constexpr int LAYOUT_THREADS = 1024;
 constexpr int LAYOUT_WAVES = LAYOUT_THREADS / 64;
 __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __restrict__ count, int num_tiles, int sum_blocks,
