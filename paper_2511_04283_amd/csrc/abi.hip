@@ -7,6 +7,7 @@
 #include <atomic>
 #include <chrono>
 #include <new>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -257,24 +258,31 @@ int record_buffers(fs_ctx* ctx, const fs_bins* bins, int tiles)
 // stream does not go on to the next kernel before it is signalled: 5.4 us and more in every ordering, and once more behind the loss.
 // A pass with events and without, in us: a render at 4k Gaussians and 128x128 43.4 and 38.1, at 300k and 1332x876 134.2 and 131.6, a
 // training iteration at 12k and 509x337 142.6 and 134.0, ten score views at 100k and 980x545 1460 and 1419.
-// Words that do not come within SPIN_MS -- behind a long queue, or never -- are left to the stream's own wait, which reports its errors.
+// Words that do not come within SPIN_MS stand behind a long queue or never come.  From then on the host sleeps between its looks and
+// asks the stream for its errors; it still goes on with the last word, not with what is enqueued behind the kernel that stores it.
+// FS_EHIP, with the caller's *_pending left as it is: the stream has failed, or is done and a word is still unset.
 constexpr uint64_t UNSET_WORD = 0xfff7a5a55a5aa55bull;   // (as a double a NaN that no conversion or arithmetic makes)
 constexpr int SPIN_MS = 20;
+constexpr int SLEEP_US = 50;
 void unset_words(uint64_t* p, int count)
 {
     for (int k = 0; k < count; k++) p[k] = UNSET_WORD;
     std::atomic_thread_fence(std::memory_order_release);
 }
-int wait_for_words(fs_ctx* ctx, const uint64_t* p, int count)
+int wait_for_words(fs_ctx* ctx, const uint64_t* p, int count, const char* never)
 {
     const volatile uint64_t* const w = p;
     const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(SPIN_MS);
     for (int k = 0; k < count; k++)
-        for (uint32_t spins = 1; w[k] == UNSET_WORD; spins++)
-            if (spins % 1024 == 0 && std::chrono::steady_clock::now() > until) {
-                FS_HIP(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
-                break;
-            }
+        for (uint32_t spins = 1; w[k] == UNSET_WORD; spins++) {
+            if (spins % 1024 || std::chrono::steady_clock::now() <= until) continue;
+            const hipError_t e = hipStreamQuery(ctx->stream);
+            if (w[k] != UNSET_WORD) break;
+            if (e == hipSuccess) return fail(ctx, FS_EHIP, never);
+            if (e != hipErrorNotReady) FS_HIP(e, "hipStreamQuery");
+            (void)hipGetLastError();   // (or the next launch's check would report that the stream was busy)
+            std::this_thread::sleep_for(std::chrono::microseconds(SLEEP_US));
+        }
     std::atomic_thread_fence(std::memory_order_acquire);
     return FS_OK;
 }
@@ -504,9 +512,7 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
         }
     }
     if (bucketed) {
-        FS_TRY(wait_for_words(ctx, ctx->total_host, 4));
-        for (int k = 0; k < 4; k++)
-            if (ctx->total_host[k] == UNSET_WORD) return fail(ctx, FS_EHIP, "fs_bin_sort: the totals did not arrive");
+        FS_TRY(wait_for_words(ctx, ctx->total_host, 4, "fs_bin_sort: the totals did not arrive"));
         ctx->totals_pending = false;
     } else {
         FS_HIP(hipEventSynchronize(ctx->totals_event), "hipEventSynchronize");
@@ -1120,7 +1126,7 @@ int fs_train_step(fs_ctx* ctx, const fs_train_state* t, const fs_camera* cam, co
         }
     }
     // the loss is complete long before the backward pass: only it is waited for
-    FS_TRY(wait_for_words(ctx, loss_words, 3));
+    FS_TRY(wait_for_words(ctx, loss_words, 3, "fs_train_step: the loss did not arrive"));
     ctx->loss_pending = false;
     for (int k = 0; k < 3; k++) out3[k] = ctx->loss_host[k];
     return FS_OK;

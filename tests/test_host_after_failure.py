@@ -1,5 +1,6 @@
-"""What a context's bookkeeping says after a call that failed half way, on the CPU: abi.hip's host code on a stub of the GPU
-(host_abi_stub.cpp) whose launches and allocations fail on request."""
+"""What a context's bookkeeping says after a call that failed half way, and how its calls wait for the GPU's words, on the CPU:
+abi.hip's host code on a stub of the GPU (host_abi_stub.cpp) whose launches and allocations fail, and whose words come late or
+never, on request."""
 import ctypes
 import os
 import shutil
@@ -59,14 +60,16 @@ class Ctx:
         if rc == self.B.FS_OK:
             rc = self.lib.fs_render_bwd(self.h, r(self.g), r(self.cam), r(self.proj), r(b), self.some, self.some, self.some,
                                         r(self.grads))
+        self.rc = rc
         return rc or ctypes.c_int64.in_dll(self.lib, "stub_stale_flags").value
 
     def train(self, mode):
         prm = self.B.fs_train_params(0.2, (ctypes.c_float * 5)(), 0.9, 0.999, 1e-15, 1, 0, 1)
-        out3 = (ctypes.c_double * 3)()
+        self.out3 = out3 = (ctypes.c_double * 3)()
         r = ctypes.byref
         self.lib.fs_set_record_mode(self.h, mode)
         rc = self.lib.fs_train_step(self.h, r(self.state), r(self.cam), self.some, r(prm), out3)
+        self.rc = rc
         return rc or ctypes.c_int64.in_dll(self.lib, "stub_stale_flags").value
 
 
@@ -100,4 +103,51 @@ def test_flags_after_their_array_failed_to_grow(stub, call):
     assert b"record flags" in stub.fs_last_error(c.h)
     c.pairs(100)
     assert step(B.FS_RECORDS_SPARSE) == 0    # not 100
+    stub.fs_destroy(c.h)
+
+
+def set_int(stub, name, value):
+    ctypes.c_int.in_dll(stub, name).value = value
+
+
+@pytest.mark.parametrize("call", ["backward", "train"])
+def test_words_behind_a_long_queue_are_all_that_is_waited_for(stub, call):
+    """Totals and loss that come later than the host looks for without a pause: the call goes on with them, not when the stream
+    has nothing left to do."""
+    c = Ctx(stub, pairs=100)
+    syncs = ctypes.c_int.in_dll(stub, "stub_syncs")
+    getattr(c, call)(c.B.FS_RECORDS_DENSE)   # (arrays that grow wait for the stream)
+    before = syncs.value
+    set_int(stub, "stub_queue", 3)
+    try:
+        for _ in range(2):
+            getattr(c, call)(c.B.FS_RECORDS_DENSE)
+            assert c.rc == c.B.FS_OK and syncs.value == before
+            if call == "train":
+                assert list(c.out3) == [0.25, 0.5, 0.75]
+    finally:
+        set_int(stub, "stub_queue", 0)
+    stub.fs_destroy(c.h)
+
+
+@pytest.mark.parametrize("words, call, message", [(1, "backward", b"totals"), (1, "train", b"totals"), (2, "train", b"loss")])
+def test_words_that_never_come(stub, words, call, message):
+    """... are an error in every call that waits for them, and the next call does not set them anew before the stream is done."""
+    c = Ctx(stub, pairs=100)
+    step, B = getattr(c, call), c.B
+    step(B.FS_RECORDS_DENSE)
+    set_int(stub, "stub_never", words)
+    try:
+        step(B.FS_RECORDS_DENSE)
+        assert c.rc == -3   # FS_EHIP
+    finally:
+        set_int(stub, "stub_never", 0)
+    assert message in stub.fs_last_error(c.h)
+    syncs = ctypes.c_int.in_dll(stub, "stub_syncs")
+    for waits in (1, 0):
+        before = syncs.value
+        step(B.FS_RECORDS_DENSE)
+        assert c.rc == B.FS_OK and syncs.value - before == waits
+        if call == "train":
+            assert list(c.out3) == [0.25, 0.5, 0.75]
     stub.fs_destroy(c.h)
