@@ -43,8 +43,9 @@
  *     flight there: the arrays it was given must stay valid, and must only be touched by work ordered
  *     after it on that stream, until then.  fs_compact reads 8 bytes back (the count), fs_sample_by_score
  *     8, and fs_measure_peaks / fs_profile_read wait for their measurements: these synchronise the
- *     stream.  fs_bin_sort reads 32 bytes back (the pair count and what it needs to choose its path) and
- *     waits for the kernels that make them, but may return with its last kernels still running.
+ *     stream.  fs_bin_sort (32 bytes: the pair count and what it needs to choose its path) and fs_train_step
+ *     (the loss) go on when these are there, which may be before the kernels that make them end: no array
+ *     that they write or read is done with when they return.
  *   - Every call returns FS_OK (0) or a negative fs_status and never throws or aborts;
  *     fs_last_error gives a message for the last failure on that ctx.
  *   - n = 0 Gaussians and P = 0 pairs are valid (the image is the background).
@@ -192,8 +193,9 @@ int fs_preprocess(fs_ctx *ctx, const fs_gaussians *g, const fs_camera *cam, fs_p
  * (bins->pair_offsets), keys emitted in index order, a global stable LSD radix sort, ranges from the sorted keys.
  * Both give bit-identical keys, order and ranges.  n = number of Gaussians in `proj`.  Also packs the projected
  * splats into bins->splats and gives every pair the place of its backward record (bins->record_offsets); later
- * calls that take `bins` must be given the same `proj`.  Reads 32 bytes back (the host waits for the counting
- * kernels, not for the whole stream: from a context's second per-tile ordering on, placement and sorts are enqueued
+ * calls that take `bins` must be given the same `proj`.  Waits for 32 bytes (the totals, which the
+ * kernel behind the counting one stores where the host sees them; that kernel may still be writing the ranges, the
+ * splats and the record places then.  From a context's second per-tile ordering on, placement and sorts are enqueued
  * ahead of that wait, bounded by what the context's buffers hold, and repeated if the totals say they did not fit).
  * Errors: FS_EINVAL, FS_ENOMEM, FS_EHIP, FS_ECAPACITY (n, P or the candidate tile count >= 2^31). */
 int fs_bin_sort(fs_ctx *ctx, const fs_projected *proj, const fs_camera *cam, int64_t n, fs_bins *out);
@@ -463,8 +465,8 @@ typedef struct {
 /* fs_activate, fs_preprocess, fs_bin_sort, fs_render_fwd, fs_photo_loss, fs_render_bwd with the absolute gradient,
  * fs_densify_accumulate, fs_activate_bwd and fs_grad_accumulate / fs_adam_step of the five groups, with the same results; the
  * image, the projected splats and the gradients are not handed out.  target: [3,H,W] on the device.  out3: three
- * HOST doubles {L1, SSIM, E}: the call returns once these are known; the rest of its work is enqueued on the ctx's
- * stream then, like that of every other call.  bins of earlier fs_bin_sort calls become invalid.
+ * HOST doubles {L1, SSIM, E}: the call returns once these are known; the rest of its work (the reads of target among
+ * it) is enqueued on the ctx's stream then, like that of every other call.  bins of earlier fs_bin_sort calls become invalid.
  * Errors: as the calls named. */
 int fs_train_step(fs_ctx *ctx, const fs_train_state *state, const fs_camera *cam, const float *target,
                   const fs_train_params *params, double *out3);

@@ -243,11 +243,13 @@ class Projected:
 @dataclass
 class Bins:
     """Result of fs_bin_sort: P and raw device pointers into ctx-owned memory (valid until the next
-    fs_bin_sort on the same Context).  `copy_*` methods clone them into torch tensors for inspection."""
+    fs_bin_sort on the same Context).  `copy_*` methods clone them into torch tensors for inspection, on torch's current
+    stream and ordered with the context's (fs_bin_sort returns with its kernels still writing)."""
     num_pairs: int
     struct: fs_bins
     num_tiles: int
     device: torch.device
+    stream: torch.cuda.Stream | None = None   # the context's
 
     def _copy(self, ptr, count, dtype):
         """Clone `count` elements at device address `ptr` into a new torch tensor (the ctx-owned
@@ -259,7 +261,13 @@ class Bins:
         class _Raw:
             __cuda_array_interface__ = {"shape": (count,), "typestr": typestr, "data": (int(ptr), False),
                                         "version": 2}
-        return torch.as_tensor(_Raw(), device=self.device).clone()
+        here = torch.cuda.current_stream(self.device)
+        if self.stream is not None and here != self.stream:
+            here.wait_stream(self.stream)
+        out = torch.as_tensor(_Raw(), device=self.device).clone()
+        if self.stream is not None and here != self.stream:
+            self.stream.wait_stream(here)   # (the next ordering overwrites what is being copied)
+        return out
 
     def copy_keys(self):
         return self._copy(self.struct.keys_sorted, self.num_pairs, torch.int64)
@@ -347,7 +355,7 @@ class Context:
         self._check(self.lib.fs_bin_sort(self.handle, ctypes.byref(ps), ctypes.byref(cam), n, ctypes.byref(b)),
                     "fs_bin_sort")
         tiles = ((cam.width + 15) // 16) * ((cam.height + 15) // 16)
-        return Bins(int(b.num_pairs), b, tiles, self.device)
+        return Bins(int(b.num_pairs), b, tiles, self.device, self.stream)
 
     def fs_render_fwd(self, proj: Projected, bins: Bins, cam: fs_camera, image=None, final_T=None, n_contrib=None):
         H, W, dev = cam.height, cam.width, self.device
