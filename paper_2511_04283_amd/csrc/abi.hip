@@ -415,12 +415,14 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
     hipStream_t st = ctx->stream;
     const int tiles = cd.tiles_x * cd.tiles_y;
 
-    // ranges [T,2] | tile_order [T] | tile totals [T] | per-tile counters [TILE_COPIES,T]
-    FS_TRY(ensure(ctx, ctx->ranges, (size_t)tiles * (4 + TILE_COPIES) * sizeof(uint32_t), "tile ranges and order"));
+    // ranges [T,2] | tile_order [T] | tile totals [T] | per-tile counters [TILE_COPIES,T] | ranges of the bands of tiles [bands,2]
+    const int num_bands = (tiles + BAND_TILES - 1) / BAND_TILES;
+    FS_TRY(ensure(ctx, ctx->ranges, ((size_t)tiles * (4 + TILE_COPIES) + 2 * (size_t)num_bands) * sizeof(uint32_t), "tile ranges and order"));
     uint32_t* const ranges_p = static_cast<uint32_t*>(ctx->ranges.ptr);
     uint32_t* const order_p = ranges_p + 2 * (size_t)tiles;
     uint32_t* const ttotal_p = ranges_p + 3 * (size_t)tiles;
     uint32_t* const tcount_p = ranges_p + 4 * (size_t)tiles;
+    const BandPlaces places = {ttotal_p, reinterpret_cast<uint2*>(tcount_p + (size_t)TILE_COPIES * tiles)};
     const bool bucketed = ctx->cfg.sort_mode == FS_SORT_AUTO && tiles <= TILE_LDS_MAX_TILES;
     FS_TRY(ensure(ctx, ctx->offsets, (size_t)(n > 0 ? n : 1) * sizeof(uint32_t), "offsets"));
     FS_TRY(ensure(ctx, ctx->scan_tmp, scan_tmp_bytes(n), "scan"));
@@ -503,11 +505,11 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
             uint64_t* const words = static_cast<uint64_t*>(ctx->keys[bands ? 0 : 1].ptr);
             FS_HIP(launch_tile_scatter(st, n, proj ? *proj : none, cf, recs_p, cd.tiles_x, tiles, (uint32_t)cap_pairs,
                                        (uint32_t)cap_recs, reinterpret_cast<const uint2*>(ranges_p), tcount_p,
-                                       words, static_cast<float*>(ctx->pair_grad.ptr)),
+                                       words, static_cast<float*>(ctx->pair_grad.ptr), places),
                    "k_tile_pairs (placement)");
             FS_HIP(launch_tile_sorts(st, tiles, spec_variants | split, (uint32_t)cap_pairs, reinterpret_cast<const uint2*>(ranges_p),
-                                     order_p, static_cast<const uint64_t*>(ctx->keys[1].ptr),
-                                     static_cast<uint64_t*>(ctx->keys[0].ptr), static_cast<uint32_t*>(ctx->vals[0].ptr)),
+                                     order_p, static_cast<uint64_t*>(ctx->keys[1].ptr),
+                                     static_cast<uint64_t*>(ctx->keys[0].ptr), static_cast<uint32_t*>(ctx->vals[0].ptr), places),
                    "k_tile_sort");
         }
     }
@@ -553,11 +555,11 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
             if (!spec_fits) {
                 FS_HIP(launch_tile_scatter(st, n, proj ? *proj : none, cf, recs_p, cd.tiles_x, tiles, (uint32_t)P,
                                            (uint32_t)NR, reinterpret_cast<const uint2*>(ranges_p), tcount_p, keys[bands ? 0 : 1],
-                                           static_cast<float*>(ctx->pair_grad.ptr)),
+                                           static_cast<float*>(ctx->pair_grad.ptr), places),
                        "k_tile_pairs (placement)");
             }
             FS_HIP(launch_tile_sorts(st, tiles, variants | (spec_fits ? 0 : split), (uint32_t)P, reinterpret_cast<const uint2*>(ranges_p), order_p,
-                                     keys[1], keys[0], vals[0]),
+                                     keys[1], keys[0], vals[0], places),
                    "k_tile_sort");
         }
         ctx->spec_set = tile_sort_variants((int64_t)max_len, long_lists, 0);

@@ -334,7 +334,8 @@ struct RecAlloc {
     uint64_t* wg_totals;             // [2][TILE_COPIES] out: each workgroup's records, and its sum of tiles_touched
 };
 
-// BANDS (placement): the words go into their band of tiles instead, and tile_place[t] <- the first place of tile t (see k_band_split).
+// BANDS (placement): the words go into their band of tiles instead, and `places` gets the first place of every tile and the bands'
+// bounds (see k_band_split).
 template <bool CB, bool SCATTER, bool BANDS>
 __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, const ushort4* __restrict__ rect,
                                                     const float* __restrict__ depth,
@@ -344,7 +345,7 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
                                                     int num_tiles, uint32_t* __restrict__ tile_counter,
                                                     const uint2* __restrict__ ranges, uint32_t P, uint32_t rec_limit,
                                                     uint64_t* __restrict__ bucket,
-                                                    float4* __restrict__ pair_grad, RecAlloc ra, uint32_t* __restrict__ tile_place)
+                                                    float4* __restrict__ pair_grad, RecAlloc ra, BandPlaces places)
 {
     static_assert(SCATTER || !BANDS, "a variant of the placement");
     extern __shared__ uint32_t s_tile[];   // this workgroup's counter per tile (BANDS: per band)
@@ -353,11 +354,12 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
     const uint32_t lane = lane_id();
     if (BANDS) {
         for (int t0 = (int)(threadIdx.x & ~63u); t0 < num_tiles; t0 += TILE_PAIR_THREADS) {
-            const uint32_t first = band_bounds(ranges, t0, num_tiles, lane).x;
-            if (lane == 0) s_tile[t0 / BAND_TILES] = first + my_row[t0];
+            const uint2 bounds = band_bounds(ranges, t0, num_tiles, lane);
+            if (lane == 0) s_tile[t0 / BAND_TILES] = bounds.x + my_row[t0];
+            if (lane == 0 && blockIdx.x == 0) places.band[t0 / BAND_TILES] = bounds;
         }
         for (int t = (int)(blockIdx.x * TILE_PAIR_THREADS + threadIdx.x); t < num_tiles; t += (int)gridDim.x * TILE_PAIR_THREADS)
-            tile_place[t] = ranges[t].x;
+            places.tile[t] = ranges[t].x;
     } else {
         for (int t = threadIdx.x; t < num_tiles; t += TILE_PAIR_THREADS) s_tile[t] = SCATTER ? ranges[t].x + my_row[t] : 0u;
     }
@@ -718,22 +720,51 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
 // Kernel durations in one step and in two, us: 166 and 57 + 36 at 10 M pairs (3 M Gaussians, 1920x1080), 394 and 126 + 108 at 27 M;
 // a step 1660 and 1585, 2480 and 2295.  Taking 2048 words with 256 threads, 4096 with 1024 or 8192 with 1024: order and placement
 // 158, 161, 162 instead of 157 at 10 M pairs, 446, 434, 433 instead of 432 at 27 M.
+// The chunks of all bands are dealt out as one row, so that bands of any lengths keep the chip busy.  With as many workgroups for each
+// band as for the next, those of the longest one went on alone; before and after, us: 5 M pairs with nine tenths of them in 6 of 128
+// bands 42.1 and 21.8, half in 4 bands 38.3 and 20.8, 10 M pairs with half in 6 bands 39.7 and 35.3; even bands 40.9 and 38.8 at 12 M
+// pairs, 153 and 142 at 36 M, 9.8 and 10.4 at 2.5 M.
 constexpr int SPLIT_THREADS = 512;
 constexpr int SPLIT_WORDS = 4096;
-__global__ __launch_bounds__(SPLIT_THREADS) void k_band_split(const uint2* __restrict__ ranges, int num_tiles, uint32_t limit,
-                                                              uint32_t* __restrict__ tile_place, const uint64_t* __restrict__ by_band,
-                                                              uint64_t* __restrict__ by_tile)
+__global__ __launch_bounds__(SPLIT_THREADS) void k_band_split(int num_tiles, uint32_t limit, BandPlaces places,
+                                                              const uint64_t* __restrict__ by_band, uint64_t* __restrict__ by_tile)
 {
     constexpr int PER = SPLIT_WORDS / SPLIT_THREADS;
+    constexpr int BANDS = (TILE_LDS_MAX_TILES + 64 * BAND_TILES - 1) / (64 * BAND_TILES);   // of a lane: BANDS lane ... BANDS lane + BANDS - 1
     __shared__ uint64_t k[SPLIT_WORDS];
     __shared__ uint32_t cnt[BAND_TILES], first[BAND_TILES], to[BAND_TILES];   // words of each tile, the first one's place in k; from there to by_tile
-    const int t = threadIdx.x, t0 = (int)blockIdx.y * BAND_TILES;
-    const uint2 band = band_bounds(ranges, t0, num_tiles, lane_id());   // (every wavefront for itself)
-    const uint32_t end = min(band.y, limit);   // (nothing was placed beyond the limit)
-    // (64 bits: the next round's first place may not fit 32)
-    for (uint64_t p = (uint64_t)band.x + (uint64_t)blockIdx.x * SPLIT_WORDS; p < end; p += (uint64_t)gridDim.x * SPLIT_WORDS) {
+    const int t = threadIdx.x, lane = (int)lane_id();
+    // (every wavefront for itself)
+    uint32_t begin[BANDS], end[BANDS], chunks[BANDS], mine = 0;
+#pragma unroll
+    for (int q = 0; q < BANDS; q++) {
+        const int b = BANDS * lane + q;
+        const uint2 bounds = b * BAND_TILES < num_tiles ? places.band[b] : make_uint2(~0u, 0u);
+        begin[q] = bounds.x;
+        end[q] = min(bounds.y, limit);   // (nothing was placed beyond the limit)
+        chunks[q] = begin[q] < end[q] ? (end[q] - begin[q] - 1) / SPLIT_WORDS + 1 : 0u;
+        mine += chunks[q];
+    }
+    const uint32_t upto = wave_inclusive_scan(mine);
+    const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+    for (uint32_t c = blockIdx.x; c < all; c += gridDim.x) {
+        uint32_t before = upto - mine, p = 0, last = 0;
+        int band = -1;
+#pragma unroll
+        for (int q = 0; q < BANDS; q++) {
+            if (c >= before && c - before < chunks[q]) {
+                band = BANDS * lane + q;
+                p = begin[q] + (c - before) * SPLIT_WORDS;
+                last = end[q];
+            }
+            before += chunks[q];
+        }
+        const int owner = __builtin_ctzll(__ballot(band >= 0));   // (c < all: there is one)
+        p = (uint32_t)__builtin_amdgcn_readlane((int)p, owner);
+        last = (uint32_t)__builtin_amdgcn_readlane((int)last, owner);
+        const int t0 = __builtin_amdgcn_readlane(band, owner) * BAND_TILES;
         const uint64_t* const src = by_band + p;
-        const int m = (int)min((uint64_t)SPLIT_WORDS, end - p);
+        const int m = (int)min((uint32_t)SPLIT_WORDS, last - p);
         uint64_t w[PER];
 #pragma unroll
         for (int u = 0; u < PER; u++) w[u] = t + u * SPLIT_THREADS < m ? src[t + u * SPLIT_THREADS] : 0ull;
@@ -747,7 +778,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) void k_band_split(const uint2* __res
         if (t < BAND_TILES) {
             const uint32_t c = cnt[t], at = wave_inclusive_scan(c) - c;
             first[t] = at;
-            to[t] = (c != 0u && t0 + t < num_tiles ? atomicAdd(&tile_place[t0 + t], c) : limit) - at;
+            to[t] = (c != 0u && t0 + t < num_tiles ? atomicAdd(&places.tile[t0 + t], c) : limit) - at;
         }
         __syncthreads();
 #pragma unroll
@@ -1186,12 +1217,6 @@ hipError_t launch_emit_pairs_cb(hipStream_t st, int64_t n, const fs_projected& p
     return hipGetLastError();
 }
 
-// The tiles' totals lie behind their ranges [T, 2] and order [T]; once k_tile_layout is done with them they are free.
-static uint32_t* tile_places(const uint2* ranges, int num_tiles)
-{
-    return const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(ranges)) + 3 * (size_t)num_tiles;
-}
-
 hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, int tiles_x,
                              int num_tiles, uint32_t* tile_count, uint32_t* tile_total, uint2* ranges,
                              uint32_t* tile_order, uint64_t* totals, uint32_t* rec_offsets, uint32_t* rec_counts,
@@ -1207,10 +1232,10 @@ hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj
         const float4* co = reinterpret_cast<const float4*>(proj.conic_opacity);
         if (cfg.compact_box)
             hipLaunchKernelGGL((k_tile_pairs<true, false, false>), grid, block, lds, st, n, rect, proj.depth, m2, co, cfg,
-                               nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, ra, nullptr);
+                               nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, ra, BandPlaces{});
         else
             hipLaunchKernelGGL((k_tile_pairs<false, false, false>), grid, block, lds, st, n, rect, proj.depth, m2, co,
-                               cfg, nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, ra, nullptr);
+                               cfg, nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, ra, BandPlaces{});
     }
     const int sum_blocks = (num_tiles + 63) / 64;
     hipLaunchKernelGGL(k_tile_layout, dim3((unsigned)(sum_blocks + std::max<int64_t>(1, (n + LAYOUT_THREADS - 1) / LAYOUT_THREADS))), dim3(LAYOUT_THREADS), 0, st,
@@ -1223,7 +1248,8 @@ hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj
 
 hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg,
                                const uint32_t* rec_offsets, int tiles_x, int num_tiles, uint32_t pair_limit,
-                               uint32_t rec_limit, const uint2* ranges, uint32_t* cursor, uint64_t* bucket, float* pair_grad)
+                               uint32_t rec_limit, const uint2* ranges, uint32_t* cursor, uint64_t* bucket, float* pair_grad,
+                               const BandPlaces& places)
 {
     if (n <= 0) return hipSuccess;
     const dim3 grid(TILE_COPIES), block(TILE_PAIR_THREADS);
@@ -1233,8 +1259,7 @@ hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& pr
     const float4* co = reinterpret_cast<const float4*>(proj.conic_opacity);
     auto launch = [&](auto kernel, size_t bytes) {
         hipLaunchKernelGGL(kernel, grid, block, bytes, st, n, rect, proj.depth, m2, co, cfg, rec_offsets, tiles_x, num_tiles, cursor,
-                           ranges, pair_limit, rec_limit, bucket, reinterpret_cast<float4*>(pair_grad), RecAlloc{},
-                           tile_places(ranges, num_tiles));
+                           ranges, pair_limit, rec_limit, bucket, reinterpret_cast<float4*>(pair_grad), RecAlloc{}, places);
     };
     if (placed_by_bands(n, num_tiles)) {
         const size_t bytes = (size_t)(num_tiles + BAND_TILES - 1) / BAND_TILES * sizeof(uint32_t);
@@ -1260,7 +1285,8 @@ int tile_sort_variants(int64_t max_len, bool long_lists, int have)
 }
 
 hipError_t launch_tile_sorts(hipStream_t st, int num_tiles, int variants, uint32_t pair_limit, const uint2* ranges,
-                             const uint32_t* tile_order, const uint64_t* bucket, uint64_t* keys_out, uint32_t* vals_out)
+                             const uint32_t* tile_order, uint64_t* bucket, uint64_t* keys_out, uint32_t* vals_out,
+                             const BandPlaces& places)
 {
     if (num_tiles <= 0) return hipSuccess;
     // Lists longer than len_lo stand at the front of the order: it is sorted by buckets of ORDER_STEP lengths (the last one
@@ -1272,11 +1298,10 @@ hipError_t launch_tile_sorts(hipStream_t st, int num_tiles, int variants, uint32
         return dim3(std::min((uint32_t)num_tiles, std::max(1u, pair_limit / least)));
     };
     if (variants & TS_SPLIT) {
-        // (the words of a band are dealt out to a fixed number of workgroups: bands are of different lengths, and the host does not know them)
+        // (no more chunks than these; a capacity far beyond the pairs would give workgroups that leave at once)
         const uint32_t bands = (uint32_t)((num_tiles + BAND_TILES - 1) / BAND_TILES);
-        const uint32_t each = std::max(1u, std::min(pair_limit / SPLIT_WORDS, 4096u) / bands);
-        hipLaunchKernelGGL(k_band_split, dim3(each, bands), dim3(SPLIT_THREADS), 0, st, ranges, num_tiles, pair_limit,
-                           tile_places(ranges, num_tiles), keys_out, const_cast<uint64_t*>(bucket));
+        hipLaunchKernelGGL(k_band_split, dim3(std::min(pair_limit / SPLIT_WORDS, 4096u) + bands), dim3(SPLIT_THREADS), 0, st, num_tiles,
+                           pair_limit, places, keys_out, bucket);
     }
     // the long lists first: few workgroups, each a long chain of steps, which more threads shorten
     if (variants & TS_HUGE)

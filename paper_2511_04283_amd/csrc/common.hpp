@@ -386,10 +386,15 @@ constexpr int64_t BAND_MIN_N = 1000000;
 inline bool placed_by_bands(int64_t n, int num_tiles) { return n >= BAND_MIN_N && n <= (int64_t)1 << BAND_SHIFT && num_tiles > BAND_TILES; }
 // Placement and the per-tile sorts.  pair_limit / rec_limit: how many words / gradient records the buffers hold; the
 // kernels write nothing at or beyond them and leave alone a segment that reaches beyond pair_limit, so they may be
-// enqueued before the host knows the totals.
+// enqueued before the host knows the totals.  places: written by a placement into bands, read by the split.
+struct BandPlaces {
+    uint32_t* tile;   // [num_tiles] where a tile's next words go (the tiles' totals of launch_tile_count, which are done with by then)
+    uint2* band;      // [ceil(num_tiles / BAND_TILES)] first and last + 1 place of its pairs ({~0, 0}: none)
+};
 hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg,
                                const uint32_t* rec_offsets, int tiles_x, int num_tiles, uint32_t pair_limit,
-                               uint32_t rec_limit, const uint2* ranges, uint32_t* cursor, uint64_t* bucket, float* pair_grad);
+                               uint32_t rec_limit, const uint2* ranges, uint32_t* cursor, uint64_t* bucket, float* pair_grad,
+                               const BandPlaces& places);
 // The sort launches, by the list lengths they take: (0, SMALL], (SMALL, MID], (MID, MAX], (MAX, HUGE], and
 // (SMALL, MAX] in one launch (TS_MIDMAX, instead of TS_MID and TS_MAX).  The lists between SMALL and MID get a launch of
 // their own (three of its workgroups fit a compute unit, two of the MAX kind) when the lists are long throughout
@@ -401,7 +406,8 @@ hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& pr
 enum { TS_SMALL = 1, TS_MID = 2, TS_MAX = 4, TS_HUGE = 8, TS_MIDMAX = 16, TS_SPLIT = 32 };
 int tile_sort_variants(int64_t max_len, bool long_lists, int have);
 hipError_t launch_tile_sorts(hipStream_t st, int num_tiles, int variants, uint32_t pair_limit, const uint2* ranges,
-                             const uint32_t* tile_order, const uint64_t* bucket, uint64_t* keys_out, uint32_t* vals_out);
+                             const uint32_t* tile_order, uint64_t* bucket, uint64_t* keys_out, uint32_t* vals_out,
+                             const BandPlaces& places);
 
 constexpr int RADIX_BLOCK_KEYS = 2048;  // keys ranked by one workgroup per pass
 constexpr int RADIX_BITS = 9;            // widest digit

@@ -90,11 +90,11 @@ hipError_t launch_tile_count(hipStream_t, int64_t, const fs_projected&, const Cf
     return hipSuccess;
 }
 hipError_t launch_tile_scatter(hipStream_t, int64_t, const fs_projected&, const CfgDev&, const uint32_t*, int, int, uint32_t, uint32_t,
-                               const uint2*, uint32_t*, uint64_t*, float*)
+                               const uint2*, uint32_t*, uint64_t*, float*, const BandPlaces&)
 {
     return hipSuccess;
 }
-hipError_t launch_tile_sorts(hipStream_t, int, int, uint32_t, const uint2*, const uint32_t*, const uint64_t*, uint64_t*, uint32_t*)
+hipError_t launch_tile_sorts(hipStream_t, int, int, uint32_t, const uint2*, const uint32_t*, uint64_t*, uint64_t*, uint32_t*, const BandPlaces&)
 {
     return hipSuccess;
 }

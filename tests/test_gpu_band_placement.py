@@ -64,3 +64,81 @@ def test_order(n, grid, crowd, compact_box):
         assert np.array_equal(bins.copy_keys().cpu().numpy(), keys), visible
         del proj, bins, put, where
     c.close()
+
+
+def scattered(n, pairs, grid, crowd_bands, share, seed):
+    """`pairs` pairs, in rows of neighbouring tiles; a share of the Gaussians starts on so many bands from the second on, the others anywhere."""
+    import torch
+    from paper_2511_04283_amd import binding as B
+    dev = "cuda:0"
+    tx, ty = grid
+    gen = torch.Generator(device=dev).manual_seed(seed)
+    rand = lambda *s: torch.rand(s, device=dev, generator=gen)
+    at = torch.where(rand(n) < share, 64 + (rand(n) * 64 * crowd_bands).long(), (rand(n) * tx * ty).long().clamp_(max=tx * ty - 1))
+    x0, y0 = at % tx, at // tx
+    w = torch.minimum(pairs // n + (rand(n) < (pairs % n) / n).long(), tx - x0)
+    rect = torch.stack([x0, y0, x0 + w, y0 + 1], 1).to(torch.int16)
+    means = torch.stack([16.0 * x0 + 8.0, 16.0 * y0 + 8.0], 1)
+    return B.Projected(means, 0.2 + 50.0 * rand(n), torch.tensor([1e-6, 0.0, 1e-6, 0.02], device=dev).repeat(n, 1), rand(n, 3),
+                       rect, w.to(torch.int32), torch.zeros((n, 3), dtype=torch.uint8, device=dev))
+
+
+def test_bands_of_very_different_lengths():
+    """The second step's chunks of 4096 words go through the bands in one row: more chunks than workgroups, bands without a pair, a
+    share of the first step's words beyond what the buffers hold.  Against the radix path's order."""
+    import torch
+    from paper_2511_04283_amd import binding as B
+    from paper_2511_04283_amd import scenes
+    grid, n = (120, 68), 3 * LEAST
+    config = B.default_config()
+    tiled = B.Context("cuda:0", config)
+    config.sort_mode = B.FS_SORT_RADIX
+    radix = B.Context("cuda:0", config)
+    cam = B.make_camera(scenes.Camera(16 * grid[0], 16 * grid[1], 500.0, 500.0, 8.0 * grid[0], 8.0 * grid[1]))
+    longest = 0
+    # (5 M: on a new context, then ahead of the totals; 8 M and 20 M outgrow the buffers of the one before)
+    for pairs, bands, share in ((5, 6, 0.9), (5, 7, 1.0), (8, 9, 0.97), (20, 12, 0.5), (20, 14, 0.6), (4, 128, 0.0)):
+        proj = scattered(n, pairs * 1000000, grid, bands, share, pairs + bands)
+        got, want = tiled.fs_bin_sort(proj, cam), radix.fs_bin_sort(proj, cam)
+        assert got.struct.pair_offsets is None and got.num_pairs == want.num_pairs   # (ordered per tile)
+        for copy in ("copy_ranges", "copy_gauss", "copy_keys"):
+            assert torch.equal(getattr(got, copy)(), getattr(want, copy)()), (pairs, bands, copy)
+        longest = max(longest, got.num_pairs)
+    assert longest > (4096 + 128) * 4096
+    tiled.close()
+    radix.close()
+
+
+def test_chunks_at_their_edges():
+    """Bands of 4096 words, of one more, of one and of none, and a last one of a single tile."""
+    import torch
+    from paper_2511_04283_amd import binding as B
+    from paper_2511_04283_amd import scenes
+    grid, n = (13, 25), LEAST   # 325 tiles: five bands and five tiles
+    lengths = [4096, 4097, 0, 1, 8192, 4095]
+    rng = np.random.default_rng(3)
+    tiles = np.concatenate([rng.integers(64 * b, min(64 * b + 64, 325), m) for b, m in enumerate(lengths)])
+    v = len(tiles)
+    dev = "cuda:0"
+    gen = torch.Generator(device=dev).manual_seed(5)
+    seen = torch.randperm(n, device=dev, generator=gen)[:v].sort().values
+    put = lambda a, shape, dtype: torch.zeros((n, *shape), dtype=dtype, device=dev).index_copy_(0, seen, a.to(dtype))
+    t = torch.from_numpy(rng.permutation(tiles)).to(dev)
+    x0, y0 = t % grid[0], t // grid[0]
+    one = torch.ones(v, device=dev)
+    proj = B.Projected(put(torch.stack([16.0 * x0 + 8, 16.0 * y0 + 8], 1), (2,), torch.float32),
+                       put(0.2 + 50.0 * torch.rand(v, device=dev, generator=gen), (), torch.float32),
+                       put(torch.tensor([1e-2, 0.0, 1e-2, 0.5], device=dev).repeat(v, 1), (4,), torch.float32),
+                       torch.zeros((n, 3), device=dev), put(torch.stack([x0, y0, x0 + 1, y0 + 1], 1), (4,), torch.int16),
+                       put(one, (), torch.int32), torch.zeros((n, 3), dtype=torch.uint8, device=dev))
+    config = B.default_config()
+    tiled = B.Context(dev, config)
+    config.sort_mode = B.FS_SORT_RADIX
+    radix = B.Context(dev, config)
+    cam = B.make_camera(scenes.Camera(16 * grid[0], 16 * grid[1], 500.0, 500.0, 8.0 * grid[0], 8.0 * grid[1]))
+    got, want = tiled.fs_bin_sort(proj, cam), radix.fs_bin_sort(proj, cam)
+    assert got.num_pairs == want.num_pairs == sum(lengths)
+    for copy in ("copy_ranges", "copy_gauss", "copy_keys"):
+        assert torch.equal(getattr(got, copy)(), getattr(want, copy)()), copy
+    tiled.close()
+    radix.close()
