@@ -49,6 +49,7 @@ struct fs_ctx {
     hipEvent_t totals_event = nullptr;   // recorded behind the copy of fs_bin_sort's totals (radix mode)
     int spec_set = 0;                    // the sort launches (TS_*) the previous per-tile ordering on this ctx would have
                                          // chosen (0: none): what fs_bin_sort enqueues ahead of its read-back
+    int64_t candidates_before = -1;      // of the previous ordering (-1: none); chooses the placement (placed_by_bands)
     uint64_t* total_dev = nullptr;   // device: totals [4]: pairs, backward records, pairs counted per tile, longest tile list
     uint64_t* total_host = nullptr;  // pinned host block of four totals (copied from total_dev, or written by k_tile_layout)
     uint64_t* counters = nullptr;    // device: TILE_COUNTERS of launch_tile_count (the first is zero between calls)
@@ -422,8 +423,10 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
     uint32_t* const order_p = ranges_p + 2 * (size_t)tiles;
     uint32_t* const ttotal_p = ranges_p + 3 * (size_t)tiles;
     uint32_t* const tcount_p = ranges_p + 4 * (size_t)tiles;
-    const BandPlaces places = {ttotal_p, reinterpret_cast<uint2*>(tcount_p + (size_t)TILE_COPIES * tiles)};
     const bool bucketed = ctx->cfg.sort_mode == FS_SORT_AUTO && tiles <= TILE_LDS_MAX_TILES;
+    const bool bands = placed_by_bands(n, tiles, ctx->candidates_before);   // (then keys[0] is placed into, and split into keys[1] ahead of the sorts)
+    const int split = bands ? TS_SPLIT : 0;
+    const BandPlaces places = bands ? BandPlaces{ttotal_p, reinterpret_cast<uint2*>(tcount_p + (size_t)TILE_COPIES * tiles)} : BandPlaces{};
     FS_TRY(ensure(ctx, ctx->offsets, (size_t)(n > 0 ? n : 1) * sizeof(uint32_t), "offsets"));
     FS_TRY(ensure(ctx, ctx->scan_tmp, scan_tmp_bytes(n), "scan"));
     FS_TRY(ensure(ctx, ctx->splats, (size_t)(n > 0 ? n : 1) * SPLAT_REC * sizeof(float), "splats"));
@@ -467,7 +470,7 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
                                  reinterpret_cast<uint2*>(ranges_p), order_p, ctx->total_host,
                                  static_cast<uint32_t*>(cb ? ctx->rec_offsets.ptr : ctx->offsets.ptr),
                                  cb ? static_cast<uint32_t*>(ctx->rec_counts.ptr) : nullptr, ctx->counters,
-                                 static_cast<float*>(ctx->splats.ptr)),
+                                 static_cast<float*>(ctx->splats.ptr), bands),
                "k_tile_pairs (count)");
         ctx->counters_dirty = false;
     } else {
@@ -487,8 +490,6 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
     // call.  The kernels write nothing beyond the capacities they are given; what the totals then say was not covered
     // (a longer list's sort variant, or buffers that have to grow first) is enqueued afterwards.
     const uint32_t* recs_p = cb ? static_cast<const uint32_t*>(ctx->rec_offsets.ptr) : static_cast<const uint32_t*>(ctx->offsets.ptr);
-    const bool bands = placed_by_bands(n, tiles);   // (then keys[0] is placed into, and split into keys[1] ahead of the sorts)
-    const int split = bands ? TS_SPLIT : 0;
     fs_projected none = {};
     uint64_t cap_pairs = 0, cap_recs = 0;
     int spec_variants = 0;
@@ -527,6 +528,7 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
         return fail(ctx, FS_EINVAL, "fs_bin_sort: tiles_touched does not match rect (proj from another configuration?)");
     if (P >= (uint64_t)1 << 31) return fail(ctx, FS_ECAPACITY, "fs_bin_sort: pair count does not fit 31 bits");
     if (NR >= (uint64_t)1 << 31) return fail(ctx, FS_ECAPACITY, "fs_bin_sort: candidate tile count does not fit 31 bits");
+    ctx->candidates_before = (int64_t)NR;
     const uint64_t max_len = bucketed ? ctx->total_host[3] : 0;
     ctx->longest_list = (int64_t)max_len;
     const bool lds_sort = bucketed && max_len <= (uint64_t)TILE_SORT_HUGE;

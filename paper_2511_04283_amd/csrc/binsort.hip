@@ -1220,7 +1220,7 @@ hipError_t launch_emit_pairs_cb(hipStream_t st, int64_t n, const fs_projected& p
 hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, int tiles_x,
                              int num_tiles, uint32_t* tile_count, uint32_t* tile_total, uint2* ranges,
                              uint32_t* tile_order, uint64_t* totals, uint32_t* rec_offsets, uint32_t* rec_counts,
-                             uint64_t* counters, float* splats)
+                             uint64_t* counters, float* splats, bool bands)
 {
     uint64_t* const wg_totals = counters + 1;
     const RecAlloc ra = {proj.tiles_touched, rec_offsets, rec_counts, wg_totals};
@@ -1242,7 +1242,7 @@ hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj
                        tile_count, num_tiles, sum_blocks, tile_total, ranges, tile_order, totals,
                        reinterpret_cast<unsigned long long*>(counters), wg_totals, n, reinterpret_cast<const ushort4*>(proj.rect),
                        reinterpret_cast<const float2*>(proj.mean2d), reinterpret_cast<const float4*>(proj.conic_opacity), proj.rgb,
-                       cfg, rec_offsets, reinterpret_cast<float4*>(splats), placed_by_bands(n, num_tiles) ? 1 : 0);
+                       cfg, rec_offsets, reinterpret_cast<float4*>(splats), bands ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -1261,7 +1261,7 @@ hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& pr
         hipLaunchKernelGGL(kernel, grid, block, bytes, st, n, rect, proj.depth, m2, co, cfg, rec_offsets, tiles_x, num_tiles, cursor,
                            ranges, pair_limit, rec_limit, bucket, reinterpret_cast<float4*>(pair_grad), RecAlloc{}, places);
     };
-    if (placed_by_bands(n, num_tiles)) {
+    if (places.band) {
         const size_t bytes = (size_t)(num_tiles + BAND_TILES - 1) / BAND_TILES * sizeof(uint32_t);
         if (cfg.compact_box) launch(k_tile_pairs<true, true, true>, bytes);
         else launch(k_tile_pairs<false, true, true>, bytes);

@@ -372,21 +372,33 @@ constexpr int TILE_SORT_HUGE = 16384;  // ... with 146 KB (a compute unit of thi
 hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, int tiles_x,
                              int num_tiles, uint32_t* tile_count, uint32_t* tile_total, uint2* ranges,
                              uint32_t* tile_order, uint64_t* totals, uint32_t* rec_offsets, uint32_t* rec_counts,
-                             uint64_t* counters, float* splats);
-// With many pairs the placement goes in two steps, into bands of BAND_TILES consecutive tiles first (see k_band_split): `bucket` of
-// launch_tile_scatter is then what launch_tile_sorts knows as keys_out, and launch_tile_sorts is given TS_SPLIT.  The words of the
-// first step hold the tile within the band above the Gaussian's index.
+                             uint64_t* counters, float* splats, bool bands);
+// With many pairs the placement goes in two steps, into bands of BAND_TILES consecutive tiles first (see k_band_split): launch_tile_count is told so, `bucket` of
+// launch_tile_scatter is what launch_tile_sorts knows as keys_out, launch_tile_scatter is given `places` and launch_tile_sorts TS_SPLIT.
+// The words of the first step hold the tile within the band above the Gaussian's index.
 constexpr int BAND_TILES = 64;                 // the tiles of one of k_tile_layout's workgroups
 constexpr int BAND_SHIFT = 26;                 // bits of a word that the index has
-// (The host does not know the number of pairs when it chooses, so the number of Gaussians decides.  Placement and sorts in one step and
-// in two, us: 1920x1080, 3.4 pairs per Gaussian, 500k 37.6 and 49.1, 700k 50.6 and 56.1, 1 M 74.1 and 64.3, 1.4 M 104 and 80, 2 M 155
-// and 109, 3 M 236 and 158; 9 pairs per Gaussian, 300k 72 and 79, 500k 115 and 107, 1 M 205 and 150, 3 M 603 and 432; 1600x1064, 1 M
-// 73.4 and 66.4; 1332x876 with the Compact Box, 300k 28.1 and 39.1.)
+// The two steps write a word twice for lines that fill: they pay where the tiles' open lines do not fit the L2 and there are enough
+// words to bind the kernel.  The host does not know these when it chooses, so it goes by the candidate tiles of the context's ordering
+// before, and by the number of Gaussians alone in the first one.  (The order does not depend on the choice.)
+// Both launches and the sorts, in one step and in two, us: 1920x1080, 2.5 M pairs 109 and 111 (3 M Gaussians of which a fifth is seen),
+// 92.6 and 100 (1.5 M, two fifths), 3.1 M 125 and 122, 105 and 108, 4.2 M 122 and 112, 12.5 M 378 and 295; Compact Box, 2.8 M candidates
+// 117 and 123, 3.3 M 138 and 132, 168 and 152, 8.3 M 384 and 321; 1332x876, 2.5 M 80.6 and 81.7, 3.0 M 95.6 and 92.0, Compact Box 2.9 M
+// 124 and 118; 640x480, 2.2 M 99.7 and 106, 3.0 M 146 and 131; few seen (0.1 to 1.3 M pairs of 1 to 3 M Gaussians) 54.6 to 87 and 62 to 100.
+// Where the Compact Box drops two of five candidates, the tests hide the writes, and two steps are within 2 % of one up to 12 M candidates
+// (112 and 113 us at 6 M, 671 and 653 at 18 M).  Fewer Gaussians with more pairs each make runs of one band's words, whose adds in LDS
+// wait for one another: 700k 102 and 105 at 2.9 M, wide 300k 131 and 145 at 3.4 M, 400k 159 and 161 at 4.5 M, 700k 222 and 204 at 8.0 M.
 constexpr int64_t BAND_MIN_N = 1000000;
-inline bool placed_by_bands(int64_t n, int num_tiles) { return n >= BAND_MIN_N && n <= (int64_t)1 << BAND_SHIFT && num_tiles > BAND_TILES; }
+constexpr int64_t BAND_MIN_CANDIDATES = 2850000;
+// candidates_before: -1 where there was no ordering yet
+inline bool placed_by_bands(int64_t n, int num_tiles, int64_t candidates_before)
+{
+    return n >= BAND_MIN_N && n <= (int64_t)1 << BAND_SHIFT && num_tiles > BAND_TILES &&
+           (candidates_before < 0 || candidates_before >= BAND_MIN_CANDIDATES);
+}
 // Placement and the per-tile sorts.  pair_limit / rec_limit: how many words / gradient records the buffers hold; the
 // kernels write nothing at or beyond them and leave alone a segment that reaches beyond pair_limit, so they may be
-// enqueued before the host knows the totals.  places: written by a placement into bands, read by the split.
+// enqueued before the host knows the totals.  places: written by a placement into bands, read by the split (null: no bands).
 struct BandPlaces {
     uint32_t* tile;   // [num_tiles] where a tile's next words go (the tiles' totals of launch_tile_count, which are done with by then)
     uint2* band;      // [ceil(num_tiles / BAND_TILES)] first and last + 1 place of its pairs ({~0, 0}: none)

@@ -13,8 +13,10 @@ int64_t stub_pairs = 0;             // pairs of every view
 int stub_queue = 0;                 // words for the host arrive when the stream has been asked this often whether it is done (0: at once)
 int stub_never = 0;                 // ... or, of 1: the totals, 2: the loss, never: the stream is done without
 // ... and reads: flags found set when k_render_bwd is launched, waits for the whole stream
+// and how many launches went by bands of tiles: counts, placements, splits
 int64_t stub_stale_flags = -1;
 int stub_syncs = 0;
+int stub_bands[3] = {0, 0, 0};
 
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -83,19 +85,23 @@ hipError_t launch_preprocess(hipStream_t, int64_t, int, const fs_gaussians&, boo
     return hipSuccess;
 }
 hipError_t launch_tile_count(hipStream_t, int64_t, const fs_projected&, const CfgDev&, int, int, uint32_t*, uint32_t*, uint2*, uint32_t*,
-                             uint64_t* totals, uint32_t*, uint32_t*, uint64_t*, float*)
+                             uint64_t* totals, uint32_t*, uint32_t*, uint64_t*, float*, bool bands)
 {
+    stub_bands[0] += bands;
     const uint64_t pairs = (uint64_t)stub_pairs, four[4] = {pairs, pairs, pairs, 1};
     words(1, totals, four, 4);
     return hipSuccess;
 }
 hipError_t launch_tile_scatter(hipStream_t, int64_t, const fs_projected&, const CfgDev&, const uint32_t*, int, int, uint32_t, uint32_t,
-                               const uint2*, uint32_t*, uint64_t*, float*, const BandPlaces&)
+                               const uint2*, uint32_t*, uint64_t*, float*, const BandPlaces& places)
 {
+    stub_bands[1] += places.band != nullptr;
     return hipSuccess;
 }
-hipError_t launch_tile_sorts(hipStream_t, int, int, uint32_t, const uint2*, const uint32_t*, uint64_t*, uint64_t*, uint32_t*, const BandPlaces&)
+hipError_t launch_tile_sorts(hipStream_t, int, int variants, uint32_t, const uint2*, const uint32_t*, uint64_t*, uint64_t*, uint32_t*,
+                             const BandPlaces&)
 {
+    stub_bands[2] += (variants & TS_SPLIT) != 0;
     return hipSuccess;
 }
 hipError_t launch_render_fwd(hipStream_t, const CamDev&, const CfgDev&, const uint32_t*, const uint32_t*, const uint32_t*, const float*,

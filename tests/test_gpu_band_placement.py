@@ -1,13 +1,32 @@
-"""The placement in two steps (bands of 64 tiles, then tiles), taken from a million Gaussians on: the order bit for bit against a
-stable sort of (tile, depth bits, index), on a new context, ahead of the totals, and where what was enqueued ahead of them does not
-fit; at the sizes where the rule begins and ends, with one tile too few, a last band of one tile, empty bands, one band that has
-nearly everything, and the highest indices."""
+"""The placement in two steps (bands of 64 tiles, then tiles), taken from a million Gaussians on where the context's ordering before
+had 2.85 M candidate tiles or there was none: the order bit for bit against a stable sort of (tile, depth bits, index) or the radix
+path's, on a new context, ahead of the totals, and where what was enqueued ahead of them does not fit; at the sizes where the rule
+begins and ends, with one tile too few, a last band of one tile, empty bands, one band that has nearly everything, and the highest
+indices."""
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 LEAST, MOST = 1000000, 1 << 26   # Gaussians
+CANDIDATES = 2850000   # of the ordering before
+
+
+def scattered(n, pairs, grid, crowd_bands, share, seed):
+    """`pairs` pairs, in rows of neighbouring tiles; a share of the Gaussians starts on so many bands from the second on, the others anywhere."""
+    import torch
+    from paper_2511_04283_amd import binding as B
+    dev = "cuda:0"
+    tx, ty = grid
+    gen = torch.Generator(device=dev).manual_seed(seed)
+    rand = lambda *s: torch.rand(s, device=dev, generator=gen)
+    at = torch.where(rand(n) < share, 64 + (rand(n) * 64 * crowd_bands).long(), (rand(n) * tx * ty).long().clamp_(max=tx * ty - 1))
+    x0, y0 = at % tx, at // tx
+    w = torch.minimum(pairs // n + (rand(n) < (pairs % n) / n).long(), tx - x0)
+    rect = torch.stack([x0, y0, x0 + w, y0 + 1], 1).to(torch.int16)
+    means = torch.stack([16.0 * x0 + 8.0, 16.0 * y0 + 8.0], 1)
+    return B.Projected(means, 0.2 + 50.0 * rand(n), torch.tensor([1e-6, 0.0, 1e-6, 0.02], device=dev).repeat(n, 1), rand(n, 3),
+                       rect, w.to(torch.int32), torch.zeros((n, 3), dtype=torch.uint8, device=dev))
 
 
 @pytest.mark.parametrize("n, grid, crowd", [(LEAST - 1, (13, 5), 0), (LEAST, (13, 5), 0), (LEAST, (16, 4), 0), (LEAST + 65, (40, 32), 0),
@@ -26,7 +45,13 @@ def test_order(n, grid, crowd, compact_box):
     c = B.Context("cuda:0", config)
     tx, ty = grid
     cam = B.make_camera(scenes.Camera(16 * tx, 16 * ty, 500.0, 500.0, 8.0 * tx, 8.0 * ty))
-    for visible in (20000, 30000, 200000 if tx * ty > 100 else 100000):   # (the last turn's pairs outgrow the buffers of the one before)
+    # (the turns with few Gaussians are by bands on the new context and behind an ordering of many candidates; below the rule's least, the
+    # last turn's pairs outgrow the buffers of the one before)
+    for turn, visible in enumerate((20000, 30000, 200000 if tx * ty > 100 else 100000)):
+        if n >= LEAST and turn:
+            many = scattered(LEAST, 3200000, (128, 120), 0, 0.0, turn)
+            assert c.fs_bin_sort(many, B.make_camera(scenes.Camera(2048, 1920, 500.0, 500.0, 1024.0, 960.0))).struct.num_records >= CANDIDATES
+            del many
         if crowd:
             visible = min(visible, 100000)
         seen = np.sort(rng.choice(n, visible - 2, replace=False)) if n < MOST else np.sort(rng.integers(0, n, visible - 2))
@@ -64,23 +89,6 @@ def test_order(n, grid, crowd, compact_box):
         assert np.array_equal(bins.copy_keys().cpu().numpy(), keys), visible
         del proj, bins, put, where
     c.close()
-
-
-def scattered(n, pairs, grid, crowd_bands, share, seed):
-    """`pairs` pairs, in rows of neighbouring tiles; a share of the Gaussians starts on so many bands from the second on, the others anywhere."""
-    import torch
-    from paper_2511_04283_amd import binding as B
-    dev = "cuda:0"
-    tx, ty = grid
-    gen = torch.Generator(device=dev).manual_seed(seed)
-    rand = lambda *s: torch.rand(s, device=dev, generator=gen)
-    at = torch.where(rand(n) < share, 64 + (rand(n) * 64 * crowd_bands).long(), (rand(n) * tx * ty).long().clamp_(max=tx * ty - 1))
-    x0, y0 = at % tx, at // tx
-    w = torch.minimum(pairs // n + (rand(n) < (pairs % n) / n).long(), tx - x0)
-    rect = torch.stack([x0, y0, x0 + w, y0 + 1], 1).to(torch.int16)
-    means = torch.stack([16.0 * x0 + 8.0, 16.0 * y0 + 8.0], 1)
-    return B.Projected(means, 0.2 + 50.0 * rand(n), torch.tensor([1e-6, 0.0, 1e-6, 0.02], device=dev).repeat(n, 1), rand(n, 3),
-                       rect, w.to(torch.int32), torch.zeros((n, 3), dtype=torch.uint8, device=dev))
 
 
 def test_bands_of_very_different_lengths():

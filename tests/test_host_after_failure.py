@@ -1,4 +1,5 @@
-"""What a context's bookkeeping says after a call that failed half way, and how its calls wait for the GPU's words, on the CPU:
+"""What a context's bookkeeping says after a call that failed half way, how its calls wait for the GPU's words and which placement
+they choose, on the CPU:
 abi.hip's host code on a stub of the GPU (host_abi_stub.cpp) whose launches and allocations fail, and whose words come late or
 never, on request."""
 import ctypes
@@ -150,4 +151,37 @@ def test_words_that_never_come(stub, words, call, message):
         assert c.rc == B.FS_OK and syncs.value - before == waits
         if call == "train":
             assert list(c.out3) == [0.25, 0.5, 0.75]
+    stub.fs_destroy(c.h)
+
+
+def test_placement_is_chosen_by_the_ordering_before(stub):
+    """From a million Gaussians on, placement by bands where the ordering before had the candidates that make it worth while (with
+    fewer it is the slower way), in a context's first ordering in any case; count, placement and split of an ordering agree."""
+    c = Ctx(stub, pairs=0)
+    c.cam.width, c.cam.height = 1920, 1080
+    bands = (ctypes.c_int * 3).in_dll(stub, "stub_bands")
+
+    def by_bands(n, pairs):
+        c.pairs(pairs)
+        before = list(bands)
+        b = c.B.fs_bins()
+        assert stub.fs_bin_sort(c.h, ctypes.byref(c.proj), ctypes.byref(c.cam), ctypes.c_int64(n), ctypes.byref(b)) == c.B.FS_OK
+        count, place, split = (x - y for x, y in zip(bands, before))
+        assert count in (0, 1) and place == split and (place > 0) == (count == 1)
+        return count == 1
+
+    M = 1000000
+    assert by_bands(M, 3 * M)            # (the first: by the number of Gaussians)
+    assert by_bands(M, 100000)           # 3 M before
+    assert not by_bands(M, 100000)
+    assert not by_bands(3 * M, 2850000 - 1)
+    assert not by_bands(3 * M, 2850000)
+    assert by_bands(3 * M, 4 * M)
+    assert not by_bands(M - 1, 4 * M)
+    assert by_bands(M, 0)
+    assert not by_bands(M, 3 * M)
+    c.cam.width = c.cam.height = 128     # 64 tiles
+    assert not by_bands(M, 3 * M)
+    c.cam.width = 129
+    assert by_bands(M, 3 * M)
     stub.fs_destroy(c.h)
