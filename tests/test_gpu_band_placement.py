@@ -3,8 +3,12 @@ had 2.85 M candidate tiles or there was none: the order bit for bit against a st
 path's, on a new context, ahead of the totals, and where what was enqueued ahead of them does not fit; at the sizes where the rule
 begins and ends, with one tile too few, a last band of one tile, empty bands, one band that has nearly everything, and the highest
 indices."""
+import math
+
 import numpy as np
 import pytest
+
+from test_gpu_tile_sort import pairs_met
 
 pytestmark = pytest.mark.gpu
 
@@ -148,5 +152,64 @@ def test_chunks_at_their_edges():
     assert got.num_pairs == want.num_pairs == sum(lengths)
     for copy in ("copy_ranges", "copy_gauss", "copy_keys"):
         assert torch.equal(getattr(got, copy)(), getattr(want, copy)()), copy
+    tiled.close()
+    radix.close()
+
+
+def test_missed_candidates():
+    """With the Compact Box, ellipses that miss tiles of their rectangles: no word for those, and their gradient records, in which the
+    turn before has left gradients, add nothing.  Against the oracle's pairs, the radix path's order, and the layout of records that
+    reads no place that nothing was written to."""
+    import torch
+    from oracle import Config, Oracle
+    from paper_2511_04283_amd import binding as B
+    from paper_2511_04283_amd import scenes
+    o = Oracle(np.float32, Config(compact_box=True))
+    tx, ty, n, dev = 120, 68, LEAST + 65, "cuda:0"
+    gen = torch.Generator(device=dev).manual_seed(11)
+    rand = lambda *s: torch.rand(s, device=dev, generator=gen)
+    config = B.default_config()
+    config.compact_box = 1
+    tiled = B.Context(dev, config)
+    tiled.fs_set_record_mode(B.FS_RECORDS_DENSE)
+    config.sort_mode = B.FS_SORT_RADIX
+    radix = B.Context(dev, config)
+    cam = B.make_camera(scenes.Camera(16 * tx, 16 * ty, 500.0, 500.0, 8.0 * tx, 8.0 * ty))
+    g = B.Gaussians(torch.tensor([0.0, 0.0, 5.0], device=dev).repeat(n, 1), torch.full((n, 3), 0.1, device=dev),
+                    torch.tensor([1.0, 0.0, 0.0, 0.0], device=dev).repeat(n, 1), torch.full((n,), 0.02, device=dev),
+                    torch.zeros((n, 1, 3), device=dev), 0)
+    dL = torch.ones((3, 16 * ty, 16 * tx), device=dev)
+    for turn in range(2):   # (the first one's placement is behind the totals, the second one's ahead of them)
+        size = 1 + (rand(n, 2) * 3).long()
+        first = (rand(n, 2) * torch.tensor([tx - 3, ty - 3], device=dev)).long()
+        # (as wide as meets every tile; then within the rectangle, round some point of it)
+        mean, conic = 16.0 * first + 8.0, torch.tensor([1e-6, 0.0, 1e-6, 0.02], device=dev).repeat(n, 1)
+        if turn == 1:
+            half = 8.0 * size * (0.3 + 0.7 * rand(n, 2))
+            conic[:, [0, 2]] = 2.0 * math.log(0.02 * 255.0) / half ** 2
+            mean = 16.0 * first + 16.0 * size * (0.1 + 0.8 * rand(n, 2))
+        rect, depth = torch.cat([first, first + size], 1), 0.2 + 50.0 * rand(n)
+        candidates = int(size.prod(1).sum())
+        assert candidates >= CANDIDATES
+        tile, gauss = pairs_met(o, *(a.cpu().numpy() for a in (rect, depth, mean, conic)), tx)
+        proj = B.Projected(mean, depth, conic, rand(n, 3), rect.to(torch.int16),
+                           torch.from_numpy(np.bincount(gauss, minlength=n)).to(dev, torch.int32), torch.zeros((n, 3), dtype=torch.uint8, device=dev))
+        got, want = tiled.fs_bin_sort(proj, cam), radix.fs_bin_sort(proj, cam)
+        assert got.num_pairs == len(gauss) and got.struct.num_records == candidates and got.struct.pair_offsets is None
+        assert (got.num_pairs == candidates) == (turn == 0)
+        ends = np.cumsum(np.bincount(tile, minlength=tx * ty))
+        ranges = got.copy_ranges().cpu().numpy()
+        assert np.array_equal(ranges[ranges[:, 1] > 0, 1], ends[ranges[:, 1] > 0])
+        for copy in ("copy_ranges", "copy_gauss", "copy_keys"):
+            assert torch.equal(getattr(got, copy)(), getattr(want, copy)()), (turn, copy)
+        final_T, n_contrib = tiled.fs_render_fwd(proj, got, cam)[1:]
+        dense = tiled.fs_render_bwd(g, cam, proj, got, final_T, n_contrib, dL, want_2d=True)
+    assert got.num_pairs < 0.9 * candidates
+    # (the terms are the same: sums of up to nine of them in single precision are within 1e-5 in whatever order)
+    tiled.fs_set_record_mode(B.FS_RECORDS_SPARSE)
+    sparse = tiled.fs_render_bwd(g, cam, proj, got, final_T, n_contrib, dL, want_2d=True)
+    for name in ("mean2d", "conic", "rgb", "opacities"):
+        assert sparse[name].abs().max() > 0
+        assert (dense[name] - sparse[name]).abs().max() <= 1e-5 * sparse[name].abs().max(), name
     tiled.close()
     radix.close()
