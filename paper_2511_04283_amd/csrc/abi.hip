@@ -483,7 +483,7 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
                "hipMemcpyAsync");
         FS_HIP(hipEventRecord(ctx->totals_event, st), "hipEventRecord");
     }
-    // Per-tile ordering, second half (placement into the tiles' segments -- keys[1] serves as the bucket array -- and
+    // Per-tile ordering, second half (placement into the tiles' segments in keys[1] -- by bands, into keys[0] and from there -- and
     // the per-tile LDS sorts; the ranges are already in place).  When this ctx has ordered pairs per tile before, the
     // second half is enqueued right here, ahead of the host's wait for the totals, sized by what the buffers hold, with
     // the sort launches the previous call's lists would have chosen: otherwise the GPU idles for the whole round trip (wait, wake-up, launch) once per

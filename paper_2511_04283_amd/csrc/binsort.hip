@@ -313,7 +313,7 @@ __device__ __forceinline__ uint2 band_bounds(const uint2* __restrict__ ranges, i
 
 // Steps (1) and (2) walk the candidate tiles of 64 consecutive Gaussians per wavefront the way k_emit_pairs
 // does.  SCATTER = false: count[tile] += 1 per pair.  SCATTER = true: slot = first[tile] + counter[tile]++
-// (k_tile_layout has turned each copy's counter into that copy's start within the tile's segment),
+// (k_tile_layout has turned each copy's counter into that copy's start within the tile's segment, or those of a band into one),
 // bucket[slot] = depth_bits << 32 | index; also, with
 // the Compact Box, zeroes the gradient records of the candidates that are no pairs.  In this mode `P` and `rec_limit`
 // are the numbers of words / records the buffers hold: nothing is written at or beyond them (the kernel may be
@@ -520,14 +520,15 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
 //
 // The first `sum_blocks` workgroups, per tile: its count summed over the workgroups' rows; each row's counter is replaced
 // by the number of the tile's pairs in the rows before it (where that workgroup's pairs start within the tile's
-// segment).  A workgroup takes 64 tiles; its wavefront g takes rows [16 g, 16 g + 16) of each.
+// segment).  A workgroup takes 64 tiles; its wavefront g takes rows [16 g, 16 g + 16) of each.  Where the placement goes by
+// bands, these 64 tiles are one, and only the counter of its first tile is replaced, by the number of the band's pairs in the rows before.
 //
-// Whichever of them is done last then turns the tile totals into ranges [first, last), by an exclusive scan (thread t owns
-// the consecutive tiles [t*per, t*per + per)); totals[2] = sum,
-// totals[3] = longest list, totals[0..1] = the sums of the counting workgroups' totals (wg_totals); and the order in which
+// Whichever of them is done last then turns the tile totals into ranges [first, last), by an exclusive scan in rounds of 1024
+// tiles, a thread each; totals[2] = sum, totals[3] = longest list; and the order in which
 // the render kernels take the tiles (longest list first, bucketed by length / 8, as k_tile_order).
 //
-// The other workgroups pack the projected splats into the records the render kernels gather (SPLAT_REC).  The placement
+// The other workgroups pack the projected splats into the records the render kernels gather (SPLAT_REC); the first of them also
+// stores totals[0..1], the sums of the counting workgroups' totals (wg_totals).  The placement
 // kernel did this on the way, with one workgroup per compute unit; here it has the whole chip and hides the chain of the
 // two steps above, and the records no longer drive the placement's half-filled lines out of the L2.
 // Placement, sums and scan together, before and after: 222 and 185 us at 3 M Gaussians / 10 M pairs, 18.3 and 16.8 at 4k.
@@ -717,9 +718,9 @@ __global__ __launch_bounds__(LAYOUT_THREADS) void k_tile_layout(uint32_t* __rest
 // workgroups of a compute die keep a half-filled line open for each of 8160 tiles, 33 MB where its L2 holds four: 345 MB
 // were written for 80 at 10 M pairs, 849 for 219 at 27 M.  A band's share is 64 times as long and all open lines fit; the second
 // step reads and writes every word once more, in whole lines (a tile's share of 4096 words is 64 of them).
-// Kernel durations in one step and in two, us: 166 and 57 + 36 at 10 M pairs (3 M Gaussians, 1920x1080), 394 and 126 + 108 at 27 M;
-// a step 1660 and 1585, 2480 and 2295.  Taking 2048 words with 256 threads, 4096 with 1024 or 8192 with 1024: order and placement
-// 158, 161, 162 instead of 157 at 10 M pairs, 446, 434, 433 instead of 432 at 27 M.
+// Kernel durations in one step and in two, us: 193 and 68 + 39 at 12 M pairs (3 M Gaussians, 1920x1080), 486 and 155 + 142 at 36 M.
+// Taking 2048 words with 256 threads, 4096 with 1024 or 8192 with 1024: order and placement 158, 161, 162 instead of 157 at 10 M
+// pairs, 446, 434, 433 instead of 432 at 27 M.
 // The chunks of all bands are dealt out as one row, so that bands of any lengths keep the chip busy.  With as many workgroups for each
 // band as for the next, those of the longest one went on alone; before and after, us: 5 M pairs with nine tenths of them in 6 of 128
 // bands 42.1 and 21.8, half in 4 bands 38.3 and 20.8, 10 M pairs with half in 6 bands 39.7 and 35.3; even bands 40.9 and 38.8 at 12 M

@@ -355,7 +355,8 @@ hipError_t launch_emit_pairs_cb(hipStream_t st, int64_t n, const fs_projected& p
 // Tile-bucketed ordering (used when no tile's list is longer than TILE_SORT_HUGE; otherwise the global
 // radix sort below): per-tile counts and ranges, then placement into the tiles' segments and an LDS sort
 // of every segment.  ranges/tile_order/tile_total: [num_tiles]; tile_count: [TILE_COPIES, num_tiles], turned by
-// launch_tile_count into each copy's start within its tile (the `cursor` of launch_tile_scatter_sort).
+// launch_tile_count into each copy's start within its tile, or, with `bands`, into each copy's start within a band in the place of the
+// band's first tile (the `cursor` of launch_tile_scatter).
 // launch_tile_count also gives every Gaussian the place of its backward records (rec_offsets [n]: disjoint,
 // contiguous per Gaussian, not ordered by index; rec_counts [n], may be null: the area of its rectangle), packs the splat
 // records, and, with `counters` (TILE_COUNTERS uint64, the first of which is zero at the start and left zero), writes
