@@ -183,7 +183,9 @@ def main() -> int:
                     f"{r['write'] / 1e6:.1f} | {gbs:.0f} | {fmt(r.get('valu'), '{:.3g}')} | {fmt(r.get('issue'))} | {fmt(r.get('lanes'))} | "
                     f"{fmt(r.get('conflict'), '{:.3f}')} |\n")
         f.write("\nKernel groups of one step, from bench.py's line of the first run (HIP-event durations measured inside the "
-                "library, algorithmic work per launch) beside the counter traffic above:\n\n")
+                "library, algorithmic work per launch) beside the counter traffic above.  The time between a group's events holds what the "
+                "host takes to launch its kernels under the profiler, which varies from run to run: with kernels of a few us it is most of it "
+                "(emit_pairs of 4k Gaussians 0.021 and 0.036 ms in two runs of the same kernels).\n\n")
         f.write("| group | kernels | ms (events) | bound | algorithmic work | achieved | peak | fraction | HBM traffic (counters) | traffic / algorithmic |\n")
         f.write("|---|---|---:|---|---:|---:|---:|---:|---:|---:|\n")
         for grp, ro in bench.get("rooflines", {}).items():
