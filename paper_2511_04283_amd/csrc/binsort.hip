@@ -129,7 +129,7 @@ __device__ __forceinline__ void pack_splat(float4* __restrict__ splats, int64_t 
     rec[1] = make_float4(co.z, co.w, rgb[3 * i], rgb[3 * i + 1]);
     rec[2] = make_float4(rgb[3 * i + 2], __uint_as_float(first_record | (is_needle(co) ? NEEDLE : 0u)), __uint_as_float((uint32_t)r.x | (uint32_t)r.y << 16),
                          __uint_as_float((uint32_t)r.z | (uint32_t)r.w << 16));
-    rec[3] = support_octagon(co, cfg);
+    rec[3] = support_strips(co, cfg);
 }
 
 // One key per tile of each Gaussian's rectangle, rows then columns, starting at offsets[i].  A

@@ -93,35 +93,57 @@ __device__ __forceinline__ bool cb_tile_hit(float mx, float my, float A, float B
 }
 
 // ---- the render kernels' bound of a Gaussian's support ----------------------------------------------
-// A Gaussian can only be blended where sigma*G >= alpha_min, i.e. where q <= qg = 2 ln(sigma/alpha_min).  With
-// Sigma_2D = conic^-1, the set {q <= Q} lies within |dx| <= sqrt(Q Sigma_xx), |dy| <= sqrt(Q Sigma_yy), and between the
-// tangent lines at +-45 degrees, |dx + dy| <= sqrt(Q (Sxx + Syy + 2 Sxy)), |dx - dy| <= sqrt(Q (Sxx + Syy - 2 Sxy)) with
-// Sxy = -b/det (which trims the corners of the box for slanted, elongated Gaussians).
-// Q is taken as qg + 0.1 + e, where e bounds the rounding error of the fp32 q
-// for any pixel of a tile the Gaussian is paired with (|dx|,|dy| <= 3 sqrt(lambda_max) + 17), and the
-// half-widths get a further 0.2 % + 0.01 px (they are computed with the fast reciprocal,
-// square root and logarithm): outside the octagon the render kernels' arithmetic yields alpha < 0.96 alpha_min,
-// so dropping the pair cannot change any result.
-// Returned: the four half-widths, each with the reach of a 4x4 sub-tile's pixel centres from its centre (1.5, and 3 along
-// the diagonals) added; negative where the Gaussian is blended nowhere, huge where they come out as NaN (a degenerate conic:
-// the exact test decides).
-__device__ __forceinline__ float4 support_octagon(const float4& co /* a, b, c, sigma */, const CfgDev& cfg)
+// A Gaussian can only be blended where sigma*G >= alpha_min, i.e. where q <= qg = 2 ln(sigma/alpha_min).  With the conic (a, b, c)
+// and y = dy, {q <= Q} is |dx + (b/a) dy| <= sqrt(Q/a - (det/a^2) dy^2): an interval of x for every line, whose upper end is concave
+// in y and largest at y = Y = -(b/c) sqrt(Q c/det), and whose lower end is least at -Y.  Over the four lines of a row of sub-tiles
+// the interval's ends are therefore those at Y and -Y, moved into the row's range of y (strip_mask): a sub-tile is met by the
+// ellipse or not, with nothing lost to a bounding polygon.
+// Q is taken as 1.004 (qg + 0.1 + e), where e bounds the rounding error of the fp32 q for any pixel of a tile the Gaussian is paired
+// with (|dx|,|dy| <= 3 sqrt(lambda_max) + 17), and the ends get 0.01 px (they are computed with the fast reciprocal, square root and
+// logarithm; what det loses to cancellation, some 1e-7 times the ratio of the eigenvalues, stays below e / Q, which is 1e-6 times
+// that ratio).  Y is drawn in by half a thousandth, a quarter of what Q's factor adds, so that it lies inside the ellipse:
+// the upper end there is still above that of {q <= qg + 0.1 + e} anywhere.  Outside, the render kernels' arithmetic yields alpha <
+// 0.96 alpha_min, so dropping the pair cannot change any result.
+// Returned: {Q/a / 16, det/a^2 / 16, -b/a / 4, Y}, x in units of four pixels; no line is met ({-1, 0, 0, 0}) where the Gaussian is blended nowhere, all are where
+// the conic is degenerate or its ellipse longer than 16384 px (the exact test decides).
+// (An octagon, the box and two diagonals, took 81 instructions for a Gaussian's 16 sub-tiles where strip_mask takes 95, and let through sub-tiles at
+// the corners of slanted ellipses.  A whole pass with it and without, us: 3 M Gaussians at 1920x1080 1577 and 1521, with a tail of
+// large splats 2333 and 2040, 500k at 1600x1064 507 and 494, a render of 300k at 1332x876 137 and 133, 100k at 980x545 168 and 165.)
+__device__ __forceinline__ float4 support_strips(const float4& co /* a, b, c, sigma */, const CfgDev& cfg)
 {
     const float ratio = co.w * __builtin_amdgcn_rcpf(cfg.alpha_min);
-    if (!(ratio >= 1.0f)) return make_float4(-1.f, -1.f, -1.f, -1.f);
+    if (!(ratio >= 1.0f)) return make_float4(-1.f, 0.f, 0.f, 0.f);
     const float det = co.x * co.z - co.y * co.y;
-    const float inv = __builtin_amdgcn_rcpf(det);
-    const float sxx = co.z * inv, syy = co.x * inv, sxy = -co.y * inv;
+    const float inv = __builtin_amdgcn_rcpf(det), ra = __builtin_amdgcn_rcpf(co.x);
+    const float sxx = co.z * inv, syy = co.x * inv;
     const float D = 3.0f * __builtin_amdgcn_sqrtf(sxx + syy) + 17.0f;
     const float e = 1e-6f * (fabsf(co.x) + 2.0f * fabsf(co.y) + fabsf(co.z)) * D * D;
-    const float Q = 2.0f * __logf(ratio) + 0.1f + e;
-    const float hx = __builtin_amdgcn_sqrtf(Q * sxx) * 1.002f + 0.01f;
-    const float hy = __builtin_amdgcn_sqrtf(Q * syy) * 1.002f + 0.01f;
-    const float hu = __builtin_amdgcn_sqrtf(fmaxf(Q * (sxx + syy + 2.0f * sxy), 0.f)) * 1.002f + 0.02f;
-    const float hv = __builtin_amdgcn_sqrtf(fmaxf(Q * (sxx + syy - 2.0f * sxy), 0.f)) * 1.002f + 0.02f;
-    const float all = 3.0e38f;
-    const bool box = hx == hx && hy == hy, diagonals = hu == hu && hv == hv;
-    return make_float4(box ? hx + 1.5f : all, box ? hy + 1.5f : all, diagonals ? hu + 3.0f : all, diagonals ? hv + 3.0f : all);
+    const float Q = 1.004f * (2.0f * __logf(ratio) + 0.1f + e);
+    const float hx = __builtin_amdgcn_sqrtf(Q * sxx), hy = __builtin_amdgcn_sqrtf(Q * syy);
+    const float p = Q * ra, r = det * ra * ra, m = -co.y * ra, Y = -0.9995f * hx * co.y * __builtin_amdgcn_rcpf(co.z);
+    // (comparisons that NaNs fail as well)
+    const bool plain = det > 0.f && co.x > 0.f && co.z > 0.f && hx < 16384.f && hy < 16384.f && p < 1.0e30f && r < 1.0e30f && fabsf(m) < 1.0e30f && fabsf(Y) < 1.0e30f;
+    return plain ? make_float4(0.0625f * p, 0.0625f * r, 0.25f * m, Y) : make_float4(3.0e38f, 0.f, 0.f, 0.f);
+}
+
+// The sub-tiles (4 x 4 pixels, bit 4 ky + kx of column kx, line ky) of the tile at whose origin the Gaussian sits at (ox, oy) that
+// hold a pixel centre's square met by the ellipse of support_strips.
+__device__ __forceinline__ uint32_t strip_mask(const float4& ell, float ox, float oy)
+{
+    // column j's centres are 4j + 0.5 ... 4j + 3.5: met are those up to the upper end, without those that end before the lower one
+    const float x_up = __builtin_fmaf(ox, 0.25f, 0.8775f), x_low = __builtin_fmaf(ox, 0.25f, 0.1225f);
+    uint32_t mask = 0;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const float y0 = (float)(4 * k) + 0.5f - oy, y1 = y0 + 3.0f;   // the strip's first and last line of centres
+        const float yh = fminf(fmaxf(ell.w, y0), y1), yl = fminf(fmaxf(-ell.w, y0), y1);
+        // (a strip that the ellipse does not reach leaves NaNs here, which the maxima with zero below make an empty interval)
+        const float sh = __builtin_amdgcn_sqrtf(__builtin_fmaf(-ell.y * yh, yh, ell.x)), sl = __builtin_amdgcn_sqrtf(__builtin_fmaf(-ell.y * yl, yl, ell.x));
+        const uint32_t upto = (uint32_t)fminf(fmaxf(__builtin_fmaf(ell.z, yh, x_up) + sh, 0.f), 4.f);
+        const uint32_t before = (uint32_t)fminf(fmaxf(__builtin_fmaf(ell.z, yl, x_low) - sl, 0.f), 4.f);
+        mask |= ((15u << before) & ((1u << upto) - 1u)) << (4 * k);
+    }
+    return mask;
 }
 
 // A needle: a splat at least some thirty times as long as wide (the ratio of the eigenvalues of Sigma_2D, which is about
@@ -338,8 +360,8 @@ size_t scan_tmp_bytes(int64_t n);
 hipError_t launch_exclusive_scan(hipStream_t st, const uint32_t* in, uint32_t* out, int64_t n, void* tmp,
                                  uint64_t* total_dev);
 
-// Splat record (SPLAT_REC floats = 64 bytes, one per Gaussian): mx my a b | c sigma r g | b offset(+NEEDLE) rect01 rect23 | the
-// half-widths of support_octagon (formed here once: the render kernels would form them for every pair)
+// Splat record (SPLAT_REC floats = 64 bytes, one per Gaussian): mx my a b | c sigma r g | b offset(+NEEDLE) rect01 rect23 |
+// support_strips (formed here once: the render kernels would form them for every pair)
 constexpr int SPLAT_REC = 16;
 hipError_t launch_emit_pairs(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, const uint32_t* offsets,
                              int tiles_x, uint64_t* keys, uint32_t* vals, float* splats);

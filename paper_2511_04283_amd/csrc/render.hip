@@ -9,9 +9,9 @@
 // quadrant (w&1, w>>1); each of its four rows of 16 lanes (the unit of the DPP row operations) owns
 // one 4x4 sub-tile of that quadrant.  The tile's depth-ordered Gaussians are staged through LDS in
 // batches of 255 (k_render_bwd: 231, with the absolute gradient 207).  Every Gaussian's support
-// {alpha >= alpha_min} is bounded by an octagon (conservatively, support_octagon; it comes with the splat
+// {alpha >= alpha_min} is bounded by its ellipse (conservatively, support_strips; it comes with the splat
 // record) and each of the 16 sub-tiles gets its own order-preserving list of the staged Gaussians
-// whose octagon meets it.  In the inner loops the four
+// whose ellipse meets it.  In the inner loops the four
 // rows of a wavefront walk their own lists side by side, so one wavefront iteration evaluates
 // four different Gaussians on 16 pixels each.  A wavefront stops as soon as all of its 64 pixels
 // have terminated.
@@ -19,7 +19,7 @@
 // alpha, T and the blend weights follow a fixed fp32 operation order (fused multiply-adds only
 // where written as __builtin_fmaf; the file is compiled with -ffp-contract=off) so that the
 // integer outputs they decide (n_contrib, counts) can be reproduced bit for bit on a CPU.  The
-// octagon only ever drops (Gaussian, pixel) pairs that this arithmetic would reject as well.
+// ellipse only ever drops (Gaussian, pixel) pairs that this arithmetic would reject as well.
 //
 // Times "at 500k Gaussians and 1600x1064" and the like are of the scenes of perf/cases.py.  They have other pairs than those of
 // bench.py with the same sizes: 6 k against 11 k at 4k Gaussians and 128x128, 0.4 M to 0.5 M against 0.5 M at 100k, 2.1 M to 2.9 M
@@ -138,14 +138,9 @@ struct Stage {
 };
 
 // Sub-tile st = wave*4 + row of a tile sits at column kx = (wave&1)*2 + (row&1), line ky = (wave>>1)*2 + (row>>1).
-// The 16-bit sets (bit st) of the sub-tiles in one column, one line, on one diagonal kx + ky = s or kx - ky = d.
 struct SubTiles {
-    static constexpr int kx(int st) { return ((st >> 2) & 1) * 2 + (st & 1); }
-    static constexpr int ky(int st) { return (st >> 3) * 2 + ((st >> 1) & 1); }
-    static constexpr uint32_t col(int k) { uint32_t m = 0; for (int st = 0; st < 16; st++) m |= kx(st) == k ? 1u << st : 0u; return m; }
-    static constexpr uint32_t line(int k) { uint32_t m = 0; for (int st = 0; st < 16; st++) m |= ky(st) == k ? 1u << st : 0u; return m; }
-    static constexpr uint32_t sum(int s) { uint32_t m = 0; for (int st = 0; st < 16; st++) m |= kx(st) + ky(st) == s ? 1u << st : 0u; return m; }
-    static constexpr uint32_t dif(int d) { uint32_t m = 0; for (int st = 0; st < 16; st++) m |= kx(st) - ky(st) == d ? 1u << st : 0u; return m; }
+    // bits 4 ky + kx to bits st: the two middle bits of the bit's number change places
+    static __device__ __forceinline__ uint32_t from_grid(uint32_t m) { return (m & 0xc3c3u) | (m & 0x0c0cu) << 2 | (m >> 2 & 0x0c0cu); }
 };
 
 template <int CTRL>
@@ -159,8 +154,7 @@ __device__ __forceinline__ uint32_t dpp_shr_add(uint32_t v)
 // Contains one workgroup barrier; every thread of the workgroup must call it, after a barrier behind the previous
 // batch's walk.  A wavefront's own four lists are complete when it returns (the others' only behind another barrier).
 //
-// Which sub-tiles may blend a Gaussian: those whose centres lie within its support octagon, widened by a sub-tile's reach
-// (support_octagon; part of the splat record).
+// Which sub-tiles may blend a Gaussian: those its support's ellipse meets (support_strips, part of the splat record).
 //
 // Lists: every thread leaves its entry's 16 sub-tile bits in LDS; then the 16 lanes that own a sub-tile in the render
 // loops gather that sub-tile's bit of 16 slots each and expand them into slot numbers with a prefix sum over the row.
@@ -174,7 +168,7 @@ __device__ __forceinline__ int stage_batch(Stage<WITH_RGB, N>& s, uint32_t* s_id
 {
     const int t = threadIdx.x;
     const int swave = t >> 6, lane = t & 63;
-    uint32_t sub_mask = 0;  // bit (wave*4 + row) of every sub-tile the octagon meets
+    uint32_t sub_mask = 0;  // bit (wave*4 + row) of every sub-tile the ellipse meets
     if (t < m) {
         const float4* rec = splats + (size_t)g * (SPLAT_REC / 4);  // one 64-byte line
         const float4 r0 = rec[0], r1 = rec[1], r2 = rec[2];
@@ -191,31 +185,13 @@ __device__ __forceinline__ int stage_batch(Stage<WITH_RGB, N>& s, uint32_t* s_id
                                  ((uint32_t)(tile % cam.tiles_x) - x0));
         }
         if (WITH_RGB) s.r2[t] = make_float4(r1.z, r1.w, r2.x, id);
-        const float4 reach = rec[3];
-        // sub-tile column k has its centre at +4k+2 from the tile origin
-        const float ox = xy.x - (float)((tile % cam.tiles_x) * TILE), oy = xy.y - (float)((tile / cam.tiles_x) * TILE);
-        // Every test below concerns a whole family of sub-tiles at once (a column, a line, a diagonal), so each is
-        // made once and switches on the family's 16-bit pattern (SubTiles::col ...): 22 tests and a few ANDs instead
-        // of four tests per sub-tile.
-        uint32_t colm = 0, rowm = 0;
-#pragma unroll
-        for (int k = 0; k < 4; k++) {
-            colm |= (fabsf(ox - (float)(4 * k + 2)) <= reach.x) ? SubTiles::col(k) : 0u;
-            rowm |= (fabsf(oy - (float)(4 * k + 2)) <= reach.y) ? SubTiles::line(k) : 0u;
-        }
-        const float su = ox + oy, sv = ox - oy;
-        // the sub-tile in column kx, line ky has its centre at sum 4 (kx + ky) + 4 and difference 4 (kx - ky)
-        uint32_t summ = 0, difm = 0;
-#pragma unroll
-        for (int d = 0; d < 7; d++) {
-            summ |= (fabsf(su - (float)(4 * d + 4)) <= reach.z) ? SubTiles::sum(d) : 0u;
-            difm |= (fabsf(sv - (float)(4 * (d - 3))) <= reach.w) ? SubTiles::dif(d - 3) : 0u;
-        }
-        sub_mask = colm & rowm & summ & difm;
+        const float4 ell = rec[3];
+        sub_mask = SubTiles::from_grid(strip_mask(ell, xy.x - (float)((tile % cam.tiles_x) * TILE), xy.y - (float)((tile / cam.tiles_x) * TILE)));
     }
     reinterpret_cast<uint16_t*>(s.sub)[s.sub_place(t)] = (uint16_t)sub_mask;
-    constexpr uint32_t PAD = 0x01010101u * (uint32_t)(N - 1);
-    if (N == 256 || t < N) reinterpret_cast<uint4*>(s.list)[t] = make_uint4(PAD, PAD, PAD, PAD);
+    uint32_t pad = 0x01010101u * (uint32_t)(N - 1);
+    asm volatile("" : "+v"(pad));   // (formed here: kept for the next batch, four copies of it spill registers of k_render_bwd)
+    if (N == 256 || t < N) reinterpret_cast<uint4*>(s.list)[t] = make_uint4(pad, pad, pad, pad);
     __syncthreads();
     // lane i of the row that owns sub-tile st expands slots [16 i, 16 i + 16)
     const int st = swave * 4 + (lane >> 4);
@@ -944,7 +920,7 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
 // ---- per-splat-parallel backward (the mapping of Taming-3DGS that the paper's baseline uses) -------------
 // Alternative to k_render_bwd with the same inputs, outputs and record layout; kept for comparison.
 // A wavefront owns one 8x8 quadrant of the tile.  Per batch it forms the quadrant's list (the staged entries
-// whose octagon meets any of its four sub-tiles), takes it in chunks of 64 entries from the back, one entry per
+// whose ellipse meets any of its four sub-tiles), takes it in chunks of 64 entries from the back, one entry per
 // lane (lane 0 = the entry furthest back), and passes the quadrant's 64 pixels by one after the other.  For a
 // pixel p every lane evaluates its own Gaussian; what the per-pixel kernel carries from entry to entry becomes
 // two scans over the lanes:
