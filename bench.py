@@ -284,8 +284,10 @@ def main() -> int:
     g_in = 4 * (3 + 3 + 4 + 1 + 3 * K)            # bytes of one Gaussian's parameters (236 at degree 3)
     g_proj = 8 + 4 + 16 + 12 + 8 + 4 + 3           # bytes of one projected splat (fs_projected)
     copies = 256                                   # workgroups of the counting / placement kernels
-    # (the library's own rule for FS_RECORDS_AUTO: sparse per-pair gradient records when the lists are long on average)
-    sparse_records = P >= 320 * tiles
+    # (the library's own rule for FS_RECORDS_AUTO: sparse per-pair gradient records behind a forward pass that noted its blended pairs,
+    # which it does for lists that the per-tile sorts take, or when the lists are long on average)
+    noted = fused and not args.radix_sort and not args.per_splat_bwd and int(tile_len.max().item()) <= 16384
+    sparse_records = noted or P >= 320 * tiles
     work = {
         "preprocess": ("hbm", n * (12 + g_proj) + n_vis * (g_in - 12)),
         "emit_pairs": ("hbm", n * 16 + n_vis * 4 + 3 * 4 * tiles * copies + 16 * tiles + n * 8 + n_vis * (40 + 64)),

@@ -210,7 +210,9 @@ int fs_render_fwd(fs_ctx *ctx, const fs_projected *proj, const fs_bins *bins, co
  * dL_dimage = sign(image - target) / (3 H W) (may be NULL), the L1 loss (loss_out: device pointer to one double, may be
  * NULL) and the per-pixel error map of fs_error_mask, which the ctx keeps for a following fs_error_mask_fused.
  * Saves reading the finished image twice more.  Same outputs as the separate calls (the two fp64 sums are formed in
- * a different order).  target: [3,H,W]. */
+ * a different order).  target: [3,H,W].
+ * Where dL_dimage is given, a backward pass follows: the call also notes which pairs it blended and in which 4x4 pixels (ctx scratch,
+ * until the next fs_bin_sort), and fs_render_bwd over the same bins walks those pairs alone.  Same gradients. */
 int fs_render_fwd_loss(fs_ctx *ctx, const fs_projected *proj, const fs_bins *bins, const fs_camera *cam,
                        const float *target, float *image, float *final_T, uint32_t *n_contrib, float *dL_dimage,
                        double *loss_out);
@@ -264,7 +266,8 @@ int fs_set_backward_mode(fs_ctx *ctx, int32_t mode);
  *   flag byte; the sums read the flags and the flagged records.  Pays where most pairs receive nothing -- deep,
  *   opaque scenes whose lists are long and mostly end behind the pixels' last blended Gaussian -- and costs a few
  *   microseconds otherwise (one more scattered byte per record, one more dependent load per chunk of records).
- * FS_RECORDS_AUTO (default): sparse when the tile lists hold 320 pairs or more on average. */
+ * FS_RECORDS_AUTO (default): sparse when the forward pass noted its blended pairs (fs_render_fwd_loss with dL_dimage,
+ *   fs_train_step) or the tile lists hold 320 pairs or more on average. */
 enum { FS_RECORDS_AUTO = 0, FS_RECORDS_DENSE = 1, FS_RECORDS_SPARSE = 2 };
 int fs_set_record_mode(fs_ctx *ctx, int32_t mode);
 

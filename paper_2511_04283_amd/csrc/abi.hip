@@ -61,6 +61,9 @@ struct fs_ctx {
     bool loss_pending = false;       // as totals_pending
     ScratchBuf tile_partial;         // double [5, tiles]: per-tile sums of the fused forward pass
     ScratchBuf pair_bits;            // the record of the forward passes for the count pass (score_record_at)
+    uint64_t blends_generation = 0;  // the forward passes' record for the backward pass (blends_at) describes the bins of this generation
+                                     // (0: none) and an image of this size
+    int blends_width = 0, blends_height = 0;
     ScratchBuf rec_valid;            // uint8 [records]: 1 where k_render_bwd left a gradient record; k_preprocess_bwd puts
                                      // every flag it finds back to 0, so the array is all zeros between calls
     size_t rec_valid_zeroed = 0;     // the capacity of rec_valid that has been zeroed since its allocation
@@ -229,20 +232,23 @@ bool proj_ok(const fs_projected* p)
 // bins of an earlier fs_bin_sort (or of another ctx) point at memory that has been reused since
 bool bins_stale(const fs_ctx* ctx, const fs_bins* bins) { return bins->generation != ctx->generation || ctx->generation == 0; }
 
-// sparse records pay where the lists are long (most of their pairs receive nothing)
-bool sparse_records(const fs_ctx* ctx, const fs_bins* bins, int tiles)
+// Sparse records pay where the lists are long (most of their pairs receive nothing), and where the backward pass walks the blended
+// pairs only: dense ones make it look for the others in a second pass over the list.  k_render_bwd with k_preprocess_bwd, dense and
+// sparse, from a forward pass's record, us: 12k Gaussians at 509x337 46.9 and 46.3, 100k at 980x545 74.5 and 71.8, 300k at 1332x876
+// 200.9 and 200.5, 500k at 1600x1064 with the Compact Box 406 and 395, without 281 and 248.
+bool sparse_records(const fs_ctx* ctx, const fs_bins* bins, int tiles, bool from_blends)
 {
     return ctx->record_mode == FS_RECORDS_SPARSE ||
-           (ctx->record_mode == FS_RECORDS_AUTO && bins->num_pairs >= (int64_t)320 * tiles);
+           (ctx->record_mode == FS_RECORDS_AUTO && (from_blends || bins->num_pairs >= (int64_t)320 * tiles));
 }
 
 // The backward pass's per-pair records and, where they are sparse, one flag per record place, all zeros here (a fresh or
 // left-over array is cleared first); the caller of a sparse pass clears rec_valid_dirty when k_preprocess_bwd is enqueued.
-int record_buffers(fs_ctx* ctx, const fs_bins* bins, int tiles)
+int record_buffers(fs_ctx* ctx, const fs_bins* bins, bool sparse)
 {
     FS_TRY(ensure(ctx, ctx->pair_grad, (size_t)(bins->num_records ? bins->num_records : 1) * PAIR_REC * sizeof(float),
                   "pair gradients"));
-    if (!sparse_records(ctx, bins, tiles)) return FS_OK;
+    if (!sparse) return FS_OK;
     const size_t flags = ((size_t)(bins->num_records ? bins->num_records : 1) + 3) / 4 * 4;
     if (flags > ctx->rec_valid.cap) ctx->rec_valid_zeroed = 0;   // (also where growing fails: a later array may have the old size)
     FS_TRY(ensure(ctx, ctx->rec_valid, flags, "record flags"));
@@ -286,6 +292,35 @@ int wait_for_words(fs_ctx* ctx, const uint64_t* p, int count, const char* never)
         }
     std::atomic_thread_fence(std::memory_order_acquire);
     return FS_OK;
+}
+
+// The forward passes' record of blended pairs lies where the per-tile ordering had its unsorted words (eight bytes for each pair) and its
+// tiles' totals, both done with by then and next written by the next ordering.
+BlendRecord blends_at(const fs_ctx* ctx, int tiles)
+{
+    return {static_cast<uint2*>(ctx->keys[1].ptr), static_cast<int32_t*>(ctx->ranges.ptr) + 3 * (size_t)tiles};
+}
+// Where a forward pass that a backward pass follows is to leave it (entries == null: nowhere).  The backward pass does without for lists
+// longer than the record's positions; longest_list is 0 from the radix ordering, which does not know it.
+BlendRecord blends_for(fs_ctx* ctx, const fs_bins* bins, int tiles)
+{
+    ctx->blends_generation = 0;
+    if (bins->num_pairs <= 0 || ctx->longest_list <= 0 || ctx->longest_list > TILE_SORT_HUGE || ctx->per_splat_bwd) return {nullptr, nullptr};
+    return blends_at(ctx, tiles);
+}
+void note_blends(fs_ctx* ctx, const BlendRecord& blends, const fs_bins* bins, const CamDev& cam)
+{
+    if (!blends.entries) return;
+    ctx->blends_generation = bins->generation;
+    ctx->blends_width = cam.width;
+    ctx->blends_height = cam.height;
+}
+// the record of a forward pass over these bins, if there is one
+BlendRecord blends_of(const fs_ctx* ctx, const fs_bins* bins, const CamDev& cam)
+{
+    if (ctx->blends_generation == 0 || ctx->blends_generation != bins->generation || ctx->blends_width != cam.width || ctx->blends_height != cam.height)
+        return {nullptr, nullptr};
+    return blends_at(ctx, cam.tiles_x * cam.tiles_y);
 }
 
 // the record in ctx->pair_bits now describes the forward pass over these bins
@@ -539,10 +574,12 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
     const int64_t nb = radix_num_blocks((int64_t)P);
     for (int k = 0; k < 2; k++) {
         FS_TRY(ensure(ctx, ctx->keys[k], (size_t)(P ? P : 1) * sizeof(uint64_t), "keys"));
-        FS_TRY(ensure(ctx, ctx->vals[k], (size_t)(P ? P : 1) * sizeof(uint32_t), "values"));
+        if (k == 0 || !lds_sort) FS_TRY(ensure(ctx, ctx->vals[k], (size_t)(P ? P : 1) * sizeof(uint32_t), "values"));
     }
-    FS_TRY(ensure(ctx, ctx->hist, (size_t)(nb ? nb : 1) * RADIX_DIGITS * sizeof(uint32_t), "histograms"));
-    FS_TRY(ensure(ctx, ctx->scan_tmp, scan_tmp_bytes(RADIX_DIGITS * nb), "scan"));
+    if (!lds_sort) {
+        FS_TRY(ensure(ctx, ctx->hist, (size_t)(nb ? nb : 1) * RADIX_DIGITS * sizeof(uint32_t), "histograms"));
+        FS_TRY(ensure(ctx, ctx->scan_tmp, scan_tmp_bytes(RADIX_DIGITS * nb), "scan"));
+    }
 
     uint64_t* keys[2] = {static_cast<uint64_t*>(ctx->keys[0].ptr), static_cast<uint64_t*>(ctx->keys[1].ptr)};
     uint32_t* vals[2] = {static_cast<uint32_t*>(ctx->vals[0].ptr), static_cast<uint32_t*>(ctx->vals[1].ptr)};
@@ -624,7 +661,8 @@ int fs_render_fwd(fs_ctx* ctx, const fs_projected* proj, const fs_bins* bins, co
     ProfScope prof(ctx, FS_K_RENDER_FWD);
     FS_HIP(launch_render_fwd(ctx->stream, cd, make_cfg(ctx->cfg), bins->tile_ranges, bins->tile_order, bins->gauss_sorted,
                              static_cast<const float*>(bins->splats), image, final_T, n_contrib,
-                             bits ? score_record_at(ctx->pair_bits.ptr, bins->num_pairs) : ScoreRecord{nullptr, nullptr, nullptr}),
+                             bits ? score_record_at(ctx->pair_bits.ptr, bins->num_pairs) : ScoreRecord{nullptr, nullptr, nullptr},
+                             BlendRecord{nullptr, nullptr}),
            "k_render_fwd");
     if (bits) note_bits(ctx, bins, cd.tiles_x * cd.tiles_y);
     return FS_OK;
@@ -650,15 +688,18 @@ int fs_render_fwd_loss(fs_ctx* ctx, const fs_projected* proj, const fs_bins* bin
     FS_TRY(ensure(ctx, ctx->partial, (size_t)fused_partials() * sizeof(double), "partials"));
     FS_TRY(ensure(ctx, ctx->tile_partial, (size_t)5 * tiles * sizeof(double), "tile partials"));
     if (bits) FS_TRY(ensure(ctx, ctx->pair_bits, score_record_bytes(bins->num_pairs, cd.tiles_x * cd.tiles_y), "score record"));
+    const BlendRecord blends = dL_dimage ? blends_for(ctx, bins, tiles) : BlendRecord{nullptr, nullptr};   // (a backward pass follows)
     {
         ProfScope prof(ctx, FS_K_RENDER_FWD);
         FS_HIP(launch_render_fwd_fused(ctx->stream, cd, make_cfg(ctx->cfg), bins->tile_ranges, bins->tile_order,
                                        bins->gauss_sorted, static_cast<const float*>(bins->splats), image, final_T, n_contrib,
                                        target, dL_dimage, static_cast<float*>(ctx->err_map.ptr),
-                                       static_cast<double*>(ctx->tile_partial.ptr), bits ? score_record_at(ctx->pair_bits.ptr, bins->num_pairs) : ScoreRecord{nullptr, nullptr, nullptr}),
+                                       static_cast<double*>(ctx->tile_partial.ptr), bits ? score_record_at(ctx->pair_bits.ptr, bins->num_pairs) : ScoreRecord{nullptr, nullptr, nullptr},
+                                       blends),
                "k_render_fwd");
     }
     if (bits) note_bits(ctx, bins, tiles);
+    note_blends(ctx, blends, bins, cd);
     ProfScope prof(ctx, FS_K_L1);
     FS_HIP(launch_fold_tile_partials(ctx->stream, static_cast<const double*>(ctx->tile_partial.ptr), tiles, 3 * pixels,
                                      static_cast<double*>(ctx->partial.ptr), loss_out),
@@ -747,16 +788,18 @@ int fs_render_bwd(fs_ctx* ctx, const fs_gaussians* g, const fs_camera* cam, cons
     // (the records, their places and -- with the Compact Box -- the zeroed records of the candidate tiles that are
     // no pairs all live in this ctx and belong to its latest fs_bin_sort)
     if (bins_stale(ctx, bins)) return fail(ctx, FS_EINVAL, "fs_render_bwd: bins do not come from this context's latest fs_bin_sort");
-    FS_TRY(record_buffers(ctx, bins, cd.tiles_x * cd.tiles_y));
+    const BlendRecord blends = ctx->per_splat_bwd ? BlendRecord{nullptr, nullptr} : blends_of(ctx, bins, cd);
+    const bool sparse = sparse_records(ctx, bins, cd.tiles_x * cd.tiles_y, blends.entries != nullptr);
+    FS_TRY(record_buffers(ctx, bins, sparse));
     float* const pair_grad = static_cast<float*>(ctx->pair_grad.ptr);
-    uint8_t* const rec_valid = sparse_records(ctx, bins, cd.tiles_x * cd.tiles_y) ? static_cast<uint8_t*>(ctx->rec_valid.ptr) : nullptr;
+    uint8_t* const rec_valid = sparse ? static_cast<uint8_t*>(ctx->rec_valid.ptr) : nullptr;
     const CfgDev cf = make_cfg(ctx->cfg);
     // a8: every pair's record is written exactly once (sparse: that of every pair that received something, and flagged)
     if (bins->num_pairs > 0) {
         ProfScope prof(ctx, FS_K_RENDER_BWD);
         FS_HIP(launch_render_bwd(st, cd, cf, bins->tile_ranges, bins->tile_order, bins->gauss_sorted,
                                  static_cast<const float*>(bins->splats), final_T, n_contrib, dL_dimage, pair_grad, rec_valid,
-                                 out->dmean2d_abs != nullptr, ctx->per_splat_bwd),
+                                 out->dmean2d_abs != nullptr, ctx->per_splat_bwd, blends),
                "k_render_bwd");
     }
     // a9: per-Gaussian sum of its records (sparse: the flagged ones; the flags go back to 0), then the chain through
@@ -1089,26 +1132,29 @@ int fs_train_step(fs_ctx* ctx, const fs_train_state* t, const fs_camera* cam, co
     }
     fs_bins bins = {};
     FS_TRY(fs_bin_sort(ctx, &proj, cam, n, &bins));
+    const BlendRecord blends = blends_for(ctx, &bins, tiles);
     {
         ProfScope prof(ctx, FS_K_RENDER_FWD);
         FS_HIP(launch_render_fwd(st, cd, cf, bins.tile_ranges, bins.tile_order, bins.gauss_sorted,
-                                 static_cast<const float*>(bins.splats), image, final_T, n_contrib, ScoreRecord{nullptr, nullptr, nullptr}),
+                                 static_cast<const float*>(bins.splats), image, final_T, n_contrib, ScoreRecord{nullptr, nullptr, nullptr}, blends),
                "k_render_fwd");
     }
+    note_blends(ctx, blends, &bins, cd);
     uint64_t* const loss_words = reinterpret_cast<uint64_t*>(ctx->loss_host);
     if (ctx->loss_pending) FS_HIP(hipStreamSynchronize(st), "hipStreamSynchronize");   // (an earlier call's kernel may yet write them)
     unset_words(loss_words, 3);
     ctx->loss_pending = true;
     FS_TRY(fs_photo_loss(ctx, image, target, cd.height, cd.width, prm->lambda, dL, ctx->loss_host));
     if (n > 0) {
-        FS_TRY(record_buffers(ctx, &bins, tiles));
-        uint8_t* const rec_valid = sparse_records(ctx, &bins, tiles) ? static_cast<uint8_t*>(ctx->rec_valid.ptr) : nullptr;
+        const bool sparse = sparse_records(ctx, &bins, tiles, blends.entries != nullptr);
+        FS_TRY(record_buffers(ctx, &bins, sparse));
+        uint8_t* const rec_valid = sparse ? static_cast<uint8_t*>(ctx->rec_valid.ptr) : nullptr;
         float* const pair_grad = static_cast<float*>(ctx->pair_grad.ptr);
         if (bins.num_pairs > 0) {
             ProfScope prof(ctx, FS_K_RENDER_BWD);
             FS_HIP(launch_render_bwd(st, cd, cf, bins.tile_ranges, bins.tile_order, bins.gauss_sorted,
                                      static_cast<const float*>(bins.splats), final_T, n_contrib, dL, pair_grad, rec_valid, true,
-                                     ctx->per_splat_bwd),
+                                     ctx->per_splat_bwd, blends),
                    "k_render_bwd");
         }
         {

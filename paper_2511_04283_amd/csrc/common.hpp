@@ -131,7 +131,7 @@ __device__ __forceinline__ float4 support_strips(const float4& co /* a, b, c, si
 __device__ __forceinline__ uint32_t strip_mask(const float4& ell, float ox, float oy)
 {
     // column j's centres are 4j + 0.5 ... 4j + 3.5: met are those up to the upper end, without those that end before the lower one
-    const float x_up = __builtin_fmaf(ox, 0.25f, 0.8775f), x_low = __builtin_fmaf(ox, 0.25f, 0.1225f);
+    const float x_up = 0.25f * (ox + 3.51f), x_low = 0.25f * (ox + 0.49f);
     uint32_t mask = 0;
 #pragma unroll
     for (int k = 0; k < 4; k++) {
@@ -496,16 +496,24 @@ inline ScoreRecord score_record_at(void* base, int64_t num_pairs)
     r.tile_rows = reinterpret_cast<int32_t*>(b + (size_t)num_pairs * (PAIR_BITS_BYTES + sizeof(uint32_t)));
     return r;
 }
+// The record a forward pass leaves for k_render_bwd: the pairs it blended at some pixel of their tile, in list order, at the start of
+// the tile's segment of the pair arrays, [ranges[tile].x, + tile_count[tile]): the Gaussian, and the pair's position in the tile's list
+// (from 0, 16 bits) with the sub-tiles that blended it above (bit st: see SubTiles in render.hip).  Lists beyond the
+// per-tile sorts' have none.  entries == null: no record.
+struct BlendRecord {
+    uint2* entries;        // [P]
+    int32_t* tile_count;   // [tiles]
+};
 hipError_t launch_render_fwd(hipStream_t st, const CamDev& cam, const CfgDev& cfg, const uint32_t* ranges,
                              const uint32_t* tile_order, const uint32_t* gauss_sorted, const float* splats, float* image, float* final_T,
-                             uint32_t* n_contrib, const ScoreRecord& record);
+                             uint32_t* n_contrib, const ScoreRecord& record, const BlendRecord& blends);
 
 // forward pass with the L1 term and the error map fused into its epilogue (see k_render_fwd);
 // tile_partial: 5 * tiles doubles, err: H*W floats, dL may be null; record as for launch_render_fwd
 hipError_t launch_render_fwd_fused(hipStream_t st, const CamDev& cam, const CfgDev& cfg, const uint32_t* ranges,
                                    const uint32_t* tile_order, const uint32_t* gauss_sorted, const float* splats,
                                    float* image, float* final_T, uint32_t* n_contrib, const float* target, float* dL,
-                                   float* err, double* tile_partial, const ScoreRecord& record);
+                                   float* err, double* tile_partial, const ScoreRecord& record, const BlendRecord& blends);
 // the count pass from that record: counts[g] += |bits(row) & mask(tile)| over the rows of every tile
 // (longest_list: an upper bound of the rows of any tile, 0 if not known)
 hipError_t launch_score_bits(hipStream_t st, const CamDev& cam, const uint32_t* ranges, const ScoreRecord& record,
@@ -527,7 +535,7 @@ hipError_t launch_error_mask_from_map(hipStream_t st, int64_t pixels, int rule, 
 hipError_t launch_render_bwd(hipStream_t st, const CamDev& cam, const CfgDev& cfg, const uint32_t* ranges,
                              const uint32_t* tile_order, const uint32_t* gauss_sorted, const float* splats, const float* final_T,
                              const uint32_t* n_contrib, const float* dL_dimage, float* pair_grad, uint8_t* rec_valid,
-                             bool abs_grad, bool per_splat);
+                             bool abs_grad, bool per_splat, const BlendRecord& blends);
 
 hipError_t launch_score(hipStream_t st, const CamDev& cam, const CfgDev& cfg, const uint32_t* ranges,
                         const uint32_t* tile_order, const uint32_t* gauss_sorted, const float* splats, const uint32_t* n_contrib,

@@ -161,10 +161,11 @@ __device__ __forceinline__ uint32_t dpp_shr_add(uint32_t v)
 // The rest of a list is filled with the empty slot, so that the loops may run past a list's end.
 // REVERSED: the lists run from the last entry to the first, and the calling lane's row leaves out slots from row_end on.
 // ID_MODE: 0 = nothing, 1 = s_id[t] <- Gaussian index, 2 = r2[t].w <- index of the pair's
-// gradient record (where the pair was emitted before the sort: offset + place in the rectangle).
-template <int ID_MODE, bool REVERSED = false, bool WITH_RGB, int N>
+// gradient record (where the pair was emitted before the sort: offset + place in the rectangle), 3 = r2[t].w <- Gaussian index.
+// GIVEN: the sub-tiles come as an argument (bit st).
+template <int ID_MODE, bool REVERSED = false, bool GIVEN = false, bool WITH_RGB, int N>
 __device__ __forceinline__ int stage_batch(Stage<WITH_RGB, N>& s, uint32_t* s_id, const CamDev& cam,
-                                           int tile, const float4* __restrict__ splats, uint32_t g, int m, int row_end = N)
+                                           int tile, const float4* __restrict__ splats, uint32_t g, int m, int row_end = N, uint32_t given = 0)
 {
     const int t = threadIdx.x;
     const int swave = t >> 6, lane = t & 63;
@@ -178,6 +179,7 @@ __device__ __forceinline__ int stage_batch(Stage<WITH_RGB, N>& s, uint32_t* s_id
         s.r1[t] = make_float4(-0.5f * co.z, co.w, r1.z, r1.w);
         float id = 0.f;
         if (ID_MODE == 1) s_id[t] = g;
+        if (ID_MODE == 3) id = __uint_as_float(g);
         if (ID_MODE == 2) {
             const uint32_t r01 = __float_as_uint(r2.z), r23 = __float_as_uint(r2.w);
             const uint32_t x0 = r01 & 0xffffu, y0 = r01 >> 16, x1 = r23 & 0xffffu;
@@ -185,8 +187,12 @@ __device__ __forceinline__ int stage_batch(Stage<WITH_RGB, N>& s, uint32_t* s_id
                                  ((uint32_t)(tile % cam.tiles_x) - x0));
         }
         if (WITH_RGB) s.r2[t] = make_float4(r1.z, r1.w, r2.x, id);
-        const float4 ell = rec[3];
-        sub_mask = SubTiles::from_grid(strip_mask(ell, xy.x - (float)((tile % cam.tiles_x) * TILE), xy.y - (float)((tile / cam.tiles_x) * TILE)));
+        if (GIVEN) {
+            sub_mask = given;
+        } else {
+            const float4 ell = rec[3];
+            sub_mask = SubTiles::from_grid(strip_mask(ell, xy.x - (float)((tile % cam.tiles_x) * TILE), xy.y - (float)((tile / cam.tiles_x) * TILE)));
+        }
     }
     reinterpret_cast<uint16_t*>(s.sub)[s.sub_place(t)] = (uint16_t)sub_mask;
     uint32_t pad = 0x01010101u * (uint32_t)(N - 1);
@@ -201,7 +207,7 @@ __device__ __forceinline__ int stage_batch(Stage<WITH_RGB, N>& s, uint32_t* s_id
     const uint32_t both = bits_of(lo.x, 0) | bits_of(lo.y, 1) | bits_of(lo.z, 2) | bits_of(lo.w, 3) | bits_of(hi.x, 4) |
                           bits_of(hi.y, 5) | bits_of(hi.z, 6) | bits_of(hi.w, 7);
     uint32_t b16 = (both & 0xffu) | (both >> 16) << 8;
-    if (REVERSED) b16 &= (1u << min(max(row_end - 16 * i, 0), 16)) - 1u;
+    if (REVERSED && !GIVEN) b16 &= (1u << min(max(row_end - 16 * i, 0), 16)) - 1u;
     const uint32_t cnt = __popc(b16);
     uint32_t inc = cnt;
     inc = dpp_shr_add<0x111>(inc);  // row_shr:1
@@ -252,12 +258,13 @@ __device__ __forceinline__ bool lane_of(uint64_t mask) { return __builtin_amdgcn
 // the mask itself, so that no scalar instruction stands between it and what depends on it.  Whichever lanes are active stay so:
 // the mask is taken out of them and they are put back.  (Outputs are written before all inputs have been read: they share no
 // registers.  `hits` is read by a vector instruction behind at least two others: it is written early.)
-template <bool HITS>
+// BLENDS: `history` moves up by one bit, and its lowest says whether the lane blended (whatever lanes are active).
+template <bool HITS, bool BLENDS>
 __device__ __forceinline__ uint64_t blend_under_mask(uint64_t mask, float& C0, float& C1, float& C2, float& T, int& last, float c0, float c1,
-                                                     float c2, float w, float Tn, float T_min, float hit_above, int at, uint64_t& stop)
+                                                     float c2, float w, float Tn, float T_min, float hit_above, int at, uint64_t& stop, uint32_t& history)
 {
     uint64_t active, hits;
-#define FS_BLEND(COUNT)                                                                                                        \
+#define FS_BLEND(COUNT, SHIFT)                                                                                                        \
     asm("s_and_saveexec_b64 %[active], %[m]\n\t"                                                                               \
         "v_cmpx_ngt_f32_e32 vcc, %[T_min], %[Tn]\n\t"                                                                          \
         "v_mov_b32_e32 %[T], %[Tn]\n\t" COUNT                                                                                  \
@@ -266,14 +273,18 @@ __device__ __forceinline__ uint64_t blend_under_mask(uint64_t mask, float& C0, f
         "v_fmac_f32_e32 %[C2], %[c2], %[w]\n\t"                                                                                \
         "v_mov_b32_e32 %[l], %[at]\n\t"                                                                                        \
         "s_andn2_b64 %[stop], %[m], vcc\n\t"                                                                                   \
-        "s_mov_b64 exec, %[active]"                                                                                            \
+        "s_mov_b64 exec, %[active]" SHIFT                                                                                      \
         : [C0] "+&v"(C0), [C1] "+&v"(C1), [C2] "+&v"(C2), [T] "+&v"(T), [l] "+&v"(last), [active] "=&s"(active), [stop] "=&s"(stop), \
-          [hits] "=&s"(hits)                                                                                                   \
+          [hits] "=&s"(hits), [h] "+&v"(history)                                                                               \
         : [m] "s"(mask), [c0] "v"(c0), [c1] "v"(c1), [c2] "v"(c2), [w] "v"(w), [Tn] "v"(Tn), [T_min] "s"(T_min), [at] "s"(at), \
           [hit_above] "v"(hit_above)                                                                                           \
         : "scc", "vcc");
-    if (HITS) { FS_BLEND("v_cmp_gt_f32_e64 %[hits], %[w], %[hit_above]\n\t") }
-    else { FS_BLEND("") }
+#define FS_HISTORY "\n\tv_addc_co_u32_e32 %[h], vcc, %[h], %[h], vcc"
+    if (HITS && BLENDS) { FS_BLEND("v_cmp_gt_f32_e64 %[hits], %[w], %[hit_above]\n\t", FS_HISTORY) }
+    else if (HITS) { FS_BLEND("v_cmp_gt_f32_e64 %[hits], %[w], %[hit_above]\n\t", "") }
+    else if (BLENDS) { FS_BLEND("", FS_HISTORY) }
+    else { FS_BLEND("", "") }
+#undef FS_HISTORY
 #undef FS_BLEND
     return hits;
 }
@@ -301,9 +312,13 @@ __device__ __forceinline__ int wave_max_of_rows(int mine)
 // within the row); only the rows with a bit set are written, packed at the start of the tile's segment, each with its Gaussian.
 // With these the count pass is a population count per pair instead of a second walk over the lists (k_score_bits).
 //
+// BLENDS: the kernel notes the pairs it blends anywhere, and in which sub-tiles, for k_render_bwd (BlendRecord).  Each lane shifts one
+// bit per entry into a register; every 32 places the 16 lanes of a row put theirs together and name the slots (history_to_slots).
+// It costs 4 to 7 us at 300k and 500k Gaussians, 14 at 3 M, and saves k_render_bwd more: see there.
+//
 // (80 registers: with two more, where the compiler goes by itself, a SIMD holds five wavefronts instead of six, and the kernel with the
 // record takes 129 us instead of 119 at 500k Gaussians and 1600x1064.)
-template <bool FUSED, bool BITS>
+template <bool FUSED, bool BITS, bool BLENDS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_render_fwd(CamDev cam, CfgDev cfg, const uint2* __restrict__ ranges,
                                                     const uint32_t* __restrict__ tile_order,
                                                     const uint32_t* __restrict__ gauss_sorted,
@@ -311,11 +326,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_re
                                                     float* __restrict__ final_T, uint32_t* __restrict__ n_contrib,
                                                     const float* __restrict__ target, float scale,
                                                     float* __restrict__ dL, float* __restrict__ err,
-                                                    double* __restrict__ tile_partial, ScoreRecord record)
+                                                    double* __restrict__ tile_partial, ScoreRecord record, BlendRecord blends)
 {
     __shared__ Stage<true> s;
     __shared__ __align__(16) uint16_t s_pb[BITS ? SLOTS : 1][16];  // this batch's bits, [slot][sub-tile]
+    __shared__ uint32_t s_blend[BLENDS ? 2 : 1][BLENDS ? SLOTS / 2 : 1];   // sub-tiles that blended a slot's pair (16 bits), this batch's and the one's before
     __shared__ uint32_t s_rows;                                    // rows of the record this tile has written so far
+    __shared__ __align__(16) int s_alive[4];                       // whether a wavefront has pixels that go on
 
     const int tile = (int)tile_order[blockIdx.x];  // longest lists first
     const int sub = (threadIdx.x >> 6) * 4 + ((threadIdx.x & 63) >> 4);  // this lane's sub-tile list
@@ -338,7 +355,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_re
         const int i = start + (int)threadIdx.x;
         return i < total && threadIdx.x < BATCH ? gauss_sorted[range.x + i] : 0u;
     };
-    uint32_t g_next = entry(0), g_here = 0;
+    uint32_t g_next = entry(0);
+    auto g_here = [&](uint32_t t) { return __float_as_uint(s.r2[t].w); };   // the Gaussian of slot t, until the next batch is staged
     auto write_bits = [&](int count) {
         // A pair that is counted nowhere (at 500k Gaussians half of them: the rectangle's corners, entries behind the
         // last blended one) leaves nothing.  The others' rows are packed at the start of the tile's segment: a
@@ -363,15 +381,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_re
                 // other arrays from the caches)
                 nt_store(lo, record.rows + at * 2);
                 nt_store(hi, record.rows + at * 2 + 1);
-                record.row_gauss[at] = g_here;
+                record.row_gauss[at] = g_here(threadIdx.x);
             }
         }
     };
-    for (int start = 0; start < total; start += BATCH) {
-        const int alive = __syncthreads_or(done != ~0ull);
+    // BLENDS: the pairs of the batch before that were blended, in order behind those of earlier batches: every wavefront looks at all
+    // slots' words, so that it knows how many stand before its own.
+    int blended = 0, batch = 0;
+    auto write_blends = [&](int batch_start) {
+        const uint16_t* const words = reinterpret_cast<const uint16_t*>(s_blend[(batch & 1) ^ 1]);
+        uint32_t t = threadIdx.x;
+        asm volatile("" : "+v"(t));   // (as in history_to_slots)
+        const uint32_t mine = words[t];
+        int before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < SLOTS / 64; w++) {
+            const int count = __popcll(ballot(words[64 * w + ((int)t & 63)] != 0));
+            before += w < (int)(t >> 6) ? count : 0;
+            all += count;
+        }
+        const uint64_t bal = ballot(mine != 0u);
+        if (mine != 0u) {
+            const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+            blends.entries[(size_t)range.x + (uint32_t)(blended + before) + below] = make_uint2(g_here(t), (uint32_t)(batch_start + (int)t) | mine << 16);
+        }
+        blended += all;
+    };
+    int start = 0;
+    for (; start < total; start += BATCH) {
+        // (before the first batch nothing has been written that another thread reads; __syncthreads_or is two barriers and a reduction for
+        // any shape of workgroup)
+        int alive = 1;
+        if (start > 0) {
+            if ((threadIdx.x & 63) == 0) s_alive[threadIdx.x >> 6] = done != ~0ull;
+            __syncthreads();
+            const int4 a = *reinterpret_cast<const int4*>(s_alive);
+            alive = __builtin_amdgcn_readfirstlane((a.x | a.y) | (a.z | a.w));
+        }
         if (BITS && pending_m > 0) {
             write_bits(pending_m);
             pending_m = 0;
+        }
+        if (BLENDS) {
+            // (the words about to be cleared were read behind the barrier before the one inside the batch before)
+            if (start > 0) write_blends(start - BATCH);
+            if (threadIdx.x < SLOTS / 2) s_blend[batch & 1][threadIdx.x] = 0u;
         }
         if (alive == 0) break;
         const int m = min(BATCH, total - start);
@@ -381,8 +435,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_re
             row[1] = make_uint4(0u, 0u, 0u, 0u);
             pending_m = m;
         }
-        const int mine = stage_batch<0>(s, nullptr, cam, tile, splats, g_next, m);
-        if (BITS) g_here = g_next;
+        const int mine = stage_batch<BITS || BLENDS ? 3 : 0>(s, nullptr, cam, tile, splats, g_next, m);
         g_next = entry(start + BATCH);   // (its latency passes during the walk)
         // a row whose 16 pixels have all finished does not lengthen the wavefront's loop
         const bool row_alive = ((~done >> (threadIdx.x & 48)) & 0xffffull) != 0;
@@ -392,9 +445,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_re
         // alone (4.5 to 6 cycles for every instruction, scalar ones included).  Four
         // entries' alphas are formed side by side from one word of slots -- four independent chains -- and only the
         // transmittance runs through them one after the other; conditions are lane masks in the scalar unit and blending
-        // happens under the mask instead of through selects: a trip of four entries has 126 vector and 37 scalar instructions, the
-        // loop's own included (41 scalar ones where the mask was formed outside), with the record of counted pixels 139 and 44 (140
-        // and 53).  Lanes past their list's end evaluate the empty record.
+        // happens under the mask instead of through selects: a trip of four entries has 126 vector and 41 scalar instructions, the
+        // loop's own included, 12 more with the record of counted pixels, 4 more with that of blended pairs.  Lanes past their list's
+        // end evaluate the empty record.  The four records are requested ahead of all arithmetic, in the order of their use: with both
+        // records the compiler by itself places each request before its use (100k Gaussians: 60 us instead of 49, 3 M: 292 and 271).
         // The record: each entry's 64 bits go into one lane of two registers, and 64 entries later to the slots' rows; stored
         // entry by entry they took a 64-bit shift, an address, an LDS store and a change of the lane mask each.  Both steps together,
         // before and after, kernel durations in us, with the record: 4k Gaussians at 128x128 18.7 and 16.9, 100k at 980x545 54.8 and
@@ -414,24 +468,44 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_re
             }
             hits_lo = hits_hi = 0;
         };
-        int k = 0;
-        for (; k < longest && done != ~0ull; k += GROUP) {   // (leaves when all of the wavefront's pixels have terminated)
-            if (BITS && k != 0 && (k & 63) == 0) hits_to_rows(k - 64);
+        // BLENDS: bit 31 - j of `history` says whether this lane blended place k0 + j of its row's list (places being how many it holds);
+        // the row's 16 lanes together name the places, two for each lane, whose slots its sub-tile blended
+        uint32_t history = 0;
+        auto history_to_slots = [&](int k0, int places) {
+            uint32_t h = history << (32 - places);
+            h |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h, 0x128, 0xF, 0xF, true);   // row_ror:8, 4, 2, 1
+            h |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h, 0x124, 0xF, 0xF, true);
+            h |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h, 0x122, 0xF, 0xF, true);
+            h |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)h, 0x121, 0xF, 0xF, true);
+            uint32_t t = threadIdx.x;
+            asm volatile("" : "+v"(t));   // (what follows from it is formed here: kept through the trips it takes registers, and with them a wavefront)
+            const int i = (int)(t & 15u), st = (int)(t >> 4);
+            const int j0 = s.slot(st, k0 + i), j1 = s.slot(st, k0 + 16 + i);
+            if (h >> (31 - i) & 1u) atomicOr(&s_blend[batch & 1][j0 >> 1], 1u << (st + 16 * (j0 & 1)));
+            if (h >> (15 - i) & 1u) atomicOr(&s_blend[batch & 1][j1 >> 1], 1u << (st + 16 * (j1 & 1)));
+            history = 0;
+        };
+        auto trip = [&](uint32_t k) {
             const uint32_t word = next;
-            next = s.list[sub][(k / GROUP + 1) & (SLOTS / GROUP - 1)];
-            float alpha[GROUP], cr[GROUP], cg[GROUP], cb[GROUP];
+            float alpha[GROUP], cb[GROUP];
+            float4 r0[GROUP], r1[GROUP];
             uint64_t ok[GROUP];
 #pragma unroll
             for (int u = 0; u < GROUP; u++) {
                 const int j = (word >> (8 * u)) & 0xffu;
-                const float4 r0 = s.r0[j], r1 = s.r1[j];
-                cr[u] = r1.z;
-                cg[u] = r1.w;
+                r0[u] = s.r0[j];
+                r1[u] = s.r1[j];
                 cb[u] = s.r2[j].z;
-                const float dx = p.px - r0.x, dy = p.py - r0.y;
-                const float h = __builtin_fmaf(r0.w, dy, r0.z * dx);
-                const float t = exponent_of(__builtin_fmaf(dx, h, (r1.x * dy) * dy));
-                alpha[u] = fminf(cfg.alpha_max, r1.y * exp_c(t));
+                if (BITS) __builtin_amdgcn_sched_barrier(0);
+            }
+            next = s.list[sub][k / GROUP + 1];   // (one past the list's end is still in `s`, and not looked at)
+            if (BITS) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < GROUP; u++) {
+                const float dx = p.px - r0[u].x, dy = p.py - r0[u].y;
+                const float h = __builtin_fmaf(r0[u].w, dy, r0[u].z * dx);
+                const float t = exponent_of(__builtin_fmaf(dx, h, (r1[u].x * dy) * dy));
+                alpha[u] = fminf(cfg.alpha_max, r1[u].y * exp_c(t));
                 ok[u] = takes_part_mask(t) & ballot(alpha[u] >= cfg.alpha_min);
             }
 #pragma unroll
@@ -440,21 +514,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_re
                 // w is alpha T with the transmittance in front of this Gaussian: where it is blended, w > alpha_min
                 // (FS_SCORE_WEIGHT) or w > 0 (FS_SCORE_ALPHA, always) decides
                 uint64_t stop;
-                const uint64_t hb = blend_under_mask<BITS>(ok[u] & ~done, C0, C1, C2, T, lastk, cr[u], cg[u], cb[u], w, Tn, cfg.T_min,
-                                                           hit_above, k + u, stop);
+                const uint64_t hb = blend_under_mask<BITS, BLENDS>(ok[u] & ~done, C0, C1, C2, T, lastk, r1[u].z, r1[u].w, cb[u], w, Tn, cfg.T_min,
+                                                                   hit_above, (int)k + u, stop, history);
                 done |= stop;
                 if (BITS) {
-                    hits_lo = fs_write_lane((uint32_t)hb, (uint32_t)(k + u) & 63u, hits_lo);
-                    hits_hi = fs_write_lane((uint32_t)(hb >> 32), (uint32_t)(k + u) & 63u, hits_hi);
+                    hits_lo = fs_write_lane((uint32_t)hb, (k + u) & 63u, hits_lo);
+                    hits_hi = fs_write_lane((uint32_t)(hb >> 32), (k + u) & 63u, hits_hi);
                 }
             }
+        };
+        // places [k, end), or until all of the wavefront's pixels have terminated; returns where the next trip would start
+        auto trips = [&](int k, int end) {
+            do {
+                trip((uint32_t)k);
+                k += GROUP;
+                if (done == ~0ull) break;
+            } while (k < end);
+            return k;
+        };
+        if (BLENDS || BITS) {
+            // as many places at a time as the record's registers hold
+            constexpr int SPAN = BLENDS ? 32 : 64;
+            int k = 0;
+            while (k < longest && done != ~0ull) {
+                const int k0 = k;
+                k = trips(k0, min(longest, k0 + SPAN));
+                if (BLENDS) history_to_slots(k0, k - k0);
+                if (BITS && (SPAN == 64 || (k0 & 32))) hits_to_rows(k0 & ~63);
+            }
+            if (BITS && SPAN == 32 && k != 0 && ((k - 1) & 32) == 0) hits_to_rows((k - 1) & ~63);
+            batch++;
+        } else if (longest > 0 && done != ~0ull) {
+            trips(0, longest);
         }
-        if (BITS && k != 0) hits_to_rows((k - 1) & ~63);
         last = lastk >= 0 ? (uint32_t)(start + s.slot(sub, lastk) + 1) : last;
+    }
+    if (BLENDS) {
+        if (start >= total && total > 0) {   // (the last batch has been walked; a break above comes behind its words)
+            __syncthreads();
+            write_blends(start - BATCH);
+        }
+        if (threadIdx.x == 0) blends.tile_count[tile] = blended;
     }
     if (BITS) {
         if (pending_m > 0) {
-            __syncthreads();
+            if (!BLENDS) __syncthreads();
             write_bits(pending_m);
         }
         // (pairs the loop never reached -- every pixel had finished -- are blended nowhere and leave no row)
@@ -561,6 +665,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_re
 // its sums are formed behind the one of the v's.  Together, before and after, kernel durations in us: 500k Gaussians at 1600x1064 224
 // and 207, 3 M at 1920x1080 512 and 484, 100k at 980x545 74.5 and 70.5; with ABS 245 and 216 (500k, Compact Box), 170 and 152 (300k at
 // 1332x876).
+// PACKED: the walk goes over the pairs that the forward pass noted as blended, each with its exact sub-tiles (BlendRecord), instead of the
+// whole list with every sub-tile that a pair's support reaches.  That leaves out pairs behind opaque ones or beside all pixels, half of
+// the list up to the furthest blended pair at 3 M Gaussians and three quarters with a tail of large splats: fewer batches to stage, a tenth to two
+// fifths fewer trips.  Kernel durations, whole lists and PACKED, us: 500k Gaussians at 1600x1064 188 and 165, 3 M at 1920x1080 460 and 380,
+// 100k at 980x545 61 and 50, 12k at 509x337 33 and 28, 300k at 1332x876 140 and 131, 4k at 128x128 22.3 and 20.8.
+//
 // A trip of eight entries has about 415 vector instructions (without needles), which at these rates would take a SIMD 1 050
 // cycles, 2.55 for each; over the whole kernel one takes 4.1 to 4.8 at bench.py's 3 M (wide) and 500k Gaussians.  What the other two
 // fifths are spent on (the LDS adds and exchanges, their waits, wavefronts that end early) has not been taken apart.
@@ -568,12 +678,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_re
 // ABS adds the absolute positional gradient (used by FastGS for the split decision): per pixel the
 // magnitudes |dL/dmu_x|, |dL/dmu_y| of its own contribution, summed like the other values and stored
 // in the record's floats 9 and 10.
-template <bool ABS, bool SPARSE>
+template <bool ABS, bool SPARSE, bool PACKED>
 __global__ __launch_bounds__(256, 4) void k_render_bwd(
     CamDev cam, CfgDev cfg, const uint2* __restrict__ ranges, const uint32_t* __restrict__ tile_order,
     const uint32_t* __restrict__ gauss_sorted,
     const float4* __restrict__ splats, const float* __restrict__ final_T, const uint32_t* __restrict__ n_contrib,
-    const float* __restrict__ dL_dimage, float4* __restrict__ pair_grad, uint8_t* __restrict__ rec_valid)
+    const float* __restrict__ dL_dimage, float4* __restrict__ pair_grad, uint8_t* __restrict__ rec_valid, BlendRecord blends)
 {
     // (as many slots as four workgroups of a compute unit's 160 KB of LDS leave room for)
     constexpr int N = ABS ? 208 : 232, B = N - 1;
@@ -588,7 +698,8 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
     __shared__ Stage<true, N> s;
     __shared__ acc_t s_acc[N][NV];
     __shared__ __align__(16) float s_turn[4][SPAN][64];   // per wavefront: one value of SPAN entries, [entry][lane]
-    static_assert(sizeof(s) + sizeof(s_acc) + sizeof(s_turn) <= 40960, "four workgroups per compute unit");
+    __shared__ uint16_t s_pos[PACKED ? N : 1];            // the slots' positions in the tile's list
+    static_assert(sizeof(s) + sizeof(s_acc) + sizeof(s_turn) + sizeof(s_pos) <= 40960, "four workgroups per compute unit");
 
     const int tile = (int)tile_order[blockIdx.x];  // longest lists first
     const Pixel p = pixel_of_thread(cam, tile);
@@ -654,43 +765,63 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
     auto both = [&](float v) { return v + other(v); };   // the sum of the two lanes, in both
 
     s.clear(threadIdx.x);
-    // the furthest position any pixel of this lane's row of 16 reaches (by rotations of the row: every lane has it)
-    int row_last = last;
-    auto rotated_max = [&](auto ctrl) {
-        row_last = max(row_last, __builtin_amdgcn_update_dpp(0, row_last, decltype(ctrl)::value, 0xF, 0xF, true));
-    };
-    rotated_max(std::integral_constant<int, 0x121>{});
-    rotated_max(std::integral_constant<int, 0x122>{});
-    rotated_max(std::integral_constant<int, 0x124>{});
-    rotated_max(std::integral_constant<int, 0x128>{});
-    // (With exchanges through LDS, a maximum added up by LDS atomics and a second barrier for it: 22.9 us instead of 22.3 at 4k Gaussians,
-    // 54.6 and 53.8 at 100k, 174.6 and 172.6 at 500k.  s_turn is not in use before the first batch's barriers.)
-    int* const wave_last = reinterpret_cast<int*>(&s_turn[0][0][0]);
-    const int wave_max = wave_max_of_rows(row_last);
-    if (lane == 0) wave_last[wave] = wave_max;
-    __syncthreads();
-    const int4 furthest = *reinterpret_cast<const int4*>(wave_last);
-    const int total = max(max(furthest.x, furthest.y), max(furthest.z, furthest.w));  // entries at positions >= total are blended by no pixel of the tile
+    int row_last = last, total;
+    if (PACKED) {
+        total = blends.tile_count[tile];
+    } else {
+        // the furthest position any pixel of this lane's row of 16 reaches (by rotations of the row: every lane has it)
+        auto rotated_max = [&](auto ctrl) {
+            row_last = max(row_last, __builtin_amdgcn_update_dpp(0, row_last, decltype(ctrl)::value, 0xF, 0xF, true));
+        };
+        rotated_max(std::integral_constant<int, 0x121>{});
+        rotated_max(std::integral_constant<int, 0x122>{});
+        rotated_max(std::integral_constant<int, 0x124>{});
+        rotated_max(std::integral_constant<int, 0x128>{});
+        // (With exchanges through LDS, a maximum added up by LDS atomics and a second barrier for it: 22.9 us instead of 22.3 at 4k Gaussians,
+        // 54.6 and 53.8 at 100k, 174.6 and 172.6 at 500k.  s_turn is not in use before the first batch's barriers.)
+        int* const wave_last = reinterpret_cast<int*>(&s_turn[0][0][0]);
+        const int wave_max = wave_max_of_rows(row_last);
+        if (lane == 0) wave_last[wave] = wave_max;
+        __syncthreads();
+        const int4 furthest = *reinterpret_cast<const int4*>(wave_last);
+        total = max(max(furthest.x, furthest.y), max(furthest.z, furthest.w));  // entries at positions >= total are blended by no pixel of the tile
+    }
 
     // batches from the back: batch b covers positions [b*B, min(total,(b+1)*B))
     const int final_start = total > 0 ? ((total - 1) / B) * B : -1;
+    // PACKED: of the pairs that the forward pass blended, which come with their sub-tiles and positions
     auto entry = [&](int start) {   // the Gaussian of this thread's slot of the batch that starts there
         const int i = start + (int)threadIdx.x;
-        return start >= 0 && i < total && threadIdx.x < B ? gauss_sorted[range.x + i] : 0u;
+        const bool in = start >= 0 && i < total && threadIdx.x < B;
+        if constexpr (PACKED) return in ? blends.entries[range.x + i] : make_uint2(0u, 0u);
+        else return make_uint2(in ? gauss_sorted[range.x + i] : 0u, 0u);
     };
-    uint32_t g_next = entry(final_start);
+    uint2 next = entry(final_start);
     for (int start = final_start; start >= 0; start -= B) {
         const int m = min(B, total - start);
-        __syncthreads();  // the previous batch's flush has read s_acc / s.r2
+        if (start != final_start) __syncthreads();  // the previous batch's flush has read s_acc / s.r2
         if ((int)threadIdx.x < N) {
 #pragma unroll
             for (int k = 0; k < NV; k++) s_acc[threadIdx.x][k] = (acc_t)0;
         }
         // (entries behind a row's furthest one are left out of its list)
-        const int mine = stage_batch<2, true>(s, nullptr, cam, tile, splats, g_next, m, row_last - start);
-        g_next = entry(start - B);   // (its latency passes during the walk)
+        if (PACKED && (int)threadIdx.x < N) s_pos[threadIdx.x] = (uint16_t)next.y;
+        const int mine = stage_batch<2, true, PACKED>(s, nullptr, cam, tile, splats, next.x, m, row_last - start, next.y >> 16);
+        next = entry(start - B);   // (its latency passes during the walk)
         const int longest = wave_max_of_rows(mine);
-        const uint32_t last_here = (uint32_t)max(last - start, 0);   // slots below this one hold entries this pixel blended (or examined)
+        uint32_t last_here = (uint32_t)max(last - start, 0);   // slots below this one hold entries this pixel blended (or examined)
+        if (PACKED) {
+            // (positions ascend with the slots)
+            last_here = (uint32_t)m;
+            if (ballot((int)s_pos[m - 1] >= last) != 0) {
+                last_here = 0;
+#pragma unroll
+                for (uint32_t step = 128; step > 0; step >>= 1) {
+                    const uint32_t to = last_here + step;
+                    last_here = to <= (uint32_t)m && (int)s_pos[min(to, (uint32_t)m) - 1] < last ? to : last_here;
+                }
+            }
+        }
         uint64_t acted = 0;   // lanes that blend any of the trip's entries
         // the records of a word's four slots
         float4 r0[GROUP], r1[GROUP];
@@ -901,10 +1032,23 @@ __global__ __launch_bounds__(256, 4) void k_render_bwd(
             }
         }
     }
-    // pairs behind the furthest blended Gaussian of the tile received nothing (SPARSE: their flags stay 0)
+    // pairs behind the furthest blended Gaussian of the tile received nothing (SPARSE: their flags stay 0); PACKED: so did those in between
     if (!SPARSE) {
-        for (uint32_t pos = range.x + total + threadIdx.x; pos < range.y; pos += 256) {
-            const float4 r2 = splats[(size_t)gauss_sorted[pos] * (SPLAT_REC / 4) + 2];
+        uint32_t* const in_record = reinterpret_cast<uint32_t*>(&s_turn[0][0][0]);   // a bit for each place on the tile's list (the walks are over)
+        const uint32_t n = range.y - range.x;
+        if (PACKED) {
+            static_assert(sizeof(s_turn) * 8 >= 65536, "a bit for every place that a record names");
+            for (uint32_t w = threadIdx.x; w < (n + 31) / 32; w += 256) in_record[w] = 0u;
+            __syncthreads();
+            for (int i = (int)threadIdx.x; i < total; i += 256) {
+                const uint32_t at = blends.entries[range.x + i].y & 0xffffu;
+                atomicOr(&in_record[at / 32], 1u << (at & 31));
+            }
+            __syncthreads();
+        }
+        for (uint32_t at = (PACKED ? 0u : (uint32_t)total) + threadIdx.x; at < n; at += 256) {
+            if (PACKED && (in_record[at / 32] >> (at & 31) & 1u)) continue;
+            const float4 r2 = splats[(size_t)gauss_sorted[range.x + at] * (SPLAT_REC / 4) + 2];
             const uint32_t r01 = __float_as_uint(r2.z), r23 = __float_as_uint(r2.w);
             const uint32_t x0 = r01 & 0xffffu, y0 = r01 >> 16, x1 = r23 & 0xffffu;
             const uint32_t idx = (__float_as_uint(r2.y) & ~NEEDLE) + ((uint32_t)(tile / cam.tiles_x) - y0) * (x1 - x0) +
@@ -1372,43 +1516,37 @@ __global__ __launch_bounds__(256) void k_record_rows(int tiles, const int32_t* _
 
 hipError_t launch_render_fwd(hipStream_t st, const CamDev& cam, const CfgDev& cfg, const uint32_t* ranges,
                              const uint32_t* tile_order, const uint32_t* gauss_sorted, const float* splats, float* image, float* final_T,
-                             uint32_t* n_contrib, const ScoreRecord& record)
+                             uint32_t* n_contrib, const ScoreRecord& record, const BlendRecord& blends)
 {
     const int tiles = cam.tiles_x * cam.tiles_y;
     if (tiles == 0) return hipSuccess;
-    const ScoreRecord none = {nullptr, nullptr, nullptr};
-    if (record.rows)
-        hipLaunchKernelGGL((k_render_fwd<false, true>), dim3(tiles), dim3(256), 0, st, cam, cfg,
-                           reinterpret_cast<const uint2*>(ranges), tile_order, gauss_sorted,
-                           reinterpret_cast<const float4*>(splats), image, final_T, n_contrib, nullptr, 0.f, nullptr,
-                           nullptr, nullptr, record);
-    else
-        hipLaunchKernelGGL((k_render_fwd<false, false>), dim3(tiles), dim3(256), 0, st, cam, cfg,
-                           reinterpret_cast<const uint2*>(ranges), tile_order, gauss_sorted,
-                           reinterpret_cast<const float4*>(splats), image, final_T, n_contrib, nullptr, 0.f, nullptr,
-                           nullptr, nullptr, none);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(tiles), dim3(256), 0, st, cam, cfg, reinterpret_cast<const uint2*>(ranges), tile_order, gauss_sorted,
+                           reinterpret_cast<const float4*>(splats), image, final_T, n_contrib, nullptr, 0.f, nullptr, nullptr, nullptr, record, blends);
+    };
+    if (record.rows && blends.entries) launch(k_render_fwd<false, true, true>);
+    else if (record.rows) launch(k_render_fwd<false, true, false>);
+    else if (blends.entries) launch(k_render_fwd<false, false, true>);
+    else launch(k_render_fwd<false, false, false>);
     return hipGetLastError();
 }
 
 hipError_t launch_render_fwd_fused(hipStream_t st, const CamDev& cam, const CfgDev& cfg, const uint32_t* ranges,
                                    const uint32_t* tile_order, const uint32_t* gauss_sorted, const float* splats,
                                    float* image, float* final_T, uint32_t* n_contrib, const float* target, float* dL,
-                                   float* err, double* tile_partial, const ScoreRecord& record)
+                                   float* err, double* tile_partial, const ScoreRecord& record, const BlendRecord& blends)
 {
     const int tiles = cam.tiles_x * cam.tiles_y;
     if (tiles == 0) return hipSuccess;
     const float scale = 1.0f / (float)((int64_t)3 * cam.width * cam.height);
-    const ScoreRecord none = {nullptr, nullptr, nullptr};
-    if (record.rows)
-        hipLaunchKernelGGL((k_render_fwd<true, true>), dim3(tiles), dim3(256), 0, st, cam, cfg,
-                           reinterpret_cast<const uint2*>(ranges), tile_order, gauss_sorted,
-                           reinterpret_cast<const float4*>(splats), image, final_T, n_contrib, target, scale, dL, err,
-                           tile_partial, record);
-    else
-        hipLaunchKernelGGL((k_render_fwd<true, false>), dim3(tiles), dim3(256), 0, st, cam, cfg,
-                           reinterpret_cast<const uint2*>(ranges), tile_order, gauss_sorted,
-                           reinterpret_cast<const float4*>(splats), image, final_T, n_contrib, target, scale, dL, err,
-                           tile_partial, none);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(tiles), dim3(256), 0, st, cam, cfg, reinterpret_cast<const uint2*>(ranges), tile_order, gauss_sorted,
+                           reinterpret_cast<const float4*>(splats), image, final_T, n_contrib, target, scale, dL, err, tile_partial, record, blends);
+    };
+    if (record.rows && blends.entries) launch(k_render_fwd<true, true, true>);
+    else if (record.rows) launch(k_render_fwd<true, true, false>);
+    else if (blends.entries) launch(k_render_fwd<true, false, true>);
+    else launch(k_render_fwd<true, false, false>);
     return hipGetLastError();
 }
 
@@ -1456,32 +1594,28 @@ hipError_t launch_record_rows(hipStream_t st, int tiles, const ScoreRecord& reco
 hipError_t launch_render_bwd(hipStream_t st, const CamDev& cam, const CfgDev& cfg, const uint32_t* ranges,
                              const uint32_t* tile_order, const uint32_t* gauss_sorted, const float* splats, const float* final_T,
                              const uint32_t* n_contrib, const float* dL_dimage, float* pair_grad, uint8_t* rec_valid,
-                             bool abs_grad, bool per_splat)
+                             bool abs_grad, bool per_splat, const BlendRecord& blends)
 {
     const int tiles = cam.tiles_x * cam.tiles_y;
     if (tiles == 0) return hipSuccess;
     const uint2* r2 = reinterpret_cast<const uint2*>(ranges);
     const float4* sp = reinterpret_cast<const float4*>(splats);
     float4* pg = reinterpret_cast<float4*>(pair_grad);
-    const dim3 grid(tiles), block(256);
+    auto launch = [&](auto kernel, auto... more) {
+        hipLaunchKernelGGL(kernel, dim3(tiles), dim3(256), 0, st, cam, cfg, r2, tile_order, gauss_sorted, sp, final_T, n_contrib, dL_dimage, pg, rec_valid,
+                           more...);
+    };
     // rec_valid: null = dense records, else the flags of the sparse records
-#define FS_BWD(KERNEL, ABS, SPARSE)                                                                                  \
-    hipLaunchKernelGGL((KERNEL<ABS, SPARSE>), grid, block, 0, st, cam, cfg, r2, tile_order, gauss_sorted, sp, final_T, \
-                       n_contrib, dL_dimage, pg, rec_valid)
-#define FS_BWD_MODE(KERNEL)                         \
-    do {                                            \
-        if (abs_grad) {                             \
-            if (rec_valid) FS_BWD(KERNEL, true, true);   \
-            else FS_BWD(KERNEL, true, false);       \
-        } else {                                    \
-            if (rec_valid) FS_BWD(KERNEL, false, true);  \
-            else FS_BWD(KERNEL, false, false);      \
-        }                                           \
-    } while (0)
-    if (per_splat) FS_BWD_MODE(k_render_bwd_splat);
-    else FS_BWD_MODE(k_render_bwd);
-#undef FS_BWD_MODE
-#undef FS_BWD
+    auto choose = [&](auto abs, auto sparse) {
+        constexpr bool ABS = decltype(abs)::value, SPARSE = decltype(sparse)::value;
+        if (per_splat) launch(k_render_bwd_splat<ABS, SPARSE>);
+        else if (blends.entries) launch(k_render_bwd<ABS, SPARSE, true>, blends);
+        else launch(k_render_bwd<ABS, SPARSE, false>, blends);
+    };
+    if (abs_grad && rec_valid) choose(std::true_type{}, std::true_type{});
+    else if (abs_grad) choose(std::true_type{}, std::false_type{});
+    else if (rec_valid) choose(std::false_type{}, std::true_type{});
+    else choose(std::false_type{}, std::false_type{});
     return hipGetLastError();
 }
 

@@ -105,7 +105,7 @@ hipError_t launch_tile_sorts(hipStream_t, int, int variants, uint32_t, const uin
     return hipSuccess;
 }
 hipError_t launch_render_fwd(hipStream_t, const CamDev&, const CfgDev&, const uint32_t*, const uint32_t*, const uint32_t*, const float*,
-                             float*, float*, uint32_t*, const ScoreRecord&)
+                             float*, float*, uint32_t*, const ScoreRecord&, const BlendRecord&)
 {
     return hipSuccess;
 }
@@ -120,7 +120,7 @@ hipError_t launch_photo_loss(hipStream_t, const float*, const float*, int, int, 
 
 // every pair's flag is set, as where every pair has received something
 hipError_t launch_render_bwd(hipStream_t, const CamDev&, const CfgDev&, const uint32_t*, const uint32_t*, const uint32_t*, const float*,
-                             const float*, const uint32_t*, const float*, float*, uint8_t* rec_valid, bool, bool)
+                             const float*, const uint32_t*, const float*, float*, uint8_t* rec_valid, bool, bool, const BlendRecord&)
 {
     if (!rec_valid) return hipSuccess;
     stub_stale_flags = 0;

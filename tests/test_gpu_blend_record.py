@@ -1,0 +1,116 @@
+"""The forward pass's record of blended pairs, which the backward pass walks instead of the whole lists: gradients with it and
+without.  The terms are the same and so is the order of all single-precision sums; a Gaussian's sub-tile sums meet in double
+precision, whose order is free and shows only where their exponents span more than 29 bits: 1e-6 of the largest gradient."""
+import numpy as np
+import pytest
+
+from paper_2511_04283_amd import scenes
+
+pytestmark = pytest.mark.gpu
+
+
+def both_ways(sc, cam, want_abs, records, compact=0, shorten=None):
+    """Gradients from a context with a record and one without; n_contrib as the pixels have it, or `shorten`ed."""
+    import torch
+    from paper_2511_04283_amd import binding as B
+    fcam, out, rows = B.make_camera(cam), [], None
+    rng = np.random.default_rng(11)
+    target = torch.from_numpy(rng.uniform(size=(3, cam.height, cam.width)).astype(np.float32)).cuda()
+    weights = torch.from_numpy(rng.normal(size=(3, cam.height, cam.width)).astype(np.float32)).cuda()
+    config = B.default_config()
+    config.compact_box = compact
+    for with_record in (True, False):
+        ctx = B.Context("cuda:0", config)
+        ctx.fs_set_record_mode({"auto": B.FS_RECORDS_AUTO, "dense": B.FS_RECORDS_DENSE, "sparse": B.FS_RECORDS_SPARSE}[records])
+        g = B.Gaussians.from_scene(sc, ctx.device)
+        proj = ctx.fs_preprocess(g, fcam)
+        bins = ctx.fs_bin_sort(proj, fcam)
+        image, T, nc = (torch.empty(s, device="cuda", dtype=d) for s, d in
+                        (((3, cam.height, cam.width), torch.float32), ((cam.height, cam.width), torch.float32), ((cam.height, cam.width), torch.int32)))
+        dL = torch.empty_like(image) if with_record else None
+        loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+        ctx.fs_render_fwd_loss(proj, bins, fcam, target, image, T, nc, dL, loss)   # (without dL no backward pass is announced)
+        if shorten is not None:
+            nc = shorten(nc)
+        gr = ctx.fs_render_bwd(g, fcam, proj, bins, T, nc, weights, want_2d=True, want_abs=want_abs)
+        out.append({k: v.cpu().numpy() for k, v in gr.items()})
+        out[-1]["forward"] = np.concatenate([image.cpu().numpy().ravel(), T.cpu().numpy().ravel()])
+        if rows is None:
+            rows = nc.cpu().numpy()
+        else:
+            assert np.array_equal(rows, nc.cpu().numpy())
+        ctx.close()
+    return out, rows
+
+
+def same(out):
+    a, b = out
+    assert np.array_equal(a.pop("forward"), b.pop("forward"))
+    for k in b:
+        assert np.abs(b[k]).max() > 0, k
+        assert np.abs(a[k] - b[k]).max() <= 1e-6 * np.abs(b[k]).max(), k
+
+
+@pytest.mark.parametrize("records", ["dense", "sparse"])
+@pytest.mark.parametrize("want_abs", [False, True])
+@pytest.mark.parametrize("n", [1, 4, 5, 31, 32, 33, 64, 207, 208, 231, 232, 255, 256, 463, 511])
+def test_every_pair_blended(n, want_abs, records):
+    """Lists whose blended pairs are all or (every third splat too faint to be blended) two thirds of them: 32 places leave the forward
+    kernel's registers at a time, 207 or 231 pairs are staged at a time by the backward kernel."""
+    sc = scenes.tiny_scene(900 + n, n, 29, 13, sh_degree=0, log_scale=(-0.5, 0.2), spread=0.6)
+    sc.opacities[:] = np.random.default_rng(n).uniform(0.006, 0.012, n)
+    out, nc = both_ways(sc, sc.cameras[0], want_abs, records)
+    assert nc.max() >= 0.9 * n
+    same(out)
+    sc.opacities[np.arange(n) % 3 == 1] = 0.003
+    same(both_ways(sc, sc.cameras[0], want_abs, records)[0])
+
+
+@pytest.mark.parametrize("compact", [0, 1])
+@pytest.mark.parametrize("records", ["auto", "dense", "sparse"])
+@pytest.mark.parametrize("n,width,height,scale", [(37, 211, 133, -3.5), (900, 61, 43, -2.5), (3000, 150, 83, -2.8), (20000, 203, 117, -3.2)])
+def test_pairs_behind_opaque_ones_and_beside_the_support(n, width, height, scale, records, compact):
+    """Tiles without pairs, pixels that stop at different places, pairs that no pixel blends, needles, ragged edges, and opacities that
+    stop all pixels within the first staged entries."""
+    sc = scenes.tiny_scene(41 + n, n, width, height, sh_degree=1, log_scale=(scale, 0.7), spread=1.0)
+    sc.scales[::7] *= np.array([30.0, 0.05, 0.05], np.float32)
+    same(both_ways(sc, sc.cameras[0], True, records, compact)[0])
+    sc.opacities[:] = 0.99
+    same(both_ways(sc, sc.cameras[0], False, records, compact)[0])
+
+
+@pytest.mark.parametrize("records", ["dense", "sparse"])
+def test_pixels_cut_short(records):
+    """n_contrib lower than the forward pass left it (none at all for some pixels): the pairs behind it take no part, whatever the record
+    says."""
+    import torch
+    sc = scenes.tiny_scene(5, 2500, 97, 75, sh_degree=0, log_scale=(-2.6, 0.6), spread=1.0)
+    share = torch.from_numpy(np.random.default_rng(2).choice([0.0, 0.3, 0.7, 1.0], (75, 97)).astype(np.float32)).cuda()
+    out, nc = both_ways(sc, sc.cameras[0], False, records, shorten=lambda nc: (nc * share).to(torch.int32))
+    same(out)
+
+
+def test_a_record_belongs_to_its_ordering():
+    """A backward pass behind a second ordering does not look at the record of the first."""
+    import torch
+    from paper_2511_04283_amd import binding as B
+    sc = scenes.tiny_scene(8, 1500, 97, 75, sh_degree=0, log_scale=(-2.6, 0.6), spread=1.0)
+    cam, ctx = B.make_camera(sc.cameras[0]), B.Context("cuda:0")
+    g = B.Gaussians.from_scene(sc, ctx.device)
+    target, weights = torch.rand((3, 75, 97), device="cuda"), torch.randn((3, 75, 97), device="cuda")
+    proj = ctx.fs_preprocess(g, cam)
+    bins = ctx.fs_bin_sort(proj, cam)
+    image, T, nc = ctx.fs_render_fwd(proj, bins, cam)
+    want = ctx.fs_render_bwd(g, cam, proj, bins, T, nc, weights, want_2d=True)
+    other = scenes.tiny_scene(9, 1500, 97, 75, sh_degree=0, log_scale=(-2.6, 0.6), spread=1.0)
+    g2 = B.Gaussians.from_scene(other, ctx.device)
+    proj2 = ctx.fs_preprocess(g2, cam)
+    bins2 = ctx.fs_bin_sort(proj2, cam)
+    ctx.fs_render_fwd_loss(proj2, bins2, cam, target, torch.empty_like(image), torch.empty_like(T), torch.empty_like(nc), torch.empty_like(image),
+                           torch.zeros(1, dtype=torch.float64, device="cuda"))
+    proj = ctx.fs_preprocess(g, cam)
+    bins = ctx.fs_bin_sort(proj, cam)
+    got = ctx.fs_render_bwd(g, cam, proj, bins, T, nc, weights, want_2d=True)
+    for k in want:
+        assert (got[k] - want[k]).abs().max() <= 1e-6 * want[k].abs().max(), k
+    ctx.close()
