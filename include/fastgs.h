@@ -267,7 +267,7 @@ int fs_set_backward_mode(fs_ctx *ctx, int32_t mode);
  *   opaque scenes whose lists are long and mostly end behind the pixels' last blended Gaussian -- and costs a few
  *   microseconds otherwise (one more scattered byte per record, one more dependent load per chunk of records).
  * FS_RECORDS_AUTO (default): sparse when the forward pass noted its blended pairs (fs_render_fwd_loss with dL_dimage,
- *   fs_train_step) or the tile lists hold 320 pairs or more on average. */
+ *   fs_train_step), with the Compact Box, or when the tile lists hold 320 pairs or more on average. */
 enum { FS_RECORDS_AUTO = 0, FS_RECORDS_DENSE = 1, FS_RECORDS_SPARSE = 2 };
 int fs_set_record_mode(fs_ctx *ctx, int32_t mode);
 

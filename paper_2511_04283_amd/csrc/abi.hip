@@ -235,11 +235,12 @@ bool bins_stale(const fs_ctx* ctx, const fs_bins* bins) { return bins->generatio
 // Sparse records pay where the lists are long (most of their pairs receive nothing), and where the backward pass walks the blended
 // pairs only: dense ones make it look for the others in a second pass over the list.  k_render_bwd with k_preprocess_bwd, dense and
 // sparse, from a forward pass's record, us: 12k Gaussians at 509x337 46.9 and 46.3, 100k at 980x545 74.5 and 71.8, 300k at 1332x876
-// 200.9 and 200.5, 500k at 1600x1064 with the Compact Box 406 and 395, without 281 and 248.
+// 200.9 and 200.5, 500k at 1600x1064 with the Compact Box 406 and 395, without 281 and 248.  With the Compact Box dense ones have to be
+// cleared first, for the candidates that are no pairs.
 bool sparse_records(const fs_ctx* ctx, const fs_bins* bins, int tiles, bool from_blends)
 {
     return ctx->record_mode == FS_RECORDS_SPARSE ||
-           (ctx->record_mode == FS_RECORDS_AUTO && (from_blends || bins->num_pairs >= (int64_t)320 * tiles));
+           (ctx->record_mode == FS_RECORDS_AUTO && (from_blends || ctx->cfg.compact_box || bins->num_pairs >= (int64_t)320 * tiles));
 }
 
 // The backward pass's per-pair records and, where they are sparse, one flag per record place, all zeros here (a fresh or
@@ -248,7 +249,14 @@ int record_buffers(fs_ctx* ctx, const fs_bins* bins, bool sparse)
 {
     FS_TRY(ensure(ctx, ctx->pair_grad, (size_t)(bins->num_records ? bins->num_records : 1) * PAIR_REC * sizeof(float),
                   "pair gradients"));
-    if (!sparse) return FS_OK;
+    if (!sparse) {
+        // (candidates that are no pairs: nothing else writes their records.  The placement cleared them on its way, whether or not
+        // a dense backward pass followed, and took 30 us instead of 20.5 at 500k Gaussians and 1600x1064, 19 instead of 16 at 300k and
+        // 1332x876, 8.2 instead of 6.5 at 100k and 980x545.)
+        if (ctx->cfg.compact_box)
+            FS_HIP(launch_fill_u32(ctx->stream, static_cast<uint32_t*>(ctx->pair_grad.ptr), 0u, bins->num_records * PAIR_REC), "k_fill_u32");
+        return FS_OK;
+    }
     const size_t flags = ((size_t)(bins->num_records ? bins->num_records : 1) + 3) / 4 * 4;
     if (flags > ctx->rec_valid.cap) ctx->rec_valid_zeroed = 0;   // (also where growing fails: a later array may have the old size)
     FS_TRY(ensure(ctx, ctx->rec_valid, flags, "record flags"));
@@ -524,24 +532,20 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
     // the sort launches the previous call's lists would have chosen: otherwise the GPU idles for the whole round trip (wait, wake-up, launch) once per
     // call.  The kernels write nothing beyond the capacities they are given; what the totals then say was not covered
     // (a longer list's sort variant, or buffers that have to grow first) is enqueued afterwards.
-    const uint32_t* recs_p = cb ? static_cast<const uint32_t*>(ctx->rec_offsets.ptr) : static_cast<const uint32_t*>(ctx->offsets.ptr);
     fs_projected none = {};
-    uint64_t cap_pairs = 0, cap_recs = 0;
+    uint64_t cap_pairs = 0;
     int spec_variants = 0;
     if (bucketed && ctx->spec_set != 0 && n > 0) {
         cap_pairs = ctx->keys[0].cap / sizeof(uint64_t);
         if (ctx->keys[1].cap / sizeof(uint64_t) < cap_pairs) cap_pairs = ctx->keys[1].cap / sizeof(uint64_t);
         if (ctx->vals[0].cap / sizeof(uint32_t) < cap_pairs) cap_pairs = ctx->vals[0].cap / sizeof(uint32_t);
         if (cap_pairs > 0x7fffffffull) cap_pairs = 0x7fffffffull;
-        cap_recs = cb ? ctx->pair_grad.cap / (PAIR_REC * sizeof(float)) : 0;
-        if (cap_recs > 0x7fffffffull) cap_recs = 0x7fffffffull;
-        if (cap_pairs > 0 && (!cb || cap_recs > 0)) {
+        if (cap_pairs > 0) {
             ProfScope prof(ctx, FS_K_ORDER);
             spec_variants = ctx->spec_set;
             uint64_t* const words = static_cast<uint64_t*>(ctx->keys[bands ? 0 : 1].ptr);
-            FS_HIP(launch_tile_scatter(st, n, proj ? *proj : none, cf, recs_p, cd.tiles_x, tiles, (uint32_t)cap_pairs,
-                                       (uint32_t)cap_recs, reinterpret_cast<const uint2*>(ranges_p), tcount_p,
-                                       words, static_cast<float*>(ctx->pair_grad.ptr), places),
+            FS_HIP(launch_tile_scatter(st, n, proj ? *proj : none, cf, cd.tiles_x, tiles, (uint32_t)cap_pairs,
+                                       reinterpret_cast<const uint2*>(ranges_p), tcount_p, words, places),
                    "k_tile_pairs (placement)");
             FS_HIP(launch_tile_sorts(st, tiles, spec_variants | split, (uint32_t)cap_pairs, reinterpret_cast<const uint2*>(ranges_p),
                                      order_p, static_cast<uint64_t*>(ctx->keys[1].ptr),
@@ -568,8 +572,7 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
     ctx->longest_list = (int64_t)max_len;
     const bool lds_sort = bucketed && max_len <= (uint64_t)TILE_SORT_HUGE;
     // did what was enqueued ahead cover this call?  (growing a buffer below waits for the stream first)
-    const bool spec_fits = spec_variants != 0 && P <= cap_pairs && (!cb || NR <= cap_recs);
-    if (cb) FS_TRY(ensure(ctx, ctx->pair_grad, (size_t)(NR ? NR : 1) * PAIR_REC * sizeof(float), "pair gradients"));
+    const bool spec_fits = spec_variants != 0 && P <= cap_pairs;
 
     const int64_t nb = radix_num_blocks((int64_t)P);
     for (int k = 0; k < 2; k++) {
@@ -592,9 +595,8 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
         if (!spec_fits || variants) {
             ProfScope prof(ctx, FS_K_ORDER);
             if (!spec_fits) {
-                FS_HIP(launch_tile_scatter(st, n, proj ? *proj : none, cf, recs_p, cd.tiles_x, tiles, (uint32_t)P,
-                                           (uint32_t)NR, reinterpret_cast<const uint2*>(ranges_p), tcount_p, keys[bands ? 0 : 1],
-                                           static_cast<float*>(ctx->pair_grad.ptr), places),
+                FS_HIP(launch_tile_scatter(st, n, proj ? *proj : none, cf, cd.tiles_x, tiles, (uint32_t)P,
+                                           reinterpret_cast<const uint2*>(ranges_p), tcount_p, keys[bands ? 0 : 1], places),
                        "k_tile_pairs (placement)");
             }
             FS_HIP(launch_tile_sorts(st, tiles, variants | (spec_fits ? 0 : split), (uint32_t)P, reinterpret_cast<const uint2*>(ranges_p), order_p,
@@ -612,8 +614,7 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
                 if (cb)
                     FS_HIP(launch_emit_pairs_cb(st, n, *proj, cf, static_cast<const uint32_t*>(ctx->offsets.ptr),
                                                 static_cast<const uint32_t*>(ctx->rec_offsets.ptr), cd.tiles_x, (int64_t)P,
-                                                keys[0], vals[0], static_cast<float*>(ctx->splats.ptr),
-                                                static_cast<float*>(ctx->pair_grad.ptr)),
+                                                keys[0], vals[0], static_cast<float*>(ctx->splats.ptr)),
                            "k_emit_pairs_cb");
                 else
                     FS_HIP(launch_emit_pairs(st, n, *proj, cf, static_cast<const uint32_t*>(ctx->offsets.ptr), cd.tiles_x,
@@ -785,8 +786,7 @@ int fs_render_bwd(fs_ctx* ctx, const fs_gaussians* g, const fs_camera* cam, cons
     hipStream_t st = ctx->stream;
     if (bins->num_pairs > 0 && (!bins->record_offsets || !bins->splats || bins->num_records < bins->num_pairs))
         return fail(ctx, FS_EINVAL, "fs_render_bwd: bins without record_offsets / splats");
-    // (the records, their places and -- with the Compact Box -- the zeroed records of the candidate tiles that are
-    // no pairs all live in this ctx and belong to its latest fs_bin_sort)
+    // (the records and their places live in this ctx and belong to its latest fs_bin_sort)
     if (bins_stale(ctx, bins)) return fail(ctx, FS_EINVAL, "fs_render_bwd: bins do not come from this context's latest fs_bin_sort");
     const BlendRecord blends = ctx->per_splat_bwd ? BlendRecord{nullptr, nullptr} : blends_of(ctx, bins, cd);
     const bool sparse = sparse_records(ctx, bins, cd.tiles_x * cd.tiles_y, blends.entries != nullptr);

@@ -202,9 +202,8 @@ __global__ __launch_bounds__(256) void k_rect_area(int64_t n, const ushort4* __r
 }
 
 // Compact Box emission.  Same wave-cooperative walk as k_emit_pairs, but over the candidates (all tiles
-// of each box): the lane that takes a candidate runs the ellipse-tile test; a hit becomes a key at
-// offsets[owner] + (hits of the same Gaussian before it, in row-major order), a miss gets its gradient
-// record zeroed.  Hits of one Gaussian before a candidate = those of earlier rounds (kept by the owner
+// each box): the lane that takes a candidate runs the ellipse-tile test; a hit becomes a key at
+// offsets[owner] + (hits of the same Gaussian before it, in row-major order).  Hits of one Gaussian before a candidate = those of earlier rounds (kept by the owner
 // lane in `emitted`) + those on lower lanes of this round (one ballot, masked to the owner's lanes).
 __global__ __launch_bounds__(256) void k_emit_pairs_cb(int64_t n, const ushort4* __restrict__ rect,
                                                        const float* __restrict__ depth,
@@ -215,7 +214,7 @@ __global__ __launch_bounds__(256) void k_emit_pairs_cb(int64_t n, const ushort4*
                                                        const uint32_t* __restrict__ rec_offsets, int tiles_x,
                                                        uint32_t P, uint64_t* __restrict__ keys,
                                                        uint32_t* __restrict__ vals,
-                                                       float4* __restrict__ splats, float4* __restrict__ pair_grad)
+                                                       float4* __restrict__ splats)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool valid = i < n;
@@ -255,7 +254,6 @@ __global__ __launch_bounds__(256) void k_emit_pairs_cb(int64_t n, const ushort4*
         const uint32_t oxy = (uint32_t)__shfl((int)rect_xy, (int)s, 64);
         const uint32_t od = (uint32_t)__shfl((int)dbits, (int)s, 64);
         const uint32_t ooff = (uint32_t)__shfl((int)off, (int)s, 64);
-        const uint32_t oroff = (uint32_t)__shfl((int)roff, (int)s, 64);
         const uint32_t oem = (uint32_t)__shfl((int)emitted, (int)s, 64);
         const float omx = __shfl(mx, (int)s, 64), omy = __shfl(my, (int)s, 64);
         const float oA = __shfl(A, (int)s, 64), oB = __shfl(B, (int)s, 64), oC = __shfl(C, (int)s, 64);
@@ -274,10 +272,6 @@ __global__ __launch_bounds__(256) void k_emit_pairs_cb(int64_t n, const ushort4*
                 keys[o] = ((uint64_t)(ty * (uint32_t)tiles_x + tx) << 32) | od;
                 vals[o] = (uint32_t)(i - lane + s);
             }
-        } else if (live) {
-            float4* g = pair_grad + ((size_t)oroff + k) * (PAIR_REC / 4);
-            const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-            g[0] = z; g[1] = z; g[2] = z;
         }
         // each owner adds the hits of its own run in this round
         const uint32_t a0 = excl > j0 ? excl - j0 : 0u;                      // run of this lane's Gaussian: [a0, a1)
@@ -314,10 +308,8 @@ __device__ __forceinline__ uint2 band_bounds(const uint2* __restrict__ ranges, i
 // Steps (1) and (2) walk the candidate tiles of 64 consecutive Gaussians per wavefront the way k_emit_pairs
 // does.  SCATTER = false: count[tile] += 1 per pair.  SCATTER = true: slot = first[tile] + counter[tile]++
 // (k_tile_layout has turned each copy's counter into that copy's start within the tile's segment, or those of a band into one),
-// bucket[slot] = depth_bits << 32 | index; also, with
-// the Compact Box, zeroes the gradient records of the candidates that are no pairs.  In this mode `P` and `rec_limit`
-// are the numbers of words / records the buffers hold: nothing is written at or beyond them (the kernel may be
-// enqueued before the host has seen the real totals).
+// bucket[slot] = depth_bits << 32 | index.  In this mode `P` is the number of words the buffers hold: nothing is written at or
+// beyond it (the kernel may be enqueued before the host has seen the real totals).
 //
 // Step (1) also hands every Gaussian the place of its backward records (one per tile of its rectangle), counted from the
 // first record of its workgroup: inside a workgroup the wavefronts, their rounds and the 64 Gaussians of a round follow each
@@ -340,12 +332,10 @@ template <bool CB, bool SCATTER, bool BANDS>
 __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, const ushort4* __restrict__ rect,
                                                     const float* __restrict__ depth,
                                                     const float2* __restrict__ mean2d,
-                                                    const float4* __restrict__ conic_opacity, CfgDev cfg,
-                                                    const uint32_t* __restrict__ rec_offsets, int tiles_x,
+                                                    const float4* __restrict__ conic_opacity, CfgDev cfg, int tiles_x,
                                                     int num_tiles, uint32_t* __restrict__ tile_counter,
-                                                    const uint2* __restrict__ ranges, uint32_t P, uint32_t rec_limit,
-                                                    uint64_t* __restrict__ bucket,
-                                                    float4* __restrict__ pair_grad, RecAlloc ra, BandPlaces places)
+                                                    const uint2* __restrict__ ranges, uint32_t P,
+                                                    uint64_t* __restrict__ bucket, RecAlloc ra, BandPlaces places)
 {
     static_assert(SCATTER || !BANDS, "a variant of the placement");
     extern __shared__ uint32_t s_tile[];   // this workgroup's counter per tile (BANDS: per band)
@@ -406,15 +396,13 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
         for (int w = 0; w < (int)(threadIdx.x >> 6); w++) rec_next += s_wave_recs[w];
     }
     // (every wavefront of the workgroup walks its own 64 Gaussians per round; no barrier inside the rounds)
-    // (the next round's rectangle, record place and depth are requested before this round's candidates are walked)
+    // (the next round's rectangle and depth are requested before this round's candidates are walked)
     const int64_t round_stride = (int64_t)gridDim.x * TILE_PAIR_THREADS;
     ushort4 r_next = i_first < n ? rect[i_first] : make_ushort4(0, 0, 0, 0);
-    uint32_t roff_next = (SCATTER && CB && i_first < n) ? rec_offsets[i_first] : 0u;
     uint32_t dbits_next = (SCATTER && i_first < n) ? __float_as_uint(depth[i_first]) : 0u;
     for (int64_t i = i_first; i - lane < n; i += round_stride) {
         const bool valid = i < n;
         const ushort4 r = r_next;
-        const uint32_t roff = roff_next;
         const uint32_t w = r.z > r.x ? (uint32_t)(r.z - r.x) : 0u, h = r.w > r.y ? (uint32_t)(r.w - r.y) : 0u;
         const uint32_t cnt = w * h;
         const uint32_t dbits = cnt ? dbits_next : 0u;
@@ -422,10 +410,7 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
             const int64_t i2 = i + round_stride;
             const bool in = i2 < n;
             r_next = in ? rect[i2] : make_ushort4(0, 0, 0, 0);
-            if (SCATTER) {
-                roff_next = CB && in ? rec_offsets[i2] : 0u;
-                dbits_next = in ? __float_as_uint(depth[i2]) : 0u;
-            }
+            if (SCATTER) dbits_next = in ? __float_as_uint(depth[i2]) : 0u;
         }
         float mx = 0.f, my = 0.f, A = 1.f, B = 0.f, C = 1.f, Q = 0.f;
         if (CB && cnt) {
@@ -452,31 +437,27 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
         // 602 at 27 M pairs; 109.4 and 107.2, 236 and 234 at 10 M; 41.5 and 40.3, 70.6 and 68.6 at 500k Gaussians.
         auto candidates = [&](uint32_t j0, auto& owners) {
             constexpr int W = sizeof(owners) / sizeof(owners[0]);
-            uint32_t k[W], tile[W], od[W], oroff[W];
-            bool live[W], hit[W];
+            uint32_t tile[W], od[W];
+            bool hit[W];
 #pragma unroll
             for (int q = 0; q < W; q++) {
                 const uint32_t j1 = j0 + 64 * q + lane, j = min(j1, total - 1), s = owners[q];
-                live[q] = j1 < total;
-                k[q] = j - (uint32_t)__shfl((int)excl, (int)s, 64);
+                const uint32_t k = j - (uint32_t)__shfl((int)excl, (int)s, 64);
                 const uint32_t ow = (uint32_t)__shfl((int)w, (int)s, 64);
                 const uint32_t oxy = (uint32_t)__shfl((int)rect_xy, (int)s, 64);
-                const uint32_t row = rect_row(k[q], ow);
-                const uint32_t col = k[q] - row * ow;
+                const uint32_t row = rect_row(k, ow);
+                const uint32_t col = k - row * ow;
                 const uint32_t tx = (oxy & 0xffffu) + col, ty = (oxy >> 16) + row;
-                hit[q] = live[q];
+                hit[q] = j1 < total;
                 if (CB) {
                     const float omx = __shfl(mx, (int)s, 64), omy = __shfl(my, (int)s, 64);
                     const float oA = __shfl(A, (int)s, 64), oB = __shfl(B, (int)s, 64), oC = __shfl(C, (int)s, 64);
                     const float oQ = __shfl(Q, (int)s, 64);
-                    hit[q] = live[q] && cb_tile_hit(omx, omy, oA, oB, oC, oQ, (int)tx, (int)ty);
+                    hit[q] = hit[q] && cb_tile_hit(omx, omy, oA, oB, oC, oQ, (int)tx, (int)ty);
                 }
                 tile[q] = ty * (uint32_t)tiles_x + tx;
                 hit[q] = hit[q] && tile[q] < (uint32_t)num_tiles;   // (always true for a rect made for this camera)
-                if (SCATTER) {
-                    od[q] = (uint32_t)__shfl((int)dbits, (int)s, 64);
-                    oroff[q] = (uint32_t)__shfl((int)roff, (int)s, 64);
-                }
+                if (SCATTER) od[q] = (uint32_t)__shfl((int)dbits, (int)s, 64);
             }
             if (!SCATTER) {
 #pragma unroll
@@ -492,10 +473,6 @@ __global__ __launch_bounds__(TILE_PAIR_THREADS) void k_tile_pairs(int64_t n, con
                 if (hit[q]) {
                     const uint32_t of = BANDS ? tile[q] % BAND_TILES << BAND_SHIFT : 0u;
                     if (slot[q] < P) bucket[slot[q]] = ((uint64_t)od[q] << 32) | of | (uint32_t)(i - lane + owners[q]);
-                } else if (CB && live[q] && (uint64_t)oroff[q] + k[q] < rec_limit) {
-                    float4* g = pair_grad + ((size_t)oroff[q] + k[q]) * (PAIR_REC / 4);
-                    const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-                    g[0] = z; g[1] = z; g[2] = z;
                 }
             }
         };
@@ -1206,15 +1183,14 @@ hipError_t launch_rect_area(hipStream_t st, int64_t n, const uint16_t* rect, uin
 
 hipError_t launch_emit_pairs_cb(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg,
                                 const uint32_t* offsets, const uint32_t* rec_offsets, int tiles_x, int64_t P,
-                                uint64_t* keys, uint32_t* vals, float* splats, float* pair_grad)
+                                uint64_t* keys, uint32_t* vals, float* splats)
 {
     if (n == 0) return hipSuccess;
     hipLaunchKernelGGL(k_emit_pairs_cb, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n,
                        reinterpret_cast<const ushort4*>(proj.rect), proj.depth,
                        reinterpret_cast<const float2*>(proj.mean2d), reinterpret_cast<const float4*>(proj.conic_opacity),
                        proj.rgb, cfg, offsets, rec_offsets, tiles_x, (uint32_t)P, keys, vals,
-                       reinterpret_cast<float4*>(splats),
-                       reinterpret_cast<float4*>(pair_grad));
+                       reinterpret_cast<float4*>(splats));
     return hipGetLastError();
 }
 
@@ -1233,10 +1209,10 @@ hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj
         const float4* co = reinterpret_cast<const float4*>(proj.conic_opacity);
         if (cfg.compact_box)
             hipLaunchKernelGGL((k_tile_pairs<true, false, false>), grid, block, lds, st, n, rect, proj.depth, m2, co, cfg,
-                               nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, ra, BandPlaces{});
+                               tiles_x, num_tiles, tile_count, nullptr, 0u, nullptr, ra, BandPlaces{});
         else
             hipLaunchKernelGGL((k_tile_pairs<false, false, false>), grid, block, lds, st, n, rect, proj.depth, m2, co,
-                               cfg, nullptr, tiles_x, num_tiles, tile_count, nullptr, 0u, 0u, nullptr, nullptr, ra, BandPlaces{});
+                               cfg, tiles_x, num_tiles, tile_count, nullptr, 0u, nullptr, ra, BandPlaces{});
     }
     const int sum_blocks = (num_tiles + 63) / 64;
     hipLaunchKernelGGL(k_tile_layout, dim3((unsigned)(sum_blocks + std::max<int64_t>(1, (n + LAYOUT_THREADS - 1) / LAYOUT_THREADS))), dim3(LAYOUT_THREADS), 0, st,
@@ -1248,8 +1224,7 @@ hipError_t launch_tile_count(hipStream_t st, int64_t n, const fs_projected& proj
 }
 
 hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg,
-                               const uint32_t* rec_offsets, int tiles_x, int num_tiles, uint32_t pair_limit,
-                               uint32_t rec_limit, const uint2* ranges, uint32_t* cursor, uint64_t* bucket, float* pair_grad,
+                               int tiles_x, int num_tiles, uint32_t pair_limit, const uint2* ranges, uint32_t* cursor, uint64_t* bucket,
                                const BandPlaces& places)
 {
     if (n <= 0) return hipSuccess;
@@ -1259,8 +1234,8 @@ hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& pr
     const float2* m2 = reinterpret_cast<const float2*>(proj.mean2d);
     const float4* co = reinterpret_cast<const float4*>(proj.conic_opacity);
     auto launch = [&](auto kernel, size_t bytes) {
-        hipLaunchKernelGGL(kernel, grid, block, bytes, st, n, rect, proj.depth, m2, co, cfg, rec_offsets, tiles_x, num_tiles, cursor,
-                           ranges, pair_limit, rec_limit, bucket, reinterpret_cast<float4*>(pair_grad), RecAlloc{}, places);
+        hipLaunchKernelGGL(kernel, grid, block, bytes, st, n, rect, proj.depth, m2, co, cfg, tiles_x, num_tiles, cursor, ranges, pair_limit,
+                           bucket, RecAlloc{}, places);
     };
     if (places.band) {
         const size_t bytes = (size_t)(num_tiles + BAND_TILES - 1) / BAND_TILES * sizeof(uint32_t);

@@ -368,11 +368,11 @@ hipError_t launch_emit_pairs(hipStream_t st, int64_t n, const fs_projected& proj
 // Compact Box: rec_counts[i] = tiles in Gaussian i's box (the candidates of the ellipse test)
 hipError_t launch_rect_area(hipStream_t st, int64_t n, const uint16_t* rect, uint32_t* rec_counts);
 // Compact Box emission: one key per candidate tile that meets the ellipse, at offsets[i] + its rank among
-// the Gaussian's hits; the gradient record of every candidate that misses (rec_offsets[i] + row-major
-// place in the box) is zeroed, since no render workgroup will ever write it.
+// the Gaussian's hits.  (No render workgroup writes the gradient record of a candidate that misses, rec_offsets[i] + its row-major
+// place in the box: a dense backward pass clears all records first.)
 hipError_t launch_emit_pairs_cb(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg,
                                 const uint32_t* offsets, const uint32_t* rec_offsets, int tiles_x, int64_t P,
-                                uint64_t* keys, uint32_t* vals, float* splats, float* pair_grad);
+                                uint64_t* keys, uint32_t* vals, float* splats);
 
 // Tile-bucketed ordering (used when no tile's list is longer than TILE_SORT_HUGE; otherwise the global
 // radix sort below): per-tile counts and ranges, then placement into the tiles' segments and an LDS sort
@@ -419,16 +419,15 @@ inline bool placed_by_bands(int64_t n, int num_tiles, int64_t candidates_before)
     return n >= BAND_MIN_N && n <= (int64_t)1 << BAND_SHIFT && num_tiles > BAND_TILES &&
            (candidates_before < 0 || candidates_before >= BAND_MIN_CANDIDATES);
 }
-// Placement and the per-tile sorts.  pair_limit / rec_limit: how many words / gradient records the buffers hold; the
-// kernels write nothing at or beyond them and leave alone a segment that reaches beyond pair_limit, so they may be
+// Placement and the per-tile sorts.  pair_limit: how many words the buffers hold; the
+// kernels write nothing at or beyond it and leave alone a segment that reaches beyond pair_limit, so they may be
 // enqueued before the host knows the totals.  places: written by a placement into bands, read by the split (null: no bands).
 struct BandPlaces {
     uint32_t* tile;   // [num_tiles] where a tile's next words go (the tiles' totals of launch_tile_count, which are done with by then)
     uint2* band;      // [ceil(num_tiles / BAND_TILES)] first and last + 1 place of its pairs ({~0, 0}: none)
 };
 hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg,
-                               const uint32_t* rec_offsets, int tiles_x, int num_tiles, uint32_t pair_limit,
-                               uint32_t rec_limit, const uint2* ranges, uint32_t* cursor, uint64_t* bucket, float* pair_grad,
+                               int tiles_x, int num_tiles, uint32_t pair_limit, const uint2* ranges, uint32_t* cursor, uint64_t* bucket,
                                const BandPlaces& places);
 // The sort launches, by the list lengths they take: (0, SMALL], (SMALL, MID], (MID, MAX], (MAX, HUGE], and
 // (SMALL, MAX] in one launch (TS_MIDMAX, instead of TS_MID and TS_MAX).  The lists between SMALL and MID get a launch of

@@ -92,8 +92,8 @@ hipError_t launch_tile_count(hipStream_t, int64_t, const fs_projected&, const Cf
     words(1, totals, four, 4);
     return hipSuccess;
 }
-hipError_t launch_tile_scatter(hipStream_t, int64_t, const fs_projected&, const CfgDev&, const uint32_t*, int, int, uint32_t, uint32_t,
-                               const uint2*, uint32_t*, uint64_t*, float*, const BandPlaces& places)
+hipError_t launch_tile_scatter(hipStream_t, int64_t, const fs_projected&, const CfgDev&, int, int, uint32_t, const uint2*, uint32_t*,
+                               uint64_t*, const BandPlaces& places)
 {
     stub_bands[1] += places.band != nullptr;
     return hipSuccess;
