@@ -52,7 +52,9 @@ struct fs_ctx {
     int64_t candidates_before = -1;      // of the previous ordering (-1: none); chooses the placement (placed_by_bands)
     uint64_t* total_dev = nullptr;   // device: totals [4]: pairs, backward records, pairs counted per tile, longest tile list
     uint64_t* total_host = nullptr;  // pinned host block of four totals (copied from total_dev, or written by k_tile_layout)
-    uint64_t* counters = nullptr;    // device: TILE_COUNTERS of launch_tile_count (the first is zero between calls)
+    uint64_t* counters = nullptr;    // device: TILE_COUNTERS of launch_tile_count (the first is zero between calls), and behind them the
+                                     // tiles' words of launch_small_frame
+    uint32_t small_call = 0;         // the number of the last launch_small_frame
     bool counters_dirty = false;     // a call failed where it may have left that one as it was
     bool totals_pending = false;     // a call failed between the launch that writes total_host and its arrival
     ScratchBuf train_proj;           // fs_train_step: the projected splats of its view ...
@@ -133,13 +135,15 @@ int ensure(fs_ctx* ctx, ScratchBuf& b, size_t bytes, const char* what)
     if (bytes <= b.cap) return FS_OK;
     size_t want = b.cap ? b.cap : 4096;
     while (want < bytes) want *= 2;
-    // nothing enqueued earlier may still use the old block when it is released
-    hipError_t e = hipStreamSynchronize(ctx->stream);
-    if (e != hipSuccess) return hip_fail(ctx, e, "hipStreamSynchronize");
-    if (b.ptr) (void)hipFree(b.ptr);
+    if (b.ptr) {
+        // nothing enqueued earlier may still use the old block when it is released
+        const hipError_t e = hipStreamSynchronize(ctx->stream);
+        if (e != hipSuccess) return hip_fail(ctx, e, "hipStreamSynchronize");
+        (void)hipFree(b.ptr);
+    }
     b.ptr = nullptr;
     b.cap = 0;
-    e = hipMalloc(&b.ptr, want);
+    const hipError_t e = hipMalloc(&b.ptr, want);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         b.ptr = nullptr;
@@ -392,8 +396,9 @@ int fs_create(fs_ctx** out, int device, void* hip_stream, const fs_config* cfg)
         fs_destroy(ctx);
         return FS_EHIP;
     }
-    if (hipMalloc(reinterpret_cast<void**>(&ctx->counters), TILE_COUNTERS * sizeof(uint64_t)) != hipSuccess ||
-        hipMemset(ctx->counters, 0, TILE_COUNTERS * sizeof(uint64_t)) != hipSuccess ||
+    constexpr size_t counter_bytes = TILE_COUNTERS * sizeof(uint64_t) + SMALL_MAX_TILES * sizeof(uint32_t);
+    if (hipMalloc(reinterpret_cast<void**>(&ctx->counters), counter_bytes) != hipSuccess ||
+        hipMemset(ctx->counters, 0, counter_bytes) != hipSuccess ||
         hipMalloc(reinterpret_cast<void**>(&ctx->total_dev), 4 * sizeof(uint64_t)) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void**>(&ctx->total_host), LOSS_HOST_AT + 3 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
@@ -445,7 +450,8 @@ int fs_preprocess(fs_ctx* ctx, const fs_gaussians* g, const fs_camera* cam, fs_p
     return FS_OK;
 }
 
-int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int64_t n, fs_bins* out)
+// training: the call is part of fs_train_step (chooses the launches, see small_frame)
+static int bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int64_t n, bool training, fs_bins* out)
 {
     if (!ctx) return FS_EINVAL;
     CamDev cd;
@@ -467,7 +473,8 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
     uint32_t* const ttotal_p = ranges_p + 3 * (size_t)tiles;
     uint32_t* const tcount_p = ranges_p + 4 * (size_t)tiles;
     const bool bucketed = ctx->cfg.sort_mode == FS_SORT_AUTO && tiles <= TILE_LDS_MAX_TILES;
-    const bool bands = placed_by_bands(n, tiles, ctx->candidates_before);   // (then keys[0] is placed into, and split into keys[1] ahead of the sorts)
+    const bool small = bucketed && small_frame(n, tiles, training);   // (one launch for all but the sorts of long lists)
+    const bool bands = !small && placed_by_bands(n, tiles, ctx->candidates_before);   // (then keys[0] is placed into, and split into keys[1] ahead of the sorts)
     const int split = bands ? TS_SPLIT : 0;
     const BandPlaces places = bands ? BandPlaces{ttotal_p, reinterpret_cast<uint2*>(tcount_p + (size_t)TILE_COPIES * tiles)} : BandPlaces{};
     FS_TRY(ensure(ctx, ctx->offsets, (size_t)(n > 0 ? n : 1) * sizeof(uint32_t), "offsets"));
@@ -499,7 +506,40 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
         }
         return FS_OK;
     };
-    if (bucketed) {
+    if (small && ctx->keys[1].cap == 0) {
+        // a new context's buffers hold sixteen tiles a Gaussian, so that its first launch seldom needs a second one (a failure shows below)
+        for (ScratchBuf* b : {&ctx->keys[0], &ctx->keys[1]}) (void)ensure(ctx, *b, (size_t)n * 16 * sizeof(uint64_t), "keys");
+        (void)ensure(ctx, ctx->vals[0], (size_t)n * 16 * sizeof(uint32_t), "values");
+    }
+    // what the buffers hold
+    uint64_t cap_pairs = 0;
+    if (bucketed && n > 0) {
+        cap_pairs = ctx->keys[0].cap / sizeof(uint64_t);
+        if (ctx->keys[1].cap / sizeof(uint64_t) < cap_pairs) cap_pairs = ctx->keys[1].cap / sizeof(uint64_t);
+        if (ctx->vals[0].cap / sizeof(uint32_t) < cap_pairs) cap_pairs = ctx->vals[0].cap / sizeof(uint32_t);
+        if (cap_pairs > 0x7fffffffull) cap_pairs = 0x7fffffffull;
+    }
+    auto small_order = [&](uint64_t limit, uint64_t* totals) {
+        uint32_t* const said = reinterpret_cast<uint32_t*>(ctx->counters + TILE_COUNTERS);
+        if (totals && ++ctx->small_call == 65536) {
+            const hipError_t e = launch_fill_u32(st, said, 0u, SMALL_MAX_TILES);
+            if (e != hipSuccess) { ctx->small_call--; return e; }
+            ctx->small_call = 1;
+        }
+        return launch_small_frame(st, n, *proj, cf, cd.tiles_x, tiles, (uint32_t)limit, said, ctx->small_call,
+                                  reinterpret_cast<uint2*>(ranges_p), order_p, totals,
+                                  static_cast<uint32_t*>(cb ? ctx->rec_offsets.ptr : ctx->offsets.ptr),
+                                  cb ? static_cast<uint32_t*>(ctx->rec_counts.ptr) : nullptr, static_cast<float*>(ctx->splats.ptr),
+                                  static_cast<uint64_t*>(ctx->keys[1].ptr), static_cast<uint64_t*>(ctx->keys[0].ptr),
+                                  static_cast<uint32_t*>(ctx->vals[0].ptr));
+    };
+    if (small) {
+        ProfScope prof(ctx, FS_K_EMIT);
+        if (ctx->totals_pending) FS_HIP(hipStreamSynchronize(st), "hipStreamSynchronize");   // (as below)
+        unset_words(ctx->total_host, 4);
+        ctx->totals_pending = true;
+        FS_HIP(small_order(cap_pairs, ctx->total_host), "k_small_frame");
+    } else if (bucketed) {
         // first half: pairs per tile, ranges, longest list, record places (needs no P-sized memory, so it is
         // enqueued ahead of the read-back)
         ProfScope prof(ctx, FS_K_EMIT);
@@ -533,13 +573,18 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
     // call.  The kernels write nothing beyond the capacities they are given; what the totals then say was not covered
     // (a longer list's sort variant, or buffers that have to grow first) is enqueued afterwards.
     fs_projected none = {};
-    uint64_t cap_pairs = 0;
     int spec_variants = 0;
-    if (bucketed && ctx->spec_set != 0 && n > 0) {
-        cap_pairs = ctx->keys[0].cap / sizeof(uint64_t);
-        if (ctx->keys[1].cap / sizeof(uint64_t) < cap_pairs) cap_pairs = ctx->keys[1].cap / sizeof(uint64_t);
-        if (ctx->vals[0].cap / sizeof(uint32_t) < cap_pairs) cap_pairs = ctx->vals[0].cap / sizeof(uint32_t);
-        if (cap_pairs > 0x7fffffffull) cap_pairs = 0x7fffffffull;
+    if (small) {
+        // (the lists up to TILE_SORT_SMALL are in order; longer ones lie as they come)
+        spec_variants = ctx->spec_set | TS_SMALL;
+        if (cap_pairs > 0 && spec_variants != TS_SMALL) {
+            ProfScope prof(ctx, FS_K_ORDER);
+            FS_HIP(launch_tile_sorts(st, tiles, spec_variants & ~TS_SMALL, (uint32_t)cap_pairs, reinterpret_cast<const uint2*>(ranges_p),
+                                     order_p, static_cast<uint64_t*>(ctx->keys[1].ptr),
+                                     static_cast<uint64_t*>(ctx->keys[0].ptr), static_cast<uint32_t*>(ctx->vals[0].ptr), places),
+                   "k_tile_sort");
+        }
+    } else if (bucketed && ctx->spec_set != 0 && n > 0) {
         if (cap_pairs > 0) {
             ProfScope prof(ctx, FS_K_ORDER);
             spec_variants = ctx->spec_set;
@@ -591,10 +636,12 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
         // (lists of more than 1024 entries on average: enough tiles beyond 2048 to give them a launch of their own)
         const bool long_lists = P > (uint64_t)1024 * (uint64_t)tiles;
         // placement and the sorts enqueued ahead have run (or are running) already: what do they leave to do?
-        const int variants = P > 0 ? tile_sort_variants((int64_t)max_len, long_lists, spec_fits ? spec_variants : 0) : 0;
+        const int variants = P > 0 ? tile_sort_variants((int64_t)max_len, long_lists, spec_fits ? spec_variants : small ? TS_SMALL : 0) : 0;
         if (!spec_fits || variants) {
             ProfScope prof(ctx, FS_K_ORDER);
-            if (!spec_fits) {
+            if (!spec_fits && small) {
+                FS_HIP(small_order(P, nullptr), "k_small_frame");
+            } else if (!spec_fits) {
                 FS_HIP(launch_tile_scatter(st, n, proj ? *proj : none, cf, cd.tiles_x, tiles, (uint32_t)P,
                                            reinterpret_cast<const uint2*>(ranges_p), tcount_p, keys[bands ? 0 : 1], places),
                        "k_tile_pairs (placement)");
@@ -643,6 +690,11 @@ int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int
     out->tile_order = static_cast<const uint32_t*>(ctx->ranges.ptr) + 2 * (size_t)tiles;
     out->generation = ctx->generation;
     return FS_OK;
+}
+
+int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int64_t n, fs_bins* out)
+{
+    return bin_sort(ctx, proj, cam, n, false, out);
 }
 
 int fs_render_fwd(fs_ctx* ctx, const fs_projected* proj, const fs_bins* bins, const fs_camera* cam, float* image,
@@ -1131,7 +1183,7 @@ int fs_train_step(fs_ctx* ctx, const fs_train_state* t, const fs_camera* cam, co
         FS_HIP(launch_preprocess(st, n, t->sh_degree, g, true, cd, cf, proj), "k_preprocess");
     }
     fs_bins bins = {};
-    FS_TRY(fs_bin_sort(ctx, &proj, cam, n, &bins));
+    FS_TRY(bin_sort(ctx, &proj, cam, n, true, &bins));
     const BlendRecord blends = blends_for(ctx, &bins, tiles);
     {
         ProfScope prof(ctx, FS_K_RENDER_FWD);

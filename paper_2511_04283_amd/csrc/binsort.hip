@@ -9,6 +9,7 @@
 //
 // Times "at 500k Gaussians" and the like are of the scenes of perf/cases.py, those at 10 M and 27 M pairs of bench.py's largest.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 
@@ -816,11 +817,15 @@ __device__ __forceinline__ void network_strided(uint64_t* k, int N, int a, int k
     __syncthreads();
 }
 
-// k[0, n) <- the segment's words in order; k holds N words, N >= 16 a power of two, N >= n.
-template <int THREADS>
-__device__ __forceinline__ void network_sort(uint64_t* k, int N, int n, const uint64_t* __restrict__ words)
+// k[0, n) <- the words in order (word(u) is word t + u THREADS of thread t); k holds N words, N >= 16 a power of two, N >= n.
+template <int THREADS, int PER, typename Word>
+__device__ __forceinline__ void network_sort(uint64_t* k, int N, int n, Word word)
 {
-    for (int i = threadIdx.x; i < N; i += THREADS) k[i] = i < n ? words[i] : ~0ull;
+#pragma unroll
+    for (int u = 0; u < PER; u++) {
+        const int i = (int)threadIdx.x + u * THREADS;
+        if (i < N) k[i] = i < n ? word(u) : ~0ull;
+    }
     __syncthreads();
     for (int g = threadIdx.x; g < N / 8; g += THREADS) {   // the complete stages 2, 4, 8
         uint64_t v[8];
@@ -857,35 +862,31 @@ __device__ __forceinline__ void network_sort(uint64_t* k, int N, int n, const ui
 // barriers.  Against the network for everything: 27 M pairs (lists of 3 350 on average) 830 -> 259 us in four launches
 // (<= 2 048, <= 4 096, <= 8 192, <= 16 384 words),
 // 10 M pairs 177 -> 75 us, 300k Gaussians at 1332x876 55 -> 23 us, 100k at 980x545 16.4 -> 8.4 us.
-// Handles the tiles whose length is in (len_lo, CAP]; the others are left to another launch.
 constexpr int COARSE = 256;
 constexpr int BUCKET_LIMIT = 256;
 
 template <int CAP, int THREADS, int NB>
-__global__ __launch_bounds__(THREADS, CAP == TILE_SORT_MAX ? 8 : 4) void k_tile_sort(const uint2* __restrict__ ranges,
-                                                   const uint32_t* __restrict__ tile_order,
-                                                   const uint64_t* __restrict__ bucket, int len_lo, uint32_t limit,
-                                                   uint64_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out)
+struct SortMem {
+    uint64_t k[CAP + NB / 2 + 1];   // the words in bucket order, and behind them the buckets' counts, then first places ([NB + 1])
+    float2 part[COARSE];            // words before a part, words in it
+    uint32_t red[3][THREADS / 64];
+};
+
+// One workgroup orders a tile's n <= CAP words: word t + u THREADS is w[u] of thread t (anything beyond the n-th), and again(u) once more
+// for the few lists that the network takes.  place() is called by all threads, between barriers, and says where the tile's segment
+// starts, or (not SURE) ~0u to write nothing.
+template <int CAP, int THREADS, int NB, bool SURE, typename Again, typename Place>
+__device__ __forceinline__ void sort_list(SortMem<CAP, THREADS, NB>& mem, const uint64_t (&w)[CAP / THREADS], int n, uint32_t tile, Again again,
+                                          Place place, uint64_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out)
 {
     constexpr int PER = CAP / THREADS, WAVES = THREADS / 64, NBT = NB / THREADS;
     static_assert(CAP % THREADS == 0 && NB % THREADS == 0 && THREADS >= COARSE, "whole words and buckets per thread");
-    __shared__ __align__(16) uint64_t k[CAP + NB / 2 + 1];           // the words in bucket order, and behind them
-    uint32_t* const start = reinterpret_cast<uint32_t*>(k + CAP);   // [NB + 1]: the buckets' counts, then first places
-    __shared__ float2 part[COARSE];                                  // words before a part, words in it
-    __shared__ uint32_t red[3][WAVES];
-    const uint32_t tile = tile_order[blockIdx.x];
-    const uint2 r = ranges[tile];
-    const int n = (int)(r.y - r.x);
-    // (uniform over the workgroup; `limit` = the words the buffers hold: a segment that reaches beyond it is left alone)
-    if (n <= len_lo || n > CAP || r.y > limit) return;
+    uint64_t* const k = mem.k;
+    uint32_t* const start = reinterpret_cast<uint32_t*>(k + CAP);
+    float2* const part = mem.part;
+    uint32_t (*const red)[WAVES] = mem.red;
     const int t = threadIdx.x, wave = t >> 6;
-    uint64_t w[PER];
     uint32_t lo = 0xffffffffu, hi = 0u;
-#pragma unroll
-    for (int u = 0; u < PER; u++) {
-        const int i = t + u * THREADS;
-        w[u] = i < n ? bucket[r.x + i] : 0ull;
-    }
 #pragma unroll
     for (int u = 0; u < PER; u++) {
         if (t + u * THREADS < n) {
@@ -973,10 +974,12 @@ __global__ __launch_bounds__(THREADS, CAP == TILE_SORT_MAX ? 8 : 4) void k_tile_
         if (most > (uint32_t)BUCKET_LIMIT) {   // (uniform over the workgroup)
             int N = 16;
             while (N < n) N <<= 1;
-            network_sort<THREADS>(k, N, n, bucket + r.x);
+            network_sort<THREADS, PER>(k, N, n, again);
+            const uint32_t to = place();
+            if (!SURE && to == ~0u) return;
             for (int i = t; i < n; i += THREADS) {
-                keys_out[r.x + i] = ((uint64_t)tile << 32) | (k[i] >> 32);
-                vals_out[r.x + i] = (uint32_t)k[i];
+                keys_out[to + i] = ((uint64_t)tile << 32) | (k[i] >> 32);
+                vals_out[to + i] = (uint32_t)k[i];
             }
             return;
         }
@@ -989,6 +992,8 @@ __global__ __launch_bounds__(THREADS, CAP == TILE_SORT_MAX ? 8 : 4) void k_tile_
     for (int u = 0; u < PER; u++)
         if (t + u * THREADS < n) k[start[at[u] >> 16] + (at[u] & 0xffffu)] = w[u];
     __syncthreads();
+    const uint32_t to = place();
+    if (!SURE && to == ~0u) return;
     // (words are taken in bucket order now, so that neighbouring lanes write neighbouring places)
 #pragma unroll
     for (int u = 0; u < PER; u++) {
@@ -1000,10 +1005,333 @@ __global__ __launch_bounds__(THREADS, CAP == TILE_SORT_MAX ? 8 : 4) void k_tile_
             uint32_t rank = s;
             if (e - s > 1u)
                 for (uint32_t q = s; q < e; q++) rank += k[q] < word ? 1u : 0u;
-            keys_out[r.x + rank] = ((uint64_t)tile << 32) | (word >> 32);
-            vals_out[r.x + rank] = (uint32_t)word;
+            keys_out[to + rank] = ((uint64_t)tile << 32) | (word >> 32);
+            vals_out[to + rank] = (uint32_t)word;
         }
     }
+}
+
+// Handles the tiles whose length is in (len_lo, CAP]; the others are left to another launch.
+template <int CAP, int THREADS, int NB>
+__global__ __launch_bounds__(THREADS, CAP == TILE_SORT_MAX ? 8 : 4) void k_tile_sort(const uint2* __restrict__ ranges,
+                                                   const uint32_t* __restrict__ tile_order,
+                                                   const uint64_t* __restrict__ bucket, int len_lo, uint32_t limit,
+                                                   uint64_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out)
+{
+    __shared__ __align__(16) SortMem<CAP, THREADS, NB> mem;
+    const uint32_t tile = tile_order[blockIdx.x];
+    const uint2 r = ranges[tile];
+    const int n = (int)(r.y - r.x);
+    // (uniform over the workgroup; `limit` = the words the buffers hold: a segment that reaches beyond it is left alone)
+    if (n <= len_lo || n > CAP || r.y > limit) return;
+    uint64_t w[CAP / THREADS];
+#pragma unroll
+    for (int u = 0; u < CAP / THREADS; u++) {
+        const int i = (int)threadIdx.x + u * THREADS;
+        w[u] = i < n ? bucket[r.x + i] : 0ull;
+    }
+    sort_list<CAP, THREADS, NB, true>(mem, w, n, tile, [&](int u) { return bucket[r.x + threadIdx.x + u * THREADS]; }, [&] { return r.x; }, keys_out, vals_out);
+}
+
+// The whole ordering of a small frame in one launch, where the four of the general way take some 5 us each and have little to do.
+//
+// Workgroups [0, num_tiles), one for each tile: it looks at every Gaussian's rectangle itself, keeps those that hold the tile (and meet
+// it, with the Compact Box), says how many they are, orders them in LDS, and writes them behind the pairs of the tiles before it once
+// all of those have said theirs.  Workgroup num_tiles waits for all tiles and leaves their order and two totals.  The others, 256
+// Gaussians each, sum the areas before theirs and pack records and record places; the last one leaves the other two totals.
+// A tile's word in `said` is the call's number << 16 | its pairs, past all caches, so that nothing has to be cleared or fenced.  A
+// workgroup waits only for workgroups of lower numbers that wait for nothing before they speak, so the lowest silent one is always
+// under way or next in line; and no wait is longer than SMALL_POLLS looks: after that its workgroup writes nothing, the totals stay
+// unset and the host says so.
+// A list longer than TILE_SORT_SMALL is left unordered in `bucket` for the launches that take longer ones.
+// What bounds it are its chains: the rectangles' loads (n / 256 of a thread, 16 at a time), list and sort in LDS, and the wait.
+// fs_bin_sort, back to back, in four launches and in this one, us: 4k at 128x128 19.6 -> 12, 3k at 509x337 20.5 -> 15.6, 9k at 400x300 20.1 -> 17.8,
+// with splats of twelve tiles 24.8 -> 17.3; a new context's first render at 4k 147 -> 98.  Lists of up to 128 ordered by comparing each word
+// with all others instead of the sort: no difference (within 2 %).
+constexpr int SMALL_THREADS = 256;
+constexpr int SMALL_PER = 16;          // rectangles a thread has in flight
+constexpr int SMALL_POLLS = 1 << 20;
+struct SmallFrame {
+    int64_t n;
+    const ushort4* rect;
+    const float* depth;
+    const float2* mean2d;
+    const float4* conic_opacity;
+    const float* rgb;
+    const uint32_t* tiles_touched;
+    int tiles_x, num_tiles;
+    uint32_t limit;                  // words the buffers hold
+    uint32_t* said;                  // [SMALL_MAX_TILES]
+    uint32_t call;                   // (16 bits)
+    uint2* ranges;
+    uint32_t* order;
+    uint64_t* totals;                // (null: only the pairs are still to be written, into the ranges of the launch before)
+    uint32_t* rec_offsets;
+    uint32_t* rec_counts;
+    float4* splats;
+    uint64_t* bucket;
+    uint64_t* keys_out;
+    uint32_t* vals_out;
+};
+
+__device__ __forceinline__ uint32_t rect_area(const ushort4& r)
+{
+    return r.z > r.x && r.w > r.y ? (uint32_t)(r.z - r.x) * (uint32_t)(r.w - r.y) : 0u;
+}
+
+// What tiles 2 t, 2 t + 1, 512 + 2 t, 512 + 2 t + 1 below `end` have said in this call (0 for the others); false when one of them
+// says nothing.
+constexpr int SMALL_TILES_PER = SMALL_MAX_TILES / SMALL_THREADS;
+static_assert(SMALL_TILES_PER == 4 && SMALL_MAX_N < 65536, "two loads of two words, 16 bits for a tile's pairs");
+__device__ __forceinline__ int said_tile(int q) { return (q >> 1) * 2 * SMALL_THREADS + 2 * (int)threadIdx.x + (q & 1); }
+__device__ __forceinline__ bool pairs_said(const SmallFrame& f, int end, uint32_t (&c)[SMALL_TILES_PER])
+{
+    const unsigned long long* const words = reinterpret_cast<const unsigned long long*>(f.said);
+    for (int k = 0; k < SMALL_POLLS; k++) {
+        unsigned long long w[SMALL_TILES_PER / 2] = {};
+#pragma unroll
+        for (int h = 0; h < SMALL_TILES_PER / 2; h++)
+            if (said_tile(2 * h) < end) w[h] = __hip_atomic_load(&words[h * SMALL_THREADS + threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bool all = true;
+#pragma unroll
+        for (int q = 0; q < SMALL_TILES_PER; q++) {
+            const uint32_t word = (uint32_t)(w[q >> 1] >> 32 * (q & 1));
+            const bool mine = said_tile(q) < end;
+            all = all & (!mine | (word >> 16 == f.call));
+            c[q] = mine ? word & 0xffffu : 0u;
+        }
+        if (all) return true;
+        __builtin_amdgcn_s_sleep(1);
+    }
+    return false;
+}
+
+template <bool CB>
+__global__ __launch_bounds__(SMALL_THREADS) void k_small_frame(SmallFrame f, CfgDev cfg)
+{
+    constexpr int T = SMALL_THREADS, WAVES = T / 64;
+    constexpr int PER_TILE = SMALL_TILES_PER;
+    constexpr int NB = ORDER_BUCKETS;
+    union Mem {
+        SortMem<TILE_SORT_SMALL, T, 1024> sort;
+        uint16_t list[SMALL_MAX_N];     // Gaussians of the tile
+        uint32_t buckets[NB];
+    };
+    __shared__ __align__(16) Mem mem;
+    __shared__ uint32_t s_count, s_wave[2][WAVES], s_late;
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    const int n = (int)f.n;
+    auto below = [](uint64_t bal) { return __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u)); };
+
+    if ((int)blockIdx.x > f.num_tiles) {
+        const int first = ((int)blockIdx.x - f.num_tiles - 1) * T, i = first + t;
+        const ushort4 r = i < n ? f.rect[i] : make_ushort4(0, 0, 0, 0);
+        const uint32_t area = rect_area(r);
+        uint32_t before = 0;
+        for (int j0 = 0; j0 < first; j0 += SMALL_PER * T) {
+            ushort4 q[SMALL_PER];
+#pragma unroll
+            for (int u = 0; u < SMALL_PER; u++) q[u] = f.rect[min(j0 + u * T + t, n - 1)];
+#pragma unroll
+            for (int u = 0; u < SMALL_PER; u++) before += j0 + u * T < first ? rect_area(q[u]) : 0u;
+        }
+        const uint32_t inc = wave_inclusive_scan(area), all_before = wave_inclusive_scan(before);
+        if (lane == 63) { s_wave[0][wave] = inc; s_wave[1][wave] = all_before; }
+        __syncthreads();
+        uint32_t at = inc - area, total = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; w++) {
+            at += s_wave[1][w] + (w < wave ? s_wave[0][w] : 0u);
+            total += s_wave[1][w] + s_wave[0][w];
+        }
+        if (i < n) {
+            f.rec_offsets[i] = at;
+            if (f.rec_counts) f.rec_counts[i] = area;
+            if (area) pack_splat(f.splats, i, f.mean2d[i], f.conic_opacity[i], f.rgb, at, r, cfg);
+        }
+        if (blockIdx.x + 1 == gridDim.x) {
+            // (below 2^31 both: at most 2^14 Gaussians in at most 2^10 tiles)
+            uint32_t touched = 0;
+            for (int j0 = 0; j0 < n; j0 += SMALL_PER * T) {
+                uint32_t q[SMALL_PER];
+#pragma unroll
+                for (int u = 0; u < SMALL_PER; u++) q[u] = f.tiles_touched[min(j0 + u * T + t, n - 1)];
+#pragma unroll
+                for (int u = 0; u < SMALL_PER; u++) touched += j0 + u * T + t < n ? q[u] : 0u;
+            }
+            touched = wave_inclusive_scan(touched);
+            __syncthreads();
+            if (lane == 63) s_wave[0][wave] = touched;
+            __syncthreads();
+            if (t == 0) {
+                uint64_t tt = 0;
+                for (int w = 0; w < WAVES; w++) tt += s_wave[0][w];
+                __hip_atomic_store(&f.totals[0], tt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                __hip_atomic_store(&f.totals[1], (uint64_t)total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+        }
+        return;
+    }
+
+    if (t == 0) { s_count = 0u; s_late = 0u; }
+    if ((int)blockIdx.x == f.num_tiles) {
+        // the order: as in k_tile_layout
+        auto bucket = [](uint32_t len) { return (int)(NB - 1 - min(len / ORDER_STEP, (uint32_t)NB - 1)); };
+        uint32_t* const cnt = mem.buckets;
+#pragma unroll
+        for (int q = 0; q < NB / T; q++) cnt[t + q * T] = 0u;
+        uint32_t c[PER_TILE], sum = 0, most = 0;
+        const bool late = !pairs_said(f, f.num_tiles, c);
+#pragma unroll
+        for (int q = 0; q < PER_TILE; q++) {
+            sum += c[q];
+            most = max(most, c[q]);
+        }
+        __syncthreads();
+        if (late) s_late = 1u;
+#pragma unroll
+        for (int q = 0; q < PER_TILE; q++)
+            if (said_tile(q) < f.num_tiles) atomicAdd(&cnt[bucket(c[q])], 1u);
+        sum = wave_inclusive_scan(sum);
+        most = wave_inclusive_max(most);
+        if (lane == 63) { s_wave[0][wave] = sum; s_wave[1][wave] = most; }
+        __syncthreads();
+        if (s_late) return;
+        if (wave == 0) {
+            uint32_t v[NB / 64], all = 0;
+#pragma unroll
+            for (int q = 0; q < NB / 64; q++) { v[q] = cnt[lane * (NB / 64) + q]; all += v[q]; }
+            uint32_t run = wave_inclusive_scan(all) - all;
+#pragma unroll
+            for (int q = 0; q < NB / 64; q++) { cnt[lane * (NB / 64) + q] = run; run += v[q]; }
+        }
+        if (t == T - 1) {
+            uint64_t pairs = 0, longest = 0;
+            for (int w = 0; w < WAVES; w++) { pairs += s_wave[0][w]; longest = max(longest, (uint64_t)s_wave[1][w]); }
+            __hip_atomic_store(&f.totals[2], pairs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(&f.totals[3], longest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PER_TILE; q++)
+            if (said_tile(q) < f.num_tiles) f.order[atomicAdd(&cnt[bucket(c[q])], 1u)] = (uint32_t)said_tile(q);
+        return;
+    }
+
+    const uint32_t tile = blockIdx.x;
+    const uint32_t tx = tile % (uint32_t)f.tiles_x, ty = tile / (uint32_t)f.tiles_x;
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    struct Rect { u16x2 first, last; };   // (one past the last)
+    const u16x2 me = {(unsigned short)tx, (unsigned short)ty};
+    const Rect* const rects = reinterpret_cast<const Rect*>(f.rect);
+    __syncthreads();
+    auto scan = [&](int i0, auto whole) {
+        Rect r[SMALL_PER];
+#pragma unroll
+        for (int u = 0; u < SMALL_PER; u++) r[u] = rects[min(i0 + u * T + t, n - 1)];   // (all requested at once: no branches between them)
+        uint64_t in[SMALL_PER];
+        uint32_t count = 0;
+#pragma unroll
+        for (int u = 0; u < SMALL_PER; u++) {
+            // first <= me < last, both coordinates at once: a place before the first wraps round to beyond any size, and a rectangle
+            // that ends before it starts has the size 0
+            const u16x2 at = me - r[u].first, size = __builtin_elementwise_sub_sat(r[u].last, r[u].first);
+            in[u] = __ballot((at.x < size.x) & (at.y < size.y) & (decltype(whole)::value || i0 + u * T + t < n));
+            count += (uint32_t)__popcll(in[u]);
+        }
+        if (count == 0) return;
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&s_count, count);
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+        for (int u = 0; u < SMALL_PER; u++) {
+            if (in[u] >> lane & 1ull) mem.list[at + below(in[u])] = (uint16_t)(i0 + u * T + t);
+            at += (uint32_t)__popcll(in[u]);
+        }
+    };
+    int i0 = 0;
+    for (; i0 + SMALL_PER * T <= n; i0 += SMALL_PER * T) scan(i0, std::true_type{});
+    if (i0 < n) scan(i0, std::false_type{});
+    __syncthreads();
+    int len = (int)s_count;
+    if (CB) {
+        // those that the ellipse leaves, packed to the front of the list: a round's places are read before any is written, and no later
+        // one's is
+        __syncthreads();
+        if (t == 0) s_count = 0u;
+        __syncthreads();
+        constexpr int PER = 4;
+        for (int i0 = 0; i0 < len; i0 += PER * T) {
+            uint32_t g[PER];
+            float2 m[PER];
+            float4 co[PER];
+#pragma unroll
+            for (int u = 0; u < PER; u++) g[u] = i0 + u * T + t < len ? mem.list[i0 + u * T + t] : ~0u;
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < PER; u++) {
+                const uint32_t at = g[u] != ~0u ? g[u] : 0u;
+                m[u] = f.mean2d[at];
+                co[u] = f.conic_opacity[at];
+            }
+            uint64_t in[PER];
+            uint32_t count = 0;
+#pragma unroll
+            for (int u = 0; u < PER; u++) {
+                if (i0 + u * T >= len) { in[u] = 0ull; continue; }
+                in[u] = __ballot(g[u] != ~0u && cb_tile_hit(m[u].x, m[u].y, co[u].x, co[u].y, co[u].z, cb_threshold(co[u].w, cfg), (int)tx, (int)ty));
+                count += (uint32_t)__popcll(in[u]);
+            }
+            uint32_t at = 0;
+            if (lane == 0 && count) at = atomicAdd(&s_count, count);
+            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+            for (int u = 0; u < PER; u++) {
+                if (in[u] >> lane & 1ull) mem.list[at + below(in[u])] = (uint16_t)g[u];
+                at += (uint32_t)__popcll(in[u]);
+            }
+        }
+        __syncthreads();
+        len = (int)s_count;
+    }
+    if (t == 0 && f.totals)
+        __hip_atomic_store(&f.said[tile], f.call << 16 | (uint32_t)len, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
+    // where the tile's segment starts, ~0u where nothing is to be written; its range
+    auto place = [&]() -> uint32_t {
+        if (!f.totals) {
+            const uint2 r = f.ranges[tile];
+            return len && r.y <= f.limit ? r.x : ~0u;
+        }
+        uint32_t c[PER_TILE], sum = 0;
+        if (!pairs_said(f, (int)tile, c)) s_late = 1u;
+#pragma unroll
+        for (int q = 0; q < PER_TILE; q++) sum += c[q];
+        sum = wave_inclusive_scan(sum);
+        if (lane == 63) s_wave[0][wave] = sum;
+        __syncthreads();
+        uint32_t first = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; w++) first += s_wave[0][w];
+        if (s_late) return ~0u;
+        if (t == 0) f.ranges[tile] = len ? make_uint2(first, first + (uint32_t)len) : make_uint2(0u, 0u);
+        return len && first + (uint32_t)len <= f.limit ? first : ~0u;
+    };
+    auto word = [&](int i) {   // (any i: the first one stands in for those past the list's end)
+        const uint32_t g = mem.list[i < len ? i : 0];
+        return (uint64_t)__float_as_uint(f.depth[g]) << 32 | g;
+    };
+    if (len == 0 || len > TILE_SORT_SMALL) {
+        const uint32_t to = place();
+        if (to != ~0u)
+            for (int i = t; i < len; i += T) f.bucket[to + i] = word(i);
+        return;
+    }
+    uint64_t w[TILE_SORT_SMALL / T];
+#pragma unroll
+    for (int u = 0; u < TILE_SORT_SMALL / T; u++) w[u] = u * T < len ? word(t + u * T) : 0ull;
+    __syncthreads();   // (the list has been read: the sort's memory is the same)
+    sort_list<TILE_SORT_SMALL, T, 1024, false>(mem.sort, w, len, tile, [&](int u) { return w[u]; }, place, f.keys_out, f.vals_out);
 }
 
 // ---- radix sort -------------------------------------------------------------------------
@@ -1243,6 +1571,20 @@ hipError_t launch_tile_scatter(hipStream_t st, int64_t n, const fs_projected& pr
         else launch(k_tile_pairs<false, true, true>, bytes);
     } else if (cfg.compact_box) launch(k_tile_pairs<true, true, false>, lds);
     else launch(k_tile_pairs<false, true, false>, lds);
+    return hipGetLastError();
+}
+
+hipError_t launch_small_frame(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, int tiles_x, int num_tiles,
+                              uint32_t pair_limit, uint32_t* said, uint32_t call, uint2* ranges, uint32_t* tile_order, uint64_t* totals,
+                              uint32_t* rec_offsets, uint32_t* rec_counts, float* splats, uint64_t* bucket, uint64_t* keys_out, uint32_t* vals_out)
+{
+    const SmallFrame f = {n, reinterpret_cast<const ushort4*>(proj.rect), proj.depth, reinterpret_cast<const float2*>(proj.mean2d),
+                          reinterpret_cast<const float4*>(proj.conic_opacity), proj.rgb, proj.tiles_touched, tiles_x, num_tiles, pair_limit,
+                          said, call, ranges, tile_order, totals, rec_offsets, rec_counts,
+                          reinterpret_cast<float4*>(splats), bucket, keys_out, vals_out};
+    const dim3 grid((unsigned)(totals ? num_tiles + 1 + (n + SMALL_THREADS - 1) / SMALL_THREADS : num_tiles));
+    if (cfg.compact_box) hipLaunchKernelGGL(k_small_frame<true>, grid, dim3(SMALL_THREADS), 0, st, f, cfg);
+    else hipLaunchKernelGGL(k_small_frame<false>, grid, dim3(SMALL_THREADS), 0, st, f, cfg);
     return hipGetLastError();
 }
 

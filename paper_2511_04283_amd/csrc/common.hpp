@@ -443,6 +443,28 @@ hipError_t launch_tile_sorts(hipStream_t st, int num_tiles, int variants, uint32
                              const uint32_t* tile_order, uint64_t* bucket, uint64_t* keys_out, uint32_t* vals_out,
                              const BandPlaces& places);
 
+// The whole ordering of a small frame in one launch (k_small_frame): what launch_tile_count, launch_tile_scatter and the sort of lists up
+// to TILE_SORT_SMALL leave, except that the record places are in index order.  said: [SMALL_MAX_TILES] words, zeroed before the first launch and
+// whenever call, a number of 16 bits, starts again from 1.  Once buffers that were too small have grown, a second launch with totals null
+// writes the pairs to the ranges that the first one left.
+constexpr int SMALL_MAX_N = 16384;
+constexpr int SMALL_MAX_TILES = 1024;
+// Every tile looks at every Gaussian, so the launch grows with the product and the four that it replaces do not.  In a training step the
+// host has waited for the loss before and the GPU has nothing to do while it launches, so three launches fewer count in full; behind
+// a render's or a step's longer queue only the GPU's own time does.  Whole passes, the four launches -> this one, us:
+//   fs_train_step, Compact Box:  3k at 256x192 (0.6 M tests) 114 -> 95, 6k at 509x337 (4.2 M) 137 -> 124, 12k at 509x337 (8.7 M) 152 -> 142,
+//     16k at 509x337 (11.5 M) 162.5 -> 152.5
+//   render, squares and Compact Box:  3k at 256x192 36 -> 30 and 36.5 -> 32, 6k at 400x300 (2.9 M) 38 -> 34 and 41 -> 37, 9k at 400x300
+//     (4.3 M) 43 -> 41 and 45 -> 44, 9k at 580x400 (8.3 M) 41 -> 43 and 43.5 -> 47, 16k at 256x192 (3.1 M) 57 -> 58 and 56.5 -> 57.5
+//   forward and backward by separate calls:  3k at 256x192 71 -> 66 and 70 -> 67, 9k at 400x300 92 -> 89 and 91 -> 91, 16k at 256x192 131 -> 133
+inline bool small_frame(int64_t n, int num_tiles, bool training)
+{
+    return n > 0 && n <= (training ? SMALL_MAX_N : 10000) && num_tiles <= SMALL_MAX_TILES && n * num_tiles <= (training ? 12000000 : 4000000);
+}
+hipError_t launch_small_frame(hipStream_t st, int64_t n, const fs_projected& proj, const CfgDev& cfg, int tiles_x, int num_tiles,
+                              uint32_t pair_limit, uint32_t* said, uint32_t call, uint2* ranges, uint32_t* tile_order, uint64_t* totals,
+                              uint32_t* rec_offsets, uint32_t* rec_counts, float* splats, uint64_t* bucket, uint64_t* keys_out, uint32_t* vals_out);
+
 constexpr int RADIX_BLOCK_KEYS = 2048;  // keys ranked by one workgroup per pass
 constexpr int RADIX_BITS = 9;            // widest digit
 constexpr int RADIX_DIGITS = 1 << RADIX_BITS;

@@ -17,6 +17,8 @@ int stub_never = 0;                 // ... or, of 1: the totals, 2: the loss, ne
 int64_t stub_stale_flags = -1;
 int stub_syncs = 0;
 int stub_bands[3] = {0, 0, 0};
+// and orderings in one launch: their first launches, their second ones
+int stub_small[2] = {0, 0};
 
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -90,6 +92,14 @@ hipError_t launch_tile_count(hipStream_t, int64_t, const fs_projected&, const Cf
     stub_bands[0] += bands;
     const uint64_t pairs = (uint64_t)stub_pairs, four[4] = {pairs, pairs, pairs, 1};
     words(1, totals, four, 4);
+    return hipSuccess;
+}
+hipError_t launch_small_frame(hipStream_t, int64_t, const fs_projected&, const CfgDev&, int, int, uint32_t, uint32_t*, uint32_t, uint2*,
+                              uint32_t*, uint64_t* totals, uint32_t*, uint32_t*, float*, uint64_t*, uint64_t*, uint32_t*)
+{
+    const uint64_t pairs = (uint64_t)stub_pairs, four[4] = {pairs, pairs, pairs, 1};
+    stub_small[totals == nullptr]++;
+    if (totals) words(1, totals, four, 4);
     return hipSuccess;
 }
 hipError_t launch_tile_scatter(hipStream_t, int64_t, const fs_projected&, const CfgDev&, int, int, uint32_t, const uint2*, uint32_t*,

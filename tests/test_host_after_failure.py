@@ -32,20 +32,20 @@ def stub(tmp_path_factory):
 class Ctx:
     """A context on the stub and the arguments of its calls (arrays nobody reads)."""
 
-    def __init__(self, lib, pairs):
+    def __init__(self, lib, pairs, n=1):
         from paper_2511_04283_amd import binding as B
-        self.B, self.lib, self.h = B, lib, ctypes.c_void_p()
+        self.B, self.lib, self.h, self.n = B, lib, ctypes.c_void_p(), n
         lib.fs_last_error.restype = ctypes.c_char_p
         assert lib.fs_create(ctypes.byref(self.h), 0, None, None) == B.FS_OK
         self.room = ctypes.create_string_buffer(1 << 16)
         some = (ctypes.addressof(self.room) + 15) // 16 * 16
         fill = lambda s, names: [setattr(s, k, some) for k in names] and s
         self.cam = B.fs_camera(width=32, height=16, fx=16.0, fy=16.0)
-        self.g = fill(B.fs_gaussians(n=1, sh_degree=0), ("means", "scales", "quats", "opacities", "sh"))
+        self.g = fill(B.fs_gaussians(n=n, sh_degree=0), ("means", "scales", "quats", "opacities", "sh"))
         self.proj = fill(B.fs_projected(), [f for f, _ in B.fs_projected._fields_])
         self.grads = fill(B.fs_grads(), ("dmeans", "dscales", "dquats", "dopacities", "dsh", "dmean2d"))
         five = (ctypes.c_void_p * 5)(*[some] * 5)
-        self.state = B.fs_train_state(1, 0, five, five, five, five, some, some, some)
+        self.state = B.fs_train_state(n, 0, five, five, five, five, some, some, some)
         self.some = ctypes.c_void_p(some)
         self.pairs(pairs)
 
@@ -57,7 +57,7 @@ class Ctx:
         b = self.B.fs_bins()
         r = ctypes.byref
         self.lib.fs_set_record_mode(self.h, mode)
-        rc = self.lib.fs_bin_sort(self.h, r(self.proj), r(self.cam), ctypes.c_int64(1), r(b))
+        rc = self.lib.fs_bin_sort(self.h, r(self.proj), r(self.cam), ctypes.c_int64(self.n), r(b))
         if rc == self.B.FS_OK:
             rc = self.lib.fs_render_bwd(self.h, r(self.g), r(self.cam), r(self.proj), r(b), self.some, self.some, self.some,
                                         r(self.grads))
@@ -111,11 +111,16 @@ def set_int(stub, name, value):
     ctypes.c_int.in_dll(stub, name).value = value
 
 
+# (the ordering in one launch, and in several)
+FRAMES = [1, 20000]
+
+
+@pytest.mark.parametrize("n", FRAMES)
 @pytest.mark.parametrize("call", ["backward", "train"])
-def test_words_behind_a_long_queue_are_all_that_is_waited_for(stub, call):
+def test_words_behind_a_long_queue_are_all_that_is_waited_for(stub, call, n):
     """Totals and loss that come later than the host looks for without a pause: the call goes on with them, not when the stream
     has nothing left to do."""
-    c = Ctx(stub, pairs=100)
+    c = Ctx(stub, pairs=100, n=n)
     syncs = ctypes.c_int.in_dll(stub, "stub_syncs")
     getattr(c, call)(c.B.FS_RECORDS_DENSE)   # (arrays that grow wait for the stream)
     before = syncs.value
@@ -131,10 +136,11 @@ def test_words_behind_a_long_queue_are_all_that_is_waited_for(stub, call):
     stub.fs_destroy(c.h)
 
 
+@pytest.mark.parametrize("n", FRAMES)
 @pytest.mark.parametrize("words, call, message", [(1, "backward", b"totals"), (1, "train", b"totals"), (2, "train", b"loss")])
-def test_words_that_never_come(stub, words, call, message):
+def test_words_that_never_come(stub, words, call, message, n):
     """... are an error in every call that waits for them, and the next call does not set them anew before the stream is done."""
-    c = Ctx(stub, pairs=100)
+    c = Ctx(stub, pairs=100, n=n)
     step, B = getattr(c, call), c.B
     step(B.FS_RECORDS_DENSE)
     set_int(stub, "stub_never", words)
@@ -185,3 +191,22 @@ def test_placement_is_chosen_by_the_ordering_before(stub):
     c.cam.width = 129
     assert by_bands(M, 3 * M)
     stub.fs_destroy(c.h)
+
+
+def test_one_launch_is_chosen_by_gaussians_and_tiles(stub):
+    """The whole ordering in one launch up to the sizes where several are the faster way, further in a training step; a second launch
+    only where the buffers were too small (a new context's hold sixteen tiles a Gaussian and more)."""
+    launches = (ctypes.c_int * 2).in_dll(stub, "stub_small")
+    for training, most, tests in ((False, 10000, 4000000), (True, 16384, 12000000)):
+        for n, tiles in ((1, 1), (most, 1), (most + 1, 1), (1000, 1024), (1000, 1025), (tests // 1000, 1000), (tests // 1000 + 1, 1000)):
+            c = Ctx(stub, pairs=16 * n, n=n)
+            c.cam.width = 16 * tiles
+            for call in range(3):
+                if call == 1:
+                    c.pairs(100 * max(n, 1000))
+                before = list(launches)
+                c.train(c.B.FS_RECORDS_DENSE) if training else c.backward(c.B.FS_RECORDS_DENSE)
+                assert c.rc == c.B.FS_OK
+                small = n <= most and tiles <= 1024 and n * tiles <= tests
+                assert [x - y for x, y in zip(launches, before)] == [small, small and call == 1], (training, n, tiles)
+            stub.fs_destroy(c.h)
