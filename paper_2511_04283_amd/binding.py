@@ -12,6 +12,8 @@ from dataclasses import dataclass
 
 import torch
 
+from . import _marshal
+
 _PKG = os.path.dirname(os.path.abspath(__file__))
 # FASTGS_HIP_LIB names another build of the same library (e.g. an experimental variant); load_library says so on
 # stderr when it is used, so that no run takes a substituted library unnoticed
@@ -169,12 +171,9 @@ def default_config() -> fs_config:
 def make_camera(cam) -> fs_camera:
     """From any object with width,height,fx,fy,cx,cy,R(3x3),t(3) (e.g. scenes.Camera)."""
     import numpy as np
-    c = fs_camera()
-    c.width, c.height = int(cam.width), int(cam.height)
-    c.fx, c.fy, c.cx, c.cy = float(cam.fx), float(cam.fy), float(cam.cx), float(cam.cy)
-    c.R = (ctypes.c_float * 9)(*np.asarray(cam.R, dtype=np.float32).reshape(9).tolist())
-    c.t = (ctypes.c_float * 3)(*np.asarray(cam.t, dtype=np.float32).reshape(3).tolist())
-    return c
+    floats = lambda a, n: (ctypes.c_float * n).from_buffer_copy(np.ascontiguousarray(a, dtype=np.float32).reshape(n))
+    return fs_camera(int(cam.width), int(cam.height), float(cam.fx), float(cam.fy), float(cam.cx), float(cam.cy), floats(cam.R, 9),
+                     floats(cam.t, 3))
 
 
 def _ptr(t):
@@ -187,6 +186,19 @@ def _chk(t, dtype, shape=None, name="tensor"):
     if shape is not None and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name}: shape {tuple(t.shape)} != {tuple(shape)}")
     return t
+
+
+def _addresses(struct, offset, tensors, shapes, names, int32=0):
+    """The addresses of contiguous CUDA tensors of these shapes, one after the other from `offset` of the structure on: float32, and
+    int32 those whose bit is set."""
+    if _marshal.fill(struct, offset, tensors, int32, shapes) == len(tensors):
+        return
+    for k, t in enumerate(tensors):   # (one of them is not as it should be, or a subclass of Tensor)
+        dtype = torch.int32 if int32 >> k & 1 else torch.float32
+        ctypes.c_void_p.from_buffer(struct, offset + 8 * k).value = _chk(t, dtype, shapes[k], names[k]).data_ptr()
+
+
+_TRAIN_NAMES = ("param",) * 5 + ("m",) * 5 + ("v",) * 5 + ("acc",) * 5 + ("grad_accum", "abs_accum", "denom")
 
 
 @dataclass
@@ -211,14 +223,9 @@ class Gaussians:
 
     def struct(self) -> fs_gaussians:
         n, K = self.n, (self.sh_degree + 1) ** 2
-        f = torch.float32
-        _chk(self.means, f, (n, 3), "means"); _chk(self.scales, f, (n, 3), "scales")
-        _chk(self.quats, f, (n, 4), "quats"); _chk(self.opacities, f, (n,), "opacities")
-        _chk(self.sh, f, (n, K, 3), "sh")
-        g = fs_gaussians()
-        g.n, g.sh_degree = n, self.sh_degree
-        g.means, g.scales, g.quats = self.means.data_ptr(), self.scales.data_ptr(), self.quats.data_ptr()
-        g.opacities, g.sh = self.opacities.data_ptr(), self.sh.data_ptr()
+        g = fs_gaussians(n, self.sh_degree)
+        _addresses(g, fs_gaussians.means.offset, (self.means, self.scales, self.quats, self.opacities, self.sh),
+                   ((n, 3), (n, 3), (n, 4), (n,), (n, K, 3)), ("means", "scales", "quats", "opacities", "sh"))
         return g
 
 
@@ -233,11 +240,8 @@ class Projected:
     clamped: torch.Tensor
 
     def struct(self) -> fs_projected:
-        p = fs_projected()
-        p.mean2d, p.depth, p.conic_opacity = self.mean2d.data_ptr(), self.depth.data_ptr(), self.conic_opacity.data_ptr()
-        p.rgb, p.rect, p.tiles_touched = self.rgb.data_ptr(), self.rect.data_ptr(), self.tiles_touched.data_ptr()
-        p.clamped = self.clamped.data_ptr()
-        return p
+        return fs_projected(self.mean2d.data_ptr(), self.depth.data_ptr(), self.conic_opacity.data_ptr(), self.rgb.data_ptr(),
+                            self.rect.data_ptr(), self.tiles_touched.data_ptr(), self.clamped.data_ptr())
 
 
 @dataclass
@@ -538,15 +542,9 @@ class Context:
         if _chk(target, torch.float32, None, "target").numel() < 3 * cam.height * cam.width:
             raise ValueError(f"target: {tuple(target.shape)} holds no [3, {cam.height}, {cam.width}] image")
         shapes = ((n, 3), (n, K, 3), (n, 3), (n, 4), (n,))
-        t = fs_train_state()
-        t.n, t.sh_degree = n, int(sh_degree)
-        for group, name in ((params, "param"), (m, "m"), (v, "v"), (acc, "acc")):
-            out = getattr(t, name)
-            for k in range(5):
-                out[k] = _chk(group[k], torch.float32, shapes[k], name).data_ptr()
-        t.grad_accum = _chk(grad_accum, torch.float32, (n,), "grad_accum").data_ptr()
-        t.abs_accum = _chk(abs_accum, torch.float32, (n,), "abs_accum").data_ptr()
-        t.denom = _chk(denom, torch.int32, (n,), "denom").data_ptr()
+        t = fs_train_state(n, int(sh_degree))
+        _addresses(t, fs_train_state.param.offset, (*(group[k] for group in (params, m, v, acc) for k in range(5)), grad_accum, abs_accum, denom),
+                   shapes * 4 + ((n,),) * 3, _TRAIN_NAMES, 1 << 22)
         prm = fs_train_params(float(lam), (ctypes.c_float * 5)(*lr), float(beta1), float(beta2), float(eps), int(step),
                               int(bool(sum)), int(bool(update)))
         out3 = (ctypes.c_double * 3)()

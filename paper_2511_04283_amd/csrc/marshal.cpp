@@ -1,0 +1,64 @@
+// The tensors of a call, checked and turned into addresses without a Python statement for each of their properties.
+//
+// fill(struct, offset, tensors, int32, shapes) -> how many of the tensors, from the first on, are contiguous ones in GPU memory, of float
+// (int32 those whose bit of the mask is set) and of the given shapes: their addresses follow each other in `struct` (a writable buffer) from `offset` on.  It stops at the
+// first other one; the caller looks at that one itself (a subclass of Tensor may be fine, anything else is refused with a reason there).
+//
+// A training iteration names 23 arrays, and where the host has waited for the iteration before, the GPU stands still while they are looked
+// at: 16 us for the 23 in Python, 1 here.
+#include <torch/csrc/autograd/python_variable.h>
+
+namespace {
+
+// Takes over nothing; false (with no Python error set) where `shape` is not a tuple of the tensor's sizes.
+bool has_shape(const at::Tensor& t, PyObject* shape)
+{
+    if (!PyTuple_Check(shape) || PyTuple_GET_SIZE(shape) != t.dim()) return false;
+    for (int64_t k = 0; k < t.dim(); k++) {
+        const long long size = PyLong_AsLongLong(PyTuple_GET_ITEM(shape, k));
+        if (size == -1 && PyErr_Occurred()) { PyErr_Clear(); return false; }
+        if (size != t.size(k)) return false;
+    }
+    return true;
+}
+
+PyObject* fill(PyObject*, PyObject* const* args, Py_ssize_t count)
+{
+    if (count != 5 || !PyTuple_Check(args[2]) || !PyTuple_Check(args[4]) || PyTuple_GET_SIZE(args[2]) != PyTuple_GET_SIZE(args[4])) {
+        PyErr_SetString(PyExc_TypeError, "fill(struct, offset, tensors, int32, shapes): as many shapes as tensors, in tuples");
+        return nullptr;
+    }
+    const Py_ssize_t offset = PyLong_AsSsize_t(args[1]), n = PyTuple_GET_SIZE(args[2]);
+    if (offset == -1 && PyErr_Occurred()) return nullptr;
+    const unsigned long long ints = PyLong_AsUnsignedLongLong(args[3]);
+    if (ints == ~0ull && PyErr_Occurred()) return nullptr;
+    Py_buffer dst;
+    if (PyObject_GetBuffer(args[0], &dst, PyBUF_WRITABLE) != 0) return nullptr;
+    if (offset < 0 || offset > dst.len || (dst.len - offset) / (Py_ssize_t)sizeof(void*) < n) {
+        PyBuffer_Release(&dst);
+        PyErr_SetString(PyExc_ValueError, "fill: the addresses do not fit the structure");
+        return nullptr;
+    }
+    Py_ssize_t k = 0;
+    try {
+        for (; k < n; k++) {
+            PyObject* const object = PyTuple_GET_ITEM(args[2], k);
+            if (!THPVariable_CheckExact(object)) break;
+            const at::Tensor& t = THPVariable_Unpack(object);
+            const auto type = k < 64 && ints >> k & 1 ? at::kInt : at::kFloat;
+            if (!t.is_cuda() || t.scalar_type() != type || !has_shape(t, PyTuple_GET_ITEM(args[4], k)) || !t.is_contiguous()) break;
+            void* const at = t.data_ptr();
+            memcpy(static_cast<char*>(dst.buf) + offset + k * sizeof(void*), &at, sizeof(void*));
+        }
+    } catch (...) {   // (a tensor that has no such property: the caller's own look says what it is)
+    }
+    PyBuffer_Release(&dst);
+    return PyLong_FromSsize_t(k);
+}
+
+PyMethodDef methods[] = {{"fill", reinterpret_cast<PyCFunction>(reinterpret_cast<void*>(fill)), METH_FASTCALL, nullptr}, {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
