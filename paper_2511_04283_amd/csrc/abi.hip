@@ -507,9 +507,9 @@ static int bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam,
         return FS_OK;
     };
     if (small && ctx->keys[1].cap == 0) {
-        // a new context's buffers hold sixteen tiles a Gaussian, so that its first launch seldom needs a second one (a failure shows below)
-        for (ScratchBuf* b : {&ctx->keys[0], &ctx->keys[1]}) (void)ensure(ctx, *b, (size_t)n * 16 * sizeof(uint64_t), "keys");
-        (void)ensure(ctx, ctx->vals[0], (size_t)n * 16 * sizeof(uint32_t), "values");
+        // a new context's buffers hold four tiles a Gaussian, so that its first launch seldom needs a second one (a failure shows below)
+        for (ScratchBuf* b : {&ctx->keys[0], &ctx->keys[1]}) (void)ensure(ctx, *b, (size_t)n * 4 * sizeof(uint64_t), "keys");
+        (void)ensure(ctx, ctx->vals[0], (size_t)n * 4 * sizeof(uint32_t), "values");
     }
     // what the buffers hold
     uint64_t cap_pairs = 0;

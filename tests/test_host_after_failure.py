@@ -195,11 +195,11 @@ def test_placement_is_chosen_by_the_ordering_before(stub):
 
 def test_one_launch_is_chosen_by_gaussians_and_tiles(stub):
     """The whole ordering in one launch up to the sizes where several are the faster way, further in a training step; a second launch
-    only where the buffers were too small (a new context's hold sixteen tiles a Gaussian and more)."""
+    only where the buffers were too small (a new context's hold four tiles a Gaussian and more)."""
     launches = (ctypes.c_int * 2).in_dll(stub, "stub_small")
     for training, most, tests in ((False, 10000, 4000000), (True, 16384, 12000000)):
         for n, tiles in ((1, 1), (most, 1), (most + 1, 1), (1000, 1024), (1000, 1025), (tests // 1000, 1000), (tests // 1000 + 1, 1000)):
-            c = Ctx(stub, pairs=16 * n, n=n)
+            c = Ctx(stub, pairs=4 * n, n=n)
             c.cam.width = 16 * tiles
             for call in range(3):
                 if call == 1:
