@@ -8,6 +8,8 @@
 // is computed in a fixed IEEE fp32 operation order, left to right as written, with no fused
 // multiply-adds (this file is compiled with -ffp-contract=off), so that a CPU implementation
 // following the same order reproduces it bit for bit.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace fs {
@@ -74,6 +76,7 @@ struct Params {
     const float* scales;
     const float* quats;
     const float* opac;
+    __device__ __forceinline__ float mean(int64_t i, int k) const { return means[3 * i + k]; }
     __device__ __forceinline__ float scale(int64_t i, int k) const { return RAW ? expf(scales[3 * i + k]) : scales[3 * i + k]; }
     __device__ __forceinline__ float4 stored_quat(int64_t i) const { return *reinterpret_cast<const float4*>(quats + 4 * i); }
     __device__ __forceinline__ float4 quat(int64_t i) const
@@ -84,14 +87,37 @@ struct Params {
     __device__ __forceinline__ float sigma(int64_t i) const { return RAW ? logistic(opac[i]) : opac[i]; }
 };
 
+// The same of one Gaussian, read ahead of their use (a chain of memory latencies otherwise).
+template <bool RAW>
+struct ParamsAhead {
+    float m[3], s[3], o;
+    float4 q;
+    __device__ __forceinline__ ParamsAhead(const Params<RAW>& par, int64_t i, bool wanted) : m{}, s{}, o(0.f), q(make_float4(0.f, 0.f, 0.f, 0.f))
+    {
+        if (!wanted) return;
+        for (int k = 0; k < 3; k++) { m[k] = par.means[3 * i + k]; s[k] = par.scales[3 * i + k]; }
+        q = par.stored_quat(i);
+        o = par.opac[i];
+    }
+    __device__ __forceinline__ float mean(int64_t, int k) const { return m[k]; }
+    __device__ __forceinline__ float scale(int64_t, int k) const { return RAW ? expf(s[k]) : s[k]; }
+    __device__ __forceinline__ float4 stored_quat(int64_t) const { return q; }
+    __device__ __forceinline__ float4 quat(int64_t) const
+    {
+        float inv;
+        return RAW ? unit_quat(q, inv) : q;
+    }
+    __device__ __forceinline__ float sigma(int64_t) const { return RAW ? logistic(o) : o; }
+};
+
 // `sigma` (the opacity) only matters with the Compact Box, whose box depends on it.  With the Compact
 // Box, s.visible still has to be and-ed with "some tile of the box meets the ellipse" by the caller.
-template <bool RAW>
-__device__ __forceinline__ void project(const Params<RAW>& par, float sigma, int64_t i, const CamDev& cam,
+template <typename Par>
+__device__ __forceinline__ void project(const Par& par, float sigma, int64_t i, const CamDev& cam,
                                         const CfgDev& cfg, Splat& s)
 {
     s.visible = false;
-    const float m0 = par.means[3 * i], m1 = par.means[3 * i + 1], m2 = par.means[3 * i + 2];
+    const float m0 = par.mean(i, 0), m1 = par.mean(i, 1), m2 = par.mean(i, 2);
     s.tx = cam.R[0] * m0 + cam.R[1] * m1 + cam.R[2] * m2 + cam.t[0];
     s.ty = cam.R[3] * m0 + cam.R[4] * m1 + cam.R[5] * m2 + cam.t[1];
     s.tz = cam.R[6] * m0 + cam.R[7] * m1 + cam.R[8] * m2 + cam.t[2];
@@ -192,13 +218,14 @@ __device__ __forceinline__ void project(const Params<RAW>& par, float sigma, int
 }
 
 // Unit direction from the camera centre (-R^T t) to the mean, and its length.
-__device__ __forceinline__ void view_dir(const float* means, int64_t i, const CamDev& cam,
+template <typename Par>
+__device__ __forceinline__ void view_dir(const Par& par, int64_t i, const CamDev& cam,
                                          float d[3], float& len)
 {
     float dir[3];
     for (int k = 0; k < 3; k++) {
         const float campos = -(cam.R[0 + k] * cam.t[0] + cam.R[3 + k] * cam.t[1] + cam.R[6 + k] * cam.t[2]);
-        dir[k] = means[3 * i + k] - campos;
+        dir[k] = par.mean(i, k) - campos;
     }
     len = sqrtf(dir[0] * dir[0] + dir[1] * dir[1] + dir[2] * dir[2]);
     d[0] = dir[0] / len;
@@ -280,7 +307,7 @@ __global__ __launch_bounds__(256) void k_preprocess(int64_t n, const float* __re
         rc = make_ushort4((unsigned short)s.x0, (unsigned short)s.y0, (unsigned short)s.x1, (unsigned short)s.y1);
         tt = hits;
         float d[3], len;
-        view_dir(means, i, cam, d, len);
+        view_dir(par, i, cam, d, len);
         constexpr int K = (DEG + 1) * (DEG + 1);
         float Y[K];
         sh_basis(DEG, d[0], d[1], d[2], Y);
@@ -379,7 +406,7 @@ __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
     float* __restrict__ d_mean2d, float* __restrict__ d_conic /* may be null */,
     float* __restrict__ d_rgb /* may be null */, float* __restrict__ d_abs /* may be null */, TrainDev train)
 {
-    const Params<OUT != BWD_GRADS> par = {means, scales, quats, opac};
+    const Params<OUT != BWD_GRADS> stored = {means, scales, quats, opac};
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     constexpr int K = (DEG + 1) * (DEG + 1);
     constexpr int F = 3 * K;                      // SH floats per Gaussian
@@ -394,7 +421,8 @@ __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const bool in_range = i < n;
     // (a Gaussian with tiles_touched > 0 passed the forward pass's culling: the count stands in for visibility)
-    const bool vis0 = in_range && touched[i] > 0;
+    const uint32_t tiles = in_range ? touched[i] : 0u, offset = in_range ? offsets[i] : 0u, places = in_range ? rec_counts[i] : 0u;
+    const bool vis0 = tiles > 0;
     const int64_t wave_first = (int64_t)blockIdx.x * blockDim.x + wave * 64;
     const int valid_rows = (int)min((int64_t)64, max((int64_t)0, n - wave_first));
     constexpr int NV = (HALF / 4 * F + 63) / 64;  // float4 per lane for the SH rows of a full half
@@ -413,6 +441,15 @@ __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
         pre = h;
     };
     request_half(0);
+    // What a Gaussian's chain reads at its end (mean, scales, quaternion, opacity) is requested with what it reads at its beginning: 3 M Gaussians
+    // 355 -> 333 us, 500k 82 -> 75, 4k 7.6 -> 7.0, 300k summing 65 -> 64 (with the run's ends from two lanes instead of twelve shuffles).
+    // With the update's registers on top they would spill.  (The second half's SH rows requested here as well where they are short, at
+    // degrees 0 and 1: no difference.)
+    constexpr bool AHEAD = OUT != BWD_UPDATE || DEG < 2;
+    const std::conditional_t<AHEAD, ParamsAhead<OUT != BWD_GRADS>, Params<OUT != BWD_GRADS>> par = [&] {
+        if constexpr (AHEAD) return ParamsAhead<OUT != BWD_GRADS>(stored, i, OUT == BWD_GRADS ? vis0 : in_range);
+        else return stored;
+    }();
 
     // ---- screen-space gradients: sum of this Gaussian's pair records, in tile order ----------
     // The 64 Gaussians of a wavefront own one contiguous run of records.  The wavefront streams that
@@ -420,13 +457,13 @@ __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
     float4 ra = make_float4(0.f, 0.f, 0.f, 0.f), rb = ra;
     float rc = 0.f, rabs_x = 0.f, rabs_y = 0.f;
     {
-        const uint32_t off = in_range ? offsets[i] : 0u;
-        const uint32_t cnt = in_range && touched[i] ? rec_counts[i] : 0u;
-        uint32_t lo_all = cnt ? off : 0xffffffffu, hi_all = cnt ? off + cnt : 0u;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            lo_all = min(lo_all, (uint32_t)__shfl_xor((int)lo_all, d, 64));
-            hi_all = max(hi_all, (uint32_t)__shfl_xor((int)hi_all, d, 64));
+        // (the places of a wavefront's Gaussians ascend: its run starts at the first one's that has any and ends at the last one's)
+        const uint32_t off = offset, cnt = vis0 ? places : 0u;
+        const uint64_t some = __ballot(cnt != 0u);
+        uint32_t lo_all = 0u, hi_all = 0u;
+        if (some) {
+            lo_all = (uint32_t)__builtin_amdgcn_readlane((int)off, __builtin_ctzll(some));
+            hi_all = (uint32_t)__builtin_amdgcn_readlane((int)(off + cnt), 63 - __builtin_clzll(some));
         }
         float4* buf = reinterpret_cast<float4*>(s_buf[wave]);
         // Chunk k+1 is requested as soon as chunk k has gone from registers to LDS, so that its latency passes
@@ -699,7 +736,7 @@ __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
 #pragma unroll
             for (int k = 0; k < K; k++) Y[k] = 0.f;
             if (vis0) {
-                view_dir(means, i, cam, d, len);
+                view_dir(par, i, cam, d, len);
                 sh_basis(DEG, d[0], d[1], d[2], Y);
                 gcol[0] = clamped[3 * i] ? 0.f : ra.x;
                 gcol[1] = clamped[3 * i + 1] ? 0.f : ra.y;
