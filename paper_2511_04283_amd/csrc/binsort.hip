@@ -1041,8 +1041,8 @@ __global__ __launch_bounds__(THREADS, CAP == TILE_SORT_MAX ? 8 : 4) void k_tile_
 // Gaussians each, sum the areas before theirs and pack records and record places; the last one leaves the other two totals.
 // A tile's word in `said` is the call's number << 16 | its pairs, past all caches, so that nothing has to be cleared or fenced.  A
 // workgroup waits only for workgroups of lower numbers that wait for nothing before they speak, so the lowest silent one is always
-// under way or next in line; and no wait is longer than SMALL_POLLS looks: after that its workgroup writes nothing, the totals stay
-// unset and the host says so.
+// under way or next in line; and no wait is longer than SMALL_POLLS looks: after that its workgroup writes nothing and takes its
+// word back, the totals stay unset and the host says so.
 // A list longer than TILE_SORT_SMALL is left unordered in `bucket` for the launches that take longer ones.
 // What bounds it are its chains: the rectangles' loads (n / 256 of a thread, 16 at a time), list and sort in LDS, and the wait.
 // fs_bin_sort, back to back, in four launches and in this one, us: 4k at 128x128 19.6 -> 12, 3k at 509x337 20.5 -> 15.6, 9k at 400x300 20.1 -> 17.8,
@@ -1196,7 +1196,10 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_frame(SmallFrame f, Cfg
         most = wave_inclusive_max(most);
         if (lane == 63) { s_wave[0][wave] = sum; s_wave[1][wave] = most; }
         __syncthreads();
-        if (s_late) return;
+        if (s_late) {   // (the host says so; sorts of long lists that are enqueued already take what is here as tiles)
+            for (int k = t; k < f.num_tiles; k += T) f.order[k] = (uint32_t)k;
+            return;
+        }
         if (wave == 0) {
             uint32_t v[NB / 64], all = 0;
 #pragma unroll
@@ -1313,7 +1316,10 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_frame(SmallFrame f, Cfg
         uint32_t first = 0;
 #pragma unroll
         for (int w = 0; w < WAVES; w++) first += s_wave[0][w];
-        if (s_late) return ~0u;
+        if (s_late) {   // (its word is taken back, so that the totals stay unset)
+            if (t == 0) __hip_atomic_store(&f.said[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return ~0u;
+        }
         if (t == 0) f.ranges[tile] = len ? make_uint2(first, first + (uint32_t)len) : make_uint2(0u, 0u);
         return len && first + (uint32_t)len <= f.limit ? first : ~0u;
     };
