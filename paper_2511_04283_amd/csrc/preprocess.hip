@@ -392,10 +392,15 @@ __device__ __forceinline__ float wave_sum_to_last(float v)
 // stored ones, the chain goes on through the activations, the densification statistics are added up, and either the
 // Adam update of the Gaussian's 11 + 3K parameters follows at once (BWD_UPDATE) or its gradients join the running sums
 // (BWD_SUM).  All of it is bound by memory, and this way the gradients (4 bytes for each parameter) are never written and
-// read again.  500k Gaussians, SH degree 3: 246 us in eight launches before, 209 in this one (1.7 KB per Gaussian at 4.1
-// TB/s); 300k, summing: 110 us in eight launches, 64 in this one.
+// read again.  500k Gaussians, SH degree 3: 246 us in eight launches before, 158 in this one (1.5 KB per Gaussian at 4.8
+// TB/s); 300k, summing: 110 us in eight launches, 60 in this one.
+// Wavefronts per SIMD that the registers are shared out for.  The update holds the SH rows of both halves from the start on and has nine 16-byte
+// words per lane in flight behind them: it needs 160 registers.  At 128 (four wavefronts) it spilled 49 of them, read the rows twice and
+// took one word of each array at a time.  500k Gaussians, SH degree 3: 206 us so; 180 at three wavefronts, 172 and 170 with two and three
+// words of each array, 158 with the rows kept; 300k, summing: 64.5 at four, 60 at three, 60 at two.  The gradients alone: the same at three and four.
+constexpr int bwd_waves(int deg, BwdOut out) { return deg < 2 || out == BWD_GRADS ? 4 : out == BWD_SUM ? 3 : 2; }
 template <int DEG, bool SPARSE, BwdOut OUT>
-__global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
+__global__ __launch_bounds__(256, bwd_waves(DEG, OUT)) void k_preprocess_bwd(
     int64_t n, const float* means, const float* scales, const float* quats,
     const float* opac, const float* sh /* (the five of them are train.p in a training iteration, written there: no __restrict__) */,
     CamDev cam, CfgDev cfg, const uint8_t* __restrict__ clamped, const uint32_t* __restrict__ touched,
@@ -406,7 +411,6 @@ __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
     float* __restrict__ d_mean2d, float* __restrict__ d_conic /* may be null */,
     float* __restrict__ d_rgb /* may be null */, float* __restrict__ d_abs /* may be null */, TrainDev train)
 {
-    const Params<OUT != BWD_GRADS> stored = {means, scales, quats, opac};
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     constexpr int K = (DEG + 1) * (DEG + 1);
     constexpr int F = 3 * K;                      // SH floats per Gaussian
@@ -428,9 +432,11 @@ __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
     constexpr int NV = (HALF / 4 * F + 63) / 64;  // float4 per lane for the SH rows of a full half
     // The SH rows of the first half are requested before the pair records are streamed, so that the two latencies
     // overlap (they wait in registers: the LDS buffer serves the records first).
-    float4 vh[NV];
-    int pre = -1;   // the half whose rows are on their way into vh (uniform over the wavefront)
-    auto request_half = [&](int h) {
+    // (KEEP: those of both halves, and they stay there for the update)
+    constexpr bool KEEP = OUT == BWD_UPDATE && DEG >= 2;
+    float4 vh[NV], vh1[KEEP ? NV : 1];
+    bool pre = false, pre1 = false;   // the half's rows are on their way into vh, vh1 (uniform over the wavefront)
+    auto request_half = [&](int h, float4* vh, bool& pre) {
         if (valid_rows < (h + 1) * HALF || __ballot(vis0 && (lane / HALF) == h) == 0) return;
         const float4* src4 = reinterpret_cast<const float4*>(sh + (wave_first + h * HALF) * F);
 #pragma unroll
@@ -438,18 +444,13 @@ __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
             const int q = lane + 64 * it;
             vh[it] = q < HALF / 4 * F ? src4[q] : make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        pre = h;
+        pre = true;
     };
-    request_half(0);
+    request_half(0, vh, pre);
+    if constexpr (KEEP) request_half(1, vh1, pre1);
     // What a Gaussian's chain reads at its end (mean, scales, quaternion, opacity) is requested with what it reads at its beginning: 3 M Gaussians
-    // 355 -> 333 us, 500k 82 -> 75, 4k 7.6 -> 7.0, 300k summing 65 -> 64 (with the run's ends from two lanes instead of twelve shuffles).
-    // With the update's registers on top they would spill.  (The second half's SH rows requested here as well where they are short, at
-    // degrees 0 and 1: no difference.)
-    constexpr bool AHEAD = OUT != BWD_UPDATE || DEG < 2;
-    const std::conditional_t<AHEAD, ParamsAhead<OUT != BWD_GRADS>, Params<OUT != BWD_GRADS>> par = [&] {
-        if constexpr (AHEAD) return ParamsAhead<OUT != BWD_GRADS>(stored, i, OUT == BWD_GRADS ? vis0 : in_range);
-        else return stored;
-    }();
+    // 355 -> 333 us, 500k 82 -> 75, 4k 7.6 -> 7.0 (with the run's ends from two lanes instead of twelve shuffles).
+    const ParamsAhead<OUT != BWD_GRADS> par(Params<OUT != BWD_GRADS>{means, scales, quats, opac}, i, OUT == BWD_GRADS ? vis0 : in_range);
 
     // ---- screen-space gradients: sum of this Gaussian's pair records, in tile order ----------
     // The 64 Gaussians of a wavefront own one contiguous run of records.  The wavefront streams that
@@ -612,10 +613,10 @@ __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
             }
         }
     };
-    auto load_half = [&](int h) {
+    auto load_half = [&](int h, const float4 (&vh)[NV], bool pre) {
         const int vr = min(HALF, max(0, valid_rows - h * HALF));
         const float* src = sh + (wave_first + h * HALF) * F;
-        if (pre == h) {
+        if (pre) {
             commit(vh);
         } else if (vr == HALF) {
             // all loads issued before the first LDS write
@@ -659,7 +660,7 @@ __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
         adam_one(p.w, g.w, m.w, v.w, train.adam, train.lr[k]);
     };
     auto plus4 = [](const float4& a, const float4& b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); };
-    auto store_half = [&](int h) {
+    auto store_half = [&](int h, const float4 (&vh)[NV], bool pre) {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         const int vr = min(HALF, max(0, valid_rows - h * HALF));
@@ -675,8 +676,8 @@ __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
                 }
                 return make_float4(comp[0], comp[1], comp[2], comp[3]);
             };
-            // 16-byte words per lane in flight (an update takes three arrays: with more than one word of each the registers spill)
-            constexpr int GROUP = OUT == BWD_UPDATE && NV > 2 ? 1 : NV;
+            // 16-byte words per lane in flight (an update takes three arrays)
+            constexpr int GROUP = KEEP && NV > 3 ? 3 : NV;
 #pragma unroll
             for (int it0 = 0; it0 < NV; it0 += GROUP) {
                 float4 p[GROUP], m[GROUP], v[GROUP];
@@ -685,7 +686,8 @@ __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
                     for (int u = 0; u < GROUP; u++) {
                         const int q = lane + 64 * (it0 + u);
                         if (it0 + u >= NV || q >= HALF / 4 * F) continue;
-                        p[u] = reinterpret_cast<const float4*>((OUT == BWD_SUM ? train.acc[1] : train.p[1]) + base)[q];
+                        if (KEEP && pre) p[u] = vh[it0 + u];
+                        else p[u] = reinterpret_cast<const float4*>((OUT == BWD_SUM ? train.acc[1] : train.p[1]) + base)[q];
                         if (OUT == BWD_UPDATE) {
                             m[u] = reinterpret_cast<const float4*>(train.m[1] + base)[q];
                             v[u] = reinterpret_cast<const float4*>(train.v[1] + base)[q];
@@ -725,10 +727,10 @@ __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
     float wk[K];
 #pragma unroll
     for (int k = 0; k < K; k++) wk[k] = 0.f;
-    for (int h = 0; h < 64 / HALF; h++) {
+    auto one_half = [&](int h, const float4 (&vh)[NV], bool pre) {
         // (culled Gaussians come in runs -- whole clusters outside the frustum -- so a half often needs no
         // coefficients at all: its gradients are zeros whatever the buffer holds)
-        if (__ballot(vis0 && (lane / HALF) == h) != 0) load_half(h);
+        if (__ballot(vis0 && (lane / HALF) == h) != 0) load_half(h, vh, pre);
         // (requesting the second half's rows here, while the first is worked on, was measured slower: the registers
         // they wait in take a wavefront per SIMD away)
         if ((lane / HALF) == h && in_range) {
@@ -751,7 +753,14 @@ __global__ __launch_bounds__(256, 4) void k_preprocess_bwd(
                 c[3 * k + 2] = gcol[2] * Y[k];
             }
         }
-        store_half(h);
+        store_half(h, vh, pre);
+    };
+    static_assert(64 / HALF == 2, "two halves");
+    if constexpr (KEEP) {
+        one_half(0, vh, pre);
+        one_half(1, vh1, pre1);
+    } else {
+        for (int h = 0; h < 2; h++) one_half(h, vh, h == 0 && pre);
     }
     Splat s;
     s.visible = false;
