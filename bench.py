@@ -31,7 +31,7 @@ BWD_FLOPS_PER_EVAL = 11
 BWD_FLOPS_PER_BLEND = 66    # exp 14; alpha 2; 1/(1-a), T, w 4; colour/alpha grads 17; conic/mean grads 20; 9-value sum 9
 PEAK_FP32_TFLOPS = 157.3    # MI355X vector fp32, 256 CU x 4 SIMD x 16 lanes x 2 (packed, or two wavefronts at a time) x 2 (FMA) x 2.4 GHz
 PEAK_HBM_GBS = 8000.0
-KERNEL_OF_GROUP = {"preprocess": "k_preprocess", "scan": "k_scan_*", "emit_pairs": "k_tile_pairs (count) + k_tile_layout",
+KERNEL_OF_GROUP = {"preprocess": "k_preprocess", "scan": "k_scan_*", "emit_pairs": "k_tile_pairs (count) + k_tile_layout, or k_small_frame",
                    "order_pairs": "k_tile_pairs (placement) + k_band_split + k_tile_sort", "tile_ranges": "k_tile_ranges + k_tile_order",
                    "render_fwd": "k_render_fwd", "l1_grad": "k_fold_tile_stats", "photo_loss": "k_ssim_*",
                    "render_bwd": "k_render_bwd", "preprocess_bwd": "k_preprocess_bwd", "error_mask": "k_err_*",

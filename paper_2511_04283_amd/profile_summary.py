@@ -31,7 +31,7 @@ SQ_COUNTERS = "SQ_WAVES SQ_INSTS_VALU SQ_INSTS_SALU SQ_INSTS_LDS SQ_ACTIVE_INST_
 # kernel-name prefixes of every timing group of bench.py (`kernels_ms`), for the default step
 GROUPS = {
     "preprocess": ["k_preprocess<"],
-    "emit_pairs": ["k_tile_pairs<false, false,", "k_tile_pairs<true, false,", "k_tile_layout"],
+    "emit_pairs": ["k_tile_pairs<false, false,", "k_tile_pairs<true, false,", "k_tile_layout", "k_small_frame<"],
     "order_pairs": ["k_tile_pairs<false, true,", "k_tile_pairs<true, true,", "k_band_split", "k_tile_sort<"],
     "render_fwd": ["k_render_fwd<true, true>"],
     "l1_grad": ["k_fold_tile_stats"],
