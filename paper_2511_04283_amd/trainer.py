@@ -81,8 +81,8 @@ class Trainer:
                                  groups(self.acc), self.grad_accum, self.abs_accum, self.denom, groups(c.lr), c.lam, eps=c.eps,
                                  step=self.updates + 1, sum=interval != 1, update=last)[2]
         # fs_train_step returns with the backward pass and the update on their way.  A program that orders its own reads behind
-        # them may call it itself and keep what this wait costs at every size: 12k Gaussians at 509x337 101 and 139 us per
-        # iteration, 500k at 1600x1064 669 and 707.
+        # them may call it itself and keep what this wait costs at every size: 12k Gaussians at 509x337 117 and 133 us per
+        # iteration, 500k at 1600x1064 628 and 647.
         ctx.stream.synchronize()
         self.iteration += 1   # (not where the call was refused)
         self.pending += 1
