@@ -197,6 +197,9 @@ int fs_preprocess(fs_ctx *ctx, const fs_gaussians *g, const fs_camera *cam, fs_p
  * kernel behind the counting one stores where the host sees them; that kernel may still be writing the ranges, the
  * splats and the record places then.  From a context's second per-tile ordering on, placement and sorts are enqueued
  * ahead of that wait, bounded by what the context's buffers hold, and repeated if the totals say they did not fit).
+ * Small frames are ordered by one kernel whose workgroups wait for each other, for a second or so at most.  Where that does not
+ * do (another stream's kernel may hold the place meant for one of them for longer) the call orders the frame with the usual
+ * kernels instead, behind that one: the same bins, later.
  * Errors: FS_EINVAL, FS_ENOMEM, FS_EHIP, FS_ECAPACITY (n, P or the candidate tile count >= 2^31). */
 int fs_bin_sort(fs_ctx *ctx, const fs_projected *proj, const fs_camera *cam, int64_t n, fs_bins *out);
 

@@ -53,7 +53,7 @@ struct fs_ctx {
     uint64_t* total_dev = nullptr;   // device: totals [4]: pairs, backward records, pairs counted per tile, longest tile list
     uint64_t* total_host = nullptr;  // pinned host block of four totals (copied from total_dev, or written by k_tile_layout)
     uint64_t* counters = nullptr;    // device: TILE_COUNTERS of launch_tile_count (the first is zero between calls), and behind them the
-                                     // tiles' words of launch_small_frame
+                                     // SMALL_WORDS of launch_small_frame
     uint32_t small_call = 0;         // the number of the last launch_small_frame
     bool counters_dirty = false;     // a call failed where it may have left that one as it was
     bool totals_pending = false;     // a call failed between the launch that writes total_host and its arrival
@@ -279,10 +279,12 @@ int record_buffers(fs_ctx* ctx, const fs_bins* bins, bool sparse)
 // training iteration at 12k and 509x337 142.6 and 134.0, ten score views at 100k and 980x545 1460 and 1419.
 // Words that do not come within SPIN_MS stand behind a long queue or never come.  From then on the host sleeps between its looks and
 // asks the stream for its errors; it still goes on with the last word, not with what is enqueued behind the kernel that stores it.
-// FS_EHIP, with the caller's *_pending left as it is: the stream has failed, or is done and a word is still unset.
+// FS_EHIP, with the caller's *_pending left as it is: the stream has failed, or is done and a word is still unset.  (Without a message
+// `never` the latter is NEVER_CAME: the caller has another way.)
 constexpr uint64_t UNSET_WORD = 0xfff7a5a55a5aa55bull;   // (as a double a NaN that no conversion or arithmetic makes)
 constexpr int SPIN_MS = 20;
 constexpr int SLEEP_US = 50;
+constexpr int NEVER_CAME = 1;   // (no fs_status)
 void unset_words(uint64_t* p, int count)
 {
     for (int k = 0; k < count; k++) p[k] = UNSET_WORD;
@@ -297,7 +299,7 @@ int wait_for_words(fs_ctx* ctx, const uint64_t* p, int count, const char* never)
             if (spins % 1024 || std::chrono::steady_clock::now() <= until) continue;
             const hipError_t e = hipStreamQuery(ctx->stream);
             if (w[k] != UNSET_WORD) break;
-            if (e == hipSuccess) return fail(ctx, FS_EHIP, never);
+            if (e == hipSuccess) return never ? fail(ctx, FS_EHIP, never) : NEVER_CAME;
             if (e != hipErrorNotReady) FS_HIP(e, "hipStreamQuery");
             (void)hipGetLastError();   // (or the next launch's check would report that the stream was busy)
             std::this_thread::sleep_for(std::chrono::microseconds(SLEEP_US));
@@ -396,7 +398,7 @@ int fs_create(fs_ctx** out, int device, void* hip_stream, const fs_config* cfg)
         fs_destroy(ctx);
         return FS_EHIP;
     }
-    constexpr size_t counter_bytes = TILE_COUNTERS * sizeof(uint64_t) + SMALL_MAX_TILES * sizeof(uint32_t);
+    constexpr size_t counter_bytes = TILE_COUNTERS * sizeof(uint64_t) + SMALL_WORDS * sizeof(uint32_t);
     if (hipMalloc(reinterpret_cast<void**>(&ctx->counters), counter_bytes) != hipSuccess ||
         hipMemset(ctx->counters, 0, counter_bytes) != hipSuccess ||
         hipMalloc(reinterpret_cast<void**>(&ctx->total_dev), 4 * sizeof(uint64_t)) != hipSuccess ||
@@ -450,8 +452,9 @@ int fs_preprocess(fs_ctx* ctx, const fs_gaussians* g, const fs_camera* cam, fs_p
     return FS_OK;
 }
 
-// training: the call is part of fs_train_step (chooses the launches, see small_frame)
-static int bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int64_t n, bool training, fs_bins* out)
+// one_launch: the whole ordering may take one launch (small_frame says where; training: the call is part of fs_train_step).  NEVER_CAME
+// when that launch's workgroups have waited too long for each other: the general launches have to order the frame.
+static int order_pairs(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int64_t n, bool training, bool one_launch, fs_bins* out)
 {
     if (!ctx) return FS_EINVAL;
     CamDev cd;
@@ -473,7 +476,7 @@ static int bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam,
     uint32_t* const ttotal_p = ranges_p + 3 * (size_t)tiles;
     uint32_t* const tcount_p = ranges_p + 4 * (size_t)tiles;
     const bool bucketed = ctx->cfg.sort_mode == FS_SORT_AUTO && tiles <= TILE_LDS_MAX_TILES;
-    const bool small = bucketed && small_frame(n, tiles, training);   // (one launch for all but the sorts of long lists)
+    const bool small = one_launch && bucketed && small_frame(n, tiles, training);   // (one launch for all but the sorts of long lists)
     const bool bands = !small && placed_by_bands(n, tiles, ctx->candidates_before);   // (then keys[0] is placed into, and split into keys[1] ahead of the sorts)
     const int split = bands ? TS_SPLIT : 0;
     const BandPlaces places = bands ? BandPlaces{ttotal_p, reinterpret_cast<uint2*>(tcount_p + (size_t)TILE_COPIES * tiles)} : BandPlaces{};
@@ -522,7 +525,7 @@ static int bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam,
     auto small_order = [&](uint64_t limit, uint64_t* totals) {
         uint32_t* const said = reinterpret_cast<uint32_t*>(ctx->counters + TILE_COUNTERS);
         if (totals && ++ctx->small_call == 65536) {
-            const hipError_t e = launch_fill_u32(st, said, 0u, SMALL_MAX_TILES);
+            const hipError_t e = launch_fill_u32(st, said, 0u, SMALL_WORDS);
             if (e != hipSuccess) { ctx->small_call--; return e; }
             ctx->small_call = 1;
         }
@@ -599,7 +602,7 @@ static int bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam,
         }
     }
     if (bucketed) {
-        FS_TRY(wait_for_words(ctx, ctx->total_host, 4, "fs_bin_sort: the totals did not arrive"));
+        FS_TRY(wait_for_words(ctx, ctx->total_host, 4, small ? nullptr : "fs_bin_sort: the totals did not arrive"));
         ctx->totals_pending = false;
     } else {
         FS_HIP(hipEventSynchronize(ctx->totals_event), "hipEventSynchronize");
@@ -690,6 +693,13 @@ static int bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam,
     out->tile_order = static_cast<const uint32_t*>(ctx->ranges.ptr) + 2 * (size_t)tiles;
     out->generation = ctx->generation;
     return FS_OK;
+}
+
+// training: the call is part of fs_train_step
+static int bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int64_t n, bool training, fs_bins* out)
+{
+    const int rc = order_pairs(ctx, proj, cam, n, training, true, out);
+    return rc == NEVER_CAME ? order_pairs(ctx, proj, cam, n, training, false, out) : rc;
 }
 
 int fs_bin_sort(fs_ctx* ctx, const fs_projected* proj, const fs_camera* cam, int64_t n, fs_bins* out)

@@ -1039,16 +1039,16 @@ __global__ __launch_bounds__(THREADS, CAP == TILE_SORT_MAX ? 8 : 4) void k_tile_
 // it, with the Compact Box), says how many they are, orders them in LDS, and writes them behind the pairs of the tiles before it once
 // all of those have said theirs.  Workgroup num_tiles waits for all tiles and leaves their order and two totals.  The others, 256
 // Gaussians each, sum the areas before theirs and pack records and record places; the last one leaves the other two totals.
-// A tile's word in `said` is the call's number << 16 | its pairs, past all caches, so that nothing has to be cleared or fenced.  A
-// workgroup waits only for workgroups of lower numbers that wait for nothing before they speak, so the lowest silent one is always
-// under way or next in line; and no wait is longer than SMALL_POLLS looks: after that its workgroup writes nothing and takes its
-// word back, the totals stay unset and the host says so.
+// What the workgroups say to each other is in small_words.hpp: words with the call's number in them, past all caches, so that nothing has
+// to be cleared or fenced.  A workgroup waits only for workgroups of lower numbers that wait for nothing before they speak, so the
+// lowest silent one is always under way or next in line; and no wait is longer than SMALL_POLLS looks (a second, in which another
+// stream's kernel may hold the place that the silent one is meant for).  After that the totals stay unset, or this workgroup's pairs and
+// range are whole all the same; unset totals make the host order the frame with the general launches.
 // A list longer than TILE_SORT_SMALL is left unordered in `bucket` for the launches that take longer ones.
 // What bounds it are its chains: the rectangles' loads (n / 256 of a thread, 16 at a time), list and sort in LDS, and the wait.
 // fs_bin_sort, back to back, in four launches and in this one, us: 4k at 128x128 19.6 -> 12, 3k at 509x337 20.5 -> 15.6, 9k at 400x300 20.1 -> 17.8,
 // with splats of twelve tiles 24.8 -> 17.3; a new context's first render at 4k 147 -> 98.  Lists of up to 128 ordered by comparing each word
 // with all others instead of the sort: no difference (within 2 %).
-constexpr int SMALL_THREADS = 256;
 constexpr int SMALL_PER = 16;          // rectangles a thread has in flight
 constexpr int SMALL_POLLS = 1 << 20;
 struct SmallFrame {
@@ -1061,7 +1061,7 @@ struct SmallFrame {
     const uint32_t* tiles_touched;
     int tiles_x, num_tiles;
     uint32_t limit;                  // words the buffers hold
-    uint32_t* said;                  // [SMALL_MAX_TILES]
+    uint32_t* said;                  // [SMALL_MAX_TILES], and the state
     uint32_t call;                   // (16 bits)
     uint2* ranges;
     uint32_t* order;
@@ -1079,32 +1079,21 @@ __device__ __forceinline__ uint32_t rect_area(const ushort4& r)
     return r.z > r.x && r.w > r.y ? (uint32_t)(r.z - r.x) * (uint32_t)(r.w - r.y) : 0u;
 }
 
-// What tiles 2 t, 2 t + 1, 512 + 2 t, 512 + 2 t + 1 below `end` have said in this call (0 for the others); false when one of them
-// says nothing.
-constexpr int SMALL_TILES_PER = SMALL_MAX_TILES / SMALL_THREADS;
-static_assert(SMALL_TILES_PER == 4 && SMALL_MAX_N < 65536, "two loads of two words, 16 bits for a tile's pairs");
-__device__ __forceinline__ int said_tile(int q) { return (q >> 1) * 2 * SMALL_THREADS + 2 * (int)threadIdx.x + (q & 1); }
-__device__ __forceinline__ bool pairs_said(const SmallFrame& f, int end, uint32_t (&c)[SMALL_TILES_PER])
-{
-    const unsigned long long* const words = reinterpret_cast<const unsigned long long*>(f.said);
-    for (int k = 0; k < SMALL_POLLS; k++) {
-        unsigned long long w[SMALL_TILES_PER / 2] = {};
-#pragma unroll
-        for (int h = 0; h < SMALL_TILES_PER / 2; h++)
-            if (said_tile(2 * h) < end) w[h] = __hip_atomic_load(&words[h * SMALL_THREADS + threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        bool all = true;
-#pragma unroll
-        for (int q = 0; q < SMALL_TILES_PER; q++) {
-            const uint32_t word = (uint32_t)(w[q >> 1] >> 32 * (q & 1));
-            const bool mine = said_tile(q) < end;
-            all = all & (!mine | (word >> 16 == f.call));
-            c[q] = mine ? word & 0xffffu : 0u;
-        }
-        if (all) return true;
-        __builtin_amdgcn_s_sleep(1);
+static_assert(SMALL_MAX_N < 65536, "16 bits for a tile's pairs");
+struct SmallMemory {
+    uint32_t* said;
+    __device__ __forceinline__ unsigned long long pair(int i) const
+    {
+        return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(said) + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    return false;
-}
+    __device__ __forceinline__ uint32_t state() const { return __hip_atomic_load(said + SMALL_MAX_TILES, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ uint32_t swap(uint32_t was, uint32_t now) const
+    {
+        __hip_atomic_compare_exchange_strong(said + SMALL_MAX_TILES, &was, now, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return was;
+    }
+    __device__ __forceinline__ void rest() const { __builtin_amdgcn_s_sleep(1); }
+};
 
 template <bool CB>
 __global__ __launch_bounds__(SMALL_THREADS) void k_small_frame(SmallFrame f, CfgDev cfg)
@@ -1118,9 +1107,12 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_frame(SmallFrame f, Cfg
         uint32_t buckets[NB];
     };
     __shared__ __align__(16) Mem mem;
-    __shared__ uint32_t s_count, s_wave[2][WAVES], s_late;
+    __shared__ uint32_t s_count, s_wave[2][WAVES], s_late, s_decided;
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
     const int n = (int)f.n;
+    const SmallMemory mem_words = {f.said};
+    auto said_tile = [&](int q) { return small_tile(t, q); };
+    auto pairs_said = [&](int end, uint32_t (&c)[PER_TILE]) { return small_look(mem_words, t, end, f.call, SMALL_POLLS, c); };
     auto below = [](uint64_t bal) { return __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u)); };
 
     if ((int)blockIdx.x > f.num_tiles) {
@@ -1181,7 +1173,8 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_frame(SmallFrame f, Cfg
 #pragma unroll
         for (int q = 0; q < NB / T; q++) cnt[t + q * T] = 0u;
         uint32_t c[PER_TILE], sum = 0, most = 0;
-        const bool late = !pairs_said(f, f.num_tiles, c);
+        const uint32_t state = t == T - 1 ? mem_words.state() : 0u;   // (requested here: only the swap follows the looks)
+        const bool late = !pairs_said(f.num_tiles, c);
 #pragma unroll
         for (int q = 0; q < PER_TILE; q++) {
             sum += c[q];
@@ -1196,7 +1189,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_frame(SmallFrame f, Cfg
         most = wave_inclusive_max(most);
         if (lane == 63) { s_wave[0][wave] = sum; s_wave[1][wave] = most; }
         __syncthreads();
-        if (s_late) {   // (the host says so; sorts of long lists that are enqueued already take what is here as tiles)
+        if (s_late) {   // (the totals stay unset; sorts of long lists that are enqueued already take what is here as tiles)
             for (int k = t; k < f.num_tiles; k += T) f.order[k] = (uint32_t)k;
             return;
         }
@@ -1208,7 +1201,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_frame(SmallFrame f, Cfg
 #pragma unroll
             for (int q = 0; q < NB / 64; q++) { cnt[lane * (NB / 64) + q] = run; run += v[q]; }
         }
-        if (t == T - 1) {
+        if (t == T - 1 && small_decide(mem_words, f.call, state, SMALL_PUBLISHED) == SMALL_PUBLISHED) {
             uint64_t pairs = 0, longest = 0;
             for (int w = 0; w < WAVES; w++) { pairs += s_wave[0][w]; longest = max(longest, (uint64_t)s_wave[1][w]); }
             __hip_atomic_store(&f.totals[2], pairs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -1306,19 +1299,27 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_frame(SmallFrame f, Cfg
             const uint2 r = f.ranges[tile];
             return len && r.y <= f.limit ? r.x : ~0u;
         }
-        uint32_t c[PER_TILE], sum = 0;
-        if (!pairs_said(f, (int)tile, c)) s_late = 1u;
-#pragma unroll
-        for (int q = 0; q < PER_TILE; q++) sum += c[q];
-        sum = wave_inclusive_scan(sum);
-        if (lane == 63) s_wave[0][wave] = sum;
-        __syncthreads();
         uint32_t first = 0;
+        for (bool again = false;; again = true) {
+            uint32_t c[PER_TILE], sum = 0;
+            if (!pairs_said((int)tile, c)) s_late = 1u;
 #pragma unroll
-        for (int w = 0; w < WAVES; w++) first += s_wave[0][w];
-        if (s_late) {   // (its word is taken back, so that the totals stay unset)
-            if (t == 0) __hip_atomic_store(&f.said[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return ~0u;
+            for (int q = 0; q < PER_TILE; q++) sum += c[q];
+            sum = wave_inclusive_scan(sum);
+            if (lane == 63) s_wave[0][wave] = sum;
+            __syncthreads();
+            first = 0;
+#pragma unroll
+            for (int w = 0; w < WAVES; w++) first += s_wave[0][w];
+            if (!s_late) break;
+            if (t == 0) s_decided = small_decide(mem_words, f.call, mem_words.state(), SMALL_GIVEN_UP);
+            __syncthreads();
+            if (s_decided != SMALL_PUBLISHED || again) {
+                if (t == 0) f.ranges[tile] = make_uint2(0u, 0u);   // (for sorts of long lists that are enqueued already)
+                return ~0u;
+            }
+            if (t == 0) s_late = 0u;   // (all words are there by now: the next look finds them)
+            __syncthreads();
         }
         if (t == 0) f.ranges[tile] = len ? make_uint2(first, first + (uint32_t)len) : make_uint2(0u, 0u);
         return len && first + (uint32_t)len <= f.limit ? first : ~0u;

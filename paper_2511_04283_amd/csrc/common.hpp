@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "fastgs.h"
+#include "small_words.hpp"
 
 namespace fs {
 
@@ -444,11 +445,12 @@ hipError_t launch_tile_sorts(hipStream_t st, int num_tiles, int variants, uint32
                              const BandPlaces& places);
 
 // The whole ordering of a small frame in one launch (k_small_frame): what launch_tile_count, launch_tile_scatter and the sort of lists up
-// to TILE_SORT_SMALL leave, except that the record places are in index order.  said: [SMALL_MAX_TILES] words, zeroed before the first launch and
+// to TILE_SORT_SMALL leave, except that the record places are in index order.  said: [SMALL_WORDS] words, zeroed before the first launch and
 // whenever call, a number of 16 bits, starts again from 1.  Once buffers that were too small have grown, a second launch with totals null
-// writes the pairs to the ranges that the first one left.
+// writes the pairs to the ranges that the first one left.  A launch whose workgroups have waited too long for each other ends with totals
+// 2 and 3 as they were: nothing that it has written counts then.
 constexpr int SMALL_MAX_N = 16384;
-constexpr int SMALL_MAX_TILES = 1024;
+constexpr int SMALL_WORDS = SMALL_MAX_TILES + 1;   // the tiles' words and the state
 // Every tile looks at every Gaussian, so the launch grows with the product and the four that it replaces do not.  In a training step the
 // host has waited for the loss before and the GPU has nothing to do while it launches, so three launches fewer count in full; behind
 // a render's or a step's longer queue only the GPU's own time does.  Whole passes, the four launches -> this one, us:

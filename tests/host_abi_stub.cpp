@@ -11,12 +11,13 @@ int stub_fail_preprocess_bwd = 0;   // the next launch of k_preprocess_bwd fails
 size_t stub_fail_malloc_of = 0;     // allocations of this size fail (0: none does)
 int64_t stub_pairs = 0;             // pairs of every view
 int stub_queue = 0;                 // words for the host arrive when the stream has been asked this often whether it is done (0: at once)
-int stub_never = 0;                 // ... or, of 1: the totals, 2: the loss, never: the stream is done without
+int stub_never = 0;                 // ... or, of 1: the totals, 2: the loss, 3: an ordering in one launch, never: the stream is done without
 // ... and reads: flags found set when k_render_bwd is launched, waits for the whole stream
-// and how many launches went by bands of tiles: counts, placements, splits
+// and how many launches went by bands of tiles: counts, placements, splits; how many counts there were
 int64_t stub_stale_flags = -1;
 int stub_syncs = 0;
 int stub_bands[3] = {0, 0, 0};
+int stub_counts = 0;
 // and orderings in one launch: their first launches, their second ones
 int stub_small[2] = {0, 0};
 
@@ -90,6 +91,7 @@ hipError_t launch_tile_count(hipStream_t, int64_t, const fs_projected&, const Cf
                              uint64_t* totals, uint32_t*, uint32_t*, uint64_t*, float*, bool bands)
 {
     stub_bands[0] += bands;
+    stub_counts++;
     const uint64_t pairs = (uint64_t)stub_pairs, four[4] = {pairs, pairs, pairs, 1};
     words(1, totals, four, 4);
     return hipSuccess;
@@ -99,7 +101,7 @@ hipError_t launch_small_frame(hipStream_t, int64_t, const fs_projected&, const C
 {
     const uint64_t pairs = (uint64_t)stub_pairs, four[4] = {pairs, pairs, pairs, 1};
     stub_small[totals == nullptr]++;
-    if (totals) words(1, totals, four, 4);
+    if (totals && stub_never != 3) words(1, totals, four, 4);
     return hipSuccess;
 }
 hipError_t launch_tile_scatter(hipStream_t, int64_t, const fs_projected&, const CfgDev&, int, int, uint32_t, const uint2*, uint32_t*,

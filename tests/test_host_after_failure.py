@@ -210,3 +210,24 @@ def test_one_launch_is_chosen_by_gaussians_and_tiles(stub):
                 small = n <= most and tiles <= 1024 and n * tiles <= tests
                 assert [x - y for x, y in zip(launches, before)] == [small, small and call == 1], (training, n, tiles)
             stub.fs_destroy(c.h)
+
+
+@pytest.mark.parametrize("call", ["backward", "train"])
+def test_one_launch_that_waited_too_long_for_itself(stub, call):
+    """Where the totals of an ordering in one launch never come, because its workgroups have given up waiting for each other, the general
+    launches order the frame; the next call takes one launch again."""
+    launches, counts = (ctypes.c_int * 2).in_dll(stub, "stub_small"), ctypes.c_int.in_dll(stub, "stub_counts")
+    c = Ctx(stub, pairs=100)
+    step, B = getattr(c, call), c.B
+    for never in (0, 3, 3, 0):
+        before = [*launches, counts.value]
+        set_int(stub, "stub_never", never)
+        try:
+            step(B.FS_RECORDS_SPARSE)
+        finally:
+            set_int(stub, "stub_never", 0)
+        assert c.rc == B.FS_OK and stub.fs_last_error(c.h) == b""
+        assert [x - y for x, y in zip([*launches, counts.value], before)] == [1, 0, never != 0]
+        if call == "train":
+            assert list(c.out3) == [0.25, 0.5, 0.75]
+    stub.fs_destroy(c.h)
