@@ -127,7 +127,8 @@ typedef struct {
 
 /* Output of fs_bin_sort.  Arrays are ctx-owned and stay valid until the next fs_bin_sort or
  * fs_destroy on the same ctx: no other call writes to them.  A later call that is handed the fs_bins
- * of an earlier fs_bin_sort (or of another ctx) returns FS_EINVAL (see `generation`). */
+ * of an earlier fs_bin_sort (or of another ctx) returns FS_EINVAL (see `generation`), and so does one whose camera has
+ * another grid of 16x16 tiles than fs_bin_sort's (another image of the same grid is taken). */
 typedef struct {
     int64_t num_pairs;            /* P, host-visible on return                                        */
     const uint64_t *keys_sorted;  /* [P] tile_id << 32 | bits(depth), ascending; ties by Gaussian index */

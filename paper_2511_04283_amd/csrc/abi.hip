@@ -46,6 +46,7 @@ struct fs_ctx {
     ScratchBuf sel_vals[2];   // uint32 [m] candidate indices, ping-pong
     ScratchBuf sel_hist;      // uint32 radix histograms of that sort
     uint64_t generation = 0;  // bumped by every fs_bin_sort; fs_bins of an earlier one are refused
+    int tiles_x = 0, tiles_y = 0;   // the grid of tiles of the latest fs_bin_sort; cameras of another one are refused with its fs_bins
     hipEvent_t totals_event = nullptr;   // recorded behind the copy of fs_bin_sort's totals (radix mode)
     int spec_set = 0;                    // the sort launches (TS_*) the previous per-tile ordering on this ctx would have
                                          // chosen (0: none): what fs_bin_sort enqueues ahead of its read-back
@@ -233,8 +234,16 @@ bool proj_ok(const fs_projected* p)
     return p && p->mean2d && p->depth && p->conic_opacity && p->rgb && p->rect && p->tiles_touched && p->clamped;
 }
 
-// bins of an earlier fs_bin_sort (or of another ctx) point at memory that has been reused since
-bool bins_stale(const fs_ctx* ctx, const fs_bins* bins) { return bins->generation != ctx->generation || ctx->generation == 0; }
+// Bins of an earlier fs_bin_sort (or of another ctx) point at memory that has been reused since, and their tiles are numbered for one
+// grid: with a camera of another one, kernels would take numbers of tiles that it has not, or write where the bins' order lies.
+int check_bins(fs_ctx* ctx, const fs_bins* bins, const CamDev& cam, const char* call)
+{
+    if (bins->generation != ctx->generation || ctx->generation == 0)
+        return fail(ctx, FS_EINVAL, "%s: bins do not come from this context's latest fs_bin_sort", call);
+    if (cam.tiles_x != ctx->tiles_x || cam.tiles_y != ctx->tiles_y)
+        return fail(ctx, FS_EINVAL, "%s: the camera has another grid of tiles than the bins", call);
+    return FS_OK;
+}
 
 // Sparse records pay where the lists are long (most of their pairs receive nothing), and where the backward pass walks the blended
 // pairs only: dense ones make it look for the others in a second pass over the list.  k_render_bwd with k_preprocess_bwd, dense and
@@ -464,6 +473,8 @@ static int order_pairs(fs_ctx* ctx, const fs_projected* proj, const fs_camera* c
     ctx->bits_pairs = -1;
     ctx->generation++;      // whatever earlier fs_bins of this ctx point at is overwritten from here on
     out->generation = 0;    // (a call that fails leaves bins that every later call refuses)
+    ctx->tiles_x = cd.tiles_x;
+    ctx->tiles_y = cd.tiles_y;
     FS_HIP(hipSetDevice(ctx->device), "hipSetDevice");
     hipStream_t st = ctx->stream;
     const int tiles = cd.tiles_x * cd.tiles_y;
@@ -716,7 +727,7 @@ int fs_render_fwd(fs_ctx* ctx, const fs_projected* proj, const fs_bins* bins, co
         return fail(ctx, FS_EINVAL, "fs_render_fwd: bad arguments");
     if (bins->num_pairs > 0 && (!proj_ok(proj) || !bins->gauss_sorted || !bins->splats))
         return fail(ctx, FS_EINVAL, "fs_render_fwd: null array");
-    if (bins_stale(ctx, bins)) return fail(ctx, FS_EINVAL, "fs_render_fwd: bins do not come from this context's latest fs_bin_sort");
+    FS_TRY(check_bins(ctx, bins, cd, "fs_render_fwd"));
     FS_HIP(hipSetDevice(ctx->device), "hipSetDevice");
     ctx->bits_pairs = -1;   // (what an earlier forward pass recorded for the count pass does not describe this one)
     const bool bits = ctx->record_bits && bins->num_pairs > 0;
@@ -740,7 +751,7 @@ int fs_render_fwd_loss(fs_ctx* ctx, const fs_projected* proj, const fs_bins* bin
         return fail(ctx, FS_EINVAL, "fs_render_fwd_loss: bad arguments");
     if (bins->num_pairs > 0 && (!proj_ok(proj) || !bins->gauss_sorted || !bins->splats))
         return fail(ctx, FS_EINVAL, "fs_render_fwd_loss: null array");
-    if (bins_stale(ctx, bins)) return fail(ctx, FS_EINVAL, "fs_render_fwd_loss: bins do not come from this context's latest fs_bin_sort");
+    FS_TRY(check_bins(ctx, bins, cd, "fs_render_fwd_loss"));
     FS_HIP(hipSetDevice(ctx->device), "hipSetDevice");
     const int tiles = cd.tiles_x * cd.tiles_y;
     const int64_t pixels = (int64_t)cd.width * cd.height;
@@ -849,7 +860,7 @@ int fs_render_bwd(fs_ctx* ctx, const fs_gaussians* g, const fs_camera* cam, cons
     if (bins->num_pairs > 0 && (!bins->record_offsets || !bins->splats || bins->num_records < bins->num_pairs))
         return fail(ctx, FS_EINVAL, "fs_render_bwd: bins without record_offsets / splats");
     // (the records and their places live in this ctx and belong to its latest fs_bin_sort)
-    if (bins_stale(ctx, bins)) return fail(ctx, FS_EINVAL, "fs_render_bwd: bins do not come from this context's latest fs_bin_sort");
+    FS_TRY(check_bins(ctx, bins, cd, "fs_render_bwd"));
     const BlendRecord blends = ctx->per_splat_bwd ? BlendRecord{nullptr, nullptr} : blends_of(ctx, bins, cd);
     const bool sparse = sparse_records(ctx, bins, cd.tiles_x * cd.tiles_y, blends.entries != nullptr);
     FS_TRY(record_buffers(ctx, bins, sparse));
@@ -930,7 +941,7 @@ int fs_score_accumulate(fs_ctx* ctx, const fs_projected* proj, const fs_bins* bi
     if (bins->num_pairs == 0) return FS_OK;
     if (!proj_ok(proj) || !bins->gauss_sorted || !bins->splats || !counts)
         return fail(ctx, FS_EINVAL, "fs_score_accumulate: null array");
-    if (bins_stale(ctx, bins)) return fail(ctx, FS_EINVAL, "fs_score_accumulate: bins do not come from this context's latest fs_bin_sort");
+    FS_TRY(check_bins(ctx, bins, cd, "fs_score_accumulate"));
     FS_HIP(hipSetDevice(ctx->device), "hipSetDevice");
     ProfScope prof(ctx, FS_K_SCORE);
     if (ctx->bits_pairs == bins->num_pairs && ctx->bits_order == bins->gauss_sorted &&
@@ -960,7 +971,7 @@ int fs_mask_score_fused(fs_ctx* ctx, const fs_projected* proj, const fs_bins* bi
         return fail(ctx, FS_EINVAL, "fs_mask_score_fused: no error map of this size from fs_render_fwd_loss is pending");
     if (bins->num_pairs > 0 && (!proj_ok(proj) || !bins->gauss_sorted || !bins->splats || !counts))
         return fail(ctx, FS_EINVAL, "fs_mask_score_fused: null array");
-    if (bins_stale(ctx, bins)) return fail(ctx, FS_EINVAL, "fs_mask_score_fused: bins do not come from this context's latest fs_bin_sort");
+    FS_TRY(check_bins(ctx, bins, cd, "fs_mask_score_fused"));
     FS_HIP(hipSetDevice(ctx->device), "hipSetDevice");
     float* err = static_cast<float*>(ctx->err_map.ptr);
     float* thr = threshold_out ? threshold_out : err + pixels;
@@ -993,7 +1004,7 @@ int fs_score_record_rows(fs_ctx* ctx, const fs_bins* bins, const fs_camera* cam,
     if (!ctx) return FS_EINVAL;
     CamDev cd;
     if (!make_cam(cam, cd) || !bins || !rows_per_tile) return fail(ctx, FS_EINVAL, "fs_score_record_rows: bad arguments");
-    if (bins_stale(ctx, bins)) return fail(ctx, FS_EINVAL, "fs_score_record_rows: bins do not come from this context's latest fs_bin_sort");
+    FS_TRY(check_bins(ctx, bins, cd, "fs_score_record_rows"));
     const int tiles = cd.tiles_x * cd.tiles_y;
     if (ctx->bits_pairs != bins->num_pairs || ctx->bits_order != bins->gauss_sorted || ctx->bits_tiles != tiles)
         return fail(ctx, FS_EINVAL, "fs_score_record_rows: the latest forward pass on this context left no record for these bins");

@@ -231,3 +231,25 @@ def test_one_launch_that_waited_too_long_for_itself(stub, call):
         if call == "train":
             assert list(c.out3) == [0.25, 0.5, 0.75]
     stub.fs_destroy(c.h)
+
+
+@pytest.mark.parametrize("call", ["fs_render_fwd", "fs_render_fwd_loss", "fs_render_bwd", "fs_score_accumulate"])
+def test_bins_are_of_one_grid_of_tiles(stub, call):
+    """A camera of another grid than the one that the bins were ordered for is refused before anything is launched: its tiles have other
+    numbers.  Another size of the same grid is not."""
+    c = Ctx(stub, pairs=100)
+    B, r, some = c.B, ctypes.byref, c.some
+    bins = B.fs_bins()
+    assert stub.fs_bin_sort(c.h, r(c.proj), r(c.cam), ctypes.c_int64(1), r(bins)) == B.FS_OK
+    args = {"fs_render_fwd": lambda: (r(c.proj), r(bins), r(c.cam), some, some, some),
+            "fs_render_fwd_loss": lambda: (r(c.proj), r(bins), r(c.cam), some, some, some, some, some, some),
+            "fs_render_bwd": lambda: (r(c.g), r(c.cam), r(c.proj), r(bins), some, some, some, r(c.grads)),
+            "fs_score_accumulate": lambda: (r(c.proj), r(bins), r(c.cam), some, some, some, some)}[call]
+    for width, height in ((16, 16), (16, 32), (48, 16), (33, 16), (32, 17)):
+        c.cam.width, c.cam.height = width, height
+        assert getattr(stub, call)(c.h, *args()) == -1   # FS_EINVAL
+        assert b"another grid" in stub.fs_last_error(c.h)
+    if call in ("fs_render_fwd", "fs_render_bwd"):
+        c.cam.width, c.cam.height = 17, 3
+        assert getattr(stub, call)(c.h, *args()) == B.FS_OK
+    stub.fs_destroy(c.h)
