@@ -103,6 +103,23 @@ def test_train_step_on_frames_and_lists_that_grow(compact, records):
     c.close()
 
 
+@pytest.mark.parametrize("compact,records", [(1, "dense"), (0, "sparse"), (1, "sparse"), (0, "dense")])
+@pytest.mark.parametrize("n, width, height, scale", [(16385, 83, 50, -3.2), (611, 650, 480, -2.3), (16384, 83, 50, -3.2), (16384, 40, 33, -1.2)])
+def test_train_step_by_general_launches_and_by_the_largest_one_launch(n, width, height, scale, compact, records):
+    """An iteration orders its pairs in one launch up to 16384 Gaussians and 1024 tiles, where the separate calls have left it: one more of
+    either, and the most of it, with lists beyond 8192 entries as well."""
+    from paper_2511_04283_amd import binding as B
+    c = context(compact, records)
+    sc = scenes.tiny_scene(72, n, width, height, sh_degree=1, log_scale=(scale, 0.5), spread=1.0)
+    cam = sc.cameras[0]
+    bins = c.fs_bin_sort(c.fs_preprocess(B.Gaussians.from_scene(sc, c.device), B.make_camera(cam)), B.make_camera(cam))
+    ranges = bins.copy_ranges()
+    longest = int((ranges[:, 1] - ranges[:, 0]).max().item())
+    assert (8192 < longest <= n) if scale > -2 else longest > 0, longest
+    compare_with_the_calls(c, sc, 1, [(cam, *it) for it in SCHEDULE[:1] + SCHEDULE[2:5]])
+    c.close()
+
+
 @pytest.mark.parametrize("shape", [(1, 3, 50, 83), (3 * 50 * 83,)])
 def test_target_of_another_shape_and_too_small_a_target(shape):
     import torch
