@@ -10,6 +10,7 @@ extern "C" {
 int stub_fail_preprocess_bwd = 0;   // the next launch of k_preprocess_bwd fails
 size_t stub_fail_malloc_of = 0;     // allocations of this size fail (0: none does)
 int64_t stub_pairs = 0;             // pairs of every view
+int64_t stub_longest = 1;           // its longest list
 int stub_queue = 0;                 // words for the host arrive when the stream has been asked this often whether it is done (0: at once)
 int stub_never = 0;                 // ... or, of 1: the totals, 2: the loss, 3: an ordering in one launch, never: the stream is done without
 // ... and reads: flags found set when k_render_bwd is launched, waits for the whole stream
@@ -20,6 +21,8 @@ int stub_bands[3] = {0, 0, 0};
 int stub_counts = 0;
 // and orderings in one launch: their first launches, their second ones
 int stub_small[2] = {0, 0};
+// and forward and backward passes with a record of blended pairs
+int stub_blends[2] = {0, 0};
 
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -92,14 +95,14 @@ hipError_t launch_tile_count(hipStream_t, int64_t, const fs_projected&, const Cf
 {
     stub_bands[0] += bands;
     stub_counts++;
-    const uint64_t pairs = (uint64_t)stub_pairs, four[4] = {pairs, pairs, pairs, 1};
+    const uint64_t pairs = (uint64_t)stub_pairs, four[4] = {pairs, pairs, pairs, (uint64_t)stub_longest};
     words(1, totals, four, 4);
     return hipSuccess;
 }
 hipError_t launch_small_frame(hipStream_t, int64_t, const fs_projected&, const CfgDev&, int, int, uint32_t, uint32_t*, uint32_t, uint2*,
                               uint32_t*, uint64_t* totals, uint32_t*, uint32_t*, float*, uint64_t*, uint64_t*, uint32_t*)
 {
-    const uint64_t pairs = (uint64_t)stub_pairs, four[4] = {pairs, pairs, pairs, 1};
+    const uint64_t pairs = (uint64_t)stub_pairs, four[4] = {pairs, pairs, pairs, (uint64_t)stub_longest};
     stub_small[totals == nullptr]++;
     if (totals && stub_never != 3) words(1, totals, four, 4);
     return hipSuccess;
@@ -116,9 +119,21 @@ hipError_t launch_tile_sorts(hipStream_t, int, int variants, uint32_t, const uin
     stub_bands[2] += (variants & TS_SPLIT) != 0;
     return hipSuccess;
 }
-hipError_t launch_render_fwd(hipStream_t, const CamDev&, const CfgDev&, const uint32_t*, const uint32_t*, const uint32_t*, const float*,
-                             float*, float*, uint32_t*, const ScoreRecord&, const BlendRecord&)
+hipError_t launch_exclusive_scan(hipStream_t, const uint32_t*, uint32_t*, int64_t, void*, uint64_t*) { return hipSuccess; }
+hipError_t launch_emit_pairs(hipStream_t, int64_t, const fs_projected&, const CfgDev&, const uint32_t*, int, uint64_t*, uint32_t*, float*)
 {
+    return hipSuccess;
+}
+hipError_t launch_radix_sort(hipStream_t, int64_t, int, uint64_t*[2], uint32_t*[2], uint32_t*, void*, uint64_t*, int* result)
+{
+    *result = 1;
+    return hipSuccess;
+}
+hipError_t launch_tile_ranges(hipStream_t, int64_t, const uint64_t*, int, uint32_t*, uint32_t*) { return hipSuccess; }
+hipError_t launch_render_fwd(hipStream_t, const CamDev&, const CfgDev&, const uint32_t*, const uint32_t*, const uint32_t*, const float*,
+                             float*, float*, uint32_t*, const ScoreRecord&, const BlendRecord& blends)
+{
+    stub_blends[0] += blends.entries != nullptr;
     return hipSuccess;
 }
 hipError_t launch_photo_loss(hipStream_t, const float*, const float*, int, int, float, float*, double*, float*, double* out3)
@@ -132,8 +147,9 @@ hipError_t launch_photo_loss(hipStream_t, const float*, const float*, int, int, 
 
 // every pair's flag is set, as where every pair has received something
 hipError_t launch_render_bwd(hipStream_t, const CamDev&, const CfgDev&, const uint32_t*, const uint32_t*, const uint32_t*, const float*,
-                             const float*, const uint32_t*, const float*, float*, uint8_t* rec_valid, bool, bool, const BlendRecord&)
+                             const float*, const uint32_t*, const float*, float*, uint8_t* rec_valid, bool, bool, const BlendRecord& blends)
 {
+    stub_blends[1] += blends.entries != nullptr;
     if (!rec_valid) return hipSuccess;
     stub_stale_flags = 0;
     for (int64_t i = 0; i < stub_pairs; i++) { stub_stale_flags += rec_valid[i]; rec_valid[i] = 1; }

@@ -9,7 +9,7 @@ from paper_2511_04283_amd import scenes
 pytestmark = pytest.mark.gpu
 
 
-def both_ways(sc, cam, want_abs, records, compact=0, shorten=None):
+def both_ways(sc, cam, want_abs, records, compact=0, shorten=None, sort=0):
     """Gradients from a context with a record and one without; n_contrib as the pixels have it, or `shorten`ed."""
     import torch
     from paper_2511_04283_amd import binding as B
@@ -18,7 +18,7 @@ def both_ways(sc, cam, want_abs, records, compact=0, shorten=None):
     target = torch.from_numpy(rng.uniform(size=(3, cam.height, cam.width)).astype(np.float32)).cuda()
     weights = torch.from_numpy(rng.normal(size=(3, cam.height, cam.width)).astype(np.float32)).cuda()
     config = B.default_config()
-    config.compact_box = compact
+    config.compact_box, config.sort_mode = compact, sort
     for with_record in (True, False):
         ctx = B.Context("cuda:0", config)
         ctx.fs_set_record_mode({"auto": B.FS_RECORDS_AUTO, "dense": B.FS_RECORDS_DENSE, "sparse": B.FS_RECORDS_SPARSE}[records])
@@ -64,6 +64,20 @@ def test_every_pair_blended(n, want_abs, records):
     same(out)
     sc.opacities[np.arange(n) % 3 == 1] = 0.003
     same(both_ways(sc, sc.cameras[0], want_abs, records)[0])
+
+
+@pytest.mark.parametrize("records", ["dense", "sparse"])
+@pytest.mark.parametrize("n, sort", [(8193, 0), (16384, 0), (16385, 0), (500, 1), (8193, 1)])
+def test_the_longest_lists_and_orderings_without_a_record(n, sort, records):
+    """Positions up to the last that a record holds, blended ones among them (every tenth splat; the others are too faint); one entry more,
+    and the radix ordering, which leave none."""
+    sc = scenes.tiny_scene(77, n, 29, 13, sh_degree=0, log_scale=(0.0, 0.1), spread=0.4)
+    depth = np.argsort(sc.means[:, 2], kind="stable")
+    sc.opacities[:] = 0.003
+    sc.opacities[depth[::10]], sc.opacities[depth[-1]], sc.means[depth[-1], :2] = 0.006, 0.02, 0.0
+    out, nc = both_ways(sc, sc.cameras[0], True, records, sort=sort)
+    assert nc.max() == n
+    same(out)
 
 
 @pytest.mark.parametrize("compact", [0, 1])

@@ -253,3 +253,20 @@ def test_bins_are_of_one_grid_of_tiles(stub, call):
         c.cam.width, c.cam.height = 17, 3
         assert getattr(stub, call)(c.h, *args()) == B.FS_OK
     stub.fs_destroy(c.h)
+
+
+@pytest.mark.parametrize("longest, record", [(1, 1), (16384, 1), (16385, 0), (70000, 0)])
+def test_a_record_of_blended_pairs_only_for_lists_sorted_per_tile(stub, longest, record):
+    """Longer lists are ordered by the radix sort, which may leave the keys where the record would lie, and have places beyond its 16
+    bits."""
+    blends = (ctypes.c_int * 2).in_dll(stub, "stub_blends")
+    ctypes.c_int64.in_dll(stub, "stub_longest").value = longest
+    try:
+        for n in FRAMES:
+            c = Ctx(stub, pairs=100, n=n)
+            before = list(blends)
+            c.train(c.B.FS_RECORDS_SPARSE)
+            assert c.rc == c.B.FS_OK and [x - y for x, y in zip(blends, before)] == [record, record]
+            stub.fs_destroy(c.h)
+    finally:
+        ctypes.c_int64.in_dll(stub, "stub_longest").value = 1
