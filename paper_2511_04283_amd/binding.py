@@ -12,7 +12,7 @@ from dataclasses import dataclass
 
 import torch
 
-from . import _marshal
+from . import build
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 # FASTGS_HIP_LIB names another build of the same library (e.g. an experimental variant); load_library says so on
@@ -94,6 +94,21 @@ class fs_train_params(ctypes.Structure):
 
 
 _lib = None
+_marshal = None
+
+
+def load_marshal():
+    """Loads _marshal, the native half of this module, or says how to build it."""
+    global _marshal
+    if _marshal is None:
+        try:
+            from . import _marshal as built
+        except ImportError as e:
+            raise RuntimeError(f"{build.MARSHAL} is missing or does not load ({e}): build it with `python -m paper_2511_04283_amd.build`") from e
+        if getattr(built, "stamp", None) != build.marshal_stamp():
+            raise RuntimeError(f"{built.__file__} is not the one {build.marshal_stamp()}: build it with `python -m paper_2511_04283_amd.build`")
+        _marshal = built
+    return _marshal
 
 
 def load_library() -> ctypes.CDLL:
@@ -107,6 +122,7 @@ def load_library() -> ctypes.CDLL:
     if os.environ.get("FASTGS_HIP_LIB"):
         import sys
         print(f"paper_2511_04283_amd: loading the library named by FASTGS_HIP_LIB: {LIB_PATH}", file=sys.stderr, flush=True)
+    load_marshal()
     lib = ctypes.CDLL(LIB_PATH)
     vp, i32, i64, f32 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_float
     P = ctypes.POINTER
@@ -191,7 +207,7 @@ def _chk(t, dtype, shape=None, name="tensor"):
 def _addresses(struct, offset, tensors, shapes, names, int32=0):
     """The addresses of contiguous CUDA tensors of these shapes, one after the other from `offset` of the structure on: float32, and
     int32 those whose bit is set."""
-    if _marshal.fill(struct, offset, tensors, int32, shapes) == len(tensors):
+    if (_marshal or load_marshal()).fill(struct, offset, tensors, int32, shapes) == len(tensors):
         return
     for k, t in enumerate(tensors):   # (one of them is not as it should be, or a subclass of Tensor)
         dtype = torch.int32 if int32 >> k & 1 else torch.float32

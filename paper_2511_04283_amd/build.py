@@ -1,4 +1,5 @@
-"""Builds libfastgs_hip.so (gfx950) in-tree with hipcc, and _marshal (binding.py's native half, host code) with g++.
+"""Builds libfastgs_hip.so (gfx950) in-tree with hipcc, and _marshal (binding.py's native half, host code, for this Python and
+this torch) with g++.
 `python -m paper_2511_04283_amd.build`."""
 from __future__ import annotations
 
@@ -6,12 +7,20 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libfastgs_hip.so")
-MARSHAL_SRC, MARSHAL = os.path.join(CSRC, "marshal.cpp"), os.path.join(PKG, "_marshal.so")
+# (another Python looks for a file of another name; another torch would load this one: it says which it was built against)
+MARSHAL_SRC, MARSHAL = os.path.join(CSRC, "marshal.cpp"), os.path.join(PKG, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+def marshal_stamp() -> str:
+    import torch
+    return f"built against torch {torch.__version__}"
+
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -29,6 +38,9 @@ def sources():
 def is_stale() -> bool:
     if not os.path.exists(LIB) or not os.path.exists(MARSHAL) or os.path.getmtime(MARSHAL_SRC) > os.path.getmtime(MARSHAL):
         return True
+    with open(MARSHAL, "rb") as f:
+        if marshal_stamp().encode() not in f.read():
+            return True
     deps = sources() + glob.glob(os.path.join(CSRC, "*.hpp")) + [os.path.join(ROOT, "include", "fastgs.h")]
     return any(os.path.getmtime(d) > os.path.getmtime(LIB) for d in deps)
 
@@ -53,11 +65,9 @@ def build(verbose: bool = False, extra=()) -> str:
 
 
 def build_marshal(verbose: bool = False) -> str:
-    import sysconfig
-
     import torch
     from torch.utils import cpp_extension
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f'-DSTAMP="{marshal_stamp()}"', f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            *(f"-I{d}" for d in [sysconfig.get_paths()["include"], *cpp_extension.include_paths()]), "-o", MARSHAL, MARSHAL_SRC,
            "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"]
     if verbose:

@@ -61,4 +61,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__marshal()
+{
+    PyObject* const m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "stamp", STAMP) != 0) {   // (what it was built against: binding.py compares)
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}
