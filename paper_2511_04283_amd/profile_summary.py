@@ -33,7 +33,7 @@ GROUPS = {
     "preprocess": ["k_preprocess<"],
     "emit_pairs": ["k_tile_pairs<false, false,", "k_tile_pairs<true, false,", "k_tile_layout", "k_small_frame<"],
     "order_pairs": ["k_tile_pairs<false, true,", "k_tile_pairs<true, true,", "k_band_split", "k_tile_sort<"],
-    "render_fwd": ["k_render_fwd<true, true>"],
+    "render_fwd": ["k_render_fwd<true, true,"],
     "l1_grad": ["k_fold_tile_stats"],
     "render_bwd": ["k_render_bwd<false,", "k_render_bwd_splat<false,"],
     "preprocess_bwd": ["k_preprocess_bwd<"],
