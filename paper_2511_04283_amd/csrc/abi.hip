@@ -6,6 +6,7 @@
 
 #include <atomic>
 #include <chrono>
+#include <initializer_list>
 #include <new>
 #include <thread>
 #include <utility>
@@ -27,14 +28,16 @@ struct fs_ctx {
     fs_config cfg;
     char err[256];
 
-    ScratchBuf offsets;       // uint32 [n]
     ScratchBuf scan_tmp;      // uint64 block sums for the scans
+    ScratchBuf per_pair;      // one allocation for keys and vals[0]
     ScratchBuf keys[2];       // uint64 [P]: final keys and the tiles' unsorted segments, or the radix ping-pong pair
-    ScratchBuf vals[2];       // uint32 [P] ping-pong
+    ScratchBuf vals[2];       // uint32 [P] ping-pong (the second one, in the radix mode alone, has an allocation of its own)
     ScratchBuf hist;          // uint32 [RADIX_DIGITS * radix blocks] (radix mode)
     ScratchBuf ranges;        // uint32: ranges [T,2] | tile order [T] | tile totals [T] | counters [TILE_COPIES,T]
     ScratchBuf pair_grad;     // float  [P, PAIR_REC] per-pair partial gradients of the backward pass
+    ScratchBuf per_gaussian;  // one allocation for the next four
     ScratchBuf splats;        // float  [n, SPLAT_REC] packed projected splats (written by fs_bin_sort)
+    ScratchBuf offsets;       // uint32 [n]
     ScratchBuf rec_counts;    // uint32 [n] Compact Box: tiles in each Gaussian's box
     ScratchBuf rec_offsets;   // uint32 [n] Compact Box: exclusive prefix sum of rec_counts
     ScratchBuf err_map;       // float  [H*W]
@@ -131,11 +134,9 @@ int hip_fail(fs_ctx* c, hipError_t e, const char* where)
         if (e_ != hipSuccess) return hip_fail(ctx, e_, where); \
     } while (0)
 
-int ensure(fs_ctx* ctx, ScratchBuf& b, size_t bytes, const char* what)
+// a buffer of this size in the place of the one that b has, if any
+int replace(fs_ctx* ctx, ScratchBuf& b, size_t bytes, const char* what)
 {
-    if (bytes <= b.cap) return FS_OK;
-    size_t want = b.cap ? b.cap : 4096;
-    while (want < bytes) want *= 2;
     if (b.ptr) {
         // nothing enqueued earlier may still use the old block when it is released
         const hipError_t e = hipStreamSynchronize(ctx->stream);
@@ -144,13 +145,52 @@ int ensure(fs_ctx* ctx, ScratchBuf& b, size_t bytes, const char* what)
     }
     b.ptr = nullptr;
     b.cap = 0;
-    const hipError_t e = hipMalloc(&b.ptr, want);
+    const hipError_t e = hipMalloc(&b.ptr, bytes);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         b.ptr = nullptr;
         return fail(ctx, FS_ENOMEM, "scratch allocation failed (%s)", what);
     }
-    b.cap = want;
+    b.cap = bytes;
+    return FS_OK;
+}
+
+int ensure(fs_ctx* ctx, ScratchBuf& b, size_t bytes, const char* what)
+{
+    if (bytes <= b.cap) return FS_OK;
+    size_t want = b.cap ? b.cap : 4096;
+    while (want < bytes) want *= 2;
+    return replace(ctx, b, want, what);
+}
+
+// Arrays that grow together share one allocation, `block`: each holds as many elements, a power of two from 1024 on, so that all start
+// on a page.  (The driver takes 15 to 60 us for an allocation of 2 MB or more, and 250 to 300 where it finds memory that has just been
+// freed, whatever the size.  A new context's first pass behind one that was given back, medians of four processes, with an
+// allocation for each array and now, us: a render of 300k Gaussians at 1332x876 900 to 1240 and 275 to 575, ten score views at
+// 100k and 980x545 2290 to 2580 and 1520 to 1650, a step there 1090 to 1510 and 360 to 1360, 500k at 1600x1064 1200 to 1360 and 930
+// to 1210.)
+struct Part {
+    ScratchBuf* buf;
+    size_t element;   // bytes
+};
+int ensure_together(fs_ctx* ctx, ScratchBuf& block, std::initializer_list<Part> parts, size_t count, const char* what)
+{
+    const Part& one = *parts.begin();
+    if (count * one.element <= one.buf->cap) return FS_OK;
+    size_t elements = one.buf->cap ? one.buf->cap / one.element : 1024, all = 0;
+    while (elements < count) elements *= 2;
+    for (const Part& p : parts) {
+        *p.buf = ScratchBuf{};
+        all += p.element;
+    }
+    const int rc = replace(ctx, block, elements * all, what);
+    if (rc != FS_OK) return rc;
+    char* at = static_cast<char*>(block.ptr);
+    for (const Part& p : parts) {
+        p.buf->ptr = at;
+        p.buf->cap = elements * p.element;
+        at += p.buf->cap;
+    }
     return FS_OK;
 }
 
@@ -426,8 +466,7 @@ void fs_destroy(fs_ctx* ctx)
     if (!ctx) return;
     (void)hipSetDevice(ctx->device);
     (void)hipStreamSynchronize(ctx->stream);
-    ScratchBuf* all[] = {&ctx->offsets, &ctx->scan_tmp, &ctx->keys[0], &ctx->keys[1], &ctx->vals[0], &ctx->vals[1],
-                         &ctx->hist, &ctx->ranges, &ctx->pair_grad, &ctx->splats, &ctx->rec_counts, &ctx->rec_offsets,
+    ScratchBuf* all[] = {&ctx->per_gaussian, &ctx->scan_tmp, &ctx->per_pair, &ctx->vals[1], &ctx->hist, &ctx->ranges, &ctx->pair_grad,
                          &ctx->err_map, &ctx->ssim_maps, &ctx->partial, &ctx->tile_partial, &ctx->pair_bits, &ctx->rec_valid,
                          &ctx->train_proj, &ctx->train_frame,
                          &ctx->compact_pos, &ctx->compact_scan, &ctx->sel_keys[0], &ctx->sel_keys[1], &ctx->sel_vals[0],
@@ -491,9 +530,7 @@ static int order_pairs(fs_ctx* ctx, const fs_projected* proj, const fs_camera* c
     const bool bands = !small && placed_by_bands(n, tiles, ctx->candidates_before);   // (then keys[0] is placed into, and split into keys[1] ahead of the sorts)
     const int split = bands ? TS_SPLIT : 0;
     const BandPlaces places = bands ? BandPlaces{ttotal_p, reinterpret_cast<uint2*>(tcount_p + (size_t)TILE_COPIES * tiles)} : BandPlaces{};
-    FS_TRY(ensure(ctx, ctx->offsets, (size_t)(n > 0 ? n : 1) * sizeof(uint32_t), "offsets"));
     FS_TRY(ensure(ctx, ctx->scan_tmp, scan_tmp_bytes(n), "scan"));
-    FS_TRY(ensure(ctx, ctx->splats, (size_t)(n > 0 ? n : 1) * SPLAT_REC * sizeof(float), "splats"));
 
     // a2: where each Gaussian's pairs / backward records start, and the pair count P (the one host read-back of
     // the path).  With the Compact Box the records are indexed by candidate tile, so the boxes' areas get
@@ -501,10 +538,13 @@ static int order_pairs(fs_ctx* ctx, const fs_projected* proj, const fs_camera* c
     // tile-bucketed path only needs disjoint places for the records and gets them from its counting kernel.
     const bool cb = ctx->cfg.compact_box != 0;
     const CfgDev cf = make_cfg(ctx->cfg);
-    if (cb) {
-        FS_TRY(ensure(ctx, ctx->rec_counts, (size_t)(n > 0 ? n : 1) * sizeof(uint32_t), "record counts"));
-        FS_TRY(ensure(ctx, ctx->rec_offsets, (size_t)(n > 0 ? n : 1) * sizeof(uint32_t), "record offsets"));
-    }
+    const size_t boxes = cb ? sizeof(uint32_t) : 0;
+    FS_TRY(ensure_together(ctx, ctx->per_gaussian, {{&ctx->splats, SPLAT_REC * sizeof(float)}, {&ctx->offsets, sizeof(uint32_t)}, {&ctx->rec_counts, boxes},
+                                                    {&ctx->rec_offsets, boxes}}, (size_t)(n > 0 ? n : 1), "splats"));
+    auto room_for_pairs = [&](size_t pairs) {
+        return ensure_together(ctx, ctx->per_pair, {{&ctx->keys[0], sizeof(uint64_t)}, {&ctx->keys[1], sizeof(uint64_t)}, {&ctx->vals[0], sizeof(uint32_t)}},
+                               pairs, "pairs");
+    };
     auto prefix_sums = [&]() -> int {
         ProfScope prof(ctx, FS_K_SCAN);
         FS_HIP(launch_exclusive_scan(st, proj ? proj->tiles_touched : nullptr, static_cast<uint32_t*>(ctx->offsets.ptr),
@@ -522,15 +562,12 @@ static int order_pairs(fs_ctx* ctx, const fs_projected* proj, const fs_camera* c
     };
     if (small && ctx->keys[1].cap == 0) {
         // a new context's buffers hold four tiles a Gaussian, so that its first launch seldom needs a second one (a failure shows below)
-        for (ScratchBuf* b : {&ctx->keys[0], &ctx->keys[1]}) (void)ensure(ctx, *b, (size_t)n * 4 * sizeof(uint64_t), "keys");
-        (void)ensure(ctx, ctx->vals[0], (size_t)n * 4 * sizeof(uint32_t), "values");
+        (void)room_for_pairs((size_t)n * 4);
     }
     // what the buffers hold
     uint64_t cap_pairs = 0;
     if (bucketed && n > 0) {
         cap_pairs = ctx->keys[0].cap / sizeof(uint64_t);
-        if (ctx->keys[1].cap / sizeof(uint64_t) < cap_pairs) cap_pairs = ctx->keys[1].cap / sizeof(uint64_t);
-        if (ctx->vals[0].cap / sizeof(uint32_t) < cap_pairs) cap_pairs = ctx->vals[0].cap / sizeof(uint32_t);
         if (cap_pairs > 0x7fffffffull) cap_pairs = 0x7fffffffull;
     }
     auto small_order = [&](uint64_t limit, uint64_t* totals) {
@@ -634,11 +671,9 @@ static int order_pairs(fs_ctx* ctx, const fs_projected* proj, const fs_camera* c
     const bool spec_fits = spec_variants != 0 && P <= cap_pairs;
 
     const int64_t nb = radix_num_blocks((int64_t)P);
-    for (int k = 0; k < 2; k++) {
-        FS_TRY(ensure(ctx, ctx->keys[k], (size_t)(P ? P : 1) * sizeof(uint64_t), "keys"));
-        if (k == 0 || !lds_sort) FS_TRY(ensure(ctx, ctx->vals[k], (size_t)(P ? P : 1) * sizeof(uint32_t), "values"));
-    }
+    FS_TRY(room_for_pairs((size_t)(P ? P : 1)));
     if (!lds_sort) {
+        FS_TRY(ensure(ctx, ctx->vals[1], (size_t)(P ? P : 1) * sizeof(uint32_t), "values"));
         FS_TRY(ensure(ctx, ctx->hist, (size_t)(nb ? nb : 1) * RADIX_DIGITS * sizeof(uint32_t), "histograms"));
         FS_TRY(ensure(ctx, ctx->scan_tmp, scan_tmp_bytes(RADIX_DIGITS * nb), "scan"));
     }

@@ -13,10 +13,10 @@ int64_t stub_pairs = 0;             // pairs of every view
 int64_t stub_longest = 1;           // its longest list
 int stub_queue = 0;                 // words for the host arrive when the stream has been asked this often whether it is done (0: at once)
 int stub_never = 0;                 // ... or, of 1: the totals, 2: the loss, 3: an ordering in one launch, never: the stream is done without
-// ... and reads: flags found set when k_render_bwd is launched, waits for the whole stream
+// ... and reads: flags found set when k_render_bwd is launched, waits for the whole stream, allocations
 // and how many launches went by bands of tiles: counts, placements, splits; how many counts there were
 int64_t stub_stale_flags = -1;
-int stub_syncs = 0;
+int stub_syncs = 0, stub_mallocs = 0;
 int stub_bands[3] = {0, 0, 0};
 int stub_counts = 0;
 // and orderings in one launch: their first launches, their second ones
@@ -29,6 +29,7 @@ hipError_t hipGetLastError() { return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "stub"; }
 hipError_t hipMalloc(void** p, size_t bytes)
 {
+    stub_mallocs++;
     if (bytes == stub_fail_malloc_of) return hipErrorOutOfMemory;
     *p = malloc(bytes);
     memset(*p, 1, bytes);   // (fresh device memory holds anything)

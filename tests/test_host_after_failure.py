@@ -270,3 +270,32 @@ def test_a_record_of_blended_pairs_only_for_lists_sorted_per_tile(stub, longest,
             stub.fs_destroy(c.h)
     finally:
         ctypes.c_int64.in_dll(stub, "stub_longest").value = 1
+
+
+@pytest.mark.parametrize("n", FRAMES)
+def test_arrays_that_grow_together_take_one_allocation(stub, n):
+    """A new context's first ordering and backward pass: ranges, the scan's sums, what there is for each Gaussian, for each pair, the
+    records and their flags.  More pairs: the last three again; as many: none."""
+    mallocs = ctypes.c_int.in_dll(stub, "stub_mallocs")
+    c = Ctx(stub, pairs=100, n=n)
+    for pairs, allocations in ((100, 6), (100, 0), (400_000, 3), (100, 0), (400_000, 0)):
+        c.pairs(pairs)
+        before = mallocs.value
+        assert c.backward(c.B.FS_RECORDS_SPARSE) == 0
+        assert mallocs.value - before == allocations, pairs
+    stub.fs_destroy(c.h)
+
+
+def test_after_an_allocation_for_several_arrays_failed(stub):
+    """None of them is there then; the next call that needs no more than before allocates anew."""
+    c = Ctx(stub, pairs=100, n=20000)
+    fail = ctypes.c_size_t.in_dll(stub, "stub_fail_malloc_of")
+    assert c.backward(c.B.FS_RECORDS_SPARSE) == 0
+    c.pairs(400_000)
+    fail.value = 20 << 19
+    assert c.backward(c.B.FS_RECORDS_SPARSE) == -2   # FS_ENOMEM
+    fail.value = 0
+    assert b"pairs" in stub.fs_last_error(c.h)
+    c.pairs(100)
+    assert c.backward(c.B.FS_RECORDS_SPARSE) == 0
+    stub.fs_destroy(c.h)
