@@ -202,10 +202,11 @@ __global__ __launch_bounds__(256) void k_rect_area(int64_t n, const ushort4* __r
     area[i] = r.z > r.x && r.w > r.y ? (uint32_t)(r.z - r.x) * (uint32_t)(r.w - r.y) : 0u;
 }
 
-// Compact Box emission.  Same wave-cooperative walk as k_emit_pairs, but over the candidates (all tiles
+// Compact Box emission.  Same wave-cooperative walk as k_emit_pairs, but over the candidates (all tiles of
 // each box): the lane that takes a candidate runs the ellipse-tile test; a hit becomes a key at
-// offsets[owner] + (hits of the same Gaussian before it, in row-major order).  Hits of one Gaussian before a candidate = those of earlier rounds (kept by the owner
-// lane in `emitted`) + those on lower lanes of this round (one ballot, masked to the owner's lanes).
+// offsets[owner] + (hits of the same Gaussian before it, in row-major order).  Hits of one Gaussian before a
+// candidate = those of earlier rounds (kept by the owner lane in `emitted`) + those on lower lanes of this
+// round (one ballot, masked to the owner's lanes).
 __global__ __launch_bounds__(256) void k_emit_pairs_cb(int64_t n, const ushort4* __restrict__ rect,
                                                        const float* __restrict__ depth,
                                                        const float2* __restrict__ mean2d,
@@ -1297,7 +1298,7 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_frame(SmallFrame f, Cfg
     auto place = [&]() -> uint32_t {
         if (!f.totals) {
             const uint2 r = f.ranges[tile];
-            return len && r.y <= f.limit ? r.x : ~0u;
+            return r.y <= f.limit ? r.x : ~0u;
         }
         uint32_t first = 0;
         for (bool again = false;; again = true) {
@@ -1321,14 +1322,18 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_small_frame(SmallFrame f, Cfg
             if (t == 0) s_late = 0u;   // (all words are there by now: the next look finds them)
             __syncthreads();
         }
-        if (t == 0) f.ranges[tile] = len ? make_uint2(first, first + (uint32_t)len) : make_uint2(0u, 0u);
-        return len && first + (uint32_t)len <= f.limit ? first : ~0u;
+        if (t == 0) f.ranges[tile] = make_uint2(first, first + (uint32_t)len);
+        return first + (uint32_t)len <= f.limit ? first : ~0u;
     };
     auto word = [&](int i) {   // (any i: the first one stands in for those past the list's end)
         const uint32_t g = mem.list[i < len ? i : 0];
         return (uint64_t)__float_as_uint(f.depth[g]) << 32 | g;
     };
-    if (len == 0 || len > TILE_SORT_SMALL) {
+    if (len == 0) {   // (its range is the same wherever the other tiles' pairs lie: it waits for none)
+        if (t == 0 && f.totals) f.ranges[tile] = make_uint2(0u, 0u);
+        return;
+    }
+    if (len > TILE_SORT_SMALL) {
         const uint32_t to = place();
         if (to != ~0u)
             for (int i = t; i < len; i += T) f.bucket[to + i] = word(i);
