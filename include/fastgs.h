@@ -216,7 +216,9 @@ int fs_render_fwd(fs_ctx *ctx, const fs_projected *proj, const fs_bins *bins, co
  * Saves reading the finished image twice more.  Same outputs as the separate calls (the two fp64 sums are formed in
  * a different order).  target: [3,H,W].
  * Where dL_dimage is given, a backward pass follows: the call also notes which pairs it blended and in which 4x4 pixels (ctx scratch,
- * until the next fs_bin_sort), and fs_render_bwd over the same bins walks those pairs alone.  Same gradients. */
+ * until the next fs_bin_sort), and fs_render_bwd over the same bins walks those pairs alone.  Same gradients for final_T and
+ * n_contrib as a forward pass leaves them, and for an n_contrib that is cut short; a pair that this call did not blend receives
+ * nothing, also where n_contrib is made to reach further than the call left it. */
 int fs_render_fwd_loss(fs_ctx *ctx, const fs_projected *proj, const fs_bins *bins, const fs_camera *cam,
                        const float *target, float *image, float *final_T, uint32_t *n_contrib, float *dL_dimage,
                        double *loss_out);
@@ -243,7 +245,8 @@ int fs_l1_grad(fs_ctx *ctx, const float *image, const float *target, int32_t hei
                float *dL_dimage, double *loss_out);
 
 /* Steps a8+a9: back-to-front gradient of the compositing, reduced per Gaussian, then chained
- * through the projection to the scene parameters.  final_T / n_contrib are fs_render_fwd's; bins
+ * through the projection to the scene parameters.  final_T / n_contrib are those of the forward pass over
+ * these bins (n_contrib may be lower, not higher: see fs_render_fwd_loss); bins
  * must be the result of the latest fs_bin_sort on this ctx for the same proj: every (Gaussian, tile) pair
  * owns one record of partial sums in ctx scratch, at bins->record_offsets[i] + the tile's place in the
  * Gaussian's rectangle, which the tile's workgroup stores once (see fs_set_record_mode for when a pair that received

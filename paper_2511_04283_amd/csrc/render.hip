@@ -445,9 +445,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_vgpr(80))) void k_re
         // alone (4.5 to 6 cycles for every instruction, scalar ones included).  Four
         // entries' alphas are formed side by side from one word of slots -- four independent chains -- and only the
         // transmittance runs through them one after the other; conditions are lane masks in the scalar unit and blending
-        // happens under the mask instead of through selects: a trip of four entries has 126 vector and 41 scalar instructions, the
-        // loop's own included, 12 more with the record of counted pixels, 4 more with that of blended pairs.  Lanes past their list's
-        // end evaluate the empty record.  The four records are requested ahead of all arithmetic, in the order of their use: with both
+        // happens under the mask instead of through selects: a trip of four entries has 125 vector and 35 scalar instructions, the
+        // loop's own included, and six waits; 138 and 41 with the record of counted pixels, 130 and 37 with that of blended pairs, 143
+        // and 41 with both.  Lanes past their list's end evaluate the empty record.  The four records are requested ahead of all arithmetic, in the order of their use: with both
         // records the compiler by itself places each request before its use (100k Gaussians: 60 us instead of 49, 3 M: 292 and 271).
         // The record: each entry's 64 bits go into one lane of two registers, and 64 entries later to the slots' rows; stored
         // entry by entry they took a 64-bit shift, an address, an LDS store and a change of the lane mask each.  Both steps together,
