@@ -113,7 +113,8 @@ __device__ __forceinline__ bool cb_tile_hit(float mx, float my, float A, float B
 __device__ __forceinline__ float4 support_strips(const float4& co /* a, b, c, sigma */, const CfgDev& cfg)
 {
     const float ratio = co.w * __builtin_amdgcn_rcpf(cfg.alpha_min);
-    if (!(ratio >= 1.0f)) return make_float4(-1.f, 0.f, 0.f, 0.f);
+    // (a little below 1 for the reciprocal's rounding: an opacity of alpha_min itself is blended at the centre; the 0.1 in Q covers it)
+    if (!(ratio >= 0.9999f)) return make_float4(-1.f, 0.f, 0.f, 0.f);
     const float det = co.x * co.z - co.y * co.y;
     const float inv = __builtin_amdgcn_rcpf(det), ra = __builtin_amdgcn_rcpf(co.x);
     const float sxx = co.z * inv, syy = co.x * inv;

@@ -52,3 +52,25 @@ def test_no_sub_tile_is_missed(longest, origin):
     ctx.close()
     assert np.array_equal(got[2].view(np.uint32), nc)
     assert np.array_equal(got[1].view(np.uint32), T.view(np.uint32))
+
+
+def test_the_least_opacity_that_is_blended():
+    """A splat of opacity alpha_min whose centre is a pixel's is blended there: the bound's own rounding of their ratio does not decide."""
+    import torch
+    from paper_2511_04283_amd import binding as B
+    rng = np.random.default_rng(4)
+    cam = B.make_camera(scenes.Camera(96, 16, 50.0, 50.0, 48.0, 8.0))
+    for alpha_min in [1 / 255, *np.exp(rng.uniform(np.log(1e-4), np.log(0.5), 60))]:
+        cfg = B.default_config()
+        cfg.alpha_min = alpha_min
+        ctx = B.Context("cuda:0", cfg)
+        least = np.float32(cfg.alpha_min)
+        sigma = np.array([np.nextafter(least, np.float32(0)), least, np.nextafter(least, np.float32(1)), least * np.float32(1.01)], np.float32)
+        x0 = np.arange(4)
+        t = lambda a, dt=np.float32: torch.from_numpy(np.ascontiguousarray(a).astype(dt)).to(ctx.device)
+        proj = B.Projected(t(np.stack([16 * x0 + 5.5, np.full(4, 9.5)], 1)), t(np.ones(4)), t(np.stack([np.full(4, 0.7), 0 * x0, np.full(4, 0.7), sigma], 1)),
+                           t(np.ones((4, 3))), t(np.stack([x0, 0 * x0, x0 + 1, 0 * x0 + 1], 1).astype(np.uint16).view(np.int16), np.int16),
+                           t(np.ones(4), np.int32), t(np.zeros((4, 3)), np.uint8))
+        nc = ctx.fs_render_fwd(proj, ctx.fs_bin_sort(proj, cam), cam)[2].cpu().numpy()
+        ctx.close()
+        assert nc[9, 16 * x0 + 5].tolist() == [0, 1, 1, 1], alpha_min
